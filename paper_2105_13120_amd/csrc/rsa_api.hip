@@ -57,30 +57,6 @@ inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) &
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workspace layout of the staged mode (offsets in bytes, each block 256-aligned).
-struct StagedWs {
-  size_t strip32, strip32b, strip16, strip16b, acc_q, acc_k, acc_v, dvec, total;
-};
-StagedWs staged_layout(const Dims &d, int dtype, int pass) {
-  const size_t heads = (size_t)d.B * d.Z;
-  const size_t strip = heads * (size_t)d.c * (size_t)d.L;
-  const size_t es = dtype == RSA_BF16 ? 2 : 4;
-  StagedWs w{};
-  size_t off = 0;
-  w.strip32 = off; off += align256(strip * 4);                 // S (fp32)
-  w.strip16 = off; off += align256(strip * es);                // P (dtype)
-  w.acc_q = off; off += align256(heads * d.c * d.A * 4);       // Oacc or dQacc
-  if (pass == 1) {
-    w.strip32b = off; off += align256(strip * 4);              // dP (fp32)
-    w.strip16b = off; off += align256(strip * es);             // dS (dtype)
-    w.acc_k = off; off += align256(heads * d.L * d.A * 4);     // dKacc
-    w.acc_v = off; off += align256(heads * d.L * d.A * 4);     // dVacc
-    w.dvec = off; off += align256(heads * d.Lq * 4);           // D
-  }
-  w.total = off;
-  return w;
-}
-
 // Fused backward: the row terms -D and -LSE / scale (fp32 per row)
 size_t fused_bwd_base(const Dims &d) {
   const size_t rows = (size_t)d.B * d.Z * d.Lq;
@@ -98,7 +74,7 @@ size_t det_bwd_bytes(const Dims &d) {
 // Fused path: the partial results of a split key walk (forward: unnormalised O and the pair
 // (max, sum) per split and row; backward: partial dQ per split and row, after the base part).
 size_t workspace_bytes(const Dims &d, int dtype, int pass) {
-  if (d.mode == RSA_MODE_STAGED) return staged_layout(d, dtype, pass).total;
+  if (d.mode == RSA_MODE_STAGED) return rsa::strip_workspace_bytes(d, dtype, pass);
   const size_t rows = (size_t)d.B * d.Z * d.Lq;
   if (pass == 1) return det_bwd_bytes(d);
   bool big;
@@ -119,92 +95,9 @@ inline float *fused_nL(const Dims &d, void *ws) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? RSA_OK : RSA_ERR_HIP; }
 
-#define RSA_TRY(expr)                             \
-  do {                                            \
-    hipError_t e_ = (expr);                       \
-    if (e_ != hipSuccess) return RSA_ERR_HIP;     \
-  } while (0)
-
 int check_rank_chunk(const Dims &d, int n, int j) {
   if (n < d.rank_begin || n >= d.rank_end) return RSA_ERR_SHAPE;
   if (j < 0 || j >= d.N) return RSA_ERR_SHAPE;
-  return RSA_OK;
-}
-
-// The paper's two-pass forward for the simulated ranks, one after the other.
-int staged_forward(const Dims &d, int dtype, const void *Q, const void *K, const void *V, void *O,
-                   float *LSE, char *ws, hipStream_t st) {
-  const StagedWs w = staged_layout(d, dtype, 0);
-  float *S = reinterpret_cast<float *>(ws + w.strip32);
-  void *P = ws + w.strip16;
-  float *Oacc = reinterpret_cast<float *>(ws + w.acc_q);
-  const size_t es = dtype == RSA_BF16 ? 2 : 4;
-  for (int n = d.rank_begin; n < d.rank_end; ++n) {
-    for (int t = 0; t < d.N; ++t) {  // K ring pass, local chunk first
-      const int j = (n - t + d.N) % d.N;
-      RSA_TRY(rsa::staged_qk_step(d, dtype, n, j, Q, K, S, st));
-    }
-    RSA_TRY(rsa::staged_row_softmax(d, dtype, n, S, P, LSE, st));
-    int first = 1;
-    for (int t = 0; t < d.N; ++t) {  // V ring pass
-      const int j = (n - t + d.N) % d.N;
-      if (d.causal && j > n) continue;  // all-zero probabilities
-      RSA_TRY(rsa::staged_av_step(d, dtype, n, j, P, V, Oacc, !first, st));
-      first = 0;
-    }
-    char *On = static_cast<char *>(O) + (size_t)(n - d.rank_begin) * d.c * d.A * es;
-    RSA_TRY(rsa::store_rows(dtype, Oacc, On, (int64_t)d.B * d.Z, d.c, d.A, d.c * d.A, d.Lq * d.A, st));
-  }
-  return RSA_OK;
-}
-
-int staged_backward(const Dims &d, int dtype, const void *dO, const void *Q, const void *K,
-                    const void *V, const void *O, void *dQ, void *dK, void *dV, char *ws,
-                    hipStream_t st) {
-  const StagedWs w = staged_layout(d, dtype, 1);
-  float *S = reinterpret_cast<float *>(ws + w.strip32);
-  void *P = ws + w.strip16;
-  float *dP = reinterpret_cast<float *>(ws + w.strip32b);
-  void *dS = ws + w.strip16b;
-  float *dQacc = reinterpret_cast<float *>(ws + w.acc_q);
-  float *dKacc = reinterpret_cast<float *>(ws + w.acc_k);
-  float *dVacc = reinterpret_cast<float *>(ws + w.acc_v);
-  float *D = reinterpret_cast<float *>(ws + w.dvec);
-  const size_t es = dtype == RSA_BF16 ? 2 : 4;
-  const int64_t heads = (int64_t)d.B * d.Z;
-  // chunks that no simulated rank looks at keep a zero gradient
-  RSA_TRY(rsa::zero_f32(dKacc, heads * d.L * d.A, st));
-  RSA_TRY(rsa::zero_f32(dVacc, heads * d.L * d.A, st));
-  RSA_TRY(rsa::rowdot(d, dtype, 0, d.Lq, dO, O, D, st));
-  // the softmax statistics are recomputed; the LSE written here is scratch
-  float *lse_scratch = dQacc;  // (heads * c) floats fit in (heads * c * A)
-  for (int n = d.rank_begin; n < d.rank_end; ++n) {
-    Dims dn = d;  // a view in which rank n is the only rank, for the scratch LSE rows
-    for (int t = 0; t < d.N; ++t) {
-      const int j = (n - t + d.N) % d.N;
-      RSA_TRY(rsa::staged_qk_step(d, dtype, n, j, Q, K, S, st));
-    }
-    dn.rank_begin = n; dn.rank_end = n + 1; dn.Lq = d.c;
-    RSA_TRY(rsa::staged_row_softmax(dn, dtype, n, S, P, lse_scratch, st));
-    for (int t = 0; t < d.N; ++t) {  // V ring pass of the backward: dP
-      const int j = (n - t + d.N) % d.N;
-      RSA_TRY(rsa::staged_dp_step(d, dtype, n, j, dO, V, dP, st));
-    }
-    RSA_TRY(rsa::staged_softmax_bwd(d, dtype, n, P, dP, D, dS, st));
-    int first = 1;
-    for (int t = 0; t < d.N; ++t) {  // K ring pass of the backward: dQ; partial dK, dV
-      const int j = (n - t + d.N) % d.N;
-      if (d.causal && j > n) continue;
-      RSA_TRY(rsa::staged_dq_step(d, dtype, n, j, dS, K, dQacc, !first, st));
-      RSA_TRY(rsa::staged_dk_step(d, dtype, n, j, dS, Q, dKacc, 1, st));
-      RSA_TRY(rsa::staged_dv_step(d, dtype, n, j, P, dO, dVacc, 1, st));
-      first = 0;
-    }
-    char *dQn = static_cast<char *>(dQ) + (size_t)(n - d.rank_begin) * d.c * d.A * es;
-    RSA_TRY(rsa::store_rows(dtype, dQacc, dQn, heads, d.c, d.A, d.c * d.A, d.Lq * d.A, st));
-  }
-  RSA_TRY(rsa::store_rows(dtype, dKacc, dK, heads, d.L, d.A, d.L * d.A, d.L * d.A, st));
-  RSA_TRY(rsa::store_rows(dtype, dVacc, dV, heads, d.L, d.A, d.L * d.A, d.L * d.A, st));
   return RSA_OK;
 }
 
@@ -246,7 +139,7 @@ int rsa_forward(const rsa_desc *d, const void *Q, const void *K, const void *V, 
   if (need > 0 && (!ws || ws_bytes < need)) return RSA_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dm.mode == RSA_MODE_STAGED)
-    return staged_forward(dm, d->dtype, Q, K, V, O, LSE, static_cast<char *>(ws), st);
+    return hip_status(rsa::strip_forward(dm, d->dtype, Q, K, V, O, LSE, ws, st));
   return hip_status(rsa::fused_forward(dm, Q, K, V, O, LSE, st, static_cast<float *>(ws)));
 }
 
@@ -264,7 +157,7 @@ int rsa_backward(const rsa_desc *d, const void *dO, const void *Q, const void *K
   if (!ws || ws_bytes < need) return RSA_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dm.mode == RSA_MODE_STAGED)
-    return staged_backward(dm, d->dtype, dO, Q, K, V, O, dQ, dK, dV, static_cast<char *>(ws), st);
+    return hip_status(rsa::strip_backward(dm, d->dtype, dO, Q, K, V, O, LSE, dQ, dK, dV, ws, st));
   return hip_status(rsa::fused_backward(dm, dO, Q, K, V, O, LSE, dQ, dK, dV, fused_nD(ws),
                                         fused_nL(dm, ws), st, fused_part(dm, ws), 1,
                                         rsa::fused_key_splits(dm)));

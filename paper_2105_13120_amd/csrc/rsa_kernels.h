@@ -30,8 +30,12 @@ hipError_t store_rows(int dtype, const float *src, void *dst, int64_t batches,
                       int64_t rows_per_batch, int64_t cols, int64_t src_batch, int64_t dst_batch,
                       hipStream_t st);
 
-// p[0..n) = 0 (n a multiple of 4), by a kernel
-hipError_t zero_f32(float *p, int64_t n, hipStream_t st);
+// --- the two-pass layout as a whole (rsa_forward / rsa_backward in staged mode), bf16 and fp32 ---
+size_t strip_workspace_bytes(const Dims &d, int dtype, int pass);
+hipError_t strip_forward(const Dims &d, int dtype, const void *Q, const void *K, const void *V, void *O, float *LSE,
+                         void *ws, hipStream_t st);
+hipError_t strip_backward(const Dims &d, int dtype, const void *dO, const void *Q, const void *K, const void *V,
+                          const void *O, const float *LSE, void *dQ, void *dK, void *dV, void *ws, hipStream_t st);
 
 // --- fused (online-softmax) path, bf16, A = 64 or 128 ---
 // Split of the walk over the keys (few query rows, many keys).  fused_fwd_plan: the forward's

@@ -544,21 +544,6 @@ hipError_t rowdot(const Dims &d, int dtype, int64_t row_off, int64_t rows_per_he
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ fill ----
-// A kernel rather than a memset, so that a caller may capture the launch sequence in a graph.
-__global__ void __launch_bounds__(256) zero_kernel(f32x4 *p, int64_t n4) {
-  const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) p[i] = z;
-}
-
-hipError_t zero_f32(float *p, int64_t n, hipStream_t st) {  // n: a multiple of 4
-  const int64_t n4 = n / 4;
-  const int64_t blocks = (n4 + 255) / 256;
-  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st,
-                     reinterpret_cast<f32x4 *>(p), n4);
-  return hipGetLastError();
-}
-
 // ----------------------------------------------------------------- store ----
 template <typename T>
 __global__ void __launch_bounds__(256) store_kernel(const float *src, T *dst, int64_t rows,

@@ -151,3 +151,20 @@ def test_staged_explicit_softmax_scale(dtype):
     x = inputs.make_inputs(cfg)
     out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED)
     compare_heads(cfg, x, out, [0, 1], mode=rsa.MODE_STAGED)
+
+
+@pytest.mark.parametrize("dtype,kw,heads", [
+    ("f32", dict(B=1, Z=1, L=192, N=3), [0]),                          # one and a half row tiles, ragged key block
+    ("bf16", dict(B=1, Z=1, L=64, N=1), [0]),                          # a single tile
+    ("f32", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
+    ("bf16", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
+    ("bf16", dict(B=2, Z=15, L=2048, N=4), [0, 9, 10, 29]),            # heads in several groups
+    ("f32", dict(B=1, Z=1, L=8192, N=8, causal=True), [0]),            # rows in several groups: fp32 accumulators
+    ("bf16", dict(B=1, Z=1, L=12288, N=12, causal=True), [0]),
+])
+def test_staged_strip_groups_and_edges(dtype, kw, heads):
+    """How the strips are cut: tile edges, groups of heads, groups of rows with dK, dV summed across them."""
+    cfg = small_cfg(dtype, seed=83, **dict(dict(causal=False), **kw))
+    x = inputs.make_inputs(cfg)
+    out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED)
+    compare_heads(cfg, x, out, heads, mode=rsa.MODE_STAGED)
