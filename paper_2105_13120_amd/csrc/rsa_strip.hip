@@ -13,8 +13,10 @@
 //
 // Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
-// passes of their own and ran every product chunk by chunk: 12 (bf16) / 20 (fp32) bytes forward,
-// 28 / 44 backward, and 10 N^2 launches.
+// passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
+// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.68,
+// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; now 0.475, 80 to 95 TFLOP/s in
+// every kernel, of which the strips' traffic hides about half).
 //
 // The tile kernels hold bf16 tiles in the layout of the fused kernels and fp32 tiles in one of their
 // own; fp32 products run on v_mfma_f32_32x32x2_f32 (IEEE fp32 multiply-add, twice the rate of the
@@ -27,20 +29,16 @@ namespace {
 
 // A 64 x 64 tile of T in LDS: how it is filled, read as MFMA operands and written as a result.
 //   rows(t, rb, s):   operand whose row index runs over tile rows rb .. rb + 31, k over columns
-//   rows_k(t, rb, s): the same with k in the order in which cols() delivers it
 //   cols(t, s, cb):   operand whose row index runs over columns 32 cb .. 32 cb + 31, k over rows
 // s: k slice of kSliceK; mfma() contracts one slice.
 template <typename T> struct TileT;
 
 template <> struct TileT<uint16_t> {
   typedef bf16x8 Frag;
-  static constexpr int kBytes = kTileBytes, kSlices = 4, kSliceK = 16;
+  static constexpr int kBytes = kTileBytes, kSlices = 4, kSliceK = 16, kStores = 4;
   TileLanes tl;
   __device__ __forceinline__ explicit TileT(int lane) : tl(lane) {}
   __device__ __forceinline__ Frag rows(const unsigned char *t, int rb, int s) const { return tl.read_rows(t, rb, s); }
-  __device__ __forceinline__ Frag rows_k(const unsigned char *t, int rb, int s) const {
-    return tl.read_rows_perm(t, rb, s);
-  }
   __device__ __forceinline__ Frag cols(const unsigned char *t, int s, int cb) const {
     const int flip = cb << 6;  // the second column block: the other four of a row's eight chunks
     const u32x2 lo = lds_read_tr16(t + s * 2048 + (tl.cols_off[0][0] ^ flip));
@@ -66,11 +64,23 @@ template <> struct TileT<uint16_t> {
                                                int64_t ld) {
     flush_rows<32>(t, 0, g, rows_valid, lane, (int)ld);
   }
-  struct DMA {
-    TileDMA d;
+  // slice i of a transposed 32-row block (c0: its columns 0 .. 31, c1: 32 .. 63) as an operand
+  static __device__ __forceinline__ Frag slice(const f32x16 &c0, const f32x16 &c1, int i) {
+    const f32x16 &c = i < 2 ? c0 : c1;
+    const int v = (i & 1) * 8;
+    const u32x4 w = {pack_bf16(c[v + 0], c[v + 1]), pack_bf16(c[v + 2], c[v + 3]), pack_bf16(c[v + 4], c[v + 5]),
+                     pack_bf16(c[v + 6], c[v + 7])};
+    return __builtin_bit_cast(Frag, w);
+  }
+  // column (of 32) of a tile that holds strip fragments -> key: a fragment's eight elements are keys
+  // 4 half .. + 3 and 8 + 4 half .. + 3 of its slice
+  static __device__ __forceinline__ int key_of_col(int c) { return (c & 16) | ((c & 4) << 1) | ((c >> 1) & 4) | (c & 3); }
+  template <int ROWS = 64> struct DMA {  // ROWS = 32: the upper half of a tile
+    TileDMAT<256 / ROWS> d;
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) : d(wave, lane, (int)ld) {}
     __device__ __forceinline__ void load(const uint16_t *g, unsigned char *t) const { d.load(g, t); }
   };
+  static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 3; return (p & 7) ^ swz_rot(row); }
 };
 
 // fp32: row r occupies bytes [256 r, 256 r + 256), its 16-byte chunk cc sits at position cc ^ rot(r).
@@ -79,7 +89,7 @@ template <> struct TileT<uint16_t> {
 // chunks each) touch disjoint halves of the row: both are free of bank conflicts.
 template <> struct TileT<float> {
   typedef f32x4 Frag;
-  static constexpr int kBytes = 64 * 64 * 4, kSlices = 8, kSliceK = 8;
+  static constexpr int kBytes = 64 * 64 * 4, kSlices = 8, kSliceK = 8, kStores = 8;
   int row0, col0;  // byte offsets of chunk `half` of row `col`, of element `col` of row 4 half
   static __device__ __forceinline__ int rot(int r) { return (r & 3) | ((r >> 1) & 4) | ((r & 4) << 1); }
   static __device__ __forceinline__ int off(int r, int cc) { return r * 256 + ((cc ^ rot(r)) << 4); }
@@ -92,7 +102,6 @@ template <> struct TileT<float> {
   __device__ __forceinline__ Frag rows(const unsigned char *t, int rb, int s) const {
     return *reinterpret_cast<const f32x4 *>(t + rb * 256 + (row0 ^ (s << 5)));
   }
-  __device__ __forceinline__ Frag rows_k(const unsigned char *t, int rb, int s) const { return rows(t, rb, s); }
   __device__ __forceinline__ Frag cols(const unsigned char *t, int s, int cb) const {
     f32x4 r;
 #pragma unroll
@@ -132,31 +141,73 @@ template <> struct TileT<float> {
         *reinterpret_cast<f32x4 *>(g + row * ld + cc * 4) = *reinterpret_cast<const f32x4 *>(t + off(row, cc));
     }
   }
-  struct DMA {
-    int g_off[4], l_off[4];
+  static __device__ __forceinline__ Frag slice(const f32x16 &c0, const f32x16 &c1, int i) {
+    const f32x16 &c = i < 4 ? c0 : c1;
+    const int v = (i & 3) * 4;
+    return f32x4{c[v], c[v + 1], c[v + 2], c[v + 3]};
+  }
+  static __device__ __forceinline__ int key_of_col(int c) { return c; }
+  static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 4; return (p & 15) ^ rot(row); }
+  template <int ROWS = 64> struct DMA {
+    static constexpr int PER = ROWS / 16;
+    int g_off[PER], l_off[PER];
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = (wave * 4 + j) * 64 + lane, row = p >> 4, cc = (p & 15) ^ rot(row);
+      for (int j = 0; j < PER; ++j) {
+        const int p = (wave * PER + j) * 64 + lane, row = p >> 4, cc = (p & 15) ^ rot(row);
         g_off[j] = row * (int)ld + cc * 4;
-        l_off[j] = (wave * 4 + j) * 1024;
+        l_off[j] = (wave * PER + j) * 1024;
       }
     }
     __device__ __forceinline__ void load(const float *g, unsigned char *t) const {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) lds_dma16(g + g_off[j], t + l_off[j]);
+      for (int j = 0; j < PER; ++j) lds_dma16(g + g_off[j], t + l_off[j]);
     }
   };
+};
+
+// How a strip lies in memory: 64 x 64 tiles, a head's tiles row tile by row tile; inside a tile its two blocks of
+// 32 rows, and of a block the operand fragments in which the scores kernels hold it and the apply
+// kernel wants it: [slice][lane][16 bytes].  A wave writes and reads a block as contiguous KiBs.
+template <typename T> __device__ __forceinline__ int64_t strip_tile(int64_t head, int64_t rtiles64, int64_t rt, int64_t ktiles, int64_t kt) {
+  return ((head * rtiles64 + rt) * ktiles + kt) * 4096;
+}
+// A wave's block of 32 rows, held transposed in c0, c1, into its place in the strip.
+template <typename T>
+__device__ __forceinline__ void strip_store(T *block, const f32x16 &c0, const f32x16 &c1, int lane) {
+  typedef TileT<T> TT;
+#pragma unroll
+  for (int i = 0; i < TT::kSlices; ++i)
+    *reinterpret_cast<typename TT::Frag *>(block + (i * 64 + lane) * (16 / (int)sizeof(T))) = TT::slice(c0, c1, i);
+}
+// Direct load of a strip tile (ROWS = 32: of one of its blocks) into LDS as rows of 16-byte chunks (chunk 2 i + h of row r: the fragment of
+// slice i that lane (r, h) holds), swizzled like every tile of its type.
+template <typename T, int ROWS> struct StripDMA {
+  static constexpr int PER = TileT<T>::kBytes * ROWS / (64 * 4096);
+  int g_off[PER], l_off[PER];
+  __device__ __forceinline__ StripDMA(int wave, int lane) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      int row;
+      const int cc = TileT<T>::chunk_at((wave * PER + j) * 64 + lane, row);
+      g_off[j] = (row >> 5) * 2048 + ((cc >> 1) * 64 + (row & 31) + (cc & 1) * 32) * (16 / (int)sizeof(T));
+      l_off[j] = (wave * PER + j) * 1024;
+    }
+  }
+  __device__ __forceinline__ void load(const T *tile, unsigned char *t) const {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) lds_dma16(tile + g_off[j], t + l_off[j]);
+  }
 };
 
 struct StripArgs {
   const void *Q, *K, *V, *dO, *O;  // first head of the group; Q, dO, O: first row of the group
   const float *LSE_in;
   float *LSE;                      // (head, Lq), first row of the group
-  void *strip, *strip2;            // (head, rows, L): exp(S - m_t) or P; dS
+  void *strip, *strip2;            // (head, rows, L) in tiles: exp(S - m_t) or P; dS
   float *stats;                    // (head, L / 64, rows, 2): m_t and l_t, base-2 logarithm domain
   int64_t L, Lq, rows, q0;         // rows of the group; token of its first row
-  int A, causal, rtiles, kblocks;  // 128-row tiles; key blocks
+  int A, causal, rtiles, kblocks, per;  // 128-row tiles; key blocks of `per` tiles
   float cl2, scale, inv_scale;
 };
 
@@ -166,38 +217,95 @@ __device__ __forceinline__ bool tile_seen(const StripArgs &a, int64_t row, int64
   return !a.causal || k0 <= a.q0 + (row | 63);
 }
 
+// n slices of a contraction: the operands of slice i + 1 are read from LDS while slice i is on the matrix pipe
+// (left to itself the compiler reads most of them right before their use).
+template <int N, typename Read, typename Use>
+__device__ __forceinline__ void pipelined(Read read, Use use) {
+  read(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + 1 < N) {
+      read(i + 1, (i + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    use(i, i & 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // ---------------------------------------------------------------- scores ----
-// Work-group: 128 rows (wave: 32, their Q as B operands in registers) x NKT tiles of 64 keys, whose K
-// tiles are in LDS.  Nothing is pipelined inside a work-group: it is short (bound by the strip's stores
-// in bf16, by the matrix pipe in fp32), and two to four of them share a compute unit.
-template <typename T, int AH, int NKT>
+// Work-group: 128 rows (wave: 32, their Q, and dO, as B operands in registers) walking `per` tiles of 64
+// keys.  One LDS buffer: the next tile is requested as soon as every wave has the products of this one, so
+// that its latency lies under this tile's exponentials and stores; two to four work-groups share a compute
+// unit.  (With one tile pair per work-group, loads, products and stores of the work-groups of a unit ran in
+// step, one after the other: the matrix pipe was busy 46 % in fp32.)
+template <typename T, int AH, int NT>  // NT: tiles per key block (K, or K and V)
+struct ScoreLds {
+  unsigned char t[NT][AH][TileT<T>::kBytes];
+};
+
+// Waits for the direct loads in flight when at most `stores` newer stores were issued behind them.
+template <int STORES> __device__ __forceinline__ void wait_loads_before_stores() {
+  static_assert(STORES < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (STORES & 15) | ((STORES >> 4) << 14));
+}
+
+// Position of a work-group in the grid of a scores kernel.
+struct ScorePos {
+  int64_t head, row0;
+  int t0, t1;  // key tiles
+  __device__ __forceinline__ explicit ScorePos(const StripArgs &a) {
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t hr = wg / (uint32_t)a.kblocks;
+    head = hr / (uint32_t)a.rtiles;
+    row0 = (int64_t)(hr % (uint32_t)a.rtiles) * 128;
+    t0 = (int)(wg % (uint32_t)a.kblocks) * a.per;
+    int n = (int)(a.L / 64);
+    if (a.causal) {
+      const int64_t row_last = (row0 + 128 < a.rows ? row0 + 128 : a.rows) - 1;
+      const int64_t seen = (a.q0 + row_last) / 64 + 1;
+      if (seen < n) n = (int)seen;
+    }
+    t1 = t0 + a.per < n ? t0 + a.per : n;
+  }
+};
+
+// Scores of keys that the lane's row does not see: -inf.
+__device__ __forceinline__ void mask_scores(const StripArgs &a, int64_t wrow, int64_t k0, int lane, f32x16 (&s)[2]) {
+  if (!a.causal || k0 + 63 <= a.q0 + wrow) return;
+  const int64_t d64 = a.q0 + wrow + (lane & 31) - k0 - (lane >> 5) * 4;  // last visible key, relative to the tile
+  const int dlast = d64 > 64 ? 64 : (int)d64;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (kb * 32 + (v >> 2) * 8 + (v & 3) > dlast) s[kb][v] = -INFINITY;
+}
+
+template <typename T, int AH>
 __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(StripArgs a) {
   typedef TileT<T> TT;
   constexpr int NS = TT::kSlices;
-  __shared__ __attribute__((aligned(16))) unsigned char Kt[NKT][AH][TT::kBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char stg[4][TT::kBytes / 2];
+  __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, 1> lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * (64 * NKT);
-  const uint32_t hr = wg / (uint32_t)a.kblocks;
-  const int64_t head = hr / (uint32_t)a.rtiles, row0 = (int64_t)(hr % (uint32_t)a.rtiles) * 128;
-  const int64_t row_last = (row0 + 128 < a.rows ? row0 + 128 : a.rows) - 1;
-  if (!tile_seen(a, row_last, key0)) return;
+  const ScorePos pos(a);
+  if (pos.t0 >= pos.t1) return;
 
-  const T *Kh = static_cast<const T *>(a.K) + head * a.L * a.A;
-  const typename TT::DMA dma(wave, lane, a.A);
+  const T *Kh = static_cast<const T *>(a.K) + pos.head * a.L * a.A;
+  const typename TT::template DMA<> dma(wave, lane, a.A);
+  auto load = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < NKT; ++u)
-    if (key0 + u * 64 < a.L)
-#pragma unroll
-      for (int ah = 0; ah < AH; ++ah) dma.load(Kh + (key0 + u * 64) * a.A + ah * 64, Kt[u][ah]);
-  const int64_t wrow = row0 + wave * 32;  // (rows come in multiples of 64: a wave's rows are there or not)
+    for (int ah = 0; ah < AH; ++ah) dma.load(Kh + (int64_t)t * 64 * a.A + ah * 64, lds.t[0][ah]);
+  };
+  load(pos.t0);
+  const int64_t wrow = pos.row0 + wave * 32;  // (rows come in multiples of 64: a wave's rows are there or not)
   const bool rows_here = wrow < a.rows;
   typename TT::Frag q[AH * NS];
   if (rows_here) {
-    const T *qp = static_cast<const T *>(a.Q) + (head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
+    const T *qp = static_cast<const T *>(a.Q) + (pos.head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
 #pragma unroll
     for (int i = 0; i < AH * NS; ++i)
       q[i] = *reinterpret_cast<const typename TT::Frag *>(qp + i * TT::kSliceK);
@@ -205,85 +313,90 @@ __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(
   const TT tt(lane);
   wait_vmem();
   __syncthreads();
-  if (!rows_here) return;
-#pragma unroll
-  for (int u = 0; u < NKT; ++u) {
-    const int64_t k0 = key0 + u * 64;
-    if (k0 >= a.L || !tile_seen(a, wrow, k0)) break;
+  for (int t = pos.t0; t < pos.t1; ++t) {
+    const int64_t k0 = (int64_t)t * 64;
+    const bool work = rows_here && tile_seen(a, wrow, k0);
     f32x16 s[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
-#pragma unroll
-      for (int i = 0; i < AH * NS; ++i) s[kb] = TT::mfma(tt.rows(Kt[u][i / NS], kb * 32, i % NS), q[i], s[kb]);
-    }
-    if (a.causal && k0 + 63 > a.q0 + wrow) {  // last visible key of the lane's row, relative to the tile
-      const int64_t d64 = a.q0 + wrow + col - k0 - half * 4;
-      const int dlast = d64 > 64 ? 64 : (int)d64;
+    if (work) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (kb * 32 + (v >> 2) * 8 + (v & 3) > dlast) s[kb][v] = -INFINITY;
+        for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
+      typename TT::Frag kf[2][2];
+      pipelined<AH * NS>(
+          [&](int i, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) kf[b][kb] = tt.rows(lds.t[0][i / NS], kb * 32, i % NS);
+          },
+          [&](int i, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) s[kb] = TT::mfma(kf[b][kb], q[i], s[kb]);
+          });
     }
-    float m = s[0][0];
+    __syncthreads();
+    if (t + 1 < pos.t1) load(t + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (work) {
+      mask_scores(a, wrow, k0, lane, s);
+      float m = s[0][0];
 #pragma unroll
-    for (int v = 1; v < 16; ++v) m = fmaxf(m, s[0][v]);
+      for (int v = 1; v < 16; ++v) m = fmaxf(m, s[0][v]);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) m = fmaxf(m, s[1][v]);
-    m = xhalf_max(m);
-    const float mc = m > -INFINITY ? m * a.cl2 : 0.f;  // a row that sees none of these keys: all zeros
-    float l = 0.f;
+      for (int v = 0; v < 16; ++v) m = fmaxf(m, s[1][v]);
+      m = xhalf_max(m);
+      const float mc = m > -INFINITY ? m * a.cl2 : 0.f;  // a row that sees none of these keys: all zeros
+      float l = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        s[kb][v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], a.cl2, -mc));
-        l += s[kb][v];
+        for (int v = 0; v < 16; ++v) {
+          s[kb][v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], a.cl2, -mc));
+          l += s[kb][v];
+        }
+      l = xhalf_sum(l);
+      if (half == 0) {
+        f32x2 p = {m > -INFINITY ? mc : -INFINITY, l};
+        *reinterpret_cast<f32x2 *>(a.stats + ((pos.head * (a.L / 64) + t) * a.rows + wrow + col) * 2) = p;
       }
-    l = xhalf_sum(l);
-    if (half == 0) {
-      f32x2 p = {m > -INFINITY ? mc : -INFINITY, l};
-      *reinterpret_cast<f32x2 *>(a.stats + ((head * (a.L / 64) + k0 / 64) * a.rows + wrow + col) * 2) = p;
+      strip_store(static_cast<T *>(a.strip) + strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) +
+                      (wave & 1) * 2048, s[0], s[1], lane);
     }
-    TT::stage(stg[wave], s[0], s[1], 1.0f, lane);
-    TT::flush(stg[wave], static_cast<T *>(a.strip) + (head * a.rows + wrow) * a.L + k0, 32, lane, a.L);
+    if (t + 1 < pos.t1) {
+      if (work) wait_loads_before_stores<TT::kStores>();
+      else wait_vmem();
+      __syncthreads();
+    }
   }
 }
 
-template <typename T, int AH, int NKT>
+template <typename T, int AH>
 __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores_bwd_kernel(StripArgs a) {
   typedef TileT<T> TT;
   constexpr int NS = TT::kSlices;
-  __shared__ __attribute__((aligned(16))) unsigned char Kt[NKT][AH][TT::kBytes], Vt[NKT][AH][TT::kBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char stg[4][TT::kBytes / 2];
+  __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, 2> lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * (64 * NKT);
-  const uint32_t hr = wg / (uint32_t)a.kblocks;
-  const int64_t head = hr / (uint32_t)a.rtiles, row0 = (int64_t)(hr % (uint32_t)a.rtiles) * 128;
-  const int64_t row_last = (row0 + 128 < a.rows ? row0 + 128 : a.rows) - 1;
-  if (!tile_seen(a, row_last, key0)) return;
+  const ScorePos pos(a);
+  if (pos.t0 >= pos.t1) return;
 
-  const T *Kh = static_cast<const T *>(a.K) + head * a.L * a.A, *Vh = static_cast<const T *>(a.V) + head * a.L * a.A;
-  const typename TT::DMA dma(wave, lane, a.A);
+  const T *Kh = static_cast<const T *>(a.K) + pos.head * a.L * a.A;
+  const T *Vh = static_cast<const T *>(a.V) + pos.head * a.L * a.A;
+  const typename TT::template DMA<> dma(wave, lane, a.A);
+  auto load = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < NKT; ++u)
-    if (key0 + u * 64 < a.L)
-#pragma unroll
-      for (int ah = 0; ah < AH; ++ah) {
-        dma.load(Kh + (key0 + u * 64) * a.A + ah * 64, Kt[u][ah]);
-        dma.load(Vh + (key0 + u * 64) * a.A + ah * 64, Vt[u][ah]);
-      }
-  const int64_t wrow = row0 + wave * 32;
+    for (int ah = 0; ah < AH; ++ah) {
+      dma.load(Kh + (int64_t)t * 64 * a.A + ah * 64, lds.t[0][ah]);
+      dma.load(Vh + (int64_t)t * 64 * a.A + ah * 64, lds.t[1][ah]);
+    }
+  };
+  load(pos.t0);
+  const int64_t wrow = pos.row0 + wave * 32;
   const bool rows_here = wrow < a.rows;
   typename TT::Frag q[AH * NS], g[AH * NS];
   float nl = 0.f, nd = 0.f;  // -LSE / scale and -D of the lane's row: what the accumulators start from
   if (rows_here) {
-    const int64_t off = (head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
+    const int64_t off = (pos.head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
     const T *qp = static_cast<const T *>(a.Q) + off, *gp = static_cast<const T *>(a.dO) + off;
     const T *op = static_cast<const T *>(a.O) + off;
     float acc = 0.f;
@@ -294,55 +407,65 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
       acc = TT::dot(g[i], *reinterpret_cast<const typename TT::Frag *>(op + i * TT::kSliceK), acc);
     }
     nd = -xhalf_sum(acc);
-    nl = -a.LSE_in[head * a.Lq + wrow + col] * a.inv_scale;
+    nl = -a.LSE_in[pos.head * a.Lq + wrow + col] * a.inv_scale;
   }
   const TT tt(lane);
   wait_vmem();
   __syncthreads();
-  if (!rows_here) return;
-#pragma unroll
-  for (int u = 0; u < NKT; ++u) {
-    const int64_t k0 = key0 + u * 64;
-    if (k0 >= a.L || !tile_seen(a, wrow, k0)) break;
+  for (int t = pos.t0; t < pos.t1; ++t) {
+    const int64_t k0 = (int64_t)t * 64;
+    const bool work = rows_here && tile_seen(a, wrow, k0);
     f32x16 s[2], dp[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { s[kb][v] = nl; dp[kb][v] = nd; }
-#pragma unroll
-      for (int i = 0; i < AH * NS; ++i) {
-        s[kb] = TT::mfma(tt.rows(Kt[u][i / NS], kb * 32, i % NS), q[i], s[kb]);
-        dp[kb] = TT::mfma(tt.rows(Vt[u][i / NS], kb * 32, i % NS), g[i], dp[kb]);
-      }
-    }
-    if (a.causal && k0 + 63 > a.q0 + wrow) {
-      const int64_t d64 = a.q0 + wrow + col - k0 - half * 4;
-      const int dlast = d64 > 64 ? 64 : (int)d64;
+    if (work) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (kb * 32 + (v >> 2) * 8 + (v & 3) > dlast) s[kb][v] = -INFINITY;
+        for (int v = 0; v < 16; ++v) { s[kb][v] = nl; dp[kb][v] = nd; }
+      typename TT::Frag kf[2][2], vf[2][2];
+      pipelined<AH * NS>(
+          [&](int i, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+              kf[b][kb] = tt.rows(lds.t[0][i / NS], kb * 32, i % NS);
+              vf[b][kb] = tt.rows(lds.t[1][i / NS], kb * 32, i % NS);
+            }
+          },
+          [&](int i, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+              s[kb] = TT::mfma(kf[b][kb], q[i], s[kb]);
+              dp[kb] = TT::mfma(vf[b][kb], g[i], dp[kb]);
+            }
+          });
     }
+    __syncthreads();
+    if (t + 1 < pos.t1) load(t + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (work) {
+      mask_scores(a, wrow, k0, lane, s);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        s[kb][v] = __builtin_amdgcn_exp2f(s[kb][v] * a.cl2);
-        dp[kb][v] *= s[kb][v];
-      }
-    const int64_t o = (head * a.rows + wrow) * a.L + k0;
-    TT::stage(stg[wave], s[0], s[1], 1.0f, lane);  // (LDS operations of a wave complete in order)
-    TT::flush(stg[wave], static_cast<T *>(a.strip) + o, 32, lane, a.L);
-    TT::stage(stg[wave], dp[0], dp[1], 1.0f, lane);
-    TT::flush(stg[wave], static_cast<T *>(a.strip2) + o, 32, lane, a.L);
+        for (int v = 0; v < 16; ++v) {
+          s[kb][v] = __builtin_amdgcn_exp2f(s[kb][v] * a.cl2);
+          dp[kb][v] *= s[kb][v];
+        }
+      const int64_t o = strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) + (wave & 1) * 2048;
+      strip_store(static_cast<T *>(a.strip) + o, s[0], s[1], lane);
+      strip_store(static_cast<T *>(a.strip2) + o, dp[0], dp[1], lane);
+    }
+    if (t + 1 < pos.t1) {
+      if (work) wait_loads_before_stores<2 * TT::kStores>();
+      else wait_vmem();
+      __syncthreads();
+    }
   }
 }
 
 // ----------------------------------------------------------------- apply ----
 // out (row, A) = scale * sum over keys of strip(row, key) X(key, A).  Work-group: 128 rows (wave: 32) x
-// 64 AHW columns, walking the key tiles; strip and X tiles reach LDS by direct loads, double-buffered,
-// one barrier per tile.  WEIGHT (forward): the strip is exp(S - m_t); the weights exp(m_t - LSE) bring
+// 64 AHW columns, walking the key tiles; X tiles reach LDS by direct loads, the wave's strip fragments
+// its registers, a tile ahead of their use; one barrier per tile.  WEIGHT (forward): the strip is exp(S - m_t); the weights exp(m_t - LSE) bring
 // the tiles to one reference, and LSE is written here.
 struct ApplyArgs {
   const void *strip, *X;
@@ -352,10 +475,10 @@ struct ApplyArgs {
 };
 
 template <typename T, int AHW, bool WEIGHT>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) strip_apply_kernel(StripArgs a, ApplyArgs p) {
+__global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(StripArgs a, ApplyArgs p) {
   typedef TileT<T> TT;
   constexpr int NS = TT::kSlices;
-  struct Stage { unsigned char S[2][TT::kBytes], X[AHW][TT::kBytes]; };
+  struct Stage { unsigned char X[AHW][TT::kBytes]; };
   __shared__ __attribute__((aligned(16))) Stage st0, st1;  // separate objects: see the fused kernels
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -372,33 +495,50 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
   int nt = ntiles;
   if (a.causal && (a.q0 + row_last) / 64 + 1 < nt) nt = (int)((a.q0 + row_last) / 64) + 1;
 
-  const T *Sh = static_cast<const T *>(p.strip) + (head * a.rows + row0) * a.L;
-  const int64_t second = row0 + 64 < a.rows ? 64 * a.L : 0;  // (no second half: refetch the first)
-  const T *Xh = static_cast<const T *>(p.X) + head * a.L * a.A + a0;
-  const typename TT::DMA dma_s(wave, lane, a.L), dma_x(wave, lane, a.A);
-  auto load = [&](int t, Stage &st) __attribute__((always_inline)) {
-    dma_s.load(Sh + t * 64, st.S[0]);
-    dma_s.load(Sh + second + t * 64, st.S[1]);
-#pragma unroll
-    for (int ah = 0; ah < AHW; ++ah) dma_x.load(Xh + (int64_t)t * 64 * a.A + ah * 64, st.X[ah]);
-  };
-  load(0, st0);
-
   const int64_t wrow = row0 + wave * 32;
   const bool rows_here = wrow < a.rows;
-  const float *stats = WEIGHT ? p.stats + ((head * ntiles) * a.rows + (rows_here ? wrow : row0) + col) * 2 : nullptr;
+  const int64_t rrow = rows_here ? wrow : row0;  // (a wave without rows reads the first wave's)
+  const T *S = static_cast<const T *>(p.strip) + strip_tile<T>(head, a.rows / 64, rrow / 64, ntiles, 0) +
+               (wave & 1) * 2048 + lane * (16 / (int)sizeof(T));
+  const T *Xh = static_cast<const T *>(p.X) + head * a.L * a.A + a0;
+  const typename TT::template DMA<> dma_x(wave, lane, a.A);
+  typename TT::Frag s0[NS], s1[NS];
+  const float *stats = WEIGHT ? p.stats + ((head * ntiles) * a.rows + rrow + col) * 2 : nullptr;
+  float m0 = 0.f, m1 = 0.f;  // m_t of the lane's row
+  auto load = [&](int t, Stage &st, typename TT::Frag(&s)[NS], float &m) __attribute__((always_inline)) {
+    if (WEIGHT) m = stats[(int64_t)t * a.rows * 2];
+#pragma unroll
+    for (int ah = 0; ah < AHW; ++ah) dma_x.load(Xh + (int64_t)t * 64 * a.A + ah * 64, st.X[ah]);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      s[i] = *reinterpret_cast<const typename TT::Frag *>(S + (int64_t)t * 4096 + i * (1024 / (int)sizeof(T)));
+  };
+  load(0, st0, s0, m0);
+
   float lse2 = 0.f;
   if (WEIGHT) {
-    // LSE = log sum_t l_t exp(m_t): the two lane halves take every other tile of their row
-    const int seen = a.causal ? (int)((a.q0 + ((rows_here ? wrow : row0) | 63)) / 64) + 1 : ntiles;
+    // LSE = log sum_t l_t exp(m_t): the two lane halves take every other tile of their row,
+    // eight pairs at a time, their loads in flight together
+    const int seen = a.causal ? (int)((a.q0 + (rrow | 63)) / 64) + 1 : ntiles;
     const int n = seen < ntiles ? seen : ntiles;
     float M = -INFINITY, l = 0.f;
-    for (int t = half; t < n; t += 2) {
-      const f32x2 ml = *reinterpret_cast<const f32x2 *>(stats + (int64_t)t * a.rows * 2);
-      const float mn = fmaxf(M, ml[0]);
-      if (mn > -INFINITY)
-        l = l * __builtin_amdgcn_exp2f(M - mn) + ml[1] * __builtin_amdgcn_exp2f(ml[0] - mn);
-      M = mn;
+    for (int t0 = half; t0 < n; t0 += 16) {
+      f32x2 ml[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int t = t0 + 2 * j < n ? t0 + 2 * j : t0;
+        ml[j] = *reinterpret_cast<const f32x2 *>(stats + (int64_t)t * a.rows * 2);
+      }
+      float mn = M;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) mn = fmaxf(mn, ml[j][0]);
+      if (mn > -INFINITY) {
+        l *= __builtin_amdgcn_exp2f(M - mn);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (t0 + 2 * j < n) l = fmaf(ml[j][1], __builtin_amdgcn_exp2f(ml[j][0] - mn), l);
+        M = mn;
+      }
     }
     const float MM = xhalf_max(M);  // finite: every row sees some key
     l = xhalf_sum(M > -INFINITY ? l * __builtin_amdgcn_exp2f(M - MM) : 0.f);
@@ -414,38 +554,44 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
 
   int t = 0;
   wait_vmem();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(s0[i]));  // (keeps the first loads in front of this wait)
+  asm volatile("" : "+v"(m0));
   __syncthreads();
-  auto step = [&](Stage &cur, Stage &nxt) __attribute__((always_inline)) {
-    float w = 0.f;
-    if (WEIGHT) w = __builtin_amdgcn_exp2f(stats[(int64_t)t * a.rows * 2] - lse2);
-    if (t + 1 < nt) load(t + 1, nxt);
+  auto step = [&](Stage &cur, typename TT::Frag(&sc)[NS], float mc, Stage &nxt, typename TT::Frag(&sn)[NS], float &mn)
+      __attribute__((always_inline)) {
+    if (t + 1 < nt) load(t + 1, nxt, sn, mn);
+    const float w = WEIGHT ? __builtin_amdgcn_exp2f(mc - lse2) : 0.f;
     if (rows_here && tile_seen(a, wrow, (int64_t)t * 64)) {
-      const unsigned char *S = cur.S[wave >> 1];
-      if constexpr (WEIGHT && sizeof(T) == 2) {
-        // the weight cannot enter the bf16 operand without rounding it again: it goes to the tile's sum
-        f32x16 c[2 * AHW];
+      // with bf16 the weight cannot enter the operand without rounding it again: it goes to the tile's sum
+      constexpr bool kSum = WEIGHT && sizeof(T) == 2;
+      f32x16 c[kSum ? 2 * AHW : 1];
+      if constexpr (kSum) {
 #pragma unroll
         for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
           for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+      }
+      typename TT::Frag xf[2][2 * AHW];
+      pipelined<NS>(
+          [&](int s, int b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const typename TT::Frag b = tt.rows_k(S, (wave & 1) * 32, s);
+            for (int db = 0; db < 2 * AHW; ++db) xf[b][db] = tt.cols(cur.X[db >> 1], s, db & 1);
+          },
+          [&](int s, int b) __attribute__((always_inline)) {
+            typename TT::Frag sf = sc[s];
+            if constexpr (WEIGHT && !kSum) sf *= w;
 #pragma unroll
-          for (int db = 0; db < 2 * AHW; ++db) c[db] = TT::mfma(tt.cols(cur.X[db >> 1], s, db & 1), b, c[db]);
-        }
+            for (int db = 0; db < 2 * AHW; ++db) {
+              f32x16 &acc = kSum ? c[kSum ? db : 0] : o[db];
+              acc = TT::mfma(xf[b][db], sf, acc);
+            }
+          });
+      if constexpr (kSum) {
 #pragma unroll
         for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
           for (int v = 0; v < 16; ++v) o[db][v] = fmaf(w, c[db][v], o[db][v]);
-      } else {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          typename TT::Frag b = tt.rows_k(S, (wave & 1) * 32, s);
-          if constexpr (WEIGHT) b *= w;
-#pragma unroll
-          for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(tt.cols(cur.X[db >> 1], s, db & 1), b, o[db]);
-        }
       }
     }
     wait_vmem();
@@ -453,12 +599,12 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
     ++t;
   };
   while (t < nt) {
-    step(st0, st1);
+    step(st0, s0, m0, st1, s1, m1);
     if (t >= nt) break;
-    step(st1, st0);
+    step(st1, s1, m1, st0, s0, m0);
   }
   if (!rows_here) return;
-  unsigned char *ot = &st0.S[0][0] + wave * (TT::kBytes / 2);
+  unsigned char *ot = (wave < 2 ? st0.X[0] : st1.X[0]) + (wave & 1) * (TT::kBytes / 2);  // (free after the last barrier)
   T *out = static_cast<T *>(p.out) + (head * a.Lq + wrow) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
@@ -481,10 +627,11 @@ struct CollectArgs {
 };
 
 template <typename T, int AHW>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
+__global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(StripArgs a, CollectArgs p) {
   typedef TileT<T> TT;
-  constexpr int NS = TT::kSlices;
-  struct Stage { unsigned char S[2][TT::kBytes], Y[AHW][TT::kBytes]; };
+  constexpr int RT = sizeof(T) == 4 ? 32 : 64;  // rows per step: 24 KiB (64 columns, either type) leave room for three
+  constexpr int NS = TT::kSlices * RT / 64;     // work-groups on a compute unit
+  struct Stage { unsigned char S[2][TT::kBytes * RT / 64], Y[AHW][TT::kBytes * RT / 64]; };
   __shared__ __attribute__((aligned(16))) Stage st0, st1;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -497,22 +644,26 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
   wg >>= 1;
   const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * 128;
   const int64_t head = wg / (uint32_t)a.kblocks;
-  const int nt = (int)(a.rows / 64);
+  const int nt = (int)(a.rows / RT);
   int t = 0;
   if (a.causal && key0 > a.q0 + 63) {  // first row tile whose last row sees the block's first key
-    const int64_t f = (key0 - a.q0) / 64;
+    const int64_t f = (key0 - a.q0) / 64 * (64 / RT);
     t = f < nt ? (int)f : nt;
   }
-  const T *Sh = static_cast<const T *>(which ? p.strip[1] : p.strip[0]) + head * a.rows * a.L + key0;
-  const int64_t second = key0 + 64 < a.L ? 64 : 0;
+  const int64_t ktiles = a.L / 64;
+  const T *Sh = static_cast<const T *>(which ? p.strip[1] : p.strip[0]) +
+                strip_tile<T>(head, a.rows / 64, 0, ktiles, key0 / 64);
+  const int64_t second = key0 + 64 < a.L ? 4096 : 0;  // (no second key tile: refetch the first)
   const T *Yh = static_cast<const T *>(which ? p.Y[1] : p.Y[0]) + head * a.Lq * a.A + a0;
-  const typename TT::DMA dma_s(wave, lane, a.L), dma_y(wave, lane, a.A);
+  const StripDMA<T, RT> dma_s(wave, lane);
+  const typename TT::template DMA<RT> dma_y(wave, lane, a.A);
   auto load = [&](int tt_, Stage &st) __attribute__((always_inline)) {
-    const T *s = Sh + (int64_t)tt_ * 64 * a.L;
+    const int row = tt_ * RT;
+    const T *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
     dma_s.load(s, st.S[0]);
     dma_s.load(s + second, st.S[1]);
 #pragma unroll
-    for (int ah = 0; ah < AHW; ++ah) dma_y.load(Yh + (int64_t)tt_ * 64 * a.A + ah * 64, st.Y[ah]);
+    for (int ah = 0; ah < AHW; ++ah) dma_y.load(Yh + (int64_t)row * a.A + ah * 64, st.Y[ah]);
   };
   load(t < nt ? t : nt - 1, st0);  // (a block that no row sees: any tile)
   const int64_t wkey = key0 + wave * 32, wtile = key0 + (wave >> 1) * 64;
@@ -527,14 +678,19 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
   __syncthreads();
   auto step = [&](Stage &cur, Stage &nxt) __attribute__((always_inline)) {
     if (t + 1 < nt) load(t + 1, nxt);
-    if (keys_here && tile_seen(a, (int64_t)t * 64, wtile)) {
+    if (keys_here && tile_seen(a, (int64_t)t * RT, wtile)) {
       const unsigned char *S = cur.S[wave >> 1];
+      typename TT::Frag sf[2], yf[2][2 * AHW];
+      pipelined<NS>(
+          [&](int s, int b) __attribute__((always_inline)) {
+            sf[b] = tt.cols(S, s, wave & 1);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const typename TT::Frag b = tt.cols(S, s, wave & 1);
+            for (int db = 0; db < 2 * AHW; ++db) yf[b][db] = tt.cols(cur.Y[db >> 1], s, db & 1);
+          },
+          [&](int s, int b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(tt.cols(cur.Y[db >> 1], s, db & 1), b, o[db]);
-      }
+            for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(yf[b][db], sf[b], o[db]);
+          });
     }
     wait_vmem();
     __syncthreads();
@@ -547,7 +703,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
   }
   if (!keys_here) return;
   if (p.add || p.keep) {
-    float *acc = (which ? p.acc[1] : p.acc[0]) + (head * a.L + wkey + col) * a.A + a0 + half * 4;
+    float *acc = (which ? p.acc[1] : p.acc[0]) + (head * a.L + wkey + TT::key_of_col(col)) * a.A + a0 + half * 4;
 #pragma unroll
     for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
@@ -562,11 +718,12 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 1 : (AHW == 1 ? 3 : 2)) 
     if (p.keep) return;
   }
   const float alpha = which ? p.alpha[1] : p.alpha[0];
-  unsigned char *ot = &st0.S[0][0] + wave * (TT::kBytes / 2);
+  // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
+  unsigned char *ot = (wave < 2 ? st0.S[0] : st1.S[0]) + (wave & 1) * (TT::kBytes / 2);
   T *out = static_cast<T *>(which ? p.out[1] : p.out[0]) + (head * a.L + wkey) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
-    TT::stage(ot, o[2 * ah], o[2 * ah + 1], alpha, lane);
+    TT::stage(ot, o[2 * ah], o[2 * ah + 1], alpha, TT::key_of_col(col) + half * 32);
     TT::flush(ot, out + ah * 64, 32, lane, a.A);
   }
 }
@@ -581,27 +738,32 @@ struct StripPlan {
   size_t strip, strip2, stats, acc_k, acc_v, total;
 };
 
-// The strips of a group fit into `kStripBytes`, or into what the strips of one rank take when every score
-// has an fp32 and a dtype copy (per pass), whichever is more: the ranks' rows are then taken together
-// whenever the sizes are ordinary.
-constexpr size_t kStripBytes = (size_t)192 << 20;
+// Sizes of a group's strips.  All heads and rows at once where that is at most kStripBytes; else groups of
+// heads of at most kCacheBytes, which the 256 MB infinity cache still holds when the next kernel reads them
+// (bert_large-shaped, 12 groups: 1678 us; 5 groups of 512 MB 1946, one group 1689); else, for a single head with longer
+// strips, groups of rows that fill kStripBytes or what one rank's strips take with an fp32 and a dtype copy
+// of every score, whichever is more.
+constexpr size_t kStripBytes = (size_t)512 << 20, kCacheBytes = (size_t)192 << 20;
 
 StripPlan strip_plan(const Dims &d, int dtype, int pass) {
   const size_t es = dtype == RSA_BF16 ? 2 : 4, strips = pass == 1 ? 2 : 1;
   const int64_t heads = (int64_t)d.B * d.Z;
   const size_t one_rank = (size_t)heads * d.c * d.L * (4 + es) * strips;
-  const size_t row = (size_t)d.L * es * strips;  // bytes of a head's row
-  const size_t budget = row * d.Lq <= kStripBytes || one_rank <= kStripBytes ? kStripBytes : one_rank;
+  const size_t row = (size_t)d.L * es * strips, head = row * d.Lq;  // bytes of a head's row, of a head
   StripPlan p{};
-  if (row * d.Lq <= budget) {
-    p.rows = d.Lq;
-    p.heads = (int64_t)(budget / (row * d.Lq));
-    if (p.heads > heads) p.heads = heads;
-    const int64_t groups = (heads + p.heads - 1) / p.heads;
-    p.heads = (heads + groups - 1) / groups;  // groups of equal size
-  } else {
-    p.heads = 1;
-    p.rows = (int64_t)(budget / row) / 128 * 128;  // at least one rank's rows of every head: never 0
+  p.rows = d.Lq;
+  p.heads = heads;
+  if (head * heads > kStripBytes) {
+    if (head <= kStripBytes) {
+      const int64_t most = head < kCacheBytes ? (int64_t)(kCacheBytes / head) : 1;
+      const int64_t groups = (heads + most - 1) / most;
+      p.heads = (heads + groups - 1) / groups;  // groups of equal size
+    } else {
+      const size_t budget = one_rank > kStripBytes ? one_rank : kStripBytes;
+      p.heads = 1;
+      p.rows = (int64_t)(budget / row) / 128 * 128;  // at least 128: budget holds one rank's rows, 64 or more, twice
+      if (p.rows > d.Lq) p.rows = d.Lq;
+    }
   }
   const size_t scores = (size_t)p.heads * p.rows * d.L;
   size_t off = 0;
@@ -620,27 +782,25 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
 }
 
 template <typename T>
-hipError_t launch_scores(const StripArgs &a0, int64_t heads, int A, bool bwd, hipStream_t st) {
+hipError_t launch_scores(const StripArgs &a0, int64_t heads, bool bwd, hipStream_t st) {
   StripArgs a = a0;
-  // key tiles per work-group: two where LDS has room for them beside a second work-group's
-#define RSA_SCORES(AH, NF, NB)                                                                     \
-  case AH: {                                                                                       \
-    constexpr int nf = NF, nb = NB;                                                                \
-    const int nk = bwd ? nb : nf;                                                                  \
-    a.kblocks = (int)((a.L / 64 + nk - 1) / nk);                                                   \
-    const dim3 grid((unsigned)(heads * a.rtiles * a.kblocks));                                     \
-    if (bwd) hipLaunchKernelGGL((strip_scores_bwd_kernel<T, AH, nb>), grid, dim3(256), 0, st, a);  \
-    else hipLaunchKernelGGL((strip_scores_fwd_kernel<T, AH, nf>), grid, dim3(256), 0, st, a);      \
-    break;                                                                                         \
+  // Key tiles per work-group: the count (at most 16) whose rounds of work-groups cost least, a work-group costing
+  // its tiles and about two more for its prologue.
+  const int64_t tiles = a.L / 64, slots = 256 * (bwd ? (sizeof(T) * a.A <= 256 ? 2 : 1) : (sizeof(T) * a.A <= 256 ? 4 : 2));
+  double best = 1e30;
+  for (int per = 1; per <= 16 && per <= tiles; ++per) {
+    const int64_t wgs = heads * a.rtiles * ((tiles + per - 1) / per);
+    const double cost = (double)((wgs + slots - 1) / slots) * (per + 2);
+    if (cost < best) { best = cost; a.per = per; }
   }
-  constexpr bool bf = sizeof(T) == 2;
-  switch (A / 64) {
-    RSA_SCORES(1, 2, (bf ? 2 : 1))
-    RSA_SCORES(2, (bf ? 2 : 1), 1)
-    RSA_SCORES(3, 1, 1)
-    default:
-    RSA_SCORES(4, 1, 1)
-  }
+  a.kblocks = (int)((tiles + a.per - 1) / a.per);
+  const dim3 grid((unsigned)(heads * a.rtiles * a.kblocks));
+#define RSA_SCORES(AH)                                                                          \
+  case AH:                                                                                      \
+    if (bwd) hipLaunchKernelGGL((strip_scores_bwd_kernel<T, AH>), grid, dim3(256), 0, st, a);   \
+    else hipLaunchKernelGGL((strip_scores_fwd_kernel<T, AH>), grid, dim3(256), 0, st, a);       \
+    break;
+  switch (a.A / 64) { RSA_SCORES(1) RSA_SCORES(2) RSA_SCORES(3) RSA_SCORES(4) }
 #undef RSA_SCORES
   return hipGetLastError();
 }
@@ -697,7 +857,7 @@ hipError_t forward_t(const Dims &d, int dtype, const void *Q, const void *K, con
     for (int64_t r0 = 0; r0 < d.Lq; r0 += pl.rows) {
       const int64_t nr = pl.rows < d.Lq - r0 ? pl.rows : d.Lq - r0;
       const StripArgs a = group_args<T>(d, pl, ws, h0, r0, nr, Q, K, V);
-      RSA_TRY(launch_scores<T>(a, nh, d.A, false, st));
+      RSA_TRY(launch_scores<T>(a, nh, false, st));
       const ApplyArgs p = {a.strip, a.V, static_cast<T *>(O) + (h0 * d.Lq + r0) * d.A, a.stats,
                            LSE + h0 * d.Lq + r0};
       RSA_TRY((launch_apply<T, true>(a, p, nh, st)));
@@ -719,7 +879,7 @@ hipError_t backward_t(const Dims &d, int dtype, const void *dO, const void *Q, c
       const int64_t q = (h0 * d.Lq + r0) * d.A, k = h0 * d.L * d.A;
       a.dO = static_cast<const T *>(dO) + q; a.O = static_cast<const T *>(O) + q;
       a.LSE_in = LSE + h0 * d.Lq + r0;
-      RSA_TRY(launch_scores<T>(a, nh, d.A, true, st));
+      RSA_TRY(launch_scores<T>(a, nh, true, st));
       const ApplyArgs p = {a.strip2, a.K, static_cast<T *>(dQ) + q, nullptr, nullptr};
       RSA_TRY((launch_apply<T, false>(a, p, nh, st)));
       CollectArgs c{};

@@ -159,7 +159,7 @@ def test_staged_explicit_softmax_scale(dtype):
     ("f32", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
     ("bf16", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
     ("bf16", dict(B=2, Z=15, L=2048, N=4), [0, 9, 10, 29]),            # heads in several groups
-    ("f32", dict(B=1, Z=1, L=8192, N=8, causal=True), [0]),            # rows in several groups: fp32 accumulators
+    ("f32", dict(B=1, Z=1, L=8448, N=11, causal=True), [0]),           # rows in several groups: fp32 accumulators
     ("bf16", dict(B=1, Z=1, L=12288, N=12, causal=True), [0]),
 ])
 def test_staged_strip_groups_and_edges(dtype, kw, heads):
