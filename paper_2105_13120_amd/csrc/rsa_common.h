@@ -106,6 +106,17 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// Causal masks as bits: the lowest n (clamped to 0 .. 32) bits set, and x where bit `bit` of `mask` is set, -inf
+// elsewhere (a field extract and a bitwise select: compares would each hold a pair of scalar registers,
+// 64 of them at once, and spill everything else).
+__device__ __forceinline__ uint32_t low_bits(int n) {
+  return n <= 0 ? 0u : (n >= 32 ? ~0u : (1u << n) - 1u);
+}
+__device__ __forceinline__ float keep_bit(float x, uint32_t mask, int bit) {
+  const uint32_t t = (uint32_t)((int32_t)(mask << (31 - bit)) >> 31);
+  return __builtin_bit_cast(float, (t & __builtin_bit_cast(uint32_t, x)) | (~t & 0xff800000u));
+}
+
 // Work-group id remap for the 8 XCDs: hardware hands consecutive work-group
 // ids to XCDs round-robin, so id i runs on XCD i % 8.  Returns a logical id
 // such that each XCD gets one contiguous range of logical ids (work-groups
@@ -117,6 +128,29 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t id, uint32_t n, uint32_t 
   const uint32_t per = n >> 3;
   if (per == 0 || id >= per * 8) return id;  // tail keeps its id
   return ((id + rot) & 7) * per + (id >> 3);
+}
+
+// (head, tile) of a work-group under the causal mask, where the tiles of a head differ in work: all heads' longest
+// tiles first, so that the short ones fill the chip's last rounds.  (Head after head, longest first within
+// a head, leaves the last heads' long tiles to the end: B8 Z16 L2048, forward, 148 us; in this order 97.)  With
+// a multiple of 8 heads the heads stay on their XCDs, since id % heads and the XCD id % 8 agree.
+// rank: the tile's place among the head's, 0 = the most work.
+__device__ __forceinline__ void longest_first(uint32_t id, uint32_t heads, uint32_t &head, uint32_t &rank) {
+  rank = id / heads;
+  head = id - rank * heads;
+}
+// Row tile of place `rank`: later rows see more keys.  Under zig-zag ownership (half: tiles per half-chunk, when they
+// divide it, else 0) the later half-chunks of the ranks come in rank order, then the earlier ones in reverse.
+__device__ __forceinline__ uint32_t row_tile_of_rank(uint32_t rank, uint32_t tiles, uint32_t half) {
+  if (half == 0) return tiles - 1 - rank;
+  const uint32_t n = tiles / (2 * half), g = rank / half, w = half - 1 - rank % half;
+  return g < n ? g * 2 * half + half + w : (2 * n - 1 - g) * 2 * half + w;
+}
+// Ends the life of everything a uniform value was computed from (scalar registers are scarce in these kernels).
+__device__ __forceinline__ uint32_t settled(uint32_t x) {
+  x = __builtin_amdgcn_readfirstlane(x);
+  asm volatile("" : "+s"(x));
+  return x;
 }
 
 // Derived sizes of a validated descriptor, shared by host code and kernels.

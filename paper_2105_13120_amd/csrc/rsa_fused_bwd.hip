@@ -42,6 +42,7 @@ struct BwdArgs {
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q, dQ; K, V, dK, dV; O, dO
   RowMap map;  // local query row -> global token index
   int N, Z, tiles_per_head;
+  int by_length, half_tiles;    // causal: order of the tiles over the work-groups (longest_first)
   float cl2, scale, inv_scale;  // scale log2(e), scale, 1 / scale
 };
 
@@ -88,10 +89,12 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(const uint16_t *dO,
 // and dK = scale * sum_i dS_ij Q_i.
 // A head of 128 is two halves of 64 (AH = 2): two LDS tiles per 64 rows, S' and dP' contract over
 // both, dV and dK have twice the accumulators, and the kernel runs one wave per SIMD.
-template <int NQ, bool CAUSAL, int AH>
-__global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(BwdArgs a) {
-  constexpr int KW = 32;      // keys per wave
-  constexpr int BK = 4 * KW;  // keys per work-group
+// WK waves share the work-group's keys, 32 each; QS groups of such waves share the query rows: group g takes
+// every QS-th stage of the walk and the groups' sums are added in LDS.
+template <int NQ, bool CAUSAL, int AH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(BwdArgs a) {
+  constexpr int KW = 32;       // keys per wave
+  constexpr int BK = WK * KW;  // keys per work-group
   constexpr int A = 64 * AH;
   // The two stage buffers are separate objects, each addressed by name, so that the
   // compiler knows a direct load into one cannot alias the LDS reads of the other.
@@ -99,14 +102,22 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
     unsigned char Qt[NQ][AH][kTileBytes], dOs[NQ][AH][kTileBytes];
     float lse[NQ][64], d[NQ][64];
   };
-  __shared__ __attribute__((aligned(16))) Stage stage0, stage1;
+  __shared__ __attribute__((aligned(16))) Stage stage0[QS], stage1[QS];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
+  const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t head = wg / a.tiles_per_head;
-  const int64_t key0 = (wg % a.tiles_per_head) * BK;  // first key of the work-group
+  uint32_t head_, kt_;  // under the causal mask the first keys are seen by the most rows
+  if (CAUSAL && a.by_length) {
+    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, kt_);
+  } else {
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x), tiles = a.tiles_per_head;
+    head_ = wg / tiles;
+    kt_ = wg % tiles;
+  }
+  const int64_t head = settled(head_), kt = settled(kt_);
+  const int64_t key0 = kt * BK;  // first key of the work-group
   const int64_t wkey0 = key0 + wave * KW;             // first key of this wave
 
   const int64_t kv_off = head_offset(head, a.Z, a.ks);
@@ -165,7 +176,7 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
   const int i_end = i_begin + per_split < nst ? i_begin + per_split : nst;
   auto advance = [&](int i) { ++i; while (i < i_end && !visible(i)) ++i; return i; };
 
-  const TileDMA dma_q(wave, lane, (int)q_ld), dma_o(wave, lane, (int)o_ld);
+  const TileDMAT<WK> dma_q(wave, lane, (int)q_ld), dma_o(wave, lane, (int)o_ld);
   auto load_stage = [&](int i, Stage &sn) __attribute__((always_inline)) {
     const int st = st_of(i);
 #pragma unroll
@@ -178,22 +189,28 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
         dma_q.load(Qh + r0 * q_ld + ah * 64, sn.Qt[u][ah]);
         dma_o.load(dOh + r0 * o_ld + ah * 64, sn.dOs[u][ah]);
       }
-      // the 64 row terms of the tile, one dword per lane: waves 0/1 fetch -LSE / scale, 2/3 fetch -D
-      if ((wave & 1) == (u & 1)) {
-        if (wave < 2) lds_dma4(nLh + r0 + lane, sn.lse[u]);
-        else lds_dma4(nDh + r0 + lane, sn.d[u]);
+      // the 64 row terms of the tile, one dword per lane: the group's first waves fetch -LSE / scale, its last -D
+      if (WK < 4 || (wave & 1) == (u & 1)) {
+        if (wave < (WK + 1) / 2) lds_dma4(nLh + r0 + lane, sn.lse[u]);
+        if (wave >= WK / 2) lds_dma4(nDh + r0 + lane, sn.d[u]);
       }
     }
   };
 
-  int i = i_begin;
-  if (i < i_end && !visible(i)) i = advance(i);
-  if (i < i_end) load_stage(i, stage0);
+  auto skip = [&](int i, int n) {
+    for (int k = 0; k < n && i < i_end; ++k) i = advance(i);
+    return i;
+  };
+  int i0 = i_begin;  // position of the walk: group 0's stage
+  if (i0 < i_end && !visible(i0)) i0 = advance(i0);
+  int i = QS == 1 ? i0 : skip(i0, grp);  // this group's stage
+  if (i < i_end) load_stage(i, stage0[grp]);
   wait_vmem();
   __syncthreads();
   // one stage: start the loads of the next stage into sn, compute on sc
   auto stage = [&](Stage &sc, Stage &sn) __attribute__((always_inline)) {
-    const int inext = advance(i);
+    const int i0next = QS == 1 ? advance(i) : skip(i0, QS);
+    const int inext = QS == 1 ? i0next : skip(i0next, grp);
     if (inext < i_end) load_stage(inext, sn);
 
     // The 32 MFMAs of a tile go in four groups of eight -- S', dP' of rows 0..31 (G0) and of
@@ -208,7 +225,7 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
     const int qt0 = st_of(i) * NQ;
     auto active = [&](int u) {
       const int qt = qt0 + u;
-      return qt < nqt && (!CAUSAL || a.map((int64_t)qt * 64) + 63 >= wkey0);
+      return (QS == 1 || i < i_end) && qt < nqt && (!CAUSAL || a.map((int64_t)qt * 64) + 63 >= wkey0);
     };
     auto fetch = [&](int u, int qb) __attribute__((always_inline)) {
       // accumulators start from -LSE / scale and -D of their rows (same for all lanes of a half)
@@ -242,12 +259,11 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
           f32x16 &sv = sacc[qb];
           const f32x16 &dp = dpacc[qb];
           if (domask) {
-            // first visible row of the lane's key, relative to the block of 32 rows (32-bit compare)
+            // rows of the block of 32 that see the lane's key: all but the first n
             const int64_t d64 = wkey0 + col - qf - qb * 32 - half * 4;
-            const int dfirst = d64 < -64 ? -64 : (int)d64;
+            const uint32_t seen = ~low_bits(d64 > 32 ? 32 : (d64 < 0 ? 0 : (int)d64));
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if ((v >> 2) * 8 + (v & 3) < dfirst) sv[v] = -INFINITY;
+            for (int v = 0; v < 16; ++v) sv[v] = keep_bit(sv[v], seen, (v >> 2) * 8 + (v & 3));
           }
 #pragma unroll
           for (int w2 = 0; w2 < 2; ++w2) {
@@ -308,12 +324,44 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
 
     wait_vmem();
     __syncthreads();
-    i = inext;
+    i = inext; i0 = i0next;
   };
-  while (i < i_end) {
-    stage(stage0, stage1);
-    if (i >= i_end) break;
-    stage(stage1, stage0);
+  while (i0 < i_end) {
+    stage(stage0[grp], stage1[grp]);
+    if (i0 >= i_end) break;
+    stage(stage1[grp], stage0[grp]);
+  }
+
+  if constexpr (QS > 1) {
+    // groups 1 .. QS - 1 leave dV in the first stage buffers and dK in the second, group 0 adds them
+    static_assert((QS - 1) * WK * 32 * A * 4 <= (int)sizeof(stage0), "room for the groups' sums");
+    auto slot = [&](unsigned char *o, int g, int db) {
+      return reinterpret_cast<f32x4 *>(o + (((g - 1) * WK + wave) * 2 * AH + db) * 4096);
+    };
+    unsigned char *ov = reinterpret_cast<unsigned char *>(stage0), *ok = reinterpret_cast<unsigned char *>(stage1);
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < 2 * AH; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          slot(ov, grp, db)[g * 64 + lane] = f32x4{dv[db][g * 4], dv[db][g * 4 + 1], dv[db][g * 4 + 2], dv[db][g * 4 + 3]};
+          slot(ok, grp, db)[g * 64 + lane] = f32x4{dk_[db][g * 4], dk_[db][g * 4 + 1], dk_[db][g * 4 + 2], dk_[db][g * 4 + 3]};
+        }
+    }
+    __syncthreads();
+    if (grp == 0) {
+      for (int q = 1; q < QS; ++q)
+#pragma unroll
+        for (int db = 0; db < 2 * AH; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = slot(ov, q, db)[g * 64 + lane], y = slot(ok, q, db)[g * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { dv[db][g * 4 + e] += x[e]; dk_[db][g * 4 + e] += y[e]; }
+          }
+    }
+    __syncthreads();  // the epilogue writes to the buffers that the other waves just read
+    if (grp > 0) return;
   }
 
   if (gridDim.y > 1) {  // fp32 partial sums: [dV | dK][split][head][key][64]
@@ -339,7 +387,8 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
 
   // the wave's 32 x 64 blocks of dV and dK leave through its own LDS tile as whole 128-byte rows
   // (every wave is past the loop's last barrier and no load is in flight: the buffers are free)
-  unsigned char *ot = wave < 2 ? stage0.Qt[wave][0] : stage0.dOs[wave - 2][0];
+  unsigned char *ot = wave < 2 ? (wave == 0 ? stage0[0].Qt[0][0] : stage1[0].Qt[0][0])
+                               : (wave == 2 ? stage0[0].dOs[0][0] : stage1[0].dOs[0][0]);
 #pragma unroll
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
     stage_block_T(ot, 0, dv[2 * ah], dv[2 * ah + 1], 1.0f, lane);
@@ -350,28 +399,37 @@ __global__ void __launch_bounds__(256, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(Bw
 }
 
 // ---------------------------------------------------------------------- dQ ---
-template <int R, bool CAUSAL, bool PRE, int AH, int NK>  // NK: key tiles per stage (one barrier per stage)
-__global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdArgs a) {
+// NK: key tiles per stage (one barrier per stage).  RW waves share the work-group's rows, R each; KS groups of
+// such waves share the keys, as in the forward.
+template <int R, bool CAUSAL, bool PRE, int AH, int NK, int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdArgs a) {
   constexpr int QB = R / 32;
-  constexpr int BM = 4 * R;
+  constexpr int BM = RW * R;
   constexpr int A = 64 * AH;  // a head of 128 is two halves of 64: two LDS tiles per 64 keys
   // two named stage buffers: see the dK/dV kernel
-  __shared__ __attribute__((aligned(16))) unsigned char Ks0[NK][AH][kTileBytes], Ks1[NK][AH][kTileBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char Vs0[NK][AH][kTileBytes], Vs1[NK][AH][kTileBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char Ks0[KS][NK][AH][kTileBytes], Ks1[KS][NK][AH][kTileBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char Vs0[KS][NK][AH][kTileBytes], Vs1[KS][NK][AH][kTileBytes];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / RW;
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y);
-  const int64_t head = wg / a.tiles_per_head;
-  // under the causal mask later rows see more keys: the long work-groups of a head start first
-  const int64_t row0 =
-      (CAUSAL ? a.tiles_per_head - 1 - wg % a.tiles_per_head : wg % a.tiles_per_head) * BM;
+  uint32_t head_, qt_;  // (order: see the forward)
+  if (CAUSAL && a.by_length) {
+    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, qt_);
+    qt_ = row_tile_of_rank(qt_, a.tiles_per_head, a.half_tiles);
+  } else {
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.tiles_per_head;
+    head_ = wg / tiles;
+    qt_ = CAUSAL ? tiles - 1 - wg % tiles : wg % tiles;
+  }
+  const int64_t head = settled(head_), qt = settled(qt_);
+  const int64_t row0 = qt * BM;
   const int n = (a.map.rb + (int)(row0 / a.c)) % a.N;  // rank that owns the first row (see the forward)
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
   int64_t q_last = 0;
 #pragma unroll
-  for (int i = 0; i < BM / 64; ++i)
+  for (int i = 0; i < (BM + 63) / 64; ++i)
     if (row0 + i * 64 < a.Lq) {
       const int64_t e = a.map(row0 + i * 64) + 63;
       q_last = e > q_last ? e : q_last;
@@ -431,7 +489,7 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
       ks = spc;
     }
   };
-  const TileDMA dma(wave, lane, (int)kv_ld);
+  const TileDMAT<RW> dma(wave, lane, (int)kv_ld);
   auto load_stage = [&](int64_t k0, auto &Kn, auto &Vn) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
@@ -445,10 +503,19 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
     }
   };
 
-  int t = f_begin / spc, kt = f_begin % spc;
+  // n stages further on; false past the end
+  auto skip = [&](int &t, int &ks, int n) -> bool {
+    bool h = true;
+    for (int i = 0; i < n && h; ++i) h = advance(t, ks);
+    return h;
+  };
+  int t = f_begin / spc, kt = f_begin % spc;  // position of the walk: group 0's stage
   bool have = f_begin < f_end;
   if (CAUSAL && have && k0_of(t, kt) > q_last) have = advance(t, kt);
-  if (have) load_stage(k0_of(t, kt), Ks0, Vs0);
+  int tg_ = t, kg_ = kt;  // this group's stage
+  int &tg = KS == 1 ? t : tg_, &kg = KS == 1 ? kt : kg_;
+  bool mine = KS == 1 ? have : have && skip(tg, kg, grp);
+  if (mine) load_stage(k0_of(tg, kg), Ks0[grp], Vs0[grp]);
   // The rows this wave keeps in registers are fetched after the first stage's tiles are on their
   // way, so that the two latencies overlap (short walks, e.g. a few hundred projected keys, are
   // mostly prologue).
@@ -479,7 +546,7 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
       }
       dd = -xhalf_sum(acc);
       l2 = -a.LSE[head * a.Lq + qrow[qb]] * a.inv_scale;
-      if (r < a.Lq && blockIdx.y == 0) {
+      if (r < a.Lq && blockIdx.y == 0 && grp == 0) {
         if (half == 0) {
           a.nD_out[head * a.Lq + r] = dd;
           a.nL_out[head * a.Lq + r] = l2;
@@ -496,15 +563,17 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
   __syncthreads();
   // one stage: start the loads of the next stage into (Kn, Vn), compute on (Kc, Vc)
   auto stage = [&](auto &Kc, auto &Vc, auto &Kn, auto &Vn) __attribute__((always_inline)) {
-    const int64_t ks0 = k0_of(t, kt);
+    const int64_t ks0 = k0_of(tg, kg);
     int t2 = t, kt2 = kt;
-    const bool have_next = advance(t2, kt2);
-    if (have_next) load_stage(k0_of(t2, kt2), Kn, Vn);
+    const bool have_next = KS == 1 ? advance(t2, kt2) : skip(t2, kt2, KS);
+    int tg2 = t2, kg2 = kt2;
+    const bool mine_next = KS == 1 ? have_next : have_next && skip(tg2, kg2, grp);
+    if (mine_next) load_stage(k0_of(tg2, kg2), Kn, Vn);
 
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
     const int64_t k0 = ks0 + u * kTileKeys;
-    if (u < nk && (!CAUSAL || k0 <= wq_last)) {
+    if ((KS == 1 || mine) && u < nk && (!CAUSAL || k0 <= wq_last)) {
       const bool domask = CAUSAL && k0 + kTileKeys - 1 > wq_first;
       bf16x8 sf[QB][4];
 #pragma unroll
@@ -523,12 +592,11 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
         if (domask) {  // uniform over the wave: only tiles on the diagonal pay for the mask
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
-            // last visible key of the lane's row, relative to the block of 32 keys (32-bit compare)
-            const int64_t d64 = qtok[qb] - k0 - kb * 32 - half * 4;
-            const int dlast = d64 > 64 ? 64 : (int)d64;
+            // keys of the block of 32 that the lane's row sees: the first n
+            const int64_t d64 = qtok[qb] + 1 - k0 - kb * 32 - half * 4;
+            const uint32_t seen = low_bits(d64 > 32 ? 32 : (d64 < 0 ? 0 : (int)d64));
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if ((v >> 2) * 8 + (v & 3) > dlast) s[qb][v] = -INFINITY;
+            for (int v = 0; v < 16; ++v) s[qb][v] = keep_bit(s[qb][v], seen, (v >> 2) * 8 + (v & 3));
           }
         }
 #pragma unroll
@@ -558,11 +626,47 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
     wait_vmem();
     __syncthreads();
     t = t2; kt = kt2; have = have_next;
+    if (KS > 1) { tg = tg2; kg = kg2; mine = mine_next; }
   };
   while (have) {
-    stage(Ks0, Vs0, Ks1, Vs1);
+    stage(Ks0[grp], Vs0[grp], Ks1[grp], Vs1[grp]);
     if (!have) break;
-    stage(Ks1, Vs1, Ks0, Vs0);
+    stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
+  }
+
+  if constexpr (KS > 1) {  // groups 1 .. KS - 1 leave their sums in the stage buffers, group 0 adds them
+    static_assert(QB == 1, "32 rows per wave");
+    constexpr int PARTS = 2 * AH;  // of 32 columns: 4 KiB per wave
+    static_assert((PARTS * (KS - 1) + 3) / 4 * RW * 4096 <= KS * NK * AH * kTileBytes, "room for the groups' sums");
+    auto slot = [&](int g, int part) -> f32x4 * {
+      const int i = (g - 1) * PARTS + part;
+      unsigned char *o = (i & 3) == 0 ? &Ks0[0][0][0][0] : (i & 3) == 1 ? &Ks1[0][0][0][0]
+                         : (i & 3) == 2 ? &Vs0[0][0][0][0] : &Vs1[0][0][0][0];
+      return reinterpret_cast<f32x4 *>(o + ((i >> 2) * RW + wave) * 4096);
+    };
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < PARTS; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          slot(grp, db)[g * 64 + lane] =
+              f32x4{dq[db][0][g * 4 + 0], dq[db][0][g * 4 + 1], dq[db][0][g * 4 + 2], dq[db][0][g * 4 + 3]};
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int q = 1; q < KS; ++q)
+#pragma unroll
+        for (int db = 0; db < PARTS; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = slot(q, db)[g * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dq[db][0][g * 4 + e] += x[e];
+          }
+    }
+    __syncthreads();  // the epilogue writes to the buffers that the other waves just read
+    if (grp > 0) return;
   }
 
   if (gridDim.y > 1) {  // fp32 partial sum of this split: [split][head][row][64]
@@ -586,7 +690,7 @@ __global__ void __launch_bounds__(256, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdA
   }
 
   // the wave's R x 64 block of dQ leaves through its own LDS tile as whole 128-byte rows
-  unsigned char *ot = wave == 0 ? Ks0[0][0] : (wave == 1 ? Ks1[0][0] : (wave == 2 ? Vs0[0][0] : Vs1[0][0]));
+  unsigned char *ot = wave == 0 ? Ks0[0][0][0] : (wave == 1 ? Ks1[0][0][0] : (wave == 2 ? Vs0[0][0][0] : Vs1[0][0][0]));
   const int64_t wr0 = row0 + wave * R;
 #pragma unroll
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
@@ -622,7 +726,7 @@ static BwdArgs make_bwd_args(const Dims &d, const void *dO, const void *Q, const
   a.L = d.L; a.c = d.c; a.Lq = d.Lq; a.map = make_row_map(d);
   a.N = d.N; a.Z = d.Z; a.cl2 = d.scale * kLog2e; a.scale = d.scale; a.inv_scale = 1.0f / d.scale;
   for (int k = 0; k < 3; ++k) { a.qs[k] = d.qs[k]; a.ks[k] = d.ks[k]; a.os[k] = d.os[k]; }
-  a.tiles_per_head = 0;
+  a.tiles_per_head = 0; a.by_length = 0; a.half_tiles = 0;
   return a;
 }
 
@@ -651,24 +755,32 @@ int fused_bwd_dkdv_splits(const Dims &d) {
   return s < 2 ? 1 : (int)s;
 }
 
+template <int NQ, int AH, int WK, int QS>
+static void launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
+  a.tiles_per_head = (int)((d.L + 32 * WK - 1) / (32 * WK));
+  a.by_length = order_by_length(d, splits);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * WK * QS);
+  if (d.causal)
+    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, false, AH, WK, QS>), grid, block, 0, st, a);
+}
+
 hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const void *K,
                           const void *V, const float *nL, const float *nD, void *dK, void *dV,
                           hipStream_t st, float *part, int splits) {
   BwdArgs a = make_bwd_args(d, dO, Q, K, V, nL, nD, nullptr, dK, dV);
-  a.tiles_per_head = (int)((d.L + 127) / 128);
   a.part = part;
   if (!part) splits = 1;
-  dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits);
-  if (d.A == 128) {
-    if (d.causal)
-      hipLaunchKernelGGL((fused_bwd_dkdv_kernel<2, true, 2>), grid, dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((fused_bwd_dkdv_kernel<2, false, 2>), grid, dim3(256), 0, st, a);
-  } else if (d.causal) {
-    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<2, true, 1>), grid, dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<2, false, 1>), grid, dim3(256), 0, st, a);
-  }
+  // Few work-groups of four waves (W: their number): fewer keys per work-group and several groups of waves on its
+  // query rows, as in the forward (same sweep, forward + backward, us: W = 8: 29.4 -> 26.2; 96: 49.4 -> 44.9;
+  // 252 causal: 104 -> 98).  Heads of 128 leave no registers for it.
+  const int64_t W = (int64_t)d.B * d.Z * ((d.L + 127) / 128);
+  if (d.A == 128) launch_dkdv<2, 2, 4, 1>(d, a, splits, st);
+  else if (splits > 1 || W > (d.causal ? 256 : 128)) launch_dkdv<2, 1, 4, 1>(d, a, splits, st);
+  else if (W <= 32) launch_dkdv<1, 1, 1, 4>(d, a, 1, st);
+  else if (W <= 128) launch_dkdv<1, 1, 2, 4>(d, a, 1, st);
+  else launch_dkdv<1, 1, 2, 2>(d, a, 1, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   const int64_t n4 = (int64_t)d.B * d.Z * d.L * (d.A / 4);
@@ -680,18 +792,30 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   return hipGetLastError();
 }
 
+template <bool PRE, int AH, int NK, int RW, int KS>
+static void launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
+  a.tiles_per_head = (int)((d.Lq + 32 * RW - 1) / (32 * RW));
+  a.by_length = order_by_length(d, splits);
+  a.half_tiles = d.zigzag && d.c / 2 % (32 * RW) == 0 ? (int)(d.c / 2 / (32 * RW)) : 0;
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * RW * KS);
+  if (d.causal)
+    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+}
+
 template <bool PRE>
-static void launch_dq(const Dims &d, const BwdArgs &a, dim3 grid, hipStream_t st) {
+static void launch_dq(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
+  // (few work-groups: see the dK/dV kernel; W = 8: 29.4 -> 26.3, 96: 49.4 -> 44.1, 252 causal: 104 -> 94; heads
+  // of 128, W = 64 causal: 100 -> 89, 256: 174 -> 162)
+  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
   if (d.A == 128) {  // one key tile (two LDS tiles) per stage
-    if (d.causal)
-      hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, 2, 1>), grid, dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, 2, 1>), grid, dim3(256), 0, st, a);
-  } else if (d.causal) {
-    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, 1, 2>), grid, dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, 1, 2>), grid, dim3(256), 0, st, a);
-  }
+    if (splits > 1 || W > 256) launch_dq_as<PRE, 2, 1, 4, 1>(d, a, splits, st);
+    else if (d.causal || W <= 128) launch_dq_as<PRE, 2, 1, 2, 2>(d, a, 1, st);
+    else launch_dq_as<PRE, 2, 1, 4, 2>(d, a, 1, st);
+  } else if (splits > 1 || W > 256) launch_dq_as<PRE, 1, 2, 4, 1>(d, a, splits, st);
+  else if (W <= 32) launch_dq_as<PRE, 1, 1, 1, 4>(d, a, 1, st);
+  else launch_dq_as<PRE, 1, 1, 2, 2>(d, a, 1, st);
 }
 
 // dQ = sum of the split walks' partial sums
@@ -706,11 +830,9 @@ hipError_t fused_bwd_dq(const Dims &d, const void *dO, const void *Q, const void
                         const float *nL, const float *nD, void *dQ, hipStream_t st, float *part,
                         int splits) {
   BwdArgs a = make_bwd_args(d, dO, Q, K, V, nL, nD, dQ, nullptr, nullptr);
-  a.tiles_per_head = (int)((d.Lq + 127) / 128);
   a.part = part;
   if (!part) splits = 1;
-  dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits);
-  launch_dq<false>(d, a, grid, st);
+  launch_dq<false>(d, a, splits, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   return dq_reduce(d, part, dQ, splits, st);
@@ -722,11 +844,9 @@ hipError_t fused_bwd_dq_pre(const Dims &d, const void *dO, const void *Q, const 
                             hipStream_t st, float *part, int splits) {
   BwdArgs a = make_bwd_args(d, dO, Q, K, V, nullptr, nullptr, dQ, nullptr, nullptr);
   a.O = (const uint16_t *)O; a.LSE = LSE; a.nL_out = nL; a.nD_out = nD;
-  a.tiles_per_head = (int)((d.Lq + 127) / 128);
   a.part = part;
   if (!part) splits = 1;
-  dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits);
-  launch_dq<true>(d, a, grid, st);
+  launch_dq<true>(d, a, splits, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   return dq_reduce(d, part, dQ, splits, st);

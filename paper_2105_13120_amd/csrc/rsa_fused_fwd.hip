@@ -31,30 +31,44 @@ struct FwdArgs {
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q; K and V; O
   RowMap map;            // local query row -> global token index
   int N, Z, tiles_per_head;
+  int by_length, half_tiles;  // causal: order of the row tiles over the work-groups (longest_first)
   float cl2;             // scale * log2(e)
   // split key walk (gridDim.y > 1): per split, head and row the unnormalised fp32 O and the pair
   // (stale max * cl2, row sum) it is relative to
   float *part_o, *part_ml;
 };
 
-template <int R, bool CAUSAL, int AH, int NK>  // NK: key tiles per stage (one barrier per stage)
-__global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) fused_fwd_kernel(FwdArgs a) {
+// NK: key tiles per stage (one barrier per stage).  RW waves share the work-group's rows, R each; KS groups of
+// such waves share its keys: group g takes every KS-th stage of the walk and the groups' results are merged in
+// LDS.
+template <int R, bool CAUSAL, int AH, int NK, int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) fused_fwd_kernel(FwdArgs a) {
   constexpr int QB = R / 32;
-  constexpr int BM = 4 * R;
+  constexpr int BM = RW * R;
   constexpr int A = 64 * AH;
   // The two stage buffers are separate objects, each addressed by name: the compiler then
   // knows that a direct load into one buffer cannot alias the LDS reads of the other and
   // does not wait for the load before them.
-  __shared__ __attribute__((aligned(16))) unsigned char Ks0[NK][AH][kTileBytes], Ks1[NK][AH][kTileBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char Vs0[NK][AH][kTileBytes], Vs1[NK][AH][kTileBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char Ks0[KS][NK][AH][kTileBytes], Ks1[KS][NK][AH][kTileBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char Vs0[KS][NK][AH][kTileBytes], Vs1[KS][NK][AH][kTileBytes];
+
+  // the walk's first maximum per row; every group's maximum and sum
+  __shared__ float ref[KS == 1 ? 1 : RW][64], mls[KS == 1 ? 1 : KS][RW][2][64];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / RW;
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y);
-  const int64_t head = wg / a.tiles_per_head;
-  // under the causal mask later rows see more keys: the long work-groups of a head start first
-  const int64_t qt = CAUSAL ? a.tiles_per_head - 1 - wg % a.tiles_per_head : wg % a.tiles_per_head;
+  uint32_t head_, qt_;
+  if (CAUSAL && a.by_length) {
+    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, qt_);
+    qt_ = row_tile_of_rank(qt_, a.tiles_per_head, a.half_tiles);
+  } else {
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.tiles_per_head;
+    head_ = wg / tiles;
+    qt_ = CAUSAL ? tiles - 1 - wg % tiles : wg % tiles;
+  }
+  const int64_t head = settled(head_), qt = settled(qt_);
   const int64_t row0 = qt * BM;  // first local row of this work-group
   // rank that owns the first row (modulo N: with projected keys, Table 3, the rows are not
   // tokens of the key sequence and any chunk may come first)
@@ -62,7 +76,7 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
   int64_t q_last = 0;
 #pragma unroll
-  for (int i = 0; i < BM / 64; ++i)
+  for (int i = 0; i < (BM + 63) / 64; ++i)
     if (row0 + i * 64 < a.Lq) {
       const int64_t e = a.map(row0 + i * 64) + 63;
       q_last = e > q_last ? e : q_last;
@@ -133,7 +147,7 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
       ks = spc;  // later stages of this chunk start even further right
     }
   };
-  const TileDMA dma(wave, lane, (int)kv_ld);
+  const TileDMAT<RW> dma(wave, lane, (int)kv_ld);
   auto load_stage = [&](int64_t k0, auto &Kn, auto &Vn) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
@@ -147,25 +161,39 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
     }
   };
 
-  int t = f_begin / spc, kt = f_begin % spc;
+  // n stages further on; false past the end
+  auto skip = [&](int &t, int &ks, int n) -> bool {
+    bool h = true;
+    for (int i = 0; i < n && h; ++i) h = advance(t, ks);
+    return h;
+  };
+  int t = f_begin / spc, kt = f_begin % spc;  // position of the walk: group 0's stage
   bool have = f_begin < f_end;
   if (CAUSAL && have && k0_of(t, kt) > q_last) have = advance(t, kt);
-  if (have) load_stage(k0_of(t, kt), Ks0, Vs0);
+  int tg_ = t, kg_ = kt;  // this group's stage
+  int &tg = KS == 1 ? t : tg_, &kg = KS == 1 ? kt : kg_;
+  bool mine = KS == 1 ? have : have && skip(tg, kg, grp);
+  if (mine) load_stage(k0_of(tg, kg), Ks0[grp], Vs0[grp]);
   wait_vmem();
   __syncthreads();
+  bool first = true;
   // one stage: start the loads of the next stage into (Kn, Vn), compute on (Kc, Vc)
   auto stage = [&](auto &Kc, auto &Vc, auto &Kn, auto &Vn) __attribute__((always_inline)) {
-    const int64_t ks0 = k0_of(t, kt);
+    const int64_t ks0 = k0_of(tg, kg);
     int t2 = t, kt2 = kt;
-    const bool have_next = advance(t2, kt2);
-    if (have_next) load_stage(k0_of(t2, kt2), Kn, Vn);
+    const bool have_next = KS == 1 ? advance(t2, kt2) : skip(t2, kt2, KS);
+    int tg2 = t2, kg2 = kt2;
+    const bool mine_next = KS == 1 ? have_next : have_next && skip(tg2, kg2, grp);
+    if (mine_next) load_stage(k0_of(tg2, kg2), Kn, Vn);
 
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
     const int64_t k0 = ks0 + u * kTileKeys;
-    if (u < nk && (!CAUSAL || k0 <= wq_last)) {
+    const bool work = (KS == 1 || mine) && u < nk && (!CAUSAL || k0 <= wq_last);
+    f32x16 s[2][QB];
+    float tm[QB];
+    auto scores = [&]() __attribute__((always_inline)) {
       // ---- S^T = K Q^T
-      f32x16 s[2][QB];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         bf16x8 ka[4 * AH];
@@ -182,20 +210,17 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
       if (CAUSAL && k0 + kTileKeys - 1 > wq_first) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-          // last visible key of the lane's row, relative to the tile (clamped: 32-bit compare)
-          const int64_t d64 = qtok[qb] - k0 - half * 4;
-          const int dlast = d64 > 64 ? 64 : (int)d64;
+          // keys of the tile that the lane's row sees: the first n, less the lane half's offset
+          const int64_t d64 = qtok[qb] + 1 - k0 - half * 4;
+          const int n = d64 > 64 ? 64 : (d64 < 0 ? 0 : (int)d64);
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
+          for (int kb = 0; kb < 2; ++kb) {
+            const uint32_t seen = low_bits(n - kb * 32);
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if (kb * 32 + (v >> 2) * 8 + (v & 3) > dlast) s[kb][qb][v] = -INFINITY;
+            for (int v = 0; v < 16; ++v) s[kb][qb][v] = keep_bit(s[kb][qb][v], seen, (v >> 2) * 8 + (v & 3));
+          }
         }
       }
-      // ---- running max; the accumulators are rescaled only when some row's max
-      // grew by more than 2^8 in the exp2 domain (exact: l and O share the stale max)
-      float tm[QB];
-      bool need = false;
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         float x = s[0][qb][0];
@@ -204,8 +229,14 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
 #pragma unroll
         for (int v = 0; v < 16; ++v) x = fmaxf(x, s[1][qb][v]);
         tm[qb] = xhalf_max(x);
-        need |= (tm[qb] - m[qb]) * a.cl2 > 8.0f;
       }
+    };
+    auto accumulate = [&]() __attribute__((always_inline)) {
+      // ---- running max; the accumulators are rescaled only when some row's max
+      // grew by more than 2^8 in the exp2 domain (exact: l and O share the stale max)
+      bool need = false;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) need |= (tm[qb] - m[qb]) * a.cl2 > 8.0f;
       if (__builtin_amdgcn_ballot_w64(need) != 0) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -253,18 +284,85 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) o[db][qb] = mfma_32x32x16(va, pf[qb][kk], o[db][qb]);
         }
+    };
+    if constexpr (KS == 1) {
+      if (work) { scores(); accumulate(); }
+    } else {
+      if (work) scores();
+      // all groups start from the maximum of the walk's first tile, as one group walking alone would
+      if (first) {
+        if (grp == 0) ref[wave][lane] = work ? tm[0] : -INFINITY;
+        __syncthreads();
+        m[0] = ref[wave][lane];
+        mc[0] = m[0] > -INFINITY ? m[0] * a.cl2 : 0.f;
+        first = false;
+      }
+      if (work) accumulate();
     }
-
     }
 
     wait_vmem();
     __syncthreads();
     t = t2; kt = kt2; have = have_next;
+    if (KS > 1) { tg = tg2; kg = kg2; mine = mine_next; }
   };
   while (have) {
-    stage(Ks0, Vs0, Ks1, Vs1);
+    stage(Ks0[grp], Vs0[grp], Ks1[grp], Vs1[grp]);
     if (!have) break;
-    stage(Ks1, Vs1, Ks0, Vs0);
+    stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
+  }
+
+  if constexpr (KS > 1) {
+    // Groups 1 .. KS - 1 leave their sums in LDS (the stage buffers are free: group g takes one of the four
+    // objects per 64 columns), group 0 brings them to a common maximum and adds them.
+    static_assert(QB == 1, "32 rows per wave");
+    constexpr int PARTS = 2 * AH;  // of 32 columns: 4 KiB per wave
+    auto slot = [&](int g, int part) -> f32x4 * {
+      // PARTS * (KS - 1) slots of RW waves x 4 KiB, dealt to the four objects
+      const int i = (g - 1) * PARTS + part;
+      unsigned char *o = (i & 3) == 0 ? &Ks0[0][0][0][0] : (i & 3) == 1 ? &Ks1[0][0][0][0]
+                         : (i & 3) == 2 ? &Vs0[0][0][0][0] : &Vs1[0][0][0][0];
+      return reinterpret_cast<f32x4 *>(o + ((i >> 2) * RW + wave) * 4096);
+    };
+    static_assert((PARTS * (KS - 1) + 3) / 4 * RW * 4096 <= KS * NK * AH * kTileBytes, "room for a group's sums");
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < PARTS; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          slot(grp, db)[g * 64 + lane] =
+              f32x4{o[db][0][g * 4 + 0], o[db][0][g * 4 + 1], o[db][0][g * 4 + 2], o[db][0][g * 4 + 3]};
+    }
+    mls[grp][wave][0][lane] = m[0];
+    mls[grp][wave][1][lane] = l[0];
+    __syncthreads();
+    if (grp == 0) {
+      float M = m[0];
+#pragma unroll
+      for (int g = 1; g < KS; ++g) M = fmaxf(M, mls[g][wave][0][lane]);
+      const bool seen = M > -INFINITY;
+      const float w0 = seen ? __builtin_amdgcn_exp2f((m[0] - M) * a.cl2) : 0.f;
+      m[0] = M; mc[0] = seen ? M * a.cl2 : 0.f; l[0] *= w0;
+#pragma unroll
+      for (int db = 0; db < PARTS; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][0][v] *= w0;
+#pragma unroll
+      for (int g = 1; g < KS; ++g) {
+        const float w = seen ? __builtin_amdgcn_exp2f((mls[g][wave][0][lane] - M) * a.cl2) : 0.f;
+        l[0] = fmaf(mls[g][wave][1][lane], w, l[0]);
+#pragma unroll
+        for (int db = 0; db < PARTS; ++db)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 x = slot(g, db)[q * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[db][0][q * 4 + e] = fmaf(x[e], w, o[db][0][q * 4 + e]);
+          }
+      }
+    }
+    __syncthreads();  // the epilogue writes to the buffers that the other waves just read
+    if (grp > 0) return;
   }
 
   if (gridDim.y > 1) {  // partial result of this split
@@ -295,7 +393,7 @@ __global__ void __launch_bounds__(256, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) 
   // ---- epilogue: O = O^T / l, LSE = s m + ln l.  The wave's R x 64 block of O goes through its
   // own LDS tile (every wave is past the loop's last barrier and no load is in flight, so the
   // stage buffers are free) and leaves as whole 128-byte rows.
-  unsigned char *ot = wave == 0 ? Ks0[0][0] : (wave == 1 ? Ks1[0][0] : (wave == 2 ? Vs0[0][0] : Vs1[0][0]));
+  unsigned char *ot = wave == 0 ? Ks0[0][0][0] : (wave == 1 ? Ks1[0][0][0] : (wave == 2 ? Vs0[0][0][0] : Vs1[0][0][0]));
   float inv[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
@@ -343,14 +441,23 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
   if (sub == 0) LSE[row] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
-template <int R, int AH, int NK>
-static hipError_t launch_fwd(const Dims &d, const FwdArgs &a, int64_t heads, int splits, hipStream_t st) {
+template <int R, int AH, int NK, int RW, int KS>
+static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
+  a.tiles_per_head = (int)((d.Lq + RW * R - 1) / (RW * R));
+  a.by_length = order_by_length(d, splits);
+  a.half_tiles = d.zigzag && d.c / 2 % (RW * R) == 0 ? (int)(d.c / 2 / (RW * R)) : 0;
   dim3 grid((unsigned)(heads * a.tiles_per_head), (unsigned)splits);
   if (d.causal)
-    hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
   else
-    hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
   return hipGetLastError();
+}
+
+// Whether a causal launch hands out its tiles by length (longest_first): when they differ by more than a
+// factor of two, and the walk is not split (splits turn the ranges over the XCDs instead, see xcd_remap).
+bool order_by_length(const Dims &d, int splits) {
+  return d.causal && splits == 1 && (d.zigzag || 2 * d.rank_begin < d.rank_end);
 }
 
 // Splits of the key walk for a kernel whose work-groups own `rows_per_wg` query rows (two
@@ -411,10 +518,25 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   const int64_t rows = heads * d.Lq;
   a.part_o = part;
   a.part_ml = part ? part + (int64_t)splits * rows * d.A : nullptr;
-  a.tiles_per_head = big ? (int)(d.Lq / 256) : (int)((d.Lq + 127) / 128);
-  hipError_t e = d.A == 128 ? launch_fwd<32, 2, 1>(d, a, heads, splits, st)
-                 : big      ? launch_fwd<64, 1, 2>(d, a, heads, splits, st)
-                            : launch_fwd<32, 1, 1>(d, a, heads, splits, st);
+  // Few work-groups of four waves (W: their number): the chip is not full, and a work-group's walk is a serial chain.
+  // Then fewer rows per work-group and several groups of waves on its keys (RW, KS in the kernel): the chain
+  // shortens, at more tile loads per flop.  The lines are those of a sweep over B Z = 1 .. 192, L = 192 .. 8192 (us,
+  // four waves -> chosen): W = 8: 9.5 -> 7.1; 96: 15.8 -> 11.2; 192 causal: 39 -> 26; 252 causal: 33 -> 26;
+  // 512 causal: 41 -> 36.
+  const int64_t W = heads * ((d.Lq + 127) / 128), walk = d.L / 64;
+  const bool c = d.causal;
+  hipError_t e;
+  if (big) e = launch_fwd<64, 1, 2, 4, 1>(d, a, heads, splits, st);
+  else if (d.A == 128) {
+    if (splits > 1 || W > (c ? 512 : 256)) e = launch_fwd<32, 2, 1, 4, 1>(d, a, heads, splits, st);
+    else if (W > 128) e = launch_fwd<32, 2, 1, 4, 2>(d, a, heads, 1, st);
+    else e = launch_fwd<32, 2, 1, 2, 2>(d, a, heads, 1, st);
+  } else if (splits > 1 || W > (c ? 576 : 256)) e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, splits, st);
+  else if (W <= 32) e = launch_fwd<32, 1, 1, 1, 4>(d, a, heads, 1, st);
+  else if (W <= (c ? 192 : 128)) e = launch_fwd<32, 1, 1, 2, 4>(d, a, heads, 1, st);
+  else if (c && W <= 256) e = launch_fwd<32, 1, 1, 2, 2>(d, a, heads, 1, st);
+  else if (c || walk >= 16) e = launch_fwd<32, 1, 1, 4, 2>(d, a, heads, 1, st);
+  else e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, 1, st);
   if (e != hipSuccess || splits == 1) return e;
   const OutLayout lay = make_out_layout(d.os, d.Lq, d.Z);
   hipLaunchKernelGGL(fwd_combine_kernel, dim3((unsigned)((rows * (d.A / 4) + 255) / 256)), dim3(256), 0, st,

@@ -110,11 +110,12 @@ def _check(status):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle: building a torch Stream object for it costs as much as launching a kernel
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _dtype_code(t):
@@ -154,9 +155,9 @@ def workspace_bytes(desc, backward):
 
 
 def _workspace(desc, backward, device):
+    """(tensor or None, bytes): nothing is allocated where nothing is needed."""
     n = workspace_bytes(desc, backward)
-    ws = torch.empty(max(n, 16), dtype=torch.uint8, device=device)
-    return ws, n
+    return (torch.empty(n, dtype=torch.uint8, device=device) if n else None), n
 
 
 def forward(desc, Q, K, V, O=None, LSE=None, ws=None):
@@ -166,7 +167,7 @@ def forward(desc, Q, K, V, O=None, LSE=None, ws=None):
     if O is None:
         O = torch.empty_like(Q)
     if LSE is None:
-        LSE = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
+        LSE = Q.new_empty(Q.shape[:3], dtype=torch.float32)
     if ws is None:
         ws, n = _workspace(desc, False, Q.device)
     else:
@@ -350,8 +351,10 @@ def linformer_backward(desc, dO, Q, Kp_, Vp_, O, LSE, dQ=None, dKp=None, dVp=Non
 
 def linformer_project_bwd(desc, dXp, X, E, dX=None, dE=None):
     """dX (rows of the descriptor's ranks; a new tensor is zero elsewhere) and dE (fp32, same)."""
-    dX = torch.zeros_like(X) if dX is None else dX
-    dE = torch.zeros(E.shape, dtype=torch.float32, device=E.device) if dE is None else dE
+    # with all ranks every row is written: zeroing both first costs as much as a fifth of the kernels' traffic
+    new = torch.empty_like if (desc.rank_begin, desc.rank_end) == (0, desc.N) else torch.zeros_like
+    dX = new(X) if dX is None else dX
+    dE = new(E, dtype=torch.float32, memory_format=torch.contiguous_format) if dE is None else dE
     _check(lib().rsa_linformer_project_bwd(ctypes.byref(desc), E.shape[1], _p(dXp), _p(X), _p(E), _p(dX),
                                            _p(dE), _stream()))
     return dX, dE
