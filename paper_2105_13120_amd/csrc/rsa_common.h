@@ -169,7 +169,8 @@ struct Dims {
 // Element offset of row 0 of flat head index head = b * Z + z in a tensor whose batch, head and
 // row strides are st[0], st[1], st[2].
 __host__ __device__ inline int64_t head_offset(int64_t head, int Z, const int64_t *st) {
-  return (head / Z) * st[0] + (head % Z) * st[1];
+  const uint32_t h = (uint32_t)head, b = h / (uint32_t)Z;  // (32 bits: a 64-bit division is a hundred instructions)
+  return (int64_t)b * st[0] + (int64_t)(h - b * (uint32_t)Z) * st[1];
 }
 
 // Where a row of a strided output tensor lives, for kernels that walk (head, row) pairs flat:
@@ -178,7 +179,8 @@ struct OutLayout {
   int64_t st[3], rows_per_head;
   int Z;
   __host__ __device__ int64_t row_off(int64_t flat_row) const {
-    return head_offset(flat_row / rows_per_head, Z, st) + (flat_row % rows_per_head) * st[2];
+    const uint32_t r = (uint32_t)flat_row, n = (uint32_t)rows_per_head, h = r / n;
+    return head_offset(h, Z, st) + (int64_t)(r - h * n) * st[2];
   }
 };
 inline OutLayout make_out_layout(const int64_t *st, int64_t rows_per_head, int Z) {
@@ -199,7 +201,10 @@ struct RowMap {
   int zigzag;
   __host__ __device__ int64_t operator()(int64_t r) const {
     if (!zigzag) return q0 + r;
-    const int64_t rho = rb + r / c, w = r % c;
+    // (32-bit division: rows are counted in memory that holds far fewer than 2^32 of them, and a uniform
+    // 64-bit division is a hundred scalar instructions)
+    const uint32_t q = (uint32_t)r / (uint32_t)c;
+    const int64_t rho = rb + (int64_t)q, w = r - (int64_t)q * c;
     return w < h ? rho * h + w : (last_half - rho) * h + (w - h);
   }
   // first key of the rows [w, ...) of the chunk (pair of half-chunks) that rank j owns
@@ -209,8 +214,8 @@ struct RowMap {
   }
   // rank that owns global token g
   __host__ __device__ int owner(int64_t g) const {
-    if (!zigzag) return (int)(g / c);
-    const int hc = (int)(g / h);
+    if (!zigzag) return (int)((uint32_t)g / (uint32_t)c);
+    const int hc = (int)((uint32_t)g / (uint32_t)h);
     return hc <= last_half / 2 ? hc : last_half - hc;
   }
 };

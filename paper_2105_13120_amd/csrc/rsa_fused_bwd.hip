@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   }
   const int64_t head = settled(head_), qt = settled(qt_);
   const int64_t row0 = qt * BM;
-  const int n = (a.map.rb + (int)(row0 / a.c)) % a.N;  // rank that owns the first row (see the forward)
+  const int n = (a.map.rb + (int)((uint32_t)row0 / (uint32_t)a.c)) % a.N;  // rank that owns the first row (see the forward)
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
   int64_t q_last = 0;
 #pragma unroll
@@ -709,8 +709,8 @@ __global__ void __launch_bounds__(256) qsplit_reduce_kernel(const float *part, u
   f32x4 s = reinterpret_cast<const f32x4 *>(part)[i];
   for (int k = 1; k < splits; ++k) s += reinterpret_cast<const f32x4 *>(part)[(int64_t)k * n4 + i];
   const u32x2 w = {pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
-  const int64_t e = i * 4;
-  *reinterpret_cast<u32x2 *>(out + lay.row_off(e / A) + e % A) = w;
+  const int64_t e = i * 4;  // (A is 64 or 128)
+  *reinterpret_cast<u32x2 *>(out + lay.row_off(e >> (A == 64 ? 6 : 7)) + (e & (A - 1))) = w;
 }
 
 static BwdArgs make_bwd_args(const Dims &d, const void *dO, const void *Q, const void *K,

@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   const int64_t row0 = qt * BM;  // first local row of this work-group
   // rank that owns the first row (modulo N: with projected keys, Table 3, the rows are not
   // tokens of the key sequence and any chunk may come first)
-  const int n = (a.map.rb + (int)(row0 / a.c)) % a.N;
+  const int n = (a.map.rb + (int)((uint32_t)row0 / (uint32_t)a.c)) % a.N;
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
   int64_t q_last = 0;
 #pragma unroll
@@ -418,9 +418,9 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
                                                           uint16_t *O, float *LSE, int64_t rows, int splits,
                                                           int A, OutLayout lay) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int lanes = A >> 2;
-  const int64_t row = gid / lanes;
-  const int sub = (int)(gid % lanes);
+  const int lg = A == 64 ? 4 : 5;  // A / 4 lanes per row
+  const int64_t row = gid >> lg;
+  const int sub = (int)gid & ((1 << lg) - 1);
   if (row >= rows) return;
   float M = -INFINITY;
   for (int s = 0; s < splits; ++s) M = fmaxf(M, part_ml[((int64_t)s * rows + row) * 2]);
