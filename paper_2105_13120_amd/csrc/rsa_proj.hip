@@ -8,8 +8,7 @@
 // re-laid out in memory.
 //
 // Work-group: 256 x 256 outputs, 8 waves of 128 x 64 (4 x 2 MFMA blocks of 32 x 32), k in slabs
-// of 64 through the swizzled LDS tiles of the attention kernels, double-buffered, one barrier
-// per slab.  The product is formed transposed (accumulator rows = n, columns = m): a lane then
+// of 32 through a ring of four LDS buffers, one barrier per slab.  The product is formed transposed (accumulator rows = n, columns = m): a lane then
 // owns one output row m and four consecutive n per register group; bf16 blocks leave through
 // LDS as whole 128-byte row segments, fp32 blocks as 16-byte pieces.
 #include "rsa_fused_tile.h"
@@ -125,60 +124,105 @@ struct GemmArgs {
 // A_KROWS / B_KROWS: the operand's tiles hold k along their rows (the view is [K][M] or [K][N])
 // instead of along their columns ([M][K], [N][K]).
 // Work-group: 8 waves, 256 (m) x 256 (n) outputs; wave (wm, wn) of a 2 x 4 grid owns 128 x 64
-// (4 x 2 MFMA blocks).  The tile is this large because a CU takes at most about 40 bytes per clock
-// from global memory (measured, L2-resident data): a 128 x 128 tile needs 32 KiB per 512 matrix-pipe
-// cycles and is bound by that at 30 % of the peak; this one needs 64 KiB per 2048.
-// A slab of 64 k is 8 tiles = 64 KiB; the next slab is fetched into registers (8 x 16 bytes per
-// lane) while the current one is used from LDS, then written to the other LDS buffer: one barrier
-// per slab.  (Direct global->LDS loads would save the registers, but the compiler only lets LDS
-// reads pass outstanding direct loads when the buffers are distinct objects, i.e. with two copies
-// of the loop body, and two copies of a body with 128 accumulator registers do not agree on
-// where the accumulators live.)
+// (4 x 2 MFMA blocks).  The tile is this large because a CU takes at most about 40 bytes per clock from global
+// memory (measured, L2-resident data): a 128 x 128 tile needs 32 KiB per 512 matrix-pipe
+// cycles and is bound by that at 30 % of the peak; this one needs 32 KiB per 1024.
+// k goes in slabs of 32: 8 half tiles = 32 KiB, one half tile per wave, by direct global->LDS loads into a ring of
+// four buffers, three slabs ahead of their use (a slab takes 1600 cycles to arrive and 1024 to use: the former
+// version, slabs of 64 one ahead through registers, waited 39 % of its time for them).
 constexpr int kGemmBM = 256, kGemmBN = 256;
+constexpr int kHalfBytes = kTileBytes / 2;
+
+// A half tile in LDS.  k along rows: 32 rows of 128 bytes, as the upper half of a tile.  k along columns: 64 rows
+// (m or n) of 32 k = 64 bytes, the row's four 16-byte chunks permuted by c ^ ((row >> 2) & 3), so that the 16 rows
+// of a phase of an operand read (four rows make 256 bytes) touch all banks once.
+struct HalfLanes {
+  int rows_off[2];     // [kk]: operand of rows 0 .. 31, slice kk
+  int cols_off[2][2];  // as TileLanes
+  __device__ __forceinline__ explicit HalfLanes(int lane) {
+    const int col = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) rows_off[kk] = col * 64 + (((kk * 2 + half) ^ ((col >> 2) & 3)) << 4);
+    const TileLanes tl(lane);
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) cols_off[db][e] = tl.cols_off[db][e];
+  }
+  __device__ __forceinline__ bf16x8 read_rows(const unsigned char *t, int row_base, int kk) const {
+    return *reinterpret_cast<const bf16x8 *>(t + row_base * 64 + rows_off[kk]);
+  }
+  // a row fragment's k into the order read_cols delivers it (see TileLanes::read_rows_perm)
+  static __device__ __forceinline__ bf16x8 perm(bf16x8 x) {
+    u32x4 w = __builtin_bit_cast(u32x4, x);
+    uint32_t lo0 = w[0], lo1 = w[1], hi0 = w[2], hi1 = w[3];
+    permlane32_swap(lo0, hi0);
+    permlane32_swap(lo1, hi1);
+    const u32x4 r = {lo0, lo1, hi0, hi1};
+    return __builtin_bit_cast(bf16x8, r);
+  }
+  __device__ __forceinline__ bf16x8 read_cols(const unsigned char *t, int kk, int db) const {
+    const u32x2 lo = lds_read_tr16(t + kk * 2048 + cols_off[db][0]);
+    const u32x2 hi = lds_read_tr16(t + kk * 2048 + cols_off[db][1]);
+    const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
+    return __builtin_bit_cast(bf16x8, w);
+  }
+};
+
+// A direct global->LDS load (16 bytes per lane, landing at lds_base + 16 lane) that the compiler does not see: it
+// would wait for every such load in flight before the next LDS read, since the ring's buffers are one object.
+// The kernel orders them itself (wait_loads before the barrier that publishes them).
+__device__ __forceinline__ void lds_dma16_unseen(const void *g, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_base) : "m0");
+}
+template <int N> __device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" : : : "memory"); }
+
 // WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE>
-__global__ void __launch_bounds__(512, 1) proj_gemm_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2][8][kTileBytes];  // [buffer][A0..A3, B0..B3]
+__global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[4][8][kHalfBytes];  // [buffer][A0..A3, B0..B3]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int col = lane & 31, half = lane >> 5;
   const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t m0 = (int64_t)(wg / g.ntiles) * kGemmBM, n0 = (int64_t)(wg % g.ntiles) * kGemmBN;
-  const int64_t mt_last = g.M / 64 - 1, nt_last = g.N / 64 - 1;
+  const int64_t m0 = (int64_t)(wg / (uint32_t)g.ntiles) * kGemmBM, n0 = (int64_t)(wg % (uint32_t)g.ntiles) * kGemmBN;
   const int64_t ks_begin = (int64_t)blockIdx.y * g.kslabs;
   int64_t ks_end = ks_begin + g.kslabs;
   if (ks_end > g.K / 64) ks_end = g.K / 64;
+  const int ns = ks_end > ks_begin ? (int)(ks_end - ks_begin) * 2 : 0;  // slabs of 32
 
-  const TileLanes tl(lane);
-  const ViewWalk wa(g.A, A_KROWS), wb(g.B, B_KROWS);
-  // (a ragged edge refetches the last tile; its outputs are never stored)
-  auto mt_of = [&](int t) { const int64_t mt = m0 / 64 + t; return mt > mt_last ? mt_last : mt; };
-  auto nt_of = [&](int t) { const int64_t nt = n0 / 64 + t; return nt > nt_last ? nt_last : nt; };
-  TileCursor ca[4] = {TileCursor(g.A, A_KROWS, mt_of(0), ks_begin), TileCursor(g.A, A_KROWS, mt_of(1), ks_begin),
-                      TileCursor(g.A, A_KROWS, mt_of(2), ks_begin), TileCursor(g.A, A_KROWS, mt_of(3), ks_begin)};
-  TileCursor cb[4] = {TileCursor(g.B, B_KROWS, nt_of(0), ks_begin), TileCursor(g.B, B_KROWS, nt_of(1), ks_begin),
-                      TileCursor(g.B, B_KROWS, nt_of(2), ks_begin), TileCursor(g.B, B_KROWS, nt_of(3), ks_begin)};
-  // this thread's 16-byte piece of every tile: row tid / 8, logical chunk tid % 8
-  const int prow = tid >> 3, pcc = tid & 7;
-  const int64_t ga_off = prow * wa.ld + pcc * 8, gb_off = prow * wb.ld + pcc * 8;
-  const int l_off = tile_off(prow, pcc);
-  u32x4 stg[8];
-  // (loads through global-address-space pointers: a flat load would also count as an LDS
-  // operation and every wait for an LDS read would then wait for the slab in flight)
-  typedef __attribute__((address_space(1))) const u32x4 *gvec_t;
-  auto fetch = [&]() __attribute__((always_inline)) {  // the slab the cursors point at, then move them on
+  // Wave w < 4 brings A's half tile w of every slab, wave w >= 4 B's half tile w - 4.  (A ragged edge refetches the
+  // last tile; its outputs are never stored.)
+  const bool is_b = wave >= 4;
+  const bool krows = is_b ? B_KROWS : A_KROWS;
+  const int64_t edge = (is_b ? g.N : g.M) / 64 - 1, want = (is_b ? n0 : m0) / 64 + (wave & 3);
+  const int64_t tile = want > edge ? edge : want;
+  ViewWalk walk = is_b ? ViewWalk(g.B, B_KROWS) : ViewWalk(g.A, A_KROWS);
+  // (held in scalar registers: reloaded from the kernel arguments inside the loop, they make every wait for an LDS
+  // read wait for all of them, since scalar loads share its counter and return out of order)
+  asm volatile("" : "+s"(walk.step), "+s"(walk.jump1), "+s"(walk.jump2), "+s"(walk.jumpA), "+s"(walk.period),
+                    "+s"(walk.mode), "+s"(walk.Z));
+  TileCursor cur = is_b ? TileCursor(g.B, B_KROWS, tile, ks_begin) : TileCursor(g.A, A_KROWS, tile, ks_begin);
+  const int64_t sub = krows ? 32 * walk.ld : 32;  // from a tile's first slab to its second
+  int g_off[4];  // bytes
 #pragma unroll
-    for (int t = 0; t < 4; ++t) stg[t] = *(gvec_t)(ca[t].ptr + ga_off);
+  for (int j = 0; j < 4; ++j) {
+    const int p = j * 64 + lane, r8 = p >> 3, r4 = p >> 2;
+    const int row = krows ? r8 : r4, cc = krows ? (p & 7) ^ swz_rot(r8) : (p & 3) ^ ((r4 >> 2) & 3);
+    g_off[j] = (row * (int)walk.ld + cc * 8) * 2;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)&lds[0][wave][0];
+  auto issue = [&](int i) __attribute__((always_inline)) {  // slab i (called for 0, 1, 2, ... in turn)
+    const char *src = reinterpret_cast<const char *>(cur.ptr + ((i & 1) ? sub : 0));
+    const uint32_t dst = lds0 + (uint32_t)(i & 3) * (8 * kHalfBytes);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) stg[4 + t] = *(gvec_t)(cb[t].ptr + gb_off);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) { ca[t].template advance<WIDE>(wa); cb[t].template advance<WIDE>(wb); }
-  };
-  auto put = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) *reinterpret_cast<u32x4 *>(lds[buf][t] + l_off) = stg[t];
+    for (int j = 0; j < 4; ++j) lds_dma16_unseen(src + g_off[j], dst + j * 1024);
+    if (i & 1) cur.template advance<WIDE>(walk);
   };
 
   f32x16 acc[2][4];  // [nb][mb]: rows n, columns m
@@ -189,53 +233,72 @@ __global__ void __launch_bounds__(512, 1) proj_gemm_kernel(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
 
-  int buf = 0;
-  if (ks_begin < ks_end) {  // uniform over the work-group
-    fetch();
-    put(0);
-  }
-  __syncthreads();
-  for (int64_t ks = ks_begin; ks < ks_end; ++ks) {
-    const bool more = ks + 1 < ks_end;
-    if (more) fetch();
-    const unsigned char(*sc)[kTileBytes] = lds[buf];
-    // the fragments of k-slice kk + 1 are read while the MFMAs of slice kk run
-    bf16x8 af[2][4], bf[2][2];
-    auto frags = [&](int kk, bf16x8(&a4)[4], bf16x8(&b2)[2]) __attribute__((always_inline)) {
+  const HalfLanes hl(lane);
+  bf16x8 af[2][4], bf[2][2];
+  auto frags = [&](int i, int kk) __attribute__((always_inline)) {  // operands of slice kk of slab i
+    const unsigned char(*sc)[kHalfBytes] = lds[i & 3];
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const unsigned char *ta = sc[wm * 2 + (mb >> 1)];
-        a4[mb] = A_KROWS ? tl.read_cols(ta, kk * 16, mb & 1)
-                         : (B_KROWS ? tl.read_rows_perm(ta, (mb & 1) * 32, kk) : tl.read_rows(ta, (mb & 1) * 32, kk));
-      }
+    for (int mb = 0; mb < 4; ++mb) {
+      const unsigned char *ta = sc[wm * 2 + (mb >> 1)];
+      af[kk][mb] = A_KROWS ? hl.read_cols(ta, kk, mb & 1) : hl.read_rows(ta, (mb & 1) * 32, kk);
+    }
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        const unsigned char *tb = sc[4 + wn];
-        b2[nb] = B_KROWS ? tl.read_cols(tb, kk * 16, nb)
-                         : (A_KROWS ? tl.read_rows_perm(tb, nb * 32, kk) : tl.read_rows(tb, nb * 32, kk));
-      }
-    };
-    frags(0, af[0], bf[0]);
+    for (int nb = 0; nb < 2; ++nb) {
+      const unsigned char *tb = sc[4 + wn];
+      bf[kk][nb] = B_KROWS ? hl.read_cols(tb, kk, nb) : hl.read_rows(tb, nb * 32, kk);
+    }
+  };
+  auto products = [&](int kk) __attribute__((always_inline)) {
+    if (A_KROWS != B_KROWS) {  // the row-read side takes its k in the other's order
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk < 3) frags(kk + 1, af[(kk + 1) & 1], bf[(kk + 1) & 1]);
+      for (int mb = 0; mb < 4; ++mb)
+        if (!A_KROWS) af[kk][mb] = HalfLanes::perm(af[kk][mb]);
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-          acc[nb][mb] = mfma_32x32x16(bf[kk & 1][nb], af[kk & 1][mb], acc[nb][mb]);
-      __builtin_amdgcn_sched_barrier(0);  // keep the slices in this order
+        if (!B_KROWS) bf[kk][nb] = HalfLanes::perm(bf[kk][nb]);
     }
-    if (more) put(buf ^ 1);  // last read one slab ago, before the barrier that ended it
-    __syncthreads();
-    buf ^= 1;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = mfma_32x32x16(bf[kk][nb], af[kk][mb], acc[nb][mb]);
+  };
+
+  if (ns > 0) {  // uniform over the work-group; ns is even
+    issue(0);
+    issue(1);
+    if (ns > 2) {
+      issue(2);
+      wait_loads<8>();
+    } else {
+      wait_loads<4>();
+    }
+    barrier_only();
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): no scalar load is pending in the loop (see above)
+    frags(0, 0);
+    for (int i = 0; i < ns; ++i) {
+      // slab i + 1 has arrived (slab i + 2 may be in flight), and behind the barrier every wave is done with slab
+      // i - 1, whose buffer takes slab i + 3
+      if (i + 2 < ns) wait_loads<4>();
+      else wait_loads<0>();
+      barrier_only();
+      if (i + 3 < ns) issue(i + 3);
+      frags(i, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      products(0);
+      __builtin_amdgcn_sched_barrier(0);
+      frags(i + 1, 0);  // (past the last slab: some buffer's contents, not used)
+      __builtin_amdgcn_sched_barrier(0);
+      products(1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+  __syncthreads();
 
   // lane (col, half) holds, for output row m, the columns n = nb*32 + grp*8 + half*4 .. +4
   if (!OUT_F32) {
     // bf16: the wave's 128 x 64 block goes through two LDS tiles of its own (every wave is past
     // the loop's last barrier) and leaves as whole 128-byte row segments.
-    unsigned char *t0 = lds[0][wave], *t1 = lds[1][wave];
+    unsigned char *t0 = &lds[0][0][0] + wave * (2 * kTileBytes), *t1 = t0 + kTileBytes;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) stage_block_T(mb < 2 ? t0 : t1, (mb & 1) * 32, acc[0][mb], acc[1][mb], 1.0f, lane);
     const int64_t nw = n0 + wn * 64;  // the block's 64 columns: (half of) one head of a head-split output
