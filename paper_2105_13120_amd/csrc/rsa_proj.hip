@@ -138,29 +138,23 @@ constexpr int kHalfBytes = kTileBytes / 2;
 // of a phase of an operand read (four rows make 256 bytes) touch all banks once.
 struct HalfLanes {
   int rows_off[2];     // [kk]: operand of rows 0 .. 31, slice kk
-  int cols_off[2][2];  // as TileLanes
+  int cols_off[2][2];  // [db][e]: operand of columns 32 db .. 32 db + 31
   __device__ __forceinline__ explicit HalfLanes(int lane) {
     const int col = lane & 31, half = lane >> 5;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) rows_off[kk] = col * 64 + (((kk * 2 + half) ^ ((col >> 2) & 3)) << 4);
-    const TileLanes tl(lane);
+    const int g = lane >> 4, j = lane & 15;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) cols_off[db][e] = tl.cols_off[db][e];
+      for (int e = 0; e < 2; ++e)
+        cols_off[db][e] = tile_off(half * 8 + e * 4 + (j >> 2), db * 4 + (g & 1) * 2 + ((j >> 1) & 1)) + (j & 1) * 8;
   }
   __device__ __forceinline__ bf16x8 read_rows(const unsigned char *t, int row_base, int kk) const {
     return *reinterpret_cast<const bf16x8 *>(t + row_base * 64 + rows_off[kk]);
   }
-  // a row fragment's k into the order read_cols delivers it (see TileLanes::read_rows_perm)
-  static __device__ __forceinline__ bf16x8 perm(bf16x8 x) {
-    u32x4 w = __builtin_bit_cast(u32x4, x);
-    uint32_t lo0 = w[0], lo1 = w[1], hi0 = w[2], hi1 = w[3];
-    permlane32_swap(lo0, hi0);
-    permlane32_swap(lo1, hi1);
-    const u32x4 r = {lo0, lo1, hi0, hi1};
-    return __builtin_bit_cast(bf16x8, r);
-  }
+  // By transpose reads, k of slice kk in the order of read_rows: 16 kk + 8 half + e in element e.  (Unlike
+  // TileLanes::read_cols, which takes k in the order of an accumulator's rows.)
   __device__ __forceinline__ bf16x8 read_cols(const unsigned char *t, int kk, int db) const {
     const u32x2 lo = lds_read_tr16(t + kk * 2048 + cols_off[db][0]);
     const u32x2 hi = lds_read_tr16(t + kk * 2048 + cols_off[db][1]);
@@ -172,8 +166,9 @@ struct HalfLanes {
 // A direct global->LDS load (16 bytes per lane, landing at lds_base + 16 lane) that the compiler does not see: it
 // would wait for every such load in flight before the next LDS read, since the ring's buffers are one object.
 // The kernel orders them itself (wait_loads before the barrier that publishes them).
-__device__ __forceinline__ void lds_dma16_unseen(const void *g, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_base) : "m0");
+__device__ __forceinline__ void lds_dma16_unseen(const void *g, int lane_off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               : : "v"(lane_off), "s"(g), "s"(lds_base) : "m0");
 }
 template <int N> __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
@@ -218,10 +213,10 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)&lds[0][wave][0];
   auto issue = [&](int i) __attribute__((always_inline)) {  // slab i (called for 0, 1, 2, ... in turn)
-    const char *src = reinterpret_cast<const char *>(cur.ptr + ((i & 1) ? sub : 0));
+    const void *src = cur.ptr + ((i & 1) ? sub : 0);
     const uint32_t dst = lds0 + (uint32_t)(i & 3) * (8 * kHalfBytes);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) lds_dma16_unseen(src + g_off[j], dst + j * 1024);
+    for (int j = 0; j < 4; ++j) lds_dma16_unseen(src, g_off[j], dst + j * 1024);
     if (i & 1) cur.template advance<WIDE>(walk);
   };
 
@@ -249,18 +244,21 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
     }
   };
   auto products = [&](int kk) __attribute__((always_inline)) {
-    if (A_KROWS != B_KROWS) {  // the row-read side takes its k in the other's order
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        if (!A_KROWS) af[kk][mb] = HalfLanes::perm(af[kk][mb]);
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        if (!B_KROWS) bf[kk][nb] = HalfLanes::perm(bf[kk][nb]);
-    }
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = mfma_32x32x16(bf[kk][nb], af[kk][mb], acc[nb][mb]);
+  };
+
+  // the next slice's reads beside the first MFMAs of this one, so that the last four cover their latency
+  auto interleave = [&]() __attribute__((always_inline)) {
+    constexpr int kReads = (A_KROWS ? 8 : 4) + (B_KROWS ? 4 : 2), kPer = (kReads + 3) / 4;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
   };
 
   if (ns > 0) {  // uniform over the work-group; ns is even
@@ -283,12 +281,12 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
       barrier_only();
       if (i + 3 < ns) issue(i + 3);
       frags(i, 1);
-      __builtin_amdgcn_sched_barrier(0);
       products(0);
+      interleave();
       __builtin_amdgcn_sched_barrier(0);
       frags(i + 1, 0);  // (past the last slab: some buffer's contents, not used)
-      __builtin_amdgcn_sched_barrier(0);
       products(1);
+      interleave();
       __builtin_amdgcn_sched_barrier(0);
     }
   }
