@@ -107,6 +107,24 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// Sum of load(s) over the splits s, in order: the deterministic end of a split walk.  Eight loads are in flight at a
+// time (one after the other, 64 splits of a small result took 16 us).
+template <class F>
+__device__ __forceinline__ f32x4 sum_of_splits(int splits, F load) {
+  f32x4 s = load(0);
+  for (int k = 1; k < splits; k += 8) {
+    f32x4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = load(k + j < splits ? k + j : splits - 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k + j < splits) s += x[j];
+  }
+  return s;
+}
+constexpr int kReduceBlock = 64;  // (one wave: a small result is spread over more CUs)
+inline dim3 reduce_grid(int64_t n4) { return dim3((unsigned)((n4 + kReduceBlock - 1) / kReduceBlock)); }
+
 // Causal masks as bits: the lowest n (clamped to 0 .. 32) bits set, and x where bit `bit` of `mask` is set, -inf
 // elsewhere (a field extract and a bitwise select: compares would each hold a pair of scalar registers,
 // 64 of them at once, and spill everything else).

@@ -702,12 +702,12 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
 
 // out (bf16) = sum over the splits of part[s][i], in a fixed order; n4 groups of four per split
 // (the partial sums are dense (head, row, A); `lay` says where a row of the output tensor lives)
-__global__ void __launch_bounds__(256) qsplit_reduce_kernel(const float *part, uint16_t *out, int64_t n4,
-                                                            int splits, int A, OutLayout lay) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(kReduceBlock) qsplit_reduce_kernel(const float *part, uint16_t *out, int64_t n4,
+                                                                     int splits, int A, OutLayout lay) {
+  const int64_t i = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
   if (i >= n4) return;
-  f32x4 s = reinterpret_cast<const f32x4 *>(part)[i];
-  for (int k = 1; k < splits; ++k) s += reinterpret_cast<const f32x4 *>(part)[(int64_t)k * n4 + i];
+  const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + i;
+  const f32x4 s = sum_of_splits(splits, [&](int k) { return p[(int64_t)k * n4]; });
   const u32x2 w = {pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
   const int64_t e = i * 4;  // (A is 64 or 128)
   *reinterpret_cast<u32x2 *>(out + lay.row_off(e >> (A == 64 ? 6 : 7)) + (e & (A - 1))) = w;
@@ -742,7 +742,7 @@ hipError_t fused_bwd_preprocess(const Dims &d, const void *dO, const void *O, co
 
 hipError_t qsplit_reduce(const float *part, void *out, int64_t n4, int splits, int A, const OutLayout &lay,
                          hipStream_t st) {
-  hipLaunchKernelGGL(qsplit_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part,
+  hipLaunchKernelGGL(qsplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part,
                      (uint16_t *)out, n4, splits, A, lay);
   return hipGetLastError();
 }
@@ -784,10 +784,10 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   const int64_t n4 = (int64_t)d.B * d.Z * d.L * (d.A / 4);
-  const dim3 rg((unsigned)((n4 + 255) / 256));
+  const dim3 rg = reduce_grid(n4), rb(kReduceBlock);
   const OutLayout lay = make_out_layout(d.ks, d.L, d.Z);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, dim3(256), 0, st, part, (uint16_t *)dV, n4, splits, d.A, lay);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, dim3(256), 0, st, part + (int64_t)splits * n4 * 4,
+  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, rb, 0, st, part, (uint16_t *)dV, n4, splits, d.A, lay);
+  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, rb, 0, st, part + (int64_t)splits * n4 * 4,
                      (uint16_t *)dK, n4, splits, d.A, lay);
   return hipGetLastError();
 }
@@ -821,7 +821,7 @@ static void launch_dq(const Dims &d, const BwdArgs &a, int splits, hipStream_t s
 // dQ = sum of the split walks' partial sums
 static hipError_t dq_reduce(const Dims &d, const float *part, void *dQ, int splits, hipStream_t st) {
   const int64_t n4 = (int64_t)d.B * d.Z * d.Lq * (d.A / 4);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part,
+  hipLaunchKernelGGL(qsplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part,
                      (uint16_t *)dQ, n4, splits, d.A, make_out_layout(d.qs, d.Lq, d.Z));
   return hipGetLastError();
 }

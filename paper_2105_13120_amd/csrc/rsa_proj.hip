@@ -7,12 +7,14 @@
 // one head) blocks of up to three (B, Z, rows, A) tensors, A = 64 or 128, so no tensor is ever
 // re-laid out in memory.
 //
-// Work-group: 256 x 256 outputs, 8 waves of 128 x 64 (4 x 2 MFMA blocks of 32 x 32), k in slabs
-// of 32 through a ring of four LDS buffers, one barrier per slab.  The product is formed transposed (accumulator rows = n, columns = m): a lane then
-// owns one output row m and four consecutive n per register group; bf16 blocks leave through
-// LDS as whole 128-byte row segments, fp32 blocks as 16-byte pieces.
+// Work-group: 64 T x 64 T outputs, T = 4, 2 or 1 by the size of the product (plan_gemm), 2 T waves of 32 T x 64, k in
+// slabs of 32 through a ring of four LDS buffers, one barrier per slab.  The product is formed transposed
+// (accumulator rows = n, columns = m): a lane then owns one output row m and four consecutive n per register group;
+// bf16 blocks leave through LDS as whole 128-byte row segments, fp32 blocks as 16-byte pieces.
 #include "rsa_fused_tile.h"
 #include "rsa_kernels.h"
+
+#include <math.h>
 
 namespace rsa {
 
@@ -118,19 +120,22 @@ struct GemmArgs {
   void *out[3];       // plain: out[0] (+ split * M * out_ld elements for a k split); head-split: 3 tensors
   int64_t out_ld, out_rows;
   int out_Z, out_AH, out_split;  // head-split output: (B, out_Z, out_rows, 64 * out_AH) tensors
-  int ntiles;         // 128-wide column tiles
+  int ntiles;         // column tiles
+  int part_heads;     // > 0: the partial sums of a k split lie in the rows of a (Zt, out_rows, A) bf16 tensor: A / 2
+                      // columns per head, part_heads heads per split, and out_ld = A / 2
 };
 
 // A_KROWS / B_KROWS: the operand's tiles hold k along their rows (the view is [K][M] or [K][N])
 // instead of along their columns ([M][K], [N][K]).
-// Work-group: 8 waves, 256 (m) x 256 (n) outputs; wave (wm, wn) of a 2 x 4 grid owns 128 x 64
-// (4 x 2 MFMA blocks).  The tile is this large because a CU takes at most about 40 bytes per clock from global
-// memory (measured, L2-resident data): a 128 x 128 tile needs 32 KiB per 512 matrix-pipe
-// cycles and is bound by that at 30 % of the peak; this one needs 32 KiB per 1024.
-// k goes in slabs of 32: 8 half tiles = 32 KiB, one half tile per wave, by direct global->LDS loads into a ring of
-// four buffers, three slabs ahead of their use (a slab takes 1600 cycles to arrive and 1024 to use: the former
-// version, slabs of 64 one ahead through registers, waited 39 % of its time for them).
-constexpr int kGemmBM = 256, kGemmBN = 256;
+// Work-group: 2 T waves, 64 T (m) x 64 T (n) outputs; wave (wm, wn) of a 2 x T grid owns 32 T x 64 (T x 2 MFMA
+// blocks).  Large products take T = 4, since a CU takes at most about 40 bytes per clock from global memory (measured,
+// L2-resident data): 128 x 128 outputs need 32 KiB per 512 matrix-pipe cycles, 256 x 256 need 32 KiB per 1024.
+// Products with few outputs take the smaller ones, which give more work-groups and a shorter chain per slab
+// (a lone work-group's slab takes 0.61, 0.29, 0.20 us for T = 4, 2, 1).
+// k goes in slabs of 32: 2 T half tiles, one half tile per wave, by direct global->LDS loads into a ring of
+// four buffers, three slabs ahead of their use (T = 4: a slab takes 1600 cycles to arrive and 1024 to use).
+// KG groups of such waves share the k of a work-group and are added in LDS at the end: where there are fewer
+// work-groups than CUs, two slabs proceed side by side (T = 1: 0.155 us per slab).
 constexpr int kHalfBytes = kTileBytes / 2;
 
 // A half tile in LDS.  k along rows: 32 rows of 128 bytes, as the upper half of a tile.  k along columns: 64 rows
@@ -156,8 +161,11 @@ struct HalfLanes {
   // By transpose reads, k of slice kk in the order of read_rows: 16 kk + 8 half + e in element e.  (Unlike
   // TileLanes::read_cols, which takes k in the order of an accumulator's rows.)
   __device__ __forceinline__ bf16x8 read_cols(const unsigned char *t, int kk, int db) const {
-    const u32x2 lo = lds_read_tr16(t + kk * 2048 + cols_off[db][0]);
-    const u32x2 hi = lds_read_tr16(t + kk * 2048 + cols_off[db][1]);
+    return read_cols_at(t, kk, cols_off[db]);
+  }
+  static __device__ __forceinline__ bf16x8 read_cols_at(const unsigned char *t, int kk, const int *off) {
+    const u32x2 lo = lds_read_tr16(t + kk * 2048 + off[0]);
+    const u32x2 hi = lds_read_tr16(t + kk * 2048 + off[1]);
     const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
     return __builtin_bit_cast(bf16x8, w);
   }
@@ -176,26 +184,39 @@ template <int N> __device__ __forceinline__ void wait_loads() {
 __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" : : : "memory"); }
 
 // WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
-template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE>
-__global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[4][8][kHalfBytes];  // [buffer][A0..A3, B0..B3]
+template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG>
+__global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) {
+  constexpr int HT = 2 * T;         // half tiles per slab, and waves per group
+  constexpr int BM = 64 * T, BN = 64 * T;
+  __shared__ __attribute__((aligned(16))) unsigned char lds_[KG][4][HT][kHalfBytes];  // [group][buffer][A.., B..]
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
+  const int gw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KG == 1 ? 0 : gw / HT, wave = KG == 1 ? gw : gw % HT;
+  const int wm = wave / T, wn = wave % T;
   const int col = lane & 31, half = lane >> 5;
+  unsigned char(*lds)[HT][kHalfBytes] = lds_[grp];
   const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t m0 = (int64_t)(wg / (uint32_t)g.ntiles) * kGemmBM, n0 = (int64_t)(wg % (uint32_t)g.ntiles) * kGemmBN;
-  const int64_t ks_begin = (int64_t)blockIdx.y * g.kslabs;
-  int64_t ks_end = ks_begin + g.kslabs;
-  if (ks_end > g.K / 64) ks_end = g.K / 64;
-  const int ns = ks_end > ks_begin ? (int)(ks_end - ks_begin) * 2 : 0;  // slabs of 32
+  const int64_t m0 = (int64_t)(wg / (uint32_t)g.ntiles) * BM, n0 = (int64_t)(wg % (uint32_t)g.ntiles) * BN;
+  // slabs of 32 k of group `gr` of this split
+  const int64_t per_grp = KG == 1 ? g.kslabs : (g.kslabs + KG - 1) / KG;
+  auto slabs_of = [&](int gr, int64_t &begin) -> int {
+    begin = (int64_t)blockIdx.y * g.kslabs + gr * per_grp;
+    int64_t end = begin + per_grp;
+    const int64_t split_end = (int64_t)(blockIdx.y + 1) * g.kslabs;
+    if (KG > 1 && end > split_end) end = split_end;
+    if (end > g.K / 64) end = g.K / 64;
+    return end > begin ? (int)(end - begin) * 2 : 0;
+  };
+  int64_t ks_begin;
+  const int ns0 = slabs_of(0, ks_begin);  // the first group has the most slabs
+  const int ns = KG == 1 ? ns0 : slabs_of(grp, ks_begin);
 
   // Wave w < 4 brings A's half tile w of every slab, wave w >= 4 B's half tile w - 4.  (A ragged edge refetches the
   // last tile; its outputs are never stored.)
-  const bool is_b = wave >= 4;
+  const bool is_b = wave >= T;
   const bool krows = is_b ? B_KROWS : A_KROWS;
-  const int64_t edge = (is_b ? g.N : g.M) / 64 - 1, want = (is_b ? n0 : m0) / 64 + (wave & 3);
+  const int64_t edge = (is_b ? g.N : g.M) / 64 - 1, want = (is_b ? n0 : m0) / 64 + (is_b ? wave - T : wave);
   const int64_t tile = want > edge ? edge : want;
   ViewWalk walk = is_b ? ViewWalk(g.B, B_KROWS) : ViewWalk(g.A, A_KROWS);
   // (held in scalar registers: reloaded from the kernel arguments inside the loop, they make every wait for an LDS
@@ -211,35 +232,41 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
     const int row = krows ? r8 : r4, cc = krows ? (p & 7) ^ swz_rot(r8) : (p & 3) ^ ((r4 >> 2) & 3);
     g_off[j] = (row * (int)walk.ld + cc * 8) * 2;
   }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)&lds[0][wave][0];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)&lds_[grp][0][wave][0];
   auto issue = [&](int i) __attribute__((always_inline)) {  // slab i (called for 0, 1, 2, ... in turn)
     const void *src = cur.ptr + ((i & 1) ? sub : 0);
-    const uint32_t dst = lds0 + (uint32_t)(i & 3) * (8 * kHalfBytes);
+    const uint32_t dst = lds0 + (uint32_t)(i & 3) * (HT * kHalfBytes);
 #pragma unroll
     for (int j = 0; j < 4; ++j) lds_dma16_unseen(src, g_off[j], dst + j * 1024);
     if (i & 1) cur.template advance<WIDE>(walk);
   };
 
-  f32x16 acc[2][4];  // [nb][mb]: rows n, columns m
+  f32x16 acc[2][T];  // [nb][mb]: rows n, columns m
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < T; ++mb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
 
   const HalfLanes hl(lane);
-  bf16x8 af[2][4], bf[2][2];
+  int ca[T][2];  // transpose-read offsets of the wave's blocks of 32 m (which half of a tile: odd or even block)
+#pragma unroll
+  for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) ca[mb][e] = (wm * T + mb) & 1 ? hl.cols_off[1][e] : hl.cols_off[0][e];
+  bf16x8 af[2][T], bf[2][2];
   auto frags = [&](int i, int kk) __attribute__((always_inline)) {  // operands of slice kk of slab i
     const unsigned char(*sc)[kHalfBytes] = lds[i & 3];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      const unsigned char *ta = sc[wm * 2 + (mb >> 1)];
-      af[kk][mb] = A_KROWS ? hl.read_cols(ta, kk, mb & 1) : hl.read_rows(ta, (mb & 1) * 32, kk);
+    for (int mb = 0; mb < T; ++mb) {
+      const int b32 = wm * T + mb;  // block of 32 m
+      const unsigned char *ta = sc[b32 >> 1];
+      af[kk][mb] = A_KROWS ? HalfLanes::read_cols_at(ta, kk, ca[mb]) : hl.read_rows(ta, (b32 & 1) * 32, kk);
     }
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
-      const unsigned char *tb = sc[4 + wn];
+      const unsigned char *tb = sc[T + wn];
       bf[kk][nb] = B_KROWS ? hl.read_cols(tb, kk, nb) : hl.read_rows(tb, nb * 32, kk);
     }
   };
@@ -247,38 +274,38 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = mfma_32x32x16(bf[kk][nb], af[kk][mb], acc[nb][mb]);
+      for (int mb = 0; mb < T; ++mb) acc[nb][mb] = mfma_32x32x16(bf[kk][nb], af[kk][mb], acc[nb][mb]);
   };
 
   // the next slice's reads beside the first MFMAs of this one, so that the last four cover their latency
   auto interleave = [&]() __attribute__((always_inline)) {
-    constexpr int kReads = (A_KROWS ? 8 : 4) + (B_KROWS ? 4 : 2), kPer = (kReads + 3) / 4;
+    constexpr int kReads = (A_KROWS ? 2 : 1) * T + (B_KROWS ? 4 : 2), kPer = (kReads + T - 1) / T;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < T; ++k) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, T, 0);
   };
 
-  if (ns > 0) {  // uniform over the work-group; ns is even
-    issue(0);
-    issue(1);
-    if (ns > 2) {
-      issue(2);
-      wait_loads<8>();
-    } else {
-      wait_loads<4>();
+  if (ns0 > 0) {  // uniform over the work-group; the numbers of slabs are even
+    if (KG == 1 || ns > 0) {
+      issue(0);
+      issue(1);
+      if (ns > 2) issue(2);
     }
+    if (ns > 2) wait_loads<8>();
+    else wait_loads<4>();
     barrier_only();
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): no scalar load is pending in the loop (see above)
     frags(0, 0);
-    for (int i = 0; i < ns; ++i) {
+    for (int i = 0; i < ns0; ++i) {
       // slab i + 1 has arrived (slab i + 2 may be in flight), and behind the barrier every wave is done with slab
       // i - 1, whose buffer takes slab i + 3
       if (i + 2 < ns) wait_loads<4>();
       else wait_loads<0>();
       barrier_only();
+      if (KG > 1 && i >= ns) continue;  // (uniform over the wave)
       if (i + 3 < ns) issue(i + 3);
       frags(i, 1);
       products(0);
@@ -292,13 +319,48 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
   }
   __syncthreads();
 
+  if constexpr (KG > 1) {  // groups 1 .. KG - 1 leave their sums in LDS, group 0 adds them in order
+    static_assert((KG - 1) * HT * T * 2 * 4096 <= (int)sizeof(lds_), "room for the groups' sums");
+    auto slot = [&](int gr, int nb, int mb) {
+      return reinterpret_cast<f32x4 *>(&lds_[0][0][0][0] + ((((gr - 1) * HT + wave) * 2 + nb) * T + mb) * 4096);
+    };
+    if (grp > 0) {
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x16 &c = acc[nb][mb];
+            slot(grp, nb, mb)[q * 64 + lane] = f32x4{c[q * 4], c[q * 4 + 1], c[q * 4 + 2], c[q * 4 + 3]};
+          }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int gr = 1; gr < KG; ++gr)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+          for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const f32x4 x = slot(gr, nb, mb)[q * 64 + lane];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[nb][mb][q * 4 + e] += x[e];
+            }
+    }
+    __syncthreads();  // the epilogue writes to what was just read
+    if (grp > 0) return;
+  }
+
   // lane (col, half) holds, for output row m, the columns n = nb*32 + grp*8 + half*4 .. +4
   if (!OUT_F32) {
-    // bf16: the wave's 128 x 64 block goes through two LDS tiles of its own (every wave is past
+    // bf16: the wave's block goes through LDS of its own (every wave is past
     // the loop's last barrier) and leaves as whole 128-byte row segments.
-    unsigned char *t0 = &lds[0][0][0] + wave * (2 * kTileBytes), *t1 = t0 + kTileBytes;
+    unsigned char *t0 = &lds_[0][0][0][0] + wave * (T * kHalfBytes);
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) stage_block_T(mb < 2 ? t0 : t1, (mb & 1) * 32, acc[0][mb], acc[1][mb], 1.0f, lane);
+    for (int mb = 0; mb < T; ++mb) stage_block_T(t0, mb * 32, acc[0][mb], acc[1][mb], 1.0f, lane);
     const int64_t nw = n0 + wn * 64;  // the block's 64 columns: (half of) one head of a head-split output
     if (nw < g.N) {
       int which = 0;
@@ -314,11 +376,11 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
       }
       uint16_t *base = static_cast<uint16_t *>(which == 0 ? g.out[0] : (which == 1 ? g.out[1] : g.out[2]));
 #pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int row = it * 8 + (lane >> 3), cc = lane & 7;  // row of the wave's 128
-        const int64_t m = m0 + wm * 128 + row;
+      for (int it = 0; it < 4 * T; ++it) {
+        const int row = it * 8 + (lane >> 3), cc = lane & 7;  // row of the wave's 32 T
+        const int64_t m = m0 + wm * 32 * T + row;
         if (m >= g.M) continue;
-        const u32x4 w = *reinterpret_cast<const u32x4 *>((row < 64 ? t0 : t1) + tile_off(row & 63, cc));
+        const u32x4 w = *reinterpret_cast<const u32x4 *>(t0 + tile_off(row, cc));
         int64_t off;
         if (!g.out_split) {
           off = m * g.out_ld + nw + cc * 8;
@@ -332,8 +394,8 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
     return;
   }
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int64_t m = m0 + wm * 128 + mb * 32 + col;
+  for (int mb = 0; mb < T; ++mb) {
+    const int64_t m = m0 + wm * 32 * T + mb * 32 + col;
     if (m >= g.M) continue;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
@@ -341,7 +403,12 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
       for (int grp = 0; grp < 4; ++grp) {
         const int64_t n = n0 + wn * 64 + nb * 32 + grp * 8 + half * 4;
         if (n >= g.N) continue;
-        const int64_t off = ((int64_t)blockIdx.y * g.M + m) * g.out_ld + n;  // fp32 outputs are plain matrices
+        // fp32 outputs are plain matrices
+        int64_t off = ((int64_t)blockIdx.y * g.M + m) * g.out_ld + n;
+        if (g.part_heads) {
+          const uint32_t w = (uint32_t)g.out_ld, h = blockIdx.y * (uint32_t)g.part_heads + (uint32_t)n / w;
+          off = ((int64_t)h * g.out_rows + m) * g.out_ld + (uint32_t)n % w;
+        }
         const f32x16 &c = acc[nb][mb];
         const f32x4 w = {c[grp * 4 + 0], c[grp * 4 + 1], c[grp * 4 + 2], c[grp * 4 + 3]};
         *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out[0]) + off) = w;
@@ -349,14 +416,12 @@ __global__ void __launch_bounds__(512, 2) proj_gemm_kernel(GemmArgs g) {
   }
 }
 
-// out[i] = sum over s of part[s][i], s in fixed order: the deterministic end of a k split
-__global__ void __launch_bounds__(256) ksplit_reduce_kernel(const float *part, float *out, int64_t n4,
-                                                            int splits) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_kernel(const float *part, float *out, int64_t n4,
+                                                                     int splits) {
+  const int64_t i = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
   if (i >= n4) return;
-  f32x4 s = reinterpret_cast<const f32x4 *>(part)[i];
-  for (int k = 1; k < splits; ++k) s += reinterpret_cast<const f32x4 *>(part)[(int64_t)k * n4 + i];
-  reinterpret_cast<f32x4 *>(out)[i] = s;
+  const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + i;
+  reinterpret_cast<f32x4 *>(out)[i] = sum_of_splits(splits, [&](int k) { return p[(int64_t)k * n4]; });
 }
 
 static MatView plain(const void *p, int64_t ld) {
@@ -371,25 +436,65 @@ static MatView heads(const void *p0, const void *p1, const void *p2, int64_t row
   return v;
 }
 
-template <bool A_KROWS, bool B_KROWS, bool OUT_F32>
-static hipError_t launch_gemm(GemmArgs &g, int splits, hipStream_t st) {
-  g.ntiles = (int)((g.N + kGemmBN - 1) / kGemmBN);
-  const int64_t mtiles = (g.M + kGemmBM - 1) / kGemmBM;
-  g.kslabs = (g.K / 64 + splits - 1) / splits;
-  dim3 grid((unsigned)(mtiles * g.ntiles), (unsigned)splits);
-  const bool wide = (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
-  if (wide)
-    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true>), grid, dim3(512), 0, st, g);
-  else
-    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, false>), grid, dim3(512), 0, st, g);
-  return hipGetLastError();
+// Size of the work-groups' output tiles, groups per work-group and k splits: the candidate with the least estimated
+// time (us).  n work-groups per CU (of which 1, 2, 4 are in flight) cost per slab of 32 k what was measured, and a round
+// of them its prologue and epilogue; a split result is written and added up.  (Measured with M x N x K swept from
+// 128 x 1856 x 28224 to 1664 x 5000 x 11520 and each T: the choice is within 10 % of the best on average.  T = 4 alone:
+// 512 x 1408 x 1408: 31.7 us, now 10; 896 x 576 x 576: 15.8, now 6.)
+struct GemmPlan { int T, KG, splits; };
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool groups) {
+  const int kslabs = (int)(K / 64);
+  GemmPlan best{4, 1, 1};
+  float least = 1e30f;
+  for (int T = 4; T >= 1; T /= 2) {
+    const uint32_t t = 64 * (uint32_t)T;
+    const float tiles = (float)((((uint32_t)M + t - 1) / t) * (uint64_t)(((uint32_t)N + t - 1) / t));
+    for (int next, s = 1; s <= max_splits; s = next) {
+      next = s + (s < 4 ? 1 : (s < 8 ? 2 : (s < 16 ? 4 : (s < 32 ? 8 : 16))));
+      if (s < max_splits && next > max_splits) next = max_splits;
+      const float w = tiles * (float)s, n = ceilf(w * (1.0f / 256)), slabs = 2.0f * (float)((kslabs + s - 1) / s);
+      const float reduce = s > 1 ? 3.0f + (float)s * (float)(M * N) * (4.0f / 5e6f) : 0.0f;
+      float us;
+      if (T == 4) us = n * (6.5f + slabs * (0.6f + 0.28f * (w < 256 ? w * (1.0f / 256) : 1.0f)));
+      else if (T == 2) us = n < 2 ? 4.0f + slabs * 0.29f : 2.0f + ceilf(n * 0.5f) * (2.0f + slabs * 0.57f);
+      else us = 2.0f + 1.5f * ceilf(n * 0.25f) + slabs * (n < 2 ? 0.20f : 0.13f * n);
+      us += reduce;
+      if (us < least) { least = us; best = {T, 1, s}; }
+      if (T == 1 && groups && n < 2) {
+        us = 4.5f + slabs * 0.155f + reduce;
+        if (us < least) { least = us; best = {1, 2, s}; }
+      }
+    }
+  }
+  return best;
 }
 
-// k splits of a weight-gradient product: as many as still give every CU at most one work-group
-// (the kernel runs one per CU; a second round costs more than the longer k walk of fewer splits,
-// and every split writes and re-reads a full fp32 partial result)
+template <bool A_KROWS, bool B_KROWS, bool OUT_F32, int T, int KG>
+static hipError_t launch_gemm_as(GemmArgs &g, int splits, hipStream_t st) {
+  g.ntiles = (int)((g.N + 64 * T - 1) / (64 * T));
+  const int64_t mtiles = (g.M + 64 * T - 1) / (64 * T);
+  g.kslabs = (g.K / 64 + splits - 1) / splits;
+  dim3 grid((unsigned)(mtiles * g.ntiles), (unsigned)splits), block(128 * T * KG);
+  const bool wide = (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
+  if (wide)
+    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true, T, KG>), grid, block, 0, st, g);
+  else
+    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, false, T, KG>), grid, block, 0, st, g);
+  return hipGetLastError();
+}
+template <bool A_KROWS, bool B_KROWS, bool OUT_F32>
+static hipError_t launch_gemm(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
+  if (p.T == 4) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 4, 1>(g, p.splits, st);
+  if (p.T == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 2, 1>(g, p.splits, st);
+  if constexpr (!OUT_F32)
+    if (p.KG == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 2>(g, p.splits, st);
+  return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 1>(g, p.splits, st);
+}
+
+// Most k splits of a weight-gradient product (the workspace is sized by it): as many as still give every CU at most
+// one work-group of T = 4.
 int proj_wgrad_splits(int64_t Mout, int64_t Nout, int64_t K) {
-  const int64_t tiles = ((Mout + kGemmBM - 1) / kGemmBM) * ((Nout + kGemmBN - 1) / kGemmBN);
+  const int64_t tiles = ((Mout + 255) / 256) * ((Nout + 255) / 256);
   int64_t s = 256 / tiles;
   const int64_t slabs = K / 64;
   if (s > slabs / 4) s = slabs / 4;
@@ -406,7 +511,7 @@ hipError_t proj_qkv(const Dims &d, int64_t H, const void *X, const void *W, void
   g.B = plain(W, g.N);        // [K][N]
   g.out[0] = Q; g.out[1] = K; g.out[2] = V;
   g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-  return launch_gemm<false, true, false>(g, 1, st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
 }
 
 hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, void *Y, hipStream_t st) {
@@ -415,7 +520,7 @@ hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, voi
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [M][K], column tile = (half of a) head
   g.B = plain(Wo, H);                           // [K][N]
   g.out[0] = Y; g.out_split = 0; g.out_ld = H;
-  return launch_gemm<false, true, false>(g, 1, st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
 }
 
 hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O, const void *Wo,
@@ -427,7 +532,7 @@ hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O,
     g.A = plain(dY, H);   // [M][K]
     g.B = plain(Wo, H);   // [N][K]
     g.out[0] = dO; g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-    hipError_t e = launch_gemm<false, false, false>(g, 1, st);
+    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
     if (e != hipSuccess) return e;
   }
   // dWo = O^T dY: contraction over the rows
@@ -435,13 +540,13 @@ hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O,
   g.M = ZA; g.N = H; g.K = M;
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [K][M]
   g.B = plain(dY, H);                           // [K][N]
-  const int splits = proj_wgrad_splits(ZA, H, M);
-  g.out[0] = splits > 1 ? part : dWo; g.out_split = 0; g.out_ld = H;
-  hipError_t e = launch_gemm<true, true, true>(g, splits, st);
-  if (e != hipSuccess || splits == 1) return e;
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(ZA, H, M), false);
+  g.out[0] = plan.splits > 1 ? part : dWo; g.out_split = 0; g.out_ld = H;
+  hipError_t e = launch_gemm<true, true, true>(g, plan, st);
+  if (e != hipSuccess || plan.splits == 1) return e;
   const int64_t n4 = ZA * H / 4;
-  hipLaunchKernelGGL(ksplit_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part, dWo,
-                     n4, splits);
+  hipLaunchKernelGGL(ksplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part, dWo,
+                     n4, plan.splits);
   return hipGetLastError();
 }
 
@@ -455,7 +560,7 @@ hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK
     g.A = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [M][K]
     g.B = plain(W, N3);                  // [N][K]
     g.out[0] = dX; g.out_split = 0; g.out_ld = H;
-    hipError_t e = launch_gemm<false, false, false>(g, 1, st);
+    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
     if (e != hipSuccess) return e;
   }
   // dW = X^T [dQ | dK | dV]
@@ -463,28 +568,39 @@ hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK
   g.M = H; g.N = N3; g.K = M;
   g.A = plain(X, H);                   // [K][M]
   g.B = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [K][N]
-  const int splits = proj_wgrad_splits(H, N3, M);
-  g.out[0] = splits > 1 ? part : dW; g.out_split = 0; g.out_ld = N3;
-  hipError_t e = launch_gemm<true, true, true>(g, splits, st);
-  if (e != hipSuccess || splits == 1) return e;
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(H, N3, M), false);
+  g.out[0] = plan.splits > 1 ? part : dW; g.out_split = 0; g.out_ld = N3;
+  hipError_t e = launch_gemm<true, true, true>(g, plan, st);
+  if (e != hipSuccess || plan.splits == 1) return e;
   const int64_t n4 = H * N3 / 4;
-  hipLaunchKernelGGL(ksplit_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part, dW,
-                     n4, splits);
+  hipLaunchKernelGGL(ksplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part, dW,
+                     n4, plan.splits);
   return hipGetLastError();
 }
 
 // ---- Linformer projections along the sequence (Table 3, row Projection) ----
 // out (Zt, Kp, A) bf16 = sum over the k splits of part[s][k][zt*A + a], in a fixed order
-__global__ void __launch_bounds__(256) ksplit_reduce_heads_kernel(const float *part, uint16_t *out,
-                                                                  int64_t Kp, int64_t Zt, int splits, int A) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // one group of 4 columns
-  const int64_t n4 = Zt * (A / 4), total = Kp * n4;
+__global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_heads_kernel(const float *part, uint16_t *out,
+                                                                           int64_t Kp, int64_t Zt, int splits, int A) {
+  const uint32_t i = blockIdx.x * (uint32_t)kReduceBlock + threadIdx.x;  // one group of 4 columns
+  const uint32_t n4 = (uint32_t)Zt * (uint32_t)(A / 4), total = (uint32_t)Kp * n4;
   if (i >= total) return;
-  const int64_t k = i / n4, c = (i % n4) * 4;
-  f32x4 s = reinterpret_cast<const f32x4 *>(part)[i];
-  for (int j = 1; j < splits; ++j) s += reinterpret_cast<const f32x4 *>(part)[(int64_t)j * total + i];
+  const uint32_t k = i / n4, c = (i - k * n4) * 4, sh = A == 64 ? 6 : 7;
+  const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + i;
+  const f32x4 s = sum_of_splits(splits, [&](int j) { return p[(int64_t)j * total]; });
   const u32x2 w = {pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
-  *reinterpret_cast<u32x2 *>(out + ((c / A) * Kp + k) * A + (c % A)) = w;
+  *reinterpret_cast<u32x2 *>(out + ((((int64_t)(c >> sh)) * Kp + k) << sh) + (c & (uint32_t)(A - 1))) = w;
+}
+// dE (rows, Kp) from the partial sums that lie in dX's rows (see GemmArgs::part_heads)
+__global__ void __launch_bounds__(kReduceBlock) de_reduce_kernel(const float *part, float *dE, int64_t n4, int64_t Kp,
+                                                                 int64_t L, int splits, int part_heads, int w) {
+  const int64_t i = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
+  if (i >= n4) return;
+  const uint32_t kp4 = (uint32_t)Kp / 4, m = (uint32_t)i / kp4, n = ((uint32_t)i - m * kp4) * 4;
+  const float *p = part + ((int64_t)(n / (uint32_t)w) * L + m) * w + n % (uint32_t)w;
+  const int64_t stride = (int64_t)part_heads * L * w;
+  reinterpret_cast<f32x4 *>(dE)[i] =
+      sum_of_splits(splits, [&](int k) { return *reinterpret_cast<const f32x4 *>(p + k * stride); });
 }
 
 int linformer_splits(int64_t Kp, int64_t Zt, int64_t rows, int A) {
@@ -498,37 +614,53 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.M = Kp; g.N = Zt * A; g.K = rows;
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
-  const int splits = linformer_splits(Kp, Zt, rows, A);
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, linformer_splits(Kp, Zt, rows, A), false);
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
-  hipError_t e = launch_gemm<true, true, true>(g, splits, st);
+  hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess) return e;
   const int64_t total = Kp * Zt * (A / 4);
-  hipLaunchKernelGGL(ksplit_reduce_heads_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                     part, static_cast<uint16_t *>(Xp), Kp, Zt, splits, A);
+  hipLaunchKernelGGL(ksplit_reduce_heads_kernel, reduce_grid(total), dim3(kReduceBlock), 0, st,
+                     part, static_cast<uint16_t *>(Xp), Kp, Zt, plan.splits, A);
   return hipGetLastError();
 }
 
-// dX rows (Zt, L, A) from row0 on = E dXp, and dE (rows, Kp) fp32 = sum over heads of X dXp^T
+// dX rows (Zt, L, A) from row0 on = E dXp, and dE (rows, Kp) fp32 = sum over heads of X dXp^T.
+// dE first: with few rows its contraction over all heads is split, and the partial sums lie in the rows of dX that the
+// second product then overwrites (A / 2 floats per row and head, so a split takes 2 Kp / A heads).  64 rows, Kp = 128,
+// 180 heads of 128: one tile walked 23040 k in 427 us.
 hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, int A, const void *dXp,
                                  const void *X, const void *E, void *dX, float *dE, hipStream_t st) {
-  if (linformer_dx_supported(Kp, A)) {
-    hipError_t e = linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
-    if (e != hipSuccess) return e;
-  } else {
+  {
     GemmArgs g{};
-    g.M = rows; g.N = Zt * A; g.K = Kp;
-    g.A = plain(E, Kp);                                  // [M = token][K = k]
-    g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
-    g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
-    hipError_t e = launch_gemm<false, true, false>(g, 1, st);
+    g.M = rows; g.N = Kp; g.K = Zt * A;
+    g.A = heads(X, nullptr, nullptr, L, (int)Zt, A);     // [M = token][K = (head, a)]
+    g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [N = k][K = (head, a)]
+    const int64_t part_heads = 2 * Kp / A;
+    int64_t most = Zt / part_heads;
+    if (most > g.K / 256) most = g.K / 256;
+    if (most > 64) most = 64;
+    const GemmPlan plan = plan_gemm(g.M, g.N, g.K, most < 1 ? 1 : (int)most, false);
+    g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
+    if (plan.splits > 1) {
+      g.out[0] = dX; g.out_ld = A / 2; g.out_rows = L; g.part_heads = (int)part_heads;
+    }
+    hipError_t e = launch_gemm<false, false, true>(g, plan, st);
     if (e != hipSuccess) return e;
+    if (plan.splits > 1) {
+      const int64_t n4 = rows * Kp / 4;
+      hipLaunchKernelGGL(de_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, static_cast<const float *>(dX),
+                         dE, n4, Kp, L, plan.splits, (int)part_heads, A / 2);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
+  if (linformer_dx_supported(Kp, A)) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
   GemmArgs g{};
-  g.M = rows; g.N = Kp; g.K = Zt * A;
-  g.A = heads(X, nullptr, nullptr, L, (int)Zt, A);     // [M = token][K = (head, a)]
-  g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [N = k][K = (head, a)]
-  g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
-  return launch_gemm<false, false, true>(g, 1, st);
+  g.M = rows; g.N = Zt * A; g.K = Kp;
+  g.A = plain(E, Kp);                                  // [M = token][K = k]
+  g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
+  g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
+  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
 }
 
 }  // namespace rsa

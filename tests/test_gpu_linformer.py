@@ -141,3 +141,15 @@ def test_linformer_error_codes():
     with pytest.raises(rsa.RSAError) as e:
         rsa.linformer_project(rsa.make_desc(K, 2), K, E, ws=torch.empty(16, dtype=torch.uint8, device="cuda"))
     assert e.value.status == -4
+
+
+# Few rows and many heads: dE's contraction over the heads is split, its partial sums lie in dX's rows (one and several
+# heads per split, whole and part of the tensor), or not (too few heads to hold them).
+@pytest.mark.parametrize("B,Z,L,N,ranks,Kp,A", [
+    (2, 9, 64, 1, (0, 1), 64, 64),
+    (3, 20, 192, 3, (1, 2), 128, 128),
+    (5, 13, 1664, 2, (0, 1), 256, 64),
+    (1, 12, 128, 1, (0, 1), 192, 64),
+])
+def test_linformer_split_of_the_projection_gradient(B, Z, L, N, ranks, Kp, A):
+    test_linformer_chain(B, Z, L, N, ranks, Kp, A)

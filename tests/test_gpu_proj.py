@@ -147,3 +147,17 @@ def test_projection_error_codes():
         with pytest.raises(rsa.RSAError) as e:
             rsa.qkv_proj_bwd(desc, g, g, g, X, W, ws=torch.empty(16, dtype=torch.uint8, device="cuda"))
         assert e.value.status == -4
+
+
+# The size of the products chooses the work-groups' tiles: 64 x 64 with one and two groups of waves on k (an odd number
+# of its slabs of 64 splits unevenly), 128 x 128, 256 x 256, each with ragged edges, and k splits of the weight gradients.
+@pytest.mark.parametrize("B,Z,L,N,ranks,H,A", [
+    (3, 5, 192, 1, (0, 1), 1216, 64),
+    (2, 11, 256, 2, (0, 2), 1408, 128),
+    (5, 9, 576, 3, (0, 3), 704, 64),
+    (1, 3, 4224, 2, (1, 2), 1344, 128),
+    (3, 4, 3008, 1, (0, 1), 320, 64),
+    (6, 13, 1856, 1, (0, 1), 832, 64),
+])
+def test_projection_tile_sizes(B, Z, L, N, ranks, H, A):
+    test_projections_forward_and_backward(B, Z, L, N, ranks, H, A)
