@@ -66,6 +66,15 @@ __device__ __forceinline__ void lds_dma4(const void *gsrc, void *lds_base) {
   __builtin_amdgcn_global_load_lds((gptr_t)gsrc, (lptr_t)lds_base, 4, 0, 0);
 }
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
+// Waits for the direct loads in flight when exactly `STORES` newer stores were issued behind them (vmcnt counts both, in
+// order of issue).
+template <int STORES> __device__ __forceinline__ void wait_loads_before_stores() {
+  static_assert(STORES < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (STORES & 15) | ((STORES >> 4) << 14));
+}
+// Work-group barrier that orders LDS alone: __syncthreads() also waits for every global store in flight, a trip to HBM
+// per step of a loop that writes its results as it goes.  Direct loads need their own wait in front of it.
+__device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
 // Exchange between the two lanes l and l^32 (the two halves of a 32x32
 // accumulator column).  v_permlane32_swap a, b swaps a[32..63] with b[0..31];
