@@ -596,10 +596,10 @@ hipError_t shortkeys_forward(const Dims &att, const void *Q, const void *K, cons
 // ---------------------------------------------------------------- dX = E dXp ---
 // The input gradient of the Linformer projection (Table 3, row Projection): for every head,
 // dX (rows, A) = E (rows, Kp) dXp (Kp, A) with Kp <= 256.  As a GEMM its contraction is only Kp long, so a
-// tiled kernel spends its time filling and draining its pipeline; here a work-group keeps its 128
-// rows of E in registers (as B operands: wave w owns rows 32 w .. 32 w + 31) and streams the heads'
+// tiled kernel spends its time filling and draining its pipeline; here a work-group keeps its 128 QB
+// rows of E in registers (as B operands: wave w owns rows 32 QB w .. 32 QB (w + 1) - 1) and streams the heads'
 // dXp tiles through LDS, double-buffered, one barrier per 64 output columns:
-//     dX^T (64 dims x 32 rows) += dXp^T (dims x 16 k) E^T (16 k x rows)     (A: LDS transpose reads)
+//     dX^T (64 dims x 32 rows, QB times) += dXp^T (dims x 16 k) E^T (16 k x rows)     (A: LDS transpose reads)
 // and the block leaves through the wave's LDS tile as whole 128-byte rows.
 struct DxArgs {
   const uint16_t *E, *dXp;
@@ -608,7 +608,9 @@ struct DxArgs {
   int A, AH, ntiles, tiles_per_group, groups;  // ntiles = heads * AH column tiles of 64
 };
 
-template <int KT>
+// QB: 32-row blocks per wave.  Every wave reads a head's whole dXp tile from LDS by transpose reads, and a compute unit
+// brings at most about 40 bytes per clock into LDS: with two blocks a fragment and a tile serve twice the rows.
+template <int KT, int QB>
 __global__ void __launch_bounds__(256, 2) linformer_dx_kernel(DxArgs g) {
   struct Buf { unsigned char t[KT][kTileBytes]; };
   __shared__ __attribute__((aligned(16))) Buf buf0, buf1;
@@ -618,48 +620,73 @@ __global__ void __launch_bounds__(256, 2) linformer_dx_kernel(DxArgs g) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t blk = blockIdx.x / g.groups;
   const int grp = blockIdx.x % g.groups;
-  const int64_t row0 = blk * 128;
+  const int64_t row0 = blk * (128 * QB);
   const int ct_begin = grp * g.tiles_per_group;
   const int nct = min(g.tiles_per_group, g.ntiles - ct_begin);
   if (nct <= 0) return;
   const TileLanes tl(lane);
   const TileDMAT<4> dma_e(wave, lane, (int)g.Kp), dma_b(wave, lane, g.A);
 
-  // E rows of the block -> LDS (its 2 x KT tiles fill the two buffers) -> registers
+  // E rows of the block -> LDS (two row tiles at a time, KT tiles each, fill the two buffers) -> registers
   const int64_t last_rt = g.rows / 64 - 1;
+  bf16x8 efrag[QB][KT * 4];
 #pragma unroll
-  for (int kt = 0; kt < KT; ++kt) {
-    const int64_t rt0 = min(row0 / 64, last_rt), rt1 = min(row0 / 64 + 1, last_rt);  // past the end: refetch
-    dma_e.load(g.E + rt0 * 64 * g.Kp + kt * 64, buf0.t[kt]);
-    dma_e.load(g.E + rt1 * 64 * g.Kp + kt * 64, buf1.t[kt]);
-  }
-  wait_vmem();
-  __syncthreads();
-  bf16x8 efrag[KT * 4];
+  for (int p = 0; p < QB; ++p) {
+    const int64_t rt = row0 / 64 + 2 * p;
+    const int64_t rt0 = min(rt, last_rt), rt1 = min(rt + 1, last_rt);  // past the end: refetch
 #pragma unroll
-  for (int ks = 0; ks < KT * 4; ++ks) {
-    const unsigned char *te = (wave >> 1) ? buf1.t[ks >> 2] : buf0.t[ks >> 2];
-    efrag[ks] = tl.read_rows_perm(te, (wave & 1) * 32, ks & 3);
+    for (int kt = 0; kt < KT; ++kt) {
+      dma_e.load(g.E + rt0 * 64 * g.Kp + kt * 64, buf0.t[kt]);
+      dma_e.load(g.E + rt1 * 64 * g.Kp + kt * 64, buf1.t[kt]);
+    }
+    wait_vmem();
+    __syncthreads();
+    if (QB == 1 || (wave >> 1) == p) {
+      const bool second = QB == 1 ? wave >> 1 : wave & 1;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int ks = 0; ks < KT * 4; ++ks) {
+          const unsigned char *te = second ? buf1.t[ks >> 2] : buf0.t[ks >> 2];
+          efrag[qb][ks] = tl.read_rows_perm(te, QB == 1 ? (wave & 1) * 32 : qb * 32, ks & 3);
+        }
+    }
+    __syncthreads();  // the buffers are free again
   }
-  __syncthreads();  // the buffers are free again
 
   auto load_b = [&](int ct, Buf &b) __attribute__((always_inline)) {
-    const int head = ct / g.AH, ah = ct % g.AH;
+    const int head = ct >> (g.AH - 1), ah = ct & (g.AH - 1);  // AH: 1 or 2
     const uint16_t *src = g.dXp + (int64_t)head * g.Kp * g.A + ah * 64;
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) dma_b.load(src + (int64_t)kt * 64 * g.A, b.t[kt]);
   };
   unsigned char *ot = stg[wave];
-  const int64_t wrow0 = row0 + wave * 32;
+  // (rows come in multiples of 64: waves past the end hold, and store, the last 64 rows again)
+  const int64_t wfirst = row0 + wave * (32 * QB), tile_row = QB == 1 ? (wave & 1) * 32 : 0;
+  const int64_t wrow0 = wfirst < g.rows ? wfirst : g.rows - 64 + tile_row;
+  // the staged block of 32 rows leaves as whole 128-byte rows
+  // (32-bit lane offsets from uniform bases: addresses per lane would spill)
+  const int out_lane = (lane >> 3) * g.A + (lane & 7) * 8, out_ld8 = 8 * g.A;
+  uint16_t *out0 = g.dX + wrow0 * g.A;
+  auto flush = [&](int ct, int qb) __attribute__((always_inline)) {
+    const int head = ct >> (g.AH - 1), ah = ct & (g.AH - 1);
+    uint16_t *base = out0 + (int64_t)head * g.L * g.A + (qb * 32 * g.A + ah * 64);
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+      *reinterpret_cast<u32x4 *>(base + it * out_ld8 + out_lane) =
+          *reinterpret_cast<const u32x4 *>(ot + tile_off(it * 8 + (lane >> 3), lane & 7));
+  };
   auto tile = [&](int ct, const Buf &b) __attribute__((always_inline)) {
-    f32x16 acc[2];
+    f32x16 acc[2][QB];
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
-    // a k slice is only two MFMAs, far less than the latency of an LDS read: the fragments are read
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[db][qb][v] = 0.f;
+    // a k slice is only two or four MFMAs, less than the latency of an LDS read: the fragments are read
     // DEPTH slices ahead
-    constexpr int DEPTH = 6, NS = KT * 4;
+    constexpr int DEPTH = QB == 1 ? 6 : 3, NS = KT * 4;
     bf16x8 af[NS][2];
     auto frags = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
@@ -672,33 +699,44 @@ __global__ void __launch_bounds__(256, 2) linformer_dx_kernel(DxArgs g) {
     for (int ks = 0; ks < NS; ++ks) {
       if (ks + DEPTH < NS) frags(ks + DEPTH);
 #pragma unroll
-      for (int db = 0; db < 2; ++db) acc[db] = mfma_32x32x16(af[ks][db], efrag[ks], acc[db]);
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) acc[db][qb] = mfma_32x32x16(af[ks][db], efrag[qb][ks], acc[db][qb]);
       __builtin_amdgcn_sched_barrier(0);
     }
-    stage_block_T(ot, 0, acc[0], acc[1], 1.0f, lane);
+    // the last block stays staged: it leaves a step later, behind the step's barrier and beside the next tile's MFMAs
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      stage_block_T(ot, 0, acc[0][qb], acc[1][qb], 1.0f, lane);
+      if (qb + 1 < QB) flush(ct, qb);
+    }
   };
-  // the staged block leaves a step later, behind the step's barrier and beside the next tile's MFMAs
-  auto flush = [&](int ct) __attribute__((always_inline)) {
-    const int head = ct / g.AH, ah = ct % g.AH;
-    flush_rows<32>(ot, 0, g.dX + ((int64_t)head * g.L + wrow0) * g.A + ah * 64, g.rows - wrow0, lane, g.A);
-  };
-
+  // A step waits for its tile only: the stores of the blocks that left behind those loads stay in flight.
+  // (With them waited for, a trip to HBM under load, a step took 2.9 us for 1 us of matrix work; 114688 rows, 48
+  // heads, Kp = 256, 0.7 GB written: 243 -> 205 us with the second block of rows below.)
   load_b(ct_begin, buf0);
-  int i = 0;
+  wait_vmem();
+  barrier_lds();
+  if (nct > 1) load_b(ct_begin + 1, buf1);
+  tile(ct_begin, buf0);
+  wait_vmem();
+  int i = 1;
   auto step = [&](Buf &cur, Buf &nxt) __attribute__((always_inline)) {
-    wait_vmem();
-    __syncthreads();
+    barrier_lds();
     if (i + 1 < nct) load_b(ct_begin + i + 1, nxt);
-    if (i > 0) flush(ct_begin + i - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    flush(ct_begin + i - 1, QB - 1);
+    __builtin_amdgcn_sched_barrier(0);
     tile(ct_begin + i, cur);
+    wait_loads_before_stores<4 * QB>();
     ++i;
   };
   while (i < nct) {
-    step(buf0, buf1);
-    if (i >= nct) break;
     step(buf1, buf0);
+    if (i >= nct) break;
+    step(buf0, buf1);
   }
-  flush(ct_begin + nct - 1);
+  flush(ct_begin + nct - 1, QB - 1);
 }
 
 bool linformer_dx_supported(int64_t Kp, int A) { return Kp % 64 == 0 && Kp <= 256 && (A == 64 || A == 128); }
@@ -708,7 +746,11 @@ hipError_t linformer_dx(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, int A, 
   DxArgs g;
   g.E = (const uint16_t *)E; g.dXp = (const uint16_t *)dXp; g.dX = (uint16_t *)dX;
   g.rows = rows; g.L = L; g.Kp = Kp; g.A = A; g.AH = A / 64; g.ntiles = (int)(Zt * g.AH);
-  const int64_t blocks = (rows + 127) / 128;
+  // Two 32-row blocks per wave where each of the 512 places for work-groups gets at least eight of their (twice as
+  // large) tiles.  The whole call with one | two blocks, us, by tiles per place: 24: 273 | 251, 12: 155 | 151,
+  // 6: 66 | 66, 3: 43 | 46, 1: 27 | 31 (Kp = 256, 4 to 48 heads of 64 and 128, 2048 to 65536 rows).
+  const bool two = rows / 256 * g.ntiles >= 512 * 8;
+  const int64_t blocks = (rows + (two ? 255 : 127)) / (two ? 256 : 128);
   // groups of column tiles per row block: few, even rounds of the 512 work-groups the chip holds
   int best = 1;
   double best_cost = 1e30;
@@ -721,12 +763,13 @@ hipError_t linformer_dx(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, int A, 
   g.groups = best;
   g.tiles_per_group = (g.ntiles + best - 1) / best;
   const dim3 grid((unsigned)(blocks * best));
-  switch (Kp / 64) {
-    case 1: hipLaunchKernelGGL(linformer_dx_kernel<1>, grid, dim3(256), 0, st, g); break;
-    case 2: hipLaunchKernelGGL(linformer_dx_kernel<2>, grid, dim3(256), 0, st, g); break;
-    case 3: hipLaunchKernelGGL(linformer_dx_kernel<3>, grid, dim3(256), 0, st, g); break;
-    default: hipLaunchKernelGGL(linformer_dx_kernel<4>, grid, dim3(256), 0, st, g); break;
-  }
+#define RSA_DX(KT)                                                                             \
+  case KT:                                                                                     \
+    if (two) hipLaunchKernelGGL((linformer_dx_kernel<KT, 2>), grid, dim3(256), 0, st, g);      \
+    else hipLaunchKernelGGL((linformer_dx_kernel<KT, 1>), grid, dim3(256), 0, st, g);          \
+    break;
+  switch (Kp / 64) { RSA_DX(1) RSA_DX(2) RSA_DX(3) RSA_DX(4) }
+#undef RSA_DX
   return hipGetLastError();
 }
 

@@ -153,3 +153,20 @@ def test_linformer_error_codes():
 ])
 def test_linformer_split_of_the_projection_gradient(B, Z, L, N, ranks, Kp, A):
     test_linformer_chain(B, Z, L, N, ranks, Kp, A)
+
+
+# dX by work-groups of 256 rows (enough rows and heads to fill the chip with them): the last work-group whole, with one,
+# two and three of its four 64-row tiles; every slice count of Kp; heads of 128.
+@pytest.mark.parametrize("heads,rows,Kp,A", [
+    (64, 16384, 256, 64), (64, 16448, 256, 64), (64, 16512, 64, 64), (64, 16576, 128, 64), (32, 16576, 192, 128),
+])
+def test_linformer_dx_of_many_rows(heads, rows, Kp, A):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, E, dXp = (torch.randn(s, generator=g, device="cuda").bfloat16()
+                 for s in ((1, heads, rows, A), (rows, Kp), (1, heads, Kp, A)))
+    dX = rsa.linformer_project_bwd(rsa.make_desc(K, 1), dXp, K, E)[0]
+    for h in range(heads):
+        ref = E.double() @ dXp[0, h].double()
+        # one rounding to bf16 (2^-9 of the value) and the fp32 sums' (Kp 2^-24 of the products' magnitude, here 1)
+        bound = 2.0 ** -8 * ref.abs() + 1e-4
+        assert ((dX[0, h].double() - ref).abs() <= bound).all(), f"head {h}"
