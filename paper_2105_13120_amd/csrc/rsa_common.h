@@ -76,6 +76,21 @@ template <int STORES> __device__ __forceinline__ void wait_loads_before_stores()
 // per step of a loop that writes its results as it goes.  Direct loads need their own wait in front of it.
 __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
+// A direct global->LDS load (16 bytes per lane, landing at lds_base + 16 lane) that the compiler does not see: it
+// would wait for every such load in flight before the next LDS read where the buffers of a ring are one object.
+// The kernel orders them itself (wait_loads before the barrier that publishes them).
+__device__ __forceinline__ void lds_dma16_unseen(const void *g, int lane_off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               : : "v"(lane_off), "s"(g), "s"(lds_base) : "m0");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+template <int N> __device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" : : : "memory"); }
+
 // Exchange between the two lanes l and l^32 (the two halves of a 32x32
 // accumulator column).  v_permlane32_swap a, b swaps a[32..63] with b[0..31];
 // with a = b = x on entry, lanes 0-31 end with (a, b) = (x[l], x[l+32]) and

@@ -171,18 +171,6 @@ struct HalfLanes {
   }
 };
 
-// A direct global->LDS load (16 bytes per lane, landing at lds_base + 16 lane) that the compiler does not see: it
-// would wait for every such load in flight before the next LDS read, since the ring's buffers are one object.
-// The kernel orders them itself (wait_loads before the barrier that publishes them).
-__device__ __forceinline__ void lds_dma16_unseen(const void *g, int lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               : : "v"(lane_off), "s"(g), "s"(lds_base) : "m0");
-}
-template <int N> __device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-__device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" : : : "memory"); }
-
 // WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG>
 __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) {

@@ -77,7 +77,12 @@ template <> struct TileT<uint16_t> {
   static __device__ __forceinline__ int key_of_col(int c) { return (c & 16) | ((c & 4) << 1) | ((c >> 1) & 4) | (c & 3); }
   template <int ROWS = 64> struct DMA {  // ROWS = 32: the upper half of a tile
     TileDMAT<256 / ROWS> d;
+    static constexpr int PER = TileDMAT<256 / ROWS>::PER;
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) : d(wave, lane, (int)ld) {}
+    __device__ __forceinline__ void load_unseen(const uint16_t *g, uint32_t t) const {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) lds_dma16_unseen(g, d.g_off[j] * 2, t + d.l_off[j]);
+    }
     __device__ __forceinline__ void load(const uint16_t *g, unsigned char *t) const { d.load(g, t); }
   };
   static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 3; return (p & 7) ^ swz_rot(row); }
@@ -163,6 +168,10 @@ template <> struct TileT<float> {
 #pragma unroll
       for (int j = 0; j < PER; ++j) lds_dma16(g + g_off[j], t + l_off[j]);
     }
+    __device__ __forceinline__ void load_unseen(const float *g, uint32_t t) const {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) lds_dma16_unseen(g, g_off[j] * 4, t + l_off[j]);
+    }
   };
 };
 
@@ -194,9 +203,9 @@ template <typename T, int ROWS> struct StripDMA {
       l_off[j] = (wave * PER + j) * 1024;
     }
   }
-  __device__ __forceinline__ void load(const T *tile, unsigned char *t) const {
+  __device__ __forceinline__ void load_unseen(const T *tile, uint32_t t) const {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) lds_dma16(tile + g_off[j], t + l_off[j]);
+    for (int j = 0; j < PER; ++j) lds_dma16_unseen(tile, g_off[j] * (int)sizeof(T), t + l_off[j]);
   }
 };
 
@@ -610,8 +619,8 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
 // --------------------------------------------------------------- collect ----
 // out (key, A) = alpha * sum over the group's rows of strip(row, key) Y(row, A), two products per launch
 // (dV from P and dO, dK from dS and Q).  Work-group: 128 keys (wave: 32) x 64 AHW columns, walking the row
-// tiles.  With several row groups the sums pass through fp32 accumulators: `add` continues them, `keep`
-// leaves them there instead of writing the result.
+// tiles through a ring of DEPTH LDS buffers, DEPTH - 1 tiles requested ahead.  With several row groups the sums pass
+// through fp32 accumulators: `add` continues them, `keep` leaves them there instead of writing the result.
 struct CollectArgs {
   const void *strip[2], *Y[2];
   void *out[2];
@@ -620,13 +629,13 @@ struct CollectArgs {
   int add, keep;
 };
 
-template <typename T, int AHW>
-__global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(StripArgs a, CollectArgs p) {
+template <typename T, int AHW, int DEPTH>
+__global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_collect_kernel(StripArgs a, CollectArgs p) {
   typedef TileT<T> TT;
   constexpr int RT = sizeof(T) == 4 ? 32 : 64;  // rows per step: 24 KiB (64 columns, either type) leave room for three
   constexpr int NS = TT::kSlices * RT / 64;     // work-groups on a compute unit
   struct Stage { unsigned char S[2][TT::kBytes * RT / 64], Y[AHW][TT::kBytes * RT / 64]; };
-  __shared__ __attribute__((aligned(16))) Stage st0, st1;
+  __shared__ __attribute__((aligned(16))) Stage st[DEPTH];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
@@ -651,15 +660,21 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(St
   const T *Yh = static_cast<const T *>(which ? p.Y[1] : p.Y[0]) + head * a.Lq * a.A + a0;
   const StripDMA<T, RT> dma_s(wave, lane);
   const typename TT::template DMA<RT> dma_y(wave, lane, a.A);
-  auto load = [&](int tt_, Stage &st) __attribute__((always_inline)) {
+  const uint32_t lds0 = lds_address(&st[0]);
+  constexpr int kLoads = 2 * StripDMA<T, RT>::PER + AHW * TT::template DMA<RT>::PER;  // of a wave, per row tile
+  auto load = [&](int tt_, int b) __attribute__((always_inline)) {  // row tile tt_ -> buffer b
     const int row = tt_ * RT;
     const T *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
-    dma_s.load(s, st.S[0]);
-    dma_s.load(s + second, st.S[1]);
+    const uint32_t d = lds0 + (uint32_t)b * (uint32_t)sizeof(Stage);
+    dma_s.load_unseen(s, d);
+    dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
 #pragma unroll
-    for (int ah = 0; ah < AHW; ++ah) dma_y.load(Yh + (int64_t)row * a.A + ah * 64, st.Y[ah]);
+    for (int ah = 0; ah < AHW; ++ah)
+      dma_y.load_unseen(Yh + (int64_t)row * a.A + ah * 64, d + (uint32_t)(sizeof(st[0].S) + ah * sizeof(st[0].Y[0])));
   };
-  load(t < nt ? t : nt - 1, st0);  // (a block that no row sees: any tile)
+#pragma unroll
+  for (int i = 0; i + 1 < DEPTH; ++i)
+    if (t + i < nt) load(t + i, i);
   const int64_t wkey = key0 + wave * 32, wtile = key0 + (wave >> 1) * 64;
   const bool keys_here = wkey < a.L;
   const TT tt(lane);
@@ -668,10 +683,14 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(St
   for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  wait_vmem();
-  __syncthreads();
-  auto step = [&](Stage &cur, Stage &nxt) __attribute__((always_inline)) {
-    if (t + 1 < nt) load(t + 1, nxt);
+  int b = 0;  // buffer of tile t
+  for (; t < nt; ++t) {
+    // tile t has arrived, and behind the barrier every wave is done with tile t - 1, whose buffer takes the next one
+    if (DEPTH == 3 && t + 1 < nt) wait_loads<kLoads>();
+    else wait_loads<0>();
+    barrier_lds();
+    if (t + DEPTH - 1 < nt) load(t + DEPTH - 1, b == 0 ? DEPTH - 1 : b - 1);
+    const Stage &cur = st[b];
     if (keys_here && tile_seen(a, (int64_t)t * RT, wtile)) {
       const unsigned char *S = cur.S[wave >> 1];
       typename TT::Frag sf[2], yf[2][2 * AHW];
@@ -686,15 +705,9 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(St
             for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(yf[b][db], sf[b], o[db]);
           });
     }
-    wait_vmem();
-    __syncthreads();
-    ++t;
-  };
-  while (t < nt) {
-    step(st0, st1);
-    if (t >= nt) break;
-    step(st1, st0);
+    b = b + 1 < DEPTH ? b + 1 : 0;
   }
+  barrier_lds();  // the epilogue writes to the buffers
   if (!keys_here) return;
   if (p.add || p.keep) {
     float *acc = (which ? p.acc[1] : p.acc[0]) + (head * a.L + wkey + TT::key_of_col(col)) * a.A + a0 + half * 4;
@@ -713,7 +726,7 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_collect_kernel(St
   }
   const float alpha = which ? p.alpha[1] : p.alpha[0];
   // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
-  unsigned char *ot = (wave < 2 ? st0.S[0] : st1.S[0]) + (wave & 1) * (TT::kBytes / 2);
+  unsigned char *ot = st[wave >> 1].S[0] + (wave & 1) * (TT::kBytes / 2);
   T *out = static_cast<T *>(which ? p.out[1] : p.out[0]) + (head * a.L + wkey) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
@@ -814,8 +827,22 @@ hipError_t launch_collect(const StripArgs &a0, const CollectArgs &p, int64_t hea
   a.kblocks = (int)((a.L + 127) / 128);
   const bool wide = a.A % 128 == 0;
   const dim3 grid((unsigned)(heads * a.kblocks * 2 * (a.A / (wide ? 128 : 64))));
-  if (wide) hipLaunchKernelGGL((strip_collect_kernel<T, 2>), grid, dim3(256), 0, st, a, p);
-  else hipLaunchKernelGGL((strip_collect_kernel<T, 1>), grid, dim3(256), 0, st, a, p);
+  if (wide) {
+    hipLaunchKernelGGL((strip_collect_kernel<T, 2, 2>), grid, dim3(256), 0, st, a, p);
+    return hipGetLastError();
+  }
+  // bf16 strips come at the rate that requests in flight allow.  With at most one work-group on a compute unit its row
+  // tiles are requested two steps ahead; several bring enough by themselves, and three fit where each takes two
+  // buffers.  The whole backward with two | three buffers, us: 64 work-groups 33.5 | 30.4, 256: 45.4 | 40.8 and
+  // 161.5 | 140.8, 384 (in groups): 1165 | 1180, 1536: 121 | 121; fp32, bound by its products: 256: 131 | 131,
+  // 768: 292 | 309.
+  if constexpr (sizeof(T) == 2) {
+    if (grid.x <= 256) {
+      hipLaunchKernelGGL((strip_collect_kernel<T, 1, 3>), grid, dim3(256), 0, st, a, p);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((strip_collect_kernel<T, 1, 2>), grid, dim3(256), 0, st, a, p);
   return hipGetLastError();
 }
 

@@ -156,6 +156,11 @@ def test_staged_explicit_softmax_scale(dtype):
 @pytest.mark.parametrize("dtype,kw,heads", [
     ("f32", dict(B=1, Z=1, L=192, N=3), [0]),                          # one and a half row tiles, ragged key block
     ("bf16", dict(B=1, Z=1, L=64, N=1), [0]),                          # a single tile
+    ("bf16", dict(B=1, Z=1, L=128, N=1), [0]),                         # as many tiles as are requested ahead, one more,
+    ("bf16", dict(B=1, Z=2, L=192, N=3), [0, 1]),                      # and walks that start late
+    ("bf16", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True), [0, 1]),
+    ("bf16", dict(B=1, Z=1, L=320, N=5, causal=True, A=192), [0]),
+    ("bf16", dict(B=4, Z=9, L=512, N=4, causal=True), [0, 17, 35]),    # more work-groups: one tile ahead
     ("f32", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
     ("bf16", dict(B=1, Z=2, L=448, N=7, rb=2, re=5, causal=True, A=256), [0, 1]),
     ("bf16", dict(B=2, Z=15, L=2048, N=4), [0, 9, 10, 29]),            # heads in several groups
