@@ -155,6 +155,20 @@ def test_linformer_split_of_the_projection_gradient(B, Z, L, N, ranks, Kp, A):
     test_linformer_chain(B, Z, L, N, ranks, Kp, A)
 
 
+@pytest.mark.parametrize("heads,rows,Kp,A", [(180, 64, 64, 128), (24, 128, 64, 64), (64, 16384, 256, 64)])
+def test_linformer_gradient_over_its_input(heads, rows, Kp, A):
+    """dX may be X's own buffer: dE has read X before dX is written (few rows: partial sums must not lie there)."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X, E, dXp = (torch.randn(s, generator=g, device="cuda").bfloat16()
+                 for s in ((1, heads, rows, A), (rows, Kp), (1, heads, Kp, A)))
+    desc = rsa.make_desc(X, 1)
+    dX, dE = rsa.linformer_project_bwd(desc, dXp, X, E)
+    dX2, dE2 = rsa.linformer_project_bwd(desc, dXp, X, E, dX=X)
+    assert dX2.data_ptr() == X.data_ptr() and torch.equal(dX2, dX)
+    # the same products summed in fp32 in another order: check_f32's bound, on each side of the sum
+    assert (dE2 - dE).abs().max() <= 4e-4 * dE.square().mean().sqrt()
+
+
 # dX by work-groups of 256 rows (enough rows and heads to fill the chip with them): the last work-group whole, with one,
 # two and three of its four 64-row tiles; every slice count of Kp; heads of 128.
 @pytest.mark.parametrize("heads,rows,Kp,A", [
