@@ -758,7 +758,7 @@ int fused_bwd_dkdv_splits(const Dims &d) {
 template <int NQ, int AH, int WK, int QS>
 static void launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.L + 32 * WK - 1) / (32 * WK));
-  a.by_length = order_by_length(d, splits);
+  a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * WK * QS);
   if (d.causal)
     hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
@@ -795,7 +795,7 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
 template <bool PRE, int AH, int NK, int RW, int KS>
 static void launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.Lq + 32 * RW - 1) / (32 * RW));
-  a.by_length = order_by_length(d, splits);
+  a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (32 * RW) == 0 ? (int)(d.c / 2 / (32 * RW)) : 0;
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * RW * KS);
   if (d.causal)

@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
 template <int R, int AH, int NK, int RW, int KS>
 static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.Lq + RW * R - 1) / (RW * R));
-  a.by_length = order_by_length(d, splits);
+  a.by_length = order_by_length(d, splits, (int64_t)400 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (RW * R) == 0 ? (int)(d.c / 2 / (RW * R)) : 0;
   dim3 grid((unsigned)(heads * a.tiles_per_head), (unsigned)splits);
   if (d.causal)
@@ -455,9 +455,14 @@ static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits
 }
 
 // Whether a causal launch hands out its tiles by length (longest_first): when they differ by more than a
-// factor of two, and the walk is not split (splits turn the ranges over the XCDs instead, see xcd_remap).
-bool order_by_length(const Dims &d, int splits) {
-  return d.causal && splits == 1 && (d.zigzag || 2 * d.rank_begin < d.rank_end);
+// factor of two, the walk is not split (splits turn the ranges over the XCDs instead, see xcd_remap), and what the
+// walks of all heads read (K and V, or Q and dO) takes at most `most` bytes: all heads are then under way together, and
+// what the caches cannot hold is fetched again and again.  Time in head order over time by length, by MB:
+// forward 37 (70 heads): 1.18, 67: 1.37, 75: 1.41, 147: 1.10, 227: 1.00, 254: 1.05, 294: 1.11, 567: 0.92; backward 37:
+// 1.15, 67: 1.14, 113: 1.10, 134: 1.04 and 0.98, 147: 1.00, 226: 0.97, 294: 0.94, 567: 0.89.
+bool order_by_length(const Dims &d, int splits, int64_t most) {
+  return d.causal && splits == 1 && (d.zigzag || 2 * d.rank_begin < d.rank_end) &&
+         (int64_t)d.B * d.Z * d.L * d.A * 4 <= most;
 }
 
 // Splits of the key walk for a kernel whose work-groups own `rows_per_wg` query rows (two

@@ -43,7 +43,7 @@ hipError_t strip_backward(const Dims &d, int dtype, const void *dO, const void *
 // splits * B*Z*Lq * (A + 2) floats, or nullptr for no split.  fused_key_splits: the dQ kernel's count.
 void fused_fwd_plan(const Dims &d, bool *big, int *splits);
 int fused_key_splits(const Dims &d);
-bool order_by_length(const Dims &d, int splits);
+bool order_by_length(const Dims &d, int splits, int64_t most);
 hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O,
                          float *LSE, hipStream_t st, float *part);
 // nD = -rowsum(dO o O) and nL = -LSE / scale, (B,Z,Lq) fp32
