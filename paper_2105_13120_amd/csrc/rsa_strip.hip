@@ -11,11 +11,19 @@
 //   backward   scores: P = exp(S - LSE), dS = P o (dO V^T - D), both tiles written in dtype
 //              apply:  dQ = s dS K;   collect: dV = P^T dO, dK = s dS^T Q
 //
+// In fp32 the backward's P is brought to its rows' own sums instead of relying on the LSE it is given, whose
+// rounding (2^-25 |LSE|) every probability of the row would share: the scores kernel leaves each tile's row sums,
+// apply adds them and scales its rows, collect scales the strips' rows as it reads them.  No accumulator starts
+// from a row term (the contraction would be rounded at that term's size), and the fp32 sums over keys or rows are
+// formed 32 at a time.  Relative RMS error against fp64, 1e-7, dQ | dK | dV | O, N(0, 1) inputs:
+// A64 L512 3.5 | 3.4 | 3.1 | 3.1 (with row terms in the accumulators and one chain per sum 12.5 | 12.2 | 12.1 | 5.8;
+// the chunk-by-chunk steps of rsa_staged.hip, N4, 3.9 | 3.8 | 3.5 | 3.6).
+//
 // Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
 // 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.68,
-// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; now 0.475, 80 to 95 TFLOP/s in
+// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; now 0.48, 80 to 95 TFLOP/s in
 // every kernel, of which the strips' traffic hides about half).
 //
 // The tile kernels hold bf16 tiles in the layout of the fused kernels and fp32 tiles in one of their
@@ -209,12 +217,16 @@ template <typename T, int ROWS> struct StripDMA {
   }
 };
 
+// fp32 strips hold P to a factor per row (see on top).
+template <typename T> constexpr bool kOwnSum = sizeof(T) == 4;
+
 struct StripArgs {
   const void *Q, *K, *V, *dO, *O;  // first head of the group; Q, dO, O: first row of the group
   const float *LSE_in;
   float *LSE;                      // (head, Lq), first row of the group
   void *strip, *strip2;            // (head, rows, L) in tiles: exp(S - m_t) or P; dS
-  float *stats;                    // (head, L / 64, rows, 2): m_t and l_t, base-2 logarithm domain
+  float *stats;                    // forward: (head, L / 64, rows, 2), m_t and l_t, base-2 logarithm domain;
+                                   // fp32 backward: (head, L / 64, rows), the tile's part of a row's sum
   int64_t L, Lq, rows, q0;         // rows of the group; token of its first row
   int A, causal, rtiles, kblocks, per;  // 128-row tiles; key blocks of `per` tiles
   float cl2, scale, inv_scale;
@@ -350,17 +362,17 @@ __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(
       for (int v = 0; v < 16; ++v) m = fmaxf(m, s[1][v]);
       m = xhalf_max(m);
       const float mc = m > -INFINITY ? m * a.cl2 : 0.f;  // a row that sees none of these keys: all zeros
-      float l = 0.f;
+      float l[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           s[kb][v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], a.cl2, -mc));
-          l += s[kb][v];
+          l[v & 3] += s[kb][v];
         }
-      l = xhalf_sum(l);
+      const float sum = xhalf_sum((l[0] + l[1]) + (l[2] + l[3]));
       if (half == 0) {
-        f32x2 p = {m > -INFINITY ? mc : -INFINITY, l};
+        f32x2 p = {m > -INFINITY ? mc : -INFINITY, sum};
         *reinterpret_cast<f32x2 *>(a.stats + ((pos.head * (a.L / 64) + t) * a.rows + wrow + col) * 2) = p;
       }
       strip_store(static_cast<T *>(a.strip) + strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) +
@@ -398,7 +410,10 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
   const int64_t wrow = pos.row0 + wave * 32;
   const bool rows_here = wrow < a.rows;
   typename TT::Frag q[AH * NS], g[AH * NS];
-  float nl = 0.f, nd = 0.f;  // -LSE / scale and -D of the lane's row: what the accumulators start from
+  // bf16: -LSE / scale and -D of the lane's row, which the accumulators start from.  fp32: the reference of the row's
+  // exponents, LSE less the logarithm of a power of two that brings likely scores near it (any value near LSE will
+  // do; an exponent is rounded at its own size.  Scores beyond about 1e8 would leave its range), and D.
+  float nl = 0.f, nd = 0.f;
   if (rows_here) {
     const int64_t off = (pos.head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
     const T *qp = static_cast<const T *>(a.Q) + off, *gp = static_cast<const T *>(a.dO) + off;
@@ -411,7 +426,13 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
       acc = TT::dot(g[i], *reinterpret_cast<const typename TT::Frag *>(op + i * TT::kSliceK), acc);
     }
     nd = -xhalf_sum(acc);
-    nl = -a.LSE_in[pos.head * a.Lq + wrow + col] * a.inv_scale;
+    const float lse = a.LSE_in[pos.head * a.Lq + wrow + col];
+    if constexpr (kOwnSum<T>) {
+      const float lse2 = lse * kLog2e;
+      nl = fminf(fmaxf(rintf(lse2), 0.f), (float)(63 - __builtin_clzll((uint64_t)a.L))) - lse2;
+    } else {
+      nl = -lse * a.inv_scale;
+    }
   }
   const TT tt(lane);
   wait_vmem();
@@ -424,7 +445,7 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { s[kb][v] = nl; dp[kb][v] = nd; }
+        for (int v = 0; v < 16; ++v) { s[kb][v] = kOwnSum<T> ? 0.f : nl; dp[kb][v] = kOwnSum<T> ? 0.f : nd; }
       typename TT::Frag kf[2][2], vf[2][2];
       pipelined<AH * NS>(
           [&](int i, int b) __attribute__((always_inline)) {
@@ -447,13 +468,27 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
     __builtin_amdgcn_sched_barrier(0);
     if (work) {
       mask_scores(a, wrow, k0, lane, s);
+      if constexpr (kOwnSum<T>) {
+        float l[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          s[kb][v] = __builtin_amdgcn_exp2f(s[kb][v] * a.cl2);
-          dp[kb][v] *= s[kb][v];
-        }
+          for (int v = 0; v < 16; ++v) {
+            s[kb][v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], a.cl2, nl));
+            dp[kb][v] = (dp[kb][v] + nd) * s[kb][v];
+            l[v & 3] += s[kb][v];
+          }
+        const float sum = xhalf_sum((l[0] + l[1]) + (l[2] + l[3]));
+        if (half == 0) a.stats[(pos.head * (a.L / 64) + t) * a.rows + wrow + col] = sum;
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            s[kb][v] = __builtin_amdgcn_exp2f(s[kb][v] * a.cl2);
+            dp[kb][v] *= s[kb][v];
+          }
+      }
       const int64_t o = strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) + (wave & 1) * 2048;
       strip_store(static_cast<T *>(a.strip) + o, s[0], s[1], lane);
       strip_store(static_cast<T *>(a.strip2) + o, dp[0], dp[1], lane);
@@ -468,13 +503,15 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
 // ----------------------------------------------------------------- apply ----
 // out (row, A) = scale * sum over keys of strip(row, key) X(key, A).  Work-group: 128 rows (wave: 32) x
 // 64 AHW columns, walking the key tiles; X tiles reach LDS by direct loads, the wave's strip fragments
-// its registers, a tile ahead of their use; one barrier per tile.  WEIGHT (forward): the strip is exp(S - m_t); the weights exp(m_t - LSE) bring
-// the tiles to one reference, and LSE is written here.
+// its registers, a tile ahead of their use; one barrier per tile.  A tile's product is formed by itself and then
+// added, where it is weighted or fp32 (see on top).  WEIGHT (forward): the strip is exp(S - m_t); the weights
+// exp(m_t - max m_t) bring the tiles to one reference, and the row's sum of weighted l_t normalises it and gives LSE.
+// fp32 backward: the sum of the tiles' l_t does, and 1 / sum is left for collect.
 struct ApplyArgs {
   const void *strip, *X;
   void *out;
-  const float *stats;
-  float *LSE;
+  float *LSE;   // forward
+  float *norm;  // fp32 backward: (head, rows)
 };
 
 template <typename T, int AHW, bool WEIGHT>
@@ -506,48 +543,40 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
   const T *Xh = static_cast<const T *>(p.X) + head * a.L * a.A + a0;
   const typename TT::template DMA<> dma_x(wave, lane, a.A);
   typename TT::Frag s0[NS], s1[NS];
-  const float *stats = WEIGHT ? p.stats + ((head * ntiles) * a.rows + rrow + col) * 2 : nullptr;
-  float m0 = 0.f, m1 = 0.f;  // m_t of the lane's row
-  auto load = [&](int t, Stage &st, typename TT::Frag(&s)[NS], float &m) __attribute__((always_inline)) {
-    if (WEIGHT) m = stats[(int64_t)t * a.rows * 2];
+  constexpr bool kStats = WEIGHT || kOwnSum<T>;
+  constexpr int kPer = WEIGHT ? 2 : 1;  // numbers per row and tile
+  const float *stats = a.stats + ((head * ntiles) * a.rows + rrow) * kPer;  // (read at col)
+  f32x2 ml0 = {0.f, 0.f}, ml1 = {0.f, 0.f};  // m_t (forward) and l_t of the lane's row
+  auto load = [&](int t, Stage &st, typename TT::Frag(&s)[NS], f32x2 &ml) __attribute__((always_inline)) {
+    const float *p = stats + (int64_t)t * a.rows * kPer;
+    if constexpr (WEIGHT) ml = reinterpret_cast<const f32x2 *>(p)[col];
+    else if constexpr (kStats) ml[1] = p[col];
 #pragma unroll
     for (int ah = 0; ah < AHW; ++ah) dma_x.load(Xh + (int64_t)t * 64 * a.A + ah * 64, st.X[ah]);
 #pragma unroll
     for (int i = 0; i < NS; ++i)
       s[i] = *reinterpret_cast<const typename TT::Frag *>(S + (int64_t)t * 4096 + i * (1024 / (int)sizeof(T)));
   };
-  load(0, st0, s0, m0);
+  load(0, st0, s0, ml0);
 
-  float lse2 = 0.f;
+  float M = -INFINITY;  // the row's largest m_t
   if (WEIGHT) {
-    // LSE = log sum_t l_t exp(m_t): the two lane halves take every other tile of their row,
-    // eight pairs at a time, their loads in flight together
+    // the two lane halves take every other tile of their row, eight at a time, their loads in flight together
     const int seen = a.causal ? (int)((a.q0 + (rrow | 63)) / 64) + 1 : ntiles;
     const int n = seen < ntiles ? seen : ntiles;
-    float M = -INFINITY, l = 0.f;
     for (int t0 = half; t0 < n; t0 += 16) {
-      f32x2 ml[8];
+      float m[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int t = t0 + 2 * j < n ? t0 + 2 * j : t0;
-        ml[j] = *reinterpret_cast<const f32x2 *>(stats + (int64_t)t * a.rows * 2);
+        m[j] = stats[((int64_t)t * a.rows + col) * 2];
       }
-      float mn = M;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) mn = fmaxf(mn, ml[j][0]);
-      if (mn > -INFINITY) {
-        l *= __builtin_amdgcn_exp2f(M - mn);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (t0 + 2 * j < n) l = fmaf(ml[j][1], __builtin_amdgcn_exp2f(ml[j][0] - mn), l);
-        M = mn;
-      }
+      for (int j = 0; j < 8; ++j) M = fmaxf(M, m[j]);
     }
-    const float MM = xhalf_max(M);  // finite: every row sees some key
-    l = xhalf_sum(M > -INFINITY ? l * __builtin_amdgcn_exp2f(M - MM) : 0.f);
-    lse2 = MM + __builtin_amdgcn_logf(l);
-    if (rows_here && half == 0 && a0 == 0) p.LSE[head * a.Lq + wrow + col] = lse2 * kLn2;
+    M = xhalf_max(M);  // finite: every row sees some key
   }
+  float l = 0.f, l_err = 0.f;  // the row's sum, and what its additions have lost so far
   const TT tt(lane);
   f32x16 o[2 * AHW];
 #pragma unroll
@@ -559,42 +588,63 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
   wait_vmem();
 #pragma unroll
   for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(s0[i]));  // (keeps the first loads in front of this wait)
-  asm volatile("" : "+v"(m0));
+  asm volatile("" : "+v"(ml0));
   __syncthreads();
-  auto step = [&](Stage &cur, typename TT::Frag(&sc)[NS], float mc, Stage &nxt, typename TT::Frag(&sn)[NS], float &mn)
+  auto step = [&](Stage &cur, typename TT::Frag(&sc)[NS], f32x2 ml, Stage &nxt, typename TT::Frag(&sn)[NS], f32x2 &mln)
       __attribute__((always_inline)) {
-    if (t + 1 < nt) load(t + 1, nxt, sn, mn);
-    const float w = WEIGHT ? __builtin_amdgcn_exp2f(mc - lse2) : 0.f;
+    if (t + 1 < nt) load(t + 1, nxt, sn, mln);
     if (rows_here && tile_seen(a, wrow, (int64_t)t * 64)) {
-      // with bf16 the weight cannot enter the operand without rounding it again: it goes to the tile's sum
-      constexpr bool kSum = WEIGHT && sizeof(T) == 2;
-      f32x16 c[kSum ? 2 * AHW : 1];
-      if constexpr (kSum) {
-#pragma unroll
-        for (int db = 0; db < 2 * AHW; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+      const float w = WEIGHT ? __builtin_amdgcn_exp2f(ml[0] - M) : 1.f;
+      if constexpr (kStats) {
+        const float x = fmaf(w, ml[1], -l_err), sum = l + x;
+        l_err = (sum - l) - x;
+        l = sum;
       }
-      typename TT::Frag xf[2][2 * AHW];
-      pipelined<NS>(
-          [&](int s, int b) __attribute__((always_inline)) {
+      auto add = [&](f32x16 &sum, const f32x16 &c) __attribute__((always_inline)) {
 #pragma unroll
-            for (int db = 0; db < 2 * AHW; ++db) xf[b][db] = tt.cols(cur.X[db >> 1], s, db & 1);
-          },
-          [&](int s, int b) __attribute__((always_inline)) {
-            typename TT::Frag sf = sc[s];
-            if constexpr (WEIGHT && !kSum) sf *= w;
+        for (int v = 0; v < 16; ++v) sum[v] = WEIGHT ? fmaf(w, c[v], sum[v]) : sum[v] + c[v];
+      };
+      if constexpr (sizeof(T) == 4) {  // one block of 32 columns after the other: registers
+        f32x16 c;
+        typename TT::Frag xf[2];
+        pipelined<NS * 2 * AHW>(
+            [&](int i, int b) __attribute__((always_inline)) {
+              const int db = i / NS;
+              xf[b] = tt.cols(cur.X[db >> 1], i % NS, db & 1);
+            },
+            [&](int i, int b) __attribute__((always_inline)) {
+              if (i % (NS / 2) == 0) {
 #pragma unroll
-            for (int db = 0; db < 2 * AHW; ++db) {
-              f32x16 &acc = kSum ? c[kSum ? db : 0] : o[db];
-              acc = TT::mfma(xf[b][db], sf, acc);
-            }
-          });
-      if constexpr (kSum) {
+                for (int v = 0; v < 16; ++v) c[v] = 0.f;
+              }
+              c = TT::mfma(xf[b], sc[i % NS], c);
+              if (i % (NS / 2) == NS / 2 - 1) add(o[i / NS], c);
+            });
+      } else {
+        f32x16 c[WEIGHT ? 2 * AHW : 1];
+        if constexpr (WEIGHT) {
 #pragma unroll
-        for (int db = 0; db < 2 * AHW; ++db)
+          for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[db][v] = fmaf(w, c[db][v], o[db][v]);
+            for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+        }
+        typename TT::Frag xf[2][2 * AHW];
+        pipelined<NS>(
+            [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+              for (int db = 0; db < 2 * AHW; ++db) xf[b][db] = tt.cols(cur.X[db >> 1], s, db & 1);
+            },
+            [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+              for (int db = 0; db < 2 * AHW; ++db) {
+                f32x16 &acc = WEIGHT ? c[WEIGHT ? db : 0] : o[db];
+                acc = TT::mfma(xf[b][db], sc[s], acc);
+              }
+            });
+        if constexpr (WEIGHT) {
+#pragma unroll
+          for (int db = 0; db < 2 * AHW; ++db) add(o[db], c[db]);
+        }
       }
     }
     wait_vmem();
@@ -602,16 +652,21 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
     ++t;
   };
   while (t < nt) {
-    step(st0, s0, m0, st1, s1, m1);
+    step(st0, s0, ml0, st1, s1, ml1);
     if (t >= nt) break;
-    step(st1, s1, m1, st0, s0, m0);
+    step(st1, s1, ml1, st0, s0, ml0);
   }
   if (!rows_here) return;
+  const float norm = kStats ? 1.0f / l : 1.0f;
+  if (half == 0 && a0 == 0) {
+    if (WEIGHT) p.LSE[head * a.Lq + wrow + col] = fmaf(M, kLn2, logf(l));
+    else if (kStats) p.norm[head * a.rows + wrow + col] = norm;
+  }
   unsigned char *ot = (wave < 2 ? st0.X[0] : st1.X[0]) + (wave & 1) * (TT::kBytes / 2);  // (free after the last barrier)
   T *out = static_cast<T *>(p.out) + (head * a.Lq + wrow) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
-    TT::stage(ot, o[2 * ah], o[2 * ah + 1], WEIGHT ? 1.0f : a.scale, lane);
+    TT::stage(ot, o[2 * ah], o[2 * ah + 1], WEIGHT ? norm : a.scale * norm, lane);
     TT::flush(ot, out + ah * 64, 32, lane, a.A);
   }
 }
@@ -625,6 +680,7 @@ struct CollectArgs {
   const void *strip[2], *Y[2];
   void *out[2];
   float *acc[2];
+  const float *norm;  // fp32: (head, rows), the factors of the strips' rows
   float alpha[2];
   int add, keep;
 };
@@ -661,11 +717,17 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
   const StripDMA<T, RT> dma_s(wave, lane);
   const typename TT::template DMA<RT> dma_y(wave, lane, a.A);
   const uint32_t lds0 = lds_address(&st[0]);
+  // fp32: the row tile's factors.  (From registers, loaded a tile ahead, they cost the compiler's waits for all loads in
+  // flight: 181 us instead of 152 at B16 Z12 L512.)
+  __shared__ __attribute__((aligned(16))) float norm[kOwnSum<T> ? DEPTH * 64 : 4];
+  const float *norms = p.norm + head * a.rows;
   constexpr int kLoads = 2 * StripDMA<T, RT>::PER + AHW * TT::template DMA<RT>::PER;  // of a wave, per row tile
   auto load = [&](int tt_, int b) __attribute__((always_inline)) {  // row tile tt_ -> buffer b
     const int row = tt_ * RT;
     const T *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
     const uint32_t d = lds0 + (uint32_t)b * (uint32_t)sizeof(Stage);
+    if (kOwnSum<T> && wave == 0)  // (64 numbers for 32 rows)
+      lds_dma4_unseen(norms + row, lane * 4, lds_address(&norm[0]) + (uint32_t)b * 256);
     dma_s.load_unseen(s, d);
     dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
 #pragma unroll
@@ -683,6 +745,7 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
   for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+  static_assert(!kOwnSum<T> || DEPTH == 2, "kLoads does not count the first wave's factors");
   int b = 0;  // buffer of tile t
   for (; t < nt; ++t) {
     // tile t has arrived, and behind the barrier every wave is done with tile t - 1, whose buffer takes the next one
@@ -693,17 +756,37 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
     const Stage &cur = st[b];
     if (keys_here && tile_seen(a, (int64_t)t * RT, wtile)) {
       const unsigned char *S = cur.S[wave >> 1];
-      typename TT::Frag sf[2], yf[2][2 * AHW];
+      const float *n = norm + b * 64 + half * (TT::kSliceK / 2);
+      typename TT::Frag sf[2], nf[2], yf[2][2 * AHW];
+      f32x16 c[kOwnSum<T> ? 2 * AHW : 1];  // fp32: the row tile's own sum
+      if constexpr (kOwnSum<T>) {
+#pragma unroll
+        for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+      }
       pipelined<NS>(
           [&](int s, int b) __attribute__((always_inline)) {
             sf[b] = tt.cols(S, s, wave & 1);
+            if constexpr (kOwnSum<T>)
+              nf[b] = *reinterpret_cast<const typename TT::Frag *>(n + s * TT::kSliceK);
 #pragma unroll
             for (int db = 0; db < 2 * AHW; ++db) yf[b][db] = tt.cols(cur.Y[db >> 1], s, db & 1);
           },
           [&](int s, int b) __attribute__((always_inline)) {
+            if constexpr (kOwnSum<T>) sf[b] *= nf[b];
 #pragma unroll
-            for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(yf[b][db], sf[b], o[db]);
+            for (int db = 0; db < 2 * AHW; ++db) {
+              f32x16 &acc = kOwnSum<T> ? c[kOwnSum<T> ? db : 0] : o[db];
+              acc = TT::mfma(yf[b][db], sf[b], acc);
+            }
           });
+      if constexpr (kOwnSum<T>) {
+#pragma unroll
+        for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[db][v] += c[db][v];
+      }
     }
     b = b + 1 < DEPTH ? b + 1 : 0;
   }
@@ -742,7 +825,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // group's buffers lie in the workspace.
 struct StripPlan {
   int64_t heads, rows;
-  size_t strip, strip2, stats, acc_k, acc_v, total;
+  size_t strip, strip2, stats, norm, acc_k, acc_v, total;
 };
 
 // Sizes of a group's strips.  All heads and rows at once where that is at most kStripBytes; else groups of
@@ -777,6 +860,10 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
   p.strip = off; off += align256(scores * es);
   if (pass == 1) {
     p.strip2 = off; off += align256(scores * es);
+    if (dtype == RSA_F32) {
+      p.stats = off; off += align256(scores / 64 * 4);
+      p.norm = off; off += align256((size_t)p.heads * p.rows * 4 + 128);  // (collect reads it 64 at a time from row 32 k)
+    }
     if (p.rows < d.Lq) {
       p.acc_k = off; off += align256((size_t)p.heads * d.L * d.A * 4);
       p.acc_v = off; off += align256((size_t)p.heads * d.L * d.A * 4);
@@ -879,8 +966,7 @@ hipError_t forward_t(const Dims &d, int dtype, const void *Q, const void *K, con
       const int64_t nr = pl.rows < d.Lq - r0 ? pl.rows : d.Lq - r0;
       const StripArgs a = group_args<T>(d, pl, ws, h0, r0, nr, Q, K, V);
       RSA_TRY(launch_scores<T>(a, nh, false, st));
-      const ApplyArgs p = {a.strip, a.V, static_cast<T *>(O) + (h0 * d.Lq + r0) * d.A, a.stats,
-                           LSE + h0 * d.Lq + r0};
+      const ApplyArgs p = {a.strip, a.V, static_cast<T *>(O) + (h0 * d.Lq + r0) * d.A, LSE + h0 * d.Lq + r0, nullptr};
       RSA_TRY((launch_apply<T, true>(a, p, nh, st)));
     }
   }
@@ -901,12 +987,14 @@ hipError_t backward_t(const Dims &d, int dtype, const void *dO, const void *Q, c
       a.dO = static_cast<const T *>(dO) + q; a.O = static_cast<const T *>(O) + q;
       a.LSE_in = LSE + h0 * d.Lq + r0;
       RSA_TRY(launch_scores<T>(a, nh, true, st));
-      const ApplyArgs p = {a.strip2, a.K, static_cast<T *>(dQ) + q, nullptr, nullptr};
+      float *norm = reinterpret_cast<float *>(ws + pl.norm);
+      const ApplyArgs p = {a.strip2, a.K, static_cast<T *>(dQ) + q, nullptr, norm};
       RSA_TRY((launch_apply<T, false>(a, p, nh, st)));
       CollectArgs c{};
       c.strip[0] = a.strip; c.Y[0] = a.dO; c.out[0] = static_cast<T *>(dV) + k; c.alpha[0] = 1.0f;
       c.strip[1] = a.strip2; c.Y[1] = a.Q; c.out[1] = static_cast<T *>(dK) + k; c.alpha[1] = d.scale;
       c.acc[0] = reinterpret_cast<float *>(ws + pl.acc_v); c.acc[1] = reinterpret_cast<float *>(ws + pl.acc_k);
+      c.norm = norm;
       c.add = r0 > 0; c.keep = r0 + nr < d.Lq;
       RSA_TRY(launch_collect<T>(a, c, nh, st));
     }

@@ -173,3 +173,79 @@ def test_staged_strip_groups_and_edges(dtype, kw, heads):
     x = inputs.make_inputs(cfg)
     out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED)
     compare_heads(cfg, x, out, heads, mode=rsa.MODE_STAGED)
+
+
+def by_steps(cfg, Q, K, V, dO):
+    """The two-pass forward and backward of cfg's ranks put together from the step-level entry points."""
+    rb, re = cfg.ranks
+    N, c, (B, Z, L, A) = cfg.N, cfg.c, K.shape
+    desc = rsa.make_desc(K, N, causal=cfg.causal, rank_begin=rb, rank_end=re, mode=rsa.MODE_STAGED)
+    f32 = lambda *s: torch.zeros(s, dtype=torch.float32, device=K.device)
+    O, LSE, D, dQ = torch.empty_like(Q), f32(B, Z, cfg.Lq), f32(B, Z, cfg.Lq), torch.empty_like(Q)
+    dK, dV, S, dP, acc = f32(B, Z, L, A), f32(B, Z, L, A), f32(B, Z, c, L), f32(B, Z, c, L), f32(B, Z, c, A)
+    P, dS, one = torch.empty_like(S, dtype=K.dtype), torch.empty_like(S, dtype=K.dtype), torch.empty_like(acc, dtype=K.dtype)
+    for n in range(rb, re):
+        rows = slice((n - rb) * c, (n - rb + 1) * c)
+        ring = [(n - t) % N for t in range(N)]
+        for j in ring:
+            rsa.qk_step(desc, n, j, Q, K, S)
+        rsa.row_softmax(desc, n, S, P, LSE)
+        for t, j in enumerate(ring):
+            rsa.av_step(desc, n, j, P, V, acc, t > 0)
+        rsa.store(desc, acc, one)
+        O[:, :, rows] = one
+        rsa.bwd_rowdot(desc, n, dO, O, D)
+        for j in ring:
+            rsa.dp_step(desc, n, j, dO, V, dP)
+        rsa.softmax_bwd(desc, n, P, dP, D, dS)
+        for t, j in enumerate(ring):
+            rsa.dq_step(desc, n, j, dS, K, acc, t > 0)
+            rsa.dk_step(desc, n, j, dS, Q, dK, True)
+            rsa.dv_step(desc, n, j, P, dO, dV, True)
+        rsa.store(desc, acc, one)
+        dQ[:, :, rows] = one
+    return dict(O=O, LSE=LSE, dQ=dQ, dK=dK, dV=dV)
+
+
+def exact(cfg, Q, K, V, dO):
+    """The same in 64 bits."""
+    Q, K, V, dO = (t.double() for t in (Q, K, V, dO))
+    s = cfg.A ** -0.5
+    S = Q @ K.transpose(2, 3).contiguous() * s
+    if cfg.causal:
+        q = torch.arange(cfg.Lq, device=Q.device) + cfg.ranks[0] * cfg.c
+        S.masked_fill_(torch.arange(cfg.L, device=Q.device) > q[:, None], float("-inf"))
+    LSE = torch.logsumexp(S, -1)
+    P = torch.exp(S - LSE[..., None])
+    O = P @ V
+    dS = P * (dO @ V.transpose(2, 3).contiguous() - (dO * O).sum(-1, keepdim=True))
+    return dict(O=O, LSE=LSE, dQ=dS @ K * s, dK=dS.transpose(2, 3).contiguous() @ Q * s,
+                dV=P.transpose(2, 3).contiguous() @ dO)
+
+
+@pytest.mark.parametrize("kw,std", [
+    (dict(L=512, N=4), 1.0),
+    (dict(L=512, N=8), 4.0),                                        # scores of 60: what LSE's own rounding would cost
+    (dict(L=512, N=4, A=256), 1.0),
+    (dict(L=1984, N=1, A=128), 1.0),
+    (dict(L=2048, N=8, rb=3, re=4, A=192, causal=True), 1.0),
+    (dict(L=4096, N=8), 0.3),                                       # long sums of values of one size
+    (dict(L=8448, N=11, causal=True, Z=1), 1.0),                    # rows in several groups
+])
+def test_f32_is_as_exact_as_its_steps(kw, std):
+    """fp32 keeps the precision of the steps it fuses: the softmax by the row's own statistics, no row term inside a
+    contraction, sums over keys and rows in short chains.  Error: RMS against 64 bits over RMS of the result.  Two
+    fp32 pipelines that round in different places differ by a few percent of their error: at most 1.1 times the
+    steps' is allowed (measured 0.5 to 1.03; with row terms inside the contractions, one chain per sum and P from the rounded LSE,
+    2 to 6)."""
+    cfg = small_cfg("f32", **dict(dict(B=1, Z=2, seed=89), **kw))
+    x = inputs.make_inputs(cfg)
+    Q, K, V, dO = (upload(x[k], "f32") for k in ("Q", "K", "V", "dO"))
+    Q, K = Q * std, K * std
+    ref, steps = exact(cfg, Q, K, V, dO), by_steps(cfg, Q, K, V, dO)
+    desc = rsa.make_desc(K, cfg.N, causal=cfg.causal, rank_begin=cfg.ranks[0], rank_end=cfg.ranks[1], mode=rsa.MODE_STAGED)
+    got = dict(zip(("O", "LSE"), rsa.forward(desc, Q, K, V)))
+    got.update(zip(("dQ", "dK", "dV"), rsa.backward(desc, dO, Q, K, V, got["O"], got["LSE"])))
+    for k, r in ref.items():
+        e, e_steps = (float((t[k].double() - r).norm() / r.norm()) for t in (got, steps))
+        assert e <= 1.1 * e_steps, f"{k}: {e:.2e}, by steps {e_steps:.2e}"
