@@ -117,6 +117,7 @@ struct GemmArgs {
   MatView A, B;       // m-side and n-side operands
   int64_t M, N, K;    // multiples of 64
   int64_t kslabs;     // slabs of 64 k per split (split s takes slabs [s * kslabs, ...))
+  int64_t chain;      // fp32 results: slabs of 64 k that one chain of additions may take (see plan_gemm)
   void *out[3];       // plain: out[0] (+ split * M * out_ld elements for a k split); head-split: 3 tensors
   int64_t out_ld, out_rows;
   int out_Z, out_AH, out_split;  // head-split output: (B, out_Z, out_rows, 64 * out_AH) tensors
@@ -237,6 +238,30 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
 
+  // fp32 results of the smaller tiles: longer sums are folded into a second set of accumulators, chain by chain
+  constexpr bool FOLD = OUT_F32 && T <= 2;
+  f32x16 done[FOLD ? 2 : 1][FOLD ? T : 1];
+  int left = FOLD ? (int)g.chain * 2 : 0;  // slabs to the next fold
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) done[nb][mb][v] = 0.f;
+  }
+  auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          done[nb][mb][v] += acc[nb][mb][v];
+          acc[nb][mb][v] = 0.f;
+        }
+  };
+
   const HalfLanes hl(lane);
   int ca[T][2];  // transpose-read offsets of the wave's blocks of 32 m (which half of a tile: odd or even block)
 #pragma unroll
@@ -303,7 +328,22 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
       products(1);
       interleave();
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (FOLD) {
+        if (--left == 0) {
+          asm volatile("" ::: "memory");  // a real branch
+          fold();
+          left = (int)g.chain * 2;
+        }
+      }
     }
+  }
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[nb][mb][v] += done[nb][mb][v];
   }
   __syncthreads();
 
@@ -429,10 +469,14 @@ static MatView heads(const void *p0, const void *p1, const void *p2, int64_t row
 // of them its prologue and epilogue; a split result is written and added up.  (Measured with M x N x K swept from
 // 128 x 1856 x 28224 to 1664 x 5000 x 11520 and each T: the choice is within 10 % of the best on average.  T = 4 alone:
 // 512 x 1408 x 1408: 31.7 us, now 10; 896 x 576 x 576: 15.8, now 6.)
-struct GemmPlan { int T, KG, splits; };
-static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool groups) {
+// chain: where the result is kept in fp32, the slabs of 64 k that one chain of additions may take; its rounding error
+// grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
+// that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
+// 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
+struct GemmPlan { int T, KG, splits, chain; };
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool groups, int chain = 1 << 29) {
   const int kslabs = (int)(K / 64);
-  GemmPlan best{4, 1, 1};
+  GemmPlan best{4, 1, max_splits, chain};
   float least = 1e30f;
   for (int T = 4; T >= 1; T /= 2) {
     const uint32_t t = 64 * (uint32_t)T;
@@ -440,6 +484,7 @@ static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool 
     for (int next, s = 1; s <= max_splits; s = next) {
       next = s + (s < 4 ? 1 : (s < 8 ? 2 : (s < 16 ? 4 : (s < 32 ? 8 : 16))));
       if (s < max_splits && next > max_splits) next = max_splits;
+      if (T == 4 && (kslabs + s - 1) / s > chain) continue;
       const float w = tiles * (float)s, n = ceilf(w * (1.0f / 256)), slabs = 2.0f * (float)((kslabs + s - 1) / s);
       const float reduce = s > 1 ? 3.0f + (float)s * (float)(M * N) * (4.0f / 5e6f) : 0.0f;
       float us;
@@ -447,10 +492,10 @@ static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool 
       else if (T == 2) us = n < 2 ? 4.0f + slabs * 0.29f : 2.0f + ceilf(n * 0.5f) * (2.0f + slabs * 0.57f);
       else us = 2.0f + 1.5f * ceilf(n * 0.25f) + slabs * (n < 2 ? 0.20f : 0.13f * n);
       us += reduce;
-      if (us < least) { least = us; best = {T, 1, s}; }
+      if (us < least) { least = us; best = {T, 1, s, chain}; }
       if (T == 1 && groups && n < 2) {
         us = 4.5f + slabs * 0.155f + reduce;
-        if (us < least) { least = us; best = {1, 2, s}; }
+        if (us < least) { least = us; best = {1, 2, s, chain}; }
       }
     }
   }
@@ -458,7 +503,9 @@ static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool 
 }
 
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, int T, int KG>
-static hipError_t launch_gemm_as(GemmArgs &g, int splits, hipStream_t st) {
+static hipError_t launch_gemm_as(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
+  const int splits = p.splits;
+  g.chain = p.chain;
   g.ntiles = (int)((g.N + 64 * T - 1) / (64 * T));
   const int64_t mtiles = (g.M + 64 * T - 1) / (64 * T);
   g.kslabs = (g.K / 64 + splits - 1) / splits;
@@ -472,11 +519,11 @@ static hipError_t launch_gemm_as(GemmArgs &g, int splits, hipStream_t st) {
 }
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32>
 static hipError_t launch_gemm(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
-  if (p.T == 4) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 4, 1>(g, p.splits, st);
-  if (p.T == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 2, 1>(g, p.splits, st);
+  if (p.T == 4) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 4, 1>(g, p, st);
+  if (p.T == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 2, 1>(g, p, st);
   if constexpr (!OUT_F32)
-    if (p.KG == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 2>(g, p.splits, st);
-  return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 1>(g, p.splits, st);
+    if (p.KG == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 2>(g, p, st);
+  return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 1>(g, p, st);
 }
 
 // Most k splits of a weight-gradient product (the workspace is sized by it): as many as still give every CU at most
@@ -489,6 +536,12 @@ int proj_wgrad_splits(int64_t Mout, int64_t Nout, int64_t K) {
   if (s < 1) s = 1;
   if (s > 64) s = 64;
   return (int)s;
+}
+
+// Slabs of 64 k of one chain of fp32 additions in such a product: what that many splits leave to each.
+static int wgrad_chain(int64_t Mout, int64_t Nout, int64_t K) {
+  const int s = proj_wgrad_splits(Mout, Nout, K);
+  return (int)((K / 64 + s - 1) / s);
 }
 
 hipError_t proj_qkv(const Dims &d, int64_t H, const void *X, const void *W, void *Q, void *K, void *V,
@@ -528,7 +581,7 @@ hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O,
   g.M = ZA; g.N = H; g.K = M;
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [K][M]
   g.B = plain(dY, H);                           // [K][N]
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(ZA, H, M), false);
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(ZA, H, M), false, wgrad_chain(ZA, H, M));
   g.out[0] = plan.splits > 1 ? part : dWo; g.out_split = 0; g.out_ld = H;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess || plan.splits == 1) return e;
@@ -556,7 +609,7 @@ hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK
   g.M = H; g.N = N3; g.K = M;
   g.A = plain(X, H);                   // [K][M]
   g.B = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [K][N]
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(H, N3, M), false);
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(H, N3, M), false, wgrad_chain(H, N3, M));
   g.out[0] = plan.splits > 1 ? part : dW; g.out_split = 0; g.out_ld = N3;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess || plan.splits == 1) return e;
@@ -602,7 +655,8 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.M = Kp; g.N = Zt * A; g.K = rows;
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, linformer_splits(Kp, Zt, rows, A), false);
+  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, linformer_splits(Kp, Zt, rows, A), false,
+                                  wgrad_chain(g.M, g.N, g.K));
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess) return e;

@@ -161,3 +161,34 @@ def test_projection_error_codes():
 ])
 def test_projection_tile_sizes(B, Z, L, N, ranks, H, A):
     test_projections_forward_and_backward(B, Z, L, N, ranks, H, A)
+
+
+@pytest.mark.parametrize("B,Z,L,H,A", [
+    (8, 16, 2048, 1024, 64),    # dWo 1024 x 1024 over 16384 rows
+    (16, 12, 512, 768, 64),
+    (4, 8, 960, 512, 128),
+    (1, 31, 4160, 448, 64),     # a number of slabs that no chain divides
+])
+def test_weight_gradients_are_summed_in_short_chains(B, Z, L, H, A):
+    """fp32 weight gradients over K rows: a chain of additions is as long as splitting K until every CU has a 256 x 256
+    tile leaves it (at most 64 splits of at least 256 rows), however the kernel cuts the product.  The matrix core adds
+    16 products at a time, so a chain of n rows rounds n / 16 times at partial sums that grow with the root, and the
+    K / n chains once each: RMS error u sqrt(n / 32 + K / 2n) of the result's RMS, u = 0.55 * 2^-24 the RMS of one
+    rounding.  1.25 times that is allowed (measured 0.7 to 1.05 of the formula; chains up to four times as long: 1.4 to 2)."""
+    K, D = B * L, Z * A
+    g = torch.Generator(device="cuda").manual_seed(5)
+    mk = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    X, dY, W, Wo, O, dQ, dK, dV = (mk(B, L, H), mk(B, L, H), mk(H, 3 * D), mk(D, H)) + tuple(mk(B, Z, L, A) for _ in range(4))
+    desc = rsa.make_desc(O, 1)
+    rows = lambda t: t.permute(0, 2, 1, 3).reshape(K, D).double()
+    _, dWo = rsa.out_proj_bwd(desc, dY, O, Wo)
+    _, dW = rsa.qkv_proj_bwd(desc, dQ, dK, dV, X, W)
+    ref = rows(O).T.contiguous() @ dY.reshape(K, H).double()
+    ref3 = X.reshape(K, H).double().T.contiguous() @ torch.cat([rows(t) for t in (dQ, dK, dV)], 1)
+    for name, got, r in (("dWo", dWo, ref), ("dWqkv", dW, ref3)):
+        tiles = -(-r.shape[0] // 256) * -(-r.shape[1] // 256)
+        splits = max(1, min(64, 256 // tiles, K // 64 // 4))
+        n = 64 * -(-(K // 64) // splits)
+        bound = 1.25 * 0.55 * 2.0 ** -24 * np.sqrt(n / 32 + K / n / 2)
+        err = float((got.double() - r).norm() / r.norm())
+        assert err <= bound, f"{name}: {err:.2e} > {bound:.2e}"
