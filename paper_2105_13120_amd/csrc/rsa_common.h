@@ -78,10 +78,14 @@ __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(
 
 // A direct global->LDS load (16 bytes per lane, landing at lds_base + 16 lane) that the compiler does not see: it
 // would wait for every such load in flight before the next LDS read where the buffers of a ring are one object.
-// The kernel orders them itself (wait_loads before the barrier that publishes them).
+// The kernel orders them itself (wait_loads before the barrier that publishes them).  lane_off: bytes, taken as unsigned.
 __device__ __forceinline__ void lds_dma16_unseen(const void *g, int lane_off, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                : : "v"(lane_off), "s"(g), "s"(lds_base) : "m0");
+}
+// Same, from an address of each lane's own.
+__device__ __forceinline__ void lds_dma16_unseen_far(const void *g, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_base) : "m0");
 }
 // Same, 4 bytes per lane, landing at lds_base + 4 lane.
 __device__ __forceinline__ void lds_dma4_unseen(const void *g, int lane_off, uint32_t lds_base) {

@@ -172,8 +172,12 @@ struct HalfLanes {
   }
 };
 
+// Longest row (elements) whose place in a tile of 64 fits the loads' unsigned 32-bit byte offset.
+constexpr int64_t kMaxLd = (int64_t)1 << 25;
+
 // WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
-template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG>
+// LONG: an operand with rows of more than kMaxLd elements; its loads take 64-bit addresses per lane.
+template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG, bool LONG>
 __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) {
   constexpr int HT = 2 * T;         // half tiles per slab, and waves per group
   constexpr int BM = 64 * T, BN = 64 * T;
@@ -214,19 +218,24 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
                     "+s"(walk.mode), "+s"(walk.Z));
   TileCursor cur = is_b ? TileCursor(g.B, B_KROWS, tile, ks_begin) : TileCursor(g.A, A_KROWS, tile, ks_begin);
   const int64_t sub = krows ? 32 * walk.ld : 32;  // from a tile's first slab to its second
-  int g_off[4];  // bytes
+  uint32_t g_off[4];  // bytes; LONG: without the rows, which g_row has
+  int64_t g_row[LONG ? 4 : 1];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = j * 64 + lane, r8 = p >> 3, r4 = p >> 2;
     const int row = krows ? r8 : r4, cc = krows ? (p & 7) ^ swz_rot(r8) : (p & 3) ^ ((r4 >> 2) & 3);
-    g_off[j] = (row * (int)walk.ld + cc * 8) * 2;
+    g_off[j] = ((LONG ? 0u : (uint32_t)row * (uint32_t)walk.ld) + cc * 8) * 2;
+    if constexpr (LONG) g_row[j] = row * walk.ld;
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)&lds_[grp][0][wave][0];
   auto issue = [&](int i) __attribute__((always_inline)) {  // slab i (called for 0, 1, 2, ... in turn)
-    const void *src = cur.ptr + ((i & 1) ? sub : 0);
+    const uint16_t *src = cur.ptr + ((i & 1) ? sub : 0);
     const uint32_t dst = lds0 + (uint32_t)(i & 3) * (HT * kHalfBytes);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) lds_dma16_unseen(src, g_off[j], dst + j * 1024);
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (LONG) lds_dma16_unseen_far(src + g_row[j] + g_off[j] / 2, dst + j * 1024);
+      else lds_dma16_unseen(src, (int)g_off[j], dst + j * 1024);
+    }
     if (i & 1) cur.template advance<WIDE>(walk);
   };
 
@@ -464,6 +473,8 @@ static MatView heads(const void *p0, const void *p1, const void *p2, int64_t row
   return v;
 }
 
+static bool long_rows(const GemmArgs &g) { return g.A.ld > kMaxLd || g.B.ld > kMaxLd; }
+
 // Size of the work-groups' output tiles, groups per work-group and k splits: the candidate with the least estimated
 // time (us).  n work-groups per CU (of which 1, 2, 4 are in flight) cost per slab of 32 k what was measured, and a round
 // of them its prologue and epilogue; a split result is written and added up.  (Measured with M x N x K swept from
@@ -473,10 +484,13 @@ static MatView heads(const void *p0, const void *p1, const void *p2, int64_t row
 // grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
 // that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
 // 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
+// Rows of more than kMaxLd elements: T = 4 (the only one with such loads) and all splits.
 struct GemmPlan { int T, KG, splits, chain; };
-static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int max_splits, bool groups, int chain = 1 << 29) {
+static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, bool groups, int chain = 1 << 29) {
+  const int64_t M = g.M, N = g.N, K = g.K;
   const int kslabs = (int)(K / 64);
   GemmPlan best{4, 1, max_splits, chain};
+  if (long_rows(g)) return best;
   float least = 1e30f;
   for (int T = 4; T >= 1; T /= 2) {
     const uint32_t t = 64 * (uint32_t)T;
@@ -511,10 +525,16 @@ static hipError_t launch_gemm_as(GemmArgs &g, const GemmPlan &p, hipStream_t st)
   g.kslabs = (g.K / 64 + splits - 1) / splits;
   dim3 grid((unsigned)(mtiles * g.ntiles), (unsigned)splits), block(128 * T * KG);
   const bool wide = (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
+  if constexpr (T == 4 && !(OUT_F32 && !A_KROWS)) {  // (dE's operands are rows of heads)
+    if (long_rows(g)) {
+      hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true, T, KG, true>), grid, block, 0, st, g);
+      return hipGetLastError();
+    }
+  }
   if (wide)
-    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true, T, KG>), grid, block, 0, st, g);
+    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true, T, KG, false>), grid, block, 0, st, g);
   else
-    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, false, T, KG>), grid, block, 0, st, g);
+    hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, false, T, KG, false>), grid, block, 0, st, g);
   return hipGetLastError();
 }
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32>
@@ -552,7 +572,7 @@ hipError_t proj_qkv(const Dims &d, int64_t H, const void *X, const void *W, void
   g.B = plain(W, g.N);        // [K][N]
   g.out[0] = Q; g.out[1] = K; g.out[2] = V;
   g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
 }
 
 hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, void *Y, hipStream_t st) {
@@ -561,7 +581,7 @@ hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, voi
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [M][K], column tile = (half of a) head
   g.B = plain(Wo, H);                           // [K][N]
   g.out[0] = Y; g.out_split = 0; g.out_ld = H;
-  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
 }
 
 hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O, const void *Wo,
@@ -573,7 +593,7 @@ hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O,
     g.A = plain(dY, H);   // [M][K]
     g.B = plain(Wo, H);   // [N][K]
     g.out[0] = dO; g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
+    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g, 1, true), st);
     if (e != hipSuccess) return e;
   }
   // dWo = O^T dY: contraction over the rows
@@ -581,7 +601,7 @@ hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O,
   g.M = ZA; g.N = H; g.K = M;
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [K][M]
   g.B = plain(dY, H);                           // [K][N]
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(ZA, H, M), false, wgrad_chain(ZA, H, M));
+  const GemmPlan plan = plan_gemm(g, proj_wgrad_splits(ZA, H, M), false, wgrad_chain(ZA, H, M));
   g.out[0] = plan.splits > 1 ? part : dWo; g.out_split = 0; g.out_ld = H;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess || plan.splits == 1) return e;
@@ -601,7 +621,7 @@ hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK
     g.A = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [M][K]
     g.B = plain(W, N3);                  // [N][K]
     g.out[0] = dX; g.out_split = 0; g.out_ld = H;
-    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
+    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g, 1, true), st);
     if (e != hipSuccess) return e;
   }
   // dW = X^T [dQ | dK | dV]
@@ -609,7 +629,7 @@ hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK
   g.M = H; g.N = N3; g.K = M;
   g.A = plain(X, H);                   // [K][M]
   g.B = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [K][N]
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, proj_wgrad_splits(H, N3, M), false, wgrad_chain(H, N3, M));
+  const GemmPlan plan = plan_gemm(g, proj_wgrad_splits(H, N3, M), false, wgrad_chain(H, N3, M));
   g.out[0] = plan.splits > 1 ? part : dW; g.out_split = 0; g.out_ld = N3;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess || plan.splits == 1) return e;
@@ -655,7 +675,7 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.M = Kp; g.N = Zt * A; g.K = rows;
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
-  const GemmPlan plan = plan_gemm(g.M, g.N, g.K, linformer_splits(Kp, Zt, rows, A), false,
+  const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), false,
                                   wgrad_chain(g.M, g.N, g.K));
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
@@ -684,7 +704,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
     // (a gradient that overwrites X itself: X is read until dE is done, so its rows cannot hold partial sums)
     const uintptr_t x0 = (uintptr_t)X, dx0 = (uintptr_t)dX, bytes = (uintptr_t)(((Zt - 1) * L + rows) * A) * 2;
     if (x0 < dx0 + bytes && dx0 < x0 + bytes) most = 1;
-    const GemmPlan plan = plan_gemm(g.M, g.N, g.K, most < 1 ? 1 : (int)most, false);
+    const GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most, false);
     g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
     if (plan.splits > 1) {
       g.out[0] = dX; g.out_ld = A / 2; g.out_rows = L; g.part_heads = (int)part_heads;
@@ -705,7 +725,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
   g.A = plain(E, Kp);                                  // [M = token][K = k]
   g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
   g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
-  return launch_gemm<false, true, false>(g, plan_gemm(g.M, g.N, g.K, 1, true), st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
 }
 
 }  // namespace rsa

@@ -192,3 +192,36 @@ def test_weight_gradients_are_summed_in_short_chains(B, Z, L, H, A):
         bound = 1.25 * 0.55 * 2.0 ** -24 * np.sqrt(n / 32 + K / n / 2)
         err = float((got.double() - r).norm() / r.norm())
         assert err <= bound, f"{name}: {err:.2e} > {bound:.2e}"
+
+
+def test_rows_longer_than_32_bits_of_offset():
+    """H = 35 * 2^20: the rows of a tile span more than 2^32 bytes, those of half a tile more than 2^31, in operands read
+    along their rows (X, dY, Wo for dO) and across them (Wo for Y, dY for dWo)."""
+    H, A, edge = 35 << 20, 64, 1024
+    dev = torch.device("cuda")
+    g = torch.Generator(device=dev).manual_seed(3)
+    mk = lambda *s: torch.randn(s, generator=g, device=dev).bfloat16()
+    ends = lambda t, d: torch.cat((t.narrow(d, 0, edge), t.narrow(d, H - edge, edge)), d).float()
+
+    def edges(*s, dim):       # zero but for the first and last rows or columns: contractions over H are these alone
+        t = torch.zeros(s, dtype=torch.bfloat16, device=dev)
+        for at in (0, H - edge):
+            t.narrow(dim, at, edge).copy_(mk(*(edge if k == dim else n for k, n in enumerate(s))))
+        return t
+
+    def close(got, ref, tol=3e-3):                     # one rounding to bf16
+        assert float((got.float() - ref).norm() / ref.norm()) <= tol
+
+    O = mk(1, 1, 64, A)
+    desc = rsa.make_desc(O, 1)
+    X, W = edges(1, 64, H, dim=2), edges(H, 3 * A, dim=0)
+    close(torch.cat(rsa.qkv_proj(desc, X, W), -1)[0, 0], ends(X[0], 1) @ ends(W, 0))
+    dY, Wo = X, torch.stack([mk(H) for _ in range(A)])
+    del X, W
+    dO, dWo = rsa.out_proj_bwd(desc, dY, O, Wo)
+    close(dO[0, 0], ends(dY[0], 1) @ ends(Wo, 1).T)
+    close(ends(dWo, 1), O[0, 0].float().T @ ends(dY[0], 1), 1e-6)   # fp32, 64 products each
+    del dO, dWo, dY
+    Y = rsa.out_proj(desc, O, Wo)
+    for at in (0, H // 2, H - (1 << 20)):
+        close(Y[0].narrow(1, at, 1 << 20), O[0, 0].float() @ Wo.narrow(1, at, 1 << 20).float())
