@@ -97,7 +97,10 @@ int rsa_version(void);
 const char *rsa_strerror(int status);
 
 /* Bytes of device workspace rsa_forward (pass 0) or rsa_backward (pass 1)
- * needs for this descriptor; 0 if the descriptor is invalid. */
+ * needs for this descriptor; 0 if the descriptor is invalid.  Staged mode: the score
+ * strips of as many ranks and heads together as fit 512 MB (a few heads at a time,
+ * 192 MB, or at least one rank's rows, where not all fit).  A caller with less memory
+ * calls for fewer ranks at a time and adds up the partial dK, dV. */
 size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
 
 /*
@@ -105,6 +108,11 @@ size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
  * [rank_begin, rank_end) and ring step t, visit chunk j = (n - t) mod N:
  * scores of Q^n against K^j, full-row softmax over all L keys, O^n = sum_j
  * P^n_j V^j.  Writes O (dtype) and LSE_i = log sum_j exp(S_ij) (fp32).
+ * An output may lie over an input in staged mode, there and in rsa_backward: the
+ * results then wait in the workspace until the inputs have been read.  Tensor exactly
+ * over tensor of the same size (dQ over Q, dK over K) needs no more workspace, any
+ * other overlap room for all results besides one head's strips (RSA_ERR_WORKSPACE if
+ * ws_bytes does not hold them).  In fused mode outputs must not overlap inputs.
  * ws: workspace of at least rsa_workspace_bytes(d, 0) bytes (may be NULL if
  * that is 0).  Staged mode keeps the score strip there; fused mode needs it
  * only when the descriptor has so few query rows for its keys (one rank's

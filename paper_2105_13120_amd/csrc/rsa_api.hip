@@ -135,11 +135,15 @@ int rsa_forward(const rsa_desc *d, const void *Q, const void *K, const void *V, 
   if (!Q || !K || !V || !O || !LSE) return RSA_ERR_NULL;
   if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) || misaligned(LSE) || misaligned(ws))
     return RSA_ERR_UNSUPPORTED;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (dm.mode == RSA_MODE_STAGED) {
+    const void *const in[6] = {Q, K, V, nullptr, nullptr, nullptr};
+    void *const out[3] = {O, LSE, nullptr};
+    if (!ws || ws_bytes < rsa::strip_workspace_bytes(dm, d->dtype, 0, in, out)) return RSA_ERR_WORKSPACE;
+    return hip_status(rsa::strip_pass(dm, d->dtype, 0, in, out, ws, ws_bytes, st));
+  }
   const size_t need = workspace_bytes(dm, d->dtype, 0);
   if (need > 0 && (!ws || ws_bytes < need)) return RSA_ERR_WORKSPACE;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (dm.mode == RSA_MODE_STAGED)
-    return hip_status(rsa::strip_forward(dm, d->dtype, Q, K, V, O, LSE, ws, st));
   return hip_status(rsa::fused_forward(dm, Q, K, V, O, LSE, st, static_cast<float *>(ws)));
 }
 
@@ -153,11 +157,15 @@ int rsa_backward(const rsa_desc *d, const void *dO, const void *Q, const void *K
   if (misaligned(dO) || misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) ||
       misaligned(LSE) || misaligned(dQ) || misaligned(dK) || misaligned(dV) || misaligned(ws))
     return RSA_ERR_UNSUPPORTED;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (dm.mode == RSA_MODE_STAGED) {
+    const void *const in[6] = {Q, K, V, dO, O, LSE};
+    void *const out[3] = {dQ, dK, dV};
+    if (!ws || ws_bytes < rsa::strip_workspace_bytes(dm, d->dtype, 1, in, out)) return RSA_ERR_WORKSPACE;
+    return hip_status(rsa::strip_pass(dm, d->dtype, 1, in, out, ws, ws_bytes, st));
+  }
   const size_t need = workspace_bytes(dm, d->dtype, 1);
   if (!ws || ws_bytes < need) return RSA_ERR_WORKSPACE;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (dm.mode == RSA_MODE_STAGED)
-    return hip_status(rsa::strip_backward(dm, d->dtype, dO, Q, K, V, O, LSE, dQ, dK, dV, ws, st));
   return hip_status(rsa::fused_backward(dm, dO, Q, K, V, O, LSE, dQ, dK, dV, fused_nD(ws),
                                         fused_nL(dm, ws), st, fused_part(dm, ws), 1,
                                         rsa::fused_key_splits(dm)));

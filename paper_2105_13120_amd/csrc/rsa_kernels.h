@@ -5,6 +5,12 @@
 
 namespace rsa {
 
+// Whether two pieces of memory share a byte.
+inline bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 // --- staged (two-pass) steps: section 3.1 stage 1, Eq. 1's softmax, Eq. 3 ---
 hipError_t staged_qk_step(const Dims &d, int dtype, int n, int j, const void *Q, const void *K,
                           float *S, hipStream_t st);
@@ -32,10 +38,11 @@ hipError_t store_rows(int dtype, const float *src, void *dst, int64_t batches,
 
 // --- the two-pass layout as a whole (rsa_forward / rsa_backward in staged mode), bf16 and fp32 ---
 size_t strip_workspace_bytes(const Dims &d, int dtype, int pass);
-hipError_t strip_forward(const Dims &d, int dtype, const void *Q, const void *K, const void *V, void *O, float *LSE,
-                         void *ws, hipStream_t st);
-hipError_t strip_backward(const Dims &d, int dtype, const void *dO, const void *Q, const void *K, const void *V,
-                          const void *O, const float *LSE, void *dQ, void *dK, void *dV, void *ws, hipStream_t st);
+// ... and for a call whose results may lie over its inputs.  in: Q, K, V; dO, O, LSE (pass 0: nullptr);
+// out: O, LSE, nullptr or dQ, dK, dV.
+size_t strip_workspace_bytes(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3]);
+hipError_t strip_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], void *ws,
+                      size_t ws_bytes, hipStream_t st);
 
 // --- fused (online-softmax) path, bf16, A = 64 or 128 ---
 // Split of the walk over the keys (few query rows, many keys).  fused_fwd_plan: the forward's

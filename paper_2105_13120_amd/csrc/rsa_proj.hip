@@ -702,8 +702,8 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
     if (most > g.K / 256) most = g.K / 256;
     if (most > 64) most = 64;
     // (a gradient that overwrites X itself: X is read until dE is done, so its rows cannot hold partial sums)
-    const uintptr_t x0 = (uintptr_t)X, dx0 = (uintptr_t)dX, bytes = (uintptr_t)(((Zt - 1) * L + rows) * A) * 2;
-    if (x0 < dx0 + bytes && dx0 < x0 + bytes) most = 1;
+    const size_t bytes = (size_t)(((Zt - 1) * L + rows) * A) * 2;
+    if (overlap(X, bytes, dX, bytes)) most = 1;
     const GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most, false);
     g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
     if (plan.splits > 1) {

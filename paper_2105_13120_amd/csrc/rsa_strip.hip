@@ -822,11 +822,32 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // How the work is cut: `heads` heads and `rows` of their query rows per group of launches, and where a
-// group's buffers lie in the workspace.
+// group's buffers lie in the workspace; out: results that may not be written yet (see apart_plan), of `chunk` heads.
 struct StripPlan {
-  int64_t heads, rows;
+  int64_t heads, rows, chunk;
+  size_t out[3];
   size_t strip, strip2, stats, norm, acc_k, acc_v, total;
 };
+
+// Places a group's buffers from byte `off` of the workspace on.
+void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
+  const size_t es = dtype == RSA_BF16 ? 2 : 4, scores = (size_t)p.heads * p.rows * d.L;
+  p.strip = off; off += align256(scores * es);
+  if (pass == 1) {
+    p.strip2 = off; off += align256(scores * es);
+    if (dtype == RSA_F32) {
+      p.stats = off; off += align256(scores / 64 * 4);
+      p.norm = off; off += align256((size_t)p.heads * p.rows * 4 + 128);  // (collect reads it 64 at a time from row 32 k)
+    }
+    if (p.rows < d.Lq) {
+      p.acc_k = off; off += align256((size_t)p.heads * d.L * d.A * 4);
+      p.acc_v = off; off += align256((size_t)p.heads * d.L * d.A * 4);
+    }
+  } else {
+    p.stats = off; off += align256(scores / 64 * 8);
+  }
+  p.total = off;
+}
 
 // Sizes of a group's strips.  All heads and rows at once where that is at most kStripBytes; else groups of
 // heads of at most kCacheBytes, which the 256 MB infinity cache still holds when the next kernel reads them
@@ -855,23 +876,39 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
       if (p.rows > d.Lq) p.rows = d.Lq;
     }
   }
-  const size_t scores = (size_t)p.heads * p.rows * d.L;
-  size_t off = 0;
-  p.strip = off; off += align256(scores * es);
-  if (pass == 1) {
-    p.strip2 = off; off += align256(scores * es);
-    if (dtype == RSA_F32) {
-      p.stats = off; off += align256(scores / 64 * 4);
-      p.norm = off; off += align256((size_t)p.heads * p.rows * 4 + 128);  // (collect reads it 64 at a time from row 32 k)
-    }
-    if (p.rows < d.Lq) {
-      p.acc_k = off; off += align256((size_t)p.heads * d.L * d.A * 4);
-      p.acc_v = off; off += align256((size_t)p.heads * d.L * d.A * 4);
-    }
-  } else {
-    p.stats = off; off += align256(scores / 64 * 8);
+  place_group(p, d, dtype, pass, 0);
+  return p;
+}
+
+// Bytes of one head of the pass's results (O and LSE, or dQ, dK and dV) and inputs (Q, K, V; dO, O, LSE).
+struct HeadBytes {
+  size_t out[3], in[6];
+  HeadBytes(const Dims &d, int dtype, int pass) {
+    const size_t es = dtype == RSA_BF16 ? 2 : 4, q = (size_t)d.Lq * d.A * es, k = (size_t)d.L * d.A * es, l = (size_t)d.Lq * 4;
+    out[0] = q; out[1] = pass == 1 ? k : l; out[2] = pass == 1 ? k : 0;
+    in[0] = q; in[1] = in[2] = k; in[3] = in[4] = q; in[5] = l;
   }
-  p.total = off;
+};
+
+// The plan for results that lie over inputs: they stay in the workspace until these have been read, and are copied
+// then.  Where each lies tensor over tensor, head over head, that is a group's results at a time; else (whole) those of
+// all heads.  The groups take what is left of a workspace of `bytes`; 0: the least plan, one head's 128 rows at a time.
+StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
+  const HeadBytes hb(d, dtype, pass);
+  const int64_t all = (int64_t)d.B * d.Z;
+  StripPlan p{};
+  auto place = [&](int64_t heads, int64_t rows) {
+    p.heads = heads; p.rows = rows; p.chunk = whole ? all : heads;
+    size_t off = 0;
+    for (int i = 0; i < 3; ++i) { p.out[i] = off; off += align256(p.chunk * hb.out[i]); }
+    place_group(p, d, dtype, pass, off);
+    return p.total <= bytes;
+  };
+  for (int64_t h = strip_plan(d, dtype, pass).heads; bytes > 0 && h > 0; h = h * 7 / 8)
+    if (place(h, d.Lq)) return p;
+  for (int64_t r = d.Lq / 128 * 128; bytes > 0 && r > 128; r = r * 7 / 8 / 128 * 128)
+    if (place(1, r)) return p;
+  place(1, d.Lq < 128 ? d.Lq : 128);
   return p;
 }
 
@@ -956,9 +993,8 @@ StripArgs group_args(const Dims &d, const StripPlan &pl, char *ws, int64_t h0, i
 }
 
 template <typename T>
-hipError_t forward_t(const Dims &d, int dtype, const void *Q, const void *K, const void *V, void *O, float *LSE,
-                     char *ws, hipStream_t st) {
-  const StripPlan pl = strip_plan(d, dtype, 0);
+hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE,
+                     char *ws, const StripPlan &pl, hipStream_t st) {
   const int64_t heads = (int64_t)d.B * d.Z;
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;
@@ -974,9 +1010,9 @@ hipError_t forward_t(const Dims &d, int dtype, const void *Q, const void *K, con
 }
 
 template <typename T>
-hipError_t backward_t(const Dims &d, int dtype, const void *dO, const void *Q, const void *K, const void *V,
-                      const void *O, const float *LSE, void *dQ, void *dK, void *dV, char *ws, hipStream_t st) {
-  const StripPlan pl = strip_plan(d, dtype, 1);
+hipError_t backward_t(const Dims &d, const void *dO, const void *Q, const void *K, const void *V,
+                      const void *O, const float *LSE, void *dQ, void *dK, void *dV, char *ws, const StripPlan &pl,
+                      hipStream_t st) {
   const int64_t heads = (int64_t)d.B * d.Z;
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;
@@ -1001,24 +1037,88 @@ hipError_t backward_t(const Dims &d, int dtype, const void *dO, const void *Q, c
   }
   return hipSuccess;
 }
+
+__global__ void __launch_bounds__(256) copy_kernel(const u32x4 *from, u32x4 *to, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) to[i] = from[i];
+}
+hipError_t copy(const void *from, void *to, size_t bytes, hipStream_t st) {  // bytes: a multiple of 16
+  const int64_t n = (int64_t)(bytes / 16);
+  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, static_cast<const u32x4 *>(from),
+                     static_cast<u32x4 *>(to), n);
+  return hipGetLastError();
+}
+
+// Whether results lie over inputs: 0 none, 1 only tensor over tensor of the same size, 2 in some other way.
+int results_over_inputs(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3]) {
+  const HeadBytes hb(d, dtype, pass);
+  const size_t heads = (size_t)d.B * d.Z;
+  int over = 0;
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 6; ++j) {
+      if (!in[j] || !out[i] || !overlap(out[i], heads * hb.out[i], in[j], heads * hb.in[j])) continue;
+      const int how = out[i] == in[j] && hb.out[i] == hb.in[j] ? 1 : 2;
+      if (how > over) over = how;
+    }
+  return over;
+}
+
+template <typename T>
+hipError_t pass_t(const Dims &d, int pass, const void *const (&in)[6], void *const (&out)[3], char *ws,
+                  const StripPlan &pl, hipStream_t st) {
+  if (pass == 0) return forward_t<T>(d, in[0], in[1], in[2], out[0], static_cast<float *>(out[1]), ws, pl, st);
+  return backward_t<T>(d, in[3], in[0], in[1], in[2], in[4], static_cast<const float *>(in[5]), out[0], out[1], out[2],
+                       ws, pl, st);
+}
+
+// A pass over the heads in chunks, each with its results in the workspace until it is done.
+template <typename T>
+hipError_t pass_apart(const Dims &d, int pass, const void *const (&in)[6], void *const (&out)[3], char *ws,
+                      const StripPlan &pl, hipStream_t st) {
+  const HeadBytes hb(d, sizeof(T) == 2 ? RSA_BF16 : RSA_F32, pass);
+  const int64_t heads = (int64_t)d.B * d.Z;
+  for (int64_t h0 = 0; h0 < heads; h0 += pl.chunk) {
+    Dims dc = d;  // (the tensors are dense)
+    dc.B = 1; dc.Z = (int)(pl.chunk < heads - h0 ? pl.chunk : heads - h0);
+    const void *in_c[6];
+    void *tmp[3];
+    for (int j = 0; j < 6; ++j) in_c[j] = static_cast<const char *>(in[j]) + (in[j] ? h0 * hb.in[j] : 0);
+    for (int i = 0; i < 3; ++i) tmp[i] = ws + pl.out[i];
+    RSA_TRY(pass_t<T>(dc, pass, in_c, tmp, ws, pl, st));
+    for (int i = 0; i < 3; ++i)
+      if (hb.out[i]) RSA_TRY(copy(tmp[i], static_cast<char *>(out[i]) + h0 * hb.out[i], dc.Z * hb.out[i], st));
+  }
+  return hipSuccess;
+}
+
+hipError_t run_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], char *ws,
+                    size_t ws_bytes, hipStream_t st) {
+  const int over = results_over_inputs(d, dtype, pass, in, out);
+  if (over) {
+    const StripPlan pl = apart_plan(d, dtype, pass, over == 2, ws_bytes);
+    return dtype == RSA_BF16 ? pass_apart<uint16_t>(d, pass, in, out, ws, pl, st)
+                             : pass_apart<float>(d, pass, in, out, ws, pl, st);
+  }
+  const StripPlan pl = strip_plan(d, dtype, pass);
+  return dtype == RSA_BF16 ? pass_t<uint16_t>(d, pass, in, out, ws, pl, st) : pass_t<float>(d, pass, in, out, ws, pl, st);
+}
 #undef RSA_TRY
 
 }  // namespace
 
-size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) { return strip_plan(d, dtype, pass).total; }
-
-hipError_t strip_forward(const Dims &d, int dtype, const void *Q, const void *K, const void *V, void *O, float *LSE,
-                         void *ws, hipStream_t st) {
-  char *w = static_cast<char *>(ws);
-  return dtype == RSA_BF16 ? forward_t<uint16_t>(d, dtype, Q, K, V, O, LSE, w, st)
-                           : forward_t<float>(d, dtype, Q, K, V, O, LSE, w, st);
+size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) {
+  const size_t usual = strip_plan(d, dtype, pass).total, apart = apart_plan(d, dtype, pass, false, 0).total;
+  return usual > apart ? usual : apart;
 }
 
-hipError_t strip_backward(const Dims &d, int dtype, const void *dO, const void *Q, const void *K, const void *V,
-                          const void *O, const float *LSE, void *dQ, void *dK, void *dV, void *ws, hipStream_t st) {
-  char *w = static_cast<char *>(ws);
-  return dtype == RSA_BF16 ? backward_t<uint16_t>(d, dtype, dO, Q, K, V, O, LSE, dQ, dK, dV, w, st)
-                           : backward_t<float>(d, dtype, dO, Q, K, V, O, LSE, dQ, dK, dV, w, st);
+size_t strip_workspace_bytes(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3]) {
+  if (results_over_inputs(d, dtype, pass, in, out) < 2) return strip_workspace_bytes(d, dtype, pass);
+  return apart_plan(d, dtype, pass, true, 0).total;
+}
+
+hipError_t strip_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], void *ws,
+                      size_t ws_bytes, hipStream_t st) {
+  return run_pass(d, dtype, pass, in, out, static_cast<char *>(ws), ws_bytes, st);
 }
 
 }  // namespace rsa

@@ -249,3 +249,49 @@ def test_f32_is_as_exact_as_its_steps(kw, std):
     for k, r in ref.items():
         e, e_steps = (float((t[k].double() - r).norm() / r.norm()) for t in (got, steps))
         assert e <= 1.1 * e_steps, f"{k}: {e:.2e}, by steps {e_steps:.2e}"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kw", [
+    dict(B=2, Z=3, L=512, N=4, causal=True),
+    dict(B=1, Z=1, L=192, N=1, A=256),                  # results larger than the strips
+    dict(B=4, Z=5, L=2048, N=4),                        # heads in several groups
+    dict(B=1, Z=1, L=8448, N=11),                       # rows in several groups
+])
+def test_staged_results_over_inputs(dtype, kw):
+    """Gradients and O may be written over what they are computed from: same results as in buffers of their own (to the
+    order of the sums over groups of rows)."""
+    cfg = small_cfg(dtype, **dict(dict(seed=91), **kw))
+    x = inputs.make_inputs(cfg)
+    t = {k: upload(x[k], dtype) for k in ("Q", "K", "V", "dO")}
+    desc = rsa.make_desc(t["K"], cfg.N, causal=cfg.causal, mode=rsa.MODE_STAGED)
+    t["O"], t["LSE"] = rsa.forward(desc, t["Q"], t["K"], t["V"])
+    grads = dict(zip(("dQ", "dK", "dV"), rsa.backward(desc, t["dO"], t["Q"], t["K"], t["V"], t["O"], t["LSE"])))
+    tol = 1e-6 if dtype == "f32" else 1e-3
+
+    def same(got, ref, what):
+        assert float((got.float() - ref.float()).norm() / ref.float().norm()) <= tol, what
+
+    for over in (dict(dQ="Q"), dict(dQ="dO"), dict(dV="dO"), dict(dK="Q"), dict(dQ="K", dV="Q"), dict(dQ="O", dK="V"),
+                 dict(dQ="Q", dK="K", dV="V")):
+        u = {k: v.clone() for k, v in t.items()}
+        out = rsa.backward(desc, u["dO"], u["Q"], u["K"], u["V"], u["O"], u["LSE"], **{k: u[i] for k, i in over.items()})
+        for (k, ref), got in zip(grads.items(), out):
+            same(got, ref, (over, k))
+    for i in ("Q", "K", "V"):
+        u = {k: v.clone() for k, v in t.items()}
+        O, LSE = rsa.forward(desc, u["Q"], u["K"], u["V"], O=u[i])
+        same(O, t["O"], i)
+        assert float((LSE - t["LSE"]).abs().max()) <= 1e-5
+    # shifted by 64 rows: all results wait, or the workspace is too small for them
+    q = t["Q"].numel()
+    buf = torch.empty(q + 64 * cfg.A, dtype=t["Q"].dtype, device="cuda")
+    Q, dQ = (buf[i:i + q].view(t["Q"].shape) for i in (0, 64 * cfg.A))
+    Q.copy_(t["Q"])
+    args = (desc, t["dO"], Q, t["K"], t["V"], t["O"], t["LSE"], dQ)
+    big = torch.empty(rsa.workspace_bytes(desc, True) + 4 * q * 4, dtype=torch.uint8, device="cuda")
+    with pytest.raises(rsa.RSAError) as e:
+        rsa.backward(*args, ws=big[:q])
+    assert e.value.status == -4
+    for (k, ref), got in zip(grads.items(), rsa.backward(*args, ws=big)):
+        same(got, ref, ("shifted", k))
