@@ -268,6 +268,7 @@ int rsa_qkv_proj_bwd(const rsa_desc *d, int32_t H, const void *dQ, const void *d
  *    backward's ws is the same workspace.
  *  rsa_linformer_project_bwd: dX rows of the ranks' tokens = E dXp (other rows are left
  *    untouched), dE rows of the ranks' tokens = sum_{b,z} X dXp^T (other rows untouched).
+ *    dX may lie over X, or dE over E, but not both.
  */
 size_t rsa_linformer_workspace_bytes(const rsa_desc *d, int32_t Kp);
 int rsa_linformer_project(const rsa_desc *d, int32_t Kp, const void *X, const void *E,

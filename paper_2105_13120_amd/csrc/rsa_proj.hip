@@ -689,9 +689,24 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
 // dX rows (Zt, L, A) from row0 on = E dXp, and dE (rows, Kp) fp32 = sum over heads of X dXp^T.
 // dE first: with few rows its contraction over all heads is split, and the partial sums lie in the rows of dX that the
 // second product then overwrites (A / 2 floats per row and head, so a split takes 2 Kp / A heads).  64 rows, Kp = 128,
-// 180 heads of 128: one tile walked 23040 k in 427 us.
+// 180 heads of 128: one tile walked 23040 k in 427 us.  dE over E: dX, which reads E, comes first.
 hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, int A, const void *dXp,
                                  const void *X, const void *E, void *dX, float *dE, hipStream_t st) {
+  const size_t x_bytes = (size_t)(((Zt - 1) * L + rows) * A) * 2;
+  const bool dx_first = overlap(dE, (size_t)(rows * Kp) * 4, E, (size_t)(rows * Kp) * 2);
+  auto form_dx = [&]() -> hipError_t {
+    if (linformer_dx_supported(Kp, A)) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
+    GemmArgs g{};
+    g.M = rows; g.N = Zt * A; g.K = Kp;
+    g.A = plain(E, Kp);                                  // [M = token][K = k]
+    g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
+    g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
+    return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
+  };
+  if (dx_first) {
+    hipError_t e = form_dx();
+    if (e != hipSuccess) return e;
+  }
   {
     GemmArgs g{};
     g.M = rows; g.N = Kp; g.K = Zt * A;
@@ -702,8 +717,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
     if (most > g.K / 256) most = g.K / 256;
     if (most > 64) most = 64;
     // (a gradient that overwrites X itself: X is read until dE is done, so its rows cannot hold partial sums)
-    const size_t bytes = (size_t)(((Zt - 1) * L + rows) * A) * 2;
-    if (overlap(X, bytes, dX, bytes)) most = 1;
+    if (dx_first || overlap(X, x_bytes, dX, x_bytes)) most = 1;
     const GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most, false);
     g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
     if (plan.splits > 1) {
@@ -719,13 +733,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
       if (e != hipSuccess) return e;
     }
   }
-  if (linformer_dx_supported(Kp, A)) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
-  GemmArgs g{};
-  g.M = rows; g.N = Zt * A; g.K = Kp;
-  g.A = plain(E, Kp);                                  // [M = token][K = k]
-  g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
-  g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
-  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
+  return dx_first ? hipSuccess : form_dx();
 }
 
 }  // namespace rsa

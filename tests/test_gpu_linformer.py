@@ -169,6 +169,23 @@ def test_linformer_gradient_over_its_input(heads, rows, Kp, A):
     assert (dE2 - dE).abs().max() <= 4e-4 * dE.square().mean().sqrt()
 
 
+@pytest.mark.parametrize("heads,rows,Kp,A", [(180, 64, 64, 128), (12, 192, 320, 64), (16, 4096, 256, 64)])
+def test_linformer_gradient_over_its_matrix(heads, rows, Kp, A):
+    """dE (fp32) may lie over E (bf16): dX has read E before dE is written."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    X, E, dXp = (torch.randn(s, generator=g, device="cuda").bfloat16()
+                 for s in ((1, heads, rows, A), (rows, Kp), (1, heads, Kp, A)))
+    desc = rsa.make_desc(X, 1)
+    dX, dE = rsa.linformer_project_bwd(desc, dXp, X, E)
+    dE2 = torch.empty((rows, Kp), dtype=torch.float32, device="cuda")
+    E2 = dE2.view(-1).view(torch.bfloat16)[:rows * Kp].view(rows, Kp)
+    E2.copy_(E)
+    dX2, _ = rsa.linformer_project_bwd(desc, dXp, X, E2, dE=dE2)
+    assert torch.equal(dX2, dX)
+    # the same products summed in fp32 in another order: check_f32's bound, on each side of the sum
+    assert (dE2 - dE).abs().max() <= 4e-4 * dE.square().mean().sqrt()
+
+
 # dX by work-groups of 256 rows (enough rows and heads to fill the chip with them): the last work-group whole, with one,
 # two and three of its four 64-row tiles; every slice count of Kp; heads of 128.
 @pytest.mark.parametrize("heads,rows,Kp,A", [
