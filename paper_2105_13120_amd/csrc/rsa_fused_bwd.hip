@@ -755,15 +755,17 @@ int fused_bwd_dkdv_splits(const Dims &d) {
   return s < 2 ? 1 : (int)s;
 }
 
-template <int NQ, int AH, int WK, int QS>
-static void launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
+template <int NQ, int AH, int WK, int QS, int MASKS = kBothMasks>
+static hipError_t launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.L + 32 * WK - 1) / (32 * WK));
   a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * WK * QS);
-  if (d.causal)
-    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, false, AH, WK, QS>), grid, block, 0, st, a);
+  if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
+  if constexpr (MASKS & kCausal)
+    if (d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
+  if constexpr (MASKS & kNoMask)
+    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, false, AH, WK, QS>), grid, block, 0, st, a);
+  return hipGetLastError();
 }
 
 hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const void *K,
@@ -776,12 +778,12 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   // query rows, as in the forward (same sweep, forward + backward, us: W = 8: 29.4 -> 26.2; 96: 49.4 -> 44.9;
   // 252 causal: 104 -> 98).  Heads of 128 leave no registers for it.
   const int64_t W = (int64_t)d.B * d.Z * ((d.L + 127) / 128);
-  if (d.A == 128) launch_dkdv<2, 2, 4, 1>(d, a, splits, st);
-  else if (splits > 1 || W > (d.causal ? 256 : 128)) launch_dkdv<2, 1, 4, 1>(d, a, splits, st);
-  else if (W <= 32) launch_dkdv<1, 1, 1, 4>(d, a, 1, st);
-  else if (W <= 128) launch_dkdv<1, 1, 2, 4>(d, a, 1, st);
-  else launch_dkdv<1, 1, 2, 2>(d, a, 1, st);
-  hipError_t e = hipGetLastError();
+  hipError_t e;
+  if (d.A == 128) e = launch_dkdv<2, 2, 4, 1>(d, a, splits, st);
+  else if (splits > 1 || W > (d.causal ? 256 : 128)) e = launch_dkdv<2, 1, 4, 1>(d, a, splits, st);
+  else if (W <= 32) e = launch_dkdv<1, 1, 1, 4>(d, a, 1, st);
+  else if (W <= 128) e = launch_dkdv<1, 1, 2, 4>(d, a, 1, st);
+  else e = launch_dkdv<1, 1, 2, 2, kCausal>(d, a, 1, st);
   if (e != hipSuccess || splits == 1) return e;
   const int64_t n4 = (int64_t)d.B * d.Z * d.L * (d.A / 4);
   const dim3 rg = reduce_grid(n4), rb(kReduceBlock);
@@ -792,30 +794,36 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   return hipGetLastError();
 }
 
-template <bool PRE, int AH, int NK, int RW, int KS>
-static void launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
+template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
+static hipError_t launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.Lq + 32 * RW - 1) / (32 * RW));
   a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (32 * RW) == 0 ? (int)(d.c / 2 / (32 * RW)) : 0;
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * RW * KS);
-  if (d.causal)
-    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+  if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
+  if constexpr (MASKS & kCausal)
+    if (d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+  if constexpr (MASKS & kNoMask)
+    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+  return hipGetLastError();
 }
 
+// (PRE: heads of 64 only, see fused_backward)
 template <bool PRE>
-static void launch_dq(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
+static hipError_t launch_dq(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
   // (few work-groups: see the dK/dV kernel; W = 8: 29.4 -> 26.3, 96: 49.4 -> 44.1, 252 causal: 104 -> 94; heads
   // of 128, W = 64 causal: 100 -> 89, 256: 174 -> 162)
   const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
-  if (d.A == 128) {  // one key tile (two LDS tiles) per stage
-    if (splits > 1 || W > 256) launch_dq_as<PRE, 2, 1, 4, 1>(d, a, splits, st);
-    else if (d.causal || W <= 128) launch_dq_as<PRE, 2, 1, 2, 2>(d, a, 1, st);
-    else launch_dq_as<PRE, 2, 1, 4, 2>(d, a, 1, st);
-  } else if (splits > 1 || W > 256) launch_dq_as<PRE, 1, 2, 4, 1>(d, a, splits, st);
-  else if (W <= 32) launch_dq_as<PRE, 1, 1, 1, 4>(d, a, 1, st);
-  else launch_dq_as<PRE, 1, 1, 2, 2>(d, a, 1, st);
+  if constexpr (!PRE) {
+    if (d.A == 128) {  // one key tile (two LDS tiles) per stage
+      if (splits > 1 || W > 256) return launch_dq_as<PRE, 2, 1, 4, 1>(d, a, splits, st);
+      if (d.causal || W <= 128) return launch_dq_as<PRE, 2, 1, 2, 2>(d, a, 1, st);
+      return launch_dq_as<PRE, 2, 1, 4, 2, kNoMask>(d, a, 1, st);
+    }
+  }
+  if (splits > 1 || W > 256) return launch_dq_as<PRE, 1, 2, 4, 1>(d, a, splits, st);
+  if (W <= 32) return launch_dq_as<PRE, 1, 1, 1, 4>(d, a, 1, st);
+  return launch_dq_as<PRE, 1, 1, 2, 2>(d, a, 1, st);
 }
 
 // dQ = sum of the split walks' partial sums
@@ -832,8 +840,7 @@ hipError_t fused_bwd_dq(const Dims &d, const void *dO, const void *Q, const void
   BwdArgs a = make_bwd_args(d, dO, Q, K, V, nL, nD, dQ, nullptr, nullptr);
   a.part = part;
   if (!part) splits = 1;
-  launch_dq<false>(d, a, splits, st);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_dq<false>(d, a, splits, st);
   if (e != hipSuccess || splits == 1) return e;
   return dq_reduce(d, part, dQ, splits, st);
 }
@@ -846,8 +853,7 @@ hipError_t fused_bwd_dq_pre(const Dims &d, const void *dO, const void *Q, const 
   a.O = (const uint16_t *)O; a.LSE = LSE; a.nL_out = nL; a.nD_out = nD;
   a.part = part;
   if (!part) splits = 1;
-  launch_dq<true>(d, a, splits, st);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_dq<true>(d, a, splits, st);
   if (e != hipSuccess || splits == 1) return e;
   return dq_reduce(d, part, dQ, splits, st);
 }

@@ -441,16 +441,17 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
   if (sub == 0) LSE[row] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
-template <int R, int AH, int NK, int RW, int KS>
+template <int R, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
   a.tiles_per_head = (int)((d.Lq + RW * R - 1) / (RW * R));
   a.by_length = order_by_length(d, splits, (int64_t)400 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (RW * R) == 0 ? (int)(d.c / 2 / (RW * R)) : 0;
   dim3 grid((unsigned)(heads * a.tiles_per_head), (unsigned)splits);
-  if (d.causal)
-    hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
-  else
-    hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+  if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
+  if constexpr (MASKS & kCausal)
+    if (d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+  if constexpr (MASKS & kNoMask)
+    if (!d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
   return hipGetLastError();
 }
 
@@ -539,7 +540,7 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   } else if (splits > 1 || W > (c ? 576 : 256)) e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, splits, st);
   else if (W <= 32) e = launch_fwd<32, 1, 1, 1, 4>(d, a, heads, 1, st);
   else if (W <= (c ? 192 : 128)) e = launch_fwd<32, 1, 1, 2, 4>(d, a, heads, 1, st);
-  else if (c && W <= 256) e = launch_fwd<32, 1, 1, 2, 2>(d, a, heads, 1, st);
+  else if (c && W <= 256) e = launch_fwd<32, 1, 1, 2, 2, kCausal>(d, a, heads, 1, st);
   else if (c || walk >= 16) e = launch_fwd<32, 1, 1, 4, 2>(d, a, heads, 1, st);
   else e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, 1, st);
   if (e != hipSuccess || splits == 1) return e;

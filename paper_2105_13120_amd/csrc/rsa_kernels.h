@@ -44,6 +44,9 @@ size_t strip_workspace_bytes(const Dims &d, int dtype, int pass, const void *con
 hipError_t strip_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], void *ws,
                       size_t ws_bytes, hipStream_t st);
 
+// Masks that a kernel shape is chosen for (the launch rules): only these are instantiated.
+enum MaskUse { kNoMask = 1, kCausal = 2, kBothMasks = 3 };
+
 // --- fused (online-softmax) path, bf16, A = 64 or 128 ---
 // Split of the walk over the keys (few query rows, many keys).  fused_fwd_plan: the forward's
 // rows per work-group (big: 256, else 128) and its split count; part: its fp32 partial results,
