@@ -1112,8 +1112,10 @@ size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) {
 }
 
 size_t strip_workspace_bytes(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3]) {
-  if (results_over_inputs(d, dtype, pass, in, out) < 2) return strip_workspace_bytes(d, dtype, pass);
-  return apart_plan(d, dtype, pass, true, 0).total;
+  const size_t any = strip_workspace_bytes(d, dtype, pass);  // (what is asked of every call)
+  if (results_over_inputs(d, dtype, pass, in, out) < 2) return any;
+  const size_t whole = apart_plan(d, dtype, pass, true, 0).total;
+  return whole > any ? whole : any;
 }
 
 hipError_t strip_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], void *ws,
