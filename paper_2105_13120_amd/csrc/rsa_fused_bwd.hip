@@ -1,4 +1,4 @@
-// Fused Ring Self-Attention backward (bf16, A = 64): the derivative of Eq. 1
+// Fused Ring Self-Attention backward (bf16, A = 64 or 128): the derivative of Eq. 1
 // with the ring structure of section 3.2.2, without the score strip in memory.
 // P is recomputed from Q, K and the forward's LSE: P = exp(s QK^T - LSE).
 //
@@ -10,14 +10,14 @@
 //   into a bf16 operand instead would save the multiply and round the operand a second time:
 //   an error of 2^-9 per element that is the same for every score of a key (or query), adds up
 //   coherently in dK (or dQ) and more than doubles their largest error.
-//   dkdv kernel: a work-group owns 4*32 keys and walks the query tiles of every
+//   dkdv kernel: a work-group owns 32 WK keys (WK waves) and walks the query tiles of every
 //     simulated rank, starting with the rank that holds those keys (ring
 //     order); the sum over ranks that the ring would all-reduce is its loop.
 //       S' = Q K^T - LSE / s, dP' = dO V^T - D      (A: Q / dO rows from LDS; B: K / V registers;
 //                                                    the row terms are the accumulators' start)
 //       P = exp2(s log2e S'), dS = P o dP'
 //       dV^T += dO^T P, dK^T += Q^T dS   (A operand: LDS transpose reads; B: P / dS registers)
-//   dq kernel: a work-group owns 4*R query rows and walks the K/V tiles in ring
+//   dq kernel: a work-group owns RW*R query rows (RW waves) and walks the K/V tiles in ring
 //     order (the paper's second K ring pass):
 //       S'^T = K Q^T - LSE / s, P^T = exp2(s log2e S'^T),
 //       dP'^T = V dO^T - D, dS^T = P^T o dP'^T, dQ^T += K^T dS^T

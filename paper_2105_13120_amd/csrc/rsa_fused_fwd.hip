@@ -1,6 +1,6 @@
 // Fused Ring Self-Attention forward (bf16, A = 64 or 128).
 //
-// One work-group owns 4*R query rows of one head and walks the K/V chunks in
+// One work-group owns RW*R query rows of one head (RW waves, R each) and walks the K/V chunks in
 // ring order -- step t of rank n visits chunk j = (n - t) mod N, local chunk
 // first (section 3.1) -- keeping a running row max and row sum, so the score
 // strip S^n of Table 2 never reaches device memory.  The result is Eq. 1 /

@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
   const int ns0 = slabs_of(0, ks_begin);  // the first group has the most slabs
   const int ns = KG == 1 ? ns0 : slabs_of(grp, ks_begin);
 
-  // Wave w < 4 brings A's half tile w of every slab, wave w >= 4 B's half tile w - 4.  (A ragged edge refetches the
+  // Wave w < T brings A's half tile w of every slab, wave w >= T B's half tile w - T.  (A ragged edge refetches the
   // last tile; its outputs are never stored.)
   const bool is_b = wave >= T;
   const bool krows = is_b ? B_KROWS : A_KROWS;

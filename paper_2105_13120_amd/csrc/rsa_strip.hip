@@ -22,7 +22,7 @@
 // Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
-// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.68,
+// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.65,
 // bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; now 0.48, 80 to 95 TFLOP/s in
 // every kernel, of which the strips' traffic hides about half).
 //
