@@ -169,6 +169,23 @@ __device__ __forceinline__ float keep_bit(float x, uint32_t mask, int bit) {
   return __builtin_bit_cast(float, (t & __builtin_bit_cast(uint32_t, x)) | (~t & 0xff800000u));
 }
 
+// Division of a uniform x < 2^31 by a number that the host knows: the high half of a product, an add and a shift (the
+// round-up method of Granlund and Montgomery, "Division by invariant integers using multiplication", 1994).  The
+// division itself is 40 dependent vector instructions, and the prologues of the fused kernels held six to eight of them.
+struct FastDiv {
+  uint32_t d, mul, shift;
+  __host__ __device__ uint32_t operator()(uint32_t x) const {
+    return ((uint32_t)(((uint64_t)x * mul) >> 32) + x) >> shift;
+  }
+};
+inline FastDiv make_fast_div(int64_t d) {  // 1 <= d < 2^31
+  FastDiv f;
+  f.d = (uint32_t)d; f.shift = 0;
+  while (((uint64_t)1 << f.shift) < (uint64_t)f.d) ++f.shift;
+  f.mul = (uint32_t)((((((uint64_t)1 << f.shift) - f.d)) << 32) / f.d + 1);
+  return f;
+}
+
 // Work-group id remap for the 8 XCDs: hardware hands consecutive work-group
 // ids to XCDs round-robin, so id i runs on XCD i % 8.  Returns a logical id
 // such that each XCD gets one contiguous range of logical ids (work-groups
@@ -187,9 +204,9 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t id, uint32_t n, uint32_t 
 // a head, leaves the last heads' long tiles to the end: B8 Z16 L2048, forward, 148 us; in this order 97.)  With
 // a multiple of 8 heads the heads stay on their XCDs, since id % heads and the XCD id % 8 agree.
 // rank: the tile's place among the head's, 0 = the most work.
-__device__ __forceinline__ void longest_first(uint32_t id, uint32_t heads, uint32_t &head, uint32_t &rank) {
-  rank = id / heads;
-  head = id - rank * heads;
+__device__ __forceinline__ void longest_first(uint32_t id, const FastDiv &heads, uint32_t &head, uint32_t &rank) {
+  rank = heads(id);
+  head = id - rank * heads.d;
 }
 // Row tile of place `rank`: later rows see more keys.  Under zig-zag ownership (half: tiles per half-chunk, when they
 // divide it, else 0) the later half-chunks of the ranks come in rank order, then the earlier ones in reverse.
@@ -225,6 +242,11 @@ __host__ __device__ inline int64_t head_offset(int64_t head, int Z, const int64_
   return (int64_t)b * st[0] + (int64_t)(h - b * (uint32_t)Z) * st[1];
 }
 
+__host__ __device__ inline int64_t head_offset(uint32_t h, const FastDiv &Z, const int64_t *st) {
+  const uint32_t b = Z(h);
+  return (int64_t)b * st[0] + (int64_t)(h - b * Z.d) * st[1];
+}
+
 // Where a row of a strided output tensor lives, for kernels that walk (head, row) pairs flat:
 // flat_row = head * rows_per_head + row.
 struct OutLayout {
@@ -249,13 +271,13 @@ inline OutLayout make_out_layout(const int64_t *st, int64_t rows_per_head, int Z
 // h is a multiple of 64: the 64 rows of a tile are consecutive tokens in both layouts.
 struct RowMap {
   int64_t q0, c, h;
+  FastDiv by_c, by_h;
   int rb, last_half;  // first simulated rank; 2N - 1
   int zigzag;
+  // (rows and tokens are below 2^31: one head's K and V of that many would not fit the memory)
   __host__ __device__ int64_t operator()(int64_t r) const {
     if (!zigzag) return q0 + r;
-    // (32-bit division: rows are counted in memory that holds far fewer than 2^32 of them, and a uniform
-    // 64-bit division is a hundred scalar instructions)
-    const uint32_t q = (uint32_t)r / (uint32_t)c;
+    const uint32_t q = by_c((uint32_t)r);
     const int64_t rho = rb + (int64_t)q, w = r - (int64_t)q * c;
     return w < h ? rho * h + w : (last_half - rho) * h + (w - h);
   }
@@ -266,16 +288,76 @@ struct RowMap {
   }
   // rank that owns global token g
   __host__ __device__ int owner(int64_t g) const {
-    if (!zigzag) return (int)((uint32_t)g / (uint32_t)c);
-    const int hc = (int)((uint32_t)g / (uint32_t)h);
+    if (!zigzag) return (int)by_c((uint32_t)g);
+    const int hc = (int)by_h((uint32_t)g);
     return hc <= last_half / 2 ? hc : last_half - hc;
   }
 };
 inline RowMap make_row_map(const Dims &d) {
   RowMap m;
   m.q0 = (int64_t)d.rank_begin * d.c; m.c = d.c; m.h = d.c / 2;
+  m.by_c = make_fast_div(d.c); m.by_h = make_fast_div(m.h > 0 ? m.h : 1);
   m.rb = d.rank_begin; m.last_half = 2 * d.N - 1; m.zigzag = d.zigzag;
   return m;
 }
+
+// The ring walk of the forward and dQ kernels over a head's keys: ring step t of rank n visits chunk (n - t) mod N in
+// stages of 2^lg keys, numbered t * spc + ks.  Only stages with a key at or before token q_last count under the
+// causal mask; within a chunk they are its first `cnt`, since its keys (also the two half-chunks of zig-zag
+// ownership) come in ascending order.  A walk is moved by adding to ks and, past cnt, going on to the next chunk: a
+// few scalar instructions a step.  (Testing stage after stage took 1150 cycles of a stage's 3100 with four groups of
+// waves, 300 of 2300 with two; forward and backward of 18 heads of 1728 causal rows 81.6 -> 71.8 us, of 2 heads of 512
+// 27.7 -> 25.4, of one rank's 4096 rows against 65536 keys 3534 -> 3461.)
+template <bool CAUSAL>
+struct KeyWalk {
+  int n, N, c, h, last_half, spc, sph, lg, q_last, f_end;  // (sph: stages of a chunk's first run of keys)
+  int t, ks, cnt, lo, hi;  // lo, hi: key of stage ks is (ks < sph ? lo : hi) + (ks << lg)
+  bool have;
+  __host__ __device__ __forceinline__ int seen(int first, int most) const {  // stages of a run that starts at key `first`
+    if (q_last < first) return 0;
+    const int k = ((q_last - first) >> lg) + 1;
+    return k < most ? k : most;
+  }
+  __host__ __device__ __forceinline__ void chunk() {
+    int j = n - t;
+    if (j < 0) j += N;
+    if (h == 0) {
+      lo = hi = j * c;
+      cnt = CAUSAL ? seen(lo, spc) : spc;
+    } else {
+      lo = j * h;
+      const int second = (last_half - j) * h;
+      hi = second - h;
+      cnt = CAUSAL ? seen(lo, sph) : spc;
+      if (CAUSAL && cnt == sph) cnt += seen(second, spc - sph);
+    }
+    if (f_end - t * spc < cnt) cnt = f_end - t * spc;
+  }
+  // n_: rank of the first row; lg_: log2 of a stage's keys; splits, split: the share of the stages this walk takes
+  __host__ __device__ __forceinline__ void begin(const RowMap &m, int n_, int N_, int lg_, int q_last_, int splits, int split) {
+    n = n_; N = N_; lg = lg_; q_last = q_last_; last_half = m.last_half;
+    c = (int)m.c; h = m.zigzag ? (int)m.h : 0;
+    spc = c >> lg; sph = m.zigzag ? h >> lg : spc;
+    t = 0; ks = 0; f_end = N * spc; have = true;
+    if (splits > 1) {
+      const int per = (int)((uint32_t)(f_end + splits - 1) / (uint32_t)splits), b = split * per;
+      f_end = b + per < f_end ? b + per : f_end;
+      t = (int)((uint32_t)b / (uint32_t)spc);
+      ks = b - t * spc;
+      have = b < f_end;
+    }
+    if (have) { chunk(); ks = ks < cnt ? ks : cnt; skip(0); }  // (a split may start behind a chunk's last stage)
+  }
+  __host__ __device__ __forceinline__ void skip(int stages) {  // that many stages further on; have: there is such a stage
+    if (!have) return;
+    ks += stages;
+    while (ks >= cnt) {
+      ks -= cnt; ++t;
+      if (t * spc >= f_end) { have = false; return; }
+      chunk();
+    }
+  }
+  __host__ __device__ __forceinline__ int key() const { return (ks < sph ? lo : hi) + (ks << lg); }
+};
 
 }  // namespace rsa

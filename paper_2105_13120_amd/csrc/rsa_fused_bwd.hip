@@ -41,7 +41,8 @@ struct BwdArgs {
   int64_t L, c, Lq;
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q, dQ; K, V, dK, dV; O, dO
   RowMap map;  // local query row -> global token index
-  int N, Z, tiles_per_head;
+  int N;
+  FastDiv by_tiles, by_heads, by_Z;  // tiles of a head, heads, Z
   int by_length, half_tiles;    // causal: order of the tiles over the work-groups (longest_first)
   float cl2, scale, inv_scale;  // scale log2(e), scale, 1 / scale
 };
@@ -110,19 +111,19 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
   const int col = lane & 31, half = lane >> 5;
   uint32_t head_, kt_;  // under the causal mask the first keys are seen by the most rows
   if (CAUSAL && a.by_length) {
-    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, kt_);
+    longest_first(blockIdx.x, a.by_heads, head_, kt_);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x), tiles = a.tiles_per_head;
-    head_ = wg / tiles;
-    kt_ = wg % tiles;
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+    head_ = a.by_tiles(wg);
+    kt_ = wg - head_ * a.by_tiles.d;
   }
   const int64_t head = settled(head_), kt = settled(kt_);
-  const int64_t key0 = kt * BK;  // first key of the work-group
-  const int64_t wkey0 = key0 + wave * KW;             // first key of this wave
+  const int key0 = (int)kt * BK;          // first key of the work-group
+  const int wkey0 = key0 + wave * KW;     // first key of this wave
 
-  const int64_t kv_off = head_offset(head, a.Z, a.ks);
-  const uint16_t *Qh = a.Q + head_offset(head, a.Z, a.qs);
-  const uint16_t *dOh = a.dO + head_offset(head, a.Z, a.os);
+  const int64_t kv_off = head_offset((uint32_t)head, a.by_Z, a.ks);
+  const uint16_t *Qh = a.Q + head_offset((uint32_t)head, a.by_Z, a.qs);
+  const uint16_t *dOh = a.dO + head_offset((uint32_t)head, a.by_Z, a.os);
   const uint16_t *Kh = a.K + kv_off;
   const uint16_t *Vh = a.V + kv_off;
   const float *nLh = a.nL + head * a.Lq;
@@ -151,30 +152,46 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
     for (int v = 0; v < 16; ++v) { dv[db][v] = 0.f; dk_[db][v] = 0.f; }
 
   // Stages of NQ query tiles in ring order: start at the rank that owns key0.
-  const int nqt = (int)(a.Lq / 64);
+  const int nqt = (int)(a.Lq >> 6);
   const int nst = (nqt + NQ - 1) / NQ;
   int start = 0;
   {
-    const int64_t r = (int64_t)(a.map.owner(key0) - a.map.rb) * a.c;  // local row of that rank's first query
-    if (r >= 0 && r < a.Lq) start = (int)(r / (64 * NQ));
+    const int r = (a.map.owner(key0) - a.map.rb) * (int)a.c;  // local row of that rank's first query
+    if (r >= 0 && r < a.Lq) start = r / (64 * NQ);
   }
   auto st_of = [&](int i) { int q = start + i; return q >= nst ? q - nst : q; };
-  // a stage matters if some row of it can see the first key of the work-group
+  // With few keys (Table 3's projected keys) the walk over the query stages is split over
+  // gridDim.y work-groups, each writing fp32 partial sums that a second kernel adds up.
+  int i_begin = 0, i_end = nst;
+  if (gridDim.y > 1) {
+    const int per_split = (nst + (int)gridDim.y - 1) / (int)gridDim.y;
+    i_begin = (int)blockIdx.y * per_split;
+    i_end = i_begin + per_split < nst ? i_begin + per_split : nst;
+  }
+  // A stage matters if some row of it can see the first key of the work-group.  Under the causal mask with rows in token
+  // order these are the stages from that key's row on (none in front of `start`), else (zig-zag) each is asked.
+  const bool ask = CAUSAL && a.map.zigzag;
+  if (CAUSAL && !ask) {
+    const int d = key0 - (int)a.map.q0, first = d > 0 ? d / (64 * NQ) - start : 0;
+    if (first > i_begin) i_begin = first;
+    if (nst - start < i_end) i_end = nst - start;
+  }
   auto visible = [&](int i) {
-    if (!CAUSAL) return true;
     const int qt = st_of(i) * NQ;
     bool v = false;
 #pragma unroll
     for (int u = 0; u < NQ; ++u)
-      v = v || (qt + u < nqt && a.map((int64_t)(qt + u) * 64) + 63 >= key0);
+      v = v || (qt + u < nqt && (int)a.map((qt + u) * 64) + 63 >= key0);
     return v;
   };
-  // With few keys (Table 3's projected keys) the walk over the query stages is split over
-  // gridDim.y work-groups, each writing fp32 partial sums that a second kernel adds up.
-  const int per_split = (nst + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int i_begin = (int)blockIdx.y * per_split;
-  const int i_end = i_begin + per_split < nst ? i_begin + per_split : nst;
-  auto advance = [&](int i) { ++i; while (i < i_end && !visible(i)) ++i; return i; };
+  auto skip = [&](int i, int n) {  // n stages that matter further on
+    if (!ask) return i + n;
+    for (int k = 0; k < n && i < i_end; ++k) {
+      ++i;
+      while (i < i_end && !visible(i)) ++i;
+    }
+    return i;
+  };
 
   const TileDMAT<WK> dma_q(wave, lane, (int)q_ld), dma_o(wave, lane, (int)o_ld);
   auto load_stage = [&](int i, Stage &sn) __attribute__((always_inline)) {
@@ -197,20 +214,15 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
     }
   };
 
-  auto skip = [&](int i, int n) {
-    for (int k = 0; k < n && i < i_end; ++k) i = advance(i);
-    return i;
-  };
   int i0 = i_begin;  // position of the walk: group 0's stage
-  if (i0 < i_end && !visible(i0)) i0 = advance(i0);
+  if (ask && i0 < i_end && !visible(i0)) i0 = skip(i0, 1);
   int i = QS == 1 ? i0 : skip(i0, grp);  // this group's stage
   if (i < i_end) load_stage(i, stage0[grp]);
   wait_vmem();
   __syncthreads();
   // one stage: start the loads of the next stage into sn, compute on sc
   auto stage = [&](Stage &sc, Stage &sn) __attribute__((always_inline)) {
-    const int i0next = QS == 1 ? advance(i) : skip(i0, QS);
-    const int inext = QS == 1 ? i0next : skip(i0next, grp);
+    const int i0next = skip(i0, QS), inext = QS == 1 ? i0next : skip(i, QS);
     if (inext < i_end) load_stage(inext, sn);
 
     // The 32 MFMAs of a tile go in four groups of eight -- S', dP' of rows 0..31 (G0) and of
@@ -225,7 +237,7 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
     const int qt0 = st_of(i) * NQ;
     auto active = [&](int u) {
       const int qt = qt0 + u;
-      return (QS == 1 || i < i_end) && qt < nqt && (!CAUSAL || a.map((int64_t)qt * 64) + 63 >= wkey0);
+      return (QS == 1 || i < i_end) && qt < nqt && (!CAUSAL || (int)a.map(qt * 64) + 63 >= wkey0);
     };
     auto fetch = [&](int u, int qb) __attribute__((always_inline)) {
       // accumulators start from -LSE / scale and -D of their rows (same for all lanes of a half)
@@ -245,7 +257,7 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       if (active(u)) {
-        const int64_t qf = a.map((int64_t)(qt0 + u) * 64);  // token of the tile's first row
+        const int qf = (int)a.map((qt0 + u) * 64);  // token of the tile's first row
         const bool domask = CAUSAL && qf < wkey0 + KW - 1;
         bf16x8 pf[4], sf[4];  // [kk]: P and dS as B operands, k = query
         auto g12 = [&](int qb) __attribute__((always_inline)) {
@@ -260,8 +272,7 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
           const f32x16 &dp = dpacc[qb];
           if (domask) {
             // rows of the block of 32 that see the lane's key: all but the first n
-            const int64_t d64 = wkey0 + col - qf - qb * 32 - half * 4;
-            const uint32_t seen = ~low_bits(d64 > 32 ? 32 : (d64 < 0 ? 0 : (int)d64));
+            const uint32_t seen = ~low_bits(wkey0 + col - qf - qb * 32 - half * 4);
 #pragma unroll
             for (int v = 0; v < 16; ++v) sv[v] = keep_bit(sv[v], seen, (v >> 2) * 8 + (v & 3));
           }
@@ -365,7 +376,7 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
   }
 
   if (gridDim.y > 1) {  // fp32 partial sums: [dV | dK][split][head][key][64]
-    const int64_t heads = gridDim.x / a.tiles_per_head;
+    const int64_t heads = a.by_heads.d;
     const int64_t key = wkey0 + col;
     float *pv = a.part + (((int64_t)blockIdx.y * heads + head) * a.L + key) * A;
     float *pk = pv + (int64_t)gridDim.y * heads * a.L * A;
@@ -393,8 +404,8 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
     stage_block_T(ot, 0, dv[2 * ah], dv[2 * ah + 1], 1.0f, lane);
     stage_block_T(ot, 32, dk_[2 * ah], dk_[2 * ah + 1], a.scale, lane);
-    flush_rows<32>(ot, 0, a.dV + kv_off + wkey0 * kv_ld + ah * 64, a.L - wkey0, lane, (int)kv_ld);
-    flush_rows<32>(ot, 32, a.dK + kv_off + wkey0 * kv_ld + ah * 64, a.L - wkey0, lane, (int)kv_ld);
+    flush_rows<32>(ot, 0, a.dV + kv_off + (int64_t)wkey0 * kv_ld + ah * 64, a.L - wkey0, lane, (int)kv_ld);
+    flush_rows<32>(ot, 32, a.dK + kv_off + (int64_t)wkey0 * kv_ld + ah * 64, a.L - wkey0, lane, (int)kv_ld);
   }
 }
 
@@ -416,30 +427,31 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   const int col = lane & 31, half = lane >> 5;
   uint32_t head_, qt_;  // (order: see the forward)
   if (CAUSAL && a.by_length) {
-    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, qt_);
-    qt_ = row_tile_of_rank(qt_, a.tiles_per_head, a.half_tiles);
+    longest_first(blockIdx.x, a.by_heads, head_, qt_);
+    qt_ = row_tile_of_rank(qt_, a.by_tiles.d, a.half_tiles);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.tiles_per_head;
-    head_ = wg / tiles;
-    qt_ = CAUSAL ? tiles - 1 - wg % tiles : wg % tiles;
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.by_tiles.d;
+    head_ = a.by_tiles(wg);
+    qt_ = wg - head_ * tiles;
+    if (CAUSAL) qt_ = tiles - 1 - qt_;
   }
   const int64_t head = settled(head_), qt = settled(qt_);
   const int64_t row0 = qt * BM;
-  const int n = (a.map.rb + (int)((uint32_t)row0 / (uint32_t)a.c)) % a.N;  // rank that owns the first row (see the forward)
+  int n = a.map.rb + (int)a.map.by_c((uint32_t)row0);  // rank that owns the first row (see the forward)
+  if (n >= a.N) n %= a.N;
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
-  int64_t q_last = 0;
+  int q_last = 0;
+  if (CAUSAL) {
 #pragma unroll
-  for (int i = 0; i < (BM + 63) / 64; ++i)
-    if (row0 + i * 64 < a.Lq) {
-      const int64_t e = a.map(row0 + i * 64) + 63;
-      q_last = e > q_last ? e : q_last;
-    }
-  // tiles per run of consecutive tokens of a chunk: the chunk, or its half under zig-zag ownership
-  const int tpc = (int)(a.c / kTileKeys);
-  const int tpr = a.map.zigzag ? tpc / 2 : tpc;
+    for (int i = 0; i < (BM + 63) / 64; ++i)
+      if (row0 + i * 64 < a.Lq) {
+        const int e = (int)a.map(row0 + i * 64) + 63;
+        q_last = e > q_last ? e : q_last;
+      }
+  }
 
-  const int64_t kv_off = head_offset(head, a.Z, a.ks), q_off = head_offset(head, a.Z, a.qs);
-  const int64_t o_off = head_offset(head, a.Z, a.os);
+  const int64_t kv_off = head_offset((uint32_t)head, a.by_Z, a.ks), q_off = head_offset((uint32_t)head, a.by_Z, a.qs);
+  const int64_t o_off = head_offset((uint32_t)head, a.by_Z, a.os);
   const uint16_t *Qh = a.Q + q_off;
   const uint16_t *dOh = a.dO + o_off;
   const uint16_t *Kh = a.K + kv_off;
@@ -450,12 +462,11 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   // over an accumulator, are what S'^T and dP'^T start from.
   bf16x8 qreg[QB][4 * AH], greg[QB][4 * AH];
   int64_t qrow[QB];
-  int64_t qtok[QB];  // global token index of the lane's row
+  int qtok[QB];      // global token index of the lane's row
   f32x16 negl[QB], negd[QB];
   // first and last token of this wave's rows (R <= 64 rows inside one tile: a run of tokens)
   const int64_t wrow = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
-  const int64_t wq_first = a.map(wrow);
-  const int64_t wq_last = wq_first + R - 1;
+  const int wq_first = (int)a.map(wrow), wq_last = wq_first + R - 1;
 
   const TileLanes tl(lane);
 
@@ -467,28 +478,10 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
 #pragma unroll
       for (int v = 0; v < 16; ++v) dq[db][qb][v] = 0.f;
 
-  // The ring walk: ring step t visits chunk (n - t) mod N.  Tiles are taken NK at a time;
-  // a stage never straddles chunks when tiles-per-chunk is even, otherwise NK falls to 1.
-  const int nk = (tpr % NK == 0) ? NK : 1;
-  const int spc = tpc / nk;  // stages per chunk
-  // the walk's stages, numbered t * spc + ks, divided over gridDim.y work-groups (see the forward)
-  const int per_split = (a.N * spc + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int f_begin = (int)blockIdx.y * per_split;
-  const int f_end = f_begin + per_split < a.N * spc ? f_begin + per_split : a.N * spc;
-  auto k0_of = [&](int t, int ks) -> int64_t {
-    int j = n - t;
-    if (j < 0) j += a.N;
-    return a.map.key_of(j, (int64_t)ks * nk * kTileKeys);
-  };
-  auto advance = [&](int &t, int &ks) -> bool {
-    ++ks;
-    for (;;) {
-      if (ks >= spc) { ++t; ks = 0; }
-      if (t * spc + ks >= f_end) return false;
-      if (!CAUSAL || k0_of(t, ks) <= q_last) return true;
-      ks = spc;
-    }
-  };
+  // the ring walk, in stages of NK tiles, divided over gridDim.y work-groups (see the forward)
+  const int nk = NK == 1 || ((int)(a.map.zigzag ? a.map.h : a.map.c) & (kTileKeys * NK - 1)) == 0 ? NK : 1;
+  KeyWalk<CAUSAL> w, wg_;  // group 0's stage, this group's
+  w.begin(a.map, n, a.N, nk == 2 ? 7 : 6, q_last, gridDim.y, blockIdx.y);
   const TileDMAT<RW> dma(wave, lane, (int)kv_ld);
   auto load_stage = [&](int64_t k0, auto &Kn, auto &Vn) __attribute__((always_inline)) {
 #pragma unroll
@@ -503,19 +496,9 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
     }
   };
 
-  // n stages further on; false past the end
-  auto skip = [&](int &t, int &ks, int n) -> bool {
-    bool h = true;
-    for (int i = 0; i < n && h; ++i) h = advance(t, ks);
-    return h;
-  };
-  int t = f_begin / spc, kt = f_begin % spc;  // position of the walk: group 0's stage
-  bool have = f_begin < f_end;
-  if (CAUSAL && have && k0_of(t, kt) > q_last) have = advance(t, kt);
-  int tg_ = t, kg_ = kt;  // this group's stage
-  int &tg = KS == 1 ? t : tg_, &kg = KS == 1 ? kt : kg_;
-  bool mine = KS == 1 ? have : have && skip(tg, kg, grp);
-  if (mine) load_stage(k0_of(tg, kg), Ks0[grp], Vs0[grp]);
+  if (KS > 1) { wg_ = w; wg_.skip(grp); }
+  KeyWalk<CAUSAL> &g = KS == 1 ? w : wg_;
+  if (g.have) load_stage(g.key(), Ks0[grp], Vs0[grp]);
   // The rows this wave keeps in registers are fetched after the first stage's tiles are on their
   // way, so that the two latencies overlap (short walks, e.g. a few hundred projected keys, are
   // mostly prologue).
@@ -524,7 +507,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
     const int64_t r = row0 + wave * R + qb * 32 + col;
     qrow[qb] = r < a.Lq ? r : a.Lq - 1;
     const int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
-    qtok[qb] = a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
+    qtok[qb] = (int)a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk) {
       qreg[qb][dk] = *reinterpret_cast<const bf16x8 *>(Qh + qrow[qb] * q_ld + dk * 16 + half * 8);
@@ -563,17 +546,16 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   __syncthreads();
   // one stage: start the loads of the next stage into (Kn, Vn), compute on (Kc, Vc)
   auto stage = [&](auto &Kc, auto &Vc, auto &Kn, auto &Vn) __attribute__((always_inline)) {
-    const int64_t ks0 = k0_of(tg, kg);
-    int t2 = t, kt2 = kt;
-    const bool have_next = KS == 1 ? advance(t2, kt2) : skip(t2, kt2, KS);
-    int tg2 = t2, kg2 = kt2;
-    const bool mine_next = KS == 1 ? have_next : have_next && skip(tg2, kg2, grp);
-    if (mine_next) load_stage(k0_of(tg2, kg2), Kn, Vn);
+    const int ks0 = g.key();
+    const bool mine = KS == 1 || g.have;
+    w.skip(KS);
+    if (KS > 1) wg_.skip(KS);
+    if (g.have) load_stage(g.key(), Kn, Vn);
 
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
-    const int64_t k0 = ks0 + u * kTileKeys;
-    if ((KS == 1 || mine) && u < nk && (!CAUSAL || k0 <= wq_last)) {
+    const int k0 = ks0 + u * kTileKeys;
+    if (mine && u < nk && (!CAUSAL || k0 <= wq_last)) {
       const bool domask = CAUSAL && k0 + kTileKeys - 1 > wq_first;
       bf16x8 sf[QB][4];
 #pragma unroll
@@ -593,8 +575,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
             // keys of the block of 32 that the lane's row sees: the first n
-            const int64_t d64 = qtok[qb] + 1 - k0 - kb * 32 - half * 4;
-            const uint32_t seen = low_bits(d64 > 32 ? 32 : (d64 < 0 ? 0 : (int)d64));
+            const uint32_t seen = low_bits(qtok[qb] + 1 - k0 - kb * 32 - half * 4);
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[qb][v] = keep_bit(s[qb][v], seen, (v >> 2) * 8 + (v & 3));
           }
@@ -625,12 +606,10 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
 
     wait_vmem();
     __syncthreads();
-    t = t2; kt = kt2; have = have_next;
-    if (KS > 1) { tg = tg2; kg = kg2; mine = mine_next; }
   };
-  while (have) {
+  while (w.have) {
     stage(Ks0[grp], Vs0[grp], Ks1[grp], Vs1[grp]);
-    if (!have) break;
+    if (!w.have) break;
     stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
   }
 
@@ -670,7 +649,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   }
 
   if (gridDim.y > 1) {  // fp32 partial sum of this split: [split][head][row][64]
-    const int64_t heads = gridDim.x / a.tiles_per_head;
+    const int64_t heads = a.by_heads.d;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const int64_t r = row0 + wave * R + qb * 32 + col;
@@ -724,9 +703,9 @@ static BwdArgs make_bwd_args(const Dims &d, const void *dO, const void *Q, const
   a.part = nullptr;
   a.O = nullptr; a.LSE = nullptr; a.nL_out = nullptr; a.nD_out = nullptr;
   a.L = d.L; a.c = d.c; a.Lq = d.Lq; a.map = make_row_map(d);
-  a.N = d.N; a.Z = d.Z; a.cl2 = d.scale * kLog2e; a.scale = d.scale; a.inv_scale = 1.0f / d.scale;
+  a.N = d.N; a.by_Z = make_fast_div(d.Z); a.by_heads = make_fast_div((int64_t)d.B * d.Z); a.cl2 = d.scale * kLog2e; a.scale = d.scale; a.inv_scale = 1.0f / d.scale;
   for (int k = 0; k < 3; ++k) { a.qs[k] = d.qs[k]; a.ks[k] = d.ks[k]; a.os[k] = d.os[k]; }
-  a.tiles_per_head = 0; a.by_length = 0; a.half_tiles = 0;
+  a.by_tiles = make_fast_div(1); a.by_length = 0; a.half_tiles = 0;
   return a;
 }
 
@@ -757,9 +736,9 @@ int fused_bwd_dkdv_splits(const Dims &d) {
 
 template <int NQ, int AH, int WK, int QS, int MASKS = kBothMasks>
 static hipError_t launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
-  a.tiles_per_head = (int)((d.L + 32 * WK - 1) / (32 * WK));
+  a.by_tiles = make_fast_div((d.L + 32 * WK - 1) / (32 * WK));
   a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
-  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * WK * QS);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d), (unsigned)splits), block(64 * WK * QS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
     if (d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
@@ -796,10 +775,10 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
 
 template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
-  a.tiles_per_head = (int)((d.Lq + 32 * RW - 1) / (32 * RW));
+  a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
   a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (32 * RW) == 0 ? (int)(d.c / 2 / (32 * RW)) : 0;
-  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.tiles_per_head), (unsigned)splits), block(64 * RW * KS);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d), (unsigned)splits), block(64 * RW * KS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
     if (d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);

@@ -30,7 +30,8 @@ struct FwdArgs {
   int64_t L, c, Lq;
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q; K and V; O
   RowMap map;            // local query row -> global token index
-  int N, Z, tiles_per_head;
+  int N;
+  FastDiv by_tiles, by_heads, by_Z;  // row tiles of a head, heads, Z
   int by_length, half_tiles;  // causal: order of the row tiles over the work-groups (longest_first)
   float cl2;             // scale * log2(e)
   // split key walk (gridDim.y > 1): per split, head and row the unnormalised fp32 O and the pair
@@ -61,32 +62,33 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   const int col = lane & 31, half = lane >> 5;
   uint32_t head_, qt_;
   if (CAUSAL && a.by_length) {
-    longest_first(blockIdx.x, gridDim.x / a.tiles_per_head, head_, qt_);
-    qt_ = row_tile_of_rank(qt_, a.tiles_per_head, a.half_tiles);
+    longest_first(blockIdx.x, a.by_heads, head_, qt_);
+    qt_ = row_tile_of_rank(qt_, a.by_tiles.d, a.half_tiles);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.tiles_per_head;
-    head_ = wg / tiles;
-    qt_ = CAUSAL ? tiles - 1 - wg % tiles : wg % tiles;
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.by_tiles.d;
+    head_ = a.by_tiles(wg);
+    qt_ = wg - head_ * tiles;
+    if (CAUSAL) qt_ = tiles - 1 - qt_;
   }
   const int64_t head = settled(head_), qt = settled(qt_);
   const int64_t row0 = qt * BM;  // first local row of this work-group
   // rank that owns the first row (modulo N: with projected keys, Table 3, the rows are not
   // tokens of the key sequence and any chunk may come first)
-  const int n = (a.map.rb + (int)((uint32_t)row0 / (uint32_t)a.c)) % a.N;
+  int n = a.map.rb + (int)a.map.by_c((uint32_t)row0);
+  if (n >= a.N) n %= a.N;
   // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
-  int64_t q_last = 0;
+  int q_last = 0;
+  if (CAUSAL) {
 #pragma unroll
-  for (int i = 0; i < (BM + 63) / 64; ++i)
-    if (row0 + i * 64 < a.Lq) {
-      const int64_t e = a.map(row0 + i * 64) + 63;
-      q_last = e > q_last ? e : q_last;
-    }
-  // tiles per run of consecutive tokens of a chunk: the chunk, or its half under zig-zag ownership
-  const int tpc = (int)(a.c / kTileKeys);
-  const int tpr = a.map.zigzag ? tpc / 2 : tpc;
+    for (int i = 0; i < (BM + 63) / 64; ++i)
+      if (row0 + i * 64 < a.Lq) {
+        const int e = (int)a.map(row0 + i * 64) + 63;
+        q_last = e > q_last ? e : q_last;
+      }
+  }
 
-  const int64_t kv_off = head_offset(head, a.Z, a.ks);
-  const uint16_t *Qh = a.Q + head_offset(head, a.Z, a.qs);
+  const int64_t kv_off = head_offset((uint32_t)head, a.by_Z, a.ks);
+  const uint16_t *Qh = a.Q + head_offset((uint32_t)head, a.by_Z, a.qs);
   const uint16_t *Kh = a.K + kv_off;
   const uint16_t *Vh = a.V + kv_off;
   const int64_t q_ld = a.qs[2], kv_ld = a.ks[2], o_ld = a.os[2];
@@ -94,21 +96,20 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   // Q^T operand: lane (col, half) holds Q[row][dk*16 + half*8 .. +8]
   bf16x8 qreg[QB][4 * AH];
   int64_t qrow[QB];  // local row (clamped to the last row for a ragged tail)
-  int64_t qtok[QB];  // its global token index
+  int qtok[QB];  // its global token index
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     int64_t r = row0 + wave * R + qb * 32 + col;
     qrow[qb] = r < a.Lq ? r : a.Lq - 1;
     const int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
-    qtok[qb] = a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
+    qtok[qb] = (int)a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk)
       qreg[qb][dk] = *reinterpret_cast<const bf16x8 *>(Qh + qrow[qb] * q_ld + dk * 16 + half * 8);
   }
   // first and last token of this wave's rows (R <= 64 rows inside one tile: a run of tokens)
   const int64_t wrow = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
-  const int64_t wq_first = a.map(wrow);
-  const int64_t wq_last = wq_first + R - 1;
+  const int wq_first = (int)a.map(wrow), wq_last = wq_first + R - 1;
 
   const TileLanes tl(lane);
 
@@ -123,30 +124,13 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
       for (int v = 0; v < 16; ++v) o[db][qb][v] = 0.f;
   }
 
-  // The ring walk: ring step t visits chunk (n - t) mod N.  Tiles are taken NK at a time;
-  // a stage never straddles chunks when tiles-per-chunk is even, otherwise NK falls to 1.
-  const int nk = (tpr % NK == 0) ? NK : 1;
-  const int spc = tpc / nk;  // stages per chunk
-  // With few work-groups the walk's stages, numbered t * spc + ks, are divided over gridDim.y
-  // work-groups, each leaving an unnormalised partial result that a second kernel merges.
-  const int per_split = (a.N * spc + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int f_begin = (int)blockIdx.y * per_split;
-  const int f_end = f_begin + per_split < a.N * spc ? f_begin + per_split : a.N * spc;
-  auto k0_of = [&](int t, int ks) -> int64_t {
-    int j = n - t;
-    if (j < 0) j += a.N;
-    return a.map.key_of(j, (int64_t)ks * nk * kTileKeys);
-  };
-  // next stage of the ring walk that holds a visible key for some row of this work-group
-  auto advance = [&](int &t, int &ks) -> bool {
-    ++ks;
-    for (;;) {
-      if (ks >= spc) { ++t; ks = 0; }
-      if (t * spc + ks >= f_end) return false;
-      if (!CAUSAL || k0_of(t, ks) <= q_last) return true;
-      ks = spc;  // later stages of this chunk start even further right
-    }
-  };
+  // Tiles are taken NK at a time; a stage never straddles runs of consecutive tokens of a chunk (the chunk, or its
+  // half under zig-zag ownership) when their tiles divide by NK, otherwise NK falls to 1.
+  const int nk = NK == 1 || ((int)(a.map.zigzag ? a.map.h : a.map.c) & (kTileKeys * NK - 1)) == 0 ? NK : 1;
+  // With few work-groups the walk's stages are divided over gridDim.y work-groups, each leaving an unnormalised partial
+  // result that a second kernel merges.
+  KeyWalk<CAUSAL> w, wg_;  // group 0's stage, this group's
+  w.begin(a.map, n, a.N, nk == 2 ? 7 : 6, q_last, gridDim.y, blockIdx.y);
   const TileDMAT<RW> dma(wave, lane, (int)kv_ld);
   auto load_stage = [&](int64_t k0, auto &Kn, auto &Vn) __attribute__((always_inline)) {
 #pragma unroll
@@ -161,35 +145,24 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
     }
   };
 
-  // n stages further on; false past the end
-  auto skip = [&](int &t, int &ks, int n) -> bool {
-    bool h = true;
-    for (int i = 0; i < n && h; ++i) h = advance(t, ks);
-    return h;
-  };
-  int t = f_begin / spc, kt = f_begin % spc;  // position of the walk: group 0's stage
-  bool have = f_begin < f_end;
-  if (CAUSAL && have && k0_of(t, kt) > q_last) have = advance(t, kt);
-  int tg_ = t, kg_ = kt;  // this group's stage
-  int &tg = KS == 1 ? t : tg_, &kg = KS == 1 ? kt : kg_;
-  bool mine = KS == 1 ? have : have && skip(tg, kg, grp);
-  if (mine) load_stage(k0_of(tg, kg), Ks0[grp], Vs0[grp]);
+  if (KS > 1) { wg_ = w; wg_.skip(grp); }
+  KeyWalk<CAUSAL> &g = KS == 1 ? w : wg_;
+  if (g.have) load_stage(g.key(), Ks0[grp], Vs0[grp]);
   wait_vmem();
   __syncthreads();
   bool first = true;
   // one stage: start the loads of the next stage into (Kn, Vn), compute on (Kc, Vc)
   auto stage = [&](auto &Kc, auto &Vc, auto &Kn, auto &Vn) __attribute__((always_inline)) {
-    const int64_t ks0 = k0_of(tg, kg);
-    int t2 = t, kt2 = kt;
-    const bool have_next = KS == 1 ? advance(t2, kt2) : skip(t2, kt2, KS);
-    int tg2 = t2, kg2 = kt2;
-    const bool mine_next = KS == 1 ? have_next : have_next && skip(tg2, kg2, grp);
-    if (mine_next) load_stage(k0_of(tg2, kg2), Kn, Vn);
+    const int ks0 = g.key();
+    const bool mine = KS == 1 || g.have;
+    w.skip(KS);
+    if (KS > 1) wg_.skip(KS);
+    if (g.have) load_stage(g.key(), Kn, Vn);
 
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
-    const int64_t k0 = ks0 + u * kTileKeys;
-    const bool work = (KS == 1 || mine) && u < nk && (!CAUSAL || k0 <= wq_last);
+    const int k0 = ks0 + u * kTileKeys;
+    const bool work = mine && u < nk && (!CAUSAL || k0 <= wq_last);
     f32x16 s[2][QB];
     float tm[QB];
     auto scores = [&]() __attribute__((always_inline)) {
@@ -211,8 +184,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
           // keys of the tile that the lane's row sees: the first n, less the lane half's offset
-          const int64_t d64 = qtok[qb] + 1 - k0 - half * 4;
-          const int n = d64 > 64 ? 64 : (d64 < 0 ? 0 : (int)d64);
+          const int n = qtok[qb] + 1 - k0 - half * 4;
 #pragma unroll
           for (int kb = 0; kb < 2; ++kb) {
             const uint32_t seen = low_bits(n - kb * 32);
@@ -303,12 +275,10 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 
     wait_vmem();
     __syncthreads();
-    t = t2; kt = kt2; have = have_next;
-    if (KS > 1) { tg = tg2; kg = kg2; mine = mine_next; }
   };
-  while (have) {
+  while (w.have) {
     stage(Ks0[grp], Vs0[grp], Ks1[grp], Vs1[grp]);
-    if (!have) break;
+    if (!w.have) break;
     stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
   }
 
@@ -366,7 +336,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   }
 
   if (gridDim.y > 1) {  // partial result of this split
-    const int64_t heads = gridDim.x / a.tiles_per_head;
+    const int64_t heads = a.by_heads.d;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const float lt = xhalf_sum(l[qb]);
@@ -407,7 +377,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) stage_block_T(ot, qb * 32, o[2 * ah][qb], o[2 * ah + 1][qb], inv[qb], lane);
-    flush_rows<R>(ot, 0, a.O + head_offset(head, a.Z, a.os) + wr0 * o_ld + ah * 64, a.Lq - wr0, lane, (int)o_ld);
+    flush_rows<R>(ot, 0, a.O + head_offset((uint32_t)head, a.by_Z, a.os) + wr0 * o_ld + ah * 64, a.Lq - wr0, lane, (int)o_ld);
   }
 }
 
@@ -443,10 +413,10 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
 
 template <int R, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
-  a.tiles_per_head = (int)((d.Lq + RW * R - 1) / (RW * R));
+  a.by_tiles = make_fast_div((d.Lq + RW * R - 1) / (RW * R));
   a.by_length = order_by_length(d, splits, (int64_t)400 << 20);
   a.half_tiles = d.zigzag && d.c / 2 % (RW * R) == 0 ? (int)(d.c / 2 / (RW * R)) : 0;
-  dim3 grid((unsigned)(heads * a.tiles_per_head), (unsigned)splits);
+  dim3 grid((unsigned)(heads * a.by_tiles.d), (unsigned)splits);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
     if (d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
@@ -513,7 +483,7 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   a.Q = (const uint16_t *)Q; a.K = (const uint16_t *)K; a.V = (const uint16_t *)V;
   a.O = (uint16_t *)O; a.LSE = LSE;
   a.L = d.L; a.c = d.c; a.Lq = d.Lq; a.map = make_row_map(d);
-  a.N = d.N; a.Z = d.Z;
+  a.N = d.N; a.by_Z = make_fast_div(d.Z); a.by_heads = make_fast_div((int64_t)d.B * d.Z);
   for (int k = 0; k < 3; ++k) { a.qs[k] = d.qs[k]; a.ks[k] = d.ks[k]; a.os[k] = d.os[k]; }
   a.cl2 = d.scale * kLog2e;
   const int64_t heads = (int64_t)d.B * d.Z;
