@@ -26,6 +26,11 @@
 
 namespace rsa {
 
+// Which tile of which head the work-groups of a kernel take.
+struct TileOrder {
+  FastDiv by_tiles;           // tiles of a head
+  int by_length, half_tiles;  // causal: order of the tiles over the work-groups (longest_first)
+};
 struct BwdArgs {
   const uint16_t *Q, *K, *V, *dO;
   const float *nL, *nD;                 // -LSE / scale and -D per query row
@@ -42,8 +47,7 @@ struct BwdArgs {
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q, dQ; K, V, dK, dV; O, dO
   RowMap map;  // local query row -> global token index
   int N;
-  FastDiv by_tiles, by_heads, by_Z;  // tiles of a head, heads, Z
-  int by_length, half_tiles;    // causal: order of the tiles over the work-groups (longest_first)
+  FastDiv by_heads, by_Z;  // heads, Z
   float cl2, scale, inv_scale;  // scale log2(e), scale, 1 / scale
 };
 
@@ -92,30 +96,32 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(const uint16_t *dO,
 // both, dV and dK have twice the accumulators, and the kernel runs one wave per SIMD.
 // WK waves share the work-group's keys, 32 each; QS groups of such waves share the query rows: group g takes
 // every QS-th stage of the walk and the groups' sums are added in LDS.
+// id of ids: the work-group's place among those of this kind; buf0, buf1: the two stage buffers.
+template <int NQ, int AH>
+struct DkdvStage {
+  unsigned char Qt[NQ][AH][kTileBytes], dOs[NQ][AH][kTileBytes];
+  float lse[NQ][64], d[NQ][64];
+};
 template <int NQ, bool CAUSAL, int AH, int WK, int QS>
-__global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(BwdArgs a) {
+__device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &order, uint32_t id, uint32_t ids,
+                                          unsigned char *buf0, unsigned char *buf1) {
   constexpr int KW = 32;       // keys per wave
   constexpr int BK = WK * KW;  // keys per work-group
   constexpr int A = 64 * AH;
-  // The two stage buffers are separate objects, each addressed by name, so that the
-  // compiler knows a direct load into one cannot alias the LDS reads of the other.
-  struct Stage {
-    unsigned char Qt[NQ][AH][kTileBytes], dOs[NQ][AH][kTileBytes];
-    float lse[NQ][64], d[NQ][64];
-  };
-  __shared__ __attribute__((aligned(16))) Stage stage0[QS], stage1[QS];
+  using Stage = DkdvStage<NQ, AH>;
+  Stage *const stage0 = reinterpret_cast<Stage *>(buf0), *const stage1 = reinterpret_cast<Stage *>(buf1);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
   const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
   const int col = lane & 31, half = lane >> 5;
   uint32_t head_, kt_;  // under the causal mask the first keys are seen by the most rows
-  if (CAUSAL && a.by_length) {
-    longest_first(blockIdx.x, a.by_heads, head_, kt_);
+  if (CAUSAL && order.by_length) {
+    longest_first(id, a.by_heads, head_, kt_);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-    head_ = a.by_tiles(wg);
-    kt_ = wg - head_ * a.by_tiles.d;
+    const uint32_t wg = xcd_remap(id, ids);
+    head_ = order.by_tiles(wg);
+    kt_ = wg - head_ * order.by_tiles.d;
   }
   const int64_t head = settled(head_), kt = settled(kt_);
   const int key0 = (int)kt * BK;          // first key of the work-group
@@ -345,18 +351,17 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
 
   if constexpr (QS > 1) {
     // groups 1 .. QS - 1 leave dV in the first stage buffers and dK in the second, group 0 adds them
-    static_assert((QS - 1) * WK * 32 * A * 4 <= (int)sizeof(stage0), "room for the groups' sums");
+    static_assert((QS - 1) * WK * 32 * A * 4 <= QS * (int)sizeof(Stage), "room for the groups' sums");
     auto slot = [&](unsigned char *o, int g, int db) {
       return reinterpret_cast<f32x4 *>(o + (((g - 1) * WK + wave) * 2 * AH + db) * 4096);
     };
-    unsigned char *ov = reinterpret_cast<unsigned char *>(stage0), *ok = reinterpret_cast<unsigned char *>(stage1);
     if (grp > 0) {
 #pragma unroll
       for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          slot(ov, grp, db)[g * 64 + lane] = f32x4{dv[db][g * 4], dv[db][g * 4 + 1], dv[db][g * 4 + 2], dv[db][g * 4 + 3]};
-          slot(ok, grp, db)[g * 64 + lane] = f32x4{dk_[db][g * 4], dk_[db][g * 4 + 1], dk_[db][g * 4 + 2], dk_[db][g * 4 + 3]};
+          slot(buf0, grp, db)[g * 64 + lane] = f32x4{dv[db][g * 4], dv[db][g * 4 + 1], dv[db][g * 4 + 2], dv[db][g * 4 + 3]};
+          slot(buf1, grp, db)[g * 64 + lane] = f32x4{dk_[db][g * 4], dk_[db][g * 4 + 1], dk_[db][g * 4 + 2], dk_[db][g * 4 + 3]};
         }
     }
     __syncthreads();
@@ -366,7 +371,7 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
         for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const f32x4 x = slot(ov, q, db)[g * 64 + lane], y = slot(ok, q, db)[g * 64 + lane];
+            const f32x4 x = slot(buf0, q, db)[g * 64 + lane], y = slot(buf1, q, db)[g * 64 + lane];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { dv[db][g * 4 + e] += x[e]; dk_[db][g * 4 + e] += y[e]; }
           }
@@ -409,29 +414,39 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
   }
 }
 
+template <int NQ, bool CAUSAL, int AH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_kernel(BwdArgs a, TileOrder order) {
+  // The two stage buffers are separate objects, each addressed by name, so that the
+  // compiler knows a direct load into one cannot alias the LDS reads of the other.
+  __shared__ __attribute__((aligned(16))) unsigned char buf0[QS * sizeof(DkdvStage<NQ, AH>)], buf1[sizeof(buf0)];
+  dkdv_body<NQ, CAUSAL, AH, WK, QS>(a, order, blockIdx.x, gridDim.x, buf0, buf1);
+}
+
 // ---------------------------------------------------------------------- dQ ---
 // NK: key tiles per stage (one barrier per stage).  RW waves share the work-group's rows, R each; KS groups of
 // such waves share the keys, as in the forward.
+template <int AH, int NK>
+struct DqStage { unsigned char K[NK][AH][kTileBytes], V[NK][AH][kTileBytes]; };
 template <int R, bool CAUSAL, bool PRE, int AH, int NK, int RW, int KS>
-__global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdArgs a) {
+__device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order, uint32_t id, uint32_t ids,
+                                        unsigned char *buf0, unsigned char *buf1) {
   constexpr int QB = R / 32;
   constexpr int BM = RW * R;
   constexpr int A = 64 * AH;  // a head of 128 is two halves of 64: two LDS tiles per 64 keys
-  // two named stage buffers: see the dK/dV kernel
-  __shared__ __attribute__((aligned(16))) unsigned char Ks0[KS][NK][AH][kTileBytes], Ks1[KS][NK][AH][kTileBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char Vs0[KS][NK][AH][kTileBytes], Vs1[KS][NK][AH][kTileBytes];
+  using Stage = DqStage<AH, NK>;
+  Stage *const stage0 = reinterpret_cast<Stage *>(buf0), *const stage1 = reinterpret_cast<Stage *>(buf1);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
   const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / RW;
   const int col = lane & 31, half = lane >> 5;
   uint32_t head_, qt_;  // (order: see the forward)
-  if (CAUSAL && a.by_length) {
-    longest_first(blockIdx.x, a.by_heads, head_, qt_);
-    qt_ = row_tile_of_rank(qt_, a.by_tiles.d, a.half_tiles);
+  if (CAUSAL && order.by_length) {
+    longest_first(id, a.by_heads, head_, qt_);
+    qt_ = row_tile_of_rank(qt_, order.by_tiles.d, order.half_tiles);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.by_tiles.d;
-    head_ = a.by_tiles(wg);
+    const uint32_t wg = xcd_remap(id, ids, blockIdx.y), tiles = order.by_tiles.d;
+    head_ = order.by_tiles(wg);
     qt_ = wg - head_ * tiles;
     if (CAUSAL) qt_ = tiles - 1 - qt_;
   }
@@ -483,14 +498,14 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   KeyWalk<CAUSAL> w, wg_;  // group 0's stage, this group's
   w.begin(a.map, n, a.N, nk == 2 ? 7 : 6, q_last, gridDim.y, blockIdx.y);
   const TileDMAT<RW> dma(wave, lane, (int)kv_ld);
-  auto load_stage = [&](int64_t k0, auto &Kn, auto &Vn) __attribute__((always_inline)) {
+  auto load_stage = [&](int64_t k0, Stage &sn) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
       if (u < nk) {
 #pragma unroll
         for (int ah = 0; ah < AH; ++ah) {
-          dma.load(Kh + (k0 + u * kTileKeys) * kv_ld + ah * 64, Kn[u][ah]);
-          dma.load(Vh + (k0 + u * kTileKeys) * kv_ld + ah * 64, Vn[u][ah]);
+          dma.load(Kh + (k0 + u * kTileKeys) * kv_ld + ah * 64, sn.K[u][ah]);
+          dma.load(Vh + (k0 + u * kTileKeys) * kv_ld + ah * 64, sn.V[u][ah]);
         }
       }
     }
@@ -498,7 +513,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
 
   if (KS > 1) { wg_ = w; wg_.skip(grp); }
   KeyWalk<CAUSAL> &g = KS == 1 ? w : wg_;
-  if (g.have) load_stage(g.key(), Ks0[grp], Vs0[grp]);
+  if (g.have) load_stage(g.key(), stage0[grp]);
   // The rows this wave keeps in registers are fetched after the first stage's tiles are on their
   // way, so that the two latencies overlap (short walks, e.g. a few hundred projected keys, are
   // mostly prologue).
@@ -544,13 +559,13 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   }
   wait_vmem();
   __syncthreads();
-  // one stage: start the loads of the next stage into (Kn, Vn), compute on (Kc, Vc)
-  auto stage = [&](auto &Kc, auto &Vc, auto &Kn, auto &Vn) __attribute__((always_inline)) {
+  // one stage: start the loads of the next stage into sn, compute on sc
+  auto stage = [&](Stage &sc, Stage &sn) __attribute__((always_inline)) {
     const int ks0 = g.key();
     const bool mine = KS == 1 || g.have;
     w.skip(KS);
     if (KS > 1) wg_.skip(KS);
-    if (g.have) load_stage(g.key(), Kn, Vn);
+    if (g.have) load_stage(g.key(), sn);
 
 #pragma unroll
     for (int u = 0; u < NK; ++u) {
@@ -563,8 +578,8 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
         f32x16 s[QB], dp[QB];
 #pragma unroll
         for (int dk = 0; dk < 4 * AH; ++dk) {
-          const bf16x8 ka = tl.read_rows(Kc[u][dk >> 2], kb * 32, dk & 3);
-          const bf16x8 va = tl.read_rows(Vc[u][dk >> 2], kb * 32, dk & 3);
+          const bf16x8 ka = tl.read_rows(sc.K[u][dk >> 2], kb * 32, dk & 3);
+          const bf16x8 va = tl.read_rows(sc.V[u][dk >> 2], kb * 32, dk & 3);
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
             s[qb] = mfma_32x32x16(ka, qreg[qb][dk], dk == 0 ? negl[qb] : s[qb]);
@@ -596,7 +611,7 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
       for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-          const bf16x8 ka = tl.read_cols(Kc[u][db >> 1], kk * 16, db & 1);
+          const bf16x8 ka = tl.read_cols(sc.K[u][db >> 1], kk * 16, db & 1);
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) dq[db][qb] = mfma_32x32x16(ka, sf[qb][kk], dq[db][qb]);
         }
@@ -608,20 +623,18 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
     __syncthreads();
   };
   while (w.have) {
-    stage(Ks0[grp], Vs0[grp], Ks1[grp], Vs1[grp]);
+    stage(stage0[grp], stage1[grp]);
     if (!w.have) break;
-    stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
+    stage(stage1[grp], stage0[grp]);
   }
 
   if constexpr (KS > 1) {  // groups 1 .. KS - 1 leave their sums in the stage buffers, group 0 adds them
     static_assert(QB == 1, "32 rows per wave");
     constexpr int PARTS = 2 * AH;  // of 32 columns: 4 KiB per wave
-    static_assert((PARTS * (KS - 1) + 3) / 4 * RW * 4096 <= KS * NK * AH * kTileBytes, "room for the groups' sums");
+    static_assert((PARTS * (KS - 1) + 1) / 2 * RW * 4096 <= KS * (int)sizeof(Stage), "room for the groups' sums");
     auto slot = [&](int g, int part) -> f32x4 * {
       const int i = (g - 1) * PARTS + part;
-      unsigned char *o = (i & 3) == 0 ? &Ks0[0][0][0][0] : (i & 3) == 1 ? &Ks1[0][0][0][0]
-                         : (i & 3) == 2 ? &Vs0[0][0][0][0] : &Vs1[0][0][0][0];
-      return reinterpret_cast<f32x4 *>(o + ((i >> 2) * RW + wave) * 4096);
+      return reinterpret_cast<f32x4 *>(((i & 1) ? buf1 : buf0) + ((i >> 1) * RW + wave) * 4096);
     };
     if (grp > 0) {
 #pragma unroll
@@ -669,13 +682,45 @@ __global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_ke
   }
 
   // the wave's R x 64 block of dQ leaves through its own LDS tile as whole 128-byte rows
-  unsigned char *ot = wave == 0 ? Ks0[0][0][0] : (wave == 1 ? Ks1[0][0][0] : (wave == 2 ? Vs0[0][0][0] : Vs1[0][0][0]));
+  unsigned char *ot = ((wave & 1) ? buf1 : buf0) + (wave >> 1) * kTileBytes;
   const int64_t wr0 = row0 + wave * R;
 #pragma unroll
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) stage_block_T(ot, qb * 32, dq[2 * ah][qb], dq[2 * ah + 1][qb], a.scale, lane);
     flush_rows<R>(ot, 0, a.dQ + q_off + wr0 * q_ld + ah * 64, a.Lq - wr0, lane, (int)q_ld);
+  }
+}
+
+template <int R, bool CAUSAL, bool PRE, int AH, int NK, int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, R == 64 ? 1 : 2) fused_bwd_dq_kernel(BwdArgs a, TileOrder order) {
+  // (two named stage buffers: see the dK/dV kernel)
+  __shared__ __attribute__((aligned(16))) unsigned char buf0[KS * sizeof(DqStage<AH, NK>)], buf1[sizeof(buf0)];
+  dq_body<R, CAUSAL, PRE, AH, NK, RW, KS>(a, order, blockIdx.x, gridDim.x, buf0, buf1);
+}
+
+// --------------------------------------------------------- dQ and dK, dV ---
+// Both kernels in one grid, for sizes where each alone leaves the chip partly idle.
+// Work-groups are dealt out in eights (one per XCD), the two kinds in turn in proportion to their numbers.
+struct BothArgs {
+  BwdArgs a;
+  TileOrder kv, q;
+  uint32_t kv_wgs, q_wgs, kv_eights;
+  FastDiv by_eights;  // eights of both kinds
+};
+template <bool CAUSAL, int AH, int NQ, int WK, int QS, int NK, int RW, int KS>
+__global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_both_kernel(BothArgs b) {
+  static_assert(WK * QS == RW * KS, "one block size");
+  constexpr int KV = QS * (int)sizeof(DkdvStage<NQ, AH>), Q = KS * (int)sizeof(DqStage<AH, NK>);
+  __shared__ __attribute__((aligned(16))) unsigned char buf0[KV > Q ? KV : Q], buf1[KV > Q ? KV : Q];
+  const uint32_t e = blockIdx.x >> 3, x = blockIdx.x & 7, up = b.by_eights.d - 1;
+  const uint32_t before = b.by_eights(e * b.kv_eights + up), upto = b.by_eights((e + 1) * b.kv_eights + up);
+  if (upto > before) {
+    const uint32_t id = before * 8 + x;
+    if (id < b.kv_wgs) dkdv_body<NQ, CAUSAL, AH, WK, QS>(b.a, b.kv, id, b.kv_wgs, buf0, buf1);
+  } else {
+    const uint32_t id = (e - before) * 8 + x;
+    if (id < b.q_wgs) dq_body<32, CAUSAL, false, AH, NK, RW, KS>(b.a, b.q, id, b.q_wgs, buf0, buf1);
   }
 }
 
@@ -705,7 +750,6 @@ static BwdArgs make_bwd_args(const Dims &d, const void *dO, const void *Q, const
   a.L = d.L; a.c = d.c; a.Lq = d.Lq; a.map = make_row_map(d);
   a.N = d.N; a.by_Z = make_fast_div(d.Z); a.by_heads = make_fast_div((int64_t)d.B * d.Z); a.cl2 = d.scale * kLog2e; a.scale = d.scale; a.inv_scale = 1.0f / d.scale;
   for (int k = 0; k < 3; ++k) { a.qs[k] = d.qs[k]; a.ks[k] = d.ks[k]; a.os[k] = d.os[k]; }
-  a.by_tiles = make_fast_div(1); a.by_length = 0; a.half_tiles = 0;
   return a;
 }
 
@@ -734,16 +778,24 @@ int fused_bwd_dkdv_splits(const Dims &d) {
   return s < 2 ? 1 : (int)s;
 }
 
+// the order of a kernel whose work-groups own `own` of `n` rows (or keys) of every head
+static TileOrder make_order(const Dims &d, int64_t n, int own, int splits, bool rows) {
+  TileOrder o;
+  o.by_tiles = make_fast_div((n + own - 1) / own);
+  o.by_length = order_by_length(d, splits, (int64_t)128 << 20);
+  o.half_tiles = rows && d.zigzag && d.c / 2 % own == 0 ? (int)(d.c / 2 / own) : 0;
+  return o;
+}
+
 template <int NQ, int AH, int WK, int QS, int MASKS = kBothMasks>
-static hipError_t launch_dkdv(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
-  a.by_tiles = make_fast_div((d.L + 32 * WK - 1) / (32 * WK));
-  a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
-  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d), (unsigned)splits), block(64 * WK * QS);
+static hipError_t launch_dkdv(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
+  const TileOrder o = make_order(d, d.L, 32 * WK, splits, false);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d), (unsigned)splits), block(64 * WK * QS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
-    if (d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a);
+    if (d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, true, AH, WK, QS>), grid, block, 0, st, a, o);
   if constexpr (MASKS & kNoMask)
-    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, false, AH, WK, QS>), grid, block, 0, st, a);
+    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dkdv_kernel<NQ, false, AH, WK, QS>), grid, block, 0, st, a, o);
   return hipGetLastError();
 }
 
@@ -774,16 +826,14 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
 }
 
 template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
-static hipError_t launch_dq_as(const Dims &d, BwdArgs a, int splits, hipStream_t st) {
-  a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
-  a.by_length = order_by_length(d, splits, (int64_t)128 << 20);
-  a.half_tiles = d.zigzag && d.c / 2 % (32 * RW) == 0 ? (int)(d.c / 2 / (32 * RW)) : 0;
-  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d), (unsigned)splits), block(64 * RW * KS);
+static hipError_t launch_dq_as(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
+  const TileOrder o = make_order(d, d.Lq, 32 * RW, splits, true);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d), (unsigned)splits), block(64 * RW * KS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
-    if (d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+    if (d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, true, PRE, AH, NK, RW, KS>), grid, block, 0, st, a, o);
   if constexpr (MASKS & kNoMask)
-    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, AH, NK, RW, KS>), grid, block, 0, st, a);
+    if (!d.causal) hipLaunchKernelGGL((fused_bwd_dq_kernel<32, false, PRE, AH, NK, RW, KS>), grid, block, 0, st, a, o);
   return hipGetLastError();
 }
 
@@ -837,6 +887,55 @@ hipError_t fused_bwd_dq_pre(const Dims &d, const void *dO, const void *Q, const 
   return dq_reduce(d, part, dQ, splits, st);
 }
 
+template <int AH, int NQ, int WK, int QS, int NK, int RW, int KS>
+static hipError_t launch_both(const Dims &d, const BwdArgs &a, hipStream_t st) {
+  BothArgs b;
+  b.a = a;
+  b.kv = make_order(d, d.L, 32 * WK, 1, false);
+  b.q = make_order(d, d.Lq, 32 * RW, 1, true);
+  const int64_t heads = (int64_t)d.B * d.Z;
+  b.kv_wgs = (uint32_t)(heads * b.kv.by_tiles.d);
+  b.q_wgs = (uint32_t)(heads * b.q.by_tiles.d);
+  b.kv_eights = (b.kv_wgs + 7) / 8;
+  b.by_eights = make_fast_div(b.kv_eights + (b.q_wgs + 7) / 8);
+  const dim3 grid(8 * b.by_eights.d), block(64 * WK * QS);
+  if (d.causal) hipLaunchKernelGGL((fused_bwd_both_kernel<true, AH, NQ, WK, QS, NK, RW, KS>), grid, block, 0, st, b);
+  else hipLaunchKernelGGL((fused_bwd_both_kernel<false, AH, NQ, WK, QS, NK, RW, KS>), grid, block, 0, st, b);
+  return hipGetLastError();
+}
+
+// Whether dQ and dK, dV go in one grid, behind the preprocess kernel: 0, or the groups of waves on a walk (then 128 / groups
+// rows or keys per work-group).  One grid costs the preprocess launch (3 us and a second read of dO and O) and gives what
+// two grids leave idle: half-filled rounds, prologues at HBM speed, under the causal mask the ends of the longest walks,
+// which now lie beside the other kind's.  W: work-groups of 128 rows or keys per kind (512 places for A = 64, 256 for A =
+// 128).  The lines are those of a sweep over 1 .. 1500 heads of 192 .. 65536 rows; backward, us, two grids -> one:
+//   A = 64, four groups, W = 32: 512 rows 17.3 -> 13.9, 2048: 33.4 -> 19.6, 4096 causal: 69.5 -> 34.7;
+//   two, W = 48: 512 rows 19.9 -> 14.1; causal W = 128: 20.8 -> 15.5, 4096 rows, W = 192: 103 -> 67, 32768, W = 256: 682 -> 607;
+//   one, W = 128: 512 rows 20.8 -> 14.9, W = 384: 36.2 -> 32.2, 4096 rows: 208 -> 193, causal 167 -> 114, W = 768: 512 rows
+//   63.6 -> 57.2; but 2048 rows, W = 512: 119 -> 124, W = 704: 180 -> 186, causal W = 1120: 164 -> 170 (whole rounds);
+//   A = 128, two groups, W = 64: 512 rows 36.3 -> 18.5, 4096: 175 -> 74; one, W = 128: 512 rows 37.6 -> 25.4, 384: 78 -> 68,
+//   causal 4096 rows, W = 256: 223 -> 148; but W = 192: 112 -> 129, 512: 142 -> 150.
+static int both_groups(const Dims &d) {
+  // (one rank's share of a longer sequence, or many rows of few keys: one kind's walks are far longer than the other's)
+  const int64_t longer = d.L > d.Lq ? d.L : d.Lq, shorter = d.L > d.Lq ? d.Lq : d.L;
+  if (longer > 2 * shorter && longer > 1024) return 0;
+  const int64_t heads = (int64_t)d.B * d.Z, L = longer;
+  const int64_t W = heads * ((d.L + 127) / 128 + (d.Lq + 127) / 128) / 2;
+  if (d.A == 128) {
+    if (W <= 64 || (d.causal && L > 512 && W <= 128)) return 2;
+    if (W <= 128 || (W <= 460 && (d.causal || W > 256))) return 1;
+    return 0;
+  }
+  if (d.causal) {
+    if (W <= 32 || (W <= 64 && L >= 2048)) return 4;
+    if (W <= 128 || (W <= 224 && L >= 1024) || (W <= 256 && L >= 1536)) return 2;
+    return W <= 640 || (W <= 768 && (L >= 4096 || L <= 512)) || (W <= 1536 && L <= 320) ? 1 : 0;
+  }
+  if (W <= 32) return 4;
+  if (W <= 64) return 2;
+  return (L <= 8192 && (W <= 460 || (W > 512 && W <= 640))) || (L <= 512 && W <= 1536) ? 1 : 0;
+}
+
 hipError_t fused_backward(const Dims &d, const void *dO, const void *Q, const void *K,
                           const void *V, const void *O, const float *LSE, void *dQ, void *dK,
                           void *dV, float *nD, float *nL, hipStream_t st, float *part,
@@ -846,6 +945,17 @@ hipError_t fused_backward(const Dims &d, const void *dO, const void *Q, const vo
   // prologue costs the dQ kernel more registers than it has: there the row terms come from
   // the preprocess kernel.)
   hipError_t e;
+  // (dK, dV may lie over K, V: each dK/dV work-group has read its own keys, but the other kind reads them all)
+  const size_t kv = 2 * (size_t)((d.B - 1) * d.ks[0] + (d.Z - 1) * d.ks[1] + (d.L - 1) * d.ks[2] + d.A);
+  const bool over = overlap(dK, kv, K, kv) || overlap(dK, kv, V, kv) || overlap(dV, kv, K, kv) || overlap(dV, kv, V, kv);
+  if (const int groups = qsplits > 1 || over ? 0 : both_groups(d)) {
+    e = fused_bwd_preprocess(d, dO, O, LSE, nD, nL, st);
+    if (e != hipSuccess) return e;
+    const BwdArgs a = make_bwd_args(d, dO, Q, K, V, nL, nD, dQ, dK, dV);
+    if (d.A == 128) return groups == 2 ? launch_both<2, 1, 2, 2, 1, 2, 2>(d, a, st) : launch_both<2, 2, 4, 1, 1, 4, 1>(d, a, st);
+    if (groups == 4) return launch_both<1, 1, 1, 4, 1, 1, 4>(d, a, st);
+    return groups == 2 ? launch_both<1, 1, 2, 2, 1, 2, 2>(d, a, st) : launch_both<1, 2, 4, 1, 2, 4, 1>(d, a, st);
+  }
   if (d.A == 128) {
     e = fused_bwd_preprocess(d, dO, O, LSE, nD, nL, st);
     if (e != hipSuccess) return e;
