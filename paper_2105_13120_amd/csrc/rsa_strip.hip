@@ -83,9 +83,9 @@ template <> struct TileT<uint16_t> {
   // column (of 32) of a tile that holds strip fragments -> key: a fragment's eight elements are keys
   // 4 half .. + 3 and 8 + 4 half .. + 3 of its slice
   static __device__ __forceinline__ int key_of_col(int c) { return (c & 16) | ((c & 4) << 1) | ((c >> 1) & 4) | (c & 3); }
-  template <int ROWS = 64> struct DMA {  // ROWS = 32: the upper half of a tile
-    TileDMAT<256 / ROWS> d;
-    static constexpr int PER = TileDMAT<256 / ROWS>::PER;
+  template <int ROWS = 64, int WAVES = 4> struct DMA {  // ROWS = 32: the upper half of a tile
+    TileDMAT<64 * WAVES / ROWS> d;
+    static constexpr int PER = TileDMAT<64 * WAVES / ROWS>::PER;
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) : d(wave, lane, (int)ld) {}
     __device__ __forceinline__ void load_unseen(const uint16_t *g, uint32_t t) const {
 #pragma unroll
@@ -161,8 +161,8 @@ template <> struct TileT<float> {
   }
   static __device__ __forceinline__ int key_of_col(int c) { return c; }
   static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 4; return (p & 15) ^ rot(row); }
-  template <int ROWS = 64> struct DMA {
-    static constexpr int PER = ROWS / 16;
+  template <int ROWS = 64, int WAVES = 4> struct DMA {
+    static constexpr int PER = ROWS / (4 * WAVES);
     int g_off[PER], l_off[PER];
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) {
 #pragma unroll
@@ -199,8 +199,8 @@ __device__ __forceinline__ void strip_store(T *block, const f32x16 &c0, const f3
 }
 // Direct load of a strip tile (ROWS = 32: of one of its blocks) into LDS as rows of 16-byte chunks (chunk 2 i + h of row r: the fragment of
 // slice i that lane (r, h) holds), swizzled like every tile of its type.
-template <typename T, int ROWS> struct StripDMA {
-  static constexpr int PER = TileT<T>::kBytes * ROWS / (64 * 4096);
+template <typename T, int ROWS, int WAVES> struct StripDMA {
+  static constexpr int PER = TileT<T>::kBytes * ROWS / (64 * 1024 * WAVES);
   int g_off[PER], l_off[PER];
   __device__ __forceinline__ StripDMA(int wave, int lane) {
 #pragma unroll
@@ -514,14 +514,18 @@ struct ApplyArgs {
   float *norm;  // fp32 backward: (head, rows)
 };
 
-template <typename T, int AHW, bool WEIGHT>
-__global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(StripArgs a, ApplyArgs p) {
+// RW waves share the work-group's rows, 32 each; KS groups of such waves share the key tiles, group g taking every
+// KS-th, and their sums are added in LDS.
+template <typename T, int AHW, bool WEIGHT, int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2)) strip_apply_kernel(StripArgs a, ApplyArgs p) {
   typedef TileT<T> TT;
-  constexpr int NS = TT::kSlices;
+  constexpr int NS = TT::kSlices, BM = 32 * RW;
   struct Stage { unsigned char X[AHW][TT::kBytes]; };
-  __shared__ __attribute__((aligned(16))) Stage st0, st1;  // separate objects: see the fused kernels
+  __shared__ __attribute__((aligned(16))) Stage st0[KS], st1[KS];  // separate objects: see the fused kernels
+  __shared__ float sums[KS == 1 ? 1 : KS][RW][2][64];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / RW;
   const int col = lane & 31, half = lane >> 5;
   const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t cblocks = (uint32_t)(a.A / (64 * AHW));
@@ -529,8 +533,8 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
   const uint32_t hr = wg / cblocks;
   // under the causal mask later rows see more keys: the long work-groups start first
   const uint32_t rt = hr % (uint32_t)a.rtiles;
-  const int64_t head = hr / (uint32_t)a.rtiles, row0 = (int64_t)(a.causal ? a.rtiles - 1 - rt : rt) * 128;
-  const int64_t row_last = (row0 + 128 < a.rows ? row0 + 128 : a.rows) - 1;
+  const int64_t head = hr / (uint32_t)a.rtiles, row0 = (int64_t)(a.causal ? a.rtiles - 1 - rt : rt) * BM;
+  const int64_t row_last = (row0 + BM < a.rows ? row0 + BM : a.rows) - 1;
   const int ntiles = (int)(a.L / 64);
   int nt = ntiles;
   if (a.causal && (a.q0 + row_last) / 64 + 1 < nt) nt = (int)((a.q0 + row_last) / 64) + 1;
@@ -539,9 +543,9 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
   const bool rows_here = wrow < a.rows;
   const int64_t rrow = rows_here ? wrow : row0;  // (a wave without rows reads the first wave's)
   const T *S = static_cast<const T *>(p.strip) + strip_tile<T>(head, a.rows / 64, rrow / 64, ntiles, 0) +
-               (wave & 1) * 2048 + lane * (16 / (int)sizeof(T));
+               (RW == 1 ? (int)(rrow >> 5) & 1 : wave & 1) * 2048 + lane * (16 / (int)sizeof(T));
   const T *Xh = static_cast<const T *>(p.X) + head * a.L * a.A + a0;
-  const typename TT::template DMA<> dma_x(wave, lane, a.A);
+  const typename TT::template DMA<64, RW> dma_x(wave, lane, a.A);
   typename TT::Frag s0[NS], s1[NS];
   constexpr bool kStats = WEIGHT || kOwnSum<T>;
   constexpr int kPer = WEIGHT ? 2 : 1;  // numbers per row and tile
@@ -557,7 +561,8 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
     for (int i = 0; i < NS; ++i)
       s[i] = *reinterpret_cast<const typename TT::Frag *>(S + (int64_t)t * 4096 + i * (1024 / (int)sizeof(T)));
   };
-  load(0, st0, s0, ml0);
+  int t = grp;  // this group's tile
+  if (KS == 1 || t < nt) load(t, st0[grp], s0, ml0);
 
   float M = -INFINITY;  // the row's largest m_t
   if (WEIGHT) {
@@ -584,7 +589,6 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
 
-  int t = 0;
   wait_vmem();
 #pragma unroll
   for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(s0[i]));  // (keeps the first loads in front of this wait)
@@ -592,8 +596,8 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
   __syncthreads();
   auto step = [&](Stage &cur, typename TT::Frag(&sc)[NS], f32x2 ml, Stage &nxt, typename TT::Frag(&sn)[NS], f32x2 &mln)
       __attribute__((always_inline)) {
-    if (t + 1 < nt) load(t + 1, nxt, sn, mln);
-    if (rows_here && tile_seen(a, wrow, (int64_t)t * 64)) {
+    if (t + KS < nt) load(t + KS, nxt, sn, mln);
+    if (rows_here && (KS == 1 || t < nt) && tile_seen(a, wrow, (int64_t)t * 64)) {
       const float w = WEIGHT ? __builtin_amdgcn_exp2f(ml[0] - M) : 1.f;
       if constexpr (kStats) {
         const float x = fmaf(w, ml[1], -l_err), sum = l + x;
@@ -649,12 +653,39 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
     }
     wait_vmem();
     __syncthreads();
-    ++t;
+    t += KS;
   };
-  while (t < nt) {
-    step(st0, s0, ml0, st1, s1, ml1);
-    if (t >= nt) break;
-    step(st1, s1, ml1, st0, s0, ml0);
+  while (t - grp < nt) {
+    step(st0[grp], s0, ml0, st1[grp], s1, ml1);
+    if (t - grp >= nt) break;
+    step(st1[grp], s1, ml1, st0[grp], s0, ml0);
+  }
+  if constexpr (KS > 1) {
+    static_assert(RW <= 2, "the epilogue's tiles are in the first buffers, the groups' sums in the second");
+    auto slot = [&](int g, int db) { return reinterpret_cast<f32x4 *>(&st1[0].X[0][0] + (((g - 1) * RW + wave) * 2 * AHW + db) * 4096); };
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
+      sums[grp][wave][0][lane] = l; sums[grp][wave][1][lane] = l_err;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int q = 1; q < KS; ++q) {
+#pragma unroll
+      for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = slot(q, db)[g * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
+        }
+      const float x = sums[q][wave][0][lane] - l_err, sum = l + x;
+      l_err = ((sum - l) - x) + sums[q][wave][1][lane];
+      l = sum;
+    }
+    l -= l_err;
   }
   if (!rows_here) return;
   const float norm = kStats ? 1.0f / l : 1.0f;
@@ -662,7 +693,7 @@ __global__ void __launch_bounds__(256, AHW == 1 ? 3 : 2) strip_apply_kernel(Stri
     if (WEIGHT) p.LSE[head * a.Lq + wrow + col] = fmaf(M, kLn2, logf(l));
     else if (kStats) p.norm[head * a.rows + wrow + col] = norm;
   }
-  unsigned char *ot = (wave < 2 ? st0.X[0] : st1.X[0]) + (wave & 1) * (TT::kBytes / 2);  // (free after the last barrier)
+  unsigned char *ot = (wave < 2 ? st0[0].X[0] : st1[0].X[0]) + (wave & 1) * (TT::kBytes / 2);  // (free after the last barrier)
   T *out = static_cast<T *>(p.out) + (head * a.Lq + wrow) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
@@ -685,15 +716,18 @@ struct CollectArgs {
   int add, keep;
 };
 
-template <typename T, int AHW, int DEPTH>
-__global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_collect_kernel(StripArgs a, CollectArgs p) {
+// WK waves share the work-group's keys, 32 each; QS groups of such waves share the row tiles (see apply).
+template <typename T, int AHW, int DEPTH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
   typedef TileT<T> TT;
   constexpr int RT = sizeof(T) == 4 ? 32 : 64;  // rows per step: 24 KiB (64 columns, either type) leave room for three
   constexpr int NS = TT::kSlices * RT / 64;     // work-groups on a compute unit
-  struct Stage { unsigned char S[2][TT::kBytes * RT / 64], Y[AHW][TT::kBytes * RT / 64]; };
-  __shared__ __attribute__((aligned(16))) Stage st[DEPTH];
+  constexpr int BK = 32 * WK, KT = (WK + 1) / 2;  // keys, and the key tiles they lie in
+  struct Stage { unsigned char S[KT][TT::kBytes * RT / 64], Y[AHW][TT::kBytes * RT / 64]; };
+  __shared__ __attribute__((aligned(16))) Stage st[QS * DEPTH];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
+  const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
   const int col = lane & 31, half = lane >> 5;
   uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t cblocks = (uint32_t)(a.A / (64 * AHW));
@@ -701,43 +735,44 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
   wg /= cblocks;
   const bool which = wg & 1;
   wg >>= 1;
-  const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * 128;
+  const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * BK;
   const int64_t head = wg / (uint32_t)a.kblocks;
   const int nt = (int)(a.rows / RT);
-  int t = 0;
+  int t0 = 0;
   if (a.causal && key0 > a.q0 + 63) {  // first row tile whose last row sees the block's first key
     const int64_t f = (key0 - a.q0) / 64 * (64 / RT);
-    t = f < nt ? (int)f : nt;
+    t0 = f < nt ? (int)f : nt;
   }
   const int64_t ktiles = a.L / 64;
   const T *Sh = static_cast<const T *>(which ? p.strip[1] : p.strip[0]) +
                 strip_tile<T>(head, a.rows / 64, 0, ktiles, key0 / 64);
   const int64_t second = key0 + 64 < a.L ? 4096 : 0;  // (no second key tile: refetch the first)
   const T *Yh = static_cast<const T *>(which ? p.Y[1] : p.Y[0]) + head * a.Lq * a.A + a0;
-  const StripDMA<T, RT> dma_s(wave, lane);
-  const typename TT::template DMA<RT> dma_y(wave, lane, a.A);
-  const uint32_t lds0 = lds_address(&st[0]);
+  const StripDMA<T, RT, WK> dma_s(wave, lane);
+  const typename TT::template DMA<RT, WK> dma_y(wave, lane, a.A);
+  const uint32_t lds0 = lds_address(&st[grp * DEPTH]);
   // fp32: the row tile's factors.  (From registers, loaded a tile ahead, they cost the compiler's waits for all loads in
   // flight: 181 us instead of 152 at B16 Z12 L512.)
-  __shared__ __attribute__((aligned(16))) float norm[kOwnSum<T> ? DEPTH * 64 : 4];
+  __shared__ __attribute__((aligned(16))) float norm[kOwnSum<T> ? QS * DEPTH * 64 : 4];
   const float *norms = p.norm + head * a.rows;
-  constexpr int kLoads = 2 * StripDMA<T, RT>::PER + AHW * TT::template DMA<RT>::PER;  // of a wave, per row tile
+  constexpr int kLoads = KT * StripDMA<T, RT, WK>::PER + AHW * TT::template DMA<RT, WK>::PER;  // of a wave, per row tile
   auto load = [&](int tt_, int b) __attribute__((always_inline)) {  // row tile tt_ -> buffer b
     const int row = tt_ * RT;
     const T *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
     const uint32_t d = lds0 + (uint32_t)b * (uint32_t)sizeof(Stage);
     if (kOwnSum<T> && wave == 0)  // (64 numbers for 32 rows)
-      lds_dma4_unseen(norms + row, lane * 4, lds_address(&norm[0]) + (uint32_t)b * 256);
+      lds_dma4_unseen(norms + row, lane * 4, lds_address(&norm[0]) + (uint32_t)(grp * DEPTH + b) * 256);
     dma_s.load_unseen(s, d);
-    dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
+    if (KT == 2) dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
 #pragma unroll
     for (int ah = 0; ah < AHW; ++ah)
       dma_y.load_unseen(Yh + (int64_t)row * a.A + ah * 64, d + (uint32_t)(sizeof(st[0].S) + ah * sizeof(st[0].Y[0])));
   };
 #pragma unroll
   for (int i = 0; i + 1 < DEPTH; ++i)
-    if (t + i < nt) load(t + i, i);
-  const int64_t wkey = key0 + wave * 32, wtile = key0 + (wave >> 1) * 64;
+    if (t0 + grp + i * QS < nt) load(t0 + grp + i * QS, i);
+  const int64_t wkey = key0 + wave * 32, wtile = wkey & ~(int64_t)63;
+  const int wcols = (int)(wkey >> 5) & 1;  // the wave's columns of the key tile
   const bool keys_here = wkey < a.L;
   const TT tt(lane);
   f32x16 o[2 * AHW];
@@ -747,16 +782,17 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
   static_assert(!kOwnSum<T> || DEPTH == 2, "kLoads does not count the first wave's factors");
   int b = 0;  // buffer of tile t
-  for (; t < nt; ++t) {
+  for (; t0 < nt; t0 += QS) {
+    const int t = t0 + grp;  // this group's tile
     // tile t has arrived, and behind the barrier every wave is done with tile t - 1, whose buffer takes the next one
-    if (DEPTH == 3 && t + 1 < nt) wait_loads<kLoads>();
+    if (DEPTH == 3 && t + QS < nt) wait_loads<kLoads>();
     else wait_loads<0>();
     barrier_lds();
-    if (t + DEPTH - 1 < nt) load(t + DEPTH - 1, b == 0 ? DEPTH - 1 : b - 1);
-    const Stage &cur = st[b];
-    if (keys_here && tile_seen(a, (int64_t)t * RT, wtile)) {
+    if (t + (DEPTH - 1) * QS < nt) load(t + (DEPTH - 1) * QS, b == 0 ? DEPTH - 1 : b - 1);
+    const Stage &cur = st[grp * DEPTH + b];
+    if (keys_here && (QS == 1 || t < nt) && tile_seen(a, (int64_t)t * RT, wtile)) {
       const unsigned char *S = cur.S[wave >> 1];
-      const float *n = norm + b * 64 + half * (TT::kSliceK / 2);
+      const float *n = norm + (grp * DEPTH + b) * 64 + half * (TT::kSliceK / 2);
       typename TT::Frag sf[2], nf[2], yf[2][2 * AHW];
       f32x16 c[kOwnSum<T> ? 2 * AHW : 1];  // fp32: the row tile's own sum
       if constexpr (kOwnSum<T>) {
@@ -767,7 +803,7 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
       }
       pipelined<NS>(
           [&](int s, int b) __attribute__((always_inline)) {
-            sf[b] = tt.cols(S, s, wave & 1);
+            sf[b] = tt.cols(S, s, wcols);
             if constexpr (kOwnSum<T>)
               nf[b] = *reinterpret_cast<const typename TT::Frag *>(n + s * TT::kSliceK);
 #pragma unroll
@@ -791,6 +827,30 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
     b = b + 1 < DEPTH ? b + 1 : 0;
   }
   barrier_lds();  // the epilogue writes to the buffers
+  if constexpr (QS > 1) {
+    // groups 1 .. QS - 1 leave their sums behind the first 16 KiB, which the epilogue takes
+    static_assert(WK <= 2 && sizeof(st) >= 16384 + (QS - 1) * WK * 2 * AHW * 4096, "room for the groups' sums");
+    auto slot = [&](int g, int db) {
+      return reinterpret_cast<f32x4 *>(reinterpret_cast<unsigned char *>(st) + 16384 + (((g - 1) * WK + wave) * 2 * AHW + db) * 4096);
+    };
+    if (grp > 0) {
+#pragma unroll
+      for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
+    }
+    barrier_lds();
+    if (grp > 0) return;
+    for (int q = 1; q < QS; ++q)
+#pragma unroll
+      for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = slot(q, db)[g * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
+        }
+  }
   if (!keys_here) return;
   if (p.add || p.keep) {
     float *acc = (which ? p.acc[1] : p.acc[0]) + (head * a.L + wkey + TT::key_of_col(col)) * a.A + a0 + half * 4;
@@ -809,7 +869,7 @@ __global__ void __launch_bounds__(256, AHW == 1 && DEPTH == 2 ? 3 : 2) strip_col
   }
   const float alpha = which ? p.alpha[1] : p.alpha[0];
   // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
-  unsigned char *ot = st[wave >> 1].S[0] + (wave & 1) * (TT::kBytes / 2);
+  unsigned char *ot = reinterpret_cast<unsigned char *>(&st[wave >> 1]) + (wave & 1) * (TT::kBytes / 2);
   T *out = static_cast<T *>(which ? p.out[1] : p.out[0]) + (head * a.L + wkey) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
@@ -936,38 +996,57 @@ hipError_t launch_scores(const StripArgs &a0, int64_t heads, bool bwd, hipStream
   return hipGetLastError();
 }
 
-template <typename T, bool WEIGHT>
-hipError_t launch_apply(const StripArgs &a, const ApplyArgs &p, int64_t heads, hipStream_t st) {
-  const bool wide = a.A % 128 == 0;
-  const dim3 grid((unsigned)(heads * a.rtiles * (a.A / (wide ? 128 : 64))));
-  if (wide) hipLaunchKernelGGL((strip_apply_kernel<T, 2, WEIGHT>), grid, dim3(256), 0, st, a, p);
-  else hipLaunchKernelGGL((strip_apply_kernel<T, 1, WEIGHT>), grid, dim3(256), 0, st, a, p);
+template <typename T, int AHW, bool WEIGHT, int RW, int KS>
+hipError_t launch_apply_as(StripArgs a, const ApplyArgs &p, int64_t heads, hipStream_t st) {
+  a.rtiles = (int)((a.rows + 32 * RW - 1) / (32 * RW));
+  const dim3 grid((unsigned)(heads * a.rtiles * (a.A / (64 * AHW))));
+  hipLaunchKernelGGL((strip_apply_kernel<T, AHW, WEIGHT, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a, p);
   return hipGetLastError();
 }
-
-template <typename T>
-hipError_t launch_collect(const StripArgs &a0, const CollectArgs &p, int64_t heads, hipStream_t st) {
-  StripArgs a = a0;
-  a.kblocks = (int)((a.L + 127) / 128);
+// Few work-groups: their walks over the key tiles are serial chains on a partly idle chip, so groups of waves share them.
+// The lines are those of a sweep over 2 .. 192 heads of 64 .. 256 elements, 256 .. 3072 rows; forward, us, by W:
+//   fp32, one group -> four: 4 (256 rows) 18.8 -> 12.9, 24 (1536) 72 -> 34, 64 (A 128) 49 -> 20, 144 causal 178 -> 133;
+//   one -> two: 96 (320 rows) 25.4 -> 21.5, 288 190 -> 177, 560 (A 128) 126 -> 110; but 210 34.9 -> 37.8, 432 234 -> 249;
+//   bf16, one -> four: 24 (1536 rows) 19.5 -> 13.6, 48 (3072) 40 -> 26; one -> two: 144 53 -> 47; but 288 47 -> 49.
+template <typename T, bool WEIGHT>
+hipError_t launch_apply(const StripArgs &a, const ApplyArgs &p, int64_t heads, hipStream_t st) {
+  const int64_t W = heads * a.rtiles * (a.A / 64);  // work-groups of 128 rows and 64 columns
   const bool wide = a.A % 128 == 0;
-  const dim3 grid((unsigned)(heads * a.kblocks * 2 * (a.A / (wide ? 128 : 64))));
-  if (wide) {
-    hipLaunchKernelGGL((strip_collect_kernel<T, 2, 2>), grid, dim3(256), 0, st, a, p);
-    return hipGetLastError();
+  if (W <= 64 || (a.causal && W <= 144)) return launch_apply_as<T, 1, WEIGHT, 1, 4>(a, p, heads, st);
+  const bool two = sizeof(T) == 4 ? W <= (wide ? 600 : 390) && (a.causal || wide || W <= 128 || W >= 230)
+                                  : W <= (a.causal ? 360 : 240);
+  if (two) return launch_apply_as<T, 1, WEIGHT, 2, 2>(a, p, heads, st);
+  return wide ? launch_apply_as<T, 2, WEIGHT, 4, 1>(a, p, heads, st) : launch_apply_as<T, 1, WEIGHT, 4, 1>(a, p, heads, st);
+}
+
+template <typename T, int AHW, int DEPTH, int WK, int QS>
+hipError_t launch_collect_as(StripArgs a, const CollectArgs &p, int64_t heads, hipStream_t st) {
+  a.kblocks = (int)((a.L + 32 * WK - 1) / (32 * WK));
+  const dim3 grid((unsigned)(heads * a.kblocks * 2 * (a.A / (64 * AHW))));
+  hipLaunchKernelGGL((strip_collect_kernel<T, AHW, DEPTH, WK, QS>), grid, dim3(64 * WK * QS), 0, st, a, p);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_collect(const StripArgs &a, const CollectArgs &p, int64_t heads, hipStream_t st) {
+  const int64_t W = heads * ((a.L + 127) / 128) * 2 * (a.A / 64);  // work-groups of 128 keys and 64 columns
+  // Groups of waves on the row tiles of few work-groups, as in apply (same sweep, backward, us, by W): fp32, one group ->
+  // four: 8 37 -> 31, 48 (1536 rows) 159 -> 118; one -> two: 192 107 -> 104, 288 261 -> 246, 576 (A 128) 495 -> 440, causal
+  // 291 -> 277; bf16: A = 128, 128 23.4 -> 21.7, causal 288 58 -> 50, but not causal 65 -> 68.
+  if constexpr (sizeof(T) == 4) {
+    if (W <= 64) return launch_collect_as<T, 1, 2, 1, 4>(a, p, heads, st);
+    if (W <= 600) return launch_collect_as<T, 1, 2, 2, 2>(a, p, heads, st);
+  } else {
+    if ((a.A % 128 == 0 && W <= 256) || (a.causal && W > 256 && W <= 400)) return launch_collect_as<T, 1, 2, 2, 2>(a, p, heads, st);
   }
+  if (a.A % 128 == 0) return launch_collect_as<T, 2, 2, 4, 1>(a, p, heads, st);
   // bf16 strips come at the rate that requests in flight allow.  With at most one work-group on a compute unit its row
   // tiles are requested two steps ahead; several bring enough by themselves, and three fit where each takes two
   // buffers.  The whole backward with two | three buffers, us: 64 work-groups 33.5 | 30.4, 256: 45.4 | 40.8 and
   // 161.5 | 140.8, 384 (in groups): 1165 | 1180, 1536: 121 | 121; fp32, bound by its products: 256: 131 | 131,
   // 768: 292 | 309.
-  if constexpr (sizeof(T) == 2) {
-    if (grid.x <= 256) {
-      hipLaunchKernelGGL((strip_collect_kernel<T, 1, 3>), grid, dim3(256), 0, st, a, p);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((strip_collect_kernel<T, 1, 2>), grid, dim3(256), 0, st, a, p);
-  return hipGetLastError();
+  if constexpr (sizeof(T) == 2)
+    if (W <= 256) return launch_collect_as<T, 1, 3, 4, 1>(a, p, heads, st);
+  return launch_collect_as<T, 1, 2, 4, 1>(a, p, heads, st);
 }
 
 #define RSA_TRY(expr)                       \
