@@ -923,7 +923,7 @@ static int both_groups(const Dims &d) {
   const int64_t W = heads * ((d.L + 127) / 128 + (d.Lq + 127) / 128) / 2;
   if (d.A == 128) {
     if (W <= 64 || (d.causal && L > 512 && W <= 128)) return 2;
-    if (W <= 128 || (W <= 460 && (d.causal || W > 256))) return 1;
+    if (W <= 128 || (d.causal ? W <= 460 : W > 256 && W <= 384)) return 1;
     return 0;
   }
   if (d.causal) {
@@ -933,7 +933,7 @@ static int both_groups(const Dims &d) {
   }
   if (W <= 32) return 4;
   if (W <= 64) return 2;
-  return (L <= 8192 && (W <= 460 || (W > 512 && W <= 640))) || (L <= 512 && W <= 1536) ? 1 : 0;
+  return (L <= 8192 && (W <= (L <= 2048 ? 460 : 384) || (W > 512 && W <= 640))) || (L <= 512 && W <= 1536) ? 1 : 0;
 }
 
 hipError_t fused_backward(const Dims &d, const void *dO, const void *Q, const void *K,

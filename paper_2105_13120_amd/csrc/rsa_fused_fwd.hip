@@ -450,6 +450,16 @@ static int key_splits_for(const Dims &d, int rows_per_wg) {
   if (d.causal && !d.zigzag && (int64_t)d.rank_end * d.c / 128 < stages) stages = (int64_t)d.rank_end * d.c / 128;
   const int64_t smax = stages / 16 < 32 ? stages / 16 : 32;
   if (smax < 2) return 1;
+  // The whole ring: splits in two, and those of walks of very different length, lose to groups of waves on a walk or
+  // to plain work-groups (forward, split -> not, us, by 128-row work-groups: 4096 rows 32: 31.3 -> 25.3, 256: 50 -> 46, 768:
+  // 124 -> 114; causal 4096 rows 192: 46 -> 28, 896: 118 -> 80, 8192 rows 256: 77 -> 57, 1024: 205 -> 165, 16384 rows 768:
+  // 311 -> 254; but 8192 rows 128: 47 -> 50, 16384 rows 512: 188 -> 198).
+  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
+  if (d.Lq == d.L) {
+    const bool wide = d.A == 128;  // (fewer work-groups on a CU: 4096 rows, W = 128: split 52, not 56)
+    if (d.causal && ((d.L < 8192 && !(wide && W <= 128)) || W >= 640 || (d.L <= 8192 && W >= (wide ? 400 : 200)))) return 1;
+    if (!d.causal && smax == 2 && (wide ? W > 128 : W <= 320 || W >= 400)) return 1;
+  }
   if (d.causal && d.zigzag) wgs = (wgs + 1) / 2;
   const int64_t min_rounds = d.causal ? 3 : 1;
   for (int64_t s = 1; s <= smax; ++s) {
@@ -465,11 +475,20 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // The forward: 64 rows per wave (256 per work-group) halve the LDS traffic per flop and are
 // taken when their work-groups, times their splits, fill the 512 slots at least once; else 32
 // rows per wave, which give twice the work-groups.  (A head of 128 elements takes 32 rows per
-// wave and one key tile per stage: registers and LDS.)
+// wave and one key tile per stage: registers and LDS.)  Unsplit, a CU's two places for large work-groups, filled in turn, are
+// compared with its four for small ones, which cost 5 % more per row: 1600 work-groups of 128 rows, L = 1024, large 74 us,
+// small 67; 1536, L = 2048: 109, 113.  Causal walks end one by one and fill places left over: small ones up to 1900
+// (1024, L = 2048: 51 -> 46; 1600, L = 1024: 47 -> 40; 2048, L = 4096: 149 -> 154).
 void fused_fwd_plan(const Dims &d, bool *big, int *splits) {
   if (d.A == 64 && d.Lq % 256 == 0) {
     const int s = key_splits_for(d, 256);
-    if ((int64_t)d.B * d.Z * (d.Lq / 256) * s >= 512) {
+    const int64_t wgs = (int64_t)d.B * d.Z * (d.Lq / 256), W = 2 * wgs;
+    bool large = wgs * s >= 512;
+    if (s == 1 && d.Lq == d.L) {
+      if (d.causal) large = W >= 1900 && d.L > 256;
+      else large = W >= 512 && (double)((W + 511) / 512) * 2 < (double)((W + 255) / 256) * (d.L > 256 && d.L <= 512 ? 1.0 : 1.055);
+    }
+    if (large) {
       *big = true; *splits = s;
       return;
     }
@@ -496,22 +515,24 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   a.part_ml = part ? part + (int64_t)splits * rows * d.A : nullptr;
   // Few work-groups of four waves (W: their number): the chip is not full, and a work-group's walk is a serial chain.
   // Then fewer rows per work-group and several groups of waves on its keys (RW, KS in the kernel): the chain
-  // shortens, at more tile loads per flop.  The lines are those of a sweep over B Z = 1 .. 192, L = 192 .. 8192 (us,
-  // four waves -> chosen): W = 8: 9.5 -> 7.1; 96: 15.8 -> 11.2; 192 causal: 39 -> 26; 252 causal: 33 -> 26;
-  // 512 causal: 41 -> 36.
-  const int64_t W = heads * ((d.Lq + 127) / 128), walk = d.L / 64;
+  // shortens, at more tile loads per flop.  The lines are those of sweeps over 1 .. 2000 heads of 192 .. 32768 rows (us,
+  // four waves -> chosen): W = 64: 9.4 -> 7.5; 128 (4096 rows): 49 -> 27; 256 (4096): 49 -> 46; causal 192 (4096): 59 -> 28;
+  // 384 (4096): 61 -> 46; 512 (2048): 33 -> 30; 640 (8192): 133 -> 116; heads of 128, W = 256 (4096): 83 -> 72, causal
+  // 512 (8192): 180 -> 149, but 400 (512): 18 -> 25.
+  const int64_t W = heads * ((d.Lq + 127) / 128), walk = d.L / 64, L = d.L;
   const bool c = d.causal;
   hipError_t e;
   if (big) e = launch_fwd<64, 1, 2, 4, 1>(d, a, heads, splits, st);
   else if (d.A == 128) {
-    if (splits > 1 || W > (c ? 512 : 256)) e = launch_fwd<32, 2, 1, 4, 1>(d, a, heads, splits, st);
+    if (splits > 1 || W > (c && L > 512 ? 512 : 256)) e = launch_fwd<32, 2, 1, 4, 1>(d, a, heads, splits, st);
     else if (W > 128) e = launch_fwd<32, 2, 1, 4, 2>(d, a, heads, 1, st);
     else e = launch_fwd<32, 2, 1, 2, 2>(d, a, heads, 1, st);
-  } else if (splits > 1 || W > (c ? 576 : 256)) e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, splits, st);
-  else if (W <= 32) e = launch_fwd<32, 1, 1, 1, 4>(d, a, heads, 1, st);
-  else if (W <= (c ? 192 : 128)) e = launch_fwd<32, 1, 1, 2, 4>(d, a, heads, 1, st);
-  else if (c && W <= 256) e = launch_fwd<32, 1, 1, 2, 2, kCausal>(d, a, heads, 1, st);
-  else if (c || walk >= 16) e = launch_fwd<32, 1, 1, 4, 2>(d, a, heads, 1, st);
+  } else if (splits > 1) e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, splits, st);
+  else if (W <= 64) e = launch_fwd<32, 1, 1, 1, 4>(d, a, heads, 1, st);
+  else if (W <= 128 || (c && W <= 300 && L >= 1536)) e = launch_fwd<32, 1, 1, 2, 4>(d, a, heads, 1, st);
+  else if (c && W <= (L >= 4096 ? 430 : 256)) e = launch_fwd<32, 1, 1, 2, 2, kCausal>(d, a, heads, 1, st);
+  else if (c ? (W <= 576 && L >= 1024) || (W <= 800 && L >= 4096) : W <= 256 && walk >= 16)
+    e = launch_fwd<32, 1, 1, 4, 2>(d, a, heads, 1, st);
   else e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, 1, st);
   if (e != hipSuccess || splits == 1) return e;
   const OutLayout lay = make_out_layout(d.os, d.Lq, d.Z);
