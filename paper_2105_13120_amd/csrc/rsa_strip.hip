@@ -16,21 +16,23 @@
 // apply adds them and scales its rows, collect scales the strips' rows as it reads them.  No accumulator starts
 // from a row term (the contraction would be rounded at that term's size), and the fp32 sums over keys or rows are
 // formed 32 at a time.  Relative RMS error against fp64, 1e-7, dQ | dK | dV | O, N(0, 1) inputs:
-// A64 L512 3.5 | 3.4 | 3.1 | 3.1 (with row terms in the accumulators and one chain per sum 12.5 | 12.2 | 12.1 | 5.8;
-// the chunk-by-chunk steps of rsa_staged.hip, N4, 3.9 | 3.8 | 3.5 | 3.6).
+// A64 L512 2.7 | 2.7 | 2.4 | 1.6 (with products by the fp32 matrix instruction 3.5 | 3.4 | 3.1 | 3.1, with row terms in the
+// accumulators and one chain per sum besides 12.5 | 12.2 | 12.1 | 5.8; the chunk-by-chunk steps of rsa_staged.hip, N4,
+// 3.9 | 3.8 | 3.5 | 3.6).
 //
 // Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
 // 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.65,
-// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; now 0.48, 80 to 95 TFLOP/s in
-// every kernel, of which the strips' traffic hides about half).
+// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32 matrix instructions 0.49, 55 to 70 % of
+// their rate; now 0.42, the strips' 1.4 GB at 3.3 to 4.2 TB/s).
 //
-// The tile kernels hold bf16 tiles in the layout of the fused kernels and fp32 tiles in one of their
-// own; fp32 products run on v_mfma_f32_32x32x2_f32 (IEEE fp32 multiply-add, twice the rate of the
-// vector unit).  All products are formed transposed: one lane owns one row of the result.
+// The tile kernels hold bf16 tiles in the layout of the fused kernels; fp32 products run on the bf16 matrix instructions
+// over numbers split in three (TileT<float>).  All products are formed transposed: one lane owns one row of the result.
 #include "rsa_fused_tile.h"
 #include "rsa_kernels.h"
+
+#include <type_traits>
 
 namespace rsa {
 namespace {
@@ -42,8 +44,8 @@ namespace {
 template <typename T> struct TileT;
 
 template <> struct TileT<uint16_t> {
-  typedef bf16x8 Frag;
-  static constexpr int kBytes = kTileBytes, kSlices = 4, kSliceK = 16, kStores = 4;
+  typedef bf16x8 Frag, Piece;
+  static constexpr int kBytes = kTileBytes, kPieces = 4;
   TileLanes tl;
   __device__ __forceinline__ explicit TileT(int lane) : tl(lane) {}
   __device__ __forceinline__ Frag rows(const unsigned char *t, int rb, int s) const { return tl.read_rows(t, rb, s); }
@@ -55,6 +57,7 @@ template <> struct TileT<uint16_t> {
     return __builtin_bit_cast(Frag, w);
   }
   static __device__ __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c) { return mfma_32x32x16(a, b, c); }
+  static __device__ __forceinline__ void mfma(Frag a, Frag b, f32x16 &c, f32x16 &) { c = mfma_32x32x16(a, b, c); }
   static __device__ __forceinline__ float dot(Frag a, Frag b, float acc) {
     const u32x4 x = __builtin_bit_cast(u32x4, a), y = __builtin_bit_cast(u32x4, b);
 #pragma unroll
@@ -73,7 +76,7 @@ template <> struct TileT<uint16_t> {
     flush_rows<32>(t, 0, g, rows_valid, lane, (int)ld);
   }
   // slice i of a transposed 32-row block (c0: its columns 0 .. 31, c1: 32 .. 63) as an operand
-  static __device__ __forceinline__ Frag slice(const f32x16 &c0, const f32x16 &c1, int i) {
+  static __device__ __forceinline__ Piece piece(const f32x16 &c0, const f32x16 &c1, int i) {
     const f32x16 &c = i < 2 ? c0 : c1;
     const int v = (i & 1) * 8;
     const u32x4 w = {pack_bf16(c[v + 0], c[v + 1]), pack_bf16(c[v + 2], c[v + 3]), pack_bf16(c[v + 4], c[v + 5]),
@@ -83,9 +86,9 @@ template <> struct TileT<uint16_t> {
   // column (of 32) of a tile that holds strip fragments -> key: a fragment's eight elements are keys
   // 4 half .. + 3 and 8 + 4 half .. + 3 of its slice
   static __device__ __forceinline__ int key_of_col(int c) { return (c & 16) | ((c & 4) << 1) | ((c >> 1) & 4) | (c & 3); }
-  template <int ROWS = 64, int WAVES = 4> struct DMA {  // ROWS = 32: the upper half of a tile
-    TileDMAT<64 * WAVES / ROWS> d;
-    static constexpr int PER = TileDMAT<64 * WAVES / ROWS>::PER;
+  template <int WAVES = 4> struct DMA {
+    TileDMAT<WAVES> d;
+    static constexpr int PER = TileDMAT<WAVES>::PER;
     __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) : d(wave, lane, (int)ld) {}
     __device__ __forceinline__ void load_unseen(const uint16_t *g, uint32_t t) const {
 #pragma unroll
@@ -93,44 +96,83 @@ template <> struct TileT<uint16_t> {
     }
     __device__ __forceinline__ void load(const uint16_t *g, unsigned char *t) const { d.load(g, t); }
   };
-  static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 3; return (p & 7) ^ swz_rot(row); }
 };
 
-// fp32: row r occupies bytes [256 r, 256 r + 256), its 16-byte chunk cc sits at position cc ^ rot(r).
-// rot takes bits 0, 1, 3, 2 of r to bits 0, 1, 2, 3: the 16 rows of a phase of a row read then
-// touch 16 different positions, and the two lane halves of a column read (rows r and r + 4, eight
-// chunks each) touch disjoint halves of the row: both are free of bank conflicts.
+// Eight fp32 numbers as sums of three bf16 each, x = h + m + l to the last bit (8 + 8 + 8 bits of 24, each rest rounded to
+// nearest; bf16 has the exponents of fp32).  A product of two such sums without its three smallest terms,
+//   h l' + l h' + m m' + h m' + m h' + h h',
+// is off by 2^-26 at most and takes six bf16 MFMAs of 16 k, 192 cycles, where v_mfma_f32_32x32x2_f32 takes 512.  The sums
+// over k are rounded less often: RMS error of 32 x 32 blocks over 64 | 256 k of N(0, 1) numbers 1.10 | 2.37e-7, by the fp32
+// instruction 1.44 | 2.88.  (An infinite input gives NaN where fp32 would give infinities; the largest finite ones, which
+// bf16 would round to infinity, are held below that.)
+struct Split { bf16x8 h, m, l; };
+// x less the low (high) half of a pair of bf16: exact, one instruction.  (The pairs (-1, 0) and (0, -1) come from registers:
+// as literals the compiler makes inline constants of them, which the instruction reads as other pairs.)
+struct Minus {
+  uint32_t lo, hi;
+  __device__ __forceinline__ Minus() : lo(0x0000bf80u), hi(0xbf800000u) { asm("" : "+s"(lo), "+s"(hi)); }
+  __device__ __forceinline__ float operator()(float x, uint32_t pair, bool high) const {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, high ? hi : lo), x, false);
+  }
+};
+template <bool HUGE = true>  // false: numbers that bf16 does not round to infinity
+__device__ __forceinline__ Split split8(f32x4 a, f32x4 b) {
+  const Minus minus;
+  u32x4 h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = e < 2 ? a[2 * e] : b[2 * e - 4], y = e < 2 ? a[2 * e + 1] : b[2 * e - 3];
+    constexpr float kMost = 3.3895314e38f;
+    if (HUGE) h[e] = pack_bf16(__builtin_amdgcn_fmed3f(x, -kMost, kMost), __builtin_amdgcn_fmed3f(y, -kMost, kMost));
+    else h[e] = pack_bf16(x, y);
+    const float rx = minus(x, h[e], false), ry = minus(y, h[e], true);
+    m[e] = pack_bf16(rx, ry);
+    l[e] = pack_bf16(minus(rx, m[e], false), minus(ry, m[e], true));
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// fp32: a tile lies in LDS as three bf16 tiles (of PLANE bytes) of its numbers' parts, and is split on its way there from
+// registers.
 template <> struct TileT<float> {
-  typedef f32x4 Frag;
-  static constexpr int kBytes = 64 * 64 * 4, kSlices = 8, kSliceK = 8, kStores = 8;
-  int row0, col0;  // byte offsets of chunk `half` of row `col`, of element `col` of row 4 half
-  static __device__ __forceinline__ int rot(int r) { return (r & 3) | ((r >> 1) & 4) | ((r & 4) << 1); }
-  static __device__ __forceinline__ int off(int r, int cc) { return r * 256 + ((cc ^ rot(r)) << 4); }
-  __device__ __forceinline__ explicit TileT(int lane) {
-    const int col = lane & 31, half = lane >> 5;
-    row0 = off(col, half);
-    col0 = off(half * 4, col >> 2) + (col & 3) * 4;
-  }
-  // k of slice s: 8 s + 4 half + e in element e, both for rows and for columns
+  typedef Split Frag;
+  typedef f32x4 Piece;
+  static constexpr int kBytes = 3 * kTileBytes, kPieces = 8;
+  TileT<uint16_t> tb;
+  __device__ __forceinline__ explicit TileT(int lane) : tb(lane) {}
+  template <int PLANE = kTileBytes>
   __device__ __forceinline__ Frag rows(const unsigned char *t, int rb, int s) const {
-    return *reinterpret_cast<const f32x4 *>(t + rb * 256 + (row0 ^ (s << 5)));
+    return {tb.rows(t, rb, s), tb.rows(t + PLANE, rb, s), tb.rows(t + 2 * PLANE, rb, s)};
   }
+  template <int PLANE = kTileBytes>
   __device__ __forceinline__ Frag cols(const unsigned char *t, int s, int cb) const {
-    f32x4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)  // row 8 s + 4 half + e: its rot differs from that of row 4 half by these bits
-      r[e] = *reinterpret_cast<const float *>(t + (s * 8 + e) * 256 + (col0 ^ (((cb << 3) ^ ((s & 1) << 2) ^ e) << 4)));
-    return r;
+    return {tb.cols(t, s, cb), tb.cols(t + PLANE, s, cb), tb.cols(t + 2 * PLANE, s, cb)};
   }
-  static __device__ __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], c, 0, 0, 0);
-    return c;
+  static __device__ __forceinline__ f32x16 mfma(const Frag &a, const Frag &b, f32x16 c) {
+    c = mfma_32x32x16(a.h, b.l, c);
+    c = mfma_32x32x16(a.l, b.h, c);
+    c = mfma_32x32x16(a.m, b.m, c);
+    c = mfma_32x32x16(a.h, b.m, c);
+    c = mfma_32x32x16(a.m, b.h, c);
+    return mfma_32x32x16(a.h, b.h, c);
   }
-  static __device__ __forceinline__ float dot(Frag a, Frag b, float acc) {
+  // with the small terms in an accumulator of their own: 0.50 | 0.89e-7 in the comparison above
+  static __device__ __forceinline__ void mfma(const Frag &a, const Frag &b, f32x16 &c, f32x16 &small) {
+    small = mfma_32x32x16(a.h, b.l, small);
+    small = mfma_32x32x16(a.l, b.h, small);
+    small = mfma_32x32x16(a.m, b.m, small);
+    small = mfma_32x32x16(a.h, b.m, small);
+    small = mfma_32x32x16(a.m, b.h, small);
+    c = mfma_32x32x16(a.h, b.h, c);
+  }
+  static __device__ __forceinline__ float dot(f32x4 a, f32x4 b, float acc) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc = fmaf(a[e], b[e], acc);
     return acc;
+  }
+  // results: rows of 256 bytes, chunk cc of row r at cc ^ rot(r) (free of bank conflicts for both accesses)
+  static __device__ __forceinline__ int off(int r, int cc) {
+    return r * 256 + ((cc ^ ((r & 3) | ((r >> 1) & 4) | ((r & 4) << 1))) << 4);
   }
   static __device__ __forceinline__ void stage(unsigned char *t, const f32x16 &c0, const f32x16 &c1, float scale,
                                                int lane) {
@@ -154,34 +196,50 @@ template <> struct TileT<float> {
         *reinterpret_cast<f32x4 *>(g + row * ld + cc * 4) = *reinterpret_cast<const f32x4 *>(t + off(row, cc));
     }
   }
-  static __device__ __forceinline__ Frag slice(const f32x16 &c0, const f32x16 &c1, int i) {
+  static __device__ __forceinline__ Piece piece(const f32x16 &c0, const f32x16 &c1, int i) {
     const f32x16 &c = i < 4 ? c0 : c1;
     const int v = (i & 3) * 4;
     return f32x4{c[v], c[v + 1], c[v + 2], c[v + 3]};
   }
   static __device__ __forceinline__ int key_of_col(int c) { return c; }
-  static __device__ __forceinline__ int chunk_at(int p, int &row) { row = p >> 4; return (p & 15) ^ rot(row); }
-  template <int ROWS = 64, int WAVES = 4> struct DMA {
-    static constexpr int PER = ROWS / (4 * WAVES);
-    int g_off[PER], l_off[PER];
-    __device__ __forceinline__ DMA(int wave, int lane, int64_t ld) {
+  // ROWS x 64 numbers of a matrix, from memory to registers (fetch) and from there, split, to LDS (put).
+  // STRIP: instead, 32 rows of the CHUNKS chunks of eight keys from chunk `first` on of a strip tile (below), where a row's
+  // chunk is two pieces 32 lanes apart.
+  template <int ROWS, int WAVES, bool STRIP = false, int CHUNKS = 8> struct Tile {
+    static constexpr int PER = ROWS * CHUNKS / (64 * WAVES);
+    static_assert(!STRIP || ROWS == 32, "a block of a strip tile");
+    uint32_t g_off[PER];  // bytes
+    int l_off[PER];
+    f32x4 r[PER][2];
+    __device__ __forceinline__ Tile(int wave, int lane, int64_t ld, int first = 0) {
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
-        const int p = (wave * PER + j) * 64 + lane, row = p >> 4, cc = (p & 15) ^ rot(row);
-        g_off[j] = row * (int)ld + cc * 4;
-        l_off[j] = (wave * PER + j) * 1024;
+        const int p = (wave * PER + j) * 64 + lane;
+        const int row = STRIP ? p & 31 : p >> 3, cc = STRIP ? (p >> 5) + first : p & 7;
+        g_off[j] = 4 * (uint32_t)(STRIP ? cc * 256 + row * 4 : row * (int)ld + cc * 8);
+        l_off[j] = tile_off(row, cc);
       }
     }
-    __device__ __forceinline__ void load(const float *g, unsigned char *t) const {
+    __device__ __forceinline__ void fetch(const float *g) {
 #pragma unroll
-      for (int j = 0; j < PER; ++j) lds_dma16(g + g_off[j], t + l_off[j]);
+      for (int j = 0; j < PER; ++j) {
+        const char *p = reinterpret_cast<const char *>(g) + g_off[j];
+        r[j][0] = *reinterpret_cast<const f32x4 *>(p);
+        r[j][1] = *reinterpret_cast<const f32x4 *>(p + (STRIP ? 512 : 16));
+      }
     }
-    __device__ __forceinline__ void load_unseen(const float *g, uint32_t t) const {
+    __device__ __forceinline__ void put(unsigned char *t, float factor = 1.f) const {
 #pragma unroll
-      for (int j = 0; j < PER; ++j) lds_dma16_unseen(g, g_off[j] * 4, t + l_off[j]);
+      for (int j = 0; j < PER; ++j) {
+        const Split x = STRIP ? split8<false>(r[j][0] * factor, r[j][1] * factor) : split8(r[j][0], r[j][1]);
+        *reinterpret_cast<bf16x8 *>(t + l_off[j]) = x.h;
+        *reinterpret_cast<bf16x8 *>(t + ROWS * 128 + l_off[j]) = x.m;
+        *reinterpret_cast<bf16x8 *>(t + 2 * ROWS * 128 + l_off[j]) = x.l;
+      }
     }
   };
 };
+constexpr int kSlices = 4, kSliceK = 16;  // of a 64 x 64 tile's contraction
 
 // How a strip lies in memory: 64 x 64 tiles, a head's tiles row tile by row tile; inside a tile its two blocks of
 // 32 rows, and of a block the operand fragments in which the scores kernels hold it and the apply
@@ -194,26 +252,25 @@ template <typename T>
 __device__ __forceinline__ void strip_store(T *block, const f32x16 &c0, const f32x16 &c1, int lane) {
   typedef TileT<T> TT;
 #pragma unroll
-  for (int i = 0; i < TT::kSlices; ++i)
-    *reinterpret_cast<typename TT::Frag *>(block + (i * 64 + lane) * (16 / (int)sizeof(T))) = TT::slice(c0, c1, i);
+  for (int i = 0; i < TT::kPieces; ++i)
+    *reinterpret_cast<typename TT::Piece *>(block + (i * 64 + lane) * (16 / (int)sizeof(T))) = TT::piece(c0, c1, i);
 }
-// Direct load of a strip tile (ROWS = 32: of one of its blocks) into LDS as rows of 16-byte chunks (chunk 2 i + h of row r: the fragment of
-// slice i that lane (r, h) holds), swizzled like every tile of its type.
-template <typename T, int ROWS, int WAVES> struct StripDMA {
-  static constexpr int PER = TileT<T>::kBytes * ROWS / (64 * 1024 * WAVES);
+// Direct load of a bf16 strip tile into LDS as rows of 16-byte chunks (chunk 2 i + h of row r: the fragment of
+// slice i that lane (r, h) holds), swizzled like every tile.
+template <int WAVES> struct StripDMA {
+  static constexpr int PER = kTileBytes / (1024 * WAVES);
   int g_off[PER], l_off[PER];
   __device__ __forceinline__ StripDMA(int wave, int lane) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      int row;
-      const int cc = TileT<T>::chunk_at((wave * PER + j) * 64 + lane, row);
-      g_off[j] = (row >> 5) * 2048 + ((cc >> 1) * 64 + (row & 31) + (cc & 1) * 32) * (16 / (int)sizeof(T));
+      const int p = (wave * PER + j) * 64 + lane, row = p >> 3, cc = (p & 7) ^ swz_rot(row);
+      g_off[j] = (row >> 5) * 2048 + ((cc >> 1) * 64 + (row & 31) + (cc & 1) * 32) * 8;
       l_off[j] = (wave * PER + j) * 1024;
     }
   }
-  __device__ __forceinline__ void load_unseen(const T *tile, uint32_t t) const {
+  __device__ __forceinline__ void load_unseen(const uint16_t *tile, uint32_t t) const {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) lds_dma16_unseen(tile, g_off[j] * (int)sizeof(T), t + l_off[j]);
+    for (int j = 0; j < PER; ++j) lds_dma16_unseen(tile, g_off[j] * 2, t + l_off[j]);
   }
 };
 
@@ -300,10 +357,79 @@ __device__ __forceinline__ void mask_scores(const StripArgs &a, int64_t wrow, in
       if (kb * 32 + (v >> 2) * 8 + (v & 3) > dlast) s[kb][v] = -INFINITY;
 }
 
-template <typename T, int AH>
-__global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(StripArgs a) {
+// A work-group's rows of a matrix (wave: 32, lane: one) as B operands, from their fp32 pieces or as they are.
+template <typename T, int AH> struct RowFrags {
   typedef TileT<T> TT;
-  constexpr int NS = TT::kSlices;
+  static constexpr bool kSplitNow = sizeof(T) == 4 && AH > 2;  // (no registers for the parts of wider heads: split at use)
+  typename TT::Frag f[kSplitNow ? 1 : AH * kSlices];
+  f32x4 raw[kSplitNow ? AH * kSlices * 2 : 1];
+  // p: the lane's row, at element 8 half.  O: the same place in another matrix, whose dot product with the row is added to acc.
+  template <bool DOT> __device__ __forceinline__ void load(const T *p, const T *O, float &acc) {
+#pragma unroll
+    for (int i = 0; i < AH * kSlices; ++i) {
+      if constexpr (sizeof(T) == 2) {
+        f[i] = *reinterpret_cast<const bf16x8 *>(p + i * kSliceK);
+        if (DOT) acc = TT::dot(f[i], *reinterpret_cast<const bf16x8 *>(O + i * kSliceK), acc);
+      } else {
+        const f32x4 *x = reinterpret_cast<const f32x4 *>(p + i * kSliceK), *y = reinterpret_cast<const f32x4 *>(O + i * kSliceK);
+        const f32x4 a = x[0], b = x[1];
+        if (DOT) acc = TT::dot(b, y[1], TT::dot(a, y[0], acc));
+        if constexpr (kSplitNow) { raw[2 * i] = a; raw[2 * i + 1] = b; }
+        else f[i] = split8(a, b);
+      }
+    }
+  }
+  __device__ __forceinline__ typename TT::Frag get(int i) const {
+    if constexpr (kSplitNow) return split8(raw[2 * i], raw[2 * i + 1]);
+    else return f[i];
+  }
+};
+
+// The key tiles of a scores kernel on their way to its one LDS buffer: bf16 by direct loads, fp32 through registers, which
+// hold the tile after the requested one where there are enough (HOLD).
+template <typename T, int AH, bool HOLD> struct KeyTiles;
+template <int AH, bool HOLD> struct KeyTiles<uint16_t, AH, HOLD> {
+  typename TileT<uint16_t>::template DMA<> dma;
+  __device__ __forceinline__ KeyTiles(int wave, int lane, int64_t ld) : dma(wave, lane, ld) {}
+  __device__ __forceinline__ void ask(const uint16_t *) {}
+  __device__ __forceinline__ void bring(const uint16_t *g, unsigned char (*t)[kTileBytes]) {
+#pragma unroll
+    for (int ah = 0; ah < AH; ++ah) dma.load(g + ah * 64, t[ah]);
+  }
+};
+template <int AH, bool HOLD> struct KeyTiles<float, AH, HOLD> {
+  typename TileT<float>::template Tile<64, 4> tile;
+  f32x4 held[HOLD ? AH - 1 : 0][2][2];
+  __device__ __forceinline__ KeyTiles(int wave, int lane, int64_t ld) : tile(wave, lane, ld) {}
+  __device__ __forceinline__ void ask(const float *g) {
+    if constexpr (HOLD) {
+#pragma unroll
+      for (int ah = AH - 1; ah >= 0; --ah) {
+        tile.fetch(g + ah * 64);
+        if (ah > 0) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) { held[ah - 1][j][0] = tile.r[j][0]; held[ah - 1][j][1] = tile.r[j][1]; }
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void bring(const float *g, unsigned char (*t)[TileT<float>::kBytes]) {
+#pragma unroll
+    for (int ah = 0; ah < AH; ++ah) {
+      if constexpr (!HOLD) tile.fetch(g + ah * 64);
+      else if (ah > 0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) { tile.r[j][0] = held[ah - 1][j][0]; tile.r[j][1] = held[ah - 1][j][1]; }
+      }
+      tile.put(t[ah]);
+    }
+  }
+};
+
+template <typename T, int AH>
+__global__ void __launch_bounds__(256, AH <= 2 ? (sizeof(T) * AH == 4 ? 3 : 2) : 1) strip_scores_fwd_kernel(StripArgs a) {
+  typedef TileT<T> TT;
+  constexpr int NS = kSlices;
   __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, 1> lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -312,46 +438,58 @@ __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(
   if (pos.t0 >= pos.t1) return;
 
   const T *Kh = static_cast<const T *>(a.K) + pos.head * a.L * a.A;
-  const typename TT::template DMA<> dma(wave, lane, a.A);
-  auto load = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ah = 0; ah < AH; ++ah) dma.load(Kh + (int64_t)t * 64 * a.A + ah * 64, lds.t[0][ah]);
-  };
-  load(pos.t0);
+  auto at = [&](int t) { return Kh + (int64_t)t * 64 * a.A; };
+  KeyTiles<T, AH, true> keys(wave, lane, a.A);
+  keys.ask(at(pos.t0));
+  keys.bring(at(pos.t0), lds.t[0]);
+  if (pos.t0 + 1 < pos.t1) keys.ask(at(pos.t0 + 1));
   const int64_t wrow = pos.row0 + wave * 32;  // (rows come in multiples of 64: a wave's rows are there or not)
   const bool rows_here = wrow < a.rows;
-  typename TT::Frag q[AH * NS];
+  RowFrags<T, AH> q;
   if (rows_here) {
-    const T *qp = static_cast<const T *>(a.Q) + (pos.head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
-#pragma unroll
-    for (int i = 0; i < AH * NS; ++i)
-      q[i] = *reinterpret_cast<const typename TT::Frag *>(qp + i * TT::kSliceK);
+    const T *qp = static_cast<const T *>(a.Q) + (pos.head * a.Lq + wrow + col) * a.A + half * (kSliceK / 2);
+    float none;
+    q.template load<false>(qp, qp, none);
   }
   const TT tt(lane);
-  wait_vmem();
-  __syncthreads();
+  if (sizeof(T) == 2) wait_vmem();
+  barrier_lds();
   for (int t = pos.t0; t < pos.t1; ++t) {
     const int64_t k0 = (int64_t)t * 64;
     const bool work = rows_here && tile_seen(a, wrow, k0);
     f32x16 s[2];
     if (work) {
+      f32x16 rest[2];  // fp32: the small terms' own sums (the row's LSE, sum and all, then errs less than with fp32 products)
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
-      typename TT::Frag kf[2][2];
-      pipelined<AH * NS>(
-          [&](int i, int b) __attribute__((always_inline)) {
+        for (int v = 0; v < 16; ++v) { s[kb][v] = 0.f; rest[kb][v] = 0.f; }
+      // (a step: both 32-key blocks of a slice; fp32, whose operands are three times the registers: one of them)
+      constexpr int KB = sizeof(T) == 4 ? 1 : 2, ST = 2 / KB;
+      typename TT::Frag kf[2][KB];
+      pipelined<AH * NS * ST>(
+          [&](int u, int b) __attribute__((always_inline)) {
+            const int i = u / ST;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) kf[b][kb] = tt.rows(lds.t[0][i / NS], kb * 32, i % NS);
+            for (int kb = 0; kb < KB; ++kb) kf[b][kb] = tt.rows(lds.t[0][i / NS], (u % ST + kb) * 32, i % NS);
           },
-          [&](int i, int b) __attribute__((always_inline)) {
+          [&](int u, int b) __attribute__((always_inline)) {
+            const typename TT::Frag qf = q.get(u / ST);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) s[kb] = TT::mfma(kf[b][kb], q[i], s[kb]);
+            for (int kb = 0; kb < KB; ++kb) TT::mfma(kf[b][kb], qf, s[u % ST + kb], rest[u % ST + kb]);
           });
+      if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) s[kb][v] += rest[kb][v];
+      }
     }
     barrier_lds();
-    if (t + 1 < pos.t1) load(t + 1);
+    if (t + 1 < pos.t1) {
+      keys.bring(at(t + 1), lds.t[0]);
+      if (t + 2 < pos.t1) keys.ask(at(t + 2));
+    }
     __builtin_amdgcn_sched_barrier(0);
     if (work) {
       mask_scores(a, wrow, k0, lane, s);
@@ -377,8 +515,8 @@ __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(
       }
       strip_store(static_cast<T *>(a.strip) + strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) +
                       (wave & 1) * 2048, s[0], s[1], lane);
-      wait_loads_before_stores<TT::kStores>();
-    } else {
+      if (sizeof(T) == 2) wait_loads_before_stores<TT::kPieces>();
+    } else if (sizeof(T) == 2) {
       wait_vmem();
     }
     barrier_lds();
@@ -388,8 +526,9 @@ __global__ void __launch_bounds__(256, AH <= 2 ? 2 : 1) strip_scores_fwd_kernel(
 template <typename T, int AH>
 __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores_bwd_kernel(StripArgs a) {
   typedef TileT<T> TT;
-  constexpr int NS = TT::kSlices;
-  __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, 2> lds;
+  constexpr int NS = kSlices;
+  constexpr bool ONE = sizeof(T) * AH == 16;  // fp32 heads of 256: K and V tiles take turns in LDS
+  __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, ONE ? 1 : 2> lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
@@ -398,33 +537,35 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
 
   const T *Kh = static_cast<const T *>(a.K) + pos.head * a.L * a.A;
   const T *Vh = static_cast<const T *>(a.V) + pos.head * a.L * a.A;
-  const typename TT::template DMA<> dma(wave, lane, a.A);
-  auto load = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ah = 0; ah < AH; ++ah) {
-      dma.load(Kh + (int64_t)t * 64 * a.A + ah * 64, lds.t[0][ah]);
-      dma.load(Vh + (int64_t)t * 64 * a.A + ah * 64, lds.t[1][ah]);
-    }
+  KeyTiles<T, AH, true> keys(wave, lane, a.A);
+  KeyTiles<T, AH, (AH <= 2)> vals(wave, lane, a.A);
+  auto ask = [&](int t) __attribute__((always_inline)) {
+    keys.ask(Kh + (int64_t)t * 64 * a.A);
+    vals.ask(Vh + (int64_t)t * 64 * a.A);
   };
-  load(pos.t0);
+  auto bring = [&](int t) __attribute__((always_inline)) {
+    keys.bring(Kh + (int64_t)t * 64 * a.A, lds.t[0]);
+    if (!ONE) vals.bring(Vh + (int64_t)t * 64 * a.A, lds.t[ONE ? 0 : 1]);
+  };
+  ask(pos.t0);
+  bring(pos.t0);
+  if (pos.t0 + 1 < pos.t1) {
+    if (ONE) keys.ask(Kh + (int64_t)(pos.t0 + 1) * 64 * a.A);
+    else ask(pos.t0 + 1);
+  }
   const int64_t wrow = pos.row0 + wave * 32;
   const bool rows_here = wrow < a.rows;
-  typename TT::Frag q[AH * NS], g[AH * NS];
+  RowFrags<T, AH> q, g;
   // bf16: -LSE / scale and -D of the lane's row, which the accumulators start from.  fp32: the reference of the row's
   // exponents, LSE less the logarithm of a power of two that brings likely scores near it (any value near LSE will
   // do; an exponent is rounded at its own size.  Scores beyond about 1e8 would leave its range), and D.
   float nl = 0.f, nd = 0.f;
   if (rows_here) {
-    const int64_t off = (pos.head * a.Lq + wrow + col) * a.A + half * (TT::kSliceK / 2);
-    const T *qp = static_cast<const T *>(a.Q) + off, *gp = static_cast<const T *>(a.dO) + off;
-    const T *op = static_cast<const T *>(a.O) + off;
+    const int64_t off = (pos.head * a.Lq + wrow + col) * a.A + half * (kSliceK / 2);
+    const T *gp = static_cast<const T *>(a.dO) + off;
     float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < AH * NS; ++i) {
-      q[i] = *reinterpret_cast<const typename TT::Frag *>(qp + i * TT::kSliceK);
-      g[i] = *reinterpret_cast<const typename TT::Frag *>(gp + i * TT::kSliceK);
-      acc = TT::dot(g[i], *reinterpret_cast<const typename TT::Frag *>(op + i * TT::kSliceK), acc);
-    }
+    q.template load<false>(static_cast<const T *>(a.Q) + off, gp, acc);
+    g.template load<true>(gp, static_cast<const T *>(a.O) + off, acc);
     nd = -xhalf_sum(acc);
     const float lse = a.LSE_in[pos.head * a.Lq + wrow + col];
     if constexpr (kOwnSum<T>) {
@@ -435,8 +576,8 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
     }
   }
   const TT tt(lane);
-  wait_vmem();
-  __syncthreads();
+  if (sizeof(T) == 2) wait_vmem();
+  barrier_lds();
   for (int t = pos.t0; t < pos.t1; ++t) {
     const int64_t k0 = (int64_t)t * 64;
     const bool work = rows_here && tile_seen(a, wrow, k0);
@@ -446,25 +587,45 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) { s[kb][v] = kOwnSum<T> ? 0.f : nl; dp[kb][v] = kOwnSum<T> ? 0.f : nd; }
-      typename TT::Frag kf[2][2], vf[2][2];
-      pipelined<AH * NS>(
-          [&](int i, int b) __attribute__((always_inline)) {
+    }
+    constexpr int KB = sizeof(T) == 4 ? 1 : 2, ST = 2 / KB;  // (see the forward)
+    auto products = [&](auto K, auto V) __attribute__((always_inline)) {
+      typename TT::Frag kf[2][KB], vf[2][KB];
+      pipelined<AH * NS * ST>(
+          [&](int u, int b) __attribute__((always_inline)) {
+            const int i = u / ST;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-              kf[b][kb] = tt.rows(lds.t[0][i / NS], kb * 32, i % NS);
-              vf[b][kb] = tt.rows(lds.t[1][i / NS], kb * 32, i % NS);
+            for (int kb = 0; kb < KB; ++kb) {
+              if (K) kf[b][kb] = tt.rows(lds.t[0][i / NS], (u % ST + kb) * 32, i % NS);
+              if (V) vf[b][kb] = tt.rows(lds.t[ONE ? 0 : 1][i / NS], (u % ST + kb) * 32, i % NS);
             }
           },
-          [&](int i, int b) __attribute__((always_inline)) {
+          [&](int u, int b) __attribute__((always_inline)) {
+            typename TT::Frag qf, gf;
+            if (K) qf = q.get(u / ST);
+            if (V) gf = g.get(u / ST);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-              s[kb] = TT::mfma(kf[b][kb], q[i], s[kb]);
-              dp[kb] = TT::mfma(vf[b][kb], g[i], dp[kb]);
+            for (int kb = 0; kb < KB; ++kb) {
+              if (K) s[u % ST + kb] = TT::mfma(kf[b][kb], qf, s[u % ST + kb]);
+              if (V) dp[u % ST + kb] = TT::mfma(vf[b][kb], gf, dp[u % ST + kb]);
             }
           });
+    };
+    if (work) products(std::true_type{}, std::integral_constant<bool, !ONE>{});
+    if constexpr (ONE) {
+      barrier_lds();
+      vals.bring(Vh + (int64_t)t * 64 * a.A, lds.t[0]);
+      barrier_lds();
+      if (work) products(std::false_type{}, std::true_type{});
     }
     barrier_lds();
-    if (t + 1 < pos.t1) load(t + 1);
+    if (t + 1 < pos.t1) {
+      bring(t + 1);
+      if (t + 2 < pos.t1) {
+        if (ONE) keys.ask(Kh + (int64_t)(t + 2) * 64 * a.A);
+        else ask(t + 2);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
     if (work) {
       mask_scores(a, wrow, k0, lane, s);
@@ -492,8 +653,8 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
       const int64_t o = strip_tile<T>(pos.head, a.rows / 64, wrow / 64, a.L / 64, t) + (wave & 1) * 2048;
       strip_store(static_cast<T *>(a.strip) + o, s[0], s[1], lane);
       strip_store(static_cast<T *>(a.strip2) + o, dp[0], dp[1], lane);
-      wait_loads_before_stores<2 * TT::kStores>();
-    } else {
+      if (sizeof(T) == 2) wait_loads_before_stores<2 * TT::kPieces>();
+    } else if (sizeof(T) == 2) {
       wait_vmem();
     }
     barrier_lds();
@@ -514,14 +675,23 @@ struct ApplyArgs {
   float *norm;  // fp32 backward: (head, rows)
 };
 
+// The tiles of X on their way to LDS.
+template <typename T, int WAVES> struct XTile;
+template <int WAVES> struct XTile<uint16_t, WAVES> { typedef typename TileT<uint16_t>::template DMA<WAVES> type; };
+template <int WAVES> struct XTile<float, WAVES> { typedef typename TileT<float>::template Tile<64, WAVES> type; };
 // RW waves share the work-group's rows, 32 each; KS groups of such waves share the key tiles, group g taking every
 // KS-th, and their sums are added in LDS.
 template <typename T, int AHW, bool WEIGHT, int RW, int KS>
 __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2)) strip_apply_kernel(StripArgs a, ApplyArgs p) {
   typedef TileT<T> TT;
-  constexpr int NS = TT::kSlices, BM = 32 * RW;
+  constexpr int NS = kSlices, NP = TT::kPieces, BM = 32 * RW;
+  constexpr bool F = sizeof(T) == 4;
+  static_assert(!F || AHW == 1, "fp32: 64 columns");
   struct Stage { unsigned char X[AHW][TT::kBytes]; };
-  __shared__ __attribute__((aligned(16))) Stage st0[KS], st1[KS];  // separate objects: see the fused kernels
+  // bf16: two stage buffers, separate objects (see the fused kernels); fp32: one, and the results' staging
+  constexpr int kBuf = KS * (int)sizeof(Stage), kOut = RW * 8192;
+  __shared__ __attribute__((aligned(16))) unsigned char buf0[F && kOut > kBuf ? kOut : kBuf], buf1[F ? 16 : kBuf];
+  Stage *const st0 = reinterpret_cast<Stage *>(buf0), *const st1 = F ? st0 : reinterpret_cast<Stage *>(buf1);
   __shared__ float sums[KS == 1 ? 1 : KS][RW][2][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
@@ -543,26 +713,41 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
   const bool rows_here = wrow < a.rows;
   const int64_t rrow = rows_here ? wrow : row0;  // (a wave without rows reads the first wave's)
   const T *S = static_cast<const T *>(p.strip) + strip_tile<T>(head, a.rows / 64, rrow / 64, ntiles, 0) +
-               (RW == 1 ? (int)(rrow >> 5) & 1 : wave & 1) * 2048 + lane * (16 / (int)sizeof(T));
+               (RW == 1 ? (int)(rrow >> 5) & 1 : wave & 1) * 2048;
   const T *Xh = static_cast<const T *>(p.X) + head * a.L * a.A + a0;
-  const typename TT::template DMA<64, RW> dma_x(wave, lane, a.A);
-  typename TT::Frag s0[NS], s1[NS];
+  typename XTile<T, RW>::type x_tile(wave, lane, a.A);
+  typename TT::Piece s0[NP], s1[F ? 1 : NP];  // (fp32: a piece is fetched for the next tile as soon as it is used)
   constexpr bool kStats = WEIGHT || kOwnSum<T>;
   constexpr int kPer = WEIGHT ? 2 : 1;  // numbers per row and tile
   const float *stats = a.stats + ((head * ntiles) * a.rows + rrow) * kPer;  // (read at col)
   f32x2 ml0 = {0.f, 0.f}, ml1 = {0.f, 0.f};  // m_t (forward) and l_t of the lane's row
-  auto load = [&](int t, Stage &st, typename TT::Frag(&s)[NS], f32x2 &ml) __attribute__((always_inline)) {
+  auto piece = [&](int t, int i) __attribute__((always_inline)) {
+    return *reinterpret_cast<const typename TT::Piece *>(reinterpret_cast<const char *>(S + (int64_t)t * 4096 + i * (1024 / (int)sizeof(T))) + (uint32_t)lane * 16);
+  };
+  auto load = [&](int t, Stage &st, auto &s, f32x2 &ml, auto pieces) __attribute__((always_inline)) {
     const float *p = stats + (int64_t)t * a.rows * kPer;
     if constexpr (WEIGHT) ml = reinterpret_cast<const f32x2 *>(p)[col];
     else if constexpr (kStats) ml[1] = p[col];
+    if constexpr (!F) {
 #pragma unroll
-    for (int ah = 0; ah < AHW; ++ah) dma_x.load(Xh + (int64_t)t * 64 * a.A + ah * 64, st.X[ah]);
+      for (int ah = 0; ah < AHW; ++ah) x_tile.load(Xh + (int64_t)t * 64 * a.A + ah * 64, st.X[ah]);
+    }
+    if constexpr (pieces) {
 #pragma unroll
-    for (int i = 0; i < NS; ++i)
-      s[i] = *reinterpret_cast<const typename TT::Frag *>(S + (int64_t)t * 4096 + i * (1024 / (int)sizeof(T)));
+      for (int i = 0; i < NP; ++i) s[i] = piece(t, i);
+    }
+  };
+  auto fetch_x = [&](int t) __attribute__((always_inline)) {  // fp32: to registers, a tile ahead of the strip's
+    if constexpr (F) { if (t < nt) x_tile.fetch(Xh + (int64_t)t * 64 * a.A); }
+  };
+  auto put_x = [&](int t) __attribute__((always_inline)) {
+    if constexpr (F) { if (t < nt) x_tile.put(st0[grp].X[0]); }
   };
   int t = grp;  // this group's tile
-  if (KS == 1 || t < nt) load(t, st0[grp], s0, ml0);
+  fetch_x(t);
+  if (KS == 1 || t < nt) load(t, st0[grp], s0, ml0, std::true_type{});
+  put_x(t);
+  fetch_x(t + KS);
 
   float M = -INFINITY;  // the row's largest m_t
   if (WEIGHT) {
@@ -591,12 +776,11 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
 
   wait_vmem();
 #pragma unroll
-  for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(s0[i]));  // (keeps the first loads in front of this wait)
+  for (int i = 0; i < NP; ++i) asm volatile("" : "+v"(s0[i]));  // (keeps the first loads in front of this wait)
   asm volatile("" : "+v"(ml0));
   __syncthreads();
-  auto step = [&](Stage &cur, typename TT::Frag(&sc)[NS], f32x2 ml, Stage &nxt, typename TT::Frag(&sn)[NS], f32x2 &mln)
-      __attribute__((always_inline)) {
-    if (t + KS < nt) load(t + KS, nxt, sn, mln);
+  auto step = [&](Stage &cur, auto &sc, f32x2 ml, Stage &nxt, auto &sn, f32x2 &mln) __attribute__((always_inline)) {
+    if (t + KS < nt) load(t + KS, nxt, sn, mln, std::integral_constant<bool, !F>{});
     if (rows_here && (KS == 1 || t < nt) && tile_seen(a, wrow, (int64_t)t * 64)) {
       const float w = WEIGHT ? __builtin_amdgcn_exp2f(ml[0] - M) : 1.f;
       if constexpr (kStats) {
@@ -608,22 +792,25 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum[v] = WEIGHT ? fmaf(w, c[v], sum[v]) : sum[v] + c[v];
       };
-      if constexpr (sizeof(T) == 4) {  // one block of 32 columns after the other: registers
-        f32x16 c;
-        typename TT::Frag xf[2];
-        pipelined<NS * 2 * AHW>(
-            [&](int i, int b) __attribute__((always_inline)) {
-              const int db = i / NS;
-              xf[b] = tt.cols(cur.X[db >> 1], i % NS, db & 1);
-            },
-            [&](int i, int b) __attribute__((always_inline)) {
-              if (i % (NS / 2) == 0) {
+      if constexpr (F) {  // 32 keys at a time (LDS reads are hidden by the other waves: three fit a SIMD without a second set)
+        f32x16 c[2];
+        const int tn = t + KS < nt ? t + KS : t;  // (after the last tile: refetched, not used)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) c[v] = 0.f;
-              }
-              c = TT::mfma(xf[b], sc[i % NS], c);
-              if (i % (NS / 2) == NS / 2 - 1) add(o[i / NS], c);
-            });
+        for (int s = 0; s < NS; ++s) {
+          const typename TT::Frag pf = split8<false>(sc[2 * s], sc[2 * s + 1]);
+          sc[2 * s] = piece(tn, 2 * s);
+          sc[2 * s + 1] = piece(tn, 2 * s + 1);
+#pragma unroll
+          for (int db = 0; db < 2; ++db) {
+            if (s % 2 == 0) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+            }
+            c[db] = TT::mfma(tt.cols(cur.X[0], s, db), pf, c[db]);
+            if (s % 2 == 1) add(o[db], c[db]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       } else {
         f32x16 c[WEIGHT ? 2 * AHW : 1];
         if constexpr (WEIGHT) {
@@ -651,18 +838,29 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
         }
       }
     }
-    wait_vmem();
-    __syncthreads();
+    if constexpr (F) {
+      barrier_lds();
+      put_x(t + KS);
+      fetch_x(t + 2 * KS);
+      barrier_lds();
+    } else {
+      wait_vmem();
+      __syncthreads();
+    }
     t += KS;
   };
   while (t - grp < nt) {
     step(st0[grp], s0, ml0, st1[grp], s1, ml1);
     if (t - grp >= nt) break;
-    step(st1[grp], s1, ml1, st0[grp], s0, ml0);
+    if constexpr (F) step(st0[grp], s0, ml1, st0[grp], s1, ml0);
+    else step(st1[grp], s1, ml1, st0[grp], s0, ml0);
   }
   if constexpr (KS > 1) {
-    static_assert(RW <= 2, "the epilogue's tiles are in the first buffers, the groups' sums in the second");
-    auto slot = [&](int g, int db) { return reinterpret_cast<f32x4 *>(&st1[0].X[0][0] + (((g - 1) * RW + wave) * 2 * AHW + db) * 4096); };
+    // the groups' sums: bf16 in the second buffers, fp32 behind the epilogue's tiles
+    static_assert(RW <= 2 && (F ? kBuf - 16384 : kBuf) >= (KS - 1) * RW * 2 * AHW * 4096, "room for the groups' sums");
+    auto slot = [&](int g, int db) {
+      return reinterpret_cast<f32x4 *>((F ? buf0 + 16384 : buf1) + (((g - 1) * RW + wave) * 2 * AHW + db) * 4096);
+    };
     if (grp > 0) {
 #pragma unroll
       for (int db = 0; db < 2 * AHW; ++db)
@@ -693,7 +891,7 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
     if (WEIGHT) p.LSE[head * a.Lq + wrow + col] = fmaf(M, kLn2, logf(l));
     else if (kStats) p.norm[head * a.rows + wrow + col] = norm;
   }
-  unsigned char *ot = (wave < 2 ? st0[0].X[0] : st1[0].X[0]) + (wave & 1) * (TT::kBytes / 2);  // (free after the last barrier)
+  unsigned char *ot = F ? buf0 + wave * 8192 : (wave < 2 ? buf0 : buf1) + (wave & 1) * 4096;  // (free after the last barrier)
   T *out = static_cast<T *>(p.out) + (head * a.Lq + wrow) * a.A + a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
@@ -717,143 +915,59 @@ struct CollectArgs {
 };
 
 // WK waves share the work-group's keys, 32 each; QS groups of such waves share the row tiles (see apply).
-template <typename T, int AHW, int DEPTH, int WK, int QS>
-__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
-  typedef TileT<T> TT;
-  constexpr int RT = sizeof(T) == 4 ? 32 : 64;  // rows per step: 24 KiB (64 columns, either type) leave room for three
-  constexpr int NS = TT::kSlices * RT / 64;     // work-groups on a compute unit
-  constexpr int BK = 32 * WK, KT = (WK + 1) / 2;  // keys, and the key tiles they lie in
-  struct Stage { unsigned char S[KT][TT::kBytes * RT / 64], Y[AHW][TT::kBytes * RT / 64]; };
-  __shared__ __attribute__((aligned(16))) Stage st[QS * DEPTH];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
-  const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
-  const int col = lane & 31, half = lane >> 5;
-  uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t cblocks = (uint32_t)(a.A / (64 * AHW));
-  const int a0 = (int)(wg % cblocks) * (64 * AHW);
-  wg /= cblocks;
-  const bool which = wg & 1;
-  wg >>= 1;
-  const int64_t key0 = (int64_t)(wg % (uint32_t)a.kblocks) * BK;
-  const int64_t head = wg / (uint32_t)a.kblocks;
-  const int nt = (int)(a.rows / RT);
-  int t0 = 0;
-  if (a.causal && key0 > a.q0 + 63) {  // first row tile whose last row sees the block's first key
+struct CollectPos {  // of a work-group of BK keys x 64 AHW columns
+  int64_t head, key0;
+  int a0;
+  bool which;
+  __device__ __forceinline__ CollectPos(const StripArgs &a, int BK, int AHW) {
+    uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t cblocks = (uint32_t)(a.A / (64 * AHW));
+    a0 = (int)(wg % cblocks) * (64 * AHW);
+    wg /= cblocks;
+    which = wg & 1;
+    wg >>= 1;
+    key0 = (int64_t)(wg % (uint32_t)a.kblocks) * BK;
+    head = wg / (uint32_t)a.kblocks;
+  }
+  // first tile of RT rows whose last row sees the block's first key
+  __device__ __forceinline__ int first_tile(const StripArgs &a, int RT, int nt) const {
+    if (!a.causal || key0 <= a.q0 + 63) return 0;
     const int64_t f = (key0 - a.q0) / 64 * (64 / RT);
-    t0 = f < nt ? (int)f : nt;
+    return f < nt ? (int)f : nt;
   }
-  const int64_t ktiles = a.L / 64;
-  const T *Sh = static_cast<const T *>(which ? p.strip[1] : p.strip[0]) +
-                strip_tile<T>(head, a.rows / 64, 0, ktiles, key0 / 64);
-  const int64_t second = key0 + 64 < a.L ? 4096 : 0;  // (no second key tile: refetch the first)
-  const T *Yh = static_cast<const T *>(which ? p.Y[1] : p.Y[0]) + head * a.Lq * a.A + a0;
-  const StripDMA<T, RT, WK> dma_s(wave, lane);
-  const typename TT::template DMA<RT, WK> dma_y(wave, lane, a.A);
-  const uint32_t lds0 = lds_address(&st[grp * DEPTH]);
-  // fp32: the row tile's factors.  (From registers, loaded a tile ahead, they cost the compiler's waits for all loads in
-  // flight: 181 us instead of 152 at B16 Z12 L512.)
-  __shared__ __attribute__((aligned(16))) float norm[kOwnSum<T> ? QS * DEPTH * 64 : 4];
-  const float *norms = p.norm + head * a.rows;
-  constexpr int kLoads = KT * StripDMA<T, RT, WK>::PER + AHW * TT::template DMA<RT, WK>::PER;  // of a wave, per row tile
-  auto load = [&](int tt_, int b) __attribute__((always_inline)) {  // row tile tt_ -> buffer b
-    const int row = tt_ * RT;
-    const T *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
-    const uint32_t d = lds0 + (uint32_t)b * (uint32_t)sizeof(Stage);
-    if (kOwnSum<T> && wave == 0)  // (64 numbers for 32 rows)
-      lds_dma4_unseen(norms + row, lane * 4, lds_address(&norm[0]) + (uint32_t)(grp * DEPTH + b) * 256);
-    dma_s.load_unseen(s, d);
-    if (KT == 2) dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
+};
+// groups 1 .. QS - 1 leave their sums in LDS behind the first 16 KiB, which the epilogue takes, and group 0 adds them;
+// false: the wave is done
+template <int WK, int QS, int DB>
+__device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], int grp, int wave, int lane) {
+  auto slot = [&](int g, int db) { return reinterpret_cast<f32x4 *>(lds + 16384 + (((g - 1) * WK + wave) * DB + db) * 4096); };
+  if (grp > 0) {
 #pragma unroll
-    for (int ah = 0; ah < AHW; ++ah)
-      dma_y.load_unseen(Yh + (int64_t)row * a.A + ah * 64, d + (uint32_t)(sizeof(st[0].S) + ah * sizeof(st[0].Y[0])));
-  };
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-  for (int i = 0; i + 1 < DEPTH; ++i)
-    if (t0 + grp + i * QS < nt) load(t0 + grp + i * QS, i);
-  const int64_t wkey = key0 + wave * 32, wtile = wkey & ~(int64_t)63;
-  const int wcols = (int)(wkey >> 5) & 1;  // the wave's columns of the key tile
-  const bool keys_here = wkey < a.L;
-  const TT tt(lane);
-  f32x16 o[2 * AHW];
+      for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
+  }
+  barrier_lds();
+  if (grp > 0) return false;
+  for (int q = 1; q < QS; ++q)
 #pragma unroll
-  for (int db = 0; db < 2 * AHW; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  static_assert(!kOwnSum<T> || DEPTH == 2, "kLoads does not count the first wave's factors");
-  int b = 0;  // buffer of tile t
-  for (; t0 < nt; t0 += QS) {
-    const int t = t0 + grp;  // this group's tile
-    // tile t has arrived, and behind the barrier every wave is done with tile t - 1, whose buffer takes the next one
-    if (DEPTH == 3 && t + QS < nt) wait_loads<kLoads>();
-    else wait_loads<0>();
-    barrier_lds();
-    if (t + (DEPTH - 1) * QS < nt) load(t + (DEPTH - 1) * QS, b == 0 ? DEPTH - 1 : b - 1);
-    const Stage &cur = st[grp * DEPTH + b];
-    if (keys_here && (QS == 1 || t < nt) && tile_seen(a, (int64_t)t * RT, wtile)) {
-      const unsigned char *S = cur.S[wave >> 1];
-      const float *n = norm + (grp * DEPTH + b) * 64 + half * (TT::kSliceK / 2);
-      typename TT::Frag sf[2], nf[2], yf[2][2 * AHW];
-      f32x16 c[kOwnSum<T> ? 2 * AHW : 1];  // fp32: the row tile's own sum
-      if constexpr (kOwnSum<T>) {
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 x = slot(q, db)[g * 64 + lane];
 #pragma unroll
-        for (int db = 0; db < 2 * AHW; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+        for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
       }
-      pipelined<NS>(
-          [&](int s, int b) __attribute__((always_inline)) {
-            sf[b] = tt.cols(S, s, wcols);
-            if constexpr (kOwnSum<T>)
-              nf[b] = *reinterpret_cast<const typename TT::Frag *>(n + s * TT::kSliceK);
-#pragma unroll
-            for (int db = 0; db < 2 * AHW; ++db) yf[b][db] = tt.cols(cur.Y[db >> 1], s, db & 1);
-          },
-          [&](int s, int b) __attribute__((always_inline)) {
-            if constexpr (kOwnSum<T>) sf[b] *= nf[b];
-#pragma unroll
-            for (int db = 0; db < 2 * AHW; ++db) {
-              f32x16 &acc = kOwnSum<T> ? c[kOwnSum<T> ? db : 0] : o[db];
-              acc = TT::mfma(yf[b][db], sf[b], acc);
-            }
-          });
-      if constexpr (kOwnSum<T>) {
-#pragma unroll
-        for (int db = 0; db < 2 * AHW; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) o[db][v] += c[db][v];
-      }
-    }
-    b = b + 1 < DEPTH ? b + 1 : 0;
-  }
-  barrier_lds();  // the epilogue writes to the buffers
-  if constexpr (QS > 1) {
-    // groups 1 .. QS - 1 leave their sums behind the first 16 KiB, which the epilogue takes
-    static_assert(WK <= 2 && sizeof(st) >= 16384 + (QS - 1) * WK * 2 * AHW * 4096, "room for the groups' sums");
-    auto slot = [&](int g, int db) {
-      return reinterpret_cast<f32x4 *>(reinterpret_cast<unsigned char *>(st) + 16384 + (((g - 1) * WK + wave) * 2 * AHW + db) * 4096);
-    };
-    if (grp > 0) {
-#pragma unroll
-      for (int db = 0; db < 2 * AHW; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
-    }
-    barrier_lds();
-    if (grp > 0) return;
-    for (int q = 1; q < QS; ++q)
-#pragma unroll
-      for (int db = 0; db < 2 * AHW; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 x = slot(q, db)[g * 64 + lane];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
-        }
-  }
-  if (!keys_here) return;
+  return true;
+}
+// ... and the wave's 32 keys from wkey on, column a0 on, become results or stay in the fp32 accumulators
+template <typename T, int AHW>
+__device__ __forceinline__ void collect_out(const StripArgs &a, const CollectArgs &p, const CollectPos &pos, f32x16 (&o)[2 * AHW],
+                                            int64_t wkey, unsigned char *ot, int lane) {
+  typedef TileT<T> TT;
+  const int col = lane & 31, half = lane >> 5;
   if (p.add || p.keep) {
-    float *acc = (which ? p.acc[1] : p.acc[0]) + (head * a.L + wkey + TT::key_of_col(col)) * a.A + a0 + half * 4;
+    float *acc = (pos.which ? p.acc[1] : p.acc[0]) + (pos.head * a.L + wkey + TT::key_of_col(col)) * a.A + pos.a0 + half * 4;
 #pragma unroll
     for (int db = 0; db < 2 * AHW; ++db)
 #pragma unroll
@@ -867,15 +981,181 @@ __global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH 
       }
     if (p.keep) return;
   }
-  const float alpha = which ? p.alpha[1] : p.alpha[0];
-  // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
-  unsigned char *ot = reinterpret_cast<unsigned char *>(&st[wave >> 1]) + (wave & 1) * (TT::kBytes / 2);
-  T *out = static_cast<T *>(which ? p.out[1] : p.out[0]) + (head * a.L + wkey) * a.A + a0;
+  const float alpha = pos.which ? p.alpha[1] : p.alpha[0];
+  T *out = static_cast<T *>(pos.which ? p.out[1] : p.out[0]) + (pos.head * a.L + wkey) * a.A + pos.a0;
 #pragma unroll
   for (int ah = 0; ah < AHW; ++ah) {
     TT::stage(ot, o[2 * ah], o[2 * ah + 1], alpha, TT::key_of_col(col) + half * 32);
     TT::flush(ot, out + ah * 64, 32, lane, a.A);
   }
+}
+
+template <int AHW, int DEPTH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
+  typedef uint16_t T;
+  typedef TileT<T> TT;
+  constexpr int BK = 32 * WK, KT = (WK + 1) / 2;  // keys, and the key tiles they lie in
+  struct Stage { unsigned char S[KT][kTileBytes], Y[AHW][kTileBytes]; };  // 24 KiB leave room for three work-groups on a CU
+  __shared__ __attribute__((aligned(16))) Stage st[QS * DEPTH];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
+  const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
+  const CollectPos pos(a, BK, AHW);
+  const int nt = (int)(a.rows / 64);
+  int t0 = pos.first_tile(a, 64, nt);
+  const int64_t ktiles = a.L / 64;
+  const T *Sh = static_cast<const T *>(pos.which ? p.strip[1] : p.strip[0]) +
+                strip_tile<T>(pos.head, nt, 0, ktiles, pos.key0 / 64);
+  const int64_t second = pos.key0 + 64 < a.L ? 4096 : 0;  // (no second key tile: refetch the first)
+  const T *Yh = static_cast<const T *>(pos.which ? p.Y[1] : p.Y[0]) + pos.head * a.Lq * a.A + pos.a0;
+  const StripDMA<WK> dma_s(wave, lane);
+  const typename TT::template DMA<WK> dma_y(wave, lane, a.A);
+  const uint32_t lds0 = lds_address(&st[grp * DEPTH]);
+  constexpr int kLoads = KT * StripDMA<WK>::PER + AHW * TT::template DMA<WK>::PER;  // of a wave, per row tile
+  auto load = [&](int tt_, int b) __attribute__((always_inline)) {  // row tile tt_ -> buffer b
+    const T *s = Sh + tt_ * (ktiles * 4096);
+    const uint32_t d = lds0 + (uint32_t)b * (uint32_t)sizeof(Stage);
+    dma_s.load_unseen(s, d);
+    if (KT == 2) dma_s.load_unseen(s + second, d + (uint32_t)sizeof(st[0].S[0]));
+#pragma unroll
+    for (int ah = 0; ah < AHW; ++ah)
+      dma_y.load_unseen(Yh + (int64_t)tt_ * 64 * a.A + ah * 64, d + (uint32_t)(sizeof(st[0].S) + ah * sizeof(st[0].Y[0])));
+  };
+#pragma unroll
+  for (int i = 0; i + 1 < DEPTH; ++i)
+    if (t0 + grp + i * QS < nt) load(t0 + grp + i * QS, i);
+  const int64_t wkey = pos.key0 + wave * 32, wtile = wkey & ~(int64_t)63;
+  const int wcols = (int)(wkey >> 5) & 1;  // the wave's columns of the key tile
+  const bool keys_here = wkey < a.L;
+  const TT tt(lane);
+  f32x16 o[2 * AHW];
+#pragma unroll
+  for (int db = 0; db < 2 * AHW; ++db)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+  int b = 0;  // buffer of tile t
+  for (; t0 < nt; t0 += QS) {
+    const int t = t0 + grp;  // this group's tile
+    // tile t has arrived, and behind the barrier every wave is done with the tile before, whose buffer takes the next one
+    if (DEPTH == 3 && t + QS < nt) wait_loads<kLoads>();
+    else wait_loads<0>();
+    barrier_lds();
+    if (t + (DEPTH - 1) * QS < nt) load(t + (DEPTH - 1) * QS, b == 0 ? DEPTH - 1 : b - 1);
+    const Stage &cur = st[grp * DEPTH + b];
+    if (keys_here && (QS == 1 || t < nt) && tile_seen(a, (int64_t)t * 64, wtile)) {
+      const unsigned char *S = cur.S[wave >> 1];
+      typename TT::Frag sf[2], yf[2][2 * AHW];
+      pipelined<kSlices>(
+          [&](int s, int b) __attribute__((always_inline)) {
+            sf[b] = tt.cols(S, s, wcols);
+#pragma unroll
+            for (int db = 0; db < 2 * AHW; ++db) yf[b][db] = tt.cols(cur.Y[db >> 1], s, db & 1);
+          },
+          [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int db = 0; db < 2 * AHW; ++db) o[db] = TT::mfma(yf[b][db], sf[b], o[db]);
+          });
+    }
+    b = b + 1 < DEPTH ? b + 1 : 0;
+  }
+  barrier_lds();  // the epilogue writes to the buffers
+  if constexpr (QS > 1) {
+    static_assert(WK <= 2 && sizeof(st) >= 16384 + (QS - 1) * WK * 2 * AHW * 4096, "room for the groups' sums");
+    if (!add_groups<WK, QS>(reinterpret_cast<unsigned char *>(st), o, grp, wave, lane)) return;
+  }
+  if (!keys_here) return;
+  // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
+  collect_out<T, AHW>(a, p, pos, o, wkey, reinterpret_cast<unsigned char *>(&st[wave >> 1]) + (wave & 1) * 4096, lane);
+}
+
+// fp32: 64 columns, 32 rows a step through registers; the strips' rows are scaled on their way to LDS.
+template <int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : 2) strip_collect_f32_kernel(StripArgs a, CollectArgs p) {
+  typedef TileT<float> TT;
+  constexpr int RT = 32, PL = RT * 128;                    // rows per step, bytes of a part's plane
+  constexpr int BK = 32 * WK, KT = (WK + 1) / 2;           // (see above)
+  constexpr int CH = WK == 1 ? 4 : 8;                      // chunks of eight keys per tile that the work-group needs
+  struct Stage { unsigned char S[KT][3 * PL], Y[3 * PL]; };
+  __shared__ __attribute__((aligned(16))) Stage st[QS];
+  static_assert(sizeof(st) >= (QS > 1 ? 16384 + (QS - 1) * WK * 2 * 4096 : WK * 8192), "room for the groups' sums and the epilogue");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
+  const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
+  const CollectPos pos(a, BK, 1);
+  const int nt = (int)(a.rows / RT);
+  int t0 = pos.first_tile(a, RT, nt);
+  const int64_t ktiles = a.L / 64;
+  const float *Sh = static_cast<const float *>(pos.which ? p.strip[1] : p.strip[0]) +
+                    strip_tile<float>(pos.head, a.rows / 64, 0, ktiles, pos.key0 / 64);
+  const int64_t second = pos.key0 + 64 < a.L ? 4096 : 0;
+  const float *Yh = static_cast<const float *>(pos.which ? p.Y[1] : p.Y[0]) + pos.head * a.Lq * a.A + pos.a0;
+  const float *norms = p.norm + pos.head * a.rows + (lane & 31);
+  const int64_t wkey = pos.key0 + wave * 32, wtile = wkey & ~(int64_t)63;
+  const int wcols = (int)(wkey >> 5) & 1;
+  const bool keys_here = wkey < a.L;
+  typename TT::template Tile<RT, WK, true, CH> s_tile(wave, lane, 0, WK == 1 ? wcols * 4 : 0), s_tile2(wave, lane, 0);
+  typename TT::template Tile<RT, WK> y_tile(wave, lane, a.A);
+  float factor = 0.f;
+  auto fetch = [&](int t) __attribute__((always_inline)) {
+    if (t >= nt) return;
+    const int row = t * RT;
+    const float *s = Sh + (row >> 6) * (ktiles * 4096) + (row & 63) * 64;
+    s_tile.fetch(s);
+    if (KT == 2) s_tile2.fetch(s + second);
+    y_tile.fetch(Yh + (int64_t)row * a.A);
+    factor = norms[row];
+  };
+  auto put = [&](int t) __attribute__((always_inline)) {
+    if (t >= nt) return;
+    s_tile.put(st[grp].S[0], factor);
+    if (KT == 2) s_tile2.put(st[grp].S[KT - 1], factor);
+    y_tile.put(st[grp].Y);
+  };
+  fetch(t0 + grp);
+  put(t0 + grp);
+  fetch(t0 + grp + QS);
+  const TT tt(lane);
+  f32x16 o[2];
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+  barrier_lds();
+  for (; t0 < nt; t0 += QS) {
+    const int t = t0 + grp;
+    if (keys_here && (QS == 1 || t < nt) && tile_seen(a, (int64_t)t * RT, wtile)) {
+      const unsigned char *S = st[grp].S[wave >> 1];
+      typename TT::Frag sf[2], yf[2][2];
+      f32x16 c[2];  // the step's own sum
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[db][v] = 0.f;
+      pipelined<RT / kSliceK>(
+          [&](int s, int b) __attribute__((always_inline)) {
+            sf[b] = tt.template cols<PL>(S, s, wcols);
+#pragma unroll
+            for (int db = 0; db < 2; ++db) yf[b][db] = tt.template cols<PL>(st[grp].Y, s, db);
+          },
+          [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int db = 0; db < 2; ++db) c[db] = TT::mfma(yf[b][db], sf[b], c[db]);
+          });
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] += c[db][v];
+    }
+    barrier_lds();
+    put(t + QS);
+    fetch(t + 2 * QS);
+    barrier_lds();
+  }
+  if constexpr (QS > 1) {
+    if (!add_groups<WK, QS>(reinterpret_cast<unsigned char *>(st), o, grp, wave, lane)) return;
+  }
+  if (!keys_here) return;
+  collect_out<float, 1>(a, p, pos, o, wkey, reinterpret_cast<unsigned char *>(st) + wave * 8192, lane);
 }
 
 // ------------------------------------------------------------------ host ----
@@ -977,7 +1257,7 @@ hipError_t launch_scores(const StripArgs &a0, int64_t heads, bool bwd, hipStream
   StripArgs a = a0;
   // Key tiles per work-group: the count (at most 16) whose rounds of work-groups cost least, a work-group costing
   // its tiles and about two more for its prologue.
-  const int64_t tiles = a.L / 64, slots = 256 * (bwd ? (sizeof(T) * a.A <= 256 ? 2 : 1) : (sizeof(T) * a.A <= 256 ? 4 : 2));
+  const int64_t tiles = a.L / 64, slots = 256 * (bwd ? (sizeof(T) * a.A <= 256 ? 2 : 1) : (sizeof(T) * a.A <= 256 ? (sizeof(T) == 4 ? 3 : 4) : 2));
   double best = 1e30;
   for (int per = 1; per <= 16 && per <= tiles; ++per) {
     const int64_t wgs = heads * a.rtiles * ((tiles + per - 1) / per);
@@ -1005,48 +1285,50 @@ hipError_t launch_apply_as(StripArgs a, const ApplyArgs &p, int64_t heads, hipSt
 }
 // Few work-groups: their walks over the key tiles are serial chains on a partly idle chip, so groups of waves share them.
 // The lines are those of a sweep over 2 .. 192 heads of 64 .. 256 elements, 256 .. 3072 rows; forward, us, by W:
-//   fp32, one group -> four: 4 (256 rows) 18.8 -> 12.9, 24 (1536) 72 -> 34, 64 (A 128) 49 -> 20, 144 causal 178 -> 133;
-//   one -> two: 96 (320 rows) 25.4 -> 21.5, 288 190 -> 177, 560 (A 128) 126 -> 110; but 210 34.9 -> 37.8, 432 234 -> 249;
+//   fp32, one group -> four: 4 (256 rows) 16.0 -> 12.8, 24 (1536) 59 -> 35, 64 (A 128) 26 -> 19, 72 causal 71 -> 46;
+//   one -> two: 96 45 -> 37, 192 67.8 -> 66, 288 causal 93 -> 82; but 300 77 -> 81, 400 causal 59.9 -> 61.2;
 //   bf16, one -> four: 24 (1536 rows) 19.5 -> 13.6, 48 (3072) 40 -> 26; one -> two: 144 53 -> 47; but 288 47 -> 49.
 template <typename T, bool WEIGHT>
 hipError_t launch_apply(const StripArgs &a, const ApplyArgs &p, int64_t heads, hipStream_t st) {
   const int64_t W = heads * a.rtiles * (a.A / 64);  // work-groups of 128 rows and 64 columns
-  const bool wide = a.A % 128 == 0;
-  if (W <= 64 || (a.causal && W <= 144)) return launch_apply_as<T, 1, WEIGHT, 1, 4>(a, p, heads, st);
-  const bool two = sizeof(T) == 4 ? W <= (wide ? 600 : 390) && (a.causal || wide || W <= 128 || W >= 230)
-                                  : W <= (a.causal ? 360 : 240);
+  if (W <= 64 || (a.causal && W <= (sizeof(T) == 4 ? 96 : 144))) return launch_apply_as<T, 1, WEIGHT, 1, 4>(a, p, heads, st);
+  const bool two = sizeof(T) == 4 ? W <= (a.causal ? 290 : 200) : W <= (a.causal ? 360 : 240);
   if (two) return launch_apply_as<T, 1, WEIGHT, 2, 2>(a, p, heads, st);
-  return wide ? launch_apply_as<T, 2, WEIGHT, 4, 1>(a, p, heads, st) : launch_apply_as<T, 1, WEIGHT, 4, 1>(a, p, heads, st);
+  if constexpr (sizeof(T) == 2)
+    if (a.A % 128 == 0) return launch_apply_as<T, 2, WEIGHT, 4, 1>(a, p, heads, st);
+  return launch_apply_as<T, 1, WEIGHT, 4, 1>(a, p, heads, st);
 }
 
 template <typename T, int AHW, int DEPTH, int WK, int QS>
 hipError_t launch_collect_as(StripArgs a, const CollectArgs &p, int64_t heads, hipStream_t st) {
   a.kblocks = (int)((a.L + 32 * WK - 1) / (32 * WK));
   const dim3 grid((unsigned)(heads * a.kblocks * 2 * (a.A / (64 * AHW))));
-  hipLaunchKernelGGL((strip_collect_kernel<T, AHW, DEPTH, WK, QS>), grid, dim3(64 * WK * QS), 0, st, a, p);
+  if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((strip_collect_f32_kernel<WK, QS>), grid, dim3(64 * WK * QS), 0, st, a, p);
+  else hipLaunchKernelGGL((strip_collect_kernel<AHW, DEPTH, WK, QS>), grid, dim3(64 * WK * QS), 0, st, a, p);
   return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_collect(const StripArgs &a, const CollectArgs &p, int64_t heads, hipStream_t st) {
   const int64_t W = heads * ((a.L + 127) / 128) * 2 * (a.A / 64);  // work-groups of 128 keys and 64 columns
   // Groups of waves on the row tiles of few work-groups, as in apply (same sweep, backward, us, by W): fp32, one group ->
-  // four: 8 37 -> 31, 48 (1536 rows) 159 -> 118; one -> two: 192 107 -> 104, 288 261 -> 246, 576 (A 128) 495 -> 440, causal
-  // 291 -> 277; bf16: A = 128, 128 23.4 -> 21.7, causal 288 58 -> 50, but not causal 65 -> 68.
+  // four: 8 32 -> 26, 48 (1536 rows) 134 -> 100; one -> two: 96 80.9 -> 69.6, 192 87.8 -> 84.9, causal 288 175 -> 155; but
+  // 512 102 -> 110; bf16: A = 128, 128 23.4 -> 21.7, causal 288 58 -> 50, but not causal 65 -> 68.
   if constexpr (sizeof(T) == 4) {
-    if (W <= 64) return launch_collect_as<T, 1, 2, 1, 4>(a, p, heads, st);
-    if (W <= 600) return launch_collect_as<T, 1, 2, 2, 2>(a, p, heads, st);
+    if (W <= 64 || (a.causal && W <= 96)) return launch_collect_as<T, 1, 2, 1, 4>(a, p, heads, st);
+    if (W <= (a.causal ? 480 : 400)) return launch_collect_as<T, 1, 2, 2, 2>(a, p, heads, st);
+    return launch_collect_as<T, 1, 2, 4, 1>(a, p, heads, st);
   } else {
     if ((a.A % 128 == 0 && W <= 256) || (a.causal && W > 256 && W <= 400)) return launch_collect_as<T, 1, 2, 2, 2>(a, p, heads, st);
   }
-  if (a.A % 128 == 0) return launch_collect_as<T, 2, 2, 4, 1>(a, p, heads, st);
-  // bf16 strips come at the rate that requests in flight allow.  With at most one work-group on a compute unit its row
-  // tiles are requested two steps ahead; several bring enough by themselves, and three fit where each takes two
-  // buffers.  The whole backward with two | three buffers, us: 64 work-groups 33.5 | 30.4, 256: 45.4 | 40.8 and
-  // 161.5 | 140.8, 384 (in groups): 1165 | 1180, 1536: 121 | 121; fp32, bound by its products: 256: 131 | 131,
-  // 768: 292 | 309.
-  if constexpr (sizeof(T) == 2)
+  if constexpr (sizeof(T) == 2) {
+    if (a.A % 128 == 0) return launch_collect_as<T, 2, 2, 4, 1>(a, p, heads, st);
+    // bf16 strips come at the rate that requests in flight allow.  With at most one work-group on a compute unit its row
+    // tiles are requested two steps ahead; several bring enough by themselves, and three fit where each takes two
+    // buffers.  The whole backward with two | three buffers, us: 64 work-groups 33.5 | 30.4, 256: 45.4 | 40.8 and
+    // 161.5 | 140.8, 384 (in groups): 1165 | 1180, 1536: 121 | 121.
     if (W <= 256) return launch_collect_as<T, 1, 3, 4, 1>(a, p, heads, st);
-  return launch_collect_as<T, 1, 2, 4, 1>(a, p, heads, st);
+    return launch_collect_as<T, 1, 2, 4, 1>(a, p, heads, st);
+  }
 }
 
 #define RSA_TRY(expr)                       \
