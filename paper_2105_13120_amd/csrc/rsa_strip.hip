@@ -8,6 +8,7 @@
 //   forward    scores: S = Q K^T tile by tile, softmaxed against the tile's own row maximum:
 //                strip tile = exp(S - m_t) (dtype), (m_t, l_t) per row and 64 keys
 //              apply:  LSE from the pairs, O = sum_t exp(m_t - LSE) (strip tile) V
+//              (fp32, where rows are many or walks short: both in one kernel, and no strip; see f32_forward_kernel)
 //   backward   scores: P = exp(S - LSE), dS = P o (dO V^T - D), both tiles written in dtype
 //              apply:  dQ = s dS K;   collect: dV = P^T dO, dK = s dS^T Q
 //
@@ -900,6 +901,187 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
   }
 }
 
+// groups 1 .. QS - 1 leave their sums in LDS behind the first 16 KiB, which the epilogue takes, and group 0 adds them;
+// false: the wave is done
+template <int WK, int QS, int DB>
+__device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], int grp, int wave, int lane) {
+  auto slot = [&](int g, int db) { return reinterpret_cast<f32x4 *>(lds + 16384 + (((g - 1) * WK + wave) * DB + db) * 4096); };
+  if (grp > 0) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
+  }
+  barrier_lds();
+  if (grp > 0) return false;
+  for (int q = 1; q < QS; ++q)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 x = slot(q, db)[g * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
+      }
+  return true;
+}
+// ------------------------------------------------- fp32 forward, one pass ----
+// fp32 heads of 64: a step's 32 keys are scored, softmaxed and applied to V in registers, without the strip (whose write
+// and read took as long as the products do now).  Work-group: as in apply; K and V of a step are split on their way to
+// one LDS buffer per group.  A row's exponents are relative to a whole number (the ceiling of its maximum so far), so that
+// bringing its sums to a new reference is exact; sums and products are formed as in scores and apply.
+struct PassArgs {
+  const float *Q, *K, *V;
+  float *O, *LSE;
+  int64_t L, Lq, q0;
+  int causal;
+  FastDiv by_tiles;  // row tiles of a head
+  float cl2;
+};
+
+template <int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kernel(PassArgs a) {
+  typedef TileT<float> TT;
+  constexpr int BM = 32 * RW, RT = 32, PL = RT * 128;
+  struct Stage { unsigned char K[3 * PL], V[3 * PL]; };
+  constexpr int kBuf = KS * (int)sizeof(Stage), kOut = RW * 8192;
+  __shared__ __attribute__((aligned(16))) unsigned char buf[kBuf > kOut ? kBuf : kOut];
+  __shared__ float sums[KS == 1 ? 1 : KS][RW][2][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % RW;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / RW;
+  const int col = lane & 31, half = lane >> 5;
+  Stage &st = reinterpret_cast<Stage *>(buf)[grp];
+  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x), head = a.by_tiles(wg);
+  uint32_t rt = wg - head * a.by_tiles.d;
+  if (a.causal) rt = a.by_tiles.d - 1 - rt;  // (the long work-groups first)
+  const int row0 = (int)rt * BM, wrow = row0 + wave * 32, Lq = (int)a.Lq, q0 = (int)a.q0;
+  const bool rows_here = wrow < Lq;
+  int nt = (int)(a.L / RT);  // steps of 32 keys
+  if (a.causal) {
+    const int seen = (q0 + (row0 + BM < Lq ? row0 + BM : Lq) - 1) / RT + 1;
+    nt = seen < nt ? seen : nt;
+  }
+  const float *Kh = a.K + (int64_t)head * a.L * 64, *Vh = a.V + (int64_t)head * a.L * 64;
+  typename TT::template Tile<RT, RW> k_tile(wave, lane, 64), v_tile(wave, lane, 64);
+  auto fetch = [&](int t) __attribute__((always_inline)) {
+    if (t >= nt) return;
+    k_tile.fetch(Kh + (int64_t)t * (RT * 64));
+    v_tile.fetch(Vh + (int64_t)t * (RT * 64));
+  };
+  auto put = [&](int t) __attribute__((always_inline)) {
+    if (t >= nt) return;
+    k_tile.put(st.K);
+    v_tile.put(st.V);
+  };
+  int t = grp;  // this group's step
+  fetch(t);
+  RowFrags<float, 1> q;
+  {
+    float none;
+    const float *qp = a.Q + ((int64_t)head * Lq + (rows_here ? wrow : row0) + col) * 64 + half * (kSliceK / 2);
+    q.template load<false>(qp, qp, none);
+  }
+  put(t);
+  fetch(t + KS);
+  const TT tt(lane);
+  f32x16 o[2];
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+  float M = -INFINITY;          // the row's reference, a whole number
+  float l = 0.f, l_err = 0.f;   // the lane's share of the row's sum, and what its additions have lost so far
+  barrier_lds();
+  while (t - grp < nt) {
+    const int k0 = t * RT;
+    if (rows_here && (KS == 1 || t < nt) && (!a.causal || k0 <= q0 + wrow + 31)) {
+      f32x16 s, rest;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[v] = rest[v] = 0.f;
+#pragma unroll
+      for (int i = 0; i < kSlices; ++i) TT::mfma(tt.template rows<PL>(st.K, 0, i), q.get(i), s, rest);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[v] += rest[v];
+      if (a.causal && k0 + 31 > q0 + wrow) {
+        const uint32_t seen = low_bits(q0 + wrow + col + 1 - k0 - half * 4);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = keep_bit(s[v], seen, (v >> 2) * 8 + (v & 3));
+      }
+      float m = s[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) m = fmaxf(m, s[v]);
+      m = ceilf(xhalf_max(m) * a.cl2);
+      if (__builtin_amdgcn_ballot_w64(m > M) != 0) {
+        const float to = fmaxf(m, M);
+        const int by = M > -INFINITY ? (int)fmaxf(M - to, -300.f) : 0;  // (2^-300 of a sum leaves nothing)
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[db][v] = __builtin_ldexpf(o[db][v], by);
+        l = __builtin_ldexpf(l, by);
+        l_err = __builtin_ldexpf(l_err, by);
+        M = to;
+      }
+      const float ref = M > -INFINITY ? M : 0.f;  // (a row that has seen no key yet)
+      float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.cl2, -ref));
+        p[v & 3] += s[v];
+      }
+      const float x = ((p[0] + p[1]) + (p[2] + p[3])) - l_err, sum = l + x;
+      l_err = (sum - l) - x;
+      l = sum;
+      typename TT::Frag pf[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        pf[i] = split8<false>(f32x4{s[i * 8], s[i * 8 + 1], s[i * 8 + 2], s[i * 8 + 3]},
+                              f32x4{s[i * 8 + 4], s[i * 8 + 5], s[i * 8 + 6], s[i * 8 + 7]});
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        f32x16 c;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) c = TT::mfma(tt.template cols<PL>(st.V, i, db), pf[i], c);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] += c[v];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    barrier_lds();
+    put(t + KS);
+    fetch(t + 2 * KS);
+    barrier_lds();
+    t += KS;
+  }
+  l = xhalf_sum(l - l_err);
+  if constexpr (KS > 1) {  // to the largest of the groups' references, and together
+    static_assert(RW <= 2 && kBuf >= 16384 + (KS - 1) * RW * 2 * 4096, "room for the groups' sums behind the epilogue's tiles");
+    sums[grp][wave][0][lane] = M;
+    barrier_lds();
+    float top = M;
+    for (int g = 0; g < KS; ++g) top = fmaxf(top, sums[g][wave][0][lane]);
+    const int by = M > -INFINITY ? (int)fmaxf(M - top, -300.f) : 0;
+    l = __builtin_ldexpf(l, by);
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[db][v] = __builtin_ldexpf(o[db][v], by);
+    M = top;
+    sums[grp][wave][1][lane] = l;
+    if (!add_groups<RW, KS>(buf, o, grp, wave, lane)) return;
+    for (int g = 1; g < KS; ++g) l += sums[g][wave][1][lane];
+  }
+  if (!rows_here) return;
+  const int64_t row = (int64_t)head * Lq + wrow;
+  if (half == 0) a.LSE[row + col] = fmaf(M, kLn2, logf(l));
+  unsigned char *ot = buf + wave * 8192;  // (free after the last barrier)
+  TT::stage(ot, o[0], o[1], 1.0f / l, lane);
+  TT::flush(ot, a.O + row * 64, 32, lane, 64);
+}
+
 // --------------------------------------------------------------- collect ----
 // out (key, A) = alpha * sum over the group's rows of strip(row, key) Y(row, A), two products per launch
 // (dV from P and dO, dK from dS and Q).  Work-group: 128 keys (wave: 32) x 64 AHW columns, walking the row
@@ -936,31 +1118,7 @@ struct CollectPos {  // of a work-group of BK keys x 64 AHW columns
     return f < nt ? (int)f : nt;
   }
 };
-// groups 1 .. QS - 1 leave their sums in LDS behind the first 16 KiB, which the epilogue takes, and group 0 adds them;
-// false: the wave is done
-template <int WK, int QS, int DB>
-__device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], int grp, int wave, int lane) {
-  auto slot = [&](int g, int db) { return reinterpret_cast<f32x4 *>(lds + 16384 + (((g - 1) * WK + wave) * DB + db) * 4096); };
-  if (grp > 0) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) slot(grp, db)[g * 64 + lane] = f32x4{o[db][g * 4], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]};
-  }
-  barrier_lds();
-  if (grp > 0) return false;
-  for (int q = 1; q < QS; ++q)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = slot(q, db)[g * 64 + lane];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[db][g * 4 + e] += x[e];
-      }
-  return true;
-}
-// ... and the wave's 32 keys from wkey on, column a0 on, become results or stay in the fp32 accumulators
+// The wave's 32 keys from wkey on, column a0 on, become results or stay in the fp32 accumulators.
 template <typename T, int AHW>
 __device__ __forceinline__ void collect_out(const StripArgs &a, const CollectArgs &p, const CollectPos &pos, f32x16 (&o)[2 * AHW],
                                             int64_t wkey, unsigned char *ot, int lane) {
@@ -1353,9 +1511,44 @@ StripArgs group_args(const Dims &d, const StripPlan &pl, char *ws, int64_t h0, i
   return a;
 }
 
+// Groups of waves on a walk of the fp32 forward in one pass (128 / groups rows per work-group), or 0: the strip, whose
+// scores are shared by work-groups along the keys too, is better where rows are few and walks long.  us, strip -> one pass, by
+// W, the work-groups of 128 rows: 4 (256 rows) 13.0 -> 10.3, 96 (320) 19.4 -> 15.7, 400 (512) 60 -> 51, 768 (512) 108 -> 75, 480
+// (1536) 210 -> 145, causal 288 (1536) 77 -> 72, 96 (768) 31 -> 24; but 12 (768) 19 -> 23, 144 (1536) 77 -> 88.
+int f32_one_pass(const Dims &d) {
+  if (d.A != 64) return 0;
+  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
+  if (d.L <= 512) {
+    if (W <= (d.causal ? 96 : 64)) return 4;
+    return W <= 128 || (W >= 230 && W <= 320) || (d.causal && W <= 400) ? 2 : 1;
+  }
+  if (d.causal && d.L <= 1024 && W > 64 && W <= 128) return 4;
+  if (d.causal && W >= 250 && W <= 400) return 2;
+  return W >= 400 ? 1 : 0;
+}
+
+template <int RW, int KS>
+hipError_t launch_f32_forward(const Dims &d, PassArgs a, hipStream_t st) {
+  a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d));
+  hipLaunchKernelGGL((f32_forward_kernel<RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+  return hipGetLastError();
+}
+hipError_t f32_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int groups,
+                       hipStream_t st) {
+  PassArgs a{};
+  a.Q = static_cast<const float *>(Q); a.K = static_cast<const float *>(K); a.V = static_cast<const float *>(V);
+  a.O = static_cast<float *>(O); a.LSE = LSE;
+  a.L = d.L; a.Lq = d.Lq; a.q0 = (int64_t)d.rank_begin * d.c; a.causal = d.causal; a.cl2 = d.scale * kLog2e;
+  if (groups == 4) return launch_f32_forward<1, 4>(d, a, st);
+  return groups == 2 ? launch_f32_forward<2, 2>(d, a, st) : launch_f32_forward<4, 1>(d, a, st);
+}
+
 template <typename T>
 hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE,
                      char *ws, const StripPlan &pl, hipStream_t st) {
+  if constexpr (sizeof(T) == 4)
+    if (const int groups = f32_one_pass(d)) return f32_forward(d, Q, K, V, O, LSE, groups, st);
   const int64_t heads = (int64_t)d.B * d.Z;
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;

@@ -12,6 +12,8 @@ CASES = [
     (1, 1, 64, 1, 64, 0, 1, False), (1, 3, 448, 7, 64, 0, 7, True), (1, 2, 192, 3, 128, 1, 2, False),   # four groups
     (5, 7, 320, 5, 64, 0, 5, False), (5, 7, 320, 5, 64, 0, 5, True), (2, 17, 576, 3, 64, 1, 3, True),   # two; four causal
     (1, 9, 320, 1, 256, 0, 1, False), (4, 25, 192, 3, 64, 0, 3, False), (4, 25, 448, 7, 64, 0, 7, True),
+    (4, 32, 512, 8, 64, 0, 8, False), (5, 15, 320, 5, 64, 0, 5, True), (1, 12, 832, 13, 64, 0, 13, True),    # fp32: one pass, strip
+    (7, 17, 448, 7, 64, 2, 7, True), (1, 11, 704, 11, 64, 0, 11, False),
 ]
 
 
