@@ -1,11 +1,14 @@
-"""Builds the HIP library (csrc/*.hip -> librsa_hip.so) for gfx950 with hipcc."""
+"""Builds the HIP library (csrc/*.hip -> librsa_hip.so) for gfx950 with hipcc, and the Python binding of its main calls
+(csrc/binding.cpp -> _binding.so) with the host compiler."""
 import glob
 import os
 import subprocess
+import sysconfig
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 LIB_PATH = os.path.join(_PKG, "librsa_hip.so")
+BINDING_PATH = os.path.join(_PKG, "_binding.so")
 
 
 def sources():
@@ -22,12 +25,31 @@ def build(verbose=False):
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
         "-Wno-unused-command-line-argument",
     ] + sources() + ["-o", LIB_PATH]
+    _run(cmd, verbose)
+    build_binding(verbose)
+    return LIB_PATH
+
+
+def build_binding(verbose=False):
+    import torch
+    base = os.path.dirname(torch.__file__)
+    inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"],
+           os.path.join(_ROOT, "include")]
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+          "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+         + ["-I" + p for p in inc] + [os.path.join(_PKG, "csrc", "binding.cpp"), "-o", BINDING_PATH,
+          "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+          "-L" + _PKG, "-l:librsa_hip.so", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(base, "lib")], verbose)
+    return BINDING_PATH
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd))
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-    return LIB_PATH
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + res.stdout + res.stderr)
 
 
 if __name__ == "__main__":

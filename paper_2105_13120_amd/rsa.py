@@ -1,4 +1,4 @@
-"""ctypes binding of the RSA C ABI (include/rsa.h): argument marshalling only.
+"""Binding of the RSA C ABI (include/rsa.h), natively for the main calls, by ctypes for the rest: argument marshalling only.
 
 Every step of the path runs in the HIP library.  PyTorch supplies device
 memory and the current stream; nothing here computes.  If the library has not
@@ -100,6 +100,29 @@ def lib():
     return _lib
 
 
+_binding = None
+
+
+def _native():
+    """The native binding of the main calls (csrc/binding.cpp); raises if it has not been built."""
+    global _binding
+    if _binding is None:
+        lib()
+        try:
+            from . import _binding as b
+        except ImportError as e:
+            raise RuntimeError("the binding does not load: build it with __graft_entry__.build() "
+                               "(python -m paper_2105_13120_amd.build); there is no fallback path") from e
+        _binding = b
+    return _binding
+
+
+def _done(result):
+    if type(result) is int:
+        _check(result)
+    return result
+
+
 def strerror(status):
     return lib().rsa_strerror(int(status)).decode()
 
@@ -154,43 +177,14 @@ def workspace_bytes(desc, backward):
     return int(lib().rsa_workspace_bytes(ctypes.byref(desc), 1 if backward else 0))
 
 
-def _workspace(desc, backward, device):
-    """(tensor or None, bytes): nothing is allocated where nothing is needed."""
-    n = workspace_bytes(desc, backward)
-    return (torch.empty(n, dtype=torch.uint8, device=device) if n else None), n
-
-
 def forward(desc, Q, K, V, O=None, LSE=None, ws=None):
     """rsa_forward.  Q: (B,Z,Lq,A); K, V: (B,Z,L,A).  Returns (O, LSE)."""
-    for t in (Q, K, V):
-        assert t.is_cuda and t.stride(-1) == 1   # other strides travel in the descriptor
-    if O is None:
-        O = torch.empty_like(Q)
-    if LSE is None:
-        LSE = Q.new_empty(Q.shape[:3], dtype=torch.float32)
-    if ws is None:
-        ws, n = _workspace(desc, False, Q.device)
-    else:
-        n = ws.numel()
-    _check(lib().rsa_forward(ctypes.byref(desc), _p(Q), _p(K), _p(V), _p(O), _p(LSE),
-                             _p(ws), n, _stream()))
-    return O, LSE
+    return _done(_native().forward(desc, Q, K, V, O, LSE, ws))
 
 
 def backward(desc, dO, Q, K, V, O, LSE, dQ=None, dK=None, dV=None, ws=None):
     """rsa_backward.  Returns (dQ, dK, dV)."""
-    for t in (dO, Q, K, V, O, LSE):
-        assert t.is_cuda and t.stride(-1) == 1
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dK = torch.empty_like(K) if dK is None else dK
-    dV = torch.empty_like(V) if dV is None else dV
-    if ws is None:
-        ws, n = _workspace(desc, True, Q.device)
-    else:
-        n = ws.numel()
-    _check(lib().rsa_backward(ctypes.byref(desc), _p(dO), _p(Q), _p(K), _p(V), _p(O), _p(LSE),
-                              _p(dQ), _p(dK), _p(dV), _p(ws), n, _stream()))
-    return dQ, dK, dV
+    return _done(_native().backward(desc, dO, Q, K, V, O, LSE, dQ, dK, dV, ws))
 
 
 # ---- step-level calls (one ring step of one simulated rank) ----
@@ -263,51 +257,22 @@ def proj_workspace_bytes(desc, H):
     return int(lib().rsa_proj_workspace_bytes(ctypes.byref(desc), int(H)))
 
 
-def _proj_ws(desc, H, device):
-    return torch.empty(max(proj_workspace_bytes(desc, H), 16), dtype=torch.uint8, device=device)
-
-
-def _head_shape(desc, X):
-    rows = (desc.rank_end - desc.rank_begin) * (desc.L // desc.N)
-    return (desc.B, desc.Z, rows, desc.A)
-
-
 def qkv_proj(desc, X, Wqkv, Q=None, K=None, V=None):
     """X (B, Lq, H), Wqkv (H, 3*Z*A) -> Q, K, V (B, Z, Lq, A)."""
-    H = X.shape[-1]
-    Q, K, V = (torch.empty(_head_shape(desc, X), dtype=X.dtype, device=X.device) if t is None else t
-               for t in (Q, K, V))
-    _check(lib().rsa_qkv_proj(ctypes.byref(desc), H, _p(X), _p(Wqkv), _p(Q), _p(K), _p(V), _stream()))
-    return Q, K, V
+    return _done(_native().qkv_proj(desc, X, Wqkv, Q, K, V))
 
 
 def out_proj(desc, O, Wo, Y=None):
     """O (B, Z, Lq, A), Wo (Z*A, H) -> Y (B, Lq, H)."""
-    H = Wo.shape[-1]
-    if Y is None:
-        Y = torch.empty((O.shape[0], O.shape[2], H), dtype=O.dtype, device=O.device)
-    _check(lib().rsa_out_proj(ctypes.byref(desc), H, _p(O), _p(Wo), _p(Y), _stream()))
-    return Y
+    return _done(_native().out_proj(desc, O, Wo, Y))
 
 
 def out_proj_bwd(desc, dY, O, Wo, dO=None, dWo=None, ws=None):
-    H = Wo.shape[-1]
-    dO = torch.empty_like(O) if dO is None else dO
-    dWo = torch.empty(Wo.shape, dtype=torch.float32, device=Wo.device) if dWo is None else dWo
-    ws = _proj_ws(desc, H, O.device) if ws is None else ws
-    _check(lib().rsa_out_proj_bwd(ctypes.byref(desc), H, _p(dY), _p(O), _p(Wo), _p(dO), _p(dWo), _p(ws),
-                                  ws.numel(), _stream()))
-    return dO, dWo
+    return _done(_native().out_proj_bwd(desc, dY, O, Wo, dO, dWo, ws))
 
 
 def qkv_proj_bwd(desc, dQ, dK, dV, X, Wqkv, dX=None, dW=None, ws=None):
-    H = X.shape[-1]
-    dX = torch.empty_like(X) if dX is None else dX
-    dW = torch.empty(Wqkv.shape, dtype=torch.float32, device=X.device) if dW is None else dW
-    ws = _proj_ws(desc, H, X.device) if ws is None else ws
-    _check(lib().rsa_qkv_proj_bwd(ctypes.byref(desc), H, _p(dQ), _p(dK), _p(dV), _p(X), _p(Wqkv), _p(dX),
-                                  _p(dW), _p(ws), ws.numel(), _stream()))
-    return dX, dW
+    return _done(_native().qkv_proj_bwd(desc, dQ, dK, dV, X, Wqkv, dX, dW, ws))
 
 
 # ---- Linformer variant (Table 3): keys and values projected along the sequence ----
@@ -315,46 +280,19 @@ def linformer_workspace_bytes(desc, Kp):
     return int(lib().rsa_linformer_workspace_bytes(ctypes.byref(desc), int(Kp)))
 
 
-def _linf_ws(desc, Kp, device):
-    return torch.empty(max(linformer_workspace_bytes(desc, Kp), 16), dtype=torch.uint8, device=device)
-
-
 def linformer_project(desc, X, E, Xp=None, ws=None):
     """X (B, Z, L, A), E (L, Kp) -> Xp (B, Z, Kp, A), over the tokens of the descriptor's ranks."""
-    Kp = E.shape[1]
-    if Xp is None:
-        Xp = torch.empty((X.shape[0], X.shape[1], Kp, X.shape[3]), dtype=X.dtype, device=X.device)
-    ws = _linf_ws(desc, Kp, X.device) if ws is None else ws
-    _check(lib().rsa_linformer_project(ctypes.byref(desc), Kp, _p(X), _p(E), _p(Xp), _p(ws), ws.numel(),
-                                       _stream()))
-    return Xp
+    return _done(_native().linformer_project(desc, X, E, Xp, ws))
 
 
 def linformer_forward(desc, Q, Kp_, Vp_, O=None, LSE=None):
-    O = torch.empty_like(Q) if O is None else O
-    LSE = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device) if LSE is None else LSE
-    _check(lib().rsa_linformer_forward(ctypes.byref(desc), Kp_.shape[2], _p(Q), _p(Kp_), _p(Vp_), _p(O),
-                                       _p(LSE), _stream()))
-    return O, LSE
+    return _done(_native().linformer_forward(desc, Q, Kp_, Vp_, O, LSE))
 
 
 def linformer_backward(desc, dO, Q, Kp_, Vp_, O, LSE, dQ=None, dKp=None, dVp=None, ws=None):
-    Kp = Kp_.shape[2]
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dKp = torch.empty_like(Kp_) if dKp is None else dKp
-    dVp = torch.empty_like(Vp_) if dVp is None else dVp
-    ws = _linf_ws(desc, Kp, Q.device) if ws is None else ws
-    _check(lib().rsa_linformer_backward(ctypes.byref(desc), Kp, _p(dO), _p(Q), _p(Kp_), _p(Vp_), _p(O),
-                                        _p(LSE), _p(dQ), _p(dKp), _p(dVp), _p(ws), ws.numel(), _stream()))
-    return dQ, dKp, dVp
+    return _done(_native().linformer_backward(desc, dO, Q, Kp_, Vp_, O, LSE, dQ, dKp, dVp, ws))
 
 
 def linformer_project_bwd(desc, dXp, X, E, dX=None, dE=None):
     """dX (rows of the descriptor's ranks; a new tensor is zero elsewhere) and dE (fp32, same)."""
-    # with all ranks every row is written: zeroing both first costs as much as a fifth of the kernels' traffic
-    new = torch.empty_like if (desc.rank_begin, desc.rank_end) == (0, desc.N) else torch.zeros_like
-    dX = new(X) if dX is None else dX
-    dE = new(E, dtype=torch.float32, memory_format=torch.contiguous_format) if dE is None else dE
-    _check(lib().rsa_linformer_project_bwd(ctypes.byref(desc), E.shape[1], _p(dXp), _p(X), _p(E), _p(dX),
-                                           _p(dE), _stream()))
-    return dX, dE
+    return _done(_native().linformer_project_bwd(desc, dXp, X, E, dX, dE))
