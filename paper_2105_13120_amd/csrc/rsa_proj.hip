@@ -177,11 +177,24 @@ constexpr int64_t kMaxLd = (int64_t)1 << 25;
 
 // WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
 // LONG: an operand with rows of more than kMaxLd elements; its loads take 64-bit addresses per lane.
+// The LDS of a work-group of KG groups, one object for every product that the kernel's branches form.
+template <int N> struct GemmLds {
+  unsigned char bytes[N * 8 * kHalfBytes];
+  template <int KG, int T> __device__ __forceinline__ auto &as() {
+    return *reinterpret_cast<unsigned char(*)[KG][4][2 * T][kHalfBytes]>(bytes);
+  }
+};
+template <int N> __device__ __forceinline__ GemmLds<N> &gemm_lds() {
+  __shared__ __attribute__((aligned(16))) GemmLds<N> lds;
+  return lds;
+}
+
+// Work-group (bx, by) of (nx, splits).
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG, bool LONG>
-__global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_t nx, uint32_t by) {
   constexpr int HT = 2 * T;         // half tiles per slab, and waves per group
   constexpr int BM = 64 * T, BN = 64 * T;
-  __shared__ __attribute__((aligned(16))) unsigned char lds_[KG][4][HT][kHalfBytes];  // [group][buffer][A.., B..]
+  auto &lds_ = gemm_lds<KG * T>().template as<KG, T>();  // [group][buffer][A.., B..]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int gw = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -189,14 +202,14 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
   const int wm = wave / T, wn = wave % T;
   const int col = lane & 31, half = lane >> 5;
   unsigned char(*lds)[HT][kHalfBytes] = lds_[grp];
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t wg = xcd_remap(bx, nx);
   const int64_t m0 = (int64_t)(wg / (uint32_t)g.ntiles) * BM, n0 = (int64_t)(wg % (uint32_t)g.ntiles) * BN;
   // slabs of 32 k of group `gr` of this split
   const int64_t per_grp = KG == 1 ? g.kslabs : (g.kslabs + KG - 1) / KG;
   auto slabs_of = [&](int gr, int64_t &begin) -> int {
-    begin = (int64_t)blockIdx.y * g.kslabs + gr * per_grp;
+    begin = (int64_t)by * g.kslabs + gr * per_grp;
     int64_t end = begin + per_grp;
-    const int64_t split_end = (int64_t)(blockIdx.y + 1) * g.kslabs;
+    const int64_t split_end = (int64_t)(by + 1) * g.kslabs;
     if (KG > 1 && end > split_end) end = split_end;
     if (end > g.K / 64) end = g.K / 64;
     return end > begin ? (int)(end - begin) * 2 : 0;
@@ -357,7 +370,7 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
   __syncthreads();
 
   if constexpr (KG > 1) {  // groups 1 .. KG - 1 leave their sums in LDS, group 0 adds them in order
-    static_assert((KG - 1) * HT * T * 2 * 4096 <= (int)sizeof(lds_), "room for the groups' sums");
+    static_assert((KG - 1) * HT * T * 2 * 4096 <= KG * 4 * HT * kHalfBytes, "room for the groups' sums");
     auto slot = [&](int gr, int nb, int mb) {
       return reinterpret_cast<f32x4 *>(&lds_[0][0][0][0] + ((((gr - 1) * HT + wave) * 2 + nb) * T + mb) * 4096);
     };
@@ -441,9 +454,9 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
         const int64_t n = n0 + wn * 64 + nb * 32 + grp * 8 + half * 4;
         if (n >= g.N) continue;
         // fp32 outputs are plain matrices
-        int64_t off = ((int64_t)blockIdx.y * g.M + m) * g.out_ld + n;
+        int64_t off = ((int64_t)by * g.M + m) * g.out_ld + n;
         if (g.part_heads) {
-          const uint32_t w = (uint32_t)g.out_ld, h = blockIdx.y * (uint32_t)g.part_heads + (uint32_t)n / w;
+          const uint32_t w = (uint32_t)g.out_ld, h = by * (uint32_t)g.part_heads + (uint32_t)n / w;
           off = ((int64_t)h * g.out_rows + m) * g.out_ld + (uint32_t)n % w;
         }
         const f32x16 &c = acc[nb][mb];
@@ -451,6 +464,26 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
         *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out[0]) + off) = w;
       }
   }
+}
+
+template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG, bool LONG>
+__global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) {
+  gemm_body<A_KROWS, B_KROWS, OUT_F32, WIDE, T, KG, LONG>(g, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// Two products in one grid of work-groups of the same size (see plan_pair): the `cut` first work-groups form the product
+// `first`.  GRAD_W: the gradients of a map of rows, by its input and, in fp32 and in k splits, by its weights; otherwise
+// those of a projection along the sequence, dX = E dXp and dE = X dXp^T.
+template <bool GRAD_W, bool WIDE, int T0, int K0, int T1, int K1>
+__global__ void __launch_bounds__(128 * T0 * K0, 2) proj_gemm_pair_kernel(GemmArgs g0, GemmArgs g1, uint32_t cut,
+                                                                          int first, uint32_t nx0, uint32_t nx1) {
+  static_assert(T0 * K0 == T1 * K1, "one work-group size");
+  const uint32_t id = blockIdx.x, own = id < cut ? id : id - cut;
+  const uint32_t by1 = __builtin_amdgcn_readfirstlane(own / nx1);
+  if ((id < cut) == (first == 0))
+    gemm_body<false, !GRAD_W, false, WIDE, T0, K0, false>(g0, own, nx0, 0);
+  else
+    gemm_body<GRAD_W, GRAD_W, true, WIDE, T1, K1, false>(g1, own - by1 * nx1, nx1, by1);
 }
 
 __global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_kernel(const float *part, float *out, int64_t n4,
@@ -475,6 +508,18 @@ static MatView heads(const void *p0, const void *p1, const void *p2, int64_t row
 
 static bool long_rows(const GemmArgs &g) { return g.A.ld > kMaxLd || g.B.ld > kMaxLd; }
 
+static float tiles_of(int64_t M, int64_t N, int T) {
+  const uint32_t t = 64 * (uint32_t)T;
+  return (float)((((uint32_t)M + t - 1) / t) * (uint64_t)(((uint32_t)N + t - 1) / t));
+}
+static int next_splits(int s, int most) {
+  const int next = s + (s < 4 ? 1 : (s < 8 ? 2 : (s < 16 ? 4 : (s < 32 ? 8 : 16))));
+  return s < most && next > most ? most : next;
+}
+static float reduce_us(int64_t M, int64_t N, int s) {
+  return s > 1 ? 3.0f + (float)s * (float)(M * N) * (4.0f / 5e6f) : 0.0f;
+}
+
 // Size of the work-groups' output tiles, groups per work-group and k splits: the candidate with the least estimated
 // time (us).  n work-groups per CU (of which 1, 2, 4 are in flight) cost per slab of 32 k what was measured, and a round
 // of them its prologue and epilogue; a split result is written and added up.  (Measured with M x N x K swept from
@@ -485,46 +530,98 @@ static bool long_rows(const GemmArgs &g) { return g.A.ld > kMaxLd || g.B.ld > kM
 // that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
 // 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
 // Rows of more than kMaxLd elements: T = 4 (the only one with such loads) and all splits.
-struct GemmPlan { int T, KG, splits, chain; };
-static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, bool groups, int chain = 1 << 29) {
+struct GemmPlan { int T, KG, splits, chain; float us; };
+static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29) {
   const int64_t M = g.M, N = g.N, K = g.K;
   const int kslabs = (int)(K / 64);
-  GemmPlan best{4, 1, max_splits, chain};
+  GemmPlan best{4, 1, max_splits, chain, 0.0f};
   if (long_rows(g)) return best;
-  float least = 1e30f;
+  best.us = 1e30f;
   for (int T = 4; T >= 1; T /= 2) {
-    const uint32_t t = 64 * (uint32_t)T;
-    const float tiles = (float)((((uint32_t)M + t - 1) / t) * (uint64_t)(((uint32_t)N + t - 1) / t));
-    for (int next, s = 1; s <= max_splits; s = next) {
-      next = s + (s < 4 ? 1 : (s < 8 ? 2 : (s < 16 ? 4 : (s < 32 ? 8 : 16))));
-      if (s < max_splits && next > max_splits) next = max_splits;
+    const float tiles = tiles_of(M, N, T);
+    for (int s = 1; s <= max_splits; s = next_splits(s, max_splits)) {
       if (T == 4 && (kslabs + s - 1) / s > chain) continue;
       const float w = tiles * (float)s, n = ceilf(w * (1.0f / 256)), slabs = 2.0f * (float)((kslabs + s - 1) / s);
-      const float reduce = s > 1 ? 3.0f + (float)s * (float)(M * N) * (4.0f / 5e6f) : 0.0f;
       float us;
       if (T == 4) us = n * (6.5f + slabs * (0.6f + 0.28f * (w < 256 ? w * (1.0f / 256) : 1.0f)));
       else if (T == 2) us = n < 2 ? 4.0f + slabs * 0.29f : 2.0f + ceilf(n * 0.5f) * (2.0f + slabs * 0.57f);
       else us = 2.0f + 1.5f * ceilf(n * 0.25f) + slabs * (n < 2 ? 0.20f : 0.13f * n);
-      us += reduce;
-      if (us < least) { least = us; best = {T, 1, s, chain}; }
-      if (T == 1 && groups && n < 2) {
-        us = 4.5f + slabs * 0.155f + reduce;
-        if (us < least) { least = us; best = {1, 2, s, chain}; }
+      const float reduce = reduce_us(M, N, s);
+      if (us + reduce < best.us) best = {T, 1, s, chain, us + reduce};
+      if (T == 1) {
+        const float second = n < 2 ? 0.0f : (w < 512 ? w * (1.0f / 256) - 1.0f : 1.0f);
+        us = ceilf(n * 0.5f) * (4.5f + slabs * (0.15f + 0.05f * second));
+        if (us + reduce < best.us) best = {1, 2, s, chain, us + reduce};
       }
     }
   }
   return best;
 }
 
+// The two products of a backward in one grid of work-groups of one size: where neither fills the chip, or fills it only
+// in part of its last round, the other's work-groups take the CUs that are left, and one launch and its ramps go.
+// (us, gradients of the Q/K/V and output maps, one launch each -> one grid: 128 rows, H = ZA = 768: 16.1 -> 11.6 and
+// 10.0 -> 6.9; 1024 rows of 1024: 35.0 -> 25.0 and 18.7 -> 12.6; 4096 rows: 75.6 -> 59.9 and 36.7 -> 29.5; 16384 rows:
+// 192 -> 188, and 88 either way.  Projection along the sequence, 5120 rows x 32 heads, Kp = 256: 30.2 -> 22.7; 87808 x
+// 16, Kp = 192: 141 -> 137.)
+// The estimate takes the work-groups in the order of the grid, the longer ones first: each lasts a + slabs * r us, with
+// r between that of a lone work-group and of a full CU (two of 256 threads, one of 512).  Its constants were fitted to
+// 33 pairs of products, 128 .. 114688 rows, 64 .. 3072 outputs, and each combination and number of splits; what it
+// picks is within 1 % of the best of them on average, 6 % at most.
+struct WgTime { float a, alone, full; };
+static WgTime wg_time(int T, int KG) {
+  if (T == 4) return {9.4f, 0.47f, 0.58f};
+  if (T == 2) return KG == 2 ? WgTime{6.0f, 0.23f, 0.25f} : WgTime{5.1f, 0.30f, 0.39f};
+  return {2.8f, 0.146f, 0.197f};
+}
+struct PairPlan { GemmPlan p0, p1; float us; };
+static PairPlan plan_pair(const GemmArgs &g0, const GemmArgs &g1, int max_splits, int chain, bool grad_w) {
+  static const int kinds[][4] = {{4, 1, 4, 1}, {2, 1, 2, 1}, {2, 1, 1, 2}, {1, 2, 1, 2}, {4, 1, 2, 2}, {1, 2, 2, 1}};
+  PairPlan best{};
+  best.us = 1e30f;
+  const int kslabs = (int)(g1.K / 64);
+  for (int k = 0; k < (grad_w ? 6 : 4); ++k) {
+    const int *c = kinds[k];
+    const float per_cu = c[0] == 4 ? 1.0f : 2.0f, slots = 256.0f * per_cu;
+    const WgTime t0 = wg_time(c[0], c[1]), t1 = wg_time(c[2], c[3]);
+    for (int s = 1; s <= max_splits; s = next_splits(s, max_splits)) {
+      const int slabs1 = (kslabs + s - 1) / s;
+      if (c[2] == 4 && slabs1 > chain) continue;
+      float wa = tiles_of(g0.M, g0.N, c[0]), wb = tiles_of(g1.M, g1.N, c[2]) * (float)s;
+      float fill = (wa + wb) * (1.0f / 256) - (per_cu - 1.0f);
+      fill = fill < 0.0f ? 0.0f : (fill > 1.0f ? 1.0f : fill);
+      float ta = t0.a + 2.0f * (float)(g0.K / 64) * (t0.alone + (t0.full - t0.alone) * fill);
+      float tb = t1.a + 2.0f * (float)slabs1 * (t1.alone + (t1.full - t1.alone) * fill);
+      if (tb > ta) { const float t = ta, w = wa; ta = tb; tb = t; wa = wb; wb = w; }
+      const float rounds = floorf(wa / slots), rest = wa - rounds * slots, free = slots - rest, begin = rounds * ta;
+      float us = rest > 0.0f ? begin + ta : begin;
+      if (rest == 0.0f || wb <= free * floorf(ta / tb)) us = fmaxf(us, begin + ceilf(wb / free) * tb);
+      else us = fmaxf(us, begin + (rest * ta + wb * tb) / slots + 0.69f * tb);
+      us += reduce_us(g1.M, g1.N, s);
+      if (us < best.us) best = {{c[0], c[1], 1, 1 << 29, us}, {c[2], c[3], s, chain, us}, us};
+    }
+  }
+  return best;
+}
+
+static bool wide_heads(const GemmArgs &g) {
+  return (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
+}
+
+// The fields of a product's arguments that its plan decides; returns the work-groups per split.
+static uint32_t set_plan(GemmArgs &g, const GemmPlan &p) {
+  const int64_t t = 64 * p.T;
+  g.chain = p.chain;
+  g.ntiles = (int)((g.N + t - 1) / t);
+  g.kslabs = (g.K / 64 + p.splits - 1) / p.splits;
+  return (uint32_t)(((g.M + t - 1) / t) * g.ntiles);
+}
+
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, int T, int KG>
 static hipError_t launch_gemm_as(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
-  const int splits = p.splits;
-  g.chain = p.chain;
-  g.ntiles = (int)((g.N + 64 * T - 1) / (64 * T));
-  const int64_t mtiles = (g.M + 64 * T - 1) / (64 * T);
-  g.kslabs = (g.K / 64 + splits - 1) / splits;
-  dim3 grid((unsigned)(mtiles * g.ntiles), (unsigned)splits), block(128 * T * KG);
-  const bool wide = (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
+  const uint32_t wgs = set_plan(g, p);
+  const dim3 grid(wgs, (unsigned)p.splits), block(128 * T * KG);
+  const bool wide = wide_heads(g);
   if constexpr (T == 4 && !(OUT_F32 && !A_KROWS)) {  // (dE's operands are rows of heads)
     if (long_rows(g)) {
       hipLaunchKernelGGL((proj_gemm_kernel<A_KROWS, B_KROWS, OUT_F32, true, T, KG, true>), grid, block, 0, st, g);
@@ -541,9 +638,38 @@ template <bool A_KROWS, bool B_KROWS, bool OUT_F32>
 static hipError_t launch_gemm(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
   if (p.T == 4) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 4, 1>(g, p, st);
   if (p.T == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 2, 1>(g, p, st);
-  if constexpr (!OUT_F32)
-    if (p.KG == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 2>(g, p, st);
+  if (p.KG == 2) return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 2>(g, p, st);
   return launch_gemm_as<A_KROWS, B_KROWS, OUT_F32, 1, 1>(g, p, st);
+}
+
+template <bool GRAD_W, int T0, int K0, int T1, int K1>
+static hipError_t launch_pair_as(GemmArgs &g0, GemmArgs &g1, const GemmPlan &p0, const GemmPlan &p1, hipStream_t st) {
+  const uint32_t nx0 = set_plan(g0, p0), nx1 = set_plan(g1, p1), n1 = nx1 * (uint32_t)p1.splits;
+  const int first = g1.kslabs * T1 * T1 / K1 > g0.kslabs * T0 * T0 / K0;  // the longer work-groups
+  const dim3 grid(nx0 + n1), block(128 * T0 * K0);
+  const uint32_t cut = first ? n1 : nx0;
+  if (wide_heads(g0) || wide_heads(g1))
+    hipLaunchKernelGGL((proj_gemm_pair_kernel<GRAD_W, true, T0, K0, T1, K1>), grid, block, 0, st, g0, g1, cut, first,
+                       nx0, nx1);
+  else
+    hipLaunchKernelGGL((proj_gemm_pair_kernel<GRAD_W, false, T0, K0, T1, K1>), grid, block, 0, st, g0, g1, cut, first,
+                       nx0, nx1);
+  return hipGetLastError();
+}
+template <bool GRAD_W>
+static hipError_t launch_pair(GemmArgs &g0, GemmArgs &g1, const PairPlan &p, hipStream_t st) {
+  const GemmPlan &p0 = p.p0, &p1 = p.p1;
+  if (p0.T == 4) {
+    if (p1.T == 4) return launch_pair_as<GRAD_W, 4, 1, 4, 1>(g0, g1, p0, p1, st);
+    if constexpr (GRAD_W) return launch_pair_as<GRAD_W, 4, 1, 2, 2>(g0, g1, p0, p1, st);
+  }
+  if (p0.T == 2) {
+    if (p1.T == 2) return launch_pair_as<GRAD_W, 2, 1, 2, 1>(g0, g1, p0, p1, st);
+    return launch_pair_as<GRAD_W, 2, 1, 1, 2>(g0, g1, p0, p1, st);
+  }
+  if constexpr (GRAD_W)
+    if (p1.T == 2) return launch_pair_as<GRAD_W, 1, 2, 2, 1>(g0, g1, p0, p1, st);
+  return launch_pair_as<GRAD_W, 1, 2, 1, 2>(g0, g1, p0, p1, st);
 }
 
 // Most k splits of a weight-gradient product (the workspace is sized by it): as many as still give every CU at most
@@ -572,7 +698,7 @@ hipError_t proj_qkv(const Dims &d, int64_t H, const void *X, const void *W, void
   g.B = plain(W, g.N);        // [K][N]
   g.out[0] = Q; g.out[1] = K; g.out[2] = V;
   g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g, 1), st);
 }
 
 hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, void *Y, hipStream_t st) {
@@ -581,62 +707,67 @@ hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, voi
   g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [M][K], column tile = (half of a) head
   g.B = plain(Wo, H);                           // [K][N]
   g.out[0] = Y; g.out_split = 0; g.out_ld = H;
-  return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
+  return launch_gemm<false, true, false>(g, plan_gemm(g, 1), st);
+}
+
+// The gradients of one of the maps, g0 that of its input and g1 that of its weights (kept in fp32, its sum over the
+// rows in splits): in one grid where that is estimated to be faster and g1 does not lie over what g0 reads.
+static hipError_t both_gradients(GemmArgs &g0, GemmArgs &g1, float *dW, float *part, const void *W, hipStream_t st) {
+  const int most = proj_wgrad_splits(g1.M, g1.N, g1.K), chain = wgrad_chain(g1.M, g1.N, g1.K);
+  const size_t n = (size_t)(g1.M * g1.N);
+  const GemmPlan p0 = plan_gemm(g0, 1), p1 = plan_gemm(g1, most, chain);
+  bool one_grid = !long_rows(g0) && !long_rows(g1) && !overlap(dW, n * 4, W, n * 2);
+  PairPlan pair{};
+  if (one_grid) {
+    pair = plan_pair(g0, g1, most, chain, true);
+    one_grid = pair.us < p0.us + p1.us;
+  }
+  const int splits = one_grid ? pair.p1.splits : p1.splits;
+  g1.out[0] = splits > 1 ? part : dW;
+  hipError_t e;
+  if (one_grid) {
+    e = launch_pair<true>(g0, g1, pair, st);
+  } else {
+    e = launch_gemm<false, false, false>(g0, p0, st);
+    if (e == hipSuccess) e = launch_gemm<true, true, true>(g1, p1, st);
+  }
+  if (e != hipSuccess || splits == 1) return e;
+  const int64_t n4 = (int64_t)n / 4;
+  hipLaunchKernelGGL(ksplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part, dW, n4, splits);
+  return hipGetLastError();
 }
 
 hipError_t proj_out_bwd(const Dims &d, int64_t H, const void *dY, const void *O, const void *Wo,
                         void *dO, float *dWo, float *part, hipStream_t st) {
   const int64_t M = (int64_t)d.B * d.Lq, ZA = (int64_t)d.Z * d.A;
-  {  // dO = dY Wo^T, head-split
-    GemmArgs g{};
-    g.M = M; g.N = ZA; g.K = H;
-    g.A = plain(dY, H);   // [M][K]
-    g.B = plain(Wo, H);   // [N][K]
-    g.out[0] = dO; g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
-    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g, 1, true), st);
-    if (e != hipSuccess) return e;
-  }
-  // dWo = O^T dY: contraction over the rows
-  GemmArgs g{};
-  g.M = ZA; g.N = H; g.K = M;
-  g.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [K][M]
-  g.B = plain(dY, H);                           // [K][N]
-  const GemmPlan plan = plan_gemm(g, proj_wgrad_splits(ZA, H, M), false, wgrad_chain(ZA, H, M));
-  g.out[0] = plan.splits > 1 ? part : dWo; g.out_split = 0; g.out_ld = H;
-  hipError_t e = launch_gemm<true, true, true>(g, plan, st);
-  if (e != hipSuccess || plan.splits == 1) return e;
-  const int64_t n4 = ZA * H / 4;
-  hipLaunchKernelGGL(ksplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part, dWo,
-                     n4, plan.splits);
-  return hipGetLastError();
+  GemmArgs g{};  // dO = dY Wo^T, head-split
+  g.M = M; g.N = ZA; g.K = H;
+  g.A = plain(dY, H);   // [M][K]
+  g.B = plain(Wo, H);   // [N][K]
+  g.out[0] = dO; g.out_split = 1; g.out_rows = d.Lq; g.out_Z = d.Z; g.out_AH = d.A / 64;
+  GemmArgs h{};  // dWo = O^T dY: contraction over the rows
+  h.M = ZA; h.N = H; h.K = M;
+  h.A = heads(O, nullptr, nullptr, d.Lq, d.Z, d.A);  // [K][M]
+  h.B = plain(dY, H);                           // [K][N]
+  h.out_split = 0; h.out_ld = H;
+  return both_gradients(g, h, dWo, part, Wo, st);
 }
 
 hipError_t proj_qkv_bwd(const Dims &d, int64_t H, const void *dQ, const void *dK, const void *dV,
                         const void *X, const void *W, void *dX, float *dW, float *part,
                         hipStream_t st) {
   const int64_t M = (int64_t)d.B * d.Lq, N3 = 3LL * d.Z * d.A;
-  {  // dX = [dQ | dK | dV] W^T
-    GemmArgs g{};
-    g.M = M; g.N = H; g.K = N3;
-    g.A = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [M][K]
-    g.B = plain(W, N3);                  // [N][K]
-    g.out[0] = dX; g.out_split = 0; g.out_ld = H;
-    hipError_t e = launch_gemm<false, false, false>(g, plan_gemm(g, 1, true), st);
-    if (e != hipSuccess) return e;
-  }
-  // dW = X^T [dQ | dK | dV]
-  GemmArgs g{};
-  g.M = H; g.N = N3; g.K = M;
-  g.A = plain(X, H);                   // [K][M]
-  g.B = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [K][N]
-  const GemmPlan plan = plan_gemm(g, proj_wgrad_splits(H, N3, M), false, wgrad_chain(H, N3, M));
-  g.out[0] = plan.splits > 1 ? part : dW; g.out_split = 0; g.out_ld = N3;
-  hipError_t e = launch_gemm<true, true, true>(g, plan, st);
-  if (e != hipSuccess || plan.splits == 1) return e;
-  const int64_t n4 = H * N3 / 4;
-  hipLaunchKernelGGL(ksplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part, dW,
-                     n4, plan.splits);
-  return hipGetLastError();
+  GemmArgs g{};  // dX = [dQ | dK | dV] W^T
+  g.M = M; g.N = H; g.K = N3;
+  g.A = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [M][K]
+  g.B = plain(W, N3);                  // [N][K]
+  g.out[0] = dX; g.out_split = 0; g.out_ld = H;
+  GemmArgs h{};  // dW = X^T [dQ | dK | dV]
+  h.M = H; h.N = N3; h.K = M;
+  h.A = plain(X, H);                   // [K][M]
+  h.B = heads(dQ, dK, dV, d.Lq, d.Z, d.A);  // [K][N]
+  h.out_split = 0; h.out_ld = N3;
+  return both_gradients(g, h, dW, part, W, st);
 }
 
 // ---- Linformer projections along the sequence (Table 3, row Projection) ----
@@ -675,8 +806,7 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.M = Kp; g.N = Zt * A; g.K = rows;
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
-  const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), false,
-                                  wgrad_chain(g.M, g.N, g.K));
+  const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), wgrad_chain(g.M, g.N, g.K));
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess) return e;
@@ -694,44 +824,55 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
                                  const void *X, const void *E, void *dX, float *dE, hipStream_t st) {
   const size_t x_bytes = (size_t)(((Zt - 1) * L + rows) * A) * 2;
   const bool dx_first = overlap(dE, (size_t)(rows * Kp) * 4, E, (size_t)(rows * Kp) * 2);
+  GemmArgs x{};  // dX
+  x.M = rows; x.N = Zt * A; x.K = Kp;
+  x.A = plain(E, Kp);                                  // [M = token][K = k]
+  x.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
+  x.out[0] = dX; x.out_split = 1; x.out_rows = L; x.out_Z = (int)Zt; x.out_AH = A / 64;
+  GemmArgs g{};  // dE
+  g.M = rows; g.N = Kp; g.K = Zt * A;
+  g.A = heads(X, nullptr, nullptr, L, (int)Zt, A);     // [M = token][K = (head, a)]
+  g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [N = k][K = (head, a)]
+  g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
+  // (a gradient that overwrites X itself: X is read until dE is done, so its rows cannot hold partial sums, nor can
+  // both be formed at once)
+  const bool over = dx_first || overlap(X, x_bytes, dX, x_bytes);
+  const bool by_heads = linformer_dx_supported(Kp, A);
+  const int64_t part_heads = 2 * Kp / A;
+  int64_t most = Zt / part_heads;
+  if (most > g.K / 256) most = g.K / 256;
+  if (most > 64) most = 64;
+  GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most), x_plan = plan_gemm(x, 1);
+  PairPlan pair{};
+  bool one_grid = !long_rows(g) && !long_rows(x);
+  if (one_grid) {
+    // (linformer_dx: its launch, and dX written at 4 TB/s)
+    const float dx_us = by_heads ? 3.0f + (float)(rows * Zt * A) * (2.0f / 4e6f) : x_plan.us;
+    pair = plan_pair(x, g, 1, 1 << 29, false);
+    one_grid = pair.us < plan.us + dx_us;
+  }
+  if (one_grid && !over) return launch_pair<false>(x, g, pair, st);
+  if (one_grid) x_plan = pair.p0;  // (dX's additions in the same order, wherever it lies)
+  if (over) plan = plan_gemm(g, 1);
   auto form_dx = [&]() -> hipError_t {
-    if (linformer_dx_supported(Kp, A)) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
-    GemmArgs g{};
-    g.M = rows; g.N = Zt * A; g.K = Kp;
-    g.A = plain(E, Kp);                                  // [M = token][K = k]
-    g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [K = k][N = (head, a)]
-    g.out[0] = dX; g.out_split = 1; g.out_rows = L; g.out_Z = (int)Zt; g.out_AH = A / 64;
-    return launch_gemm<false, true, false>(g, plan_gemm(g, 1, true), st);
+    if (by_heads && !one_grid) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
+    return launch_gemm<false, true, false>(x, x_plan, st);
   };
   if (dx_first) {
     hipError_t e = form_dx();
     if (e != hipSuccess) return e;
   }
-  {
-    GemmArgs g{};
-    g.M = rows; g.N = Kp; g.K = Zt * A;
-    g.A = heads(X, nullptr, nullptr, L, (int)Zt, A);     // [M = token][K = (head, a)]
-    g.B = heads(dXp, nullptr, nullptr, Kp, (int)Zt, A);  // [N = k][K = (head, a)]
-    const int64_t part_heads = 2 * Kp / A;
-    int64_t most = Zt / part_heads;
-    if (most > g.K / 256) most = g.K / 256;
-    if (most > 64) most = 64;
-    // (a gradient that overwrites X itself: X is read until dE is done, so its rows cannot hold partial sums)
-    if (dx_first || overlap(X, x_bytes, dX, x_bytes)) most = 1;
-    const GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most, false);
-    g.out[0] = dE; g.out_split = 0; g.out_ld = Kp;
-    if (plan.splits > 1) {
-      g.out[0] = dX; g.out_ld = A / 2; g.out_rows = L; g.part_heads = (int)part_heads;
-    }
-    hipError_t e = launch_gemm<false, false, true>(g, plan, st);
+  if (plan.splits > 1) {
+    g.out[0] = dX; g.out_ld = A / 2; g.out_rows = L; g.part_heads = (int)part_heads;
+  }
+  hipError_t e = launch_gemm<false, false, true>(g, plan, st);
+  if (e != hipSuccess) return e;
+  if (plan.splits > 1) {
+    const int64_t n4 = rows * Kp / 4;
+    hipLaunchKernelGGL(de_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, static_cast<const float *>(dX),
+                       dE, n4, Kp, L, plan.splits, (int)part_heads, A / 2);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (plan.splits > 1) {
-      const int64_t n4 = rows * Kp / 4;
-      hipLaunchKernelGGL(de_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, static_cast<const float *>(dX),
-                         dE, n4, Kp, L, plan.splits, (int)part_heads, A / 2);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
   }
   return dx_first ? hipSuccess : form_dx();
 }

@@ -1,0 +1,88 @@
+"""The gradients of the maps around RSA formed in one grid: sizes at which each combination of tiles is taken, with
+ragged tiles of every size, k splits of the weight gradient, heads of 128, and the calls that keep two launches."""
+import pytest
+import torch
+
+from paper_2105_13120_amd import rsa
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -8  # one rounding to bf16
+
+
+def close(x, ref, bound, k, f32=False):
+    """An element is a sum of k exact products: its error is at most k roundings of the sum of their magnitudes in fp32
+    (2^-24 each, far less in effect), and one rounding to bf16 where it is stored as such."""
+    err = (x.double() - ref).abs()
+    tol = bound * (k * 2.0 ** -24) + (0 if f32 else EPS * ref.abs()) + 1e-30
+    assert bool((err <= tol).all()), float((err / tol).max())
+
+
+def rand(*shape):
+    return torch.randn(*shape, device="cuda").bfloat16()
+
+
+def heads_to_rows(x):  # (B, Z, L, A) -> (B L, Z A), in 64 bits
+    B, Z, L, A = x.shape
+    return x.double().permute(0, 2, 1, 3).reshape(B * L, Z * A)
+
+
+def check(rows, Z, A, H, in_place=False):
+    torch.manual_seed(rows + H)
+    d = rsa.make_desc(torch.empty(1, Z, rows, A, device="cuda", dtype=torch.bfloat16), 1)
+    g = [rand(1, Z, rows, A) for _ in range(3)]
+    X, W, Wo, dY = rand(1, rows, H), rand(H, 3 * Z * A), rand(Z * A, H), rand(1, rows, H)
+    cat = torch.cat([heads_to_rows(t) for t in g], 1)
+    Xd, Wd, dYd, Wod = X[0].double(), W.double(), dY[0].double(), Wo.double()
+    dW = None
+    if in_place:  # fp32 gradients whose first half is the weights themselves
+        dW = torch.empty(H, 3 * Z * A, device="cuda")
+        flat = dW.view(torch.bfloat16).flatten()[:W.numel()]
+        flat.copy_(W.flatten())
+        W = flat.view_as(W)
+    dX, dW = rsa.qkv_proj_bwd(d, *g, X, W, dW=dW)
+    close(dX[0], cat @ Wd.T, cat.abs() @ Wd.abs().T, 3 * Z * A)
+    close(dW, Xd.T @ cat, Xd.abs().T @ cat.abs(), rows, f32=True)
+    dO, dWo = rsa.out_proj_bwd(d, dY, g[0], Wo)
+    O = heads_to_rows(g[0])
+    close(heads_to_rows(dO), dYd @ Wod.T, dYd.abs() @ Wod.abs().T, H)
+    close(dWo, O.T @ dYd, O.abs().T @ dYd.abs(), rows, f32=True)
+
+
+@pytest.mark.parametrize("rows,Z,A,H", [
+    (64, 1, 64, 64),        # one tile
+    (192, 5, 64, 448),      # tiles of 64, in groups; ragged tiles of 128 and 256
+    (1024, 3, 128, 960),
+    (1536, 19, 64, 1216),   # tiles of 128
+    (2048, 6, 128, 704),
+    (3072, 19, 64, 1216),   # tiles of 256 beside tiles of 128 in two groups
+    (8256, 16, 64, 1088),   # the weight gradient in k splits
+    (16384, 16, 64, 1024),  # tiles of 256
+])
+def test_maps(rows, Z, A, H):
+    check(rows, Z, A, H)
+
+
+def test_weight_gradient_over_the_weights():
+    check(320, 4, 64, 256, in_place=True)
+
+
+@pytest.mark.parametrize("rows,Z,A,Kp,over", [
+    (64, 1, 64, 64, False),
+    (896, 6, 64, 128, False),     # tiles of 64
+    (6272, 5, 128, 128, False),   # tiles of 128 beside tiles of 64
+    (13312, 18, 64, 128, False),  # tiles of 128
+    (4160, 14, 64, 512, False),
+    (19136, 7, 64, 512, False),   # tiles of 256
+    (896, 6, 64, 128, True),      # dX over X: two launches
+])
+def test_projection_along_the_sequence(rows, Z, A, Kp, over):
+    torch.manual_seed(rows + Kp)
+    d = rsa.make_desc(torch.empty(1, Z, rows, A, device="cuda", dtype=torch.bfloat16), 1)
+    X, E, D = rand(1, Z, rows, A), rand(rows, Kp), rand(1, Z, Kp, A)
+    Xd, Ed, Dd = X[0].double(), E.double(), D[0].double()
+    dX, dE = rsa.linformer_project_bwd(d, D, X, E, dX=X if over else None)
+    for z in range(Z):
+        close(dX[0, z], Ed @ Dd[z], Ed.abs() @ Dd[z].abs(), Kp)
+    x, y = Xd.permute(1, 0, 2).reshape(rows, Z * A), Dd.permute(1, 0, 2).reshape(Kp, Z * A)
+    close(dE, x @ y.T, x.abs() @ y.abs().T, Z * A, f32=True)
