@@ -725,9 +725,14 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_both_
 }
 
 // out (bf16) = sum over the splits of part[s][i], in a fixed order; n4 groups of four per split
-// (the partial sums are dense (head, row, A); `lay` says where a row of the output tensor lives)
-__global__ void __launch_bounds__(kReduceBlock) qsplit_reduce_kernel(const float *part, uint16_t *out, int64_t n4,
-                                                                     int splits, int A, OutLayout lay) {
+// (the partial sums are dense (head, row, A); `lay` says where a row of the output tensor lives).  A grid of two rows
+// adds up two tensors, out1's sums behind out's: dV and dK in one launch (two: 3.9 us each where they are small).
+__global__ void __launch_bounds__(kReduceBlock) qsplit_reduce_kernel(const float *part, uint16_t *out, uint16_t *out1,
+                                                                     int64_t n4, int splits, int A, OutLayout lay) {
+  if (blockIdx.y) {
+    part += (int64_t)splits * n4 * 4;
+    out = out1;
+  }
   const int64_t i = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
   if (i >= n4) return;
   const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + i;
@@ -763,19 +768,12 @@ hipError_t fused_bwd_preprocess(const Dims &d, const void *dO, const void *O, co
   return hipGetLastError();
 }
 
-hipError_t qsplit_reduce(const float *part, void *out, int64_t n4, int splits, int A, const OutLayout &lay,
+hipError_t qsplit_reduce(const float *part, void *out, void *out1, int64_t n4, int splits, int A, const OutLayout &lay,
                          hipStream_t st) {
-  hipLaunchKernelGGL(qsplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part,
-                     (uint16_t *)out, n4, splits, A, lay);
+  const dim3 grid(reduce_grid(n4).x, out1 ? 2 : 1);
+  hipLaunchKernelGGL(qsplit_reduce_kernel, grid, dim3(kReduceBlock), 0, st, part, (uint16_t *)out, (uint16_t *)out1, n4,
+                     splits, A, lay);
   return hipGetLastError();
-}
-
-int fused_bwd_dkdv_splits(const Dims &d) {
-  const int64_t wgs = (int64_t)d.B * d.Z * ((d.L + 127) / 128), stages = (d.Lq / 64 + 1) / 2;
-  int64_t s = 1024 / wgs;  // aim at two work-groups per CU's worth of them
-  if (s > stages / 8) s = stages / 8;
-  if (s > 64) s = 64;
-  return s < 2 ? 1 : (int)s;
 }
 
 // the order of a kernel whose work-groups own `own` of `n` rows (or keys) of every head
@@ -799,6 +797,42 @@ static hipError_t launch_dkdv(const Dims &d, const BwdArgs &a, int splits, hipSt
   return hipGetLastError();
 }
 
+// dK/dV of few keys that many query rows see (projected keys): the waves per work-group, on WK blocks of 32 keys in QS
+// groups, and the splits of the rows' walk with the least estimated time.  Work-groups run in rounds of `places`; a
+// stage of a walk (two row tiles, or one per group) takes `alone` .. `full` us by how full the CUs are.  The constants
+// were fitted to a sweep of 5 .. 96 heads of 896 .. 87808 rows and 64 .. 512 keys, heads of 64 and 128, all shapes and
+// splits: what is picked is within 1 % of the best but for one call (4 %).  (Whole backward, us, splits of at least
+// eight stages -> this: 2176 rows, 64 keys, 12 heads: 31.8 -> 20.6; 13824, 64, 5: 36.8 -> 28.6; 7488, 512, 15: 82.1 ->
+// 76.8; 16384, 512, 64: 576 -> 553; heads of 128, 2048, 128, 12: 53.6 -> 33.6; 16384, 256, 64: 756 -> 706.)
+struct DkdvPlan { int WK, QS, splits; };
+static DkdvPlan plan_dkdv(const Dims &d) {
+  struct Shape { int WK, QS, places; float fixed, alone, full; };
+  static const Shape wide[] = {{4, 1, 256, 6.2f, 3.1f, 3.1f}, {2, 2, 256, 5.8f, 1.8f, 1.8f}};
+  static const Shape narrow[] = {
+      {4, 1, 512, 3.4f, 1.4f, 2.17f}, {1, 4, 256, 3.2f, 1.09f, 1.17f}, {2, 2, 512, 2.8f, 1.27f, 1.5f}};
+  const int64_t heads = (int64_t)d.B * d.Z;
+  DkdvPlan best{4, 1, 1};
+  float least = 1e30f;
+  for (int k = 0; k < (d.A == 128 ? 2 : 3); ++k) {
+    const Shape &c = d.A == 128 ? wide[k] : narrow[k];
+    const int64_t stages = c.QS == 1 ? (d.Lq / 64 + 1) / 2 : d.Lq / 64;
+    for (int s = 1; s <= 64 && s <= stages; s *= 2) {
+      const int64_t steps = ((stages + s - 1) / s + c.QS - 1) / c.QS;
+      const float wgs = (float)(heads * ((d.L + 32 * c.WK - 1) / (32 * c.WK)) * s), rounds = wgs / (float)c.places;
+      float fill = c.places == 512 ? wgs * (1.0f / 256) - 1.0f : rounds;
+      fill = fill < 0.0f ? 0.0f : (fill > 1.0f ? 1.0f : fill);
+      float us = (0.85f * ceilf(rounds) + 0.15f * fmaxf(rounds, 1.0f)) *
+                 (c.fixed + (float)steps * (c.alone + (c.full - c.alone) * fill));
+      if (s > 1) us += 1.6f + (float)s * (0.05f + (float)(heads * d.L * d.A) * (8.0f / 3.5e6f));
+      if (us < least) { least = us; best = {c.WK, c.QS, s}; }
+    }
+  }
+  return best;
+}
+
+static int both_groups(const Dims &d);
+int fused_bwd_dkdv_splits(const Dims &d) { return both_groups(d) ? 1 : plan_dkdv(d).splits; }
+
 hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const void *K,
                           const void *V, const float *nL, const float *nD, void *dK, void *dV,
                           hipStream_t st, float *part, int splits) {
@@ -807,22 +841,26 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   if (!part) splits = 1;
   // Few work-groups of four waves (W: their number): fewer keys per work-group and several groups of waves on its
   // query rows, as in the forward (same sweep, forward + backward, us: W = 8: 29.4 -> 26.2; 96: 49.4 -> 44.9;
-  // 252 causal: 104 -> 98).  Heads of 128 leave no registers for it.
+  // 252 causal: 104 -> 98).
   const int64_t W = (int64_t)d.B * d.Z * ((d.L + 127) / 128);
   hipError_t e;
-  if (d.A == 128) e = launch_dkdv<2, 2, 4, 1>(d, a, splits, st);
-  else if (splits > 1 || W > (d.causal ? 256 : 128)) e = launch_dkdv<2, 1, 4, 1>(d, a, splits, st);
+  if (!d.causal && (splits > 1 || d.Lq > d.L)) {  // projected keys
+    const DkdvPlan p = plan_dkdv(d);
+    if (d.A == 128) {
+      e = p.QS == 2 ? launch_dkdv<1, 2, 2, 2, kNoMask>(d, a, splits, st) : launch_dkdv<2, 2, 4, 1>(d, a, splits, st);
+    } else if (p.QS == 4) {
+      e = launch_dkdv<1, 1, 1, 4>(d, a, splits, st);
+    } else {
+      e = p.QS == 2 ? launch_dkdv<1, 1, 2, 2>(d, a, splits, st) : launch_dkdv<2, 1, 4, 1>(d, a, splits, st);
+    }
+  } else if (d.A == 128) e = launch_dkdv<2, 2, 4, 1>(d, a, 1, st);
+  else if (W > (d.causal ? 256 : 128)) e = launch_dkdv<2, 1, 4, 1>(d, a, 1, st);
   else if (W <= 32) e = launch_dkdv<1, 1, 1, 4>(d, a, 1, st);
   else if (W <= 128) e = launch_dkdv<1, 1, 2, 4>(d, a, 1, st);
-  else e = launch_dkdv<1, 1, 2, 2, kCausal>(d, a, 1, st);
+  else e = launch_dkdv<1, 1, 2, 2>(d, a, 1, st);
   if (e != hipSuccess || splits == 1) return e;
   const int64_t n4 = (int64_t)d.B * d.Z * d.L * (d.A / 4);
-  const dim3 rg = reduce_grid(n4), rb(kReduceBlock);
-  const OutLayout lay = make_out_layout(d.ks, d.L, d.Z);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, rb, 0, st, part, (uint16_t *)dV, n4, splits, d.A, lay);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, rg, rb, 0, st, part + (int64_t)splits * n4 * 4,
-                     (uint16_t *)dK, n4, splits, d.A, lay);
-  return hipGetLastError();
+  return qsplit_reduce(part, dV, dK, n4, splits, d.A, make_out_layout(d.ks, d.L, d.Z), st);
 }
 
 template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
@@ -858,9 +896,7 @@ static hipError_t launch_dq(const Dims &d, const BwdArgs &a, int splits, hipStre
 // dQ = sum of the split walks' partial sums
 static hipError_t dq_reduce(const Dims &d, const float *part, void *dQ, int splits, hipStream_t st) {
   const int64_t n4 = (int64_t)d.B * d.Z * d.Lq * (d.A / 4);
-  hipLaunchKernelGGL(qsplit_reduce_kernel, reduce_grid(n4), dim3(kReduceBlock), 0, st, part,
-                     (uint16_t *)dQ, n4, splits, d.A, make_out_layout(d.qs, d.Lq, d.Z));
-  return hipGetLastError();
+  return qsplit_reduce(part, dQ, nullptr, n4, splits, d.A, make_out_layout(d.qs, d.Lq, d.Z), st);
 }
 
 hipError_t fused_bwd_dq(const Dims &d, const void *dO, const void *Q, const void *K, const void *V,

@@ -75,8 +75,8 @@ hipError_t fused_backward(const Dims &d, const void *dO, const void *Q, const vo
                           float *part = nullptr, int qsplits = 1, int ksplits = 1);
 
 // out (bf16, layout lay) = the sum over `splits` fp32 partial results of n4 * 4 floats each, in a
-// fixed order
-hipError_t qsplit_reduce(const float *part, void *out, int64_t n4, int splits, int A, const OutLayout &lay,
+// fixed order; out1, unless null, that of the `splits` results behind those
+hipError_t qsplit_reduce(const float *part, void *out, void *out1, int64_t n4, int splits, int A, const OutLayout &lay,
                          hipStream_t st);
 
 // --- attention to Kp = 128 or 256 keys that one work-group holds (Table 3's shape), bf16, A = 64 ---

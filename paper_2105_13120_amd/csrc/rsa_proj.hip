@@ -846,8 +846,8 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
   PairPlan pair{};
   bool one_grid = !long_rows(g) && !long_rows(x);
   if (one_grid) {
-    // (linformer_dx: its launch, and dX written at 4 TB/s)
-    const float dx_us = by_heads ? 3.0f + (float)(rows * Zt * A) * (2.0f / 4e6f) : x_plan.us;
+    // (linformer_dx: its launch, E moved into registers, and dX written at 3.6 TB/s)
+    const float dx_us = by_heads ? 2.5f + 0.015f * (float)Kp + (float)(rows * Zt * A) * (2.0f / 3.6e6f) : x_plan.us;
     pair = plan_pair(x, g, 1, 1 << 29, false);
     one_grid = pair.us < plan.us + dx_us;
   }

@@ -821,10 +821,7 @@ hipError_t shortkeys_backward(const Dims &att, const void *dO, const void *Q, co
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
   const int64_t n4 = (int64_t)att.B * att.Z * att.L * (64 / 4);
-  const OutLayout lay = make_out_layout(att.ks, att.L, att.Z);
-  e = qsplit_reduce(part, dV, n4, a.splits, 64, lay, st);
-  if (e != hipSuccess) return e;
-  return qsplit_reduce(part + (int64_t)a.splits * n4 * 4, dK, n4, a.splits, 64, lay, st);
+  return qsplit_reduce(part, dV, dK, n4, a.splits, 64, make_out_layout(att.ks, att.L, att.Z), st);
 }
 
 }  // namespace rsa
