@@ -562,41 +562,81 @@ static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29
 // in part of its last round, the other's work-groups take the CUs that are left, and one launch and its ramps go.
 // (us, gradients of the Q/K/V and output maps, one launch each -> one grid: 128 rows, H = ZA = 768: 16.1 -> 11.6 and
 // 10.0 -> 6.9; 1024 rows of 1024: 35.0 -> 25.0 and 18.7 -> 12.6; 4096 rows: 75.6 -> 59.9 and 36.7 -> 29.5; 16384 rows:
-// 192 -> 188, and 88 either way.  Projection along the sequence, 5120 rows x 32 heads, Kp = 256: 30.2 -> 22.7; 87808 x
-// 16, Kp = 192: 141 -> 137.)
-// The estimate takes the work-groups in the order of the grid, the longer ones first: each lasts a + slabs * r us, with
-// r between that of a lone work-group and of a full CU (two of 256 threads, one of 512).  Its constants were fitted to
-// 33 pairs of products, 128 .. 114688 rows, 64 .. 3072 outputs, and each combination and number of splits; what it
-// picks is within 1 % of the best of them on average, 6 % at most.
-struct WgTime { float a, alone, full; };
-static WgTime wg_time(int T, int KG) {
-  if (T == 4) return {9.4f, 0.47f, 0.58f};
-  if (T == 2) return KG == 2 ? WgTime{6.0f, 0.23f, 0.25f} : WgTime{5.1f, 0.30f, 0.39f};
-  return {2.8f, 0.146f, 0.197f};
+// 192 -> 188, and 88 either way; two launches stay where each is nearly full: 8192 rows of 1600, 254 against 289 in one
+// grid.  Projection along the sequence, 5120 rows x 32 heads, Kp = 256: 30.2 -> 22.7; 87808 x 16, Kp = 192: 141 -> 137.)
+// A work-group lasts fixed + slabs * r us, with r between that of a lone one and of a full chip (two of 256 threads per
+// CU, one of 512).  The constants were fitted, those of the maps to 1400 timed launches of 65 pairs of 128 .. 50688 rows
+// (off by 8 % RMS among the forms near the best; what is picked is 2 % above the best on average, and at most 1 % above
+// two launches), those of the projections along the sequence, whose operands lie along the products' k, to 11 pairs.
+struct WgTime {
+  float fixed, alone, full;
+  float operator()(int slabs, float fill) const {
+    return fixed + (float)slabs * (alone + (full - alone) * (fill < 0.0f ? 0.0f : (fill > 1.0f ? 1.0f : fill)));
+  }
+};
+static WgTime wg_time(int T, int KG, bool map) {
+  if (T == 4) return map ? WgTime{8.5f, 0.47f, 0.74f} : WgTime{9.4f, 0.47f, 0.60f};
+  if (T == 2 && KG == 2) return {7.2f, 0.19f, 0.265f};
+  if (T == 2) return map ? WgTime{6.0f, 0.305f, 0.48f} : WgTime{5.1f, 0.30f, 0.41f};
+  return map ? WgTime{2.7f, 0.15f, 0.24f} : WgTime{2.8f, 0.146f, 0.197f};
 }
+static int slabs_of(const GemmArgs &g, int splits) { return 2 * (int)((g.K / 64 + splits - 1) / splits); }
+
+// A map's gradient alone in its launch, by the same constants.
+static float launch_us(const GemmArgs &g, const GemmPlan &p) {
+  const float per_cu = p.T == 4 ? 1.0f : (p.T == 1 && p.KG == 1 ? 4.0f : 2.0f);
+  const float wgs = tiles_of(g.M, g.N, p.T) * (float)p.splits, rounds = wgs / (256.0f * per_cu);
+  const int slabs = slabs_of(g, p.splits);
+  const float each = p.T == 1 && p.KG == 1 ? 2.0f + (float)slabs * 0.2f
+                                           : wg_time(p.T, p.KG, true)(slabs, wgs * (1.0f / 256) - (per_cu - 1.0f));
+  return 2.5f + (0.7f * ceilf(rounds) + 0.3f * fmaxf(rounds, 1.0f)) * each + reduce_us(g.M, g.N, p.splits);
+}
+
+// The end of `na` work-groups of `ta` us, then `nb` of `tb`, each at the place that is free first; 0.3 of it by their sum,
+// since they do not keep step.
+static float both_us(int na, float ta, int nb, float tb, int places) {
+  const int rounds = na / places, rest = na % places, free = places - rest;
+  const float begin = (float)rounds * ta, sum = ((float)na * ta + (float)nb * tb) / (float)places;
+  float end;
+  if (rest == 0) {
+    end = begin + (float)((nb + places - 1) / places) * tb;
+  } else {
+    // the least of begin + j tb and begin + ta + j tb by which all of the second kind are done
+    auto done = [&](float t) {
+      return free * (int)(t / tb + 1e-4f) + (t > ta ? rest * (int)((t - ta) / tb + 1e-4f) : 0) >= nb;
+    };
+    const float area = ((float)rest * ta + (float)nb * tb) / (float)places;
+    int i = (int)(area / tb), j = area > ta ? (int)((area - ta) / tb) : 0;
+    while (!done((float)i * tb)) ++i;
+    while (!done(ta + (float)j * tb)) ++j;
+    end = begin + fmaxf(ta, fminf((float)i * tb, ta + (float)j * tb));
+  }
+  return 0.7f * end + 0.3f * fmaxf(sum, fmaxf(ta, tb));
+}
+
+// Whether the work-groups of the second product are the longer ones, which the grid begins with.
+static bool longer_first(int T0, int K0, int slabs0, int T1, int K1, int slabs1) {
+  return (int64_t)slabs1 * T1 * T1 / K1 > (int64_t)slabs0 * T0 * T0 / K0;
+}
+
 struct PairPlan { GemmPlan p0, p1; float us; };
-static PairPlan plan_pair(const GemmArgs &g0, const GemmArgs &g1, int max_splits, int chain, bool grad_w) {
+static PairPlan plan_pair(const GemmArgs &g0, const GemmArgs &g1, int max_splits, int chain, bool map) {
   static const int kinds[][4] = {{4, 1, 4, 1}, {2, 1, 2, 1}, {2, 1, 1, 2}, {1, 2, 1, 2}, {4, 1, 2, 2}, {1, 2, 2, 1}};
   PairPlan best{};
   best.us = 1e30f;
-  const int kslabs = (int)(g1.K / 64);
-  for (int k = 0; k < (grad_w ? 6 : 4); ++k) {
-    const int *c = kinds[k];
-    const float per_cu = c[0] == 4 ? 1.0f : 2.0f, slots = 256.0f * per_cu;
-    const WgTime t0 = wg_time(c[0], c[1]), t1 = wg_time(c[2], c[3]);
+  for (int k = 0; k < (map ? 6 : 4); ++k) {
+    const int *c = kinds[k], per_cu = c[0] == 4 ? 1 : 2;
+    const WgTime t0 = wg_time(c[0], c[1], map), t1 = wg_time(c[2], c[3], map);
+    const float n0 = tiles_of(g0.M, g0.N, c[0]), tiles1 = tiles_of(g1.M, g1.N, c[2]);
+    if (n0 + tiles1 * (float)max_splits > 1e6f) continue;  // (far beyond where one grid gives anything)
     for (int s = 1; s <= max_splits; s = next_splits(s, max_splits)) {
-      const int slabs1 = (kslabs + s - 1) / s;
-      if (c[2] == 4 && slabs1 > chain) continue;
-      float wa = tiles_of(g0.M, g0.N, c[0]), wb = tiles_of(g1.M, g1.N, c[2]) * (float)s;
-      float fill = (wa + wb) * (1.0f / 256) - (per_cu - 1.0f);
-      fill = fill < 0.0f ? 0.0f : (fill > 1.0f ? 1.0f : fill);
-      float ta = t0.a + 2.0f * (float)(g0.K / 64) * (t0.alone + (t0.full - t0.alone) * fill);
-      float tb = t1.a + 2.0f * (float)slabs1 * (t1.alone + (t1.full - t1.alone) * fill);
-      if (tb > ta) { const float t = ta, w = wa; ta = tb; tb = t; wa = wb; wb = w; }
-      const float rounds = floorf(wa / slots), rest = wa - rounds * slots, free = slots - rest, begin = rounds * ta;
-      float us = rest > 0.0f ? begin + ta : begin;
-      if (rest == 0.0f || wb <= free * floorf(ta / tb)) us = fmaxf(us, begin + ceilf(wb / free) * tb);
-      else us = fmaxf(us, begin + (rest * ta + wb * tb) / slots + 0.69f * tb);
+      const int slabs0 = slabs_of(g0, 1), slabs1 = slabs_of(g1, s);
+      if (c[2] == 4 && slabs1 > 2 * (int64_t)chain) continue;
+      const float n1 = tiles1 * (float)s, fill = (n0 + n1) * (1.0f / 256) - (float)(per_cu - 1);
+      const float ta = t0(slabs0, fill), tb = t1(slabs1, fill);
+      float us = longer_first(c[0], c[1], slabs0, c[2], c[3], slabs1)
+                     ? both_us((int)n1, tb, (int)n0, ta, 256 * per_cu)
+                     : both_us((int)n0, ta, (int)n1, tb, 256 * per_cu);
       us += reduce_us(g1.M, g1.N, s);
       if (us < best.us) best = {{c[0], c[1], 1, 1 << 29, us}, {c[2], c[3], s, chain, us}, us};
     }
@@ -645,7 +685,7 @@ static hipError_t launch_gemm(GemmArgs &g, const GemmPlan &p, hipStream_t st) {
 template <bool GRAD_W, int T0, int K0, int T1, int K1>
 static hipError_t launch_pair_as(GemmArgs &g0, GemmArgs &g1, const GemmPlan &p0, const GemmPlan &p1, hipStream_t st) {
   const uint32_t nx0 = set_plan(g0, p0), nx1 = set_plan(g1, p1), n1 = nx1 * (uint32_t)p1.splits;
-  const int first = g1.kslabs * T1 * T1 / K1 > g0.kslabs * T0 * T0 / K0;  // the longer work-groups
+  const int first = longer_first(T0, K0, slabs_of(g0, p0.splits), T1, K1, slabs_of(g1, p1.splits));
   const dim3 grid(nx0 + n1), block(128 * T0 * K0);
   const uint32_t cut = first ? n1 : nx0;
   if (wide_heads(g0) || wide_heads(g1))
@@ -720,7 +760,7 @@ static hipError_t both_gradients(GemmArgs &g0, GemmArgs &g1, float *dW, float *p
   PairPlan pair{};
   if (one_grid) {
     pair = plan_pair(g0, g1, most, chain, true);
-    one_grid = pair.us < p0.us + p1.us;
+    one_grid = pair.us < 0.92f * (launch_us(g0, p0) + launch_us(g1, p1));
   }
   const int splits = one_grid ? pair.p1.splits : p1.splits;
   g1.out[0] = splits > 1 ? part : dW;
