@@ -525,6 +525,8 @@ static float reduce_us(int64_t M, int64_t N, int s) {
 // of them its prologue and epilogue; a split result is written and added up.  (Measured with M x N x K swept from
 // 128 x 1856 x 28224 to 1664 x 5000 x 11520 and each T: the choice is within 10 % of the best on average.  T = 4 alone:
 // 512 x 1408 x 1408: 31.7 us, now 10; 896 x 576 x 576: 15.8, now 6.)
+// (Results in bf16: T = 4 as 62 products of 512 .. 50688 rows take it, and a last round of T = 2 that is partly empty for
+// as much as it holds.  Q/K/V of 4096 rows of 2048: 127 -> 103 us with T = 4; of 8704 rows, 1088 -> 4608: 117 -> 99.)
 // chain: where the result is kept in fp32, the slabs of 64 k that one chain of additions may take; its rounding error
 // grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
 // that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
@@ -537,14 +539,18 @@ static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29
   GemmPlan best{4, 1, max_splits, chain, 0.0f};
   if (long_rows(g)) return best;
   best.us = 1e30f;
+  const bool sum = chain != 1 << 29;
+  const float t4_full = sum ? 0.28f : 0.14f, last = sum ? 1.0f : 0.35f;
   for (int T = 4; T >= 1; T /= 2) {
     const float tiles = tiles_of(M, N, T);
     for (int s = 1; s <= max_splits; s = next_splits(s, max_splits)) {
       if (T == 4 && (kslabs + s - 1) / s > chain) continue;
       const float w = tiles * (float)s, n = ceilf(w * (1.0f / 256)), slabs = 2.0f * (float)((kslabs + s - 1) / s);
       float us;
-      if (T == 4) us = n * (6.5f + slabs * (0.6f + 0.28f * (w < 256 ? w * (1.0f / 256) : 1.0f)));
-      else if (T == 2) us = n < 2 ? 4.0f + slabs * 0.29f : 2.0f + ceilf(n * 0.5f) * (2.0f + slabs * 0.57f);
+      if (T == 4) us = n * (6.5f + slabs * (0.6f + t4_full * (w < 256 ? w * (1.0f / 256) : 1.0f)));
+      else if (T == 2) us = n < 2 ? 4.0f + slabs * 0.29f
+                            : 2.0f + (last * ceilf(n * 0.5f) + (1.0f - last) * fmaxf(1.0f, w * (1.0f / 512))) *
+                                         (2.0f + slabs * 0.57f);
       else us = 2.0f + 1.5f * ceilf(n * 0.25f) + slabs * (n < 2 ? 0.20f : 0.13f * n);
       const float reduce = reduce_us(M, N, s);
       if (us + reduce < best.us) best = {T, 1, s, chain, us + reduce};
