@@ -2,8 +2,9 @@
 // with the ring structure of section 3.2.2, without the score strip in memory.
 // P is recomputed from Q, K and the forward's LSE: P = exp(s QK^T - LSE).
 //
-//   preprocess: the row terms -D = -rowsum(dO o O) and -LSE / s; a kernel of its own for the
-//     step-level entry point, the prologue of the dQ kernel in rsa_backward.
+//   preprocess: the row terms -D = -rowsum(dO o O) and -LSE / s; a kernel of its own for the step-level entry
+//     point, for heads of 128 and where both kinds of gradients share a grid (fused_bwd_both_kernel), else the
+//     prologue of the dQ kernel.
 //   Both kernels recompute P = exp2(s log2e (Q K^T - LSE / s)): the matrix core forms the bracket
 //   from the caller's bf16 Q and K as they are (its accumulator starts from -LSE / s) and the
 //   factor s log2e is applied to the fp32 result, one multiply per score.  Folding that factor
