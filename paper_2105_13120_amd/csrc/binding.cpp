@@ -122,7 +122,21 @@ at::Tensor workspace(const Call &c, int i, size_t need, const at::Tensor &like, 
 at::Tensor row_terms(const at::Tensor &Q) {
   return at::empty(Q.sizes().slice(0, 3), Q.options().dtype(at::kFloat).memory_format(std::nullopt));
 }
-int64_t rows_of(const rsa_desc *d) { return (int64_t)(d->rank_end - d->rank_begin) * (d->L / d->N); }
+// The ranks' rows, as Python divides: a descriptor that the library will refuse gets there with any numbers in it.
+int64_t rows_of(const rsa_desc *d) {
+  if (d->N == 0) {
+    PyErr_SetString(PyExc_ZeroDivisionError, "integer division or modulo by zero");
+    throw Refused{};
+  }
+  int64_t chunk;
+  if (d->N == -1) {
+    chunk = (int64_t)(0 - (uint64_t)d->L);
+  } else {
+    chunk = d->L / d->N;
+    if (d->L % d->N != 0 && (d->L < 0) != (d->N < 0)) --chunk;
+  }
+  return (int64_t)((uint64_t)((int64_t)d->rank_end - d->rank_begin) * (uint64_t)chunk);
+}
 
 // desc, Q, K, V, O, LSE, ws
 PyObject *forward(Call &c) {
