@@ -529,17 +529,18 @@ static float reduce_us(int64_t M, int64_t N, int s) {
 // as much as it holds.  Q/K/V of 4096 rows of 2048: 127 -> 103 us with T = 4; of 8704 rows, 1088 -> 4608: 117 -> 99.)
 // chain: where the result is kept in fp32, the slabs of 64 k that one chain of additions may take; its rounding error
 // grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
-// that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
-// 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
+// that asks for; the smaller tiles fold theirs, after kFoldSlabs at the latest, which costs them nothing that shows.
+// (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
+// sum: the times of sums over many rows (weight gradients, projections along the sequence).
 // Rows of more than kMaxLd elements: T = 4 (the only one with such loads) and all splits.
+constexpr int64_t kFoldSlabs = 16;
 struct GemmPlan { int T, KG, splits, chain; float us; };
-static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29) {
+static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29, bool sum = false) {
   const int64_t M = g.M, N = g.N, K = g.K;
   const int kslabs = (int)(K / 64);
   GemmPlan best{4, 1, max_splits, chain, 0.0f};
   if (long_rows(g)) return best;
   best.us = 1e30f;
-  const bool sum = chain != 1 << 29;
   const float t4_full = sum ? 0.28f : 0.14f, last = sum ? 1.0f : 0.35f;
   for (int T = 4; T >= 1; T /= 2) {
     const float tiles = tiles_of(M, N, T);
@@ -657,7 +658,7 @@ static bool wide_heads(const GemmArgs &g) {
 // The fields of a product's arguments that its plan decides; returns the work-groups per split.
 static uint32_t set_plan(GemmArgs &g, const GemmPlan &p) {
   const int64_t t = 64 * p.T;
-  g.chain = p.chain;
+  g.chain = p.chain < kFoldSlabs ? p.chain : kFoldSlabs;
   g.ntiles = (int)((g.N + t - 1) / t);
   g.kslabs = (g.K / 64 + p.splits - 1) / p.splits;
   return (uint32_t)(((g.M + t - 1) / t) * g.ntiles);
@@ -761,7 +762,7 @@ hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, voi
 static hipError_t both_gradients(GemmArgs &g0, GemmArgs &g1, float *dW, float *part, const void *W, hipStream_t st) {
   const int most = proj_wgrad_splits(g1.M, g1.N, g1.K), chain = wgrad_chain(g1.M, g1.N, g1.K);
   const size_t n = (size_t)(g1.M * g1.N);
-  const GemmPlan p0 = plan_gemm(g0, 1), p1 = plan_gemm(g1, most, chain);
+  const GemmPlan p0 = plan_gemm(g0, 1), p1 = plan_gemm(g1, most, chain, true);
   bool one_grid = !long_rows(g0) && !long_rows(g1) && !overlap(dW, n * 4, W, n * 2);
   PairPlan pair{};
   if (one_grid) {
@@ -852,7 +853,7 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.M = Kp; g.N = Zt * A; g.K = rows;
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
-  const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), wgrad_chain(g.M, g.N, g.K));
+  const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), wgrad_chain(g.M, g.N, g.K), true);
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess) return e;
@@ -885,21 +886,28 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
   const bool over = dx_first || overlap(X, x_bytes, dX, x_bytes);
   const bool by_heads = linformer_dx_supported(Kp, A);
   const int64_t part_heads = 2 * Kp / A;
-  int64_t most = Zt / part_heads;
-  if (most > g.K / 256) most = g.K / 256;
-  if (most > 64) most = 64;
-  GemmPlan plan = plan_gemm(g, most < 1 ? 1 : (int)most), x_plan = plan_gemm(x, 1);
+  int64_t splits = Zt / part_heads;
+  if (splits > g.K / 256) splits = g.K / 256;
+  const int most = splits < 1 ? 1 : (splits > 64 ? 64 : (int)splits);
+  // dE is kept in fp32, and its error grows with the root of its chains' length: T = 4 takes none longer than a sum that is
+  // timed like the weight gradients' would be split into, and the smaller tiles fold theirs as those do.  (2048 rows, 32
+  // heads of 64, Kp = 128, one grid, relative RMS error: chains of 1024 k 1.87e-7, of 256 0.99e-7, at 13.3 and 13.6 us.)
+  const int slabs = (int)(g.K / 64), chain_splits = plan_gemm(g, most, slabs, true).splits;
+  const int chain = (slabs + chain_splits - 1) / chain_splits, fold = wgrad_chain(g.M, g.N, g.K);
+  GemmPlan plan = plan_gemm(g, most, chain), x_plan = plan_gemm(x, 1);
   PairPlan pair{};
   bool one_grid = !long_rows(g) && !long_rows(x);
   if (one_grid) {
     // (linformer_dx: its launch, E moved into registers, and dX written at 3.6 TB/s)
     const float dx_us = by_heads ? 2.5f + 0.015f * (float)Kp + (float)(rows * Zt * A) * (2.0f / 3.6e6f) : x_plan.us;
-    pair = plan_pair(x, g, 1, 1 << 29, false);
-    one_grid = pair.us < plan.us + dx_us;
+    pair = plan_pair(x, g, 1, chain, false);
+    pair.p1.chain = fold;
+    one_grid = pair.us < 0.97f * (plan.us + dx_us);  // (16384 rows, 64 heads, Kp = 128: 70.2 to 70.6; it takes 79 to 66)
   }
   if (one_grid && !over) return launch_pair<false>(x, g, pair, st);
   if (one_grid) x_plan = pair.p0;  // (dX's additions in the same order, wherever it lies)
   if (over) plan = plan_gemm(g, 1);
+  plan.chain = fold;
   auto form_dx = [&]() -> hipError_t {
     if (by_heads && !one_grid) return linformer_dx(Zt, L, rows, Kp, A, dXp, E, dX, st);
     return launch_gemm<false, true, false>(x, x_plan, st);

@@ -86,3 +86,28 @@ def test_projection_along_the_sequence(rows, Z, A, Kp, over):
         close(dX[0, z], Ed @ Dd[z], Ed.abs() @ Dd[z].abs(), Kp)
     x, y = Xd.permute(1, 0, 2).reshape(rows, Z * A), Dd.permute(1, 0, 2).reshape(Kp, Z * A)
     close(dE, x @ y.T, x.abs() @ y.abs().T, Z * A, f32=True)
+
+
+@pytest.mark.parametrize("rows,Z,A,Kp,chain", [
+    (64, 32, 64, 128, 256),
+    (2048, 32, 64, 128, 256),
+    (2048, 48, 64, 192, 384),
+    (1024, 16, 128, 256, 256),
+    (16384, 64, 64, 128, 1024),
+])
+@pytest.mark.parametrize("over", [False, True])
+def test_fp32_chains_of_the_projection_matrix_gradient(rows, Z, A, Kp, chain, over):
+    """dE sums over all heads in fp32 chains of at most `chain` products, in one grid, in two launches and over X.
+    The matrix instruction rounds after every 8 k, each time by 2.5e-8 of the partial sum (RMS: uniform in an ulp, over
+    numbers spread evenly by their logarithm), so that a chain of n errs by 2.5e-8 sqrt(n / 16) of its result; the chains'
+    own sum errs by 2.5e-8 sqrt(chains / 2).  A quarter more is allowed; chains of twice the length would err by
+    1.2 to 1.4 times the model, of four times by 1.6 to 2."""
+    torch.manual_seed(rows + Kp)
+    d = rsa.make_desc(torch.empty(1, Z, rows, A, device="cuda", dtype=torch.bfloat16), 1)
+    X, E, D = rand(1, Z, rows, A), rand(rows, Kp), rand(1, Z, Kp, A)
+    x, y = X[0].double().permute(1, 0, 2).reshape(rows, Z * A), D[0].double().permute(1, 0, 2).reshape(Kp, Z * A)
+    ref = x @ y.T
+    _, dE = rsa.linformer_project_bwd(d, D, X, E, dX=X if over else None)
+    err = float((dE.double() - ref).norm() / ref.norm())
+    chains = Z * A / chain
+    assert err <= 1.25 * 2.53e-8 * (chain / 16 + chains / 2) ** 0.5, err
