@@ -104,8 +104,9 @@ template <> struct TileT<uint16_t> {
 //   h l' + l h' + m m' + h m' + m h' + h h',
 // is off by 2^-26 at most and takes six bf16 MFMAs of 16 k, 192 cycles, where v_mfma_f32_32x32x2_f32 takes 512.  The sums
 // over k are rounded less often: RMS error of 32 x 32 blocks over 64 | 256 k of N(0, 1) numbers 1.10 | 2.37e-7, by the fp32
-// instruction 1.44 | 2.88.  (An infinite input gives NaN where fp32 would give infinities; the largest finite ones, which
-// bf16 would round to infinity, are held below that.)
+// instruction 1.44 | 2.88.  h and m are held to finite numbers: bf16 would round the largest to infinity, and the
+// remainders are formed by a product over a pair, where an infinity or NaN (which l alone carries) would reach the neighbour.
+// (The two medians of m: 2 of 11 vector instructions a pair, 385 -> 390 us for forward and backward of 192 heads of 512 rows.)
 struct Split { bf16x8 h, m, l; };
 // x less the low (high) half of a pair of bf16: exact, one instruction.  (The pairs (-1, 0) and (0, -1) come from registers:
 // as literals the compiler makes inline constants of them, which the instruction reads as other pairs.)
@@ -116,18 +117,20 @@ struct Minus {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, high ? hi : lo), x, false);
   }
 };
-template <bool HUGE = true>  // false: numbers that bf16 does not round to infinity
+template <bool ANY = true>  // false: numbers of at most 1, or NaN that every result of their neighbours is as well
 __device__ __forceinline__ Split split8(f32x4 a, f32x4 b) {
   const Minus minus;
   u32x4 h, m, l;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float x = e < 2 ? a[2 * e] : b[2 * e - 4], y = e < 2 ? a[2 * e + 1] : b[2 * e - 3];
-    constexpr float kMost = 3.3895314e38f;
-    if (HUGE) h[e] = pack_bf16(__builtin_amdgcn_fmed3f(x, -kMost, kMost), __builtin_amdgcn_fmed3f(y, -kMost, kMost));
-    else h[e] = pack_bf16(x, y);
+    constexpr float kMost = 3.3895314e38f;  // (a median with NaN is the lesser of the other two)
+    auto pack = [](float x, float y) __attribute__((always_inline)) {
+      return ANY ? pack_bf16(__builtin_amdgcn_fmed3f(x, -kMost, kMost), __builtin_amdgcn_fmed3f(y, -kMost, kMost)) : pack_bf16(x, y);
+    };
+    h[e] = pack(x, y);
     const float rx = minus(x, h[e], false), ry = minus(y, h[e], true);
-    m[e] = pack_bf16(rx, ry);
+    m[e] = pack(rx, ry);
     l[e] = pack_bf16(minus(rx, m[e], false), minus(ry, m[e], true));
   }
   return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
@@ -232,7 +235,7 @@ template <> struct TileT<float> {
     __device__ __forceinline__ void put(unsigned char *t, float factor = 1.f) const {
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
-        const Split x = STRIP ? split8<false>(r[j][0] * factor, r[j][1] * factor) : split8(r[j][0], r[j][1]);
+        const Split x = STRIP ? split8(r[j][0] * factor, r[j][1] * factor) : split8(r[j][0], r[j][1]);
         *reinterpret_cast<bf16x8 *>(t + l_off[j]) = x.h;
         *reinterpret_cast<bf16x8 *>(t + ROWS * 128 + l_off[j]) = x.m;
         *reinterpret_cast<bf16x8 *>(t + 2 * ROWS * 128 + l_off[j]) = x.l;
@@ -798,7 +801,7 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : (AHW == 1 ? 3 : 2))
         const int tn = t + KS < nt ? t + KS : t;  // (after the last tile: refetched, not used)
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          const typename TT::Frag pf = split8<false>(sc[2 * s], sc[2 * s + 1]);
+          const typename TT::Frag pf = split8<!WEIGHT>(sc[2 * s], sc[2 * s + 1]);
           sc[2 * s] = piece(tn, 2 * s);
           sc[2 * s + 1] = piece(tn, 2 * s + 1);
 #pragma unroll

@@ -295,3 +295,32 @@ def test_staged_results_over_inputs(dtype, kw):
     assert e.value.status == -4
     for (k, ref), got in zip(grads.items(), rsa.backward(*args, ws=big)):
         same(got, ref, ("shifted", k))
+
+
+@pytest.mark.parametrize("A,L", [(64, 256), (64, 1024), (128, 512)])     # forward in one pass; with the strip
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+def test_f32_infinities_and_nan_reach_their_own_results_only(A, L, bad):
+    """One element of V or dO that is infinite or NaN: its column of O or dV becomes what 64 bits give, the rest stays
+    as it was, bit by bit (the split of a number is formed beside that of its neighbour)."""
+    x = inputs.make_inputs(small_cfg("f32", B=1, Z=2, L=L, N=1, A=A, seed=97))
+    Q, K, V, dO = (upload(x[k], "f32") for k in ("Q", "K", "V", "dO"))
+    desc = rsa.make_desc(K, 1, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(desc, Q, K, V)
+    dQ, dK, dV = rsa.backward(desc, dO, Q, K, V, O, LSE)
+    P = torch.softmax(Q[0, 0].double() @ K[0, 0].double().T * A ** -0.5, -1)
+    for a in (10, 21):
+
+        def check_column(got, clean, ref):
+            assert torch.equal(got[0, 0, :, a].isnan(), ref.isnan())
+            assert torch.equal(got[0, 0, :, a][ref.isinf()].double(), ref[ref.isinf()])
+            got = got.clone()
+            got[0, 0, :, a] = clean[0, 0, :, a]
+            assert torch.equal(got, clean)
+
+        V2, dO2 = V.clone(), dO.clone()
+        V2[0, 0, 37, a] = dO2[0, 0, 37, a] = bad
+        O2, LSE2 = rsa.forward(desc, Q, K, V2)
+        check_column(O2, O, (P @ V2[0, 0, :, a:a + 1].double())[:, 0])
+        assert torch.equal(LSE2, LSE)
+        _, _, dV2 = rsa.backward(desc, dO2, Q, K, V, O, LSE)
+        check_column(dV2, dV, (P.T @ dO2[0, 0, :, a:a + 1].double())[:, 0])
