@@ -17,9 +17,9 @@
 // apply adds them and scales its rows, collect scales the strips' rows as it reads them.  No accumulator starts
 // from a row term (the contraction would be rounded at that term's size), and the fp32 sums over keys or rows are
 // formed 32 at a time.  Relative RMS error against fp64, 1e-7, dQ | dK | dV | O, N(0, 1) inputs:
-// A64 L512 2.7 | 2.7 | 2.4 | 1.6 (with products by the fp32 matrix instruction 3.5 | 3.4 | 3.1 | 3.1, with row terms in the
+// A64 L512 2.0 | 2.0 | 1.6 | 1.6 (with products by the fp32 matrix instruction 3.5 | 3.5 | 3.2 | 3.2, with row terms in the
 // accumulators and one chain per sum besides 12.5 | 12.2 | 12.1 | 5.8; the chunk-by-chunk steps of rsa_staged.hip, N4,
-// 3.9 | 3.8 | 3.5 | 3.6).
+// 3.9 | 3.8 | 3.5 | 3.6); Q and K of N(0, 16), scores of 60: 14.8 | 14.8 | 5.4 | 5.4 (fp32 instruction 35 | 36 | 14 | 14).
 //
 // Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
@@ -160,7 +160,8 @@ template <> struct TileT<float> {
     c = mfma_32x32x16(a.m, b.h, c);
     return mfma_32x32x16(a.h, b.h, c);
   }
-  // with the small terms in an accumulator of their own: 0.50 | 0.89e-7 in the comparison above
+  // with the small terms in an accumulator of their own: 0.50 | 0.89e-7 in the comparison above.  (Scores are formed so, in
+  // both passes: at scores of 60 the backward's dQ errs 15e-7, with all terms in one accumulator 38, by the fp32 instruction 35.)
   static __device__ __forceinline__ void mfma(const Frag &a, const Frag &b, f32x16 &c, f32x16 &small) {
     small = mfma_32x32x16(a.h, b.l, small);
     small = mfma_32x32x16(a.l, b.h, small);
@@ -531,6 +532,7 @@ template <typename T, int AH>
 __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores_bwd_kernel(StripArgs a) {
   typedef TileT<T> TT;
   constexpr int NS = kSlices;
+  constexpr bool F = sizeof(T) == 4;
   constexpr bool ONE = sizeof(T) * AH == 16;  // fp32 heads of 256: K and V tiles take turns in LDS
   __shared__ __attribute__((aligned(16))) ScoreLds<T, AH, ONE ? 1 : 2> lds;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -585,12 +587,15 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
   for (int t = pos.t0; t < pos.t1; ++t) {
     const int64_t k0 = (int64_t)t * 64;
     const bool work = rows_here && tile_seen(a, wrow, k0);
-    f32x16 s[2], dp[2];
+    f32x16 s[2], dp[2], rest[F ? 2 : 1];  // (rest: see the forward)
     if (work) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { s[kb][v] = kOwnSum<T> ? 0.f : nl; dp[kb][v] = kOwnSum<T> ? 0.f : nd; }
+        for (int v = 0; v < 16; ++v) {
+          s[kb][v] = kOwnSum<T> ? 0.f : nl; dp[kb][v] = kOwnSum<T> ? 0.f : nd;
+          rest[F ? kb : 0][v] = 0.f;
+        }
     }
     constexpr int KB = sizeof(T) == 4 ? 1 : 2, ST = 2 / KB;  // (see the forward)
     auto products = [&](auto K, auto V) __attribute__((always_inline)) {
@@ -610,16 +615,25 @@ __global__ void __launch_bounds__(256, sizeof(T) * AH <= 4 ? 2 : 1) strip_scores
             if (V) gf = g.get(u / ST);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-              if (K) s[u % ST + kb] = TT::mfma(kf[b][kb], qf, s[u % ST + kb]);
+              if (K) TT::mfma(kf[b][kb], qf, s[u % ST + kb], rest[F ? u % ST + kb : 0]);
               if (V) dp[u % ST + kb] = TT::mfma(vf[b][kb], gf, dp[u % ST + kb]);
             }
           });
     };
-    if (work) products(std::true_type{}, std::integral_constant<bool, !ONE>{});
-    if constexpr (ONE) {
-      barrier_lds();
-      vals.bring(Vh + (int64_t)t * 64 * a.A, lds.t[0]);
-      barrier_lds();
+    if (work) products(std::true_type{}, std::integral_constant<bool, !F>{});
+    if constexpr (F) {  // (S first, and its sums made one, so that their second set of registers is free for dP)
+      if (work) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) s[kb][v] += rest[kb][v];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (ONE) {
+        barrier_lds();
+        vals.bring(Vh + (int64_t)t * 64 * a.A, lds.t[0]);
+        barrier_lds();
+      }
       if (work) products(std::false_type{}, std::true_type{});
     }
     barrier_lds();

@@ -324,3 +324,35 @@ def test_f32_infinities_and_nan_reach_their_own_results_only(A, L, bad):
         assert torch.equal(LSE2, LSE)
         _, _, dV2 = rsa.backward(desc, dO2, Q, K, V, O, LSE)
         check_column(dV2, dV, (P.T @ dO2[0, 0, :, a:a + 1].double())[:, 0])
+
+
+@pytest.mark.parametrize("A,L,std,causal", [(64, 512, 4.0, False), (64, 1024, 8.0, True), (128, 512, 4.0, False), (192, 512, 4.0, False),
+                                            (256, 512, 4.0, True)])
+def test_f32_gradients_of_scores_that_spread_wide(A, L, std, causal):
+    """Where scores reach 60 and more, the gradients err by what the scores do.  One rounding of every score to fp32 is the
+    measure: a score's sum is rounded after every 8 of A products, at the sizes that the partial sums have by then,
+    which adds up to sqrt(A / 16) single roundings (2 to 4); as much again is allowed for what else rounds, and for
+    chance where few rows count (ten seeds of each: 0.9 to 1.7 of that sum).  With the five small products of split numbers
+    in the same accumulator there are six times as many roundings, 2.4 times the sum."""
+    x = inputs.make_inputs(small_cfg("f32", causal, B=1, Z=2, L=L, N=1, A=A, seed=101))
+    Q, K, V, dO = (upload(x[k], "f32") for k in ("Q", "K", "V", "dO"))
+    Q, K = Q * std, K * std
+
+    def gradients(of_scores):
+        q, k, v, g = (t.double() for t in (Q, K, V, dO))
+        S = of_scores(q @ k.transpose(2, 3).contiguous() * A ** -0.5)
+        if causal:
+            S = S.masked_fill(torch.ones(L, L, device="cuda").triu(1).bool(), float("-inf"))
+        LSE = torch.logsumexp(S, -1)
+        P = torch.exp(S - LSE[..., None])
+        O = P @ v
+        dS = P * (g @ v.transpose(2, 3).contiguous() - (g * O).sum(-1, keepdim=True))
+        return O, LSE, dS @ k * A ** -0.5, dS.transpose(2, 3).contiguous() @ q * A ** -0.5, P.transpose(2, 3).contiguous() @ g
+
+    ref, rounded = gradients(lambda S: S), gradients(lambda S: S.float().double())
+    desc = rsa.make_desc(K, 1, causal=causal, mode=rsa.MODE_STAGED)
+    got = rsa.backward(desc, dO, Q, K, V, ref[0].float(), ref[1].float())
+    for name, t, r, one in zip(("dQ", "dK", "dV"), got, ref[2:], rounded[2:]):
+        ratio = float((t.double() - r).norm() / (one - r).norm())
+        print(f"A{A} L{L} {name}: {ratio:.2f} of one rounding of the scores")
+        assert ratio <= 2 * (A / 16) ** 0.5, name
