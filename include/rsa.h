@@ -29,8 +29,10 @@
  *    round-to-nearest-even per stored element.  dtype RSA_F32: fp32
  *    throughout (staged mode only; rsa_forward and rsa_backward form products
  *    from numbers split in three bf16 parts, which errs less than fp32
- *    multiply-adds do; an infinite or NaN input element reaches the results
- *    that it takes part in, as in fp32, and no others).
+ *    multiply-adds do down to numbers of 2^-110; smaller ones, of the inputs
+ *    and of P and dS, are held to 2^-134 instead of 2^-24 of themselves.  An
+ *    infinite or NaN input element reaches the results that it takes part
+ *    in, as in fp32, and no others).
  *  - Supported: A = 64 or 128 in fused mode, any multiple of 64 up to 256 in
  *    staged mode; L divisible by N (section 4.2: the sequence length must be
  *    divisible by the sequence-parallel size); c divisible by 64.

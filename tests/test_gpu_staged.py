@@ -356,3 +356,23 @@ def test_f32_gradients_of_scores_that_spread_wide(A, L, std, causal):
         ratio = float((t.double() - r).norm() / (one - r).norm())
         print(f"A{A} L{L} {name}: {ratio:.2f} of one rounding of the scores")
         assert ratio <= 2 * (A / 16) ** 0.5, name
+
+
+@pytest.mark.parametrize("k", [0, 100, 112, 118])
+def test_f32_small_numbers(k):
+    """Numbers are split to 2^-24 of themselves down to 2^-110 and to 2^-134 below: V and dO times 2^-k.  An element of O or
+    dV is a sum of products with probabilities, each off by the split of either factor; the sums' own roundings, in chains
+    of 32 and two dozen in all, are 2^-21 of the magnitudes at most.  Subnormal results have 2^-149."""
+    x = inputs.make_inputs(small_cfg("f32", B=1, Z=2, L=512, N=1, seed=103))
+    Q, K, V, dO = (upload(x[i], "f32") for i in ("Q", "K", "V", "dO"))
+    V, dO = V * 2.0 ** -k, dO * 2.0 ** -k
+    desc = rsa.make_desc(K, 1, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(desc, Q, K, V)
+    _, _, dV = rsa.backward(desc, dO, Q, K, V, O, LSE)
+    P = torch.softmax(Q.double() @ K.double().transpose(2, 3).contiguous() * 64 ** -0.5, -1)
+    for got, p, y in ((O, P, V.double()), (dV, P.transpose(2, 3).contiguous(), dO.double())):
+        ref, size = p @ y, p @ y.abs()
+        bound = 2.0 ** -21 * size + 2.0 ** -134 * p.sum(-1, keepdim=True) + 2.0 ** -149
+        assert bool(((got.double() - ref).abs() <= bound).all())
+        if k <= 100:
+            assert float((got.double() - ref).norm() / ref.norm()) <= 4e-7
