@@ -1338,10 +1338,29 @@ __global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : 2) strip_collect_f3
 // ------------------------------------------------------------------ host ----
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Groups of waves on a walk of the fp32 forward in one pass (128 / groups rows per work-group), or 0: the strip, whose
+// scores are shared by work-groups along the keys too, is better where rows are few and walks long.  us, strip -> one pass, by
+// W, the work-groups of 128 rows: 4 (256 rows) 13.0 -> 10.3, 96 (320) 19.4 -> 15.7, 400 (512) 60 -> 51, 768 (512) 108 -> 75, 480
+// (1536) 210 -> 145, causal 288 (1536) 77 -> 72, 96 (768) 31 -> 24; but 12 (768) 19 -> 23, 144 (1536) 77 -> 88.
+int f32_one_pass(const Dims &d) {
+  if (d.A != 64) return 0;
+  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
+  if (d.L <= 512) {
+    if (W <= (d.causal ? 96 : 64)) return 4;
+    return W <= 128 || (W >= 230 && W <= 320) || (d.causal && W <= 400) ? 2 : 1;
+  }
+  if (d.causal && d.L <= 1024 && W > 64 && W <= 128) return 4;
+  if (d.causal && W >= 250 && W <= 400) return 2;
+  return W >= 400 ? 1 : 0;
+}
+
 // How the work is cut: `heads` heads and `rows` of their query rows per group of launches, and where a
 // group's buffers lie in the workspace; out: results that may not be written yet (see apart_plan), of `chunk` heads.
+// usual, one_pass: what kernels and their shapes are chosen by, the heads of a group and f32_one_pass of the call as it is
+// where its results lie beside its inputs, so that they round alike wherever they lie.
 struct StripPlan {
-  int64_t heads, rows, chunk;
+  int64_t heads, rows, chunk, usual;
+  int one_pass;
   size_t out[3];
   size_t strip, strip2, stats, norm, acc_k, acc_v, total;
 };
@@ -1381,6 +1400,7 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
   StripPlan p{};
   p.rows = d.Lq;
   p.heads = heads;
+  p.one_pass = pass == 0 && dtype == RSA_F32 ? f32_one_pass(d) : 0;
   if (head * heads > kStripBytes) {
     if (head <= kStripBytes) {
       const int64_t most = head < kCacheBytes ? (int64_t)(kCacheBytes / head) : 1;
@@ -1393,6 +1413,7 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
       if (p.rows > d.Lq) p.rows = d.Lq;
     }
   }
+  p.usual = p.heads;
   place_group(p, d, dtype, pass, 0);
   return p;
 }
@@ -1413,7 +1434,7 @@ struct HeadBytes {
 StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
   const HeadBytes hb(d, dtype, pass);
   const int64_t all = (int64_t)d.B * d.Z;
-  StripPlan p{};
+  StripPlan p = strip_plan(d, dtype, pass);
   auto place = [&](int64_t heads, int64_t rows) {
     p.heads = heads; p.rows = rows; p.chunk = whole ? all : heads;
     size_t off = 0;
@@ -1421,7 +1442,7 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t byte
     place_group(p, d, dtype, pass, off);
     return p.total <= bytes;
   };
-  for (int64_t h = strip_plan(d, dtype, pass).heads; bytes > 0 && h > 0; h = h * 7 / 8)
+  for (int64_t h = p.usual; bytes > 0 && h > 0; h = h * 7 / 8)
     if (place(h, d.Lq)) return p;
   for (int64_t r = d.Lq / 128 * 128; bytes > 0 && r > 128; r = r * 7 / 8 / 128 * 128)
     if (place(1, r)) return p;
@@ -1466,8 +1487,8 @@ hipError_t launch_apply_as(StripArgs a, const ApplyArgs &p, int64_t heads, hipSt
 //   one -> two: 96 45 -> 37, 192 67.8 -> 66, 288 causal 93 -> 82; but 300 77 -> 81, 400 causal 59.9 -> 61.2;
 //   bf16, one -> four: 24 (1536 rows) 19.5 -> 13.6, 48 (3072) 40 -> 26; one -> two: 144 53 -> 47; but 288 47 -> 49.
 template <typename T, bool WEIGHT>
-hipError_t launch_apply(const StripArgs &a, const ApplyArgs &p, int64_t heads, hipStream_t st) {
-  const int64_t W = heads * a.rtiles * (a.A / 64);  // work-groups of 128 rows and 64 columns
+hipError_t launch_apply(const StripArgs &a, const ApplyArgs &p, int64_t heads, int64_t usual, hipStream_t st) {
+  const int64_t W = usual * a.rtiles * (a.A / 64);  // work-groups of 128 rows and 64 columns
   if (W <= 64 || (a.causal && W <= (sizeof(T) == 4 ? 96 : 144))) return launch_apply_as<T, 1, WEIGHT, 1, 4>(a, p, heads, st);
   const bool two = sizeof(T) == 4 ? W <= (a.causal ? 290 : 200) : W <= (a.causal ? 360 : 240);
   if (two) return launch_apply_as<T, 1, WEIGHT, 2, 2>(a, p, heads, st);
@@ -1485,8 +1506,8 @@ hipError_t launch_collect_as(StripArgs a, const CollectArgs &p, int64_t heads, h
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_collect(const StripArgs &a, const CollectArgs &p, int64_t heads, hipStream_t st) {
-  const int64_t W = heads * ((a.L + 127) / 128) * 2 * (a.A / 64);  // work-groups of 128 keys and 64 columns
+hipError_t launch_collect(const StripArgs &a, const CollectArgs &p, int64_t heads, int64_t usual, hipStream_t st) {
+  const int64_t W = usual * ((a.L + 127) / 128) * 2 * (a.A / 64);  // work-groups of 128 keys and 64 columns
   // Groups of waves on the row tiles of few work-groups, as in apply (same sweep, backward, us, by W): fp32, one group ->
   // four: 8 32 -> 26, 48 (1536 rows) 134 -> 100; one -> two: 96 80.9 -> 69.6, 192 87.8 -> 84.9, causal 288 175 -> 155; but
   // 512 102 -> 110; bf16: A = 128, 128 23.4 -> 21.7, causal 288 58 -> 50, but not causal 65 -> 68.
@@ -1530,22 +1551,6 @@ StripArgs group_args(const Dims &d, const StripPlan &pl, char *ws, int64_t h0, i
   return a;
 }
 
-// Groups of waves on a walk of the fp32 forward in one pass (128 / groups rows per work-group), or 0: the strip, whose
-// scores are shared by work-groups along the keys too, is better where rows are few and walks long.  us, strip -> one pass, by
-// W, the work-groups of 128 rows: 4 (256 rows) 13.0 -> 10.3, 96 (320) 19.4 -> 15.7, 400 (512) 60 -> 51, 768 (512) 108 -> 75, 480
-// (1536) 210 -> 145, causal 288 (1536) 77 -> 72, 96 (768) 31 -> 24; but 12 (768) 19 -> 23, 144 (1536) 77 -> 88.
-int f32_one_pass(const Dims &d) {
-  if (d.A != 64) return 0;
-  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
-  if (d.L <= 512) {
-    if (W <= (d.causal ? 96 : 64)) return 4;
-    return W <= 128 || (W >= 230 && W <= 320) || (d.causal && W <= 400) ? 2 : 1;
-  }
-  if (d.causal && d.L <= 1024 && W > 64 && W <= 128) return 4;
-  if (d.causal && W >= 250 && W <= 400) return 2;
-  return W >= 400 ? 1 : 0;
-}
-
 template <int RW, int KS>
 hipError_t launch_f32_forward(const Dims &d, PassArgs a, hipStream_t st) {
   a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
@@ -1567,7 +1572,7 @@ template <typename T>
 hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE,
                      char *ws, const StripPlan &pl, hipStream_t st) {
   if constexpr (sizeof(T) == 4)
-    if (const int groups = f32_one_pass(d)) return f32_forward(d, Q, K, V, O, LSE, groups, st);
+    if (pl.one_pass) return f32_forward(d, Q, K, V, O, LSE, pl.one_pass, st);
   const int64_t heads = (int64_t)d.B * d.Z;
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;
@@ -1576,7 +1581,7 @@ hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V,
       const StripArgs a = group_args<T>(d, pl, ws, h0, r0, nr, Q, K, V);
       RSA_TRY(launch_scores<T>(a, nh, false, st));
       const ApplyArgs p = {a.strip, a.V, static_cast<T *>(O) + (h0 * d.Lq + r0) * d.A, LSE + h0 * d.Lq + r0, nullptr};
-      RSA_TRY((launch_apply<T, true>(a, p, nh, st)));
+      RSA_TRY((launch_apply<T, true>(a, p, nh, pl.usual, st)));
     }
   }
   return hipSuccess;
@@ -1598,14 +1603,14 @@ hipError_t backward_t(const Dims &d, const void *dO, const void *Q, const void *
       RSA_TRY(launch_scores<T>(a, nh, true, st));
       float *norm = reinterpret_cast<float *>(ws + pl.norm);
       const ApplyArgs p = {a.strip2, a.K, static_cast<T *>(dQ) + q, nullptr, norm};
-      RSA_TRY((launch_apply<T, false>(a, p, nh, st)));
+      RSA_TRY((launch_apply<T, false>(a, p, nh, pl.usual, st)));
       CollectArgs c{};
       c.strip[0] = a.strip; c.Y[0] = a.dO; c.out[0] = static_cast<T *>(dV) + k; c.alpha[0] = 1.0f;
       c.strip[1] = a.strip2; c.Y[1] = a.Q; c.out[1] = static_cast<T *>(dK) + k; c.alpha[1] = d.scale;
       c.acc[0] = reinterpret_cast<float *>(ws + pl.acc_v); c.acc[1] = reinterpret_cast<float *>(ws + pl.acc_k);
       c.norm = norm;
       c.add = r0 > 0; c.keep = r0 + nr < d.Lq;
-      RSA_TRY(launch_collect<T>(a, c, nh, st));
+      RSA_TRY(launch_collect<T>(a, c, nh, pl.usual, st));
     }
   }
   return hipSuccess;

@@ -376,3 +376,29 @@ def test_f32_small_numbers(k):
         assert bool(((got.double() - ref).abs() <= bound).all())
         if k <= 100:
             assert float((got.double() - ref).norm() / ref.norm()) <= 4e-7
+
+
+@pytest.mark.parametrize("dtype,kw", [
+    ("f32", dict(B=4, Z=8, L=2048, N=8)),                 # forward in one pass, also a few heads at a time
+    ("f32", dict(B=2, Z=12, L=1984, N=1, causal=True)),   # strips, in groups of heads
+    ("f32", dict(B=1, Z=9, L=2048, N=4, A=128)),
+    ("bf16", dict(B=2, Z=16, L=2048, N=4)),
+    ("bf16", dict(B=1, Z=24, L=2048, N=4, A=128, causal=True)),
+])
+def test_staged_results_over_inputs_round_alike(dtype, kw):
+    """The kernels and their shapes are chosen by the call, not by how many heads' results wait in the workspace at a time:
+    bit-identical wherever the results lie (all rows of a head fit a group here)."""
+    cfg = small_cfg(dtype, **dict(dict(seed=107), **kw))
+    x = inputs.make_inputs(cfg)
+    t = {k: upload(x[k], dtype) for k in ("Q", "K", "V", "dO")}
+    desc = rsa.make_desc(t["K"], cfg.N, causal=cfg.causal, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(desc, t["Q"], t["K"], t["V"])
+    for i in ("Q", "K", "V"):
+        u = {k: v.clone() for k, v in t.items()}
+        got = rsa.forward(desc, u["Q"], u["K"], u["V"], O=u[i])
+        assert torch.equal(got[0], O) and torch.equal(got[1], LSE), i
+    grads = rsa.backward(desc, t["dO"], t["Q"], t["K"], t["V"], O, LSE)
+    u = {k: v.clone() for k, v in t.items()}
+    got = rsa.backward(desc, u["dO"], u["Q"], u["K"], u["V"], O, LSE, dQ=u["Q"], dK=u["K"], dV=u["V"])
+    for a, b in zip(got, grads):
+        assert torch.equal(a, b)
