@@ -1365,8 +1365,10 @@ struct StripPlan {
   size_t strip, strip2, stats, norm, acc_k, acc_v, total;
 };
 
-// Places a group's buffers from byte `off` of the workspace on.
+// Places a group's buffers from byte `off` of the workspace on (one pass: it has none).
 void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
+  p.total = off;
+  if (p.one_pass) return;
   const size_t es = dtype == RSA_BF16 ? 2 : 4, scores = (size_t)p.heads * p.rows * d.L;
   p.strip = off; off += align256(scores * es);
   if (pass == 1) {
@@ -1401,7 +1403,7 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
   p.rows = d.Lq;
   p.heads = heads;
   p.one_pass = pass == 0 && dtype == RSA_F32 ? f32_one_pass(d) : 0;
-  if (head * heads > kStripBytes) {
+  if (head * heads > kStripBytes && !p.one_pass) {
     if (head <= kStripBytes) {
       const int64_t most = head < kCacheBytes ? (int64_t)(kCacheBytes / head) : 1;
       const int64_t groups = (heads + most - 1) / most;
@@ -1430,7 +1432,8 @@ struct HeadBytes {
 
 // The plan for results that lie over inputs: they stay in the workspace until these have been read, and are copied
 // then.  Where each lies tensor over tensor, head over head, that is a group's results at a time; else (whole) those of
-// all heads.  The groups take what is left of a workspace of `bytes`; 0: the least plan, one head's 128 rows at a time.
+// all heads.  The groups take what is left of a workspace of `bytes`; 0: the least plan, one head's 128 rows at a time or,
+// in one pass, heads whose work-groups fill the chip twice.
 StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
   const HeadBytes hb(d, dtype, pass);
   const int64_t all = (int64_t)d.B * d.Z;
@@ -1446,7 +1449,9 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t byte
     if (place(h, d.Lq)) return p;
   for (int64_t r = d.Lq / 128 * 128; bytes > 0 && r > 128; r = r * 7 / 8 / 128 * 128)
     if (place(1, r)) return p;
-  place(1, d.Lq < 128 ? d.Lq : 128);
+  const int64_t fill = (512 * 128 + d.Lq - 1) / d.Lq;
+  if (p.one_pass) place(fill < all ? fill : all, d.Lq);
+  else place(1, d.Lq < 128 ? d.Lq : 128);
   return p;
 }
 
@@ -1672,12 +1677,19 @@ hipError_t pass_apart(const Dims &d, int pass, const void *const (&in)[6], void 
 hipError_t run_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], char *ws,
                     size_t ws_bytes, hipStream_t st) {
   const int over = results_over_inputs(d, dtype, pass, in, out);
-  if (over) {
-    const StripPlan pl = apart_plan(d, dtype, pass, over == 2, ws_bytes);
+  StripPlan pl = strip_plan(d, dtype, pass);
+  // In one pass O may lie over Q as it is: a work-group has read its own rows when it writes them, and no other reads them.
+  const HeadBytes hb(d, dtype, pass);
+  const size_t heads = (size_t)d.B * d.Z;
+  auto over_q_alone = [&]() {
+    return over == 1 && !overlap(out[0], heads * hb.out[0], in[1], heads * hb.in[1]) &&
+           !overlap(out[0], heads * hb.out[0], in[2], heads * hb.in[2]);
+  };
+  if (over && !(pl.one_pass && over_q_alone())) {
+    pl = apart_plan(d, dtype, pass, over == 2, ws_bytes);
     return dtype == RSA_BF16 ? pass_apart<uint16_t>(d, pass, in, out, ws, pl, st)
                              : pass_apart<float>(d, pass, in, out, ws, pl, st);
   }
-  const StripPlan pl = strip_plan(d, dtype, pass);
   return dtype == RSA_BF16 ? pass_t<uint16_t>(d, pass, in, out, ws, pl, st) : pass_t<float>(d, pass, in, out, ws, pl, st);
 }
 #undef RSA_TRY

@@ -121,6 +121,16 @@ def test_workspace_sizes_follow_table2():
         assert rsa.strerror(s)
 
 
+def test_forward_in_one_pass_asks_for_no_strip():
+    kw = dict(dtype=rsa.RSA_F32, flags=rsa.MODE_STAGED)
+    d = desc(B=16, Z=12, L=512, N=4, rank_end=4, **kw)
+    strip = 16 * 12 * 512 * 512 * 4
+    assert 0 < rsa.workspace_bytes(d, False) <= 2 * 512 * 128 * (64 + 1) * 4 < strip    # results of a few heads
+    assert rsa.workspace_bytes(d, True) >= 2 * strip
+    d = desc(B=1, Z=2, L=2048, N=4, rank_end=4, **kw)                                   # few rows, long walks: the strip
+    assert rsa.workspace_bytes(d, False) >= 2 * 2048 * 2048 * 4
+
+
 def test_split_plan_of_the_key_walk():
     """Host logic behind rsa_workspace_bytes in fused mode: how many work-groups share a row
     tile's walk over the keys (forward: (A + 2) floats per row and split; dQ: A floats)."""

@@ -379,7 +379,9 @@ def test_f32_small_numbers(k):
 
 
 @pytest.mark.parametrize("dtype,kw", [
-    ("f32", dict(B=4, Z=8, L=2048, N=8)),                 # forward in one pass, also a few heads at a time
+    ("f32", dict(B=4, Z=8, L=2048, N=8)),                 # forward in one pass,
+    ("f32", dict(B=16, Z=12, L=512, N=4, causal=True)),   # O over K and V a few heads at a time
+    ("f32", dict(B=1, Z=3, L=320, N=5)),                  # groups of waves on a walk
     ("f32", dict(B=2, Z=12, L=1984, N=1, causal=True)),   # strips, in groups of heads
     ("f32", dict(B=1, Z=9, L=2048, N=4, A=128)),
     ("bf16", dict(B=2, Z=16, L=2048, N=4)),
