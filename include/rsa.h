@@ -119,7 +119,8 @@ size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
  * results then wait in the workspace until the inputs have been read.  Tensor exactly
  * over tensor of the same size (dQ over Q, dK over K) needs no more workspace, any
  * other overlap room for all results besides one head's strips (RSA_ERR_WORKSPACE if
- * ws_bytes does not hold them).  In fused mode outputs must not overlap inputs.
+ * ws_bytes does not hold them).  In fused mode outputs must not overlap inputs, but for
+ * dK and dV, which may lie exactly over K and V, either over either.
  * ws: workspace of at least rsa_workspace_bytes(d, 0) bytes (may be NULL if
  * that is 0).  Staged mode keeps the score strip there; fused mode needs it
  * only when the descriptor has so few query rows for its keys (one rank's

@@ -982,7 +982,8 @@ hipError_t fused_backward(const Dims &d, const void *dO, const void *Q, const vo
   // prologue costs the dQ kernel more registers than it has: there the row terms come from
   // the preprocess kernel.)
   hipError_t e;
-  // (dK, dV may lie over K, V: each dK/dV work-group has read its own keys, but the other kind reads them all)
+  // (dK, dV may lie over K, V: a dK/dV work-group has read its own keys by then and no other of its kind reads them, but the
+  // dQ kind reads them all, and has to be done)
   const size_t kv = 2 * (size_t)((d.B - 1) * d.ks[0] + (d.Z - 1) * d.ks[1] + (d.L - 1) * d.ks[2] + d.A);
   const bool over = overlap(dK, kv, K, kv) || overlap(dK, kv, V, kv) || overlap(dV, kv, K, kv) || overlap(dV, kv, V, kv);
   if (const int groups = qsplits > 1 || over ? 0 : both_groups(d)) {

@@ -39,3 +39,22 @@ def test_against_the_oracle_and_the_kernels_one_by_one(A, B, Z, L, N, rb, re, ca
         # the same products in another order of the fp32 sums: an element's bf16 may round the other way
         assert (np.abs(a - b) <= 2.0 ** -7 * np.abs(b) + 1e-4 * np.sqrt(np.mean(b * b))).all(), name
         assert np.sqrt(np.mean((a - b) ** 2)) <= 1e-3 * np.sqrt(np.mean(b * b)), name
+
+
+@pytest.mark.parametrize("A,B,Z,L,N,causal", [(64, 1, 3, 1088, 17, True), (64, 3, 11, 512, 4, False), (128, 2, 9, 576, 9, False),
+                                              (64, 16, 8, 1024, 4, False)])
+@pytest.mark.parametrize("dk,dv", [("K", "V"), ("V", "K"), ("K", None), (None, "K")])
+def test_gradients_over_keys_and_values(A, B, Z, L, N, causal, dk, dv):
+    """dK and dV may lie exactly over K and V: the two kinds then take turns, the gradients are those of buffers of their
+    own (to the order of the fp32 sums, see above)."""
+    cfg = inputs.RSAConfig("g", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=0, rank_end=N, seed=47)
+    x = inputs.make_inputs(cfg)
+    t = {k: upload(x[k], "bf16") for k in ("Q", "K", "V", "dO")}
+    desc = rsa.make_desc(t["K"], N, causal=causal)
+    O, LSE = rsa.forward(desc, t["Q"], t["K"], t["V"])
+    ref = [download(g) for g in rsa.backward(desc, t["dO"], t["Q"], t["K"], t["V"], O, LSE)]
+    got = rsa.backward(desc, t["dO"], t["Q"], t["K"], t["V"], O, LSE, dK=t.get(dk), dV=t.get(dv))
+    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+        a = download(a)
+        assert (np.abs(a - b) <= 2.0 ** -7 * np.abs(b) + 1e-4 * np.sqrt(np.mean(b * b))).all(), name
+        assert np.sqrt(np.mean((a - b) ** 2)) <= 1e-3 * np.sqrt(np.mean(b * b)), name
