@@ -3,7 +3,7 @@
 // two heads of 512 rows: 8.8 us of host time, of which the launch 3; 13.7 for the backward).  Argument marshalling only.
 //
 // Every function takes its arguments by position, None for a tensor to be allocated, and returns its results, or the
-// library's status as an int where that is not RSA_OK.
+// library's status as an int where that is not RSA_OK.  What is allocated here are plain tensors.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -119,8 +119,8 @@ at::Tensor workspace(const Call &c, int i, size_t need, const at::Tensor &like, 
   n = (size_t)t.numel();
   return t;
 }
-at::Tensor row_terms(const at::Tensor &Q) {
-  return at::empty(Q.sizes().slice(0, 3), Q.options().dtype(at::kFloat).memory_format(std::nullopt));
+at::Tensor row_terms(const at::Tensor &Q) {  // (Q may have fewer dimensions than the descriptor's four: taken as dense)
+  return at::empty(Q.sizes().slice(0, Q.dim() < 3 ? Q.dim() : 3), Q.options().dtype(at::kFloat).memory_format(std::nullopt));
 }
 // The ranks' rows, as Python divides: a descriptor that the library will refuse gets there with any numbers in it.
 int64_t rows_of(const rsa_desc *d) {
