@@ -123,6 +123,15 @@ def _done(result):
     return result
 
 
+# Results like a tensor of these types are allocated natively, like one of a subclass by torch's own functions, which
+# may make them of the same kind.
+_PLAIN = frozenset((torch.Tensor, torch.nn.Parameter))
+
+
+def _like(given, t, new=torch.empty_like, **kw):
+    return given if given is not None or type(t) in _PLAIN else new(t, **kw)
+
+
 def strerror(status):
     return lib().rsa_strerror(int(status)).decode()
 
@@ -179,11 +188,16 @@ def workspace_bytes(desc, backward):
 
 def forward(desc, Q, K, V, O=None, LSE=None, ws=None):
     """rsa_forward.  Q: (B,Z,Lq,A); K, V: (B,Z,L,A).  Returns (O, LSE)."""
+    if type(Q) not in _PLAIN:
+        O = _like(O, Q)
+        LSE = _like(LSE, Q, lambda t: t.new_empty(t.shape[:3], dtype=torch.float32))
     return _done(_native().forward(desc, Q, K, V, O, LSE, ws))
 
 
 def backward(desc, dO, Q, K, V, O, LSE, dQ=None, dK=None, dV=None, ws=None):
     """rsa_backward.  Returns (dQ, dK, dV)."""
+    if not _PLAIN.issuperset((type(Q), type(K), type(V))):
+        dQ, dK, dV = _like(dQ, Q), _like(dK, K), _like(dV, V)
     return _done(_native().backward(desc, dO, Q, K, V, O, LSE, dQ, dK, dV, ws))
 
 
@@ -268,11 +282,11 @@ def out_proj(desc, O, Wo, Y=None):
 
 
 def out_proj_bwd(desc, dY, O, Wo, dO=None, dWo=None, ws=None):
-    return _done(_native().out_proj_bwd(desc, dY, O, Wo, dO, dWo, ws))
+    return _done(_native().out_proj_bwd(desc, dY, O, Wo, _like(dO, O), dWo, ws))
 
 
 def qkv_proj_bwd(desc, dQ, dK, dV, X, Wqkv, dX=None, dW=None, ws=None):
-    return _done(_native().qkv_proj_bwd(desc, dQ, dK, dV, X, Wqkv, dX, dW, ws))
+    return _done(_native().qkv_proj_bwd(desc, dQ, dK, dV, X, Wqkv, _like(dX, X), dW, ws))
 
 
 # ---- Linformer variant (Table 3): keys and values projected along the sequence ----
@@ -286,13 +300,17 @@ def linformer_project(desc, X, E, Xp=None, ws=None):
 
 
 def linformer_forward(desc, Q, Kp_, Vp_, O=None, LSE=None):
-    return _done(_native().linformer_forward(desc, Q, Kp_, Vp_, O, LSE))
+    return _done(_native().linformer_forward(desc, Q, Kp_, Vp_, _like(O, Q), LSE))
 
 
 def linformer_backward(desc, dO, Q, Kp_, Vp_, O, LSE, dQ=None, dKp=None, dVp=None, ws=None):
+    dQ, dKp, dVp = _like(dQ, Q), _like(dKp, Kp_), _like(dVp, Vp_)
     return _done(_native().linformer_backward(desc, dO, Q, Kp_, Vp_, O, LSE, dQ, dKp, dVp, ws))
 
 
 def linformer_project_bwd(desc, dXp, X, E, dX=None, dE=None):
     """dX (rows of the descriptor's ranks; a new tensor is zero elsewhere) and dE (fp32, same)."""
+    if not _PLAIN.issuperset((type(X), type(E))):
+        new = torch.empty_like if (desc.rank_begin, desc.rank_end) == (0, desc.N) else torch.zeros_like
+        dX, dE = _like(dX, X, new), _like(dE, E, new, dtype=torch.float32, memory_format=torch.contiguous_format)
     return _done(_native().linformer_project_bwd(desc, dXp, X, E, dX, dE))

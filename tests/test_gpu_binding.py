@@ -1,11 +1,15 @@
 """What the native binding accepts and returns, as the Python functions did: a Q with fewer dimensions, which the descriptor
-lays out."""
+lays out, and subclasses of Tensor, whose results are of their kind."""
 import pytest
 import torch
 
 from paper_2105_13120_amd import rsa
 
 pytestmark = pytest.mark.gpu
+
+
+class Tagged(torch.Tensor):
+    pass
 
 
 def rand(*shape):
@@ -26,3 +30,26 @@ def test_q_with_fewer_dimensions(dims):
     O, LSE = rsa.linformer_forward(d, Q, K2, K2)
     O2, LSE2 = rsa.linformer_forward(d, q, K2, K2)
     assert torch.equal(O2.reshape(O.shape), O) and torch.equal(LSE2.flatten()[:512], LSE.flatten())
+
+
+def test_subclasses_of_tensor():
+    torch.manual_seed(0)
+    Q, K, V, dO = (rand(1, 2, 256, 64).as_subclass(Tagged) for _ in range(4))
+    d = rsa.make_desc(K, 4)
+    O, LSE = rsa.forward(d, Q, K, V)
+    grads = rsa.backward(d, dO, Q, K, V, O, LSE)
+    assert all(type(t) is Tagged for t in (O, LSE, *grads))
+    plain = [t.as_subclass(torch.Tensor) for t in (Q, K, V, dO)]
+    O2, LSE2 = rsa.forward(d, *plain[:3])
+    assert type(O2) is torch.Tensor and torch.equal(O2, O.as_subclass(torch.Tensor))
+    mixed = rsa.backward(d, plain[3], plain[0], K, plain[2], O2, LSE2)
+    assert [type(t) for t in mixed] == [torch.Tensor, Tagged, torch.Tensor]
+    for a, b in zip(mixed, grads):
+        assert torch.equal(a.as_subclass(torch.Tensor), b.as_subclass(torch.Tensor))
+    X, E, D = rand(1, 2, 256, 64).as_subclass(Tagged), rand(256, 64).as_subclass(Tagged), rand(1, 2, 64, 64)
+    assert [type(t) for t in rsa.linformer_project_bwd(d, D, X, E)] == [Tagged, Tagged]
+    W = rand(64, 384)
+    dX, dW = rsa.qkv_proj_bwd(d, *plain[:3], rand(1, 256, 64).as_subclass(Tagged), W)
+    assert type(dX) is Tagged and type(dW) is torch.Tensor
+    p = torch.nn.Parameter(plain[0].clone(), requires_grad=False)
+    assert torch.equal(rsa.forward(d, p, *plain[1:3])[0], O2)
