@@ -3,6 +3,7 @@
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -15,8 +16,8 @@ def sources():
     return sorted(glob.glob(os.path.join(_PKG, "csrc", "*.hip")))
 
 
-def build(verbose=False):
-    """Compile every HIP source for gfx950 into one shared library (always recompiles)."""
+def build_library(verbose=False):
+    """Compile every HIP source for gfx950 into one shared library (always recompiles); needs hipcc alone."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [
         hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -26,11 +27,11 @@ def build(verbose=False):
         "-Wno-unused-command-line-argument",
     ] + sources() + ["-o", LIB_PATH]
     _run(cmd, verbose)
-    build_binding(verbose)
     return LIB_PATH
 
 
 def build_binding(verbose=False):
+    """Compile the binding against the library; needs torch's headers and a host compiler."""
     import torch
     base = os.path.dirname(torch.__file__)
     inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
@@ -44,6 +45,13 @@ def build_binding(verbose=False):
     return BINDING_PATH
 
 
+def build(verbose=False):
+    """Both; the library is there as soon as it is compiled, also where the binding cannot be built."""
+    build_library(verbose)
+    build_binding(verbose)
+    return LIB_PATH
+
+
 def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd))
@@ -53,4 +61,4 @@ def _run(cmd, verbose):
 
 
 if __name__ == "__main__":
-    print(build(verbose=True))
+    print(build_library(verbose=True) if sys.argv[1:] == ["--library"] else build(verbose=True))

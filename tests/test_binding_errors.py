@@ -33,3 +33,11 @@ def test_not_a_descriptor():
     X = torch.empty(1, 64, 64, dtype=torch.bfloat16)
     with pytest.raises((TypeError, ctypes.ArgumentError, AttributeError)):
         rsa.qkv_proj(b"no descriptor", X, X)
+
+
+def test_the_library_alone_needs_hipcc_alone(monkeypatch):
+    from paper_2105_13120_amd import build
+    ran = []
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: ran.append(cmd))
+    assert build.build_library() == build.LIB_PATH
+    assert len(ran) == 1 and not any("torch" in word or word.endswith("binding.cpp") for word in ran[0])
