@@ -1340,14 +1340,19 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Groups of waves on a walk of the fp32 forward in one pass (128 / groups rows per work-group), or 0: the strip, whose
 // scores are shared by work-groups along the keys too, is better where rows are few and walks long.  us, strip -> one pass, by
-// W, the work-groups of 128 rows: 4 (256 rows) 13.0 -> 10.3, 96 (320) 19.4 -> 15.7, 400 (512) 60 -> 51, 768 (512) 108 -> 75, 480
-// (1536) 210 -> 145, causal 288 (1536) 77 -> 72, 96 (768) 31 -> 24; but 12 (768) 19 -> 23, 144 (1536) 77 -> 88.
+// W, the work-groups of 128 rows: 64 (256 rows) 15.4 -> 10.7, 100 (320) 20.6 -> 16.3, 400 (512) 62 -> 53, 512 (512) 75 -> 57, 516
+// (1536) 252 -> 197, causal 288 (1536) 79 -> 76, 96 (768) 31 -> 25; but 48 (2048) 51 -> 61, 192 (2048) 115 -> 121.
+// Short walks: a work-group alone on its CU takes 18, 23.5, 33 us (512 rows) with four, two, one group; a second one on the
+// CU adds 15, 11, 17 us.  So as many groups as leave each work-group a CU; else two where they make one work-group per CU
+// more of both kinds (320 rows, W = 288: two 24.7, one 33.3; but 512 rows: 52, 50), under the causal mask, whose short walks
+// leave room, up to 720 of them (512 rows, W = 320: 39.8, 50.1; W = 400: 50.8 either way; 256 rows, W = 320: 29.9, 28.8).
 int f32_one_pass(const Dims &d) {
   if (d.A != 64) return 0;
-  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
+  const int64_t heads = (int64_t)d.B * d.Z, W = heads * ((d.Lq + 127) / 128);
   if (d.L <= 512) {
-    if (W <= (d.causal ? 96 : 64)) return 4;
-    return W <= 128 || (W >= 230 && W <= 320) || (d.causal && W <= 400) ? 2 : 1;
+    const int64_t by_two = heads * (d.Lq / 64), by_four = heads * (d.Lq / 32);
+    if (by_four <= 256) return 4;
+    return by_two <= (d.causal ? 720 : (W > 256 ? 512 : 256)) ? 2 : 1;
   }
   if (d.causal && d.L <= 1024 && W > 64 && W <= 128) return 4;
   if (d.causal && W >= 250 && W <= 400) return 2;
