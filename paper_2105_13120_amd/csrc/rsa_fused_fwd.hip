@@ -476,17 +476,19 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // taken when their work-groups, times their splits, fill the 512 slots at least once; else 32
 // rows per wave, which give twice the work-groups.  (A head of 128 elements takes 32 rows per
 // wave and one key tile per stage: registers and LDS.)  Unsplit, a CU's two places for large work-groups, filled in turn, are
-// compared with its four for small ones, which cost 5 % more per row: 1600 work-groups of 128 rows, L = 1024, large 74 us,
-// small 67; 1536, L = 2048: 109, 113.  Causal walks end one by one and fill places left over: small ones up to 1900
-// (1024, L = 2048: 51 -> 46; 1600, L = 1024: 47 -> 40; 2048, L = 4096: 149 -> 154).
+// compared with its four for small ones, which cost 5 % more per row where walks are longer than 512 keys (W, work-groups of
+// 128 rows, small -> large, us: 1024 rows, 896: 41.2 -> 39.2, 1536: 61.9 -> 59.5, but 1200: 51 -> 57; 2048 rows, 1536: 117 ->
+// 112) and less where they are shorter (512 rows, 1024: 25.6 -> 26.7, 256 rows: 17.3 -> 20.5).  Causal walks end one by one
+// and fill places left over: large ones only for long walks on a full chip (8192 rows, 2048: 306 -> 299, 4096 rows: 160 -> 156;
+// but 1888: 156 -> 166, 2048 rows, 3072: 129 -> 140, 1024 rows, 2048: 50.6 -> 53.6).
 void fused_fwd_plan(const Dims &d, bool *big, int *splits) {
   if (d.A == 64 && d.Lq % 256 == 0) {
     const int s = key_splits_for(d, 256);
     const int64_t wgs = (int64_t)d.B * d.Z * (d.Lq / 256), W = 2 * wgs;
     bool large = wgs * s >= 512;
     if (s == 1 && d.Lq == d.L) {
-      if (d.causal) large = W >= 1900 && d.L > 256;
-      else large = W >= 512 && (double)((W + 511) / 512) * 2 < (double)((W + 255) / 256) * (d.L > 256 && d.L <= 512 ? 1.0 : 1.055);
+      if (d.causal) large = W >= 2000 && d.L >= 4096;
+      else large = W >= 512 && d.L > 512 && (double)((W + 511) / 512) * 2 < (double)((W + 255) / 256) * 1.055;
     }
     if (large) {
       *big = true; *splits = s;
