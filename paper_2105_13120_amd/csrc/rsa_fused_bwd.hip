@@ -950,6 +950,8 @@ static hipError_t launch_both(const Dims &d, const BwdArgs &a, hipStream_t st) {
 //   two, W = 48: 512 rows 19.9 -> 14.1; causal W = 128: 20.8 -> 15.5, 4096 rows, W = 192: 103 -> 67, 32768, W = 256: 682 -> 607;
 //   one, W = 128: 512 rows 20.8 -> 14.9, W = 384: 36.2 -> 32.2, 4096 rows: 208 -> 193, causal 167 -> 114, W = 768: 512 rows
 //   63.6 -> 57.2; but 2048 rows, W = 512: 119 -> 124, W = 704: 180 -> 186, causal W = 1120: 164 -> 170 (whole rounds);
+//   just above whole rounds each kind begins another, and one grid only one for both: 2048 rows, W = 544: 169 -> 149, 640: 172 ->
+//   156, 672: 172 -> 177, 8192 rows, 576: 593 -> 563;
 //   A = 128, two groups, W = 64: 512 rows 36.3 -> 18.5, 4096: 175 -> 74; one, W = 128: 512 rows 37.6 -> 25.4, 384: 78 -> 68,
 //   causal 4096 rows, W = 256: 223 -> 148; but W = 192: 112 -> 129, 512: 142 -> 150.
 static int both_groups(const Dims &d) {
