@@ -529,8 +529,10 @@ static float reduce_us(int64_t M, int64_t N, int s) {
 // as much as it holds.  Q/K/V of 4096 rows of 2048: 127 -> 103 us with T = 4; of 8704 rows, 1088 -> 4608: 117 -> 99.)
 // chain: where the result is kept in fp32, the slabs of 64 k that one chain of additions may take; its rounding error
 // grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
-// that asks for; the smaller tiles fold theirs, after kFoldSlabs at the latest, which costs them nothing that shows.
-// (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
+// that asks for; the smaller tiles fold theirs after three quarters of it, since their folds are a chain as well, and after
+// kFoldSlabs at the latest.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each 4.0e-7, folded at 1024 k
+// 2.0e-7, as 16 splits give.  2304 rows, 640 -> 2880 weights, chain 320 k, in one split: 1.12e-7 folded at the chain,
+// 1.04 at three quarters; in two splits folded at it 1.06.)
 // sum: the times of sums over many rows (weight gradients, projections along the sequence).
 // Rows of more than kMaxLd elements: T = 4 (the only one with such loads) and all splits.
 constexpr int64_t kFoldSlabs = 16;
@@ -658,7 +660,8 @@ static bool wide_heads(const GemmArgs &g) {
 // The fields of a product's arguments that its plan decides; returns the work-groups per split.
 static uint32_t set_plan(GemmArgs &g, const GemmPlan &p) {
   const int64_t t = 64 * p.T;
-  g.chain = p.chain < kFoldSlabs ? p.chain : kFoldSlabs;
+  const int64_t fold = ((int64_t)p.chain * 3 + 3) / 4;
+  g.chain = fold < kFoldSlabs ? fold : kFoldSlabs;
   g.ntiles = (int)((g.N + t - 1) / t);
   g.kslabs = (g.K / 64 + p.splits - 1) / p.splits;
   return (uint32_t)(((g.M + t - 1) / t) * g.ntiles);
@@ -891,7 +894,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
   const int most = splits < 1 ? 1 : (splits > 64 ? 64 : (int)splits);
   // dE is kept in fp32, and its error grows with the root of its chains' length: T = 4 takes none longer than a sum that is
   // timed like the weight gradients' would be split into, and the smaller tiles fold theirs as those do.  (2048 rows, 32
-  // heads of 64, Kp = 128, one grid, relative RMS error: chains of 1024 k 1.87e-7, of 256 0.99e-7, at 13.3 and 13.6 us.)
+  // heads of 64, Kp = 128, one grid, relative RMS error: chains of 1024 k 1.87e-7, folds of 192 0.93e-7, at 13.3 and 13.7 us.)
   const int slabs = (int)(g.K / 64), chain_splits = plan_gemm(g, most, slabs, true).splits;
   const int chain = (slabs + chain_splits - 1) / chain_splits, fold = wgrad_chain(g.M, g.N, g.K);
   GemmPlan plan = plan_gemm(g, most, chain), x_plan = plan_gemm(x, 1);

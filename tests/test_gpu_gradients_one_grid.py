@@ -111,3 +111,28 @@ def test_fp32_chains_of_the_projection_matrix_gradient(rows, Z, A, Kp, chain, ov
     err = float((dE.double() - ref).norm() / ref.norm())
     chains = Z * A / chain
     assert err <= 1.25 * 2.53e-8 * (chain / 16 + chains / 2) ** 0.5, err
+
+
+@pytest.mark.parametrize("rows,Z,H,splits,fold", [(2304, 10, 960, 2, 5), (1344, 13, 832, 3, 5), (2496, 10, 640, 3, 5)])
+def test_fp32_chains_of_the_weight_gradient(rows, Z, H, splits, fold):
+    """dW in one grid errs no more than by its own launch, which takes more splits at these sizes: as many here, each folded
+    after `fold` slabs of 64 rows and added up in turn, with one rounding per 8 rows as the matrix instruction has.  2 % are
+    allowed for the difference between that and the instruction."""
+    torch.manual_seed(rows)
+    d = rsa.make_desc(torch.empty(1, Z, rows, 64, device="cuda", dtype=torch.bfloat16), 1)
+    g, X, W = [rand(1, Z, rows, 64) for _ in range(3)], rand(1, rows, H), rand(H, 3 * Z * 64)
+    x, y = X[0].double(), torch.cat([heads_to_rows(t) for t in g], 1)
+    _, dW = rsa.qkv_proj_bwd(d, *g, X, W)
+    ref, total = x.T @ y, None
+    per = -(-rows // 64 // splits) * 64
+    for s in range(0, rows, per):
+        done = None
+        for f in range(s, min(s + per, rows), fold * 64):
+            acc = torch.zeros_like(dW)
+            for k in range(f, min(f + fold * 64, s + per, rows), 8):
+                acc = (acc + x[k:k + 8].T @ y[k:k + 8]).float()
+            done = acc if done is None else done + acc
+        total = done if total is None else total + done
+    err, one_launch = (float((t.double() - ref).norm() / ref.norm()) for t in (dW, total))
+    print(f"{err:.3e} {one_launch:.3e} {err / one_launch:.3f}")
+    assert err <= 1.02 * one_launch
