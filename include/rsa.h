@@ -105,9 +105,9 @@ const char *rsa_strerror(int status);
  * needs for this descriptor; 0 if the descriptor is invalid.  Staged mode: the score
  * strips of as many ranks and heads together as fit 512 MB (a few heads at a time,
  * 192 MB, or at least one rank's rows, where not all fit); the fp32 forward of heads of
- * 64 with many rows or short ones has no strip, only room for results that have to wait
- * (at most 17 MB or one head's).  A caller with less memory calls for fewer ranks at a
- * time and adds up the partial dK, dV. */
+ * 64 with many rows or short ones has no strip, only room for its results, should they
+ * have to wait (at most what strips would take).  A caller with less memory calls for
+ * fewer ranks at a time and adds up the partial dK, dV. */
 size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
 
 /*

@@ -1399,7 +1399,7 @@ void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
 // of every score, whichever is more.
 constexpr size_t kStripBytes = (size_t)512 << 20, kCacheBytes = (size_t)192 << 20;
 
-StripPlan strip_plan(const Dims &d, int dtype, int pass) {
+StripPlan strip_plan(const Dims &d, int dtype, int pass, bool strips_only = false) {
   const size_t es = dtype == RSA_BF16 ? 2 : 4, strips = pass == 1 ? 2 : 1;
   const int64_t heads = (int64_t)d.B * d.Z;
   const size_t one_rank = (size_t)heads * d.c * d.L * (4 + es) * strips;
@@ -1407,7 +1407,7 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass) {
   StripPlan p{};
   p.rows = d.Lq;
   p.heads = heads;
-  p.one_pass = pass == 0 && dtype == RSA_F32 ? f32_one_pass(d) : 0;
+  p.one_pass = pass == 0 && dtype == RSA_F32 && !strips_only ? f32_one_pass(d) : 0;
   if (head * heads > kStripBytes && !p.one_pass) {
     if (head <= kStripBytes) {
       const int64_t most = head < kCacheBytes ? (int64_t)(kCacheBytes / head) : 1;
@@ -1702,7 +1702,13 @@ hipError_t run_pass(const Dims &d, int dtype, int pass, const void *const (&in)[
 }  // namespace
 
 size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) {
-  const size_t usual = strip_plan(d, dtype, pass).total, apart = apart_plan(d, dtype, pass, false, 0).total;
+  const StripPlan pl = strip_plan(d, dtype, pass);
+  size_t usual = pl.total;
+  const size_t apart = apart_plan(d, dtype, pass, false, 0).total;
+  if (pl.one_pass) {  // (room for all results, so that O may lie over K or V in any way, but no more than strips would take)
+    const size_t results = apart_plan(d, dtype, pass, true, 0).total, strips = strip_plan(d, dtype, pass, true).total;
+    usual = results < strips ? results : strips;
+  }
   return usual > apart ? usual : apart;
 }
 

@@ -131,6 +131,14 @@ def test_forward_in_one_pass_asks_for_no_strip():
     assert rsa.workspace_bytes(d, False) >= 2 * 2048 * 2048 * 4
 
 
+@pytest.mark.parametrize("B,Z,L,N,causal", [(16, 12, 512, 4, 0), (1, 2, 256, 4, 0), (4, 8, 2048, 8, 0), (4, 25, 192, 3, 1), (16, 16, 1536, 8, 1)])
+def test_forward_in_one_pass_has_room_for_all_results(B, Z, L, N, causal):
+    """What the strip left room for: O over K or V by any number of rows, with the workspace that is asked for."""
+    d = desc(B=B, Z=Z, L=L, N=N, rank_end=N, causal=causal, dtype=rsa.RSA_F32, flags=rsa.MODE_STAGED)
+    results, strips = B * Z * L * (64 + 1) * 4, B * Z * L * (L + L // 32) * 4
+    assert results <= rsa.workspace_bytes(d, False) < results + 4096 < strips
+
+
 def test_split_plan_of_the_key_walk():
     """Host logic behind rsa_workspace_bytes in fused mode: how many work-groups share a row
     tile's walk over the keys (forward: (A + 2) floats per row and split; dQ: A floats)."""

@@ -404,3 +404,21 @@ def test_staged_results_over_inputs_round_alike(dtype, kw):
     got = rsa.backward(desc, u["dO"], u["Q"], u["K"], u["V"], O, LSE, dQ=u["Q"], dK=u["K"], dV=u["V"])
     for a, b in zip(got, grads):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kw", [dict(B=4, Z=8, L=2048, N=8), dict(B=16, Z=12, L=512, N=4, causal=True), dict(B=1, Z=3, L=320, N=5)])
+@pytest.mark.parametrize("over", ["Q", "K", "V"])
+def test_f32_forward_over_shifted_inputs(kw, over):
+    """O from the 64th row of an input on, in one pass, with the workspace that the descriptor asks for."""
+    cfg = small_cfg("f32", **dict(dict(seed=109), **kw))
+    x = inputs.make_inputs(cfg)
+    t = {k: upload(x[k], "f32") for k in ("Q", "K", "V")}
+    desc = rsa.make_desc(t["K"], cfg.N, causal=cfg.causal, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(desc, t["Q"], t["K"], t["V"])
+    n = O.numel()
+    buf = torch.empty(n + 64 * 64, device="cuda")
+    u = dict(t)
+    u[over], out = buf[:n].view(O.shape), buf[64 * 64:].view(O.shape)
+    u[over].copy_(t[over])
+    got = rsa.forward(desc, u["Q"], u["K"], u["V"], O=out)
+    assert torch.equal(got[0], O) and torch.equal(got[1], LSE)
