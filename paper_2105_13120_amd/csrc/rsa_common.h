@@ -141,8 +141,9 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 // Sum of load(s) over the splits s, always in the same order: the deterministic end of a split walk.  Eight loads are in
-// flight at a time (one after the other, 64 splits of a small result took 16 us) and added as a tree, which rounds less.
-template <class F>
+// flight at a time (one after the other, 64 splits of a small result took 16 us).  TREE: these eight are added in pairs, which
+// rounds less than one after the other does.
+template <bool TREE = false, class F>
 __device__ __forceinline__ f32x4 sum_of_splits(int splits, F load) {
   f32x4 s = load(0);
   for (int k = 1; k < splits; k += 8) {
@@ -150,9 +151,11 @@ __device__ __forceinline__ f32x4 sum_of_splits(int splits, F load) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = load(k + j < splits ? k + j : splits - 1);
 #pragma unroll
-    for (int j = 1; j < 8; ++j)
-      if (k + j >= splits) x[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    for (int j = 0; j < 8; ++j) {
+      if (TREE && j > 0 && k + j >= splits) x[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (!TREE && k + j < splits) s += x[j];
+    }
+    if (TREE) s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
   }
   return s;
 }

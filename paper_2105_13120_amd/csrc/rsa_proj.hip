@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_kernel(const float
   const int64_t i = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
   if (i >= n4) return;
   const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + i;
-  reinterpret_cast<f32x4 *>(out)[i] = sum_of_splits(splits, [&](int k) { return p[(int64_t)k * n4]; });
+  reinterpret_cast<f32x4 *>(out)[i] = sum_of_splits<true>(splits, [&](int k) { return p[(int64_t)k * n4]; });
 }
 
 static MatView plain(const void *p, int64_t ld) {
@@ -529,13 +529,10 @@ static float reduce_us(int64_t M, int64_t N, int s) {
 // as much as it holds.  Q/K/V of 4096 rows of 2048: 127 -> 103 us with T = 4; of 8704 rows, 1088 -> 4608: 117 -> 99.)
 // chain: where the result is kept in fp32, the slabs of 64 k that one chain of additions may take; its rounding error
 // grows with the root of its length.  T = 4 has no registers for a second set of sums and takes as many splits as
-// that asks for; the smaller tiles fold theirs after three quarters of it, since their folds are a chain as well, and after
-// kFoldSlabs at the latest.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each 4.0e-7, folded at 1024 k
-// 2.0e-7, as 16 splits give.  2304 rows, 640 -> 2880 weights, chain 320 k, in one split: 1.12e-7 folded at the chain,
-// 1.04 at three quarters; in two splits folded at it 1.06.)
+// that asks for; the smaller tiles fold theirs.  (1024 x 1024 x 16384 in 4 splits, relative RMS error: one chain each
+// 4.0e-7, folded at 1024 k 2.0e-7, as 16 splits give.)
 // sum: the times of sums over many rows (weight gradients, projections along the sequence).
 // Rows of more than kMaxLd elements: T = 4 (the only one with such loads) and all splits.
-constexpr int64_t kFoldSlabs = 16;
 struct GemmPlan { int T, KG, splits, chain; float us; };
 static GemmPlan plan_gemm(const GemmArgs &g, int max_splits, int chain = 1 << 29, bool sum = false) {
   const int64_t M = g.M, N = g.N, K = g.K;
@@ -660,8 +657,7 @@ static bool wide_heads(const GemmArgs &g) {
 // The fields of a product's arguments that its plan decides; returns the work-groups per split.
 static uint32_t set_plan(GemmArgs &g, const GemmPlan &p) {
   const int64_t t = 64 * p.T;
-  const int64_t fold = ((int64_t)p.chain * 3 + 3) / 4;
-  g.chain = fold < kFoldSlabs ? fold : kFoldSlabs;
+  g.chain = p.chain;
   g.ntiles = (int)((g.N + t - 1) / t);
   g.kslabs = (g.K / 64 + p.splits - 1) / p.splits;
   return (uint32_t)(((g.M + t - 1) / t) * g.ntiles);
@@ -739,6 +735,10 @@ static int wgrad_chain(int64_t Mout, int64_t Nout, int64_t K) {
   const int s = proj_wgrad_splits(Mout, Nout, K);
   return (int)((K / 64 + s - 1) / s);
 }
+// ... after which the smaller tiles fold a gradient's: three quarters of it, since in few splits the folds are a chain as
+// well, and 1024 k at the most.  (2304 rows, 640 -> 2880 weights, chain 320 k, relative RMS error in one split: 1.12e-7
+// folded at the chain, 1.04 at three quarters; in two splits folded at it 1.06.)
+static int grad_fold(int chain) { return chain > 21 ? 16 : (chain * 3 + 3) / 4; }
 
 hipError_t proj_qkv(const Dims &d, int64_t H, const void *X, const void *W, void *Q, void *K, void *V,
                     hipStream_t st) {
@@ -765,13 +765,15 @@ hipError_t proj_out(const Dims &d, int64_t H, const void *O, const void *Wo, voi
 static hipError_t both_gradients(GemmArgs &g0, GemmArgs &g1, float *dW, float *part, const void *W, hipStream_t st) {
   const int most = proj_wgrad_splits(g1.M, g1.N, g1.K), chain = wgrad_chain(g1.M, g1.N, g1.K);
   const size_t n = (size_t)(g1.M * g1.N);
-  const GemmPlan p0 = plan_gemm(g0, 1), p1 = plan_gemm(g1, most, chain, true);
+  const GemmPlan p0 = plan_gemm(g0, 1);
+  GemmPlan p1 = plan_gemm(g1, most, chain, true);
   bool one_grid = !long_rows(g0) && !long_rows(g1) && !overlap(dW, n * 4, W, n * 2);
   PairPlan pair{};
   if (one_grid) {
     pair = plan_pair(g0, g1, most, chain, true);
     one_grid = pair.us < 0.92f * (launch_us(g0, p0) + launch_us(g1, p1));
   }
+  p1.chain = pair.p1.chain = grad_fold(chain);
   const int splits = one_grid ? pair.p1.splits : p1.splits;
   g1.out[0] = splits > 1 ? part : dW;
   hipError_t e;
@@ -896,7 +898,7 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
   // timed like the weight gradients' would be split into, and the smaller tiles fold theirs as those do.  (2048 rows, 32
   // heads of 64, Kp = 128, one grid, relative RMS error: chains of 1024 k 1.87e-7, folds of 192 0.93e-7, at 13.3 and 13.7 us.)
   const int slabs = (int)(g.K / 64), chain_splits = plan_gemm(g, most, slabs, true).splits;
-  const int chain = (slabs + chain_splits - 1) / chain_splits, fold = wgrad_chain(g.M, g.N, g.K);
+  const int chain = (slabs + chain_splits - 1) / chain_splits, fold = grad_fold(wgrad_chain(g.M, g.N, g.K));
   GemmPlan plan = plan_gemm(g, most, chain), x_plan = plan_gemm(x, 1);
   PairPlan pair{};
   bool one_grid = !long_rows(g) && !long_rows(x);
