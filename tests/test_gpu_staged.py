@@ -422,3 +422,26 @@ def test_f32_forward_over_shifted_inputs(kw, over):
     u[over].copy_(t[over])
     got = rsa.forward(desc, u["Q"], u["K"], u["V"], O=out)
     assert torch.equal(got[0], O) and torch.equal(got[1], LSE)
+
+
+@pytest.mark.parametrize("B,Z,L,N,causal,on_a_walk", [
+    (4, 8, 2048, 8, False, 1), (1, 35, 1536, 1, True, 1), (3, 8, 1536, 6, True, 2), (1, 12, 1024, 4, True, 4),
+])
+@pytest.mark.parametrize("scores", ["unit", "wide", "rising"])
+def test_f32_one_pass_on_long_walks(B, Z, L, N, causal, on_a_walk, scores):
+    """The fp32 forward in one pass where walks are longer than 512 keys: as exact as its steps, also where scores reach 60,
+    and where they grow along the keys, so that every step of a walk moves the reference that a row's sums are kept to."""
+    cfg = small_cfg("f32", causal, B=B, Z=Z, L=L, N=N, seed=113)
+    x = inputs.make_inputs(cfg)
+    Q, K, V, dO = (upload(x[k], "f32") for k in ("Q", "K", "V", "dO"))
+    if scores == "wide":
+        Q, K = Q * 4, K * 4
+    if scores == "rising":  # keys from an eighth to eight times their length
+        K = K * torch.exp2(torch.linspace(-3, 3, L, device="cuda"))[:, None]
+    ref, steps = exact(cfg, Q, K, V, dO), by_steps(cfg, Q, K, V, dO)
+    O, LSE = rsa.forward(rsa.make_desc(K, N, causal=causal, mode=rsa.MODE_STAGED), Q, K, V)
+    for k, t in (("O", O), ("LSE", LSE)):
+        e, e_steps = (float((y.double() - ref[k]).norm() / ref[k].norm()) for y in (t, steps[k]))
+        print(f"{k} {scores}: {e:.2e}, by steps {e_steps:.2e}")
+        assert e <= 1.1 * e_steps, f"{k}: {e:.2e}, by steps {e_steps:.2e}"
+        assert float((t.double() - ref[k]).abs().max()) <= 2 * float((steps[k].double() - ref[k]).abs().max()), k

@@ -1,0 +1,132 @@
+"""Which kernels a call takes, on the CPU: the cases of the GPU tests of a dispatch reach the forms that they are there for."""
+import pytest
+
+import launches
+import test_gpu_backward_one_grid as one_grid
+import test_gpu_gradients_one_grid as gradients
+import test_gpu_projected_keys_backward as projected
+import test_gpu_staged as staged
+import test_gpu_staged_groups as groups
+from paper_2105_13120_amd import rsa
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    return launches.Recorder(str(tmp_path_factory.mktemp("recorder")))
+
+
+def params(test, name=None):
+    """The parameters of a test's only (or of its `name`) parametrisation."""
+    marks = [m for m in test.pytestmark if m.name == "parametrize" and (name is None or m.args[0] == name)]
+    return marks[-1].args[1]
+
+
+def names(calls):
+    return [k.name for k in calls]
+
+
+# fused_bwd_both_kernel's shape by (halves of a head, groups of waves on a walk)
+BOTH = {(1, 4): "1, 1, 1, 4, 1, 1, 4", (1, 2): "1, 1, 2, 2, 1, 2, 2", (1, 1): "1, 2, 4, 1, 2, 4, 1",
+        (2, 2): "2, 1, 2, 2, 1, 2, 2", (2, 1): "2, 2, 4, 1, 1, 4, 1"}
+
+
+@pytest.mark.parametrize("case,on_a_walk", zip(one_grid.CASES, [4, 4, 4, 2, 2, 2, 1, 1, 1, 2, 4, 2, 1, 1]))
+def test_backward_in_one_grid(rec, case, on_a_walk):
+    A, B, Z, L, N, rb, re, causal, zigzag = case
+    d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, zigzag)
+    both = f"fused_bwd_both_kernel<{str(causal).lower()}, {BOTH[A // 64, on_a_walk]}>"
+    assert names(launches.backward(rec, d)) == ["bwd_preprocess_kernel", both]
+    assert names(rec("bwd_dkdv", d, "dO", "Q", "K", "V", "ws", "dK", "dV"))[0].startswith("fused_bwd_dkdv_kernel")
+    assert names(rec("bwd_dq", d, "dO", "Q", "K", "V", "ws", "dQ"))[0].startswith("fused_bwd_dq_kernel")
+
+
+@pytest.mark.parametrize("case,one", zip(params(one_grid.test_gradients_over_keys_and_values, "A,B,Z,L,N,causal"), [True, True, True, False]))
+def test_backward_over_keys_and_values_takes_two_grids(rec, case, one):
+    A, B, Z, L, N, causal = case
+    d = launches.descriptor(B, Z, L, N, A, causal=causal)
+    assert any("both" in n for n in names(launches.backward(rec, d))) == one
+    for dK, dV in (("K", "V"), ("V", "K"), ("K", "dV"), ("dK", "K")):
+        assert not any("both" in n for n in names(launches.backward(rec, d, dK, dV)))
+
+
+# groups of waves: fp32 forward in one pass (0: the strip), fp32 apply, collect, bf16 apply, collect
+STAGED = [(4, 4, 4, 4, 1), (4, 4, 4, 4, 1), (0, 4, 4, 4, 2), (2, 2, 2, 2, 1), (2, 2, 2, 4, 1), (4, 2, 2, 4, 2), (0, 2, 2, 2, 2),
+          (1, 2, 2, 2, 1), (2, 1, 1, 1, 1), (1, 1, 1, 1, 1), (2, 2, 2, 2, 1), (4, 4, 2, 4, 1), (2, 1, 1, 2, 1), (0, 2, 2, 2, 1)]
+
+
+@pytest.mark.parametrize("case,on_a_walk", zip(groups.CASES, STAGED))
+def test_two_pass_groups(rec, case, on_a_walk):
+    B, Z, L, N, A, rb, re, causal = case
+
+    def last(kernels, start):  # (the last number of a kernel's shape: its groups)
+        return [int(n.rstrip(">").split(", ")[-1]) for n in names(kernels) if n.startswith(start)]
+
+    one_pass, *rest = on_a_walk
+    for dtype, apply, collect in ((rsa.RSA_F32, *rest[:2]), (rsa.RSA_BF16, *rest[2:])):
+        d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, dtype=dtype, mode=rsa.MODE_STAGED)
+        fwd, bwd = launches.forward(rec, d), launches.backward(rec, d)
+        assert last(bwd, "strip_apply") == [apply] and last(bwd, "strip_collect") == [collect]
+        assert last(fwd, "f32_forward") == ([one_pass] if dtype == rsa.RSA_F32 and one_pass else [])
+
+
+@pytest.mark.parametrize("case", params(staged.test_f32_one_pass_on_long_walks, "B,Z,L,N,causal,on_a_walk"))
+def test_two_pass_long_walks_in_one_pass(rec, case):
+    B, Z, L, N, causal, on_a_walk = case
+    d = launches.descriptor(B, Z, L, N, causal=causal, dtype=rsa.RSA_F32, mode=rsa.MODE_STAGED)
+    assert names(launches.forward(rec, d)) == [f"f32_forward_kernel<{4 // on_a_walk}, {on_a_walk}>"]
+
+
+def tiles(launch):
+    """(T, groups) of the products of a launch."""
+    t = [x.strip() for x in launch.name[launch.name.index("<") + 1:-1].split(",")]
+    if launch.name.startswith("proj_gemm_pair"):
+        return (int(t[2]), int(t[3])), (int(t[4]), int(t[5]))
+    return ((int(t[4]), int(t[5])),)
+
+
+# the input's and the weights' gradient, in one grid or (None) in two: of the Q/K/V map, of the output map
+SMALL, LARGE = (1, 2), (4, 1)
+MAPS = [((SMALL, SMALL), (SMALL, SMALL)), ((SMALL, SMALL), (SMALL, SMALL)), ((SMALL, SMALL), (SMALL, SMALL)),
+        (None, ((2, 1), (2, 1))), (((2, 1), (2, 1)), ((2, 1), SMALL)), (None, ((2, 1), (2, 1))),
+        (((2, 1), (2, 1)), ((2, 1), (2, 1))), (None, (LARGE, (2, 2))),
+        ((SMALL, (2, 1)), (SMALL, (2, 1))), ((LARGE, (2, 2)), (SMALL, SMALL)), ((LARGE, LARGE), (LARGE, (2, 2))),
+        ((LARGE, LARGE), ((2, 1), (2, 1)))]
+
+
+@pytest.mark.parametrize("case,want", zip(params(gradients.test_maps), MAPS))
+def test_gradients_of_the_maps(rec, case, want):
+    rows, Z, A, H = case
+    d = launches.descriptor(1, Z, rows, 1, A)
+    for call, form in zip((rec("qkv_proj_bwd", d, H, "dQ", "dK", "dV", "X", "W", "dX", "dW", "ws"),
+                           rec("out_proj_bwd", d, H, "dY", "O", "Wo", "dO", "dWo", "ws")), want):
+        got = [tiles(k) for k in call if k.name.startswith("proj_gemm")]
+        if form:
+            assert got == [form]
+        else:
+            assert len(got) == 2
+    # dW over W keeps two launches
+    assert len([k for k in rec("qkv_proj_bwd", d, H, "dQ", "dK", "dV", "X", "W", "dX", "W", "ws") if "gemm" in k.name]) == 2
+
+
+ALONG = [(SMALL, SMALL), (SMALL, SMALL), ((2, 1), SMALL), ((2, 1), (2, 1)), ((2, 1), (2, 1)), ((2, 1), (2, 1)), None, (LARGE, LARGE),
+         (LARGE, LARGE)]
+
+
+@pytest.mark.parametrize("case,want", zip(params(gradients.test_projection_along_the_sequence), ALONG))
+def test_gradients_of_the_projection_along_the_sequence(rec, case, want):
+    rows, Z, A, Kp, over = case
+    d = launches.descriptor(1, Z, rows, 1, A)
+    got = [tiles(k) for k in rec("linformer_project_bwd", d, Kp, "dXp", "X", "E", "X" if over else "dX", "dE") if "gemm" in k.name]
+    assert got == [want] if want else len(got) == 2
+
+
+# blocks of 32 keys, groups, splits
+@pytest.mark.parametrize("case,want", zip(params(projected.test_few_keys), [
+    (1, 4, 8), (1, 4, 16), (1, 4, 1), (4, 1, 4), (2, 2, 8), (1, 4, 8), (2, 2, 8), (2, 2, 1)]))
+def test_few_projected_keys(rec, case, want):
+    B, Z, L, N, ranks, Kp, A = case
+    d = launches.descriptor(B, Z, L, N, A, ranks)
+    kernels = rec("linformer_backward", d, Kp, "dO", "Q", "Kp", "Vp", "O", "LSE", "dQ", "dKp", "dVp", "ws")
+    k = next(k for k in kernels if k.name.startswith("fused_bwd_dkdv"))
+    assert (*(int(x) for x in k.name.rstrip(">").split(", ")[-2:]), k.grid[1]) == want
+    assert any(k.name.startswith("qsplit_reduce") for k in kernels) == (want[2] > 1)
