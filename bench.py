@@ -6,7 +6,9 @@ Prints ONE JSON line.  `value` is algorithmic TFLOP/s: 12 * B * Z * A * (visible
 query-key pairs) flops per step (4 forward: QK^T, PV; 8 backward: dV, dP, dQ, dK;
 recomputation and softmax flops are not credited) over the wall time of the timed
 steps.  `roofline` prices the dominant kernel (the fused dK/dV kernel) against
-the bf16 dense MFMA peak; `mfma_executed_tflops` / `mfma_util` count what the matrix
+the bf16 dense MFMA peak, launched by its own entry point (`kernel_ms_of`: where rsa_backward
+forms dQ and dK, dV in one grid, as for bert_base, `kernel_ms` are those of the kernels one by
+one and add up to more than the step); `mfma_executed_tflops` / `mfma_util` count what the matrix
 cores actually execute (9 GEMM units for the 6 algorithmic ones: the backward
 recomputes the scores in both of its kernels and dP in the dQ kernel);
 `cpu_baseline` times the fp64 oracle on the host cores on a bounded sample of the
@@ -73,6 +75,7 @@ def workload_summary(cfg, res):
         "frac_of_bf16_peak": round(res["tflops"] / PEAK_BF16_TFLOPS, 4),
         "mfma_executed_tflops": round(executed, 2), "mfma_util": round(executed / PEAK_BF16_TFLOPS, 4),
         "kernel_ms": {n: round(v, 4) for n, v in res["kernel_ms"].items()},
+        "kernel_ms_of": "step-level entry points, one kernel at a time",
         "roofline": r["bwd_dkdv"], "kernel_rooflines": {k: r[k] for k in ("fwd", "bwd_dq")},
     }
 

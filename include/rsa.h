@@ -189,9 +189,10 @@ int rsa_store(const rsa_desc *d, const float *src, void *dst, size_t count,
  * The kernels of the deterministic fused backward on their own (bf16, fused mode),
  * for profiling and tests, on one workspace `ws` of at least
  * rsa_workspace_bytes(d, 1) bytes (checked on the host: RSA_ERR_WORKSPACE).  With
- * RSA_DETERMINISTIC rsa_backward runs the dQ kernel first, with the preprocess folded
- * into its prologue, then the dK/dV kernel; the three calls below in the order
- * given produce the same gradients up to the fp32 summation order of D.
+ * RSA_DETERMINISTIC as without it, rsa_backward runs the dQ kernel first, with the
+ * preprocess folded into its prologue, then the dK/dV kernel, or for small and middle
+ * sizes the preprocess and then both kinds of work-groups in one grid; the three calls
+ * below in the order given produce the same gradients up to the order of fp32 sums.
  *  rsa_bwd_preprocess: fills ws with the row terms -D_i = -sum_a dO_ia O_ia and
  *    -LSE_i / s (fp32).  Both other kernels recompute
  *    P = exp2(s log2(e) (Q K^T - LSE / s)) tile by tile from the caller's Q and K

@@ -87,11 +87,6 @@ __device__ __forceinline__ void lds_dma16_unseen(const void *g, int lane_off, ui
 __device__ __forceinline__ void lds_dma16_unseen_far(const void *g, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_base) : "m0");
 }
-// Same, 4 bytes per lane, landing at lds_base + 4 lane.
-__device__ __forceinline__ void lds_dma4_unseen(const void *g, int lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-               : : "v"(lane_off), "s"(g), "s"(lds_base) : "m0");
-}
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
 }

@@ -175,8 +175,6 @@ struct HalfLanes {
 // Longest row (elements) whose place in a tile of 64 fits the loads' unsigned 32-bit byte offset.
 constexpr int64_t kMaxLd = (int64_t)1 << 25;
 
-// WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
-// LONG: an operand with rows of more than kMaxLd elements; its loads take 64-bit addresses per lane.
 // The LDS of a work-group of KG groups, one object for every product that the kernel's branches form.
 template <int N> struct GemmLds {
   unsigned char bytes[N * 8 * kHalfBytes];
@@ -190,6 +188,8 @@ template <int N> __device__ __forceinline__ GemmLds<N> &gemm_lds() {
 }
 
 // Work-group (bx, by) of (nx, splits).
+// WIDE: heads of 128 elements somewhere in the product (an operand view or the output).
+// LONG: an operand with rows of more than kMaxLd elements; its loads take 64-bit addresses per lane.
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG, bool LONG>
 __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_t nx, uint32_t by) {
   constexpr int HT = 2 * T;         // half tiles per slab, and waves per group

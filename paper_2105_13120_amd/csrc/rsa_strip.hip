@@ -1380,7 +1380,7 @@ void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
     p.strip2 = off; off += align256(scores * es);
     if (dtype == RSA_F32) {
       p.stats = off; off += align256(scores / 64 * 4);
-      p.norm = off; off += align256((size_t)p.heads * p.rows * 4 + 128);  // (collect reads it 64 at a time from row 32 k)
+      p.norm = off; off += align256((size_t)p.heads * p.rows * 4);
     }
     if (p.rows < d.Lq) {
       p.acc_k = off; off += align256((size_t)p.heads * d.L * d.A * 4);
