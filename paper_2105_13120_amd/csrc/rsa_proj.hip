@@ -907,7 +907,12 @@ hipError_t linformer_project_bwd(int64_t Zt, int64_t L, int64_t rows, int64_t Kp
     const float dx_us = by_heads ? 2.5f + 0.015f * (float)Kp + (float)(rows * Zt * A) * (2.0f / 3.6e6f) : x_plan.us;
     pair = plan_pair(x, g, 1, chain, false);
     pair.p1.chain = fold;
-    one_grid = pair.us < 0.97f * (plan.us + dx_us);  // (16384 rows, 64 heads, Kp = 128: 70.2 to 70.6; it takes 79 to 66)
+    // (One grid moves X and dX at 3.6 TB/s at most, where the two launches' dX is a stream of its own: 16384 rows, 64 heads,
+    // Kp = 128: 82 us, 68 in two launches, 80640 rows, 22 heads of 128: 293, 248; but 7296 rows, 27 heads, Kp = 256: 25.6, 36.5.
+    // dE's folds are not in its estimate, hence the 3 %: of 260 calls of 128 .. 108864 rows and 2 .. 170 heads, the time of the slower
+    // form where it is taken adds 0.6 % on average, 16 at most; with the line at 0.97 of two launches: 1.0 and 43.)
+    const float one_us = fmaxf(pair.us, (float)(rows * Zt * A) * (4.0f / 3.6e6f));
+    one_grid = one_us < 1.03f * (plan.us + dx_us);
   }
   if (one_grid && !over) return launch_pair<false>(x, g, pair, st);
   if (one_grid) x_plan = pair.p0;  // (dX's additions in the same order, wherever it lies)

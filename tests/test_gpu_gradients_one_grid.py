@@ -85,6 +85,7 @@ def test_weight_gradient_over_the_weights():
     (896, 6, 64, 128, True),      # dX over X: two launches
     (19136, 3, 64, 320, False),   # tiles of 256
     (19136, 2, 128, 256, False),
+    (7296, 27, 64, 256, False),   # tiles of 128, close to the line between one grid and two launches
 ])
 def test_projection_along_the_sequence(rows, Z, A, Kp, over):
     torch.manual_seed(rows + Kp)

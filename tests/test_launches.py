@@ -109,7 +109,7 @@ def test_gradients_of_the_maps(rec, case, want):
 
 
 ALONG = [(SMALL, SMALL), (SMALL, SMALL), ((2, 1), SMALL), ((2, 1), (2, 1)), ((2, 1), (2, 1)), ((2, 1), (2, 1)), None, (LARGE, LARGE),
-         (LARGE, LARGE)]
+         (LARGE, LARGE), ((2, 1), (2, 1))]
 
 
 @pytest.mark.parametrize("case,want", zip(params(gradients.test_projection_along_the_sequence), ALONG))
@@ -118,6 +118,12 @@ def test_gradients_of_the_projection_along_the_sequence(rec, case, want):
     d = launches.descriptor(1, Z, rows, 1, A)
     got = [tiles(k) for k in rec("linformer_project_bwd", d, Kp, "dXp", "X", "E", "X" if over else "dX", "dE") if "gemm" in k.name]
     assert got == [want] if want else len(got) == 2
+
+
+@pytest.mark.parametrize("rows,Z,A,Kp", [(16384, 64, 64, 128), (80640, 22, 128, 128)])
+def test_gradients_that_are_bound_by_memory_take_two_launches(rec, rows, Z, A, Kp):
+    kernels = names(rec("linformer_project_bwd", launches.descriptor(1, Z, rows, 1, A), Kp, "dXp", "X", "E", "dX", "dE"))
+    assert any(k.startswith("linformer_dx") for k in kernels) and not any(k.startswith("proj_gemm_pair") for k in kernels)
 
 
 # blocks of 32 keys, groups, splits
