@@ -44,6 +44,7 @@ struct BwdArgs {
   // fp32 partial sums per split: dV then dK of the dK/dV kernel with a split query walk,
   // dQ of the dQ kernel with a split key walk
   float *part;
+  uint16_t *strip;  // dS^T (strip_collect_keys_kernel)
   int64_t L, c, Lq;
   int64_t qs[3], ks[3], os[3];  // element strides (batch, head, row) of Q, dQ; K, V, dK, dV; O, dO
   RowMap map;  // local query row -> global token index
@@ -98,12 +99,13 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(const uint16_t *dO,
 // WK waves share the work-group's keys, 32 each; QS groups of such waves share the query rows: group g takes
 // every QS-th stage of the walk and the groups' sums are added in LDS.
 // id of ids: the work-group's place among those of this kind; buf0, buf1: the two stage buffers.
+// STRIP: dS^T leaves as well, in the operand registers' own order.
 template <int NQ, int AH>
 struct DkdvStage {
   unsigned char Qt[NQ][AH][kTileBytes], dOs[NQ][AH][kTileBytes];
   float lse[NQ][64], d[NQ][64];
 };
-template <int NQ, bool CAUSAL, int AH, int WK, int QS>
+template <int NQ, bool CAUSAL, int AH, int WK, int QS, bool STRIP = false>
 __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &order, uint32_t id, uint32_t ids,
                                           unsigned char *buf0, unsigned char *buf1) {
   constexpr int KW = 32;       // keys per wave
@@ -151,6 +153,10 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
   }
 
   const TileLanes tl(lane);
+  // the wave's block of 32 keys in the first of its strip's tiles
+  const bool keys_here = wkey0 < a.L;
+  uint16_t *const strip =
+      STRIP ? a.strip + ((head * (a.L >> 6) + (wkey0 >> 6)) * (a.Lq >> 6)) * 4096 + ((wkey0 >> 5) & 1) * 2048 : nullptr;
 
   f32x16 dv[2 * AH], dk_[2 * AH];  // [db], transposed: rows = head dim, columns = keys
 #pragma unroll
@@ -295,6 +301,10 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
             }
             pf[qb * 2 + w2] = __builtin_bit_cast(bf16x8, w);
             sf[qb * 2 + w2] = __builtin_bit_cast(bf16x8, x);
+            if constexpr (STRIP) {
+              if (keys_here)
+                *reinterpret_cast<u32x4 *>(strip + (int64_t)(qt0 + u) * 4096 + (qb * 2 + w2) * 512 + lane * 8) = x;
+            }
           }
         };
         bf16x8 gt[2][2][2 * AH], qt2[2][2][2 * AH];  // [qb][kk & 1][db]: dO^T and Q^T fragments
@@ -340,8 +350,14 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
       }
     }
 
-    wait_vmem();
-    __syncthreads();
+    if constexpr (STRIP) {  // this stage's strip stores stay in flight: four a tile, behind the next stage's loads
+      if (keys_here && active(0) && active(NQ - 1)) wait_loads_before_stores<4 * NQ>();
+      else wait_vmem();
+      barrier_lds();
+    } else {
+      wait_vmem();
+      __syncthreads();
+    }
     i = inext; i0 = i0next;
   };
   while (i0 < i_end) {
@@ -421,6 +437,15 @@ __global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) fused_bwd_dkdv_
   // compiler knows a direct load into one cannot alias the LDS reads of the other.
   __shared__ __attribute__((aligned(16))) unsigned char buf0[QS * sizeof(DkdvStage<NQ, AH>)], buf1[sizeof(buf0)];
   dkdv_body<NQ, CAUSAL, AH, WK, QS>(a, order, blockIdx.x, gridDim.x, buf0, buf1);
+}
+
+// The backward's first kernel in the two-pass layout: the same, and dS^T as a strip of 64 x 64 tiles, key tile by key
+// tile (the layout of rsa_strip.hip with rows and keys changed over), for the pass that forms dQ.
+template <bool CAUSAL, int AH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, AH == 2 ? 1 : 2) strip_collect_keys_kernel(BwdArgs a, TileOrder order) {
+  constexpr int NQ = QS == 1 ? 2 : 1;
+  __shared__ __attribute__((aligned(16))) unsigned char buf0[QS * sizeof(DkdvStage<NQ, AH>)], buf1[sizeof(buf0)];
+  dkdv_body<NQ, CAUSAL, AH, WK, QS, true>(a, order, blockIdx.x, gridDim.x, buf0, buf1);
 }
 
 // ---------------------------------------------------------------------- dQ ---
@@ -751,7 +776,7 @@ static BwdArgs make_bwd_args(const Dims &d, const void *dO, const void *Q, const
   a.K = (const uint16_t *)K; a.V = (const uint16_t *)V;
   a.dO = (const uint16_t *)dO; a.nL = nL; a.nD = nD;
   a.dQ = (uint16_t *)dQ; a.dK = (uint16_t *)dK; a.dV = (uint16_t *)dV;
-  a.part = nullptr;
+  a.part = nullptr; a.strip = nullptr;
   a.O = nullptr; a.LSE = nullptr; a.nL_out = nullptr; a.nD_out = nullptr;
   a.L = d.L; a.c = d.c; a.Lq = d.Lq; a.map = make_row_map(d);
   a.N = d.N; a.by_Z = make_fast_div(d.Z); a.by_heads = make_fast_div((int64_t)d.B * d.Z); a.cl2 = d.scale * kLog2e; a.scale = d.scale; a.inv_scale = 1.0f / d.scale;
@@ -862,6 +887,23 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
   if (e != hipSuccess || splits == 1) return e;
   const int64_t n4 = (int64_t)d.B * d.Z * d.L * (d.A / 4);
   return qsplit_reduce(part, dV, dK, n4, splits, d.A, make_out_layout(d.ks, d.L, d.Z), st);
+}
+
+template <int AH, int WK, int QS>
+static hipError_t launch_collect_keys(const Dims &d, const BwdArgs &a, hipStream_t st) {
+  const TileOrder o = make_order(d, d.L, 32 * WK, 1, false);
+  const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d)), block(64 * WK * QS);
+  if (d.causal) hipLaunchKernelGGL((strip_collect_keys_kernel<true, AH, WK, QS>), grid, block, 0, st, a, o);
+  else hipLaunchKernelGGL((strip_collect_keys_kernel<false, AH, WK, QS>), grid, block, 0, st, a, o);
+  return hipGetLastError();
+}
+hipError_t collect_keys(const Dims &d, const void *dO, const void *Q, const void *K, const void *V, const float *nL,
+                        const float *nD, void *dK, void *dV, void *strip, int groups, hipStream_t st) {
+  BwdArgs a = make_bwd_args(d, dO, Q, K, V, nL, nD, nullptr, dK, dV);
+  a.strip = (uint16_t *)strip;
+  if (d.A == 128) return groups > 1 ? launch_collect_keys<2, 2, 2>(d, a, st) : launch_collect_keys<2, 4, 1>(d, a, st);
+  if (groups == 4) return launch_collect_keys<1, 2, 4>(d, a, st);
+  return groups == 2 ? launch_collect_keys<1, 2, 2>(d, a, st) : launch_collect_keys<1, 4, 1>(d, a, st);
 }
 
 template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>

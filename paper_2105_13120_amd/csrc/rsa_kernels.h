@@ -44,6 +44,11 @@ size_t strip_workspace_bytes(const Dims &d, int dtype, int pass, const void *con
 hipError_t strip_pass(const Dims &d, int dtype, int pass, const void *const (&in)[6], void *const (&out)[3], void *ws,
                       size_t ws_bytes, hipStream_t st);
 
+// dK and dV of a call (heads of 64 or 128, bf16) and dS^T as a strip of B Z L Lq bf16; nL, nD: see fused_bwd_preprocess;
+// groups of waves on a walk: 1, 2, or with heads of 64 also 4
+hipError_t collect_keys(const Dims &d, const void *dO, const void *Q, const void *K, const void *V, const float *nL,
+                        const float *nD, void *dK, void *dV, void *strip, int groups, hipStream_t st);
+
 // Masks that a kernel shape is chosen for (the launch rules): only these are instantiated.
 enum MaskUse { kNoMask = 1, kCausal = 2, kBothMasks = 3 };
 

@@ -9,8 +9,10 @@
 //                strip tile = exp(S - m_t) (dtype), (m_t, l_t) per row and 64 keys
 //              apply:  LSE from the pairs, O = sum_t exp(m_t - LSE) (strip tile) V
 //              (fp32, where rows are many or walks short: both in one kernel, and no strip; see f32_forward_kernel)
-//   backward   scores: P = exp(S - LSE), dS = P o (dO V^T - D), both tiles written in dtype
-//              apply:  dQ = s dS K;   collect: dV = P^T dO, dK = s dS^T Q
+//   backward   by rows  scores: P = exp(S - LSE), dS = P o (dO V^T - D), both tiles written in dtype
+//                       apply:  dQ = s dS K;   collect: dV = P^T dO, dK = s dS^T Q
+//              by keys  (bf16, where work-groups that own 128 keys fill the chip: plan_by_keys)
+//                       collect: dV and dK from P and dS in registers, dS^T written;   apply: dQ = s dS K
 //
 // In fp32 the backward's P is brought to its rows' own sums instead of relying on the LSE it is given, whose
 // rounding (2^-25 |LSE|) every probability of the row would share: the scores kernel leaves each tile's row sums,
@@ -21,10 +23,10 @@
 // accumulators and one chain per sum besides 12.5 | 12.2 | 12.1 | 5.8; the chunk-by-chunk steps of rsa_staged.hip, N4,
 // 3.9 | 3.8 | 3.5 | 3.6); Q and K of N(0, 16), scores of 60: 14.8 | 14.8 | 5.4 | 5.4 (fp32 instruction 35 | 36 | 14 | 14).
 //
-// Bytes per score: 2 es forward, 5 es backward (es: bytes of the dtype); every other operand is read
+// Bytes per score: 2 es forward, 5 es backward, by keys 2 es (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
-// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.65,
+// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.10,
 // bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32 matrix instructions 0.49, 55 to 70 % of
 // their rate; now 0.42, the strips' 1.4 GB at 3.3 to 4.2 TB/s).
 //
@@ -1120,14 +1122,15 @@ struct CollectPos {  // of a work-group of BK keys x 64 AHW columns
   int64_t head, key0;
   int a0;
   bool which;
-  __device__ __forceinline__ CollectPos(const StripArgs &a, int BK, int AHW) {
+  __device__ __forceinline__ CollectPos(const StripArgs &a, int BK, int AHW, bool dq = false) {
     uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t cblocks = (uint32_t)(a.A / (64 * AHW));
     a0 = (int)(wg % cblocks) * (64 * AHW);
     wg /= cblocks;
-    which = wg & 1;
-    wg >>= 1;
+    which = !dq && (wg & 1);
+    wg >>= dq ? 0 : 1;
     key0 = (int64_t)(wg % (uint32_t)a.kblocks) * BK;
+    if (dq && a.causal) key0 = (int64_t)(a.kblocks - 1) * BK - key0;  // (the long walks first)
     head = wg / (uint32_t)a.kblocks;
   }
   // first tile of RT rows whose last row sees the block's first key
@@ -1167,8 +1170,9 @@ __device__ __forceinline__ void collect_out(const StripArgs &a, const CollectArg
   }
 }
 
-template <int AHW, int DEPTH, int WK, int QS>
-__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
+// DQ: the strip is dS^T, rows and keys change places, and the sums are dQ.
+template <bool DQ, int AHW, int DEPTH, int WK, int QS>
+__device__ __forceinline__ void collect_body(const StripArgs &a, const CollectArgs &p) {
   typedef uint16_t T;
   typedef TileT<T> TT;
   constexpr int BK = 32 * WK, KT = (WK + 1) / 2;  // keys, and the key tiles they lie in
@@ -1177,12 +1181,17 @@ __global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WK;
   const int grp = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WK;
-  const CollectPos pos(a, BK, AHW);
-  const int nt = (int)(a.rows / 64);
-  int t0 = pos.first_tile(a, 64, nt);
+  const CollectPos pos(a, BK, AHW, DQ);
+  const int tiles = (int)(a.rows / 64);
+  int nt = tiles;
+  if (DQ && a.causal) {
+    const int64_t seen = (a.q0 + (pos.key0 + BK < a.L ? pos.key0 + BK : a.L) - 1) / 64 + 1;
+    if (seen < nt) nt = (int)seen;
+  }
+  int t0 = DQ ? 0 : pos.first_tile(a, 64, nt);
   const int64_t ktiles = a.L / 64;
   const T *Sh = static_cast<const T *>(pos.which ? p.strip[1] : p.strip[0]) +
-                strip_tile<T>(pos.head, nt, 0, ktiles, pos.key0 / 64);
+                strip_tile<T>(pos.head, tiles, 0, ktiles, pos.key0 / 64);
   const int64_t second = pos.key0 + 64 < a.L ? 4096 : 0;  // (no second key tile: refetch the first)
   const T *Yh = static_cast<const T *>(pos.which ? p.Y[1] : p.Y[0]) + pos.head * a.Lq * a.A + pos.a0;
   const StripDMA<WK> dma_s(wave, lane);
@@ -1219,7 +1228,8 @@ __global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH 
     barrier_lds();
     if (t + (DEPTH - 1) * QS < nt) load(t + (DEPTH - 1) * QS, b == 0 ? DEPTH - 1 : b - 1);
     const Stage &cur = st[grp * DEPTH + b];
-    if (keys_here && (QS == 1 || t < nt) && tile_seen(a, (int64_t)t * 64, wtile)) {
+    const int64_t tile = (int64_t)t * 64;
+    if (keys_here && (QS == 1 || t < nt) && (DQ ? tile_seen(a, wtile, tile) : tile_seen(a, tile, wtile))) {
       const unsigned char *S = cur.S[wave >> 1];
       typename TT::Frag sf[2], yf[2][2 * AHW];
       pipelined<kSlices>(
@@ -1243,6 +1253,15 @@ __global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH 
   if (!keys_here) return;
   // (the buffers are free after the last barrier; a Stage holds at least two blocks of 32 x 64)
   collect_out<T, AHW>(a, p, pos, o, wkey, reinterpret_cast<unsigned char *>(&st[wave >> 1]) + (wave & 1) * 4096, lane);
+}
+
+template <int AHW, int DEPTH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_collect_kernel(StripArgs a, CollectArgs p) {
+  collect_body<false, AHW, DEPTH, WK, QS>(a, p);
+}
+template <int AHW, int DEPTH, int WK, int QS>
+__global__ void __launch_bounds__(64 * WK * QS, QS > 1 ? 1 : (AHW == 1 && DEPTH == 2 ? 3 : 2)) strip_apply_keys_kernel(StripArgs a, CollectArgs p) {
+  collect_body<true, AHW, DEPTH, WK, QS>(a, p);
 }
 
 // fp32: 64 columns, 32 rows a step through registers; the strips' rows are scaled on their way to LDS.
@@ -1363,17 +1382,24 @@ int f32_one_pass(const Dims &d) {
 // group's buffers lie in the workspace; out: results that may not be written yet (see apart_plan), of `chunk` heads.
 // usual, one_pass: what kernels and their shapes are chosen by, the heads of a group and f32_one_pass of the call as it is
 // where its results lie beside its inputs, so that they round alike wherever they lie.
+// keys: the groups of waves of collect_keys' work-groups, or 0 for the backward by rows.
 struct StripPlan {
   int64_t heads, rows, chunk, usual;
-  int one_pass;
+  int one_pass, keys;
   size_t out[3];
-  size_t strip, strip2, stats, norm, acc_k, acc_v, total;
+  size_t terms, strip, strip2, stats, norm, acc_k, acc_v, total;
 };
 
 // Places a group's buffers from byte `off` of the workspace on (one pass: it has none).
 void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
   p.total = off;
   if (p.one_pass) return;
+  if (p.keys) {
+    p.terms = off; off += align256((size_t)p.chunk * d.Lq * 8);
+    p.strip = off; off += align256((size_t)p.heads * p.rows * d.L * 2);
+    p.total = off;
+    return;
+  }
   const size_t es = dtype == RSA_BF16 ? 2 : 4, scores = (size_t)p.heads * p.rows * d.L;
   p.strip = off; off += align256(scores * es);
   if (pass == 1) {
@@ -1399,7 +1425,7 @@ void place_group(StripPlan &p, const Dims &d, int dtype, int pass, size_t off) {
 // of every score, whichever is more.
 constexpr size_t kStripBytes = (size_t)512 << 20, kCacheBytes = (size_t)192 << 20;
 
-StripPlan strip_plan(const Dims &d, int dtype, int pass, bool strips_only = false) {
+StripPlan strip_plan_by_rows(const Dims &d, int dtype, int pass, bool strips_only = false) {
   const size_t es = dtype == RSA_BF16 ? 2 : 4, strips = pass == 1 ? 2 : 1;
   const int64_t heads = (int64_t)d.B * d.Z;
   const size_t one_rank = (size_t)heads * d.c * d.L * (4 + es) * strips;
@@ -1421,7 +1447,58 @@ StripPlan strip_plan(const Dims &d, int dtype, int pass, bool strips_only = fals
     }
   }
   p.usual = p.heads;
+  p.chunk = heads;
   place_group(p, d, dtype, pass, 0);
+  return p;
+}
+
+StripPlan strip_plan(const Dims &d, int dtype, int pass);
+StripPlan apart_plan(const Dims &d, int dtype, int pass, StripPlan p, bool whole, size_t bytes);
+
+// The bf16 backward by keys (collect_keys: dK, dV, and dS as the only strip, written once and read once) where its
+// work-groups of 128 keys fill the chip, in no more workspace than the backward by rows takes (P and dS, five passes over a
+// strip).  W: work-groups of a group of heads.  Heads of 64, us, by rows -> by keys: 18 heads of 1024 rows (W = 144) 48 -> 38, 40 of
+// 512 (160) 31.6 -> 25.4, 12 of 2048 causal (192) 70 -> 51, 50 of 576 (250) 39 -> 30, 128 of 512 (512) 69 -> 46, 128 of 2048
+// (256, eight times) 1141 -> 580; but 24 heads of 384 of 1536 rows (168) 20 -> 21, 42 of 320 causal (126) 20.1 -> 20.7, 10 of 1280
+// causal (100) 36 -> 47.  Heads of 128: 30 heads of 896 causal (210) 63 -> 59, 64 of 1024 (512) 189 -> 130; but 30 of 768 causal
+// (180) 51 -> 52.
+bool plan_by_keys(const Dims &d, StripPlan &p) {
+  if (d.A > 128) return false;
+  const int64_t heads = (int64_t)d.B * d.Z, blocks = (d.L + 127) / 128;
+  StripPlan k = p;
+  k.rows = d.Lq; k.keys = 1;
+  const size_t strip = (size_t)d.Lq * d.L * 2, terms = align256((size_t)heads * d.Lq * 8);
+  if (p.total < terms + align256(strip)) return false;
+  const int64_t most = (int64_t)((p.total - terms - 255) / strip);
+  if (most < 1) return false;
+  k.heads = heads;
+  if (most < heads) {  // groups whose work-groups come in whole rounds of one to a CU; a group's launches cost a fifth of one
+    float least = 1e30f;
+    for (int64_t g = most; g > most / 2; g -= 1 + most / 64) {
+      const int64_t n = (heads + g - 1) / g, last = heads - (n - 1) * g;
+      auto rounds = [&](int64_t h) {  // (causal walks of several rounds even out)
+        const float r = (float)(h * blocks) / 256;
+        return d.causal ? fmaxf(r, 1.f) : ceilf(r);
+      };
+      const float cost = (float)(n - 1) * rounds(g) + rounds(last) + 0.2f * (float)n;
+      if (cost < least) { least = cost; k.heads = g; }
+    }
+  }
+  const int64_t W = k.heads * blocks;
+  if (d.A == 128 ? W < 200 : W < 240 && (W < 128 || d.Lq < 512)) return false;
+  // groups of waves on the walks of uneven length (causal, heads of 64: 12 heads of 2048, W = 192: one 63, two 56, four 51;
+  // 72 of 512, 288: 33.7, 31.2, 40.6; 52 of 1024, 416: 54.8, 53.2; 42 of 1344, 462: 67.4, 67.7; of 128: 21 of 1536, 252: 90, 82.5)
+  if (d.causal) k.keys = d.A == 128 ? (W <= 256 ? 2 : 1) : (W <= 200 ? 4 : (W <= 360 ? 2 : 1));
+  k.usual = k.heads;
+  place_group(k, d, RSA_BF16, 1, 0);
+  const size_t apart = apart_plan(d, RSA_BF16, 1, p, false, 0).total;
+  if (apart_plan(d, RSA_BF16, 1, k, false, 0).total > (apart > p.total ? apart : p.total)) return false;
+  p = k;
+  return true;
+}
+StripPlan strip_plan(const Dims &d, int dtype, int pass) {
+  StripPlan p = strip_plan_by_rows(d, dtype, pass);
+  if (dtype == RSA_BF16 && pass == 1) plan_by_keys(d, p);
   return p;
 }
 
@@ -1437,12 +1514,11 @@ struct HeadBytes {
 
 // The plan for results that lie over inputs: they stay in the workspace until these have been read, and are copied
 // then.  Where each lies tensor over tensor, head over head, that is a group's results at a time; else (whole) those of
-// all heads.  The groups take what is left of a workspace of `bytes`; 0: the least plan, one head's 128 rows at a time or,
-// in one pass, heads whose work-groups fill the chip twice.
-StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
+// all heads.  The groups take what is left of a workspace of `bytes`; 0: the least plan, one head's 128 rows at a time,
+// by keys all of a head's rows, or, in one pass, heads whose work-groups fill the chip twice.  p: the call's plan beside its inputs.
+StripPlan apart_plan(const Dims &d, int dtype, int pass, StripPlan p, bool whole, size_t bytes) {
   const HeadBytes hb(d, dtype, pass);
   const int64_t all = (int64_t)d.B * d.Z;
-  StripPlan p = strip_plan(d, dtype, pass);
   auto place = [&](int64_t heads, int64_t rows) {
     p.heads = heads; p.rows = rows; p.chunk = whole ? all : heads;
     size_t off = 0;
@@ -1452,12 +1528,15 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t byte
   };
   for (int64_t h = p.usual; bytes > 0 && h > 0; h = h * 7 / 8)
     if (place(h, d.Lq)) return p;
-  for (int64_t r = d.Lq / 128 * 128; bytes > 0 && r > 128; r = r * 7 / 8 / 128 * 128)
+  for (int64_t r = d.Lq / 128 * 128; !p.keys && bytes > 0 && r > 128; r = r * 7 / 8 / 128 * 128)
     if (place(1, r)) return p;
   const int64_t fill = (512 * 128 + d.Lq - 1) / d.Lq;
   if (p.one_pass) place(fill < all ? fill : all, d.Lq);
-  else place(1, d.Lq < 128 ? d.Lq : 128);
+  else place(1, d.Lq < 128 || p.keys ? d.Lq : 128);
   return p;
+}
+StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
+  return apart_plan(d, dtype, pass, strip_plan(d, dtype, pass), whole, bytes);
 }
 
 template <typename T>
@@ -1539,6 +1618,25 @@ hipError_t launch_collect(const StripArgs &a, const CollectArgs &p, int64_t head
   }
 }
 
+// dQ from dS^T: a.rows are the keys here, a.L the query rows.
+template <int AHW, int DEPTH, int WK, int QS>
+hipError_t launch_apply_keys_as(StripArgs a, const CollectArgs &p, int64_t heads, hipStream_t st) {
+  a.kblocks = (int)((a.L + 32 * WK - 1) / (32 * WK));
+  const dim3 grid((unsigned)(heads * a.kblocks * (a.A / (64 * AHW))));
+  hipLaunchKernelGGL((strip_apply_keys_kernel<AHW, DEPTH, WK, QS>), grid, dim3(64 * WK * QS), 0, st, a, p);
+  return hipGetLastError();
+}
+// W: the usual group's work-groups of 128 rows.  Two groups of waves share the walks of uneven length where W barely fills
+// the CUs (19 heads of 2048 causal rows, W = 304: 263 -> 232 us for the whole backward; 5 of 3840, W = 150: 579, 586); a
+// ring of three tiles beats one of two that lets three work-groups share a CU (W = 256, 512, 2048 of 2048 rows: 580, 564, 600
+// against 637, 558, 606).
+hipError_t launch_apply_keys(const StripArgs &a, const CollectArgs &p, int64_t heads, int64_t usual, hipStream_t st) {
+  if (a.A == 128) return launch_apply_keys_as<2, 2, 4, 1>(a, p, heads, st);
+  const int64_t W = usual * ((a.L + 127) / 128);
+  if (a.causal && W > 256 && W <= 360) return launch_apply_keys_as<1, 2, 2, 2>(a, p, heads, st);
+  return launch_apply_keys_as<1, 3, 4, 1>(a, p, heads, st);
+}
+
 #define RSA_TRY(expr)                       \
   do {                                      \
     hipError_t e_ = (expr);                 \
@@ -1597,11 +1695,37 @@ hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V,
   return hipSuccess;
 }
 
+// bf16: dK and dV while the scores are in registers, and of the strips dS alone, which dQ is formed from.
+hipError_t backward_by_keys(const Dims &d, const void *dO, const void *Q, const void *K, const void *V, const void *O,
+                            const float *LSE, void *dQ, void *dK, void *dV, char *ws, const StripPlan &pl, hipStream_t st) {
+  const int64_t heads = (int64_t)d.B * d.Z;
+  float *nL = reinterpret_cast<float *>(ws + pl.terms), *nD = nL + heads * d.Lq;
+  char *strip = ws + pl.strip;
+  RSA_TRY(fused_bwd_preprocess(d, dO, O, LSE, nD, nL, st));
+  for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
+    const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0, q = h0 * d.Lq * d.A, k = h0 * d.L * d.A;
+    auto in = [](const void *p, int64_t n) { return static_cast<const uint16_t *>(p) + n; };
+    auto out = [](void *p, int64_t n) { return static_cast<uint16_t *>(p) + n; };
+    Dims dg = d;  // (the tensors are dense)
+    dg.B = 1; dg.Z = (int)nh;
+    RSA_TRY(collect_keys(dg, in(dO, q), in(Q, q), in(K, k), in(V, k), nL + h0 * d.Lq, nD + h0 * d.Lq, out(dK, k), out(dV, k),
+                         strip, pl.keys, st));
+    StripArgs a = group_args<uint16_t>(d, pl, ws, h0, 0, d.Lq, Q, K, V);
+    a.rows = d.L; a.L = d.Lq; a.Lq = d.L;  // (keys for rows: collect_body)
+    CollectArgs c{};
+    c.strip[0] = strip; c.Y[0] = in(K, k); c.out[0] = out(dQ, q); c.alpha[0] = d.scale;
+    RSA_TRY(launch_apply_keys(a, c, nh, pl.usual, st));
+  }
+  return hipSuccess;
+}
+
 template <typename T>
 hipError_t backward_t(const Dims &d, const void *dO, const void *Q, const void *K, const void *V,
                       const void *O, const float *LSE, void *dQ, void *dK, void *dV, char *ws, const StripPlan &pl,
                       hipStream_t st) {
   const int64_t heads = (int64_t)d.B * d.Z;
+  if constexpr (sizeof(T) == 2)
+    if (pl.keys) return backward_by_keys(d, dO, Q, K, V, O, LSE, dQ, dK, dV, ws, pl, st);
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;
     for (int64_t r0 = 0; r0 < d.Lq; r0 += pl.rows) {
@@ -1706,7 +1830,7 @@ size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) {
   size_t usual = pl.total;
   const size_t apart = apart_plan(d, dtype, pass, false, 0).total;
   if (pl.one_pass) {  // (room for all results, so that O may lie over K or V in any way, but no more than strips would take)
-    const size_t results = apart_plan(d, dtype, pass, true, 0).total, strips = strip_plan(d, dtype, pass, true).total;
+    const size_t results = apart_plan(d, dtype, pass, true, 0).total, strips = strip_plan_by_rows(d, dtype, pass, true).total;
     usual = results < strips ? results : strips;
   }
   return usual > apart ? usual : apart;

@@ -6,6 +6,7 @@ import test_gpu_backward_one_grid as one_grid
 import test_gpu_gradients_one_grid as gradients
 import test_gpu_projected_keys_backward as projected
 import test_gpu_staged as staged
+import test_gpu_staged_by_keys as by_keys
 import test_gpu_staged_groups as groups
 from paper_2105_13120_amd import rsa
 
@@ -74,6 +75,18 @@ def test_two_pass_long_walks_in_one_pass(rec, case):
     B, Z, L, N, causal, on_a_walk = case
     d = launches.descriptor(B, Z, L, N, causal=causal, dtype=rsa.RSA_F32, mode=rsa.MODE_STAGED)
     assert names(launches.forward(rec, d)) == [f"f32_forward_kernel<{4 // on_a_walk}, {on_a_walk}>"]
+
+
+# groups of waves of the kernel that walks the rows, and groups of heads
+@pytest.mark.parametrize("case,on_a_walk,of_heads", zip(by_keys.CASES, [1, 1, 1, 1, 2, 4, 2, 1, 2, 1, 1, 2, 1], [1] * 10 + [3, 3, 3]))
+def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
+    B, Z, L, N, A, rb, re, causal = case
+    d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, mode=rsa.MODE_STAGED)
+    first, *rest = names(launches.backward(rec, d))
+    assert first == "bwd_preprocess_kernel" and len(rest) == 2 * of_heads
+    shape = {1: "4, 1", 2: "2, 2", 4: "2, 4"}[on_a_walk]
+    assert set(rest[::2]) == {f"strip_collect_keys_kernel<{str(causal).lower()}, {A // 64}, {shape}>"}
+    assert all(n.startswith("strip_apply_keys") for n in rest[1::2])
 
 
 def tiles(launch):
