@@ -207,13 +207,6 @@ __device__ __forceinline__ void longest_first(uint32_t id, const FastDiv &heads,
   rank = heads(id);
   head = id - rank * heads.d;
 }
-// Row tile of place `rank`: later rows see more keys.  Under zig-zag ownership (half: tiles per half-chunk, when they
-// divide it, else 0) the later half-chunks of the ranks come in rank order, then the earlier ones in reverse.
-__device__ __forceinline__ uint32_t row_tile_of_rank(uint32_t rank, uint32_t tiles, uint32_t half) {
-  if (half == 0) return tiles - 1 - rank;
-  const uint32_t n = tiles / (2 * half), g = rank / half, w = half - 1 - rank % half;
-  return g < n ? g * 2 * half + half + w : (2 * n - 1 - g) * 2 * half + w;
-}
 // Ends the life of everything a uniform value was computed from (scalar registers are scarce in these kernels).
 __device__ __forceinline__ uint32_t settled(uint32_t x) {
   x = __builtin_amdgcn_readfirstlane(x);
@@ -273,12 +266,34 @@ struct RowMap {
   FastDiv by_c, by_h;
   int rb, last_half;  // first simulated rank; 2N - 1
   int zigzag;
+  int first, q1, last_row;  // see row_at: rows of the first run, first token of the second; zig-zag: Lq - h
   // (rows and tokens are below 2^31: one head's K and V of that many would not fit the memory)
   __host__ __device__ int64_t operator()(int64_t r) const {
     if (!zigzag) return q0 + r;
     const uint32_t q = by_c((uint32_t)r);
     const int64_t rho = rb + (int64_t)q, w = r - (int64_t)q * c;
     return w < h ? rho * h + w : (last_half - rho) * h + (w - h);
+  }
+  // The rows in the order of their tokens, which the causal kernels take them in: the v-th row's token, its place in the
+  // tensors, the rank that owns it.  Under zig-zag ownership the simulated ranks' earlier half-chunks are one run of
+  // tokens and their later ones, in reverse, a second; 64 rows from a multiple of 64 on are rows of one half-chunk.
+  // (Tiles cut from the rows as they lie straddle a rank's two half-chunks, one of few keys and one of many, and have no
+  // order by length where h is no multiple of them.  Forward and backward, us: 36 heads of 7680 rows, h = 320, 1453 -> 1232;
+  // 70 of 1536, h = 64, 176 -> 141; 70 of 384, h = 64, 28.8 -> 26.8.)
+  __host__ __device__ int token_at(int v) const { return v < first ? (int)q0 + v : q1 + (v - first); }
+  __host__ __device__ int64_t row_at(int v) const {
+    if (!zigzag) return v;
+    const int u = v < first ? v : v - first, hc = (int)by_h((uint32_t)u), w = u - hc * (int)h;
+    return v < first ? (int64_t)hc * c + w : (int64_t)last_row - (int64_t)hc * c + w;
+  }
+  __host__ __device__ int rank_at(int v) const {
+    if (!zigzag) return rb + (int)by_c((uint32_t)v);
+    return v < first ? rb + (int)by_h((uint32_t)v) : last_half - (int)by_h((uint32_t)token_at(v));
+  }
+  // the first v of a token at or after g
+  __host__ __device__ int from_token(int g) const {
+    if (g < (int)q0 + first) return g > (int)q0 ? g - (int)q0 : 0;
+    return zigzag && g > q1 ? first + (g - q1) : first;
   }
   // first key of the rows [w, ...) of the chunk (pair of half-chunks) that rank j owns
   __host__ __device__ int64_t key_of(int j, int64_t w) const {
@@ -297,6 +312,10 @@ inline RowMap make_row_map(const Dims &d) {
   m.q0 = (int64_t)d.rank_begin * d.c; m.c = d.c; m.h = d.c / 2;
   m.by_c = make_fast_div(d.c); m.by_h = make_fast_div(m.h > 0 ? m.h : 1);
   m.rb = d.rank_begin; m.last_half = 2 * d.N - 1; m.zigzag = d.zigzag;
+  const int64_t rows = (int64_t)(d.rank_end - d.rank_begin) * d.c;
+  m.first = d.zigzag ? (int)(rows / 2) : 0x7fffffff - (int)m.q0; m.q1 = d.zigzag ? (int)((2 * d.N - d.rank_end) * m.h) : 0;
+  m.last_row = (int)(rows - m.h);
+  if (d.zigzag) m.q0 = (int64_t)d.rank_begin * m.h;
   return m;
 }
 

@@ -29,8 +29,8 @@ namespace rsa {
 
 // Which tile of which head the work-groups of a kernel take.
 struct TileOrder {
-  FastDiv by_tiles;           // tiles of a head
-  int by_length, half_tiles;  // causal: order of the tiles over the work-groups (longest_first)
+  FastDiv by_tiles;  // tiles of a head
+  int by_length;     // causal: order of the tiles over the work-groups (longest_first)
 };
 struct BwdArgs {
   const uint16_t *Q, *K, *V, *dO;
@@ -164,11 +164,14 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
 #pragma unroll
     for (int v = 0; v < 16; ++v) { dv[db][v] = 0.f; dk_[db][v] = 0.f; }
 
-  // Stages of NQ query tiles in ring order: start at the rank that owns key0.
+  // Stages of NQ query tiles in ring order: start at the rank that owns key0.  Under the causal mask the rows are taken in
+  // the order of their tokens (see RowMap), from the first that sees key0 on.
   const int nqt = (int)(a.Lq >> 6);
   const int nst = (nqt + NQ - 1) / NQ;
   int start = 0;
-  {
+  if (CAUSAL) {
+    start = a.map.from_token(key0) / (64 * NQ);
+  } else {
     const int r = (a.map.owner(key0) - a.map.rb) * (int)a.c;  // local row of that rank's first query
     if (r >= 0 && r < a.Lq) start = r / (64 * NQ);
   }
@@ -181,30 +184,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
     i_begin = (int)blockIdx.y * per_split;
     i_end = i_begin + per_split < nst ? i_begin + per_split : nst;
   }
-  // A stage matters if some row of it can see the first key of the work-group.  Under the causal mask with rows in token
-  // order these are the stages from that key's row on (none in front of `start`), else (zig-zag) each is asked.
-  const bool ask = CAUSAL && a.map.zigzag;
-  if (CAUSAL && !ask) {
-    const int d = key0 - (int)a.map.q0, first = d > 0 ? d / (64 * NQ) - start : 0;
-    if (first > i_begin) i_begin = first;
-    if (nst - start < i_end) i_end = nst - start;
-  }
-  auto visible = [&](int i) {
-    const int qt = st_of(i) * NQ;
-    bool v = false;
-#pragma unroll
-    for (int u = 0; u < NQ; ++u)
-      v = v || (qt + u < nqt && (int)a.map((qt + u) * 64) + 63 >= key0);
-    return v;
-  };
-  auto skip = [&](int i, int n) {  // n stages that matter further on
-    if (!ask) return i + n;
-    for (int k = 0; k < n && i < i_end; ++k) {
-      ++i;
-      while (i < i_end && !visible(i)) ++i;
-    }
-    return i;
-  };
+  if (CAUSAL && nst - start < i_end) i_end = nst - start;
 
   const TileDMAT<WK> dma_q(wave, lane, (int)q_ld), dma_o(wave, lane, (int)o_ld);
   auto load_stage = [&](int i, Stage &sn) __attribute__((always_inline)) {
@@ -213,7 +193,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
     for (int u = 0; u < NQ; ++u) {
       int qt = st * NQ + u;
       if (qt >= nqt) qt = nqt - 1;  // past the last tile: refetch it (never used)
-      const int64_t r0 = (int64_t)qt * 64;
+      const int64_t r0 = CAUSAL ? a.map.row_at(qt * 64) : (int64_t)qt * 64;
 #pragma unroll
       for (int ah = 0; ah < AH; ++ah) {
         dma_q.load(Qh + r0 * q_ld + ah * 64, sn.Qt[u][ah]);
@@ -228,14 +208,13 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
   };
 
   int i0 = i_begin;  // position of the walk: group 0's stage
-  if (ask && i0 < i_end && !visible(i0)) i0 = skip(i0, 1);
-  int i = QS == 1 ? i0 : skip(i0, grp);  // this group's stage
+  int i = i0 + grp;    // this group's stage
   if (i < i_end) load_stage(i, stage0[grp]);
   wait_vmem();
   __syncthreads();
   // one stage: start the loads of the next stage into sn, compute on sc
   auto stage = [&](Stage &sc, Stage &sn) __attribute__((always_inline)) {
-    const int i0next = skip(i0, QS), inext = QS == 1 ? i0next : skip(i, QS);
+    const int i0next = i0 + QS, inext = i + QS;
     if (inext < i_end) load_stage(inext, sn);
 
     // The 32 MFMAs of a tile go in four groups of eight -- S', dP' of rows 0..31 (G0) and of
@@ -250,7 +229,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
     const int qt0 = st_of(i) * NQ;
     auto active = [&](int u) {
       const int qt = qt0 + u;
-      return (QS == 1 || i < i_end) && qt < nqt && (!CAUSAL || (int)a.map(qt * 64) + 63 >= wkey0);
+      return (QS == 1 || i < i_end) && qt < nqt && (!CAUSAL || a.map.token_at(qt * 64) + 63 >= wkey0);
     };
     auto fetch = [&](int u, int qb) __attribute__((always_inline)) {
       // accumulators start from -LSE / scale and -D of their rows (same for all lanes of a half)
@@ -270,7 +249,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs &a, const TileOrder &ord
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       if (active(u)) {
-        const int qf = (int)a.map((qt0 + u) * 64);  // token of the tile's first row
+        const int qf = a.map.token_at((qt0 + u) * 64);  // token of the tile's first row
         const bool domask = CAUSAL && qf < wkey0 + KW - 1;
         bf16x8 pf[4], sf[4];  // [kk]: P and dS as B operands, k = query
         auto g12 = [&](int qb) __attribute__((always_inline)) {
@@ -469,27 +448,18 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
   uint32_t head_, qt_;  // (order: see the forward)
   if (CAUSAL && order.by_length) {
     longest_first(id, a.by_heads, head_, qt_);
-    qt_ = row_tile_of_rank(qt_, order.by_tiles.d, order.half_tiles);
   } else {
-    const uint32_t wg = xcd_remap(id, ids, blockIdx.y), tiles = order.by_tiles.d;
+    const uint32_t wg = xcd_remap(id, ids, blockIdx.y);
     head_ = order.by_tiles(wg);
-    qt_ = wg - head_ * tiles;
-    if (CAUSAL) qt_ = tiles - 1 - qt_;
+    qt_ = wg - head_ * order.by_tiles.d;
   }
+  if (CAUSAL) qt_ = order.by_tiles.d - 1 - qt_;
   const int64_t head = settled(head_), qt = settled(qt_);
   const int64_t row0 = qt * BM;
-  int n = a.map.rb + (int)a.map.by_c((uint32_t)row0);  // rank that owns the first row (see the forward)
+  int n = CAUSAL ? a.map.rank_at((int)row0) : a.map.rb + (int)a.map.by_c((uint32_t)row0);  // rank that owns the first row (see the forward)
   if (n >= a.N) n %= a.N;
-  // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
-  int q_last = 0;
-  if (CAUSAL) {
-#pragma unroll
-    for (int i = 0; i < (BM + 63) / 64; ++i)
-      if (row0 + i * 64 < a.Lq) {
-        const int e = (int)a.map(row0 + i * 64) + 63;
-        q_last = e > q_last ? e : q_last;
-      }
-  }
+  // last token any row of the work-group may look at
+  const int q_last = CAUSAL ? a.map.token_at((int)(row0 + BM < a.Lq ? row0 + BM : a.Lq) - 1) : 0;
 
   const int64_t kv_off = head_offset((uint32_t)head, a.by_Z, a.ks), q_off = head_offset((uint32_t)head, a.by_Z, a.qs);
   const int64_t o_off = head_offset((uint32_t)head, a.by_Z, a.os);
@@ -504,10 +474,12 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
   bf16x8 qreg[QB][4 * AH], greg[QB][4 * AH];
   int64_t qrow[QB];
   int qtok[QB];      // global token index of the lane's row
+  bool here[QB];
   f32x16 negl[QB], negd[QB];
-  // first and last token of this wave's rows (R <= 64 rows inside one tile: a run of tokens)
-  const int64_t wrow = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
-  const int wq_first = (int)a.map(wrow), wq_last = wq_first + R - 1;
+  // this wave's rows (see the forward)
+  const int64_t wblk = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
+  const int64_t wrow = CAUSAL ? a.map.row_at((int)wblk) : wblk;
+  const int wq_first = CAUSAL ? a.map.token_at((int)wblk) : 0, wq_last = wq_first + R - 1;
 
   const TileLanes tl(lane);
 
@@ -545,10 +517,11 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
   // mostly prologue).
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    const int64_t r = row0 + wave * R + qb * 32 + col;
-    qrow[qb] = r < a.Lq ? r : a.Lq - 1;
-    const int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
-    qtok[qb] = (int)a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
+    int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
+    here[qb] = blk < a.Lq;
+    if (!here[qb]) blk = a.Lq - 32;
+    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + col;
+    qtok[qb] = CAUSAL ? a.map.token_at((int)blk) + col : 0;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk) {
       qreg[qb][dk] = *reinterpret_cast<const bf16x8 *>(Qh + qrow[qb] * q_ld + dk * 16 + half * 8);
@@ -570,10 +543,10 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
       }
       dd = -xhalf_sum(acc);
       l2 = -a.LSE[head * a.Lq + qrow[qb]] * a.inv_scale;
-      if (r < a.Lq && blockIdx.y == 0 && grp == 0) {
+      if (here[qb] && blockIdx.y == 0 && grp == 0) {
         if (half == 0) {
-          a.nD_out[head * a.Lq + r] = dd;
-          a.nL_out[head * a.Lq + r] = l2;
+          a.nD_out[head * a.Lq + qrow[qb]] = dd;
+          a.nL_out[head * a.Lq + qrow[qb]] = l2;
         }
       }
     } else {
@@ -691,9 +664,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
     const int64_t heads = a.by_heads.d;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const int64_t r = row0 + wave * R + qb * 32 + col;
-      if (r < a.Lq) {
-        float *po = a.part + (((int64_t)blockIdx.y * heads + head) * a.Lq + r) * A + half * 4;
+      if (here[qb]) {
+        float *po = a.part + (((int64_t)blockIdx.y * heads + head) * a.Lq + qrow[qb]) * A + half * 4;
 #pragma unroll
         for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
@@ -709,12 +681,12 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
 
   // the wave's R x 64 block of dQ leaves through its own LDS tile as whole 128-byte rows
   unsigned char *ot = ((wave & 1) ? buf1 : buf0) + (wave >> 1) * kTileBytes;
-  const int64_t wr0 = row0 + wave * R;
+  const int64_t rows_here = a.Lq - (row0 + wave * R);
 #pragma unroll
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) stage_block_T(ot, qb * 32, dq[2 * ah][qb], dq[2 * ah + 1][qb], a.scale, lane);
-    flush_rows<R>(ot, 0, a.dQ + q_off + wr0 * q_ld + ah * 64, a.Lq - wr0, lane, (int)q_ld);
+    flush_rows<R>(ot, 0, a.dQ + q_off + wrow * q_ld + ah * 64, rows_here, lane, (int)q_ld);
   }
 }
 
@@ -803,17 +775,16 @@ hipError_t qsplit_reduce(const float *part, void *out, void *out1, int64_t n4, i
 }
 
 // the order of a kernel whose work-groups own `own` of `n` rows (or keys) of every head
-static TileOrder make_order(const Dims &d, int64_t n, int own, int splits, bool rows) {
+static TileOrder make_order(const Dims &d, int64_t n, int own, int splits) {
   TileOrder o;
   o.by_tiles = make_fast_div((n + own - 1) / own);
   o.by_length = order_by_length(d, splits, (int64_t)128 << 20);
-  o.half_tiles = rows && d.zigzag && d.c / 2 % own == 0 ? (int)(d.c / 2 / own) : 0;
   return o;
 }
 
 template <int NQ, int AH, int WK, int QS, int MASKS = kBothMasks>
 static hipError_t launch_dkdv(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
-  const TileOrder o = make_order(d, d.L, 32 * WK, splits, false);
+  const TileOrder o = make_order(d, d.L, 32 * WK, splits);
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d), (unsigned)splits), block(64 * WK * QS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
@@ -891,7 +862,7 @@ hipError_t fused_bwd_dkdv(const Dims &d, const void *dO, const void *Q, const vo
 
 template <int AH, int WK, int QS>
 static hipError_t launch_collect_keys(const Dims &d, const BwdArgs &a, hipStream_t st) {
-  const TileOrder o = make_order(d, d.L, 32 * WK, 1, false);
+  const TileOrder o = make_order(d, d.L, 32 * WK, 1);
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d)), block(64 * WK * QS);
   if (d.causal) hipLaunchKernelGGL((strip_collect_keys_kernel<true, AH, WK, QS>), grid, block, 0, st, a, o);
   else hipLaunchKernelGGL((strip_collect_keys_kernel<false, AH, WK, QS>), grid, block, 0, st, a, o);
@@ -908,7 +879,7 @@ hipError_t collect_keys(const Dims &d, const void *dO, const void *Q, const void
 
 template <bool PRE, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_dq_as(const Dims &d, const BwdArgs &a, int splits, hipStream_t st) {
-  const TileOrder o = make_order(d, d.Lq, 32 * RW, splits, true);
+  const TileOrder o = make_order(d, d.Lq, 32 * RW, splits);
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * o.by_tiles.d), (unsigned)splits), block(64 * RW * KS);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
@@ -970,8 +941,8 @@ template <int AH, int NQ, int WK, int QS, int NK, int RW, int KS>
 static hipError_t launch_both(const Dims &d, const BwdArgs &a, hipStream_t st) {
   BothArgs b;
   b.a = a;
-  b.kv = make_order(d, d.L, 32 * WK, 1, false);
-  b.q = make_order(d, d.Lq, 32 * RW, 1, true);
+  b.kv = make_order(d, d.L, 32 * WK, 1);
+  b.q = make_order(d, d.Lq, 32 * RW, 1);
   const int64_t heads = (int64_t)d.B * d.Z;
   b.kv_wgs = (uint32_t)(heads * b.kv.by_tiles.d);
   b.q_wgs = (uint32_t)(heads * b.q.by_tiles.d);

@@ -32,7 +32,7 @@ struct FwdArgs {
   RowMap map;            // local query row -> global token index
   int N;
   FastDiv by_tiles, by_heads, by_Z;  // row tiles of a head, heads, Z
-  int by_length, half_tiles;  // causal: order of the row tiles over the work-groups (longest_first)
+  int by_length;         // causal: order of the row tiles over the work-groups (longest_first)
   float cl2;             // scale * log2(e)
   // split key walk (gridDim.y > 1): per split, head and row the unnormalised fp32 O and the pair
   // (stale max * cl2, row sum) it is relative to
@@ -63,29 +63,20 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   uint32_t head_, qt_;
   if (CAUSAL && a.by_length) {
     longest_first(blockIdx.x, a.by_heads, head_, qt_);
-    qt_ = row_tile_of_rank(qt_, a.by_tiles.d, a.half_tiles);
   } else {
-    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y), tiles = a.by_tiles.d;
+    const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x, blockIdx.y);
     head_ = a.by_tiles(wg);
-    qt_ = wg - head_ * tiles;
-    if (CAUSAL) qt_ = tiles - 1 - qt_;
+    qt_ = wg - head_ * a.by_tiles.d;
   }
+  if (CAUSAL) qt_ = a.by_tiles.d - 1 - qt_;  // later rows see more keys
   const int64_t head = settled(head_), qt = settled(qt_);
-  const int64_t row0 = qt * BM;  // first local row of this work-group
+  const int64_t row0 = qt * BM;  // first row of this work-group (causal: in the order of their tokens, see RowMap)
   // rank that owns the first row (modulo N: with projected keys, Table 3, the rows are not
   // tokens of the key sequence and any chunk may come first)
-  int n = a.map.rb + (int)a.map.by_c((uint32_t)row0);
+  int n = CAUSAL ? a.map.rank_at((int)row0) : a.map.rb + (int)a.map.by_c((uint32_t)row0);
   if (n >= a.N) n %= a.N;
-  // last token any row of the work-group may look at (its 64-row tiles are runs of tokens)
-  int q_last = 0;
-  if (CAUSAL) {
-#pragma unroll
-    for (int i = 0; i < (BM + 63) / 64; ++i)
-      if (row0 + i * 64 < a.Lq) {
-        const int e = (int)a.map(row0 + i * 64) + 63;
-        q_last = e > q_last ? e : q_last;
-      }
-  }
+  // last token any row of the work-group may look at
+  const int q_last = CAUSAL ? a.map.token_at((int)(row0 + BM < a.Lq ? row0 + BM : a.Lq) - 1) : 0;
 
   const int64_t kv_off = head_offset((uint32_t)head, a.by_Z, a.ks);
   const uint16_t *Qh = a.Q + head_offset((uint32_t)head, a.by_Z, a.qs);
@@ -95,21 +86,24 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 
   // Q^T operand: lane (col, half) holds Q[row][dk*16 + half*8 .. +8]
   bf16x8 qreg[QB][4 * AH];
-  int64_t qrow[QB];  // local row (clamped to the last row for a ragged tail)
+  int64_t qrow[QB];  // the lane's row (of a ragged tail that is not there: some other)
   int qtok[QB];  // its global token index
+  bool here[QB];     // (a block of 32 rows is whole or absent)
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    int64_t r = row0 + wave * R + qb * 32 + col;
-    qrow[qb] = r < a.Lq ? r : a.Lq - 1;
-    const int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
-    qtok[qb] = (int)a.map(blk < a.Lq ? blk : a.Lq - 32) + col;
+    int64_t blk = row0 + wave * R + qb * 32;
+    here[qb] = blk < a.Lq;
+    if (!here[qb]) blk = a.Lq - 32;
+    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + col;
+    qtok[qb] = CAUSAL ? a.map.token_at((int)blk) + col : 0;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk)
       qreg[qb][dk] = *reinterpret_cast<const bf16x8 *>(Qh + qrow[qb] * q_ld + dk * 16 + half * 8);
   }
-  // first and last token of this wave's rows (R <= 64 rows inside one tile: a run of tokens)
-  const int64_t wrow = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
-  const int wq_first = (int)a.map(wrow), wq_last = wq_first + R - 1;
+  // this wave's rows, R of them in a run of tokens: the first one's place in the tensors, first and last token
+  const int64_t wblk = row0 + wave * R < a.Lq ? row0 + wave * R : a.Lq - R;
+  const int64_t wrow = CAUSAL ? a.map.row_at((int)wblk) : wblk;
+  const int wq_first = CAUSAL ? a.map.token_at((int)wblk) : 0, wq_last = wq_first + R - 1;
 
   const TileLanes tl(lane);
 
@@ -340,9 +334,8 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const float lt = xhalf_sum(l[qb]);
-      const int64_t r = row0 + wave * R + qb * 32 + col;
-      if (r < a.Lq) {
-        const int64_t pr = ((int64_t)blockIdx.y * heads + head) * a.Lq + r;
+      if (here[qb]) {
+        const int64_t pr = ((int64_t)blockIdx.y * heads + head) * a.Lq + qrow[qb];
         float *po = a.part_o + pr * A + half * 4;
 #pragma unroll
         for (int db = 0; db < 2 * AH; ++db)
@@ -369,15 +362,14 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   for (int qb = 0; qb < QB; ++qb) {
     const float lt = xhalf_sum(l[qb]);
     inv[qb] = 1.0f / lt;
-    const int64_t r = row0 + wave * R + qb * 32 + col;
-    if (r < a.Lq && half == 0) a.LSE[head * a.Lq + r] = (mc[qb] + __builtin_amdgcn_logf(lt)) * kLn2;
+    if (here[qb] && half == 0) a.LSE[head * a.Lq + qrow[qb]] = (mc[qb] + __builtin_amdgcn_logf(lt)) * kLn2;
   }
-  const int64_t wr0 = row0 + wave * R;
+  const int64_t rows_here = a.Lq - (row0 + wave * R);
 #pragma unroll
   for (int ah = 0; ah < AH; ++ah) {  // one half of the head at a time through the wave's tile
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) stage_block_T(ot, qb * 32, o[2 * ah][qb], o[2 * ah + 1][qb], inv[qb], lane);
-    flush_rows<R>(ot, 0, a.O + head_offset((uint32_t)head, a.by_Z, a.os) + wr0 * o_ld + ah * 64, a.Lq - wr0, lane, (int)o_ld);
+    flush_rows<R>(ot, 0, a.O + head_offset((uint32_t)head, a.by_Z, a.os) + wrow * o_ld + ah * 64, rows_here, lane, (int)o_ld);
   }
 }
 
@@ -415,7 +407,6 @@ template <int R, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
   a.by_tiles = make_fast_div((d.Lq + RW * R - 1) / (RW * R));
   a.by_length = order_by_length(d, splits, (int64_t)400 << 20);
-  a.half_tiles = d.zigzag && d.c / 2 % (RW * R) == 0 ? (int)(d.c / 2 / (RW * R)) : 0;
   dim3 grid((unsigned)(heads * a.by_tiles.d), (unsigned)splits);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)

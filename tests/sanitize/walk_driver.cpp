@@ -35,6 +35,24 @@ static int check_walk(const rsa::RowMap &m, int n, int N, int lg, int q_last, in
   return 0;
 }
 
+// The rows in the order of their tokens: each once, 64 at a time in one run, as RowMap says whose token and rank they are.
+static int check_row_order(const rsa::RowMap &m, const rsa::Dims &d) {
+  const int rows = (d.rank_end - d.rank_begin) * (int)d.c;
+  std::vector<char> seen((size_t)rows, 0);
+  int last = -1;
+  for (int v = 0; v < rows; ++v) {
+    const int64_t r = m.row_at(v);
+    if (r < 0 || r >= rows || seen[(size_t)r] || (v % 64 && r != m.row_at(v - 1) + 1)) return 1;
+    seen[(size_t)r] = 1;
+    const int g = m.token_at(v);
+    if (g != (int)m(r) || g <= last || m.rank_at(v) != m.owner(g) || m.rank_at(v) != d.rank_begin + (int)(r / d.c)) return 1;
+    for (int key = last + 1; key <= g; ++key)
+      if (m.from_token(key) != v) return 1;
+    last = g;
+  }
+  return m.from_token(last + 1) < rows;
+}
+
 int main() {
   int bad = 0;
   for (int it = 0; it < 20000 && !bad; ++it) {
@@ -48,6 +66,7 @@ int main() {
     const int64_t run = d.zigzag ? d.c / 2 : d.c;
     const int lg = run % 128 == 0 ? pick(6, 7) : 6, n = pick(0, d.N - 1), splits = pick(0, 1) ? 1 : pick(1, 6);
     const int q_last = pick(0, (int)d.L - 1), split = pick(0, splits - 1), groups = 1 << pick(0, 2);
+    if (it < 2000) bad |= check_row_order(m, d);
     bad |= check_walk<true>(m, n, d.N, lg, q_last, splits, split, groups);
     bad |= check_walk<false>(m, n, d.N, lg, q_last, splits, split, groups);
     if (bad) std::fprintf(stderr, "walk %d failed\n", it);

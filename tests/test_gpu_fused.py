@@ -199,6 +199,19 @@ def test_zigzag_ownership(B, Z, L, N, rb, re, causal):
     compare_heads(cfg, x, out, list(range(B * Z)))
 
 
+@pytest.mark.parametrize("A", [64, 128])
+@pytest.mark.parametrize("B,Z,L,N,rb,re", [
+    (1, 2, 1920, 5, 1, 4),      # h of three tiles: work-groups' rows from the ends of two ranks' half-chunks, a gap of tokens
+    (5, 13, 1920, 5, 0, 5),     # one group of waves
+    (2, 9, 4480, 7, 2, 6),      # longer walks, groups of waves
+])
+def test_zigzag_rows_by_token(A, B, Z, L, N, rb, re):
+    """Half-chunks of an odd number of 64-row tiles: work-groups take rows in the order of their tokens, across ranks."""
+    cfg = cfg_of(B, Z, L, N, True, rb=rb, re=re, seed=19, zigzag=True, A=A)
+    x = inputs.make_inputs(cfg)
+    compare_heads(cfg, x, gpu_forward_backward(cfg, x), [0, B * Z - 1])
+
+
 def test_zigzag_whole_ring_is_a_row_permutation_of_the_contiguous_ring():
     """Ownership only decides which rank holds a row: over the whole ring the outputs are
     those of the contiguous layout, rows permuted (different summation order: tolerance)."""

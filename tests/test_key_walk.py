@@ -1,5 +1,5 @@
 """The scalar arithmetic of the fused kernels' walks (KeyWalk, FastDiv of rsa_common.h), on the host: every order of
-ranks, both ownerships, splits and groups against the stages written out one by one."""
+ranks, both ownerships, splits and groups against the stages written out one by one; the rows in the order of their tokens."""
 import os
 
 from test_sanitizers import ROOT, SAN, run
