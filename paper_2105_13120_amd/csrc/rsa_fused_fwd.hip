@@ -472,14 +472,17 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // 112) and less where they are shorter (512 rows, 1024: 25.6 -> 26.7, 256 rows: 17.3 -> 20.5).  Causal walks end one by one
 // and fill places left over: large ones only for long walks on a full chip (8192 rows, 2048: 306 -> 299, 4096 rows: 160 -> 156;
 // but 1888: 156 -> 166, 2048 rows, 3072: 129 -> 140, 1024 rows, 2048: 50.6 -> 53.6).
+// Rows that are no multiple of 256 leave part of a head's last work-group idle: the rounds of the whole ring count that (4160
+// rows, W = 1815: 290 -> 276, 3366: 510 -> 483; 2496 rows, 1820: 178 -> 169), one rank's share takes large ones only where 128
+// would leave as much (1472 rows of 2944, 2424: 265 -> 250; but 832 of 6656, 1484: 372 -> 439, 2368 of 4736 causal, 3325: 164 -> 186).
 void fused_fwd_plan(const Dims &d, bool *big, int *splits) {
-  if (d.A == 64 && d.Lq % 256 == 0) {
+  if (d.A == 64) {
     const int s = key_splits_for(d, 256);
-    const int64_t wgs = (int64_t)d.B * d.Z * (d.Lq / 256), W = 2 * wgs;
-    bool large = wgs * s >= 512;
+    const int64_t heads = (int64_t)d.B * d.Z, wgs = heads * ((d.Lq + 255) / 256), W = heads * ((d.Lq + 127) / 128);
+    bool large = wgs * s >= 512 && (d.Lq % 256 == 0 || (s == 1 && 2 * wgs == W));
     if (s == 1 && d.Lq == d.L) {
       if (d.causal) large = W >= 2000 && d.L >= 4096;
-      else large = W >= 512 && d.L > 512 && (double)((W + 511) / 512) * 2 < (double)((W + 255) / 256) * 1.055;
+      else large = W >= 512 && d.L > 512 && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
     }
     if (large) {
       *big = true; *splits = s;

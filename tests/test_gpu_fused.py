@@ -199,6 +199,21 @@ def test_zigzag_ownership(B, Z, L, N, rb, re, causal):
     compare_heads(cfg, x, out, list(range(B * Z)))
 
 
+@pytest.mark.parametrize("B,Z,L,N,rb,re,causal", [
+    (1, 73, 1600, 5, 0, 5, False),     # the last work-group of a head holds 64 rows,
+    (6, 17, 1152, 3, 0, 3, False),     # 128,
+    (25, 8, 1472, 1, 0, 1, False),     # 192
+    (8, 38, 896, 2, 1, 2, False),      # one rank's 448
+    (5, 12, 4416, 3, 0, 3, True),      # causal
+])
+def test_forward_ragged_256_row_tiles(B, Z, L, N, rb, re, causal):
+    """Work-groups of 256 rows whose last one of a head is in part not there."""
+    cfg = cfg_of(B, Z, L, N, causal, rb=rb, re=re, seed=23)
+    x = inputs.make_inputs(cfg)
+    out = gpu_forward_backward(cfg, x, backward=False)
+    compare_heads(cfg, x, out, [0, B * Z - 1], backward=False)
+
+
 @pytest.mark.parametrize("A", [64, 128])
 @pytest.mark.parametrize("B,Z,L,N,rb,re", [
     (1, 2, 1920, 5, 1, 4),      # h of three tiles: work-groups' rows from the ends of two ranks' half-chunks, a gap of tokens
