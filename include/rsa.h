@@ -104,9 +104,9 @@ const char *rsa_strerror(int status);
 /* Bytes of device workspace rsa_forward (pass 0) or rsa_backward (pass 1)
  * needs for this descriptor; 0 if the descriptor is invalid.  Staged mode: the score
  * strips of as many ranks and heads together as fit 512 MB (a few heads at a time,
- * 192 MB, or at least one rank's rows, where not all fit); the fp32 forward of heads of
- * 64 with many rows or short ones has no strip, only room for its results, should they
- * have to wait (at most what strips would take).  A caller with less memory calls for
+ * 192 MB, or at least one rank's rows, where not all fit); the forward of many rows (heads
+ * of 64, in fp32 also short rows; in bf16 also heads of 128) has no strip, only room for its
+ * results, should they have to wait (at most what strips would take).  A caller with less memory calls for
  * fewer ranks at a time and adds up the partial dK, dV. */
 size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
 

@@ -42,7 +42,11 @@ struct FwdArgs {
 // NK: key tiles per stage (one barrier per stage).  RW waves share the work-group's rows, R each; KS groups of
 // such waves share its keys: group g takes every KS-th stage of the walk and the groups' results are merged in
 // LDS.
-template <int R, bool CAUSAL, int AH, int NK, int RW, int KS>
+// OWN (the two-pass layout, whose strip held them so): a tile's probabilities are rounded to bf16 against the tile's own
+// maximum per row, its product with V is formed by itself and weighted, and sums are short and compensated.  The largest of
+// a tile are then exact: RMS error of O against fp64, N(0, 1) inputs, 1e-3: 2.10 (576 rows), 1.99 (4096, causal), as the
+// strip; 2.32, 2.12 against a common reference.  It costs a multiply-add per two scores (B8 Z16 L2048: 154 -> 158 us).
+template <int R, bool CAUSAL, int AH, int NK, int RW, int KS, bool OWN>
 __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) ? 4 : 2) fused_fwd_kernel(FwdArgs a) {
   constexpr int QB = R / 32;
   constexpr int BM = RW * R;
@@ -106,12 +110,20 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   const int wq_first = CAUSAL ? a.map.token_at((int)wblk) : 0, wq_last = wq_first + R - 1;
 
   const TileLanes tl(lane);
+  // A maximum as exponents are taken against it.  (OWN: the same rounded number in probabilities, weights and the LSE, and
+  // not a product that the compiler contracts with the sum that it stands in: at scores of 60 the LSE erred twice as much.)
+  auto ref_of = [&](float x) __attribute__((always_inline)) {
+    float y = x * a.cl2;
+    if constexpr (OWN) asm("" : "+v"(y));
+    return y;
+  };
 
   f32x16 o[2 * AH][QB];
-  float m[QB], mc[QB], l[QB];
+  float m[QB], mc[QB], l[QB], l_err[OWN ? QB : 1];  // l_err: what the sum over tiles lost to rounding
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     m[qb] = -INFINITY; mc[qb] = 0.f; l[qb] = 0.f;
+    if (OWN) l_err[OWN ? qb : 0] = 0.f;
 #pragma unroll
     for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
@@ -209,10 +221,11 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
           // a row that has seen no key yet (a split walk can start right of it) keeps mc = 0
           const float mn = fmaxf(m[qb], tm[qb]);
           const bool seen = mn > -INFINITY;
-          const float alpha = seen ? __builtin_amdgcn_exp2f((m[qb] - mn) * a.cl2) : 1.0f;
+          const float alpha = seen ? __builtin_amdgcn_exp2f(OWN ? ref_of(m[qb]) - ref_of(mn) : (m[qb] - mn) * a.cl2) : 1.0f;
           m[qb] = mn;
-          mc[qb] = seen ? mn * a.cl2 : 0.f;
+          mc[qb] = seen ? ref_of(mn) : 0.f;
           l[qb] *= alpha;
+          if (OWN) l_err[OWN ? qb : 0] *= alpha;
 #pragma unroll
           for (int db = 0; db < 2 * AH; ++db)
 #pragma unroll
@@ -221,16 +234,19 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
       }
       // ---- P^T = exp2(S^T cl2 - m cl2), packed to bf16 as the B operand
       bf16x8 pf[QB][4];
+      float wt[QB];  // OWN: the tile's weight
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
-        float ls = 0.f;
+        float l4[OWN ? 4 : 1] = {};
+        const float own = ref_of(tm[qb]), mt = !OWN ? mc[qb] : own > -INFINITY ? own : 0.f;
+        wt[qb] = OWN ? __builtin_amdgcn_exp2f(own - mc[qb]) : 1.f;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
           float p[16];
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            p[v] = __builtin_amdgcn_exp2f(fmaf(s[kb][qb][v], a.cl2, -mc[qb]));
-            ls += p[v];
+            p[v] = __builtin_amdgcn_exp2f(fmaf(s[kb][qb][v], a.cl2, -mt));
+            l4[OWN ? v & 3 : 0] += p[v];
           }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
@@ -239,17 +255,40 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
             pf[qb][kb * 2 + u] = __builtin_bit_cast(bf16x8, w);
           }
         }
-        l[qb] += ls;
+        if constexpr (OWN) {
+          const float x = fmaf(wt[qb], (l4[0] + l4[1]) + (l4[2] + l4[3]), -l_err[qb]), sum = l[qb] + x;
+          l_err[qb] = (sum - l[qb]) - x;
+          l[qb] = sum;
+        } else {
+          l[qb] += l4[0];
+        }
       }
       // ---- O^T += V^T P^T
 #pragma unroll
-      for (int db = 0; db < 2 * AH; ++db)
+      for (int db = 0; db < 2 * AH; ++db) {
+        f32x16 c[OWN ? QB : 1];
+        if constexpr (OWN) {
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) c[qb][v] = 0.f;
+        }
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
           const bf16x8 va = tl.read_cols(Vc[u][db >> 1], kk * 16, db & 1);
 #pragma unroll
-          for (int qb = 0; qb < QB; ++qb) o[db][qb] = mfma_32x32x16(va, pf[qb][kk], o[db][qb]);
+          for (int qb = 0; qb < QB; ++qb) {
+            f32x16 &acc = OWN ? c[OWN ? qb : 0] : o[db][qb];
+            acc = mfma_32x32x16(va, pf[qb][kk], acc);
+          }
         }
+        if constexpr (OWN) {
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[db][qb][v] = fmaf(wt[qb], c[qb][v], o[db][qb][v]);
+        }
+      }
     };
     if constexpr (KS == 1) {
       if (work) { scores(); accumulate(); }
@@ -260,7 +299,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
         if (grp == 0) ref[wave][lane] = work ? tm[0] : -INFINITY;
         __syncthreads();
         m[0] = ref[wave][lane];
-        mc[0] = m[0] > -INFINITY ? m[0] * a.cl2 : 0.f;
+        mc[0] = m[0] > -INFINITY ? ref_of(m[0]) : 0.f;
         first = false;
       }
       if (work) accumulate();
@@ -276,6 +315,10 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
     stage(Ks1[grp], Vs1[grp], Ks0[grp], Vs0[grp]);
   }
 
+  if constexpr (OWN) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l[qb] -= l_err[qb];
+  }
   if constexpr (KS > 1) {
     // Groups 1 .. KS - 1 leave their sums in LDS (the stage buffers are free: group g takes one of the four
     // objects per 64 columns), group 0 brings them to a common maximum and adds them.
@@ -305,15 +348,16 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 #pragma unroll
       for (int g = 1; g < KS; ++g) M = fmaxf(M, mls[g][wave][0][lane]);
       const bool seen = M > -INFINITY;
-      const float w0 = seen ? __builtin_amdgcn_exp2f((m[0] - M) * a.cl2) : 0.f;
-      m[0] = M; mc[0] = seen ? M * a.cl2 : 0.f; l[0] *= w0;
+      auto weight = [&](float x) { return __builtin_amdgcn_exp2f(OWN ? ref_of(x) - ref_of(M) : (x - M) * a.cl2); };
+      const float w0 = seen ? weight(m[0]) : 0.f;
+      m[0] = M; mc[0] = seen ? ref_of(M) : 0.f; l[0] *= w0;
 #pragma unroll
       for (int db = 0; db < PARTS; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][0][v] *= w0;
 #pragma unroll
       for (int g = 1; g < KS; ++g) {
-        const float w = seen ? __builtin_amdgcn_exp2f((mls[g][wave][0][lane] - M) * a.cl2) : 0.f;
+        const float w = seen ? weight(mls[g][wave][0][lane]) : 0.f;
         l[0] = fmaf(mls[g][wave][1][lane], w, l[0]);
 #pragma unroll
         for (int db = 0; db < PARTS; ++db)
@@ -362,7 +406,9 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
   for (int qb = 0; qb < QB; ++qb) {
     const float lt = xhalf_sum(l[qb]);
     inv[qb] = 1.0f / lt;
-    if (here[qb] && half == 0) a.LSE[head * a.Lq + qrow[qb]] = (mc[qb] + __builtin_amdgcn_logf(lt)) * kLn2;
+    if (here[qb] && half == 0) {
+      a.LSE[head * a.Lq + qrow[qb]] = OWN ? (float)(mc[qb] * 0.6931471805599453 + log((double)lt)) : (mc[qb] + __builtin_amdgcn_logf(lt)) * kLn2;
+    }
   }
   const int64_t rows_here = a.Lq - (row0 + wave * R);
 #pragma unroll
@@ -403,16 +449,16 @@ __global__ void __launch_bounds__(256) fwd_combine_kernel(const float *part_o, c
   if (sub == 0) LSE[row] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
-template <int R, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
+template <bool OWN, int R, int AH, int NK, int RW, int KS, int MASKS = kBothMasks>
 static hipError_t launch_fwd(const Dims &d, FwdArgs a, int64_t heads, int splits, hipStream_t st) {
   a.by_tiles = make_fast_div((d.Lq + RW * R - 1) / (RW * R));
   a.by_length = order_by_length(d, splits, (int64_t)400 << 20);
   dim3 grid((unsigned)(heads * a.by_tiles.d), (unsigned)splits);
   if (!(MASKS & (d.causal ? kCausal : kNoMask))) return hipErrorInvalidValue;
   if constexpr (MASKS & kCausal)
-    if (d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+    if (d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, true, AH, NK, RW, KS, OWN>), grid, dim3(64 * RW * KS), 0, st, a);
   if constexpr (MASKS & kNoMask)
-    if (!d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK, RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+    if (!d.causal) hipLaunchKernelGGL((fused_fwd_kernel<R, false, AH, NK, RW, KS, OWN>), grid, dim3(64 * RW * KS), 0, st, a);
   return hipGetLastError();
 }
 
@@ -492,8 +538,9 @@ void fused_fwd_plan(const Dims &d, bool *big, int *splits) {
   *big = false; *splits = key_splits_for(d, 128);
 }
 
-hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O,
-                         float *LSE, hipStream_t st, float *part) {
+template <bool OWN>
+static hipError_t forward_as(const Dims &d, const void *Q, const void *K, const void *V, void *O,
+                         float *LSE, hipStream_t st, float *part, int64_t usual) {
   FwdArgs a;
   a.Q = (const uint16_t *)Q; a.K = (const uint16_t *)K; a.V = (const uint16_t *)V;
   a.O = (uint16_t *)O; a.LSE = LSE;
@@ -504,7 +551,9 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   const int64_t heads = (int64_t)d.B * d.Z;
   bool big;
   int splits;
-  fused_fwd_plan(d, &big, &splits);
+  Dims call = d;  // what the shapes are chosen by
+  if (usual) { call.B = 1; call.Z = (int)usual; }
+  fused_fwd_plan(call, &big, &splits);
   if (!part) splits = 1;
   const int64_t rows = heads * d.Lq;
   a.part_o = part;
@@ -515,26 +564,35 @@ hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void
   // four waves -> chosen): W = 64: 9.4 -> 7.5; 128 (4096 rows): 49 -> 27; 256 (4096): 49 -> 46; causal 192 (4096): 59 -> 28;
   // 384 (4096): 61 -> 46; 512 (2048): 33 -> 30; 640 (8192): 133 -> 116; heads of 128, W = 256 (4096): 83 -> 72, causal
   // 512 (8192): 180 -> 149, but 400 (512): 18 -> 25.
-  const int64_t W = heads * ((d.Lq + 127) / 128), walk = d.L / 64, L = d.L;
+  const int64_t W = (usual ? usual : heads) * ((d.Lq + 127) / 128), walk = d.L / 64, L = d.L;
   const bool c = d.causal;
   hipError_t e;
-  if (big) e = launch_fwd<64, 1, 2, 4, 1>(d, a, heads, splits, st);
+  if (big) e = launch_fwd<OWN, 64, 1, 2, 4, 1>(d, a, heads, splits, st);
   else if (d.A == 128) {
-    if (splits > 1 || W > (c && L > 512 ? 512 : 256)) e = launch_fwd<32, 2, 1, 4, 1>(d, a, heads, splits, st);
-    else if (W > 128) e = launch_fwd<32, 2, 1, 4, 2>(d, a, heads, 1, st);
-    else e = launch_fwd<32, 2, 1, 2, 2>(d, a, heads, 1, st);
-  } else if (splits > 1) e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, splits, st);
-  else if (W <= 64) e = launch_fwd<32, 1, 1, 1, 4>(d, a, heads, 1, st);
-  else if (W <= 128 || (c && W <= 300 && L >= 1536)) e = launch_fwd<32, 1, 1, 2, 4>(d, a, heads, 1, st);
-  else if (c && W <= (L >= 4096 ? 430 : 256)) e = launch_fwd<32, 1, 1, 2, 2, kCausal>(d, a, heads, 1, st);
+    if (splits > 1 || W > (c && L > 512 ? 512 : 256)) e = launch_fwd<OWN, 32, 2, 1, 4, 1>(d, a, heads, splits, st);
+    else if (W > 128) e = launch_fwd<OWN, 32, 2, 1, 4, 2>(d, a, heads, 1, st);
+    else e = launch_fwd<OWN, 32, 2, 1, 2, 2>(d, a, heads, 1, st);
+  } else if (splits > 1) e = launch_fwd<OWN, 32, 1, 1, 4, 1>(d, a, heads, splits, st);
+  else if (!OWN && W <= 64) e = launch_fwd<OWN, 32, 1, 1, 1, 4>(d, a, heads, 1, st);
+  else if (W <= 128 || (c && W <= 300 && L >= 1536)) e = launch_fwd<OWN, 32, 1, 1, 2, 4>(d, a, heads, 1, st);
+  else if (c && W <= (L >= 4096 ? 430 : 256)) e = launch_fwd<OWN, 32, 1, 1, 2, 2, kCausal>(d, a, heads, 1, st);
   else if (c ? (W <= 576 && L >= 1024) || (W <= 800 && L >= 4096) : W <= 256 && walk >= 16)
-    e = launch_fwd<32, 1, 1, 4, 2>(d, a, heads, 1, st);
-  else e = launch_fwd<32, 1, 1, 4, 1>(d, a, heads, 1, st);
+    e = launch_fwd<OWN, 32, 1, 1, 4, 2>(d, a, heads, 1, st);
+  else e = launch_fwd<OWN, 32, 1, 1, 4, 1>(d, a, heads, 1, st);
   if (e != hipSuccess || splits == 1) return e;
   const OutLayout lay = make_out_layout(d.os, d.Lq, d.Z);
   hipLaunchKernelGGL(fwd_combine_kernel, dim3((unsigned)((rows * (d.A / 4) + 255) / 256)), dim3(256), 0, st,
                      a.part_o, a.part_ml, (uint16_t *)O, LSE, rows, splits, d.A, lay);
   return hipGetLastError();
+}
+
+hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, hipStream_t st,
+                         float *part) {
+  return forward_as<false>(d, Q, K, V, O, LSE, st, part, 0);
+}
+hipError_t two_pass_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int64_t usual,
+                            hipStream_t st) {
+  return forward_as<true>(d, Q, K, V, O, LSE, st, nullptr, usual);
 }
 
 }  // namespace rsa

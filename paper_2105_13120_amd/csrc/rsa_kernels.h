@@ -61,6 +61,10 @@ int fused_key_splits(const Dims &d);
 bool order_by_length(const Dims &d, int splits, int64_t most);
 hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O,
                          float *LSE, hipStream_t st, float *part);
+// ... of the two-pass layout (more than 64 work-groups of 128 rows), without a split; usual: the heads by which shapes are
+// chosen, where a call is made a few heads at a time
+hipError_t two_pass_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int64_t usual,
+                            hipStream_t st);
 // nD = -rowsum(dO o O) and nL = -LSE / scale, (B,Z,Lq) fp32
 hipError_t fused_bwd_preprocess(const Dims &d, const void *dO, const void *O, const float *LSE,
                                 float *nD, float *nL, hipStream_t st);

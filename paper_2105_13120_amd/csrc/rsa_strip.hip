@@ -8,7 +8,8 @@
 //   forward    scores: S = Q K^T tile by tile, softmaxed against the tile's own row maximum:
 //                strip tile = exp(S - m_t) (dtype), (m_t, l_t) per row and 64 keys
 //              apply:  LSE from the pairs, O = sum_t exp(m_t - LSE) (strip tile) V
-//              (fp32, where rows are many or walks short: both in one kernel, and no strip; see f32_forward_kernel)
+//              (where rows are many, in fp32 also where walks are short: both in one kernel, and no strip; see
+//              f32_forward_kernel and bf16_one_pass)
 //   backward   by rows  scores: P = exp(S - LSE), dS = P o (dO V^T - D), both tiles written in dtype
 //                       apply:  dQ = s dS K;   collect: dV = P^T dO, dK = s dS^T Q
 //              by keys  (bf16, where work-groups that own 128 keys fill the chip: plan_by_keys)
@@ -26,8 +27,8 @@
 // Bytes per score: 2 es forward, 5 es backward, by keys 2 es (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
-// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 1.10,
-// bound by the strips' 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32 matrix instructions 0.49, 55 to 70 % of
+// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 0.72,
+// the backward bound by its strip's 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32 matrix instructions 0.49, 55 to 70 % of
 // their rate; now 0.42, the strips' 1.4 GB at 3.3 to 4.2 TB/s).
 //
 // The tile kernels hold bf16 tiles in the layout of the fused kernels; fp32 products run on the bf16 matrix instructions
@@ -1378,10 +1379,22 @@ int f32_one_pass(const Dims &d) {
   return W >= 400 ? 1 : 0;
 }
 
+// The bf16 forward by the kernels that keep no strip (two_pass_forward), for heads of 64 and 128 with more
+// than 64 work-groups of 128 rows (W); the strip, whose scores are shared by work-groups along the keys too, where rows are few.
+// The strip was written and read at 4 to 5 TB/s, the products of one pass are bound by the matrix pipe and the exponentials.
+// us, strip -> one pass: W = 128 (8 heads of 2048 rows) 33 -> 18, 512 (128 of 512) 37 -> 17, 1024 (128 of 1024) 139 -> 46, 2048
+// (128 of 2048) 495 -> 161, causal 384 (12 of 4096) 113 -> 48; heads of 128: 80 (640 rows) 17.2 -> 14.3, causal 14.6 both, 512
+// (512) 40 -> 27; but 64 (2048) 28.6 -> 31.5, 32 (2048) 20 -> 31.  (Heads of 64 gain at fewer W as well, 64 (2048) 22.5 -> 15.3,
+// 32 (1024) 11.9 -> 10.0, where the layout is kept for its own sake.)  L >= A: all results then take no more room than strips.
+int bf16_one_pass(const Dims &d) {
+  const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
+  return d.A <= 128 && d.L >= d.A && W > 64;
+}
+
 // How the work is cut: `heads` heads and `rows` of their query rows per group of launches, and where a
 // group's buffers lie in the workspace; out: results that may not be written yet (see apart_plan), of `chunk` heads.
-// usual, one_pass: what kernels and their shapes are chosen by, the heads of a group and f32_one_pass of the call as it is
-// where its results lie beside its inputs, so that they round alike wherever they lie.
+// usual, one_pass: what kernels and their shapes are chosen by, the heads of a group and f32_one_pass or bf16_one_pass of the call
+// as it is where its results lie beside its inputs, so that they round alike wherever they lie.
 // keys: the groups of waves of collect_keys' work-groups, or 0 for the backward by rows.
 struct StripPlan {
   int64_t heads, rows, chunk, usual;
@@ -1433,7 +1446,7 @@ StripPlan strip_plan_by_rows(const Dims &d, int dtype, int pass, bool strips_onl
   StripPlan p{};
   p.rows = d.Lq;
   p.heads = heads;
-  p.one_pass = pass == 0 && dtype == RSA_F32 && !strips_only ? f32_one_pass(d) : 0;
+  p.one_pass = pass == 0 && !strips_only ? (dtype == RSA_F32 ? f32_one_pass(d) : bf16_one_pass(d)) : 0;
   if (head * heads > kStripBytes && !p.one_pass) {
     if (head <= kStripBytes) {
       const int64_t most = head < kCacheBytes ? (int64_t)(kCacheBytes / head) : 1;
@@ -1681,6 +1694,8 @@ hipError_t forward_t(const Dims &d, const void *Q, const void *K, const void *V,
                      char *ws, const StripPlan &pl, hipStream_t st) {
   if constexpr (sizeof(T) == 4)
     if (pl.one_pass) return f32_forward(d, Q, K, V, O, LSE, pl.one_pass, st);
+  if constexpr (sizeof(T) == 2)
+    if (pl.one_pass) return two_pass_forward(d, Q, K, V, O, LSE, pl.usual, st);
   const int64_t heads = (int64_t)d.B * d.Z;
   for (int64_t h0 = 0; h0 < heads; h0 += pl.heads) {
     const int64_t nh = pl.heads < heads - h0 ? pl.heads : heads - h0;

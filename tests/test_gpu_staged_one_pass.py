@@ -1,0 +1,85 @@
+"""The two-pass bf16 forward where it keeps no strip: on either side of the line of its rule, with ragged last work-groups, one
+rank's share, scores that spread wide or grow along a walk, and results that lie over inputs."""
+import pytest
+import torch
+
+from helpers import compare_heads, gpu_forward_backward, upload
+from paper_2105_13120_amd import inputs, rsa
+
+pytestmark = pytest.mark.gpu
+
+# (B, Z, L, N, A, first rank, last rank + 1, causal), whether a strip is kept
+CASES = [
+    ((1, 16, 512, 4, 64, 0, 4, False), True),       # 64 work-groups of 128 rows,
+    ((1, 13, 576, 9, 64, 0, 9, False), False),      # 65: the last of a head half empty
+    ((1, 13, 576, 9, 128, 0, 9, True), False),
+    ((4, 8, 512, 8, 128, 3, 7, False), True),       # 64 and 96 of one rank's share
+    ((4, 8, 512, 8, 128, 2, 8, True), False),
+    ((5, 14, 64, 1, 64, 0, 1, False), False),       # one tile of keys; too few keys for the results' room
+    ((5, 14, 64, 1, 128, 0, 1, True), True),
+    ((3, 22, 832, 13, 64, 0, 13, True), False),     # 256-row, 128-row work-groups and groups of waves
+    ((2, 48, 1600, 5, 64, 0, 5, False), False),
+    ((1, 6, 4096, 4, 64, 0, 4, True), False),
+    ((1, 24, 8192, 16, 64, 15, 16, False), False),  # a walk that the fused mode splits
+    ((1, 96, 4096, 8, 128, 7, 8, True), False),
+    ((1, 23, 640, 5, 192, 0, 5, False), True),
+]
+
+
+@pytest.mark.parametrize("case,strip", CASES)
+def test_forward_in_one_pass(case, strip):
+    B, Z, L, N, A, rb, re, causal = case
+    cfg = inputs.RSAConfig("o", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=rb, rank_end=re, seed=59)
+    x = inputs.make_inputs(cfg)
+    out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED, backward=False)
+    compare_heads(cfg, x, out, sorted({0, B * Z // 2, B * Z - 1}), mode=rsa.MODE_STAGED, backward=False)
+
+
+@pytest.mark.parametrize("case", [CASES[1][0], CASES[7][0], CASES[8][0], CASES[11][0]])
+def test_forward_in_one_pass_over_its_inputs(case):
+    """Wherever O lies, bit by bit the same: over an input, or from its 64th row on, with the workspace that is asked for."""
+    B, Z, L, N, A, rb, re, causal = case
+    cfg = inputs.RSAConfig("o", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=rb, rank_end=re, seed=61)
+    x = inputs.make_inputs(cfg)
+    t = {k: upload(x[k], "bf16") for k in ("Q", "K", "V")}
+    desc = rsa.make_desc(t["K"], N, causal=causal, rank_begin=rb, rank_end=re, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(desc, t["Q"], t["K"], t["V"])
+    for over in ("Q", "K", "V"):
+        for rows in (0, 64):
+            n = max(O.numel(), t[over].numel())
+            buf = torch.empty(n + rows * A, dtype=torch.bfloat16, device="cuda")
+            u = dict(t)
+            u[over], out = buf[:t[over].numel()].view(t[over].shape), buf[rows * A:][:O.numel()].view(O.shape)
+            u[over].copy_(t[over])
+            got = rsa.forward(desc, u["Q"], u["K"], u["V"], O=out)
+            assert torch.equal(got[0], O) and torch.equal(got[1], LSE), (over, rows)
+
+
+@pytest.mark.parametrize("case", [CASES[1][0], CASES[2][0], CASES[9][0]])
+@pytest.mark.parametrize("scores", ["unit", "wide", "rising"])
+def test_forward_in_one_pass_is_as_exact_as_the_strip(case, scores):
+    """RMS error against 64 bits, beside that of the same rows taken a head at a time, which keep the strip: both round a tile's
+    probabilities to bf16 against its own maximum and results once, so that O errs alike (2 %: different elements fall to
+    either side); LSE, one fp32 number of about ten, no more (1e-8: a sixth of its last bit)."""
+    B, Z, L, N, A, rb, re, causal = case
+    cfg = inputs.RSAConfig("o", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=rb, rank_end=re, seed=67)
+    x = inputs.make_inputs(cfg)
+    Q, K, V = (upload(x[k], "bf16") for k in ("Q", "K", "V"))
+    if scores == "wide":
+        Q, K = Q * 4, K * 4
+    if scores == "rising":
+        K = (K * torch.exp2(torch.linspace(-3, 3, L, device="cuda"))[:, None]).bfloat16()
+    S = Q.double() @ K.double().mT.contiguous() / A ** 0.5
+    if causal:
+        S.masked_fill_(torch.ones(L, L, dtype=torch.bool, device="cuda").triu(1), -float("inf"))
+    lse = torch.logsumexp(S, -1)
+    ref = torch.softmax(S, -1) @ V.double()
+    mk = dict(causal=causal, mode=rsa.MODE_STAGED)
+    O, LSE = rsa.forward(rsa.make_desc(K, N, **mk), Q, K, V)
+    heads = [tuple(y[b:b + 1, z:z + 1].contiguous() for y in (Q, K, V)) for b in range(B) for z in range(Z)]
+    by_head = [rsa.forward(rsa.make_desc(k, N, **mk), q, k, v) for q, k, v in heads]
+    for name, got, parts, exact in (("O", O, 0, ref), ("LSE", LSE, 1, lse)):
+        other = torch.cat([y[parts] for y in by_head], 1).view(got.shape)
+        e, e_strip = (float((y.double() - exact).norm() / exact.norm()) for y in (got, other))
+        print(f"{name} {scores}: {e:.2e}, strip {e_strip:.2e}")
+        assert e <= 1.02 * e_strip + 1e-8, name

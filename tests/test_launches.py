@@ -8,6 +8,7 @@ import test_gpu_projected_keys_backward as projected
 import test_gpu_staged as staged
 import test_gpu_staged_by_keys as by_keys
 import test_gpu_staged_groups as groups
+import test_gpu_staged_one_pass as one_pass
 from paper_2105_13120_amd import rsa
 
 
@@ -75,6 +76,14 @@ def test_two_pass_long_walks_in_one_pass(rec, case):
     B, Z, L, N, causal, on_a_walk = case
     d = launches.descriptor(B, Z, L, N, causal=causal, dtype=rsa.RSA_F32, mode=rsa.MODE_STAGED)
     assert names(launches.forward(rec, d)) == [f"f32_forward_kernel<{4 // on_a_walk}, {on_a_walk}>"]
+
+
+@pytest.mark.parametrize("case,strip", one_pass.CASES)
+def test_two_pass_forward_keeps_a_strip_where_rows_are_few(rec, case, strip):
+    B, Z, L, N, A, rb, re, causal = case
+    d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, mode=rsa.MODE_STAGED)
+    got = names(launches.forward(rec, d))
+    assert [n.startswith("strip_scores_fwd") for n in got] == [True, False] if strip else [n.startswith("fused_fwd") for n in got] == [True]
 
 
 # groups of waves of the kernel that walks the rows, and groups of heads
