@@ -26,10 +26,10 @@ struct MatView {
   int Z;                 // head-split: heads per tensor
   int AH;                // head-split: column tiles per head (A / 64: 1 or 2), head-major order
   int split;             // 0: plain row-major; 1: (B, Z, rows, A) tensors, row index = b * rows + r
+  FastDiv by_rows, by_tensor;  // rows; Z * AH
 };
 
-// A value that is the same in every lane, moved to scalar registers (integer division leaves
-// its result in vector registers even when its operands are uniform).
+// A value that is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ int64_t uniform64(int64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
@@ -81,12 +81,11 @@ struct TileCursor {
       ptr = krows ? v.p[0] + ks * 64 * v.ld + fixed * 64 : v.p[0] + fixed * 64 * v.ld + ks * 64;
     } else {
       const uint32_t ct = (uint32_t)(krows ? fixed : ks), rt = (uint32_t)(krows ? ks : fixed);
-      const uint32_t per_tensor = (uint32_t)(v.Z * v.AH);
-      which = (int)(ct / per_tensor);
-      const uint32_t rem = ct % per_tensor;
-      const int64_t z = rem / (uint32_t)v.AH;
-      const int ah = (int)(rem % (uint32_t)v.AH);
-      const uint32_t m0 = rt * 64u, b = m0 / (uint32_t)v.rows, r0 = m0 % (uint32_t)v.rows;
+      which = (int)v.by_tensor(ct);
+      const uint32_t rem = ct - (uint32_t)which * v.by_tensor.d;
+      const int64_t z = v.AH == 2 ? rem >> 1 : rem;
+      const int ah = v.AH == 2 ? (int)(rem & 1) : 0;
+      const uint32_t m0 = rt * 64u, b = v.by_rows(m0), r0 = m0 - b * v.by_rows.d;
       const uint16_t *t = which == 0 ? v.p[0] : (which == 1 ? v.p[1] : v.p[2]);
       ptr = t + (((int64_t)b * v.Z + z) * v.rows + r0) * v.ld + ah * 64;
       cnt = krows ? (int)(r0 / 64) : (v.AH == 1 ? (int)z : ah);
@@ -121,10 +120,16 @@ struct GemmArgs {
   void *out[3];       // plain: out[0] (+ split * M * out_ld elements for a k split); head-split: 3 tensors
   int64_t out_ld, out_rows;
   int out_Z, out_AH, out_split;  // head-split output: (B, out_Z, out_rows, 64 * out_AH) tensors
-  int ntiles;         // column tiles
+  FastDiv by_out_rows, by_out_tensor;  // out_rows; out_Z * out_AH
+  FastDiv by_ntiles;  // column tiles
   int part_heads;     // > 0: the partial sums of a k split lie in the rows of a (Zt, out_rows, A) bf16 tensor: A / 2
                       // columns per head, part_heads heads per split, and out_ld = A / 2
 };
+
+// Divisions by run-time sizes are multiplications by numbers that the host prepares, and a head-split result's are done once
+// per 64 rows: as chains of vector instructions they stood in front of a work-group's first loads (five) and among its
+// stores (sixteen a lane), 3 to 9 % of the Q/K/V map (52224 rows, 1536 -> 3072: 468 -> 459 us; 178112 rows of 448: 314 -> 294;
+// 4096 rows of 768: 22.9 -> 22.1).
 
 // A_KROWS / B_KROWS: the operand's tiles hold k along their rows (the view is [K][M] or [K][N])
 // instead of along their columns ([M][K], [N][K]).
@@ -203,7 +208,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_
   const int col = lane & 31, half = lane >> 5;
   unsigned char(*lds)[HT][kHalfBytes] = lds_[grp];
   const uint32_t wg = xcd_remap(bx, nx);
-  const int64_t m0 = (int64_t)(wg / (uint32_t)g.ntiles) * BM, n0 = (int64_t)(wg % (uint32_t)g.ntiles) * BN;
+  const uint32_t mt = g.by_ntiles(wg);
+  const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)(wg - mt * g.by_ntiles.d) * BN;
   // slabs of 32 k of group `gr` of this split
   const int64_t per_grp = KG == 1 ? g.kslabs : (g.kslabs + KG - 1) / KG;
   auto slabs_of = [&](int gr, int64_t &begin) -> int {
@@ -413,32 +419,33 @@ __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_
     for (int mb = 0; mb < T; ++mb) stage_block_T(t0, mb * 32, acc[0][mb], acc[1][mb], 1.0f, lane);
     const int64_t nw = n0 + wn * 64;  // the block's 64 columns: (half of) one head of a head-split output
     if (nw < g.N) {
-      int which = 0;
-      int64_t zoff = 0, aoff = 0;
-      const int out_AH = WIDE ? g.out_AH : 1;
-      const int64_t out_A = 64 * out_AH;
+      uint16_t *base = static_cast<uint16_t *>(g.out[0]);
+      int64_t ld = g.out_ld, zoff = 0, aoff = nw;
       if (g.out_split) {
-        const uint32_t hb = (uint32_t)(nw / 64), per_tensor = (uint32_t)(g.out_Z * out_AH);
-        which = (int)(hb / per_tensor);
-        const uint32_t rem = hb % per_tensor;
-        zoff = rem / (uint32_t)out_AH;
-        aoff = (rem % (uint32_t)out_AH) * 64;
+        const int out_AH = WIDE ? g.out_AH : 1;
+        const uint32_t hb = (uint32_t)nw >> 6, which = g.by_out_tensor(hb), rem = hb - which * g.by_out_tensor.d;
+        if (which) base = static_cast<uint16_t *>(which == 1 ? g.out[1] : g.out[2]);
+        ld = 64 * out_AH;
+        zoff = out_AH == 2 ? rem >> 1 : rem;
+        aoff = out_AH == 2 ? (rem & 1) * 64 : 0;
       }
-      uint16_t *base = static_cast<uint16_t *>(which == 0 ? g.out[0] : (which == 1 ? g.out[1] : g.out[2]));
+      constexpr int BLOCKS = T == 4 ? 2 : 1;  // of 64 rows (T = 1: half of one), which lie in one batch element
+      const int64_t mw = m0 + wm * 32 * T;
 #pragma unroll
-      for (int it = 0; it < 4 * T; ++it) {
-        const int row = it * 8 + (lane >> 3), cc = lane & 7;  // row of the wave's 32 T
-        const int64_t m = m0 + wm * 32 * T + row;
-        if (m >= g.M) continue;
-        const u32x4 w = *reinterpret_cast<const u32x4 *>(t0 + tile_off(row, cc));
-        int64_t off;
-        if (!g.out_split) {
-          off = m * g.out_ld + nw + cc * 8;
-        } else {
-          const uint32_t b = (uint32_t)m / (uint32_t)g.out_rows, r = (uint32_t)m % (uint32_t)g.out_rows;
-          off = (((int64_t)b * g.out_Z + zoff) * g.out_rows + r) * out_A + aoff + cc * 8;
+      for (int blk = 0; blk < BLOCKS; ++blk) {
+        int64_t r = mw + blk * 64;
+        if (g.out_split) {
+          const uint32_t b = g.by_out_rows((uint32_t)r);
+          r = ((int64_t)b * g.out_Z + zoff) * g.out_rows + (r - (int64_t)b * g.out_rows);
         }
-        *reinterpret_cast<u32x4 *>(base + off) = w;
+        uint16_t *const rows = base + r * ld + aoff;
+#pragma unroll
+        for (int it = 0; it < 4 * T / BLOCKS; ++it) {
+          const int row = it * 8 + (lane >> 3), cc = lane & 7;
+          if (mw + blk * 64 + row >= g.M) continue;
+          const u32x4 w = *reinterpret_cast<const u32x4 *>(t0 + tile_off(blk * 64 + row, cc));
+          *reinterpret_cast<u32x4 *>(rows + row * ld + cc * 8) = w;
+        }
       }
     }
     return;
@@ -456,8 +463,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_
         // fp32 outputs are plain matrices
         int64_t off = ((int64_t)by * g.M + m) * g.out_ld + n;
         if (g.part_heads) {
-          const uint32_t w = (uint32_t)g.out_ld, h = by * (uint32_t)g.part_heads + (uint32_t)n / w;
-          off = ((int64_t)h * g.out_rows + m) * g.out_ld + (uint32_t)n % w;
+          const uint32_t w = (uint32_t)g.out_ld, sh = w == 32 ? 5 : 6;  // (A / 2)
+          const uint32_t h = by * (uint32_t)g.part_heads + ((uint32_t)n >> sh);
+          off = ((int64_t)h * g.out_rows + m) * g.out_ld + ((uint32_t)n & (w - 1));
         }
         const f32x16 &c = acc[nb][mb];
         const f32x4 w = {c[grp * 4 + 0], c[grp * 4 + 1], c[grp * 4 + 2], c[grp * 4 + 3]};
@@ -476,10 +484,10 @@ __global__ void __launch_bounds__(128 * T * KG, 2) proj_gemm_kernel(GemmArgs g) 
 // those of a projection along the sequence, dX = E dXp and dE = X dXp^T.
 template <bool GRAD_W, bool WIDE, int T0, int K0, int T1, int K1>
 __global__ void __launch_bounds__(128 * T0 * K0, 2) proj_gemm_pair_kernel(GemmArgs g0, GemmArgs g1, uint32_t cut,
-                                                                          int first, uint32_t nx0, uint32_t nx1) {
+                                                                          int first, uint32_t nx0, FastDiv by_nx1) {
   static_assert(T0 * K0 == T1 * K1, "one work-group size");
   const uint32_t id = blockIdx.x, own = id < cut ? id : id - cut;
-  const uint32_t by1 = __builtin_amdgcn_readfirstlane(own / nx1);
+  const uint32_t by1 = by_nx1(own), nx1 = by_nx1.d;
   if ((id < cut) == (first == 0))
     gemm_body<false, !GRAD_W, false, WIDE, T0, K0, false>(g0, own, nx0, 0);
   else
@@ -497,12 +505,14 @@ __global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_kernel(const float
 static MatView plain(const void *p, int64_t ld) {
   MatView v{};
   v.p[0] = static_cast<const uint16_t *>(p); v.ld = ld; v.split = 0; v.rows = 64; v.Z = 1; v.AH = 1;
+  v.by_rows = make_fast_div(64); v.by_tensor = make_fast_div(1);
   return v;
 }
 static MatView heads(const void *p0, const void *p1, const void *p2, int64_t rows, int Z, int A = 64) {
   MatView v{};
   v.p[0] = static_cast<const uint16_t *>(p0); v.p[1] = static_cast<const uint16_t *>(p1);
   v.p[2] = static_cast<const uint16_t *>(p2); v.ld = A; v.rows = rows; v.Z = Z; v.AH = A / 64; v.split = 1;
+  v.by_rows = make_fast_div(rows); v.by_tensor = make_fast_div((int64_t)Z * v.AH);
   return v;
 }
 
@@ -658,9 +668,11 @@ static bool wide_heads(const GemmArgs &g) {
 static uint32_t set_plan(GemmArgs &g, const GemmPlan &p) {
   const int64_t t = 64 * p.T;
   g.chain = p.chain;
-  g.ntiles = (int)((g.N + t - 1) / t);
+  const int64_t ntiles = (g.N + t - 1) / t;
+  g.by_ntiles = make_fast_div(ntiles);
+  if (g.out_split) { g.by_out_rows = make_fast_div(g.out_rows); g.by_out_tensor = make_fast_div((int64_t)g.out_Z * g.out_AH); }
   g.kslabs = (g.K / 64 + p.splits - 1) / p.splits;
-  return (uint32_t)(((g.M + t - 1) / t) * g.ntiles);
+  return (uint32_t)(((g.M + t - 1) / t) * ntiles);
 }
 
 template <bool A_KROWS, bool B_KROWS, bool OUT_F32, int T, int KG>
@@ -696,10 +708,10 @@ static hipError_t launch_pair_as(GemmArgs &g0, GemmArgs &g1, const GemmPlan &p0,
   const uint32_t cut = first ? n1 : nx0;
   if (wide_heads(g0) || wide_heads(g1))
     hipLaunchKernelGGL((proj_gemm_pair_kernel<GRAD_W, true, T0, K0, T1, K1>), grid, block, 0, st, g0, g1, cut, first,
-                       nx0, nx1);
+                       nx0, make_fast_div(nx1));
   else
     hipLaunchKernelGGL((proj_gemm_pair_kernel<GRAD_W, false, T0, K0, T1, K1>), grid, block, 0, st, g0, g1, cut, first,
-                       nx0, nx1);
+                       nx0, make_fast_div(nx1));
   return hipGetLastError();
 }
 template <bool GRAD_W>
