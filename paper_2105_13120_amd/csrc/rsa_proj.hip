@@ -10,7 +10,7 @@
 // Work-group: 64 T x 64 T outputs, T = 4, 2 or 1 by the size of the product (plan_gemm), 2 T waves of 32 T x 64, k in
 // slabs of 32 through a ring of four LDS buffers, one barrier per slab.  The product is formed transposed
 // (accumulator rows = n, columns = m): a lane then owns one output row m and four consecutive n per register group;
-// bf16 blocks leave through LDS as whole 128-byte row segments, fp32 blocks as 16-byte pieces.
+// blocks leave through LDS as whole row segments of 128 (bf16) or 256 bytes.
 #include "rsa_fused_tile.h"
 #include "rsa_kernels.h"
 
@@ -450,27 +450,38 @@ __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_
     }
     return;
   }
+  // fp32 (plain matrices): 32 rows of the wave's block at a time, through LDS of its own, as 256-byte row segments; row r's
+  // 16-byte chunk c at c ^ rot(r), free of bank conflicts for both accesses.  (Stored from the accumulators, an instruction
+  // touched 32 rows of 32 bytes.  us, projection along the sequence and its gradients, 48 heads of 114688 rows, Kp = 256: 217,
+  // 444 -> 214, 435; 2 of 96768, 128: 22.3, 25.7 -> 22.2, 23.8; 11 of 128 of 8640, 192: 20.0, 22.2 -> 19.6, 21.5.)
+  unsigned char *t0 = &lds_[0][0][0][0] + wave * 8192;
+  static_assert(HT * 8192 <= KG * 4 * HT * kHalfBytes, "8 KiB a wave");
+  auto place = [](int r, int c) { return r * 256 + ((c ^ ((r & 3) | ((r >> 1) & 4) | ((r & 4) << 1))) << 4); };
+  const int64_t nw = n0 + wn * 64;
+  if (nw >= g.N) return;
 #pragma unroll
   for (int mb = 0; mb < T; ++mb) {
-    const int64_t m = m0 + wm * 32 * T + mb * 32 + col;
-    if (m >= g.M) continue;
+    const int64_t mw = m0 + wm * 32 * T + mb * 32;
+    if (mw >= g.M) return;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const int64_t n = n0 + wn * 64 + nb * 32 + grp * 8 + half * 4;
-        if (n >= g.N) continue;
-        // fp32 outputs are plain matrices
-        int64_t off = ((int64_t)by * g.M + m) * g.out_ld + n;
-        if (g.part_heads) {
-          const uint32_t w = (uint32_t)g.out_ld, sh = w == 32 ? 5 : 6;  // (A / 2)
-          const uint32_t h = by * (uint32_t)g.part_heads + ((uint32_t)n >> sh);
-          off = ((int64_t)h * g.out_rows + m) * g.out_ld + ((uint32_t)n & (w - 1));
-        }
+      for (int q = 0; q < 4; ++q) {
         const f32x16 &c = acc[nb][mb];
-        const f32x4 w = {c[grp * 4 + 0], c[grp * 4 + 1], c[grp * 4 + 2], c[grp * 4 + 3]};
-        *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out[0]) + off) = w;
+        *reinterpret_cast<f32x4 *>(t0 + place(col, nb * 8 + q * 2 + half)) = f32x4{c[q * 4], c[q * 4 + 1], c[q * 4 + 2], c[q * 4 + 3]};
       }
+    const int cc = lane & 15;
+    int64_t off = ((int64_t)by * g.M + mw) * g.out_ld + nw + cc * 4;
+    if (g.part_heads) {
+      const uint32_t n = (uint32_t)nw + cc * 4, w = (uint32_t)g.out_ld, sh = w == 32 ? 5 : 6;  // (A / 2)
+      off = ((int64_t)(by * (uint32_t)g.part_heads + (n >> sh)) * g.out_rows + mw) * g.out_ld + (n & (w - 1));
+    }
+    float *const out = static_cast<float *>(g.out[0]) + off;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int r = it * 4 + (lane >> 4);
+      *reinterpret_cast<f32x4 *>(out + r * g.out_ld) = *reinterpret_cast<const f32x4 *>(t0 + place(r, cc));
+    }
   }
 }
 
