@@ -242,17 +242,17 @@ __host__ __device__ inline int64_t head_offset(uint32_t h, const FastDiv &Z, con
 // Where a row of a strided output tensor lives, for kernels that walk (head, row) pairs flat:
 // flat_row = head * rows_per_head + row.
 struct OutLayout {
-  int64_t st[3], rows_per_head;
-  int Z;
+  int64_t st[3];
+  FastDiv by_rows, by_Z;  // rows per head (flat rows are below 2^31), Z
   __host__ __device__ int64_t row_off(int64_t flat_row) const {
-    const uint32_t r = (uint32_t)flat_row, n = (uint32_t)rows_per_head, h = r / n;
-    return head_offset(h, Z, st) + (int64_t)(r - h * n) * st[2];
+    const uint32_t r = (uint32_t)flat_row, h = by_rows(r);
+    return head_offset(h, by_Z, st) + (int64_t)(r - h * by_rows.d) * st[2];
   }
 };
 inline OutLayout make_out_layout(const int64_t *st, int64_t rows_per_head, int Z) {
   OutLayout l;
   for (int k = 0; k < 3; ++k) l.st[k] = st[k];
-  l.rows_per_head = rows_per_head; l.Z = Z;
+  l.by_rows = make_fast_div(rows_per_head); l.by_Z = make_fast_div(Z);
   return l;
 }
 

@@ -25,6 +25,8 @@
 #include "rsa_fused_tile.h"
 #include "rsa_kernels.h"
 
+#include <type_traits>
+
 namespace rsa {
 
 // Which tile of which head the work-groups of a kernel take.
@@ -54,7 +56,17 @@ struct BwdArgs {
 };
 
 // ------------------------------------------------------------- preprocess ---
-// nD_i = -sum_a dO_ia O_ia and nL_i = -LSE_i / scale: 8 lanes per row, 8 elements of every 64 each.
+// nD_i = -sum_a dO_ia O_ia and nL_i = -LSE_i / scale: 8 lanes per row, 8 elements of every 64 each.  Where rows are few it
+// is a launch and one chain of latencies: a row's place by multiplications, its loads (LSE among them) in flight together,
+// the sum over lanes without LDS.
+__device__ __forceinline__ float sum_of_8_lanes(float x) {
+  auto other = [](float y, auto ctrl) __attribute__((always_inline)) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, y), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += other(x, std::integral_constant<int, 0xB1>{});   // quad_perm 1 0 3 2
+  x += other(x, std::integral_constant<int, 0x4E>{});   // quad_perm 2 3 0 1
+  return x + other(x, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other four
+}
 __global__ void __launch_bounds__(256) bwd_preprocess_kernel(const uint16_t *dO, const uint16_t *O,
                                                              const float *LSE, float *nD, float *nL,
                                                              int64_t rows, int A, float inv_scale,
@@ -62,27 +74,25 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(const uint16_t *dO,
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t row = gid >> 3;
   const int sub = (int)(gid & 7);
+  if (row >= rows) return;  // (all eight lanes of a row)
+  const int64_t off = lay.row_off(row) + sub * 8;
+  auto at = [&](const uint16_t *p, int a) { return *reinterpret_cast<const u32x4 *>(p + off + a); };
+  const u32x4 x0 = at(dO, 0), y0 = at(O, 0);
+  u32x4 x1 = {0, 0, 0, 0}, y1 = x1;
+  if (A > 64) { x1 = at(dO, 64); y1 = at(O, 64); }
+  const float lse = LSE[row];
   float acc = 0.f;
-  if (row < rows) {
-    const int64_t base = lay.row_off(row);
-    for (int a0 = 0; a0 < A; a0 += 64) {
-      const int64_t off = base + a0 + sub * 8;
-      const u32x4 x = *reinterpret_cast<const u32x4 *>(dO + off);
-      const u32x4 y = *reinterpret_cast<const u32x4 *>(O + off);
+  auto add = [&](const u32x4 &x, const u32x4 &y) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc = fmaf(bf16_to_f32(x[e] & 0xffffu), bf16_to_f32(y[e] & 0xffffu), acc);
-        acc = fmaf(bf16_to_f32(x[e] >> 16), bf16_to_f32(y[e] >> 16), acc);
-      }
+    for (int e = 0; e < 4; ++e) {
+      acc = fmaf(bf16_to_f32(x[e] & 0xffffu), bf16_to_f32(y[e] & 0xffffu), acc);
+      acc = fmaf(bf16_to_f32(x[e] >> 16), bf16_to_f32(y[e] >> 16), acc);
     }
-  }
-  acc += __shfl_xor(acc, 1);
-  acc += __shfl_xor(acc, 2);
-  acc += __shfl_xor(acc, 4);
-  if (row < rows && sub == 0) {
-    nD[row] = -acc;
-    nL[row] = -LSE[row] * inv_scale;
-  }
+  };
+  add(x0, y0);
+  if (A > 64) add(x1, y1);
+  acc = sum_of_8_lanes(acc);
+  if (sub < 2) (sub == 0 ? nD : nL)[row] = sub == 0 ? -acc : -lse * inv_scale;
 }
 
 // ------------------------------------------------------------------ dK, dV ---
