@@ -266,8 +266,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
 
-  // fp32 results of the smaller tiles: longer sums are folded into a second set of accumulators, chain by chain
-  constexpr bool FOLD = OUT_F32 && T <= 2;
+  // fp32 results, and sums over rows, of the smaller tiles: longer sums are folded into a second set of accumulators, chain
+  // by chain
+  constexpr bool FOLD = (OUT_F32 || (A_KROWS && B_KROWS)) && T <= 2;
   f32x16 done[FOLD ? 2 : 1][FOLD ? T : 1];
   int left = FOLD ? (int)g.chain * 2 : 0;  // slabs to the next fold
   if constexpr (FOLD) {
@@ -882,6 +883,14 @@ hipError_t linformer_project(int64_t Zt, int64_t L, int64_t rows, int64_t Kp, in
   g.A = plain(E, Kp);                               // [K = token][M = k]
   g.B = heads(X, nullptr, nullptr, L, (int)Zt, A);  // [K = token][N = (head, a)]; one "batch" of Zt heads
   const GemmPlan plan = plan_gemm(g, linformer_splits(Kp, Zt, rows, A), wgrad_chain(g.M, g.N, g.K), true);
+  const size_t out_bytes = (size_t)(Zt * Kp * A) * 2;
+  // One split leaves its sums in bf16, to the same bits, where Xp lies on nothing that other work-groups still read (us: 13 heads
+  // of 448 rows, Kp = 512: 8.8 -> 6.1, 15 of 1280, 512: 12.0 -> 9.0, 160 of 1024, 512: 28.9 -> 19.7; 63 of 640, 3008: 39 -> 21).
+  if (plan.splits == 1 && !overlap(Xp, out_bytes, X, (size_t)(((Zt - 1) * L + rows) * A) * 2) &&
+      !overlap(Xp, out_bytes, E, (size_t)(rows * Kp) * 2)) {
+    g.out[0] = Xp; g.out_split = 1; g.out_rows = Kp; g.out_Z = (int)Zt; g.out_AH = A / 64;
+    return launch_gemm<true, true, false>(g, plan, st);
+  }
   g.out[0] = part; g.out_split = 0; g.out_ld = g.N;
   hipError_t e = launch_gemm<true, true, true>(g, plan, st);
   if (e != hipSuccess) return e;

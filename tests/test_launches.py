@@ -5,6 +5,7 @@ import launches
 import test_gpu_backward_one_grid as one_grid
 import test_gpu_gradients_one_grid as gradients
 import test_gpu_projected_keys_backward as projected
+import test_gpu_projection_in_one_split as one_split
 import test_gpu_staged as staged
 import test_gpu_staged_by_keys as by_keys
 import test_gpu_staged_groups as groups
@@ -140,6 +141,15 @@ def test_gradients_of_the_projection_along_the_sequence(rec, case, want):
     d = launches.descriptor(1, Z, rows, 1, A)
     got = [tiles(k) for k in rec("linformer_project_bwd", d, Kp, "dXp", "X", "E", "X" if over else "dX", "dE") if "gemm" in k.name]
     assert got == [want] if want else len(got) == 2
+
+
+@pytest.mark.parametrize("case,form", one_split.CASES)
+def test_projection_along_the_sequence_in_one_split(rec, case, form):
+    heads, L, N, rb, re, Kp, A = case
+    d = launches.descriptor(1, heads, L, N, A, (rb, re))
+    got = rec("linformer_project", d, Kp, "X", "E", "Xp", "ws")
+    assert len(got) == 1 and tiles(got[0]) == (form,) and got[0].name.startswith("proj_gemm_kernel<true, true, false")
+    assert names(rec("linformer_project", d, Kp, "X", "E", "X", "ws"))[1:] == ["ksplit_reduce_heads_kernel"]
 
 
 @pytest.mark.parametrize("rows,Z,A,Kp", [(16384, 64, 64, 128), (80640, 22, 128, 128)])
