@@ -952,6 +952,10 @@ __device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], 
 // and read took as long as the products do now).  Work-group: as in apply; K and V of a step are split on their way to
 // one LDS buffer per group.  A row's exponents are relative to a whole number (the ceiling of its maximum so far), so that
 // bringing its sums to a new reference is exact; sums and products are formed as in scores and apply.
+// With 32 rows to a work-group a wave walks its steps alone (ALONE): K goes from memory to operand registers, V through LDS
+// of the wave's own, and nothing waits for a barrier; the splits, 1.2 us of a step where they came in front of the products, lie
+// beside them.  us: 2 heads of 256 rows 9.9 -> 9.5, 16 of 512 17.2 -> 14.8, causal 10 of 832 26.9 -> 22.0, 12 of 1024 36.1 ->
+// 30.5; but 128 rows, one step a wave, 6.7 -> 6.9.  (Eight such waves: 512 rows 15.3, 256 rows 10.8.)
 struct PassArgs {
   const float *Q, *K, *V;
   float *O, *LSE;
@@ -965,7 +969,8 @@ template <int RW, int KS>
 __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kernel(PassArgs a) {
   typedef TileT<float> TT;
   constexpr int BM = 32 * RW, RT = 32, PL = RT * 128;
-  struct Stage { unsigned char K[3 * PL], V[3 * PL]; };
+  constexpr bool ALONE = RW == 1;
+  struct Stage { unsigned char V[3 * PL], K[ALONE ? 16 : 3 * PL]; };
   constexpr int kBuf = KS * (int)sizeof(Stage), kOut = RW * 8192;
   __shared__ __attribute__((aligned(16))) unsigned char buf[kBuf > kOut ? kBuf : kOut];
   __shared__ float sums[KS == 1 ? 1 : KS][RW][2][64];
@@ -986,26 +991,53 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
   }
   const float *Kh = a.K + (int64_t)head * a.L * 64, *Vh = a.V + (int64_t)head * a.L * 64;
   typename TT::template Tile<RT, RW> k_tile(wave, lane, 64), v_tile(wave, lane, 64);
-  auto fetch = [&](int t) __attribute__((always_inline)) {
-    if (t >= nt) return;
-    k_tile.fetch(Kh + (int64_t)t * (RT * 64));
+  f32x4 key[ALONE ? 2 * kSlices : 1];  // a lone wave's step of K, as it multiplies it
+  // (a lone wave past its last step fetches that again: a branch would part the splits from the products)
+  auto fetch_k = [&](int t) __attribute__((always_inline)) {
+    if (!ALONE && t >= nt) return;
+    if (t >= nt) t = nt - 1;
+    if constexpr (ALONE) {
+      const float *p = Kh + ((int64_t)t * RT + col) * 64 + half * (kSliceK / 2);
+#pragma unroll
+      for (int i = 0; i < 2 * kSlices; ++i) key[i] = *reinterpret_cast<const f32x4 *>(p + (i >> 1) * kSliceK + (i & 1) * 4);
+    } else {
+      k_tile.fetch(Kh + (int64_t)t * (RT * 64));
+    }
+  };
+  auto fetch_v = [&](int t) __attribute__((always_inline)) {
+    if (!ALONE && t >= nt) return;
+    if (t >= nt) t = nt - 1;
     v_tile.fetch(Vh + (int64_t)t * (RT * 64));
   };
+  auto fetch = [&](int t) __attribute__((always_inline)) { fetch_k(t); fetch_v(t); };
   auto put = [&](int t) __attribute__((always_inline)) {
-    if (t >= nt) return;
+    if (ALONE || t >= nt) return;
     k_tile.put(st.K);
     v_tile.put(st.V);
   };
   int t = grp;  // this group's step
-  fetch(t);
   RowFrags<float, 1> q;
   {
-    float none;
     const float *qp = a.Q + ((int64_t)head * Lq + (rows_here ? wrow : row0) + col) * 64 + half * (kSliceK / 2);
-    q.template load<false>(qp, qp, none);
+    if constexpr (ALONE) {
+      f32x4 raw[2 * kSlices];  // (in front of the step's loads, under which it is split)
+#pragma unroll
+      for (int i = 0; i < 2 * kSlices; ++i) raw[i] = *reinterpret_cast<const f32x4 *>(qp + (i >> 1) * kSliceK + (i & 1) * 4);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(t);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < kSlices; ++i) q.f[i] = split8(raw[2 * i], raw[2 * i + 1]);
+    } else {
+      fetch(t);
+      float none;
+      q.template load<false>(qp, qp, none);
+    }
   }
-  put(t);
-  fetch(t + KS);
+  if (!ALONE) {
+    put(t);
+    fetch(t + KS);
+  }
   const TT tt(lane);
   f32x16 o[2];
 #pragma unroll
@@ -1014,15 +1046,32 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
   float M = -INFINITY;          // the row's reference, a whole number
   float l = 0.f, l_err = 0.f;   // the lane's share of the row's sum, and what its additions have lost so far
-  barrier_lds();
-  while (t - grp < nt) {
+  if (!ALONE) barrier_lds();
+  while (ALONE ? t < nt : t - grp < nt) {
     const int k0 = t * RT;
-    if (rows_here && (KS == 1 || t < nt) && (!a.causal || k0 <= q0 + wrow + 31)) {
+    if (ALONE || (rows_here && (KS == 1 || t < nt) && (!a.causal || k0 <= q0 + wrow + 31))) {
       f32x16 s, rest;
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[v] = rest[v] = 0.f;
+      if constexpr (ALONE) {  // (V is split beside the products; its place is the wave's own, which takes no barrier)
+        typename TT::Frag kf[kSlices];
 #pragma unroll
-      for (int i = 0; i < kSlices; ++i) TT::mfma(tt.template rows<PL>(st.K, 0, i), q.get(i), s, rest);
+        for (int i = 0; i < kSlices; ++i) kf[i] = split8(key[2 * i], key[2 * i + 1]);
+        fetch_k(t + KS);
+#pragma unroll
+        for (int i = 0; i < kSlices; ++i) TT::mfma(kf[i], q.get(i), s, rest);
+        v_tile.put(st.V);
+        fetch_v(t + KS);
+#pragma unroll
+        for (int i = 0; i < 6 * kSlices; ++i) {  // a lone wave's vector instructions in the shadow of its products
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kSlices; ++i) TT::mfma(tt.template rows<PL>(st.K, 0, i), q.get(i), s, rest);
+      }
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[v] += rest[v];
       if (a.causal && k0 + 31 > q0 + wrow) {
@@ -1072,10 +1121,12 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    barrier_lds();
-    put(t + KS);
-    fetch(t + 2 * KS);
-    barrier_lds();
+    if constexpr (!ALONE) {
+      barrier_lds();
+      put(t + KS);
+      fetch(t + 2 * KS);
+      barrier_lds();
+    }
     t += KS;
   }
   l = xhalf_sum(l - l_err);
