@@ -79,7 +79,7 @@ size_t workspace_bytes(const Dims &d, int dtype, int pass) {
   if (pass == 1) return det_bwd_bytes(d);
   bool big;
   int fs;
-  rsa::fused_fwd_plan(d, &big, &fs);
+  rsa::fused_fwd_plan(d, true, &big, &fs);
   return fs > 1 ? align256(fs * rows * (d.A + 2) * 4) : 0;
 }
 // where the split walks' partial sums start in the backward workspace
@@ -144,7 +144,7 @@ int rsa_forward(const rsa_desc *d, const void *Q, const void *K, const void *V, 
   }
   const size_t need = workspace_bytes(dm, d->dtype, 0);
   if (need > 0 && (!ws || ws_bytes < need)) return RSA_ERR_WORKSPACE;
-  return hip_status(rsa::fused_forward(dm, Q, K, V, O, LSE, st, static_cast<float *>(ws)));
+  return hip_status(rsa::fused_forward(dm, Q, K, V, O, LSE, st, true, static_cast<float *>(ws)));
 }
 
 int rsa_backward(const rsa_desc *d, const void *dO, const void *Q, const void *K, const void *V,
@@ -440,7 +440,7 @@ int rsa_linformer_forward(const rsa_desc *d, int32_t Kp, const void *Q, const vo
                           void *O, float *LSE, void *stream) {
   RSA_LINF_PROLOGUE(Q && Kp_ && Vp_ && O && LSE, Q, Kp_, Vp_, O, LSE);
   if (rsa::shortkeys_supported(att)) return hip_status(rsa::shortkeys_forward(att, Q, Kp_, Vp_, O, LSE, st));
-  return hip_status(rsa::fused_forward(att, Q, Kp_, Vp_, O, LSE, st, nullptr));
+  return hip_status(rsa::fused_forward(att, Q, Kp_, Vp_, O, LSE, st, false, nullptr));
 }
 
 int rsa_linformer_backward(const rsa_desc *d, int32_t Kp, const void *dO, const void *Q, const void *Kp_,

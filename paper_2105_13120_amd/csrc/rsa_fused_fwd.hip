@@ -521,26 +521,31 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // Rows that are no multiple of 256 leave part of a head's last work-group idle: the rounds of the whole ring count that (4160
 // rows, W = 1815: 290 -> 276, 3366: 510 -> 483; 2496 rows, 1820: 178 -> 169), one rank's share takes large ones only where 128
 // would leave as much (1472 rows of 2944, 2424: 265 -> 250; but 832 of 6656, 1484: 372 -> 439, 2368 of 4736 causal, 3325: 164 -> 186).
-void fused_fwd_plan(const Dims &d, bool *big, int *splits) {
+// A walk that would be split but has no room for partial results (the two-pass layout, projected keys) goes by the rounds as
+// well, one rank's causal share by 512 large work-groups of its own: such as were to fill the chip times their splits left it half
+// empty (two-pass, us, shape of the split -> this: 1 head of 16384 rows 337 -> 103, causal 341 -> 100; 4 of 8192 171 -> 98; 16 heads of
+// 1024 of 16384 335 -> 104, 130 of 512 of 4096 139 -> 115; 160 heads of 512 rows, 4096 projected keys 123 -> 108; large ones as
+// before: last 512 of 4096 causal, 256 heads, 166, not 173; 64 of 1024 of 8192 175, not 180).
+void fused_fwd_plan(const Dims &d, bool may_split, bool *big, int *splits) {
   if (d.A == 64) {
     const int s = key_splits_for(d, 256);
     const int64_t heads = (int64_t)d.B * d.Z, wgs = heads * ((d.Lq + 255) / 256), W = heads * ((d.Lq + 127) / 128);
     bool large = wgs * s >= 512 && (d.Lq % 256 == 0 || (s == 1 && 2 * wgs == W));
-    if (s == 1 && d.Lq == d.L) {
-      if (d.causal) large = W >= 2000 && d.L >= 4096;
+    if (s == 1 ? d.Lq == d.L : !may_split) {
+      if (d.causal) large = d.Lq == d.L ? W >= 2000 && d.L >= 4096 : wgs >= 512 && d.Lq % 256 == 0;
       else large = W >= 512 && d.L > 512 && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
     }
     if (large) {
-      *big = true; *splits = s;
+      *big = true; *splits = may_split ? s : 1;
       return;
     }
   }
-  *big = false; *splits = key_splits_for(d, 128);
+  *big = false; *splits = may_split ? key_splits_for(d, 128) : 1;
 }
 
 template <bool OWN>
 static hipError_t forward_as(const Dims &d, const void *Q, const void *K, const void *V, void *O,
-                         float *LSE, hipStream_t st, float *part, int64_t usual) {
+                         float *LSE, hipStream_t st, bool may_split, float *part, int64_t usual) {
   FwdArgs a;
   a.Q = (const uint16_t *)Q; a.K = (const uint16_t *)K; a.V = (const uint16_t *)V;
   a.O = (uint16_t *)O; a.LSE = LSE;
@@ -553,8 +558,7 @@ static hipError_t forward_as(const Dims &d, const void *Q, const void *K, const 
   int splits;
   Dims call = d;  // what the shapes are chosen by
   if (usual) { call.B = 1; call.Z = (int)usual; }
-  fused_fwd_plan(call, &big, &splits);
-  if (!part) splits = 1;
+  fused_fwd_plan(call, may_split, &big, &splits);
   const int64_t rows = heads * d.Lq;
   a.part_o = part;
   a.part_ml = part ? part + (int64_t)splits * rows * d.A : nullptr;
@@ -587,12 +591,12 @@ static hipError_t forward_as(const Dims &d, const void *Q, const void *K, const 
 }
 
 hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, hipStream_t st,
-                         float *part) {
-  return forward_as<false>(d, Q, K, V, O, LSE, st, part, 0);
+                         bool may_split, float *part) {
+  return forward_as<false>(d, Q, K, V, O, LSE, st, may_split, part, 0);
 }
 hipError_t two_pass_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int64_t usual,
                             hipStream_t st) {
-  return forward_as<true>(d, Q, K, V, O, LSE, st, nullptr, usual);
+  return forward_as<true>(d, Q, K, V, O, LSE, st, false, nullptr, usual);
 }
 
 }  // namespace rsa

@@ -54,13 +54,14 @@ enum MaskUse { kNoMask = 1, kCausal = 2, kBothMasks = 3 };
 
 // --- fused (online-softmax) path, bf16, A = 64 or 128 ---
 // Split of the walk over the keys (few query rows, many keys).  fused_fwd_plan: the forward's
-// rows per work-group (big: 256, else 128) and its split count; part: its fp32 partial results,
-// splits * B*Z*Lq * (A + 2) floats, or nullptr for no split.  fused_key_splits: the dQ kernel's count.
-void fused_fwd_plan(const Dims &d, bool *big, int *splits);
+// rows per work-group (big: 256, else 128) and its split count, 1 unless may_split (a call without room for partial
+// results gets the shape that suits a whole walk, not the one of a split that is then not made); part: the fp32
+// partial results, splits * B*Z*Lq * (A + 2) floats.  fused_key_splits: the dQ kernel's count.
+void fused_fwd_plan(const Dims &d, bool may_split, bool *big, int *splits);
 int fused_key_splits(const Dims &d);
 bool order_by_length(const Dims &d, int splits, int64_t most);
 hipError_t fused_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O,
-                         float *LSE, hipStream_t st, float *part);
+                         float *LSE, hipStream_t st, bool may_split, float *part);
 // ... of the two-pass layout (more than 64 work-groups of 128 rows), without a split; usual: the heads by which shapes are
 // chosen, where a call is made a few heads at a time
 hipError_t two_pass_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int64_t usual,

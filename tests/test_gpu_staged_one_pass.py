@@ -20,7 +20,9 @@ CASES = [
     ((3, 22, 832, 13, 64, 0, 13, True), False),     # 256-row, 128-row work-groups and groups of waves
     ((2, 48, 1600, 5, 64, 0, 5, False), False),
     ((1, 6, 4096, 4, 64, 0, 4, True), False),
-    ((1, 24, 8192, 16, 64, 15, 16, False), False),  # a walk that the fused mode splits
+    ((1, 24, 8192, 16, 64, 15, 16, False), False),  # walks that the fused mode splits
+    ((1, 16, 16384, 16, 64, 3, 4, False), False),
+    ((1, 17, 16384, 16, 64, 15, 16, True), False),
     ((1, 96, 4096, 8, 128, 7, 8, True), False),
     ((1, 23, 640, 5, 192, 0, 5, False), True),
 ]

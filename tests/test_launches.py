@@ -87,6 +87,30 @@ def test_two_pass_forward_keeps_a_strip_where_rows_are_few(rec, case, strip):
     assert [n.startswith("strip_scores_fwd") for n in got] == [True, False] if strip else [n.startswith("fused_fwd") for n in got] == [True]
 
 
+# heads, L, N, ranks, causal; rows a wave, waves on the rows, groups of waves
+@pytest.mark.parametrize("heads,L,N,ranks,causal,shape,grid", [
+    (1, 16384, 1, (0, 1), False, (32, 2, 4), 256),
+    (1, 16384, 1, (0, 1), True, (32, 2, 4), 256),
+    (4, 8192, 1, (0, 1), False, (32, 4, 2), 256),
+    (16, 16384, 16, (3, 4), False, (32, 2, 4), 256),
+    (130, 4096, 8, (5, 6), False, (32, 4, 1), 520),
+    (64, 8192, 8, (4, 5), False, (64, 4, 1), 256),
+    (256, 4096, 8, (7, 8), True, (64, 4, 1), 512),
+])
+def test_walks_without_room_for_a_split_are_not_planned_with_one(rec, heads, L, N, ranks, causal, shape, grid):
+    d = launches.descriptor(1, heads, L, N, 64, ranks, causal, mode=rsa.MODE_STAGED)
+    (k,) = launches.forward(rec, d)
+    rows, waves, on_a_walk = shape
+    assert k.name == f"fused_fwd_kernel<{rows}, {str(causal).lower()}, 1, {rows // 32}, {waves}, {on_a_walk}, true>"
+    assert k.grid == (grid, 1, 1)
+
+
+@pytest.mark.parametrize("heads,rows,grid", [(160, 512, 640), (48, 2560, 480)])
+def test_attention_to_many_projected_keys_fills_the_chip(rec, heads, rows, grid):
+    (k,) = rec("linformer_forward", launches.descriptor(1, heads, rows, 1), 4096, "Q", "K", "V", "O", "LSE")
+    assert k.grid == (grid, 1, 1)
+
+
 # groups of waves of the kernel that walks the rows, and groups of heads
 @pytest.mark.parametrize("case,on_a_walk,of_heads", zip(by_keys.CASES, [1, 1, 1, 1, 2, 4, 2, 1, 2, 1, 1, 2, 1], [1] * 10 + [3, 3, 3]))
 def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
