@@ -1446,10 +1446,12 @@ int bf16_one_pass(const Dims &d) {
 // group's buffers lie in the workspace; out: results that may not be written yet (see apart_plan), of `chunk` heads.
 // usual, one_pass: what kernels and their shapes are chosen by, the heads of a group and f32_one_pass or bf16_one_pass of the call
 // as it is where its results lie beside its inputs, so that they round alike wherever they lie.
-// keys: the groups of waves of collect_keys' work-groups, or 0 for the backward by rows.
+// keys: the groups of waves of collect_keys' work-groups, or 0 for the backward by rows; by_rows: what the latter would ask of
+// every call.
 struct StripPlan {
   int64_t heads, rows, chunk, usual;
   int one_pass, keys;
+  size_t by_rows;
   size_t out[3];
   size_t terms, strip, strip2, stats, norm, acc_k, acc_v, total;
 };
@@ -1556,7 +1558,8 @@ bool plan_by_keys(const Dims &d, StripPlan &p) {
   k.usual = k.heads;
   place_group(k, d, RSA_BF16, 1, 0);
   const size_t apart = apart_plan(d, RSA_BF16, 1, p, false, 0).total;
-  if (apart_plan(d, RSA_BF16, 1, k, false, 0).total > (apart > p.total ? apart : p.total)) return false;
+  k.by_rows = apart > p.total ? apart : p.total;
+  if (apart_plan(d, RSA_BF16, 1, k, false, 0).total > k.by_rows) return false;
   p = k;
   return true;
 }
@@ -1599,8 +1602,14 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, StripPlan p, bool whole
   else place(1, d.Lq < 128 || p.keys ? d.Lq : 128);
   return p;
 }
+// ... of the call as it is.  By keys the least plan holds all of a head's rows: beside all results, where a workspace that was
+// asked for by rows holds no more than 128 of them, the call goes by rows (as it does where a head's rows are cut, it then rounds
+// otherwise).
 StripPlan apart_plan(const Dims &d, int dtype, int pass, bool whole, size_t bytes) {
-  return apart_plan(d, dtype, pass, strip_plan(d, dtype, pass), whole, bytes);
+  const StripPlan p = apart_plan(d, dtype, pass, strip_plan(d, dtype, pass), whole, bytes);
+  if (!p.keys || !whole || p.total <= bytes) return p;
+  const StripPlan rows = apart_plan(d, dtype, pass, strip_plan_by_rows(d, dtype, pass), whole, bytes);
+  return bytes > 0 || rows.total < p.total ? rows : p;
 }
 
 template <typename T>
@@ -1898,6 +1907,11 @@ size_t strip_workspace_bytes(const Dims &d, int dtype, int pass) {
   if (pl.one_pass) {  // (room for all results, so that O may lie over K or V in any way, but no more than strips would take)
     const size_t results = apart_plan(d, dtype, pass, true, 0).total, strips = strip_plan_by_rows(d, dtype, pass, true).total;
     usual = results < strips ? results : strips;
+  }
+  if (pl.keys) {  // (room for all results where every call was asked for as much by rows)
+    const size_t keys = apart_plan(d, dtype, pass, pl, true, 0).total, least = apart_plan(d, dtype, pass, true, 0).total;
+    const size_t results = keys <= pl.by_rows ? keys : least;
+    if (results <= pl.by_rows && results > usual) usual = results;
   }
   return usual > apart ? usual : apart;
 }

@@ -1,4 +1,7 @@
 """Which kernels a call takes, on the CPU: the cases of the GPU tests of a dispatch reach the forms that they are there for."""
+import ctypes
+import random
+
 import pytest
 
 import launches
@@ -121,6 +124,41 @@ def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
     shape = {1: "4, 1", 2: "2, 2", 4: "2, 4"}[on_a_walk]
     assert set(rest[::2]) == {f"strip_collect_keys_kernel<{str(causal).lower()}, {A // 64}, {shape}>"}
     assert all(n.startswith("strip_apply_keys") for n in rest[1::2])
+
+
+def shifted_backward(rec, d):
+    """Status of a two-pass backward whose dK starts at the 65th row of K, with the workspace that every call is asked for."""
+    at = lambda i: (i + 1) << 40
+    ws = rec.lib.rsa_workspace_bytes(ctypes.byref(d), 1)
+    return rec.lib.rsa_backward(ctypes.byref(d), at(0), at(1), at(2), at(3), at(4), at(5), at(6), at(2) + 64 * d.A * 2, at(7), at(8), ws, None), ws
+
+
+# (accepted with the strips by rows, whose least plan holds 128 rows of a head)
+@pytest.mark.parametrize("heads,L,N,A,causal", [(126, 3200, 10, 64, False), (101, 2496, 3, 128, True)])
+def test_backward_by_keys_where_results_fill_the_workspace(rec, heads, L, N, A, causal):
+    assert shifted_backward(rec, launches.descriptor(1, heads, L, N, A, None, causal, mode=rsa.MODE_STAGED))[0] == 0
+
+
+def test_two_pass_backward_over_its_inputs_needs_no_more_than_by_rows(rec):
+    """Wherever all results and the strips of 128 rows of a head fit what every call is asked for, results may lie over inputs in
+    any way, also by keys, whose strip is a whole head's."""
+    rng = random.Random(5)
+    up = lambda n: (n + 255) // 256 * 256
+    told = 0
+    for _ in range(4000):
+        N = rng.randint(1, 8)
+        c = 64 * rng.randint(1, max(1, 64 // N))
+        rb = rng.randrange(N)
+        re = rng.randint(rb + 1, N) if rng.random() < 0.3 else N
+        d = launches.descriptor(1, rng.randint(1, 200), N * c, N, rng.choice([64, 128]), (rb, re), rng.random() < 0.5, mode=rsa.MODE_STAGED)
+        Lq = (re - rb) * c
+        rows = min(Lq, 128)
+        need = up(d.Z * Lq * d.A * 2) + 2 * up(d.Z * d.L * d.A * 2) + 2 * up(rows * d.L * 2) + (2 * up(d.L * d.A * 4) if rows < Lq else 0)
+        status, ws = shifted_backward(rec, d)
+        if need <= ws:
+            told += 1
+            assert status == 0, (d.Z, d.L, d.N, d.A, rb, re, d.causal)
+    assert told > 1000
 
 
 def tiles(launch):
