@@ -518,9 +518,11 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // 112) and less where they are shorter (512 rows, 1024: 25.6 -> 26.7, 256 rows: 17.3 -> 20.5).  Causal walks end one by one
 // and fill places left over: large ones only for long walks on a full chip (8192 rows, 2048: 306 -> 299, 4096 rows: 160 -> 156;
 // but 1888: 156 -> 166, 2048 rows, 3072: 129 -> 140, 1024 rows, 2048: 50.6 -> 53.6).
-// Rows that are no multiple of 256 leave part of a head's last work-group idle: the rounds of the whole ring count that (4160
-// rows, W = 1815: 290 -> 276, 3366: 510 -> 483; 2496 rows, 1820: 178 -> 169), one rank's share takes large ones only where 128
-// would leave as much (1472 rows of 2944, 2424: 265 -> 250; but 832 of 6656, 1484: 372 -> 439, 2368 of 4736 causal, 3325: 164 -> 186).
+// Rows that are no multiple of 256 leave part of a head's last work-group idle: the rounds count that (whole ring: 4160
+// rows, W = 1815: 290 -> 276, 3366: 510 -> 483; 2496 rows, 1820: 178 -> 169).  One rank's share and projected keys take large ones
+// then only where 128 would leave as much (1472 rows of 2944, 2424: 265 -> 250; 960 rows, 1024 projected keys, 1536: 59.4 -> 58.2, but
+// 1096: 48.5 -> 55.7; 832 of 6656, 1484: 372 -> 439), and not under the causal mask (last 1984 of 3968, 1392: 178 -> 193, 6000:
+// 662 -> 675, first 448 of 1344, 1040: 20 -> 26; from 2040 on, of 4416 rows, 3 % either way).
 // A walk that would be split but has no room for partial results (the two-pass layout, projected keys) goes by the rounds as
 // well, one rank's causal share by 512 large work-groups of its own: such as were to fill the chip times their splits left it half
 // empty (two-pass, us, shape of the split -> this: 1 head of 16384 rows 337 -> 103, causal 341 -> 100; 4 of 8192 171 -> 98; 16 heads of
@@ -530,10 +532,11 @@ void fused_fwd_plan(const Dims &d, bool may_split, bool *big, int *splits) {
   if (d.A == 64) {
     const int s = key_splits_for(d, 256);
     const int64_t heads = (int64_t)d.B * d.Z, wgs = heads * ((d.Lq + 255) / 256), W = heads * ((d.Lq + 127) / 128);
-    bool large = wgs * s >= 512 && (d.Lq % 256 == 0 || (s == 1 && 2 * wgs == W));
-    if (s == 1 ? d.Lq == d.L : !may_split) {
-      if (d.causal) large = d.Lq == d.L ? W >= 2000 && d.L >= 4096 : wgs >= 512 && d.Lq % 256 == 0;
-      else large = W >= 512 && d.L > 512 && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
+    const bool whole = d.Lq == d.L, even = d.Lq % 256 == 0;
+    bool large = even && wgs * s >= 512;
+    if (s == 1 ? whole || !even : !may_split) {
+      if (d.causal) large = whole ? W >= 2000 && d.L >= 4096 : even && wgs >= 512;
+      else large = W >= 512 && d.L > 512 && (whole || 2 * wgs == W) && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
     }
     if (large) {
       *big = true; *splits = may_split ? s : 1;

@@ -108,6 +108,25 @@ def test_walks_without_room_for_a_split_are_not_planned_with_one(rec, heads, L, 
     assert k.grid == (grid, 1, 1)
 
 
+# rows of one rank's share that are no multiple of 256; rows of a work-group
+@pytest.mark.parametrize("heads,L,N,ranks,causal,rows", [
+    (202, 2944, 2, (1, 2), False, 256),    # as many rounds of large work-groups as of two small ones in their place,
+    (260, 1344, 3, (2, 3), False, 128),    # one more
+    (200, 2112, 3, (2, 3), False, 128),
+    (200, 1408, 2, (1, 2), True, 128),
+    (202, 2944, 2, (1, 2), True, 128),
+])
+def test_forward_of_a_ragged_share(rec, heads, L, N, ranks, causal, rows):
+    (k,) = launches.forward(rec, launches.descriptor(1, heads, L, N, 64, ranks, causal))
+    assert k.grid == (heads * -(-(L // N) // rows), 1, 1)
+
+
+@pytest.mark.parametrize("heads,rows,Kp,want", [(192, 960, 1024, 256), (137, 960, 1024, 128), (192, 960, 512, 128), (260, 448, 512, 128)])
+def test_ragged_rows_to_projected_keys(rec, heads, rows, Kp, want):
+    (k,) = rec("linformer_forward", launches.descriptor(1, heads, rows, 1), Kp, "Q", "K", "V", "O", "LSE")
+    assert k.grid == (heads * -(-rows // want), 1, 1)
+
+
 @pytest.mark.parametrize("heads,rows,grid", [(160, 512, 640), (48, 2560, 480)])
 def test_attention_to_many_projected_keys_fills_the_chip(rec, heads, rows, grid):
     (k,) = rec("linformer_forward", launches.descriptor(1, heads, rows, 1), 4096, "Q", "K", "V", "O", "LSE")
