@@ -530,7 +530,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &a, const TileOrder &order
     int64_t blk = row0 + wave * R + qb * 32;  // the block of 32 rows is whole or absent
     here[qb] = blk < a.Lq;
     if (!here[qb]) blk = a.Lq - 32;
-    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + col;
+    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + (here[qb] ? col : 31);  // (one row for all lanes: see the forward)
     qtok[qb] = CAUSAL ? a.map.token_at((int)blk) + col : 0;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk) {

@@ -90,7 +90,10 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
 
   // Q^T operand: lane (col, half) holds Q[row][dk*16 + half*8 .. +8]
   bf16x8 qreg[QB][4 * AH];
-  int64_t qrow[QB];  // the lane's row (of a ragged tail that is not there: some other)
+  // The lane's row.  Of a block that is not there: the last of another, the same for all lanes, since products of equal rows
+  // take less power (32 rows of it instead, us: 1150 heads of 192 rows, 1024 projected keys 100.4 -> 102.7, 1025 of 448 of 896 rows
+  // 142 -> 145).
+  int64_t qrow[QB];
   int qtok[QB];  // its global token index
   bool here[QB];     // (a block of 32 rows is whole or absent)
 #pragma unroll
@@ -98,7 +101,7 @@ __global__ void __launch_bounds__(64 * RW * KS, (R == 32 && NK == 1 && AH == 1) 
     int64_t blk = row0 + wave * R + qb * 32;
     here[qb] = blk < a.Lq;
     if (!here[qb]) blk = a.Lq - 32;
-    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + col;
+    qrow[qb] = (CAUSAL ? a.map.row_at((int)blk) : blk) + (here[qb] ? col : 31);
     qtok[qb] = CAUSAL ? a.map.token_at((int)blk) + col : 0;
 #pragma unroll
     for (int dk = 0; dk < 4 * AH; ++dk)
