@@ -955,7 +955,8 @@ __device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], 
 // With 32 rows to a work-group a wave walks its steps alone (ALONE): K goes from memory to operand registers, V through LDS
 // of the wave's own, and nothing waits for a barrier; the splits, 1.2 us of a step where they came in front of the products, lie
 // beside them.  us: 2 heads of 256 rows 9.9 -> 9.5, 16 of 512 17.2 -> 14.8, causal 10 of 832 26.9 -> 22.0, 12 of 1024 36.1 ->
-// 30.5; but 128 rows, one step a wave, 6.7 -> 6.9.  (Eight such waves: 512 rows 15.3, 256 rows 10.8.)
+// 30.5.  (Eight such waves: 512 rows 15.3, 256 rows 10.8.)  One step a wave has nothing to lie beside: up to 128 rows the waves
+// fill LDS together (64 rows 6.9, 6.5; 128 rows 7.1, 6.7; 192 rows 9.5, 9.7).
 struct PassArgs {
   const float *Q, *K, *V;
   float *O, *LSE;
@@ -965,12 +966,12 @@ struct PassArgs {
   float cl2;
 };
 
-template <int RW, int KS>
-__global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kernel(PassArgs a) {
+template <int RW, int KS, bool ALONE>
+__device__ __forceinline__ void f32_forward_body(const PassArgs &a) {
   typedef TileT<float> TT;
   constexpr int BM = 32 * RW, RT = 32, PL = RT * 128;
-  constexpr bool ALONE = RW == 1;
-  struct Stage { unsigned char V[3 * PL], K[ALONE ? 16 : 3 * PL]; };
+  static_assert(!ALONE || RW == 1, "a lone wave shares its keys with none");
+  struct Stage { unsigned char K[ALONE ? 16 : 3 * PL], V[3 * PL]; };
   constexpr int kBuf = KS * (int)sizeof(Stage), kOut = RW * 8192;
   __shared__ __attribute__((aligned(16))) unsigned char buf[kBuf > kOut ? kBuf : kOut];
   __shared__ float sums[KS == 1 ? 1 : KS][RW][2][64];
@@ -994,8 +995,7 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
   f32x4 key[ALONE ? 2 * kSlices : 1];  // a lone wave's step of K, as it multiplies it
   // (a lone wave past its last step fetches that again: a branch would part the splits from the products)
   auto fetch_k = [&](int t) __attribute__((always_inline)) {
-    if (!ALONE && t >= nt) return;
-    if (t >= nt) t = nt - 1;
+    if (ALONE && t >= nt) t = nt - 1;
     if constexpr (ALONE) {
       const float *p = Kh + ((int64_t)t * RT + col) * 64 + half * (kSliceK / 2);
 #pragma unroll
@@ -1005,11 +1005,14 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
     }
   };
   auto fetch_v = [&](int t) __attribute__((always_inline)) {
-    if (!ALONE && t >= nt) return;
-    if (t >= nt) t = nt - 1;
+    if (ALONE && t >= nt) t = nt - 1;
     v_tile.fetch(Vh + (int64_t)t * (RT * 64));
   };
-  auto fetch = [&](int t) __attribute__((always_inline)) { fetch_k(t); fetch_v(t); };
+  auto fetch = [&](int t) __attribute__((always_inline)) {
+    if (!ALONE && t >= nt) return;
+    fetch_k(t);
+    fetch_v(t);
+  };
   auto put = [&](int t) __attribute__((always_inline)) {
     if (ALONE || t >= nt) return;
     k_tile.put(st.K);
@@ -1153,6 +1156,15 @@ __global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kern
   unsigned char *ot = buf + wave * 8192;  // (free after the last barrier)
   TT::stage(ot, o[0], o[1], 1.0f / l, lane);
   TT::flush(ot, a.O + row * 64, 32, lane, 64);
+}
+template <int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, KS > 1 ? 1 : 3) f32_forward_kernel(PassArgs a) {
+  f32_forward_body<RW, KS, RW == 1>(a);
+}
+// ... of walks of one step a wave
+template <int RW, int KS>
+__global__ void __launch_bounds__(64 * RW * KS, 1) f32_forward_step_kernel(PassArgs a) {
+  f32_forward_body<RW, KS, false>(a);
 }
 
 // --------------------------------------------------------------- collect ----
@@ -1736,7 +1748,8 @@ template <int RW, int KS>
 hipError_t launch_f32_forward(const Dims &d, PassArgs a, hipStream_t st) {
   a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d));
-  hipLaunchKernelGGL((f32_forward_kernel<RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
+  if (RW == 1 && a.L <= 32 * KS) hipLaunchKernelGGL((f32_forward_step_kernel<1, 4>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((f32_forward_kernel<RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
   return hipGetLastError();
 }
 hipError_t f32_forward(const Dims &d, const void *Q, const void *K, const void *V, void *O, float *LSE, int groups,

@@ -24,3 +24,17 @@ def test_groups_of_waves_on_a_walk(dtype, B, Z, L, N, A, rb, re, causal):
     x = inputs.make_inputs(cfg)
     out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED)
     compare_heads(cfg, x, out, sorted({0, B * Z // 2, B * Z - 1}), mode=rsa.MODE_STAGED)
+
+
+# fp32 forward of four groups: as many steps of 32 keys as waves, fewer, more
+STEP_CASES = [((1, 3, 128, 2, 64, 0, 2, False), True), ((1, 3, 128, 2, 64, 1, 2, True), True), ((2, 2, 64, 1, 64, 0, 1, True), True),
+              ((1, 3, 192, 3, 64, 0, 3, True), False)]
+
+
+@pytest.mark.parametrize("case,one_step", STEP_CASES)
+def test_f32_walks_of_one_step(case, one_step):
+    B, Z, L, N, A, rb, re, causal = case
+    cfg = inputs.RSAConfig("s", B=B, Z=Z, L=L, A=A, N=N, dtype="f32", causal=causal, rank_begin=rb, rank_end=re, seed=73)
+    x = inputs.make_inputs(cfg)
+    out = gpu_forward_backward(cfg, x, mode=rsa.MODE_STAGED, backward=False)
+    compare_heads(cfg, x, out, list(range(B * Z)), mode=rsa.MODE_STAGED, backward=False)

@@ -75,6 +75,13 @@ def test_two_pass_groups(rec, case, on_a_walk):
         assert last(fwd, "f32_forward") == ([one_pass] if dtype == rsa.RSA_F32 and one_pass else [])
 
 
+@pytest.mark.parametrize("case,one_step", groups.STEP_CASES)
+def test_two_pass_fp32_walks_of_one_step(rec, case, one_step):
+    B, Z, L, N, A, rb, re, causal = case
+    d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, dtype=rsa.RSA_F32, mode=rsa.MODE_STAGED)
+    assert names(launches.forward(rec, d)) == [("f32_forward_step_kernel" if one_step else "f32_forward_kernel") + "<1, 4>"]
+
+
 @pytest.mark.parametrize("case", params(staged.test_f32_one_pass_on_long_walks, "B,Z,L,N,causal,on_a_walk"))
 def test_two_pass_long_walks_in_one_pass(rec, case):
     B, Z, L, N, causal, on_a_walk = case
