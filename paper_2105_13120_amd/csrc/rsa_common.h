@@ -179,8 +179,7 @@ struct FastDiv {
 };
 inline FastDiv make_fast_div(int64_t d) {  // 1 <= d < 2^31
   FastDiv f;
-  f.d = (uint32_t)d; f.shift = 0;
-  while (((uint64_t)1 << f.shift) < (uint64_t)f.d) ++f.shift;
+  f.d = (uint32_t)d; f.shift = d > 1 ? 32 - __builtin_clz(f.d - 1) : 0;
   f.mul = (uint32_t)((((((uint64_t)1 << f.shift) - f.d)) << 32) / f.d + 1);
   return f;
 }
