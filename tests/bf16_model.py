@@ -18,9 +18,11 @@ its error on the same inputs.  Two details of how P is rounded in the forward:
 The two differ only on rows that one key dominates (a sharp softmax: that key's rounding is
 most of the row's error); the fused forward is an online softmax and is compared with the second.
 
-`strip_bf16_pipeline` is the model of the paper's two-pass layout with the score strip stored
-in bf16: the normalised P is rounded once, when it is written, and both O = P V and
-dS = P o (dP - D) are formed from that rounded P (dS is then rounded again as an operand).
+`strip_bf16_pipeline` is the model of the paper's two-pass layout put together from the step-level
+entry points, whose score strip is stored in bf16: the normalised P is rounded once, when it is
+written, and both O = P V and dS = P o (dP - D) are formed from that rounded P (dS is then rounded
+again as an operand).  The whole two-pass forward and backward form dS while P is in registers and
+are held to the ideal pipeline.
 
 `folded_scale_pipeline` adds the one rounding an earlier version of the backward kernels
 made on top: the factor s log2(e) folded into a bf16 operand (K for dK/dV, Q for dQ).
@@ -113,7 +115,7 @@ def ideal_bf16_pipeline(Q, K, V, dO=None, scale=None, qtok=None, causal=False, r
 
 
 def strip_bf16_pipeline(Q, K, V, dO=None, scale=None, qtok=None, causal=False):
-    """The same for the two-pass layout whose probability strip is stored in bf16."""
+    """The same for the steps of the two-pass layout, whose probability strip is stored in bf16."""
     return _pipeline(Q, K, V, dO, scale, qtok, causal, strip=True)
 
 

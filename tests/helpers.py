@@ -3,7 +3,7 @@ import numpy as np
 import torch
 
 import oracle
-from bf16_model import ideal_bf16_pipeline, strip_bf16_pipeline
+from bf16_model import ideal_bf16_pipeline
 from paper_2105_13120_amd import inputs, rsa
 
 # Tolerances of the comparison with the fp64 oracle.
@@ -146,8 +146,8 @@ def check(name, got, ref, dtype, extra=None, ideal=None, both_rounded=False, str
     to the bf16 bound; ideal: the same tensor from the ideal bf16 pipeline (criterion (3));
     both_rounded: ref is itself a bf16 result of the HIP path (two layouts or ring sizes compared
     with each other), so the difference carries both sides' noise: bounds times sqrt(2).
-    strip: a result of the two-pass layout, whose bf16 probability strip rounds P once more on the
-    way into dS (RMS error of dQ, dK sqrt(1.5) times the ideal pipeline's): criterion (2) times 1.25."""
+    strip: a result whose dS was formed from a P already rounded to bf16, as the step-level entry points
+    do (RMS error of dQ, dK sqrt(1.5) times the ideal pipeline's): criterion (2) times 1.25."""
     assert got.shape == ref.shape, (name, got.shape, ref.shape)
     assert np.isfinite(got).all(), f"{name}: non-finite values"
     diff = np.abs(got - ref)
@@ -258,7 +258,9 @@ def compare_heads(cfg, x, out, heads, backward=True, ideal=True, ideal_heads=16,
     """Full comparison with the oracle on the listed flat head indices.  ideal: also hold the bf16
     outputs to the stated multiples of the error of the CPU model of their pipeline (criterion (3)
     on top), on the first `ideal_heads` of the listed heads: the ideal bf16 pipeline with P relative
-    to a running maximum for the fused kernels, the bf16-strip pipeline for the two-pass layout."""
+    to a running maximum for the fused kernels, to the true one for the two-pass layout, which rounds
+    a tile's probabilities against the tile's own.  (Its dS is formed from the unrounded P, by rows
+    and by keys.)"""
     Qh, Kh, Vh = (heads_view(x[k], heads) for k in ("Q", "K", "V"))
     dOh = heads_view(x["dO"], heads) if backward else None
     O_ref, LSE_ref, dQ_ref, dK_ref, dV_ref, dq_x, dk_x = oracle_on_segments(cfg, Qh, Kh, Vh, dOh)
@@ -267,7 +269,7 @@ def compare_heads(cfg, x, out, heads, backward=True, ideal=True, ideal_heads=16,
     refs = dict(O=O_ref, dQ=dQ_ref, dK=dK_ref, dV=dV_ref)
     errs = {}
     for name in got:
-        errs[name] = check(name, got[name], refs[name], cfg.dtype, strip=mode == rsa.MODE_STAGED,
+        errs[name] = check(name, got[name], refs[name], cfg.dtype,
                            extra=extras.get(name) if cfg.dtype == "bf16" else None)
     lse = download(out["LSE"]).reshape(-1, cfg.Lq)[heads][None]
     err = float(np.abs(lse - LSE_ref).max())
@@ -276,18 +278,15 @@ def compare_heads(cfg, x, out, heads, backward=True, ideal=True, ideal_heads=16,
     if ideal and cfg.dtype == "bf16":
         n = min(ideal_heads, len(heads))
         cut = lambda a: None if a is None else a[:, :n]
-        if mode == rsa.MODE_STAGED:
-            m = strip_bf16_pipeline(cut(Qh), cut(Kh), cut(Vh), cut(dOh), scale=att_scale(cfg),
-                                    qtok=row_tokens(cfg), causal=cfg.causal)
-        else:
-            m = ideal_bf16_pipeline(cut(Qh), cut(Kh), cut(Vh), cut(dOh), scale=att_scale(cfg),
-                                    qtok=row_tokens(cfg), causal=cfg.causal, reference="running_max")
+        m = ideal_bf16_pipeline(cut(Qh), cut(Kh), cut(Vh), cut(dOh), scale=att_scale(cfg),
+                                qtok=row_tokens(cfg), causal=cfg.causal,
+                                reference="true_max" if mode == rsa.MODE_STAGED else "running_max")
         model = dict(O=m[0])
         if backward:
             model.update(dQ=m[2], dK=m[3], dV=m[4])
         for name in got:
             errs[name] = check(name, cut(got[name]), cut(refs[name]), cfg.dtype, ideal=model[name],
-                               extra=cut(extras.get(name)), strip=mode == rsa.MODE_STAGED)
+                               extra=cut(extras.get(name)))
     return errs
 
 

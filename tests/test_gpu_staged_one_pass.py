@@ -85,3 +85,57 @@ def test_forward_in_one_pass_is_as_exact_as_the_strip(case, scores):
         e, e_strip = (float((y.double() - exact).norm() / exact.norm()) for y in (got, other))
         print(f"{name} {scores}: {e:.2e}, strip {e_strip:.2e}")
         assert e <= 1.02 * e_strip + 1e-8, name
+
+
+def inputs_of(case, seed):
+    B, Z, L, N, A, rb, re, causal = case
+    cfg = inputs.RSAConfig("o", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=rb, rank_end=re, seed=seed)
+    x = inputs.make_inputs(cfg)
+    return [upload(x[k], "bf16") for k in ("Q", "K", "V", "dO")], rsa.make_desc(upload(x["K"], "bf16"), N, causal=causal, mode=rsa.MODE_STAGED)
+
+
+@pytest.mark.parametrize("case", [CASES[1][0], CASES[2][0], CASES[9][0]])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+def test_infinities_and_nan_reach_their_own_results_only(case, bad):
+    """One element of V that is infinite or NaN: its column of O, for the rows that see it, is not finite, the rest stays as it
+    was, bit by bit.  A NaN in Q: that row's results are NaN, the rest stays as it was."""
+    (Q, K, V, _), desc = inputs_of(case, 83)
+    causal = case[-1]
+    O, LSE = rsa.forward(desc, Q, K, V)
+    V2 = V.clone()
+    V2[0, 1, 37, 10] = bad
+    O2, LSE2 = rsa.forward(desc, Q, K, V2)
+    first = 37 if causal else 0
+    hit = O2[0, 1, first:, 10].float()
+    assert torch.equal(LSE2, LSE)
+    # (rows before 37 of its tile may meet 0 x infinity, as any product over a masked tile does)
+    assert not hit.isfinite().any() and (hit.isnan().all() if bad != bad else (hit == bad).all())
+    O2[0, 1, :, 10] = O[0, 1, :, 10]
+    assert torch.equal(O2, O)
+    Q2 = Q.clone()
+    Q2[0, 2, 100] = float("nan")
+    O2, LSE2 = rsa.forward(desc, Q2, K, V)
+    assert O2[0, 2, 100].isnan().all() and LSE2[0, 2, 100].isnan()
+    O2[0, 2, 100], LSE2[0, 2, 100] = O[0, 2, 100], LSE[0, 2, 100]
+    assert torch.equal(O2, O) and torch.equal(LSE2, LSE)
+
+
+@pytest.mark.parametrize("case", [CASES[1][0], CASES[2][0], CASES[8][0]])
+@pytest.mark.parametrize("gone", [(0, 64), (64, 192), (0, 32)])
+def test_tiles_whose_scores_are_all_minus_infinity(case, gone):
+    """Keys that no row gives any weight, a whole tile of them first, between others, or half a tile: as if they were not there.
+    RMS error as without them (2.4e-3 of the RMS), LSE to fp32 rounding."""
+    (Q, K, V, _), desc = inputs_of(case, 89)
+    A, causal = case[4], case[-1]
+    Q, K = Q.clone(), K.clone()
+    Q[..., 5] = Q[..., 5].abs() + 0.5
+    K[:, :, gone[0]:gone[1], 5] = -float("inf")
+    O, LSE = rsa.forward(desc, Q, K, V)
+    S = Q.double() @ K.double().mT.contiguous() / A ** 0.5
+    if causal:
+        S.masked_fill_(torch.ones(S.shape[-2:], dtype=torch.bool, device="cuda").triu(1), -float("inf"))
+    seen = slice(gone[1] if causal and gone[0] == 0 else 0, None)          # (rows before see no other key)
+    S, O, LSE = S[:, :, seen], O[:, :, seen], LSE[:, :, seen]
+    ref = torch.softmax(S, -1) @ V.double()
+    assert float((O.double() - ref).norm() / ref.norm()) <= 3e-3
+    assert float((LSE.double() - torch.logsumexp(S, -1)).abs().max()) <= 1e-5

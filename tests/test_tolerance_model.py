@@ -64,8 +64,9 @@ def test_ideal_pipeline_sits_at_a_stated_fraction_of_the_bounds(causal, L, A, qk
 def test_running_max_and_strip_variants_of_the_model(causal):
     """An online softmax rounds P relative to a running maximum (the row's largest probability is
     then rounded like the rest): the same statistics as the two-pass model except on rows one key
-    dominates.  The two-pass layout with a bf16 strip rounds P before dS is formed from it: RMS error
-    of dQ and dK sqrt(1.5) = 1.22 times the ideal's.  Both stay inside criteria (1) and (2)."""
+    dominates.  Steps with a bf16 strip round P before dS is formed from it: RMS error
+    of dQ and dK sqrt(1.5) = 1.22 times the ideal's.  Both stay inside criteria (1) and (2); criterion
+    (3) rejects the second."""
     Q, K, V, dO, refs = case(causal, 768)
     base = pick(ideal_bf16_pipeline(Q, K, V, dO, causal=causal))
     online = pick(ideal_bf16_pipeline(Q, K, V, dO, causal=causal, reference="running_max"))
@@ -81,6 +82,8 @@ def test_running_max_and_strip_variants_of_the_model(causal):
         assert 0.95 <= rmse(online[i], refs[i]) / rmse(base[i], refs[i]) <= (1.2 if causal else 1.08), name
     for i in (1, 2):
         assert 1.15 <= rmse(strip[i], refs[i]) / rmse(base[i], refs[i]) <= 1.3, NAMES[i]
+        with pytest.raises(AssertionError, match="times the ideal"):
+            check(NAMES[i], strip[i], refs[i], "bf16", extra=extra if i == 1 else None, strip=True, ideal=base[i])
 
 
 def test_a_second_rounding_of_a_scaled_operand_is_rejected():
