@@ -22,11 +22,11 @@ namespace rsa {
 struct MatView {
   const uint16_t *p[3];  // plain: p[0]; head-split: tensor cb / (Z * AH) holds column tile cb
   int64_t ld;            // row stride in elements (head-split: the head size A)
+  int64_t rows;          // head-split: rows per (b, z) block (a multiple of 64)
   int Z;                 // head-split: heads per tensor
-  int AH;                // 0: plain row-major; else (B, Z, rows, A) tensors, row index = b * rows + r, with AH column tiles
-                         // per head (A / 64: 1 or 2), head-major order
-  FastDiv by_rows, by_tensor;  // head-split: rows per (b, z) block (a multiple of 64); Z * AH
-  __device__ __forceinline__ int64_t rows() const { return by_rows.d; }
+  int AH;                // head-split: column tiles per head (A / 64: 1 or 2), head-major order
+  int split;             // 0: plain row-major; 1: (B, Z, rows, A) tensors, row index = b * rows + r
+  FastDiv by_rows, by_tensor;  // rows; Z * AH
 };
 
 // A value that is the same in every lane, moved to scalar registers.
@@ -48,12 +48,12 @@ struct ViewWalk {
   // krows: k runs over the row tiles of the view; else over its column tiles
   __device__ __forceinline__ ViewWalk(const MatView &v, bool krows) {
     jump1 = 0; jump2 = 0; jumpA = 0; period = 0x7fffffff; mode = 0; Z = v.Z;
-    if (v.AH == 0) {
+    if (!v.split) {
       ld = v.ld;
       step = krows ? 64 * v.ld : 64;
     } else if (!krows) {  // k runs over heads, then over the tensors of the view
       ld = v.ld;
-      const int64_t head = v.rows() * v.ld;  // elements from one head to the next
+      const int64_t head = v.rows * v.ld;  // elements from one head to the next
       // after the last head of a tensor the pointer has moved Z heads; the next tensor starts over
       jump1 = (v.p[1] - v.p[0]) - (int64_t)v.Z * head;
       jump2 = (v.p[2] - v.p[1]) - (int64_t)v.Z * head;
@@ -65,8 +65,8 @@ struct ViewWalk {
     } else {  // k runs over the rows of a batch element, then over batch elements
       ld = v.ld;
       step = 64 * v.ld;
-      jump1 = (int64_t)(v.Z - 1) * v.rows() * v.ld;
-      period = (int)(v.by_rows.d / 64); mode = 1;
+      jump1 = (int64_t)(v.Z - 1) * v.rows * v.ld;
+      period = (int)(v.rows / 64); mode = 1;
     }
   }
 };
@@ -77,7 +77,7 @@ struct TileCursor {
   // krows: the tile index `fixed` selects columns and k (slab ks) selects rows; else the reverse
   __device__ __forceinline__ TileCursor(const MatView &v, bool krows, int64_t fixed, int64_t ks) {
     cnt = 0; which = 0;
-    if (v.AH == 0) {
+    if (!v.split) {
       ptr = krows ? v.p[0] + ks * 64 * v.ld + fixed * 64 : v.p[0] + fixed * 64 * v.ld + ks * 64;
     } else {
       const uint32_t ct = (uint32_t)(krows ? fixed : ks), rt = (uint32_t)(krows ? ks : fixed);
@@ -87,7 +87,7 @@ struct TileCursor {
       const int ah = v.AH == 2 ? (int)(rem & 1) : 0;
       const uint32_t m0 = rt * 64u, b = v.by_rows(m0), r0 = m0 - b * v.by_rows.d;
       const uint16_t *t = which == 0 ? v.p[0] : (which == 1 ? v.p[1] : v.p[2]);
-      ptr = t + (((int64_t)b * v.Z + z) * v.rows() + r0) * v.ld + ah * 64;
+      ptr = t + (((int64_t)b * v.Z + z) * v.rows + r0) * v.ld + ah * 64;
       cnt = krows ? (int)(r0 / 64) : (v.AH == 1 ? (int)z : ah);
       if (!krows && v.AH == 2) which |= (int)z << 2;
     }
@@ -516,14 +516,14 @@ __global__ void __launch_bounds__(kReduceBlock) ksplit_reduce_kernel(const float
 
 static MatView plain(const void *p, int64_t ld) {
   MatView v{};
-  v.p[0] = static_cast<const uint16_t *>(p); v.ld = ld; v.Z = 1; v.AH = 0;
+  v.p[0] = static_cast<const uint16_t *>(p); v.ld = ld; v.split = 0; v.rows = 64; v.Z = 1; v.AH = 1;
   v.by_rows = make_fast_div(64); v.by_tensor = make_fast_div(1);
   return v;
 }
 static MatView heads(const void *p0, const void *p1, const void *p2, int64_t rows, int Z, int A = 64) {
   MatView v{};
   v.p[0] = static_cast<const uint16_t *>(p0); v.p[1] = static_cast<const uint16_t *>(p1);
-  v.p[2] = static_cast<const uint16_t *>(p2); v.ld = A; v.Z = Z; v.AH = A / 64;
+  v.p[2] = static_cast<const uint16_t *>(p2); v.ld = A; v.rows = rows; v.Z = Z; v.AH = A / 64; v.split = 1;
   v.by_rows = make_fast_div(rows); v.by_tensor = make_fast_div((int64_t)Z * v.AH);
   return v;
 }
@@ -673,7 +673,7 @@ static PairPlan plan_pair(const GemmArgs &g0, const GemmArgs &g1, int max_splits
 }
 
 static bool wide_heads(const GemmArgs &g) {
-  return g.A.AH == 2 || g.B.AH == 2 || (g.out_split && g.out_AH == 2);
+  return (g.A.split && g.A.AH == 2) || (g.B.split && g.B.AH == 2) || (g.out_split && g.out_AH == 2);
 }
 
 // The fields of a product's arguments that its plan decides; returns the work-groups per split.
