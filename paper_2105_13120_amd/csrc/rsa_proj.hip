@@ -128,7 +128,7 @@ struct GemmArgs {
 
 // Divisions by run-time sizes are multiplications by numbers that the host prepares, and a head-split result's are done once
 // per 64 rows: as chains of vector instructions they stood in front of a work-group's first loads (five) and among its
-// stores (sixteen a lane), 3 to 9 % of the Q/K/V map (52224 rows, 1536 -> 3072: 468 -> 459 us; 178112 rows of 448: 314 -> 294;
+// stores (sixteen a lane), 2 to 6 % of the Q/K/V map (52224 rows, 1536 -> 3072: 468 -> 459 us; 178112 rows of 448: 314 -> 294;
 // 4096 rows of 768: 22.9 -> 22.1).
 
 // A_KROWS / B_KROWS: the operand's tiles hold k along their rows (the view is [K][M] or [K][N])
@@ -199,6 +199,10 @@ template <bool A_KROWS, bool B_KROWS, bool OUT_F32, bool WIDE, int T, int KG, bo
 __device__ __forceinline__ void gemm_body(const GemmArgs g, uint32_t bx, uint32_t nx, uint32_t by) {
   constexpr int HT = 2 * T;         // half tiles per slab, and waves per group
   constexpr int BM = 64 * T, BN = 64 * T;
+  // (The last word of A's divisors, asked for with the rest of the view: by a scalar load of its own, in front of a small map's
+  // first tile, it cost 0.15 us.  Y of 384 rows of 4 heads, H = 1792: 4.64 -> 4.45 us, of 192 of 8, 576: 6.09 -> 5.89.  A view of 64
+  // bytes, without the fields that plain ones do not need, did as much for these and made maps of 256 x 256 tiles 0.6 % slower.)
+  if constexpr (!A_KROWS && B_KROWS && T == 1) asm volatile("" : : "s"(g.A.by_tensor.shift));
   auto &lds_ = gemm_lds<KG * T>().template as<KG, T>();  // [group][buffer][A.., B..]
 
   const int tid = threadIdx.x, lane = tid & 63;
