@@ -58,7 +58,8 @@ typedef enum { RSA_F32 = 0, RSA_BF16 = 1 } rsa_dtype;
 
 /* flags: one mode, optionally or-ed with the bits below */
 #define RSA_MODE_FUSED 0u  /* online-softmax kernels, no score strip in HBM   */
-#define RSA_MODE_STAGED 1u /* the paper's two-pass layout: strip S^n in HBM   */
+#define RSA_MODE_STAGED 1u /* two passes, scores between them as a strip in HBM */
+                           /* where that is faster (see rsa_workspace_bytes)    */
 /* Zig-zag chunk ownership (fused mode only; an extension for the causal mask, which
  * the paper leaves open in section 3.1): the sequence is cut into 2N half-chunks of
  * h = c/2 rows and rank n owns half-chunks n and 2N-1-n, so that every rank sees the
@@ -104,10 +105,12 @@ const char *rsa_strerror(int status);
 /* Bytes of device workspace rsa_forward (pass 0) or rsa_backward (pass 1)
  * needs for this descriptor; 0 if the descriptor is invalid.  Staged mode: the score
  * strips of as many ranks and heads together as fit 512 MB (a few heads at a time,
- * 192 MB, or at least one rank's rows, where not all fit); the forward of many rows (heads
+ * 192 MB, or at least one rank's rows, where not all fit).  The forward of many rows (heads
  * of 64, in fp32 also short rows; in bf16 also heads of 128) has no strip, only room for its
- * results, should they have to wait (at most what strips would take).  A caller with less memory calls for
- * fewer ranks at a time and adds up the partial dK, dV. */
+ * results, should they have to wait (at most what strips would take); the bf16 backward of
+ * many keys (heads of 64 and 128) has one strip, dS, instead of two, P and dS, in no more
+ * room.  A caller with less memory calls for fewer ranks at a time and adds up the partial
+ * dK, dV. */
 size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
 
 /*
@@ -122,7 +125,7 @@ size_t rsa_workspace_bytes(const rsa_desc *d, int pass);
  * ws_bytes does not hold them).  In fused mode outputs must not overlap inputs, but for
  * dK and dV, which may lie exactly over K and V, either over either.
  * ws: workspace of at least rsa_workspace_bytes(d, 0) bytes (may be NULL if
- * that is 0).  Staged mode keeps the score strip there; fused mode needs it
+ * that is 0).  Staged mode keeps there what it has of a score strip; fused mode needs it
  * only when the descriptor has so few query rows for its keys (one rank's
  * share of a long sequence) that the pass over the keys is divided among
  * several work-groups per row tile, whose fp32 partial results it holds.

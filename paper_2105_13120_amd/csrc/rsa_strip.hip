@@ -27,9 +27,9 @@
 // Bytes per score: 2 es forward, 5 es backward, by keys 2 es (es: bytes of the dtype); every other operand is read
 // from the caches.  The former version of this path kept S and dP as fp32 strips, softmaxed them in
 // passes of their own and ran every product chunk by chunk: 12 (bf16) / 16 (fp32) bytes forward,
-// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 0.72,
-// the backward bound by its strip's 3.9 to 5.1 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32 matrix instructions 0.49, 55 to 70 % of
-// their rate; now 0.42, the strips' 1.4 GB at 3.3 to 4.2 TB/s).
+// 28 / 40 backward, and 10 N^2 launches (B8 Z16 L2048 N8 bf16, forward and backward: 8.9 ms; now 0.71,
+// forward 0.16, dK and dV 0.36 with one work-group to a CU, dQ 0.18, its strip read at 6 TB/s.  B16 Z12 L512 N4 fp32: 1.99 ms; with fp32
+// matrix instructions 0.49, 55 to 70 % of their rate; now 0.37, the backward's 1.0 GB of strips at 3.4 to 3.6 TB/s).
 //
 // The tile kernels hold bf16 tiles in the layout of the fused kernels; fp32 products run on the bf16 matrix instructions
 // over numbers split in three (TileT<float>).  All products are formed transposed: one lane owns one row of the result.
@@ -1423,12 +1423,15 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Groups of waves on a walk of the fp32 forward in one pass (128 / groups rows per work-group), or 0: the strip, whose
 // scores are shared by work-groups along the keys too, is better where rows are few and walks long.  us, strip -> one pass, by
-// W, the work-groups of 128 rows: 64 (256 rows) 15.4 -> 10.7, 100 (320) 20.6 -> 16.3, 400 (512) 62 -> 53, 512 (512) 75 -> 57, 516
-// (1536) 252 -> 197, causal 288 (1536) 79 -> 76, 96 (768) 31 -> 25; but 48 (2048) 51 -> 61, 192 (2048) 115 -> 121.
-// Short walks: a work-group alone on its CU takes 18, 23.5, 33 us (512 rows) with four, two, one group; a second one on the
-// CU adds 15, 11, 17 us.  So as many groups as leave each work-group a CU; else two where they make one work-group per CU
-// more of both kinds (320 rows, W = 288: two 24.7, one 33.3; but 512 rows: 52, 50), under the causal mask, whose short walks
-// leave room, up to 720 of them (512 rows, W = 320: 39.8, 50.1; W = 400: 50.8 either way; 256 rows, W = 320: 29.9, 28.8).
+// W, the work-groups of 128 rows: 64 (256 rows) 13.6 -> 9.6, 120 (320) 21.2 -> 15.8, 400 (512) 61.7 -> 51.4, 512 (512) 72.8 -> 53.5, 516
+// (1536) 245 -> 193, causal 288 (1536) 75.7 -> 71.8, 96 (768) 30.4 -> 20.4; but 192 (2048) 117.3 -> 117.8, 64 (1024) with
+// one or two groups 30.4 -> 61, 42.
+// Short walks: a work-group alone on its CU takes 14.5, 22.8, 32.6 us (512 rows) with four, two, one group; a second one on the
+// CU adds 13, 11, 18 us.  So as many groups as leave each work-group a CU; else two where they make one work-group per CU
+// more of both kinds (320 rows, W = 288: two 23.7, one 33.6; but 512 rows: 50.2, 50.5), under the causal mask, whose short walks
+// leave room, up to 720 of them (512 rows, W = 320: 38.7, 50.2; W = 400: 49.8, 50.7; 256 rows, W = 320: 29.5, 28.7).
+// (Long walks of four groups with a CU to each work-group would be faster than the strip as well, 8 heads of 768 rows 24.1 -> 19.3,
+// 3 of 2048 47.5 -> 43.4, 8 of 2048 causal 75.6 -> 49.3: only causal ones of up to 1024 rows have a line here.)
 int f32_one_pass(const Dims &d) {
   if (d.A != 64) return 0;
   const int64_t heads = (int64_t)d.B * d.Z, W = heads * ((d.Lq + 127) / 128);
@@ -1445,10 +1448,11 @@ int f32_one_pass(const Dims &d) {
 // The bf16 forward by the kernels that keep no strip (two_pass_forward), for heads of 64 and 128 with more
 // than 64 work-groups of 128 rows (W); the strip, whose scores are shared by work-groups along the keys too, where rows are few.
 // The strip was written and read at 4 to 5 TB/s, the products of one pass are bound by the matrix pipe and the exponentials.
-// us, strip -> one pass: W = 128 (8 heads of 2048 rows) 33 -> 18, 512 (128 of 512) 37 -> 17, 1024 (128 of 1024) 139 -> 46, 2048
-// (128 of 2048) 495 -> 161, causal 384 (12 of 4096) 113 -> 48; heads of 128: 80 (640 rows) 17.2 -> 14.3, causal 14.6 both, 512
-// (512) 40 -> 27; but 64 (2048) 28.6 -> 31.5, 32 (2048) 20 -> 31.  (Heads of 64 gain at fewer W as well, 64 (2048) 22.5 -> 15.3,
-// 32 (1024) 11.9 -> 10.0, where the layout is kept for its own sake.)  L >= A: all results then take no more room than strips.
+// us, strip -> one pass: W = 128 (8 heads of 2048 rows) 33 -> 17, 512 (128 of 512) 37 -> 15.5, 1024 (128 of 1024) 139 -> 45, 2048
+// (128 of 2048) 495 -> 159, causal 384 (12 of 4096) 113 -> 47; heads of 128: 80 (640 rows) 17.2 -> 14.3, causal 14.6 both, 512
+// (512) 40 -> 27; but 64 (2048) 26.9 -> 32.1, 32 (2048) 18.8 -> 31.7.  Heads of 64 lose later, with one or two heads of long rows (1
+// of 1024 10.0 -> 11.1, 1 of 2048 14.7 -> 17.1), and gain at other W below the line (8 of 1024 14.0 -> 11.3, 4 of 2048 21.7 -> 17.2, 16 of
+// 256 8.7 -> 6.8): they have no line of their own.  L >= A: all results then take no more room than strips.
 int bf16_one_pass(const Dims &d) {
   const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
   return d.A <= 128 && d.L >= d.A && W > 64;
