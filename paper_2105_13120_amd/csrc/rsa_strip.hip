@@ -1539,11 +1539,33 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, StripPlan p, bool whole
 
 // The bf16 backward by keys (collect_keys: dK, dV, and dS as the only strip, written once and read once) where its
 // work-groups of 128 keys fill the chip, in no more workspace than the backward by rows takes (P and dS, five passes over a
-// strip).  W: work-groups of a group of heads.  Heads of 64, us, by rows -> by keys: 18 heads of 1024 rows (W = 144) 48 -> 38, 40 of
-// 512 (160) 31.6 -> 25.4, 12 of 2048 causal (192) 70 -> 51, 50 of 576 (250) 39 -> 30, 128 of 512 (512) 69 -> 46, 128 of 2048
-// (256, eight times) 1141 -> 580; but 24 heads of 384 of 1536 rows (168) 20 -> 21, 42 of 320 causal (126) 20.1 -> 20.7, 10 of 1280
-// causal (100) 36 -> 47.  Heads of 128: 30 heads of 896 causal (210) 63 -> 59, 64 of 1024 (512) 189 -> 130; but 30 of 768 causal
-// (180) 51 -> 52.
+// strip).  Wk, Wq: work-groups of 128 keys and of 128 rows (those of dQ) of a group of heads.  The lines are those of 1600 calls,
+// whole rings of 64 .. 2048 rows and shares of 1/2 .. 1/16 of up to 4096: where it is taken it takes 0.76 of the time on average and
+// 1.04 at most.  us, by rows -> by keys, heads of 64: 18 heads of 1024 rows (Wk = 144) 48 -> 38, 40 of 512 (160) 31.6 -> 25.4, 12 of 2048
+// causal (192) 70 -> 51, 50 of 576 (250) 39 -> 30, 128 of 512 (512) 69 -> 46, 128 of 2048 (256, eight times) 1141 -> 545; but 24 heads of
+// 384 of 1536 rows (168) 20 -> 21, 42 of 320 causal (126) 20.1 -> 20.7, 10 of 1280 causal (100) 36 -> 47.  One rank's rows leave dQ few
+// work-groups on long walks: 9 heads of 512 of 2048 rows (Wq = 36) 33.6 -> 37.2, the last causal ones 33.8 -> 41.5, 62 of 64 of 512 16.5 ->
+// 18.1; 16 of 512 of 2048 (64) 40.4 -> 36.4.  Heads of 128 fill a CU with one work-group: a round of 256 that is nearly empty costs as
+// much as a full one (128 of 256, 256, 34.9 -> 30.3, 150 of 256, 300, 43.8 -> 43.7, 30 of 1088, 270, 100 -> 105), and two groups of waves on
+// causal walks pay for long ones alone (41 of 768, 246, 53.2 -> 55.0, 85 of 320, 255, 32.6 -> 37.3; 32 of 1024, 256, 65.4 -> 58.1); 30 heads of
+// 896 causal (210) 63 -> 59, 64 of 1024 (512) 189 -> 130; 62 of 64 of 512 20.7 -> 22.9, 125 of 128 of 1024, last causal, 62.7 -> 68.1.  Strips of
+// all heads that the infinity cache cannot hold (64 M scores of P and dS) cost most: 21 of 1792 (294) 217 -> 160, 22 of 1024 of 4096, last
+// causal, 264 -> 189.  Keys that no row sees are work-groups all the same: not the first of sixteen causal ranks (256, 400 heads of 64 of
+// 1024 rows 25 -> 28, 32 -> 39).
+bool by_keys_pays(const Dims &d, int64_t heads) {
+  const int64_t Wk = heads * ((d.L + 127) / 128), Wq = heads * ((d.Lq + 127) / 128), seen = d.causal ? d.rank_end * d.c : d.L;
+  const bool whole = d.Lq == d.L;
+  if (16 * seen <= d.L) return false;
+  if (d.A == 64) {
+    if (Wk < 240 && (Wk < 128 || d.Lq < 512)) return false;
+    if (Wq < 64 || Wk + Wq < (d.causal ? 260 : 240)) return false;
+    return !d.causal || whole || d.Lq >= 128 || Wk >= 500;
+  }
+  if (Wk < 200) return false;
+  if (d.Lq >= 512 && Wq >= 96 && (int64_t)d.B * d.Z * d.Lq * d.L >= (int64_t)64 << 20) return true;
+  if (!d.causal) return Wq >= 128 && (Wk <= 256 ? d.Lq >= 128 : Wk >= 320 && d.Lq >= 384);
+  return Wk <= 256 ? d.Lq >= 960 && Wq >= 200 : Wk >= 300 && Wq >= 240 && d.Lq >= (whole ? 192 : 384);
+}
 bool plan_by_keys(const Dims &d, StripPlan &p) {
   if (d.A > 128) return false;
   const int64_t heads = (int64_t)d.B * d.Z, blocks = (d.L + 127) / 128;
@@ -1567,7 +1589,7 @@ bool plan_by_keys(const Dims &d, StripPlan &p) {
     }
   }
   const int64_t W = k.heads * blocks;
-  if (d.A == 128 ? W < 200 : W < 240 && (W < 128 || d.Lq < 512)) return false;
+  if (!by_keys_pays(d, k.heads)) return false;
   // groups of waves on the walks of uneven length (causal, heads of 64: 12 heads of 2048, W = 192: one 63, two 56, four 51;
   // 72 of 512, 288: 33.7, 31.2, 40.6; 52 of 1024, 416: 54.8, 53.2; 42 of 1344, 462: 67.4, 67.7; of 128: 21 of 1536, 252: 90, 82.5)
   if (d.causal) k.keys = d.A == 128 ? (W <= 256 ? 2 : 1) : (W <= 200 ? 4 : (W <= 360 ? 2 : 1));

@@ -17,9 +17,9 @@ CASES = [
     (2, 15, 1984, 31, 64, 0, 31, True),   # causal: one group of waves, two, four
     (5, 12, 704, 11, 64, 0, 11, True),
     (3, 4, 1600, 5, 64, 1, 5, True),
-    (2, 60, 256, 4, 64, 1, 2, True),      # one tile of rows
+    (2, 130, 256, 4, 64, 1, 2, True),     # one tile of rows
     (4, 16, 448, 7, 128, 2, 7, False),    # heads of 128,
-    (4, 9, 832, 13, 128, 0, 13, True),    # two groups of waves
+    (4, 7, 1088, 17, 128, 0, 17, True),   # two groups of waves
     (2, 25, 1088, 17, 128, 3, 16, True),
     (3, 13, 2112, 3, 64, 0, 3, False),    # several groups of heads
     (2, 20, 2048, 4, 64, 0, 4, True),

@@ -141,7 +141,7 @@ def test_attention_to_many_projected_keys_fills_the_chip(rec, heads, rows, grid)
 
 
 # groups of waves of the kernel that walks the rows, and groups of heads
-@pytest.mark.parametrize("case,on_a_walk,of_heads", zip(by_keys.CASES, [1, 1, 1, 1, 2, 4, 2, 1, 2, 1, 1, 2, 1], [1] * 10 + [3, 3, 3]))
+@pytest.mark.parametrize("case,on_a_walk,of_heads", zip(by_keys.CASES, [1, 1, 1, 1, 2, 4, 1, 1, 2, 1, 1, 2, 1], [1] * 10 + [3, 3, 3]))
 def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
     B, Z, L, N, A, rb, re, causal = case
     d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, mode=rsa.MODE_STAGED)
@@ -150,6 +150,24 @@ def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
     shape = {1: "4, 1", 2: "2, 2", 4: "2, 4"}[on_a_walk]
     assert set(rest[::2]) == {f"strip_collect_keys_kernel<{str(causal).lower()}, {A // 64}, {shape}>"}
     assert all(n.startswith("strip_apply_keys") for n in rest[1::2])
+
+
+# heads, L, N, A, ranks, causal: on either side of the lines
+@pytest.mark.parametrize("heads,L,N,A,ranks,causal,by_keys", [
+    (9, 2048, 4, 64, (0, 1), False, False), (16, 2048, 4, 64, (0, 1), False, True),      # work-groups that dQ has
+    (9, 2048, 4, 64, (3, 4), True, False), (16, 2048, 4, 64, (3, 4), True, True),
+    (75, 512, 8, 64, (7, 8), True, False), (130, 512, 8, 64, (7, 8), True, True),        # one tile of rows
+    (200, 1024, 16, 64, (0, 1), True, False), (200, 1024, 16, 64, (8, 9), True, True),   # keys that no row sees
+    (256, 64, 1, 128, (0, 1), False, False), (128, 256, 1, 128, (0, 1), False, True),    # heads of 128: rounds of one work-group to a CU
+    (150, 256, 1, 128, (0, 1), False, False), (100, 512, 1, 128, (0, 1), False, True),
+    (85, 320, 1, 128, (0, 1), True, False), (41, 768, 1, 128, (0, 1), True, False), (32, 1024, 1, 128, (0, 1), True, True),
+    (100, 448, 1, 128, (0, 1), True, True), (62, 512, 8, 128, (7, 8), True, False),
+    (125, 1024, 8, 128, (7, 8), True, False), (65, 1024, 2, 128, (1, 2), True, True),
+    (21, 1792, 1, 128, (0, 1), False, True), (12, 3584, 4, 128, (3, 4), True, False), (22, 4096, 4, 128, (3, 4), True, True),
+])
+def test_two_pass_backward_takes_the_faster_way(rec, heads, L, N, A, ranks, causal, by_keys):
+    got = names(launches.backward(rec, launches.descriptor(1, heads, L, N, A, ranks, causal, mode=rsa.MODE_STAGED)))
+    assert any(n.startswith("strip_collect_keys") for n in got) == by_keys
 
 
 def shifted_backward(rec, d):
