@@ -575,12 +575,19 @@ static hipError_t forward_as(const Dims &d, const void *Q, const void *K, const 
   // four waves -> chosen): W = 64: 9.4 -> 7.5; 128 (4096 rows): 49 -> 27; 256 (4096): 49 -> 46; causal 192 (4096): 59 -> 28;
   // 384 (4096): 61 -> 46; 512 (2048): 33 -> 30; 640 (8192): 133 -> 116; heads of 128, W = 256 (4096): 83 -> 72, causal
   // 512 (8192): 180 -> 149, but 400 (512): 18 -> 25.
-  const int64_t W = (usual ? usual : heads) * ((d.Lq + 127) / 128), walk = d.L / 64, L = d.L;
+  // The two-pass layout, whose strip went by what the rows see, takes one rank's causal rows by that where it is short (300 heads,
+  // us: the first 64 of 1024 rows 10.7 -> 6.3, strip 9.0, heads of 128 13.2 -> 7.7, strip 10.4; 128 rows 15.9 -> 7.8, strip 12.6;
+  // from 1000 keys on it would be slower: 38 heads, first 1024 of 4096, 16 -> 18.5).  Rows whose walks are about as long go by
+  // the lines of walks without a mask (heads of 128, last 64 of 1024, 264 heads: 50 -> 37, strip 40; 64 of 1024 behind the first
+  // 512, 420: 36 -> 25, strip 36; third 512 of 2048, 66: 62 -> 50, strip 58).
   const bool c = d.causal;
+  const int64_t W = (usual ? usual : heads) * ((d.Lq + 127) / 128), walk = d.L / 64;
+  const int64_t seen = c && !d.zigzag ? (int64_t)d.rank_end * d.c : d.L, L = OWN && seen <= 512 ? seen : d.L;
+  const bool uneven = c && !(OWN && 2 * d.rank_begin >= d.rank_end);
   hipError_t e;
   if (big) e = launch_fwd<OWN, 64, 1, 2, 4, 1>(d, a, heads, splits, st);
   else if (d.A == 128) {
-    if (splits > 1 || W > (c && L > 512 ? 512 : 256)) e = launch_fwd<OWN, 32, 2, 1, 4, 1>(d, a, heads, splits, st);
+    if (splits > 1 || W > (uneven && L > 512 ? 512 : 256)) e = launch_fwd<OWN, 32, 2, 1, 4, 1>(d, a, heads, splits, st);
     else if (W > 128) e = launch_fwd<OWN, 32, 2, 1, 4, 2>(d, a, heads, 1, st);
     else e = launch_fwd<OWN, 32, 2, 1, 2, 2>(d, a, heads, 1, st);
   } else if (splits > 1) e = launch_fwd<OWN, 32, 1, 1, 4, 1>(d, a, heads, splits, st);

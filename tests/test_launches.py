@@ -116,6 +116,18 @@ def test_walks_without_room_for_a_split_are_not_planned_with_one(rec, heads, L, 
 
 
 # rows of one rank's share that are no multiple of 256; rows of a work-group
+# the shape: waves along the rows, groups of waves on a walk
+@pytest.mark.parametrize("heads,L,N,A,ranks,shape", [
+    (300, 1024, 16, 64, (0, 1), "4, 1"), (300, 1024, 16, 128, (0, 1), "4, 1"), (75, 2048, 4, 64, (0, 1), "4, 1"),  # few keys
+    (18, 8192, 4, 64, (0, 1), "2, 4"), (264, 1024, 16, 128, (0, 1), "4, 1"),
+    (264, 1024, 16, 128, (15, 16), "4, 1"), (420, 1024, 16, 128, (8, 9), "4, 1"), (256, 1024, 16, 128, (15, 16), "4, 2"),  # walks as long
+    (38, 2048, 4, 128, (0, 2), "4, 2"), (33, 1024, 1, 128, (0, 1), "4, 2"),                                               # and others
+])
+def test_two_pass_shapes_go_by_what_the_rows_see(rec, heads, L, N, A, ranks, shape):
+    (k,) = launches.forward(rec, launches.descriptor(1, heads, L, N, A, ranks, True, mode=rsa.MODE_STAGED))
+    assert k.name == f"fused_fwd_kernel<32, true, {A // 64}, 1, {shape}, true>"
+
+
 @pytest.mark.parametrize("heads,L,N,ranks,causal,rows", [
     (202, 2944, 2, (1, 2), False, 256),    # as many rounds of large work-groups as of two small ones in their place,
     (260, 1344, 3, (2, 3), False, 128),    # one more
