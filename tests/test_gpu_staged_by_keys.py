@@ -25,9 +25,11 @@ CASES = [
     (2, 20, 2048, 4, 64, 0, 4, True),
     (1, 22, 3008, 47, 128, 0, 47, False),
 ]
+# near the line, faster by rows: one tile of rows, heads of 128 on short causal walks
+BY_ROWS = [(2, 60, 256, 4, 64, 1, 2, True), (4, 9, 832, 13, 128, 0, 13, True)]
 
 
-@pytest.mark.parametrize("B,Z,L,N,A,rb,re,causal", CASES)
+@pytest.mark.parametrize("B,Z,L,N,A,rb,re,causal", CASES + BY_ROWS)
 def test_backward_by_keys(B, Z, L, N, A, rb, re, causal):
     cfg = inputs.RSAConfig("k", B=B, Z=Z, L=L, A=A, N=N, dtype="bf16", causal=causal, rank_begin=rb, rank_end=re, seed=47)
     x = inputs.make_inputs(cfg)

@@ -115,7 +115,6 @@ def test_walks_without_room_for_a_split_are_not_planned_with_one(rec, heads, L, 
     assert k.grid == (grid, 1, 1)
 
 
-# rows of one rank's share that are no multiple of 256; rows of a work-group
 # the shape: waves along the rows, groups of waves on a walk
 @pytest.mark.parametrize("heads,L,N,A,ranks,shape", [
     (300, 1024, 16, 64, (0, 1), "4, 1"), (300, 1024, 16, 128, (0, 1), "4, 1"), (75, 2048, 4, 64, (0, 1), "4, 1"),  # few keys
@@ -128,6 +127,7 @@ def test_two_pass_shapes_go_by_what_the_rows_see(rec, heads, L, N, A, ranks, sha
     assert k.name == f"fused_fwd_kernel<32, true, {A // 64}, 1, {shape}, true>"
 
 
+# rows of one rank's share that are no multiple of 256; rows of a work-group
 @pytest.mark.parametrize("heads,L,N,ranks,causal,rows", [
     (202, 2944, 2, (1, 2), False, 256),    # as many rounds of large work-groups as of two small ones in their place,
     (260, 1344, 3, (2, 3), False, 128),    # one more
@@ -162,6 +162,13 @@ def test_two_pass_backward_by_keys(rec, case, on_a_walk, of_heads):
     shape = {1: "4, 1", 2: "2, 2", 4: "2, 4"}[on_a_walk]
     assert set(rest[::2]) == {f"strip_collect_keys_kernel<{str(causal).lower()}, {A // 64}, {shape}>"}
     assert all(n.startswith("strip_apply_keys") for n in rest[1::2])
+
+
+@pytest.mark.parametrize("case", by_keys.BY_ROWS)
+def test_two_pass_backward_by_rows_near_the_line(rec, case):
+    B, Z, L, N, A, rb, re, causal = case
+    d = launches.descriptor(B, Z, L, N, A, (rb, re), causal, mode=rsa.MODE_STAGED)
+    assert not any(n.startswith("strip_collect_keys") for n in names(launches.backward(rec, d)))
 
 
 # heads, L, N, A, ranks, causal: on either side of the lines
