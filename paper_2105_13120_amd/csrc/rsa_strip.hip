@@ -956,7 +956,8 @@ __device__ __forceinline__ bool add_groups(unsigned char *lds, f32x16 (&o)[DB], 
 // of the wave's own, and nothing waits for a barrier; the splits, 1.2 us of a step where they came in front of the products, lie
 // beside them.  us: 2 heads of 256 rows 9.9 -> 9.5, 16 of 512 17.2 -> 14.8, causal 10 of 832 26.9 -> 22.0, 12 of 1024 36.1 ->
 // 30.5.  (Eight such waves: 512 rows 15.3, 256 rows 10.8.)  One step a wave has nothing to lie beside: up to 128 rows the waves
-// fill LDS together (64 rows 6.9, 6.5; 128 rows 7.1, 6.7; 192 rows 9.5, 9.7).
+// fill LDS together (64 rows 6.9, 6.5; 128 rows 7.1, 6.7; 192 rows 9.5, 9.7), also where causal rows see no more (94 heads, the first 64
+// of 1024 rows 7.1, 6.7).
 struct PassArgs {
   const float *Q, *K, *V;
   float *O, *LSE;
@@ -1774,7 +1775,8 @@ template <int RW, int KS>
 hipError_t launch_f32_forward(const Dims &d, PassArgs a, hipStream_t st) {
   a.by_tiles = make_fast_div((d.Lq + 32 * RW - 1) / (32 * RW));
   const dim3 grid((unsigned)((int64_t)d.B * d.Z * a.by_tiles.d));
-  if (RW == 1 && a.L <= 32 * KS) hipLaunchKernelGGL((f32_forward_step_kernel<1, 4>), grid, dim3(256), 0, st, a);
+  const int64_t seen = d.causal ? d.rank_end * d.c : d.L;
+  if (RW == 1 && seen <= 32 * KS) hipLaunchKernelGGL((f32_forward_step_kernel<1, 4>), grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL((f32_forward_kernel<RW, KS>), grid, dim3(64 * RW * KS), 0, st, a);
   return hipGetLastError();
 }

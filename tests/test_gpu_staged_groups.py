@@ -28,7 +28,7 @@ def test_groups_of_waves_on_a_walk(dtype, B, Z, L, N, A, rb, re, causal):
 
 # fp32 forward of four groups: as many steps of 32 keys as waves, fewer, more
 STEP_CASES = [((1, 3, 128, 2, 64, 0, 2, False), True), ((1, 3, 128, 2, 64, 1, 2, True), True), ((2, 2, 64, 1, 64, 0, 1, True), True),
-              ((1, 3, 192, 3, 64, 0, 3, True), False)]
+              ((1, 3, 192, 3, 64, 0, 3, True), False), ((1, 3, 512, 4, 64, 0, 1, True), True), ((1, 3, 384, 2, 64, 0, 1, True), False)]
 
 
 @pytest.mark.parametrize("case,one_step", STEP_CASES)
