@@ -1451,12 +1451,24 @@ int f32_one_pass(const Dims &d) {
 // The strip was written and read at 4 to 5 TB/s, the products of one pass are bound by the matrix pipe and the exponentials.
 // us, strip -> one pass: W = 128 (8 heads of 2048 rows) 33 -> 17, 512 (128 of 512) 37 -> 15.5, 1024 (128 of 1024) 139 -> 45, 2048
 // (128 of 2048) 495 -> 159, causal 384 (12 of 4096) 113 -> 47; heads of 128: 80 (640 rows) 17.2 -> 14.3, causal 14.6 both, 512
-// (512) 40 -> 27; but 64 (2048) 26.9 -> 32.1, 32 (2048) 18.8 -> 31.7.  Heads of 64 lose later, with one or two heads of long rows (1
+// (512) 40 -> 27; but 64 (2048) 26.9 -> 32.1, 32 (2048) 18.8 -> 31.7.  Heads of 128 have at most two work-groups to a CU, each as long as
+// the longest walk, where the strip's scores are shared along it: on long walks the line lies at more rows, under the causal mask, whose
+// strip is half as long, at more again.  Over 9300 calls of 65 to 270 work-groups the time by these lines is 0.79 to 0.80 of the strip's on
+// average and more than 1.04 of it in 79, by the 64 work-groups in 1690 (2 heads of 4608 rows 55.6 -> 66.1, causal 5 of 1600 22.9 ->
+// 27.8, 2 of 8192 99 -> 117, 8 of the third 1280 of 5120 46.3 -> 57.5).  Heads of 64 lose later, with one or two heads of long rows (1
 // of 1024 10.0 -> 11.1, 1 of 2048 14.7 -> 17.1), and gain at other W below the line (8 of 1024 14.0 -> 11.3, 4 of 2048 21.7 -> 17.2, 16 of
 // 256 8.7 -> 6.8): they have no line of their own.  L >= A: all results then take no more room than strips.
 int bf16_one_pass(const Dims &d) {
   const int64_t W = (int64_t)d.B * d.Z * ((d.Lq + 127) / 128);
-  return d.A <= 128 && d.L >= d.A && W > 64;
+  if (d.A > 128 || d.L < d.A || W <= 64) return 0;
+  const int64_t walk = (d.causal ? d.rank_end * d.c : d.L) / 64;
+  if (d.A == 64 || walk < 6) return 1;
+  int64_t line = 40 + walk * 5 / 4, most = 110;  // in blocks of 128 rows
+  if (d.causal) {
+    const bool uneven = 2 * d.rank_begin < d.rank_end;  // walks of a few keys beside long ones
+    line = 40 + walk * (uneven ? 3 : 2); most = uneven ? 180 : 130;
+  }
+  return (int64_t)d.B * d.Z * d.Lq > 128 * (line < most ? line : most);
 }
 
 // How the work is cut: `heads` heads and `rows` of their query rows per group of launches, and where a

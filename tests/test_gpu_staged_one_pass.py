@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ((1, 16, 512, 4, 64, 0, 4, False), True),       # 64 work-groups of 128 rows,
     ((1, 13, 576, 9, 64, 0, 9, False), False),      # 65: the last of a head half empty
-    ((1, 13, 576, 9, 128, 0, 9, True), False),
+    ((1, 20, 576, 9, 128, 0, 9, True), False),      # heads of 128, by their rows: 90 blocks of 128,
     ((4, 8, 512, 8, 128, 3, 7, False), True),       # 64 and 96 of one rank's share
     ((4, 8, 512, 8, 128, 2, 8, True), False),
     ((5, 14, 64, 1, 64, 0, 1, False), False),       # one tile of keys; too few keys for the results' room
@@ -25,6 +25,7 @@ CASES = [
     ((1, 17, 16384, 16, 64, 15, 16, True), False),
     ((1, 96, 4096, 8, 128, 7, 8, True), False),
     ((1, 23, 640, 5, 192, 0, 5, False), True),
+    ((1, 13, 576, 9, 128, 0, 9, True), True),       # 58
 ]
 
 

@@ -115,6 +115,19 @@ def test_walks_without_room_for_a_split_are_not_planned_with_one(rec, heads, L, 
     assert k.grid == (grid, 1, 1)
 
 
+# heads of 128: on either side of the lines
+@pytest.mark.parametrize("heads,L,N,ranks,causal,one_pass", [
+    (2, 4608, 1, (0, 1), False, False), (4, 4608, 1, (0, 1), False, True), (16, 640, 1, (0, 1), False, True),
+    (5, 1600, 1, (0, 1), True, False), (10, 1600, 1, (0, 1), True, True),                  # whole causal rings
+    (2, 8192, 1, (0, 1), True, False), (3, 8192, 1, (0, 1), True, True),
+    (8, 5120, 4, (2, 3), True, False), (14, 5120, 4, (2, 3), True, True),                  # walks about as long
+    (66, 8192, 128, (0, 1), True, True), (80, 320, 5, (4, 5), False, True),                # few keys
+])
+def test_two_pass_forward_of_heads_of_128(rec, heads, L, N, ranks, causal, one_pass):
+    got = names(launches.forward(rec, launches.descriptor(1, heads, L, N, 128, ranks, causal, mode=rsa.MODE_STAGED)))
+    assert any(n.startswith("fused_fwd_kernel") for n in got) == one_pass
+
+
 # the shape: waves along the rows, groups of waves on a walk
 @pytest.mark.parametrize("heads,L,N,A,ranks,shape", [
     (300, 1024, 16, 64, (0, 1), "4, 1"), (300, 1024, 16, 128, (0, 1), "4, 1"), (75, 2048, 4, 64, (0, 1), "4, 1"),  # few keys
