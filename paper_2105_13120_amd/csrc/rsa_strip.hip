@@ -1564,10 +1564,13 @@ StripPlan apart_plan(const Dims &d, int dtype, int pass, StripPlan p, bool whole
 // 896 causal (210) 63 -> 59, 64 of 1024 (512) 189 -> 130; 62 of 64 of 512 20.7 -> 22.9, 125 of 128 of 1024, last causal, 62.7 -> 68.1.  Strips of
 // all heads that the infinity cache cannot hold (64 M scores of P and dS) cost most: 21 of 1792 (294) 217 -> 160, 22 of 1024 of 4096, last
 // causal, 264 -> 189.  Keys that no row sees are work-groups all the same: not the first of sixteen causal ranks (256, 400 heads of 64 of
-// 1024 rows 25 -> 28, 32 -> 39).
+// 1024 rows 25 -> 28, 32 -> 39); heads of 128, which lose more where fewer work-groups than CUs have rows, by 240 of all heads that see any
+// (5 heads of 128, the first 2816 of 7040 rows, 110: 101 -> 142, 9 of 1984 of 3968, 139: 80 -> 106; 4700 such calls: 181 took more than 1.04
+// of the time by rows, now 40) and, of smaller strips, from a third of the keys on (109 heads, the first 384 of 3072 rows, 79 -> 119, 121 of
+// 448 of 2240 85 -> 112).
 bool by_keys_pays(const Dims &d, int64_t heads) {
   const int64_t Wk = heads * ((d.L + 127) / 128), Wq = heads * ((d.Lq + 127) / 128), seen = d.causal ? d.rank_end * d.c : d.L;
-  const bool whole = d.Lq == d.L;
+  const bool whole = d.Lq == d.L, part = d.causal && !whole;
   if (16 * seen <= d.L) return false;
   if (d.A == 64) {
     if (Wk < 240 && (Wk < 128 || d.Lq < 512)) return false;
@@ -1575,7 +1578,8 @@ bool by_keys_pays(const Dims &d, int64_t heads) {
     return !d.causal || whole || d.Lq >= 128 || Wk >= 500;
   }
   if (Wk < 200) return false;
-  if (d.Lq >= 512 && Wq >= 96 && (int64_t)d.B * d.Z * d.Lq * d.L >= (int64_t)64 << 20) return true;
+  if (d.Lq >= 512 && Wq >= 96 && (int64_t)d.B * d.Z * d.Lq * d.L >= (int64_t)64 << 20) return !part || (int64_t)d.B * d.Z * seen >= 240 * 128;
+  if (part && 20 * seen < 7 * d.L) return false;
   if (!d.causal) return Wq >= 128 && (Wk <= 256 ? d.Lq >= 128 : Wk >= 320 && d.Lq >= 384);
   return Wk <= 256 ? d.Lq >= 960 && Wq >= 200 : Wk >= 300 && Wq >= 240 && d.Lq >= (whole ? 192 : 384);
 }

@@ -195,6 +195,8 @@ def test_two_pass_backward_by_rows_near_the_line(rec, case):
     (85, 320, 1, 128, (0, 1), True, False), (41, 768, 1, 128, (0, 1), True, False), (32, 1024, 1, 128, (0, 1), True, True),
     (100, 448, 1, 128, (0, 1), True, True), (62, 512, 8, 128, (7, 8), True, False),
     (125, 1024, 8, 128, (7, 8), True, False), (65, 1024, 2, 128, (1, 2), True, True),
+    (9, 3968, 2, 128, (0, 1), True, False), (16, 3968, 2, 128, (0, 1), True, True),      # ... that see some rows
+    (121, 2240, 5, 128, (0, 1), True, False), (121, 2240, 5, 128, (1, 2), True, True),
     (21, 1792, 1, 128, (0, 1), False, True), (12, 3584, 4, 128, (3, 4), True, False), (22, 4096, 4, 128, (3, 4), True, True),
 ])
 def test_two_pass_backward_takes_the_faster_way(rec, heads, L, N, A, ranks, causal, by_keys):
