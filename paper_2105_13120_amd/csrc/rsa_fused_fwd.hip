@@ -526,7 +526,9 @@ int fused_key_splits(const Dims &d) { return key_splits_for(d, 128); }
 // rows, W = 1815: 290 -> 276, 3366: 510 -> 483; 2496 rows, 1820: 178 -> 169).  One rank's share and projected keys take large ones
 // then only where 128 would leave as much (1472 rows of 2944, 2424: 265 -> 250; 960 rows, 1024 projected keys, 1536: 59.4 -> 58.2, but
 // 1096: 48.5 -> 55.7; 832 of 6656, 1484: 372 -> 439), and not under the causal mask (last 1984 of 3968, 1392: 178 -> 193, 6000:
-// 662 -> 675, first 448 of 1344, 1040: 20 -> 26; from 2040 on, of 4416 rows, 3 % either way).
+// 662 -> 675, first 448 of 1344, 1040: 20 -> 26; from 2040 on, of 4416 rows, 3 % either way).  One full round of either kind is shorter
+// with the small ones (W = 512: 256 heads of 192 of 1536 rows 32.6 -> 34.3, 128 of 448 rows, 1024 projected keys, 23.7 -> 24.8, 64 whole
+// rings of 960 21.9 -> 22.9, 32 of 1984 41.0 -> 42.0).
 // A walk that would be split but has no room for partial results (the two-pass layout, projected keys) goes by the rounds as
 // well, one rank's causal share by 512 large work-groups of its own: such as were to fill the chip times their splits left it half
 // empty (two-pass, us, shape of the split -> this: 1 head of 16384 rows 337 -> 103, causal 341 -> 100; 4 of 8192 171 -> 98; 16 heads of
@@ -540,7 +542,7 @@ void fused_fwd_plan(const Dims &d, bool may_split, bool *big, int *splits) {
     bool large = even && wgs * s >= 512;
     if (s == 1 ? whole || !even : !may_split) {
       if (d.causal) large = whole ? W >= 2000 && d.L >= 4096 : even && wgs >= 512;
-      else large = W >= 512 && d.L > 512 && (whole || 2 * wgs == W) && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
+      else large = (even ? W >= 512 : W > 512) && d.L > 512 && (whole || 2 * wgs == W) && (double)((wgs + 255) / 256) * 2 < (double)((W + 255) / 256) * 1.055;
     }
     if (large) {
       *big = true; *splits = may_split ? s : 1;

@@ -153,7 +153,7 @@ def test_forward_of_a_ragged_share(rec, heads, L, N, ranks, causal, rows):
     assert k.grid == (heads * -(-(L // N) // rows), 1, 1)
 
 
-@pytest.mark.parametrize("heads,rows,Kp,want", [(192, 960, 1024, 256), (137, 960, 1024, 128), (192, 960, 512, 128), (260, 448, 512, 128)])
+@pytest.mark.parametrize("heads,rows,Kp,want", [(192, 960, 1024, 256), (64, 960, 1024, 128), (128, 448, 2048, 128), (137, 960, 1024, 128), (192, 960, 512, 128), (260, 448, 512, 128)])
 def test_ragged_rows_to_projected_keys(rec, heads, rows, Kp, want):
     (k,) = rec("linformer_forward", launches.descriptor(1, heads, rows, 1), Kp, "Q", "K", "V", "O", "LSE")
     assert k.grid == (heads * -(-rows // want), 1, 1)
